@@ -3,7 +3,8 @@
 The three operations keep their C names (``salr_encode_bitmap``, ``salr_decode``,
 ``salr_sparse_lowrank_linear``); this module only marshals arguments: torch CUDA tensors supply
 device memory and the current stream, every step of the computation runs in the HIP kernels of
-``libsalr_hip.so``.  There is no CPU or PyTorch fallback: a missing library is an ImportError.
+``libsalr_hip.so``.  There is no CPU or PyTorch fallback: a missing library is an ImportError.  The layer's entry points
+are marshalled in native code (``csrc/salr_binding.cpp``), the others through ctypes.
 
 bf16 tensors may be given as ``torch.bfloat16`` or as their raw patterns (``torch.int16`` /
 ``torch.uint16``); bitmap and row offsets are ``torch.int32`` / ``torch.uint32``.
@@ -22,6 +23,7 @@ LIB_PATH = os.path.join(_HERE, "libsalr_hip.so")
 SALR_OK, SALR_ERR_INVALID_ARG, SALR_ERR_SHAPE, SALR_ERR_CAPACITY, SALR_ERR_UNSUPPORTED, SALR_ERR_HIP = range(6)
 
 _lib = None
+_binding = None
 _vp = ctypes.c_void_p
 _i64 = ctypes.c_int64
 
@@ -104,6 +106,17 @@ def lib() -> ctypes.CDLL:
     return _lib
 
 
+def _native():
+    """The native half of this binding (built beside the library); its calls raise this module's SalrError."""
+    global _binding
+    if _binding is None:
+        lib()
+        from . import _salr_binding
+        _salr_binding.set_error(SalrError)
+        _binding = _salr_binding
+    return _binding
+
+
 _BF16_TYPES = (torch.bfloat16, torch.int16, torch.uint16)
 _U32_TYPES = (torch.int32, torch.uint32)
 
@@ -123,6 +136,11 @@ def _ptr(t: Optional[torch.Tensor], kinds, name: str) -> Optional[int]:
 def _stream(stream) -> Optional[int]:
     s = torch.cuda.current_stream() if stream is None else stream
     return s.cuda_stream or None
+
+
+def _handle(stream) -> Optional[int]:
+    """A stream argument for the native calls: None = the current stream, else the stream's handle."""
+    return None if stream is None else stream.cuda_stream
 
 
 def _check(status: int, where: str) -> None:
@@ -186,21 +204,7 @@ def salr_sparse_lowrank_linear(x: torch.Tensor, bitmap: torch.Tensor, values: to
                                b_cat: Optional[torch.Tensor], y: torch.Tensor,
                                workspace: Optional[torch.Tensor], stream=None) -> None:
     """Enqueue Y = X What^T + (X A_cat) B_cat.  Shapes: x [M,K], bitmap [N,K/32], a_cat [K,R], b_cat [R,N], y [M,N]."""
-    M, K = x.shape
-    N = y.shape[1]
-    R = 0 if a_cat is None else a_cat.shape[1]
-    if y.shape[0] != M or bitmap.shape[0] != N or row_offsets.numel() != N + 1:
-        raise ValueError("inconsistent shapes")
-    if R and (tuple(a_cat.shape) != (K, R) or tuple(b_cat.shape) != (R, N)):
-        raise ValueError("adapter shapes")
-    ws_ptr = None if workspace is None else workspace.data_ptr()
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    st = lib().salr_sparse_lowrank_linear(_ptr(x, _BF16_TYPES, "x"), M, K, N, _ptr(bitmap, _U32_TYPES, "bitmap"),
-                                          _ptr(values, _BF16_TYPES, "values"),
-                                          _ptr(row_offsets, _U32_TYPES, "row_offsets"),
-                                          _ptr(a_cat, _BF16_TYPES, "a_cat"), _ptr(b_cat, _BF16_TYPES, "b_cat"), R,
-                                          _ptr(y, _BF16_TYPES, "y"), ws_ptr, ws_bytes, _stream(stream))
-    _check(st, "salr_sparse_lowrank_linear")
+    _native().linear(0, x, bitmap, values, row_offsets, None, a_cat, b_cat, y, workspace, _handle(stream))
 
 
 def salr_slice_table_bytes(N: int, K: int) -> int:
@@ -222,21 +226,7 @@ def salr_sparse_lowrank_linear_prepared(x: torch.Tensor, bitmap: torch.Tensor, v
                                         a_cat: Optional[torch.Tensor], b_cat: Optional[torch.Tensor], y: torch.Tensor,
                                         workspace: Optional[torch.Tensor], stream=None) -> None:
     """salr_sparse_lowrank_linear with the layer's slice table as one more input."""
-    M, K = x.shape
-    N = y.shape[1]
-    R = 0 if a_cat is None else a_cat.shape[1]
-    if y.shape[0] != M or bitmap.shape[0] != N or row_offsets.numel() != N + 1 or slice_table.numel() != N * 16:
-        raise ValueError("inconsistent shapes")
-    if R and (tuple(a_cat.shape) != (K, R) or tuple(b_cat.shape) != (R, N)):
-        raise ValueError("adapter shapes")
-    ws_ptr = None if workspace is None else workspace.data_ptr()
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    st = lib().salr_sparse_lowrank_linear_prepared(
-        _ptr(x, _BF16_TYPES, "x"), M, K, N, _ptr(bitmap, _U32_TYPES, "bitmap"), _ptr(values, _BF16_TYPES, "values"),
-        _ptr(row_offsets, _U32_TYPES, "row_offsets"), _ptr(slice_table, _U32_TYPES, "slice_table"),
-        _ptr(a_cat, _BF16_TYPES, "a_cat"), _ptr(b_cat, _BF16_TYPES, "b_cat"), R, _ptr(y, _BF16_TYPES, "y"), ws_ptr, ws_bytes,
-        _stream(stream))
-    _check(st, "salr_sparse_lowrank_linear_prepared")
+    _native().linear(1, x, bitmap, values, row_offsets, slice_table, a_cat, b_cat, y, workspace, _handle(stream))
 
 
 def salr_nf4_quantize_values(values: torch.Tensor, codes: torch.Tensor, scales: torch.Tensor, stream=None) -> None:
@@ -266,21 +256,7 @@ def salr_qsalr_linear(x: torch.Tensor, bitmap: torch.Tensor, codes: torch.Tensor
                       row_offsets: torch.Tensor, nnz: int, a_cat: Optional[torch.Tensor], b_cat: Optional[torch.Tensor],
                       y: torch.Tensor, workspace: Optional[torch.Tensor], stream=None) -> None:
     """Enqueue Y = X decode(bitmap, dequantised codes)^T + (X A_cat) B_cat."""
-    M, K = x.shape
-    N = y.shape[1]
-    R = 0 if a_cat is None else a_cat.shape[1]
-    if y.shape[0] != M or bitmap.shape[0] != N or row_offsets.numel() != N + 1:
-        raise ValueError("inconsistent shapes")
-    if R and (tuple(a_cat.shape) != (K, R) or tuple(b_cat.shape) != (R, N)):
-        raise ValueError("adapter shapes")
-    ws_ptr = None if workspace is None else workspace.data_ptr()
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    st = lib().salr_qsalr_linear(_ptr(x, _BF16_TYPES, "x"), M, K, N, _ptr(bitmap, _U32_TYPES, "bitmap"),
-                                 _ptr(codes, (torch.uint8,), "codes"), _ptr(scales, _BF16_TYPES, "scales"),
-                                 _ptr(row_offsets, _U32_TYPES, "row_offsets"), nnz, _ptr(a_cat, _BF16_TYPES, "a_cat"),
-                                 _ptr(b_cat, _BF16_TYPES, "b_cat"), R, _ptr(y, _BF16_TYPES, "y"), ws_ptr, ws_bytes,
-                                 _stream(stream))
-    _check(st, "salr_qsalr_linear")
+    _native().qsalr_linear(x, bitmap, codes, scales, row_offsets, nnz, a_cat, b_cat, y, workspace, _handle(stream))
 
 
 def codes_alloc(count: int, device) -> torch.Tensor:
@@ -305,13 +281,7 @@ def nf4_dequantize(codes: torch.Tensor, scales: torch.Tensor, count: int) -> tor
 
 
 def qsalr_linear(x, bitmap, codes, scales, row_offsets, nnz, a_cat, b_cat) -> torch.Tensor:
-    M, K = x.shape
-    N = bitmap.shape[0]
-    R = 0 if a_cat is None else a_cat.shape[1]
-    y = torch.empty((M, N), dtype=x.dtype, device=x.device)
-    ws = torch.empty(max(salr_qsalr_linear_workspace_bytes(M, K, N, R, nnz), 256), dtype=torch.uint8, device=x.device)
-    salr_qsalr_linear(x, bitmap, codes, scales, row_offsets, nnz, a_cat, b_cat, y, ws)
-    return y
+    return _native().qsalr_linear(x, bitmap, codes, scales, row_offsets, nnz, a_cat, b_cat, None, None, None)
 
 
 NOALLOC_SCRATCH_BYTES = 16 * 1024 * 1024   # SALR_NOALLOC_SCRATCH_BYTES of include/salr.h
@@ -353,21 +323,7 @@ def salr_sparse_lowrank_linear_2of4(x: torch.Tensor, bitmap: torch.Tensor, value
                                     b_cat: Optional[torch.Tensor], y: torch.Tensor,
                                     workspace: Optional[torch.Tensor], stream=None) -> None:
     """Enqueue Y = X What^T + (X A_cat) B_cat for a weight that passes salr_bitmap_is_2of4 (not checked here)."""
-    M, K = x.shape
-    N = y.shape[1]
-    R = 0 if a_cat is None else a_cat.shape[1]
-    if y.shape[0] != M or bitmap.shape[0] != N or row_offsets.numel() != N + 1:
-        raise ValueError("inconsistent shapes")
-    if R and (tuple(a_cat.shape) != (K, R) or tuple(b_cat.shape) != (R, N)):
-        raise ValueError("adapter shapes")
-    ws_ptr = None if workspace is None else workspace.data_ptr()
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    st = lib().salr_sparse_lowrank_linear_2of4(_ptr(x, _BF16_TYPES, "x"), M, K, N, _ptr(bitmap, _U32_TYPES, "bitmap"),
-                                               _ptr(values, _BF16_TYPES, "values"),
-                                               _ptr(row_offsets, _U32_TYPES, "row_offsets"),
-                                               _ptr(a_cat, _BF16_TYPES, "a_cat"), _ptr(b_cat, _BF16_TYPES, "b_cat"), R,
-                                               _ptr(y, _BF16_TYPES, "y"), ws_ptr, ws_bytes, _stream(stream))
-    _check(st, "salr_sparse_lowrank_linear_2of4")
+    _native().linear(2, x, bitmap, values, row_offsets, None, a_cat, b_cat, y, workspace, _handle(stream))
 
 
 def salr_linear_backward_workspace_bytes(M: int, K: int, N: int, R: int, want_dx: bool, want_dadb: bool) -> int:
@@ -402,17 +358,7 @@ def salr_sparse_lowrank_linear_backward(x: Optional[torch.Tensor], dy: torch.Ten
 
 def linear_backward(x, dy, bitmap, values, row_offsets, a_cat, b_cat, need_dx=True, need_dadb=True):
     """(dx, da, db); entries not asked for (or without adapters) are None."""
-    M, N = dy.shape
-    K = bitmap.shape[1] * 32
-    R = 0 if a_cat is None else a_cat.shape[1]
-    dev = dy.device
-    dx = torch.empty((M, K), dtype=dy.dtype, device=dev) if need_dx else None
-    da = torch.empty((K, R), dtype=dy.dtype, device=dev) if need_dadb and R else None
-    db = torch.empty((R, N), dtype=dy.dtype, device=dev) if need_dadb and R else None
-    need = salr_linear_backward_workspace_bytes(M, K, N, R, need_dx, need_dadb and R > 0)
-    ws = torch.empty(max(need, 256), dtype=torch.uint8, device=dev)
-    salr_sparse_lowrank_linear_backward(x, dy, bitmap, values, row_offsets, a_cat, b_cat, dx, da, db, ws)
-    return dx, da, db
+    return _native().linear_backward(x, dy, bitmap, values, row_offsets, a_cat, b_cat, need_dx, need_dadb)
 
 
 class PreparedLinear:
@@ -611,15 +557,7 @@ def bitmap_is_2of4(bitmap: torch.Tensor) -> bool:
 
 
 def linear_2of4(x, bitmap, values, row_offsets, a_cat, b_cat, workspace: Optional[torch.Tensor] = None) -> torch.Tensor:
-    M, K = x.shape
-    N = bitmap.shape[0]
-    R = 0 if a_cat is None else a_cat.shape[1]
-    y = torch.empty((M, N), dtype=x.dtype, device=x.device)
-    need = salr_linear_2of4_workspace_bytes(M, K, N, R)
-    if workspace is None and need:
-        workspace = torch.empty(need, dtype=torch.uint8, device=x.device)
-    salr_sparse_lowrank_linear_2of4(x, bitmap, values, row_offsets, a_cat, b_cat, y, workspace)
-    return y
+    return _native().linear(2, x, bitmap, values, row_offsets, None, a_cat, b_cat, None, workspace, None)
 
 
 def build_slice_table(bitmap, row_offsets, K: int) -> torch.Tensor:
@@ -631,24 +569,8 @@ def build_slice_table(bitmap, row_offsets, K: int) -> torch.Tensor:
 
 def linear_prepared(x, bitmap, values, row_offsets, slice_table, a_cat, b_cat,
                     workspace: Optional[torch.Tensor] = None) -> torch.Tensor:
-    M, K = x.shape
-    N = bitmap.shape[0]
-    R = 0 if a_cat is None else a_cat.shape[1]
-    y = torch.empty((M, N), dtype=x.dtype, device=x.device)
-    need = salr_linear_workspace_bytes(M, K, N, R)
-    if workspace is None and need:
-        workspace = torch.empty(need, dtype=torch.uint8, device=x.device)
-    salr_sparse_lowrank_linear_prepared(x, bitmap, values, row_offsets, slice_table, a_cat, b_cat, y, workspace)
-    return y
+    return _native().linear(1, x, bitmap, values, row_offsets, slice_table, a_cat, b_cat, None, workspace, None)
 
 
 def linear(x, bitmap, values, row_offsets, a_cat, b_cat, workspace: Optional[torch.Tensor] = None) -> torch.Tensor:
-    M, K = x.shape
-    N = bitmap.shape[0]
-    R = 0 if a_cat is None else a_cat.shape[1]
-    y = torch.empty((M, N), dtype=x.dtype, device=x.device)
-    need = salr_linear_workspace_bytes(M, K, N, R)
-    if workspace is None and need:
-        workspace = torch.empty(need, dtype=torch.uint8, device=x.device)
-    salr_sparse_lowrank_linear(x, bitmap, values, row_offsets, a_cat, b_cat, y, workspace)
-    return y
+    return _native().linear(0, x, bitmap, values, row_offsets, None, a_cat, b_cat, None, workspace, None)

@@ -1,13 +1,16 @@
 """Compile the HIP library for gfx950 into paper_2601_16991_amd/libsalr_hip.so (in-tree).
 
 Every source is compiled to an object of its own (in parallel), then linked; `python build.py --changed` skips
-objects that are newer than their source and every header (for quick rebuilds while working on one kernel)."""
+objects that are newer than their source and every header (for quick rebuilds while working on one kernel).  The native
+half of the Python binding (csrc/salr_binding.cpp, host code against torch's headers) becomes _salr_binding.so beside
+the library and links to it."""
 from __future__ import annotations
 
 import glob
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -15,6 +18,8 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OBJ_DIR = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libsalr_hip.so")
+BINDING_SRC = os.path.join(CSRC, "salr_binding.cpp")
+BINDING = os.path.join(HERE, "_salr_binding.so")
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950",
@@ -43,8 +48,23 @@ def _run(cmd: list[str]) -> str:
     proc = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     out = "\n".join(l for l in proc.stdout.splitlines() if "packed-fp32-ops" not in l)
     if proc.returncode != 0:
-        raise RuntimeError("hipcc failed: " + " ".join(cmd) + "\n" + out)
+        raise RuntimeError("build failed: " + " ".join(cmd) + "\n" + out)
     return out
+
+
+def _binding_commands() -> list[list[str]]:
+    """Compile and link lines of the binding (host code only)."""
+    from torch.utils import cpp_extension as ext
+    import torch
+    obj = os.path.join(OBJ_DIR, "salr_binding.o")
+    includes = ext.include_paths("cuda") + [sysconfig.get_paths()["include"], os.path.join(ROOT, "include")]
+    cxx = os.environ.get("CXX", "g++")
+    compile_ = [cxx, "-O2", "-std=c++17", "-fPIC", "-fvisibility=hidden", "-Wno-attributes", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+                f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+                *[f for i in includes for f in ("-isystem" if "dist-packages" in i or "rocm" in i else "-I", i)], "-c", "-o", obj, BINDING_SRC]
+    link = [cxx, "-shared", "-o", BINDING, obj, *["-L" + p for p in ext.library_paths("cuda")[:1]], "-L" + HERE, "-lsalr_hip", "-lc10",
+            "-lc10_hip", "-ltorch_cpu", "-ltorch_hip", "-ltorch_python", "-Wl,-rpath,$ORIGIN"]
+    return [compile_, link]
 
 
 def build(verbose: bool = False, only_changed: bool = False, jobs: int | None = None) -> str:
@@ -58,6 +78,11 @@ def build(verbose: bool = False, only_changed: bool = False, jobs: int | None = 
         fresh = os.path.exists(obj) and os.path.getmtime(obj) > max(os.path.getmtime(src), newest_header)
         if not (only_changed and fresh):
             todo.append([hipcc, *HIPCC_FLAGS, "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-c", "-o", obj, src])
+    compile_binding, link_binding = _binding_commands()
+    obj = os.path.join(OBJ_DIR, "salr_binding.o")
+    header = os.path.join(ROOT, "include", "salr.h")
+    if not (only_changed and os.path.exists(obj) and os.path.getmtime(obj) > max(os.path.getmtime(BINDING_SRC), os.path.getmtime(header))):
+        todo.insert(0, compile_binding)   # the longest one first
     if jobs is None:
         jobs = min(8, max(1, len(os.sched_getaffinity(0))))
     if verbose:
@@ -66,9 +91,10 @@ def build(verbose: bool = False, only_changed: bool = False, jobs: int | None = 
     with ThreadPoolExecutor(max_workers=jobs) as pool:
         outs = list(pool.map(_run, todo))
     link = [hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objects]
-    if verbose:
-        print(" ".join(link), flush=True)
-    outs.append(_run(link))
+    for cmd in (link, link_binding):
+        if verbose:
+            print(" ".join(cmd), flush=True)
+        outs.append(_run(cmd))
     text = "\n".join(o for o in outs if o.strip())
     if verbose and text:
         print(text)
