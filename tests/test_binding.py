@@ -13,7 +13,7 @@ import torch
                                                           None), ValueError),                                    # adapter shapes
     (lambda s, x, bm, v, ro: s.linear_prepared(x, bm, v, ro, None, None, None), (TypeError, ValueError)),
     (lambda s, x, bm, v, ro: s.salr_qsalr_linear(x, bm, v, v, ro[:1], 8, None, None, x[:, :3].clone(), None), ValueError),
-    (lambda s, x, bm, v, ro: s.linear_backward(x[:, :8].clone(), x[:, :3].clone(), bm, v, ro, None, None), ValueError),
+    (lambda s, x, bm, v, ro: s.linear_backward(x[:, :8].clone(), x[:, :3].clone(), bm, v, ro, None, None), (TypeError, ValueError)),
 ])
 def test_bad_arguments(call, error):
     import paper_2601_16991_amd as salr
