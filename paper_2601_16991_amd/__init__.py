@@ -435,15 +435,11 @@ def values_alloc(nnz: int, device) -> torch.Tensor:
 
 
 def mask_rows(w: torch.Tensor, keep: int) -> torch.Tensor:
-    w_hat = torch.empty_like(w)
-    salr_magnitude_mask_rows(w, keep, w_hat)
-    return w_hat
+    return _native().mask(w, keep, 0, True)
 
 
 def mask_nm(w: torch.Tensor, n_keep: int, m_group: int) -> torch.Tensor:
-    w_hat = torch.empty_like(w)
-    salr_magnitude_mask_nm(w, n_keep, m_group, w_hat)
-    return w_hat
+    return _native().mask(w, n_keep, m_group, False)
 
 
 def salr_residual(w: torch.Tensor, w_hat: torch.Tensor, e: torch.Tensor, stream=None) -> None:
@@ -529,24 +525,14 @@ def concat_adapters(a_list: Sequence[torch.Tensor], b_list: Sequence[torch.Tenso
 
 
 def encode(w_dense: torch.Tensor) -> Tuple[torch.Tensor, torch.Tensor, torch.Tensor]:
-    """(bitmap, values, row_offsets) of an already pruned dense matrix; two passes with one sync
-    in between to size ``values``."""
-    rows, cols = w_dense.shape
-    dev = w_dense.device
-    bitmap = torch.empty((rows, salr_bitmap_words_per_row(cols)), dtype=torch.int32, device=dev)
-    offsets = torch.empty(rows + 1, dtype=torch.int32, device=dev)
-    salr_encode_bitmap(w_dense, bitmap, None, offsets)
-    nnz = int(offsets[-1].item()) & 0xFFFFFFFF
-    values = values_alloc(nnz, dev)
-    salr_encode_bitmap(w_dense, bitmap, values, offsets)
-    return bitmap, values, offsets
+    """(bitmap, values, row_offsets) of an already pruned dense matrix; one sync after the nonzeros are counted,
+    to size ``values``."""
+    return _native().encode(w_dense)
 
 
 def decode(bitmap: torch.Tensor, values: torch.Tensor, row_offsets: torch.Tensor, rows: int, cols: int
            ) -> torch.Tensor:
-    out = torch.empty((rows, cols), dtype=torch.int16, device=bitmap.device)
-    salr_decode(bitmap, values, row_offsets, rows, cols, out)
-    return out
+    return _native().decode(bitmap, values, row_offsets, rows, cols)
 
 
 def bitmap_is_2of4(bitmap: torch.Tensor) -> bool:

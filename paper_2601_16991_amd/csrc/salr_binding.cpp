@@ -6,11 +6,19 @@
 // for the interpreter.  Read straight from the tensor objects the call takes about a third of that, most of it the HIP
 // launches.  Nothing here computes: a status other than SALR_OK comes back as the binding's SalrError.
 #include <ATen/hip/EmptyTensor.h>
+#include <ATen/ops/empty.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include "salr.h"
+
+namespace salr {   // the two halves of the encoder (see salr_internal.hpp)
+hipError_t launch_encode_index(const uint16_t* w, int64_t rows, int64_t cols, uint32_t* bitmap, uint32_t* row_offsets,
+                               uint32_t* nnz_host, hipStream_t stream);
+hipError_t launch_encode_values(const uint16_t* w, int64_t rows, int64_t cols, const uint32_t* bitmap, const uint32_t* row_offsets,
+                                uint16_t* values, int64_t capacity, hipStream_t stream);
+}  // namespace salr
 
 namespace {
 
@@ -276,6 +284,95 @@ PyObject* py_linear_backward(PyObject*, PyObject* const* v, Py_ssize_t n) {
     SALR_CATCH
 }
 
+int64_t int_of(PyObject* o) {
+    const long long v = PyLong_AsLongLong(o);
+    if (v == -1 && PyErr_Occurred()) throw PyFailure{};
+    return v;
+}
+
+// A packed-values buffer of nnz elements whose storage is whole 16-byte vectors.
+at::Tensor values_alloc(int64_t nnz, const at::Tensor& like) {
+    const int64_t padded = (nnz + 7) / 8 * 8;
+    return empty_on({padded < 8 ? 8 : padded}, at::kShort, like).narrow(0, 0, nnz);
+}
+
+// mask(w, n_keep, m_group, per_row) -> pruned copy; per_row: n_keep per row, m_group unused
+PyObject* py_mask(PyObject*, PyObject* const* v, Py_ssize_t n) {
+    SALR_TRY
+    need_args(n, 4, "mask");
+    const at::Tensor& w = tensor_of(v[0], "w");
+    need_matrix(w, "w");
+    const uint16_t* wp = device_ptr<uint16_t>(w, kBf16, "w");
+    const int64_t keep = int_of(v[1]), group = int_of(v[2]);
+    const bool per_row = PyObject_IsTrue(v[3]) == 1;
+    if (!w.is_cuda()) fail(PyExc_TypeError, "%s must be a CUDA tensor", "w");
+    at::Tensor out = empty_on(w.sizes(), w.scalar_type(), w);
+    uint16_t* op = device_ptr<uint16_t>(out, kBf16, "w_hat");
+    void* stream = stream_of(Py_None);
+    salr_status_t st;
+    {
+        Gil release;
+        st = per_row ? salr_magnitude_mask_rows(wp, w.size(0), w.size(1), keep, op, stream)
+                        : salr_magnitude_mask_nm(wp, w.size(0), w.size(1), keep, group, op, stream);
+    }
+    check(st, per_row ? "salr_magnitude_mask_rows" : "salr_magnitude_mask_nm");
+    return THPVariable_Wrap(std::move(out));
+    SALR_CATCH
+}
+
+// encode(w) -> (bitmap, values, row_offsets).  `values` can only be sized once the nonzeros are counted: the encoder's
+// first half leaves their number in pinned memory, the host waits for it once, and the second half follows.
+PyObject* py_encode(PyObject*, PyObject* w_o) {
+    SALR_TRY
+    const at::Tensor& w = tensor_of(w_o, "w_dense");
+    need_matrix(w, "w_dense");
+    const uint16_t* wp = device_ptr<uint16_t>(w, kBf16, "w_dense");
+    const int64_t rows = w.size(0), cols = w.size(1);
+    if (!w.is_cuda()) fail(PyExc_TypeError, "%s must be a CUDA tensor", "w_dense");
+    if (rows > 0x7FFFFFFFLL || cols > 0x7FFFFFFFLL - 31 || (cols > 0 && rows > 0xFFFFFFFFLL / cols)) check(SALR_ERR_SHAPE, "salr_encode_bitmap");
+    at::Tensor bitmap = empty_on({rows, (cols + 31) / 32}, at::kInt, w), offsets = empty_on({rows + 1}, at::kInt, w);
+    uint32_t *bp = device_ptr<uint32_t>(bitmap, kU32, "bitmap"), *rp = device_ptr<uint32_t>(offsets, kU32, "row_offsets");
+    at::Tensor count = at::empty({1}, at::TensorOptions().dtype(at::kInt).pinned_memory(true));
+    uint32_t* nnz_host = static_cast<uint32_t*>(count.data_ptr());
+    hipStream_t stream = static_cast<hipStream_t>(stream_of(Py_None));
+    hipError_t e;
+    {
+        Gil release;
+        e = salr::launch_encode_index(wp, rows, cols, bp, rp, nnz_host, stream);
+        if (e == hipSuccess) e = hipStreamSynchronize(stream);
+    }
+    check(e == hipSuccess ? SALR_OK : SALR_ERR_HIP, "salr_encode_bitmap");
+    const int64_t nnz = *static_cast<volatile uint32_t*>(nnz_host);
+    at::Tensor values = values_alloc(nnz, w);
+    e = nnz > 0 ? salr::launch_encode_values(wp, rows, cols, bp, rp, static_cast<uint16_t*>(values.data_ptr()), nnz, stream) : hipSuccess;
+    check(e == hipSuccess ? SALR_OK : SALR_ERR_HIP, "salr_encode_bitmap");
+    return Py_BuildValue("NNN", THPVariable_Wrap(std::move(bitmap)), THPVariable_Wrap(std::move(values)), THPVariable_Wrap(std::move(offsets)));
+    SALR_CATCH
+}
+
+// decode(bitmap, values, row_offsets, rows, cols) -> [rows, cols] int16
+PyObject* py_decode(PyObject*, PyObject* const* v, Py_ssize_t n) {
+    SALR_TRY
+    need_args(n, 5, "decode");
+    const at::Tensor& bm = tensor_of(v[0], "bitmap");
+    const uint32_t* bp = device_ptr<uint32_t>(bm, kU32, "bitmap");
+    const uint16_t* vp = device_ptr<uint16_t>(tensor_of(v[1], "values"), kBf16, "values");
+    const uint32_t* rp = device_ptr<uint32_t>(tensor_of(v[2], "row_offsets"), kU32, "row_offsets");
+    const int64_t rows = int_of(v[3]), cols = int_of(v[4]);
+    if (!bm.defined()) fail(PyExc_TypeError, "%s must be a tensor", "bitmap");
+    at::Tensor out = empty_on({rows, cols}, at::kShort, bm);
+    uint16_t* op = device_ptr<uint16_t>(out, kBf16, "w_dense_out");
+    void* stream = stream_of(Py_None);
+    salr_status_t st;
+    {
+        Gil release;
+        st = salr_decode(bp, vp, rp, rows, cols, op, stream);
+    }
+    check(st, "salr_decode");
+    return THPVariable_Wrap(std::move(out));
+    SALR_CATCH
+}
+
 PyObject* py_set_error(PyObject*, PyObject* cls) {
     Py_XINCREF(cls);
     Py_XSETREF(g_salr_error, cls);
@@ -287,6 +384,9 @@ PyMethodDef kMethods[] = {
     SALR_FAST("linear", py_linear),
     SALR_FAST("qsalr_linear", py_qsalr_linear),
     SALR_FAST("linear_backward", py_linear_backward),
+    SALR_FAST("mask", py_mask),
+    SALR_FAST("decode", py_decode),
+    {"encode", py_encode, METH_O, nullptr},
     {"set_error", py_set_error, METH_O, nullptr},
     {nullptr, nullptr, 0, nullptr},
 };

@@ -3,7 +3,8 @@
 // Encoding is three launches on the caller's stream:
 //   1. encode_count_kernel   one workgroup per row: bitmap words + the row's nonzero count
 //   2. row_scan_kernel       one workgroup: counts -> row_offsets (exclusive prefix, in place)
-//   3. encode_compact_kernel one workgroup per row: order-preserving compaction of the nonzeros
+//   3. encode_compact_rows_kernel (encode_compact_kernel where rows do not allow 16-byte loads)
+//                            one workgroup per row: order-preserving compaction of the nonzeros
 // Decoding is one launch, one workgroup per row.  All of it is integer/bit work; the traffic is the
 // dense matrix (2 B/element) against bitmap + values (1/8 + 2(1-p) B/element).
 #include "salr_device.hpp"
@@ -48,20 +49,35 @@ __global__ __launch_bounds__(kCodecThreads) void encode_count_kernel(const uint1
 }
 
 constexpr int kScanThreads = 1024;
+constexpr int kScanItems = 8;   // consecutive rows per thread and round
 
-// row_offsets[1..rows] holds per-row counts on entry and inclusive prefix sums on exit; [0] = 0.
-__global__ __launch_bounds__(kScanThreads) void row_scan_kernel(uint32_t* __restrict__ row_offsets, int64_t rows) {
+// row_offsets[1..rows] holds per-row counts on entry and inclusive prefix sums on exit; [0] = 0; *nnz_host (pinned host
+// memory, may be null) gets the total as well.  One workgroup, bound by the latency of its rounds, so a thread takes
+// kScanItems rows a round with all their loads in flight (one row a round took 14.7 us on 14336 rows).
+__global__ __launch_bounds__(kScanThreads) void row_scan_kernel(uint32_t* __restrict__ row_offsets, int64_t rows,
+                                                                uint32_t* __restrict__ nnz_host) {
     __shared__ uint32_t scratch[kScanThreads / kWave];
     uint32_t carry = 0;
-    for (int64_t base = 0; base < rows; base += kScanThreads) {
-        const int64_t i = base + threadIdx.x;
-        const uint32_t v = (i < rows) ? row_offsets[i + 1] : 0u;
+    for (int64_t base = 0; base < rows; base += kScanThreads * kScanItems) {
+        const int64_t i0 = base + (int64_t)threadIdx.x * kScanItems;
+        uint32_t v[kScanItems], sum = 0;
+#pragma unroll
+        for (int j = 0; j < kScanItems; ++j) v[j] = (i0 + j < rows) ? row_offsets[i0 + j + 1] : 0u;
+#pragma unroll
+        for (int j = 0; j < kScanItems; ++j) sum += v[j];
         uint32_t total;
-        const uint32_t excl = block_exclusive_scan<kScanThreads>(v, scratch, total);
-        if (i < rows) row_offsets[i + 1] = carry + excl + v;
+        uint32_t at = carry + block_exclusive_scan<kScanThreads>(sum, scratch, total);
+#pragma unroll
+        for (int j = 0; j < kScanItems; ++j) {
+            at += v[j];
+            if (i0 + j < rows) row_offsets[i0 + j + 1] = at;
+        }
         carry += total;
     }
-    if (threadIdx.x == 0) row_offsets[0] = 0;
+    if (threadIdx.x == 0) {
+        row_offsets[0] = 0;
+        if (nnz_host != nullptr) *nnz_host = carry;
+    }
 }
 
 template <bool kVec>
@@ -90,6 +106,96 @@ __global__ __launch_bounds__(kCodecThreads) void encode_compact_kernel(const uin
             }
         }
         cursor += total;
+    }
+}
+
+constexpr int kDecWaves = kCodecThreads / kWave;
+constexpr int kDecMaxGroups = 1024;   // rows up to 524288 columns
+
+// prefix[g] = nonzeros of a bitmap row before group g of 16 words (512 columns), prefix[groups] = all of them; the whole
+// workgroup calls it and it ends with a barrier.
+__device__ __forceinline__ void group_prefix(const uint32_t* brow, int64_t wpr, int groups, uint32_t* prefix) {
+    const int lane = lane_id();
+    for (int g = threadIdx.x >> 4; g < groups; g += kCodecThreads / 16) {
+        const int64_t w = 16 * (int64_t)g + (lane & 15);
+        uint32_t c = w < wpr ? __popc(brow[w]) : 0u;
+#pragma unroll
+        for (int d = 8; d > 0; d >>= 1) c += __shfl_xor(c, d, kWave);
+        if ((lane & 15) == 0) prefix[g + 1] = c;
+    }
+    __syncthreads();
+    if (threadIdx.x < kWave) {
+        uint32_t carry = 0;
+        for (int base = 0; base < groups; base += kWave) {
+            const int g = base + lane;
+            const uint32_t c = g < groups ? prefix[g + 1] : 0u;
+            const uint32_t incl = wave_inclusive_scan(c);
+            if (g < groups) prefix[g + 1] = carry + incl;
+            carry += __shfl(incl, kWave - 1, kWave);
+        }
+        if (lane == 0) prefix[0] = 0;
+    }
+    __syncthreads();
+}
+
+// Compaction of rows that allow 16-byte loads, one workgroup per row.  The bitmap is written by then, so the waves need
+// nothing from each other: a first pass popcounts the bitmap row into start offsets per group of 512 columns (the only
+// block barriers), then every wave takes groups on its own -- one 16-byte load per lane (the next group's in flight), a
+// wave scan of the byte popcounts, the nonzeros dropped into the wave's LDS slot at their place in the output's 16-byte
+// vectors, whole vectors stored as such, the ragged ends of the piece as single values.  Bound by memory: 4096 x 14336 at
+// 50 %, 176 MB: 43.6 us with a block scan per 2048 columns and a two-byte store per value, now 36.
+__global__ __launch_bounds__(kCodecThreads) void encode_compact_rows_kernel(const uint16_t* __restrict__ w, int64_t cols, int64_t wpr,
+                                                                            const uint32_t* __restrict__ bitmap,
+                                                                            const uint32_t* __restrict__ row_offsets,
+                                                                            uint16_t* __restrict__ values, int64_t capacity) {
+    __shared__ uint32_t prefix[kDecMaxGroups + 1];
+    __shared__ __attribute__((aligned(16))) uint16_t slot[kDecWaves][65 * 8];
+    const int lane = lane_id();
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int64_t n = blockIdx.x;
+    const uint32_t* brow = bitmap + n * wpr;
+    const int groups = (int)((wpr + 15) / 16);
+    const uint16_t* row = w + n * cols;
+    const int64_t units = cols / kUnit;
+    const uint8_t* mask_bytes = reinterpret_cast<const uint8_t*>(brow);
+    // units past the row end repeat its last one and count as empty
+    auto load_group = [&](int g, uint32_t& m) -> uint4 {
+        const int64_t u = 64 * (int64_t)g + lane, uc = u < units ? u : units - 1;
+        const uint32_t b = mask_bytes[uc];
+        m = u < units ? b : 0u;
+        return *reinterpret_cast<const uint4*>(row + uc * kUnit);
+    };
+    uint32_t m;
+    uint4 q = load_group(wave, m);
+    group_prefix(brow, wpr, groups, prefix);
+    const uint32_t row_start = row_offsets[n];
+    uint16_t* my_slot = slot[wave];
+    const uint32_t cap = capacity < 0xFFFFFFFFLL ? (uint32_t)capacity : 0xFFFFFFFFu;
+    for (int g = wave; g < groups; g += kDecWaves) {
+        uint32_t m_next;
+        const uint4 next = load_group(g + kDecWaves, m_next);
+        const uint32_t cursor = row_start + prefix[g], total = prefix[g + 1] - prefix[g];
+        const uint32_t first = cursor & 7u;   // position of the piece's first value in its first output vector
+        uint32_t at = first + wave_inclusive_scan(__popc(m)) - __popc(m);
+#pragma unroll
+        for (int j = 0; j < kUnit; ++j) {
+            if ((m >> j) & 1u) my_slot[at] = (uint16_t)unit_elem(q, j);
+            at += (m >> j) & 1u;
+        }
+        __builtin_amdgcn_wave_barrier();   // LDS executes a wave's accesses in order
+        const uint32_t base = cursor - first, end = first + total;   // output index of slot 0; the piece is slots [first, end)
+        for (uint32_t v = lane; 8 * v < end; v += kWave) {           // at most two trips
+            const uint32_t lo = 8 * v < first ? first : 8 * v, hi = 8 * v + 8 < end ? 8 * v + 8 : end;
+            if (hi - lo == 8u && base + hi <= cap) {
+                *reinterpret_cast<uint4*>(values + base + lo) = *reinterpret_cast<const uint4*>(my_slot + lo);
+            } else {
+                for (uint32_t i = lo; i < hi; ++i)
+                    if (base + i < cap) values[base + i] = my_slot[i];
+            }
+        }
+        __builtin_amdgcn_wave_barrier();
+        q = next;
+        m = m_next;
     }
 }
 
@@ -151,9 +257,6 @@ __global__ __launch_bounds__(kCodecThreads) void decode_kernel(const uint32_t* _
 // own -- wave scan of the byte popcounts, the group's values (one contiguous piece, at most 65 aligned 16-byte
 // vectors) copied into the wave's LDS slot, nibble expansion, one 16-byte store per lane -- with the loads of
 // its next group already in flight.
-constexpr int kDecWaves = kCodecThreads / kWave;
-constexpr int kDecMaxGroups = 1024;   // rows up to 524288 columns
-
 // kNf4 (QSALR, paper Sec. 4): `values` are the 4-bit codes, eight to a dword where the bf16 kernel has a 16-byte vector of
 // eight values; a lane dequantises its dword (all eight codes lie in one scale block of 64) on the way into the slot,
 // and everything after that is the same.  scale_last: index of the last scale.
@@ -174,27 +277,7 @@ __global__ __launch_bounds__(kCodecThreads) void decode_rows_kernel(const uint32
     const int64_t n = blockIdx.x;
     const uint32_t* brow = bitmap + n * wpr;
     const int groups = (int)((wpr + 15) / 16);
-    // ---- pass 1: nonzeros per group of 16 words, then their exclusive prefix
-    for (int g = threadIdx.x >> 4; g < groups; g += kCodecThreads / 16) {
-        const int64_t w = 16 * (int64_t)g + (lane & 15);
-        uint32_t c = w < wpr ? __popc(brow[w]) : 0u;
-#pragma unroll
-        for (int d = 8; d > 0; d >>= 1) c += __shfl_xor(c, d, kWave);
-        if ((lane & 15) == 0) prefix[g + 1] = c;
-    }
-    __syncthreads();
-    if (wave == 0) {
-        uint32_t carry = 0;
-        for (int base = 0; base < groups; base += kWave) {
-            const int g = base + lane;
-            const uint32_t c = g < groups ? prefix[g + 1] : 0u;
-            const uint32_t incl = wave_inclusive_scan(c);
-            if (g < groups) prefix[g + 1] = carry + incl;
-            carry += __shfl(incl, kWave - 1, kWave);
-        }
-        if (lane == 0) prefix[0] = 0;
-    }
-    __syncthreads();
+    group_prefix(brow, wpr, groups, prefix);   // ---- pass 1
     // ---- pass 2
     const uint8_t* mask_bytes = reinterpret_cast<const uint8_t*>(brow);
     const uint4* values128 = reinterpret_cast<const uint4*>(values);
@@ -272,20 +355,34 @@ static bool vec_ok(const void* p, int64_t cols) {
     return (cols % kUnit == 0) && ((reinterpret_cast<uintptr_t>(p) & 15u) == 0);
 }
 
-hipError_t launch_encode(const uint16_t* w, int64_t rows, int64_t cols, uint32_t* bitmap, uint16_t* values,
-                         int64_t capacity, uint32_t* row_offsets, hipStream_t stream) {
+hipError_t launch_encode_index(const uint16_t* w, int64_t rows, int64_t cols, uint32_t* bitmap, uint32_t* row_offsets,
+                               uint32_t* nnz_host, hipStream_t stream) {
     const int64_t wpr = (cols + 31) / 32;
-    const bool vec = vec_ok(w, cols);
     if (rows > 0) {
-        if (vec) hipLaunchKernelGGL(encode_count_kernel<true>, dim3((unsigned)rows), dim3(kCodecThreads), 0, stream, w, cols, wpr, bitmap, row_offsets);
+        if (vec_ok(w, cols)) hipLaunchKernelGGL(encode_count_kernel<true>, dim3((unsigned)rows), dim3(kCodecThreads), 0, stream, w, cols, wpr, bitmap, row_offsets);
         else hipLaunchKernelGGL(encode_count_kernel<false>, dim3((unsigned)rows), dim3(kCodecThreads), 0, stream, w, cols, wpr, bitmap, row_offsets);
     }
-    hipLaunchKernelGGL(row_scan_kernel, dim3(1), dim3(kScanThreads), 0, stream, row_offsets, rows);
-    if (values != nullptr && rows > 0 && cols > 0) {
-        if (vec) hipLaunchKernelGGL(encode_compact_kernel<true>, dim3((unsigned)rows), dim3(kCodecThreads), 0, stream, w, cols, row_offsets, values, capacity);
-        else hipLaunchKernelGGL(encode_compact_kernel<false>, dim3((unsigned)rows), dim3(kCodecThreads), 0, stream, w, cols, row_offsets, values, capacity);
-    }
+    hipLaunchKernelGGL(row_scan_kernel, dim3(1), dim3(kScanThreads), 0, stream, row_offsets, rows, nnz_host);
     return hipGetLastError();
+}
+
+hipError_t launch_encode_values(const uint16_t* w, int64_t rows, int64_t cols, const uint32_t* bitmap, const uint32_t* row_offsets,
+                                uint16_t* values, int64_t capacity, hipStream_t stream) {
+    if (values == nullptr || rows == 0 || cols == 0) return hipSuccess;
+    const int64_t wpr = (cols + 31) / 32;
+    if (vec_ok(w, cols) && vec_ok(values, kUnit) && (wpr + 15) / 16 <= kDecMaxGroups)
+        hipLaunchKernelGGL(encode_compact_rows_kernel, dim3((unsigned)rows), dim3(kCodecThreads), 0, stream, w, cols, wpr, bitmap, row_offsets, values, capacity);
+    else if (vec_ok(w, cols))
+        hipLaunchKernelGGL(encode_compact_kernel<true>, dim3((unsigned)rows), dim3(kCodecThreads), 0, stream, w, cols, row_offsets, values, capacity);
+    else
+        hipLaunchKernelGGL(encode_compact_kernel<false>, dim3((unsigned)rows), dim3(kCodecThreads), 0, stream, w, cols, row_offsets, values, capacity);
+    return hipGetLastError();
+}
+
+hipError_t launch_encode(const uint16_t* w, int64_t rows, int64_t cols, uint32_t* bitmap, uint16_t* values,
+                         int64_t capacity, uint32_t* row_offsets, hipStream_t stream) {
+    const hipError_t e = launch_encode_index(w, rows, cols, bitmap, row_offsets, nullptr, stream);
+    return e != hipSuccess ? e : launch_encode_values(w, rows, cols, bitmap, row_offsets, values, capacity, stream);
 }
 
 hipError_t launch_decode(const uint32_t* bitmap, const uint16_t* values, const uint32_t* row_offsets, int64_t rows,

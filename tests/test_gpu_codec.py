@@ -115,3 +115,25 @@ def test_codec_config_shapes(name, permille, rows):
     w = wl.dense_weight(cfg, rows=rows)
     w_hat = oracle.mask_topk_rows(w, cfg.keep(permille))
     _check_codec(w_hat, f"{name} p={permille} rows={w.shape[0]}")
+
+
+@pytest.mark.parametrize("rows,cols", [(8192, 8), (8193, 16), (17000, 8)])
+def test_codec_many_rows(rows, cols):
+    """Row counts around and past one round of the scan over rows."""
+    _check_codec(_random_sparse(rows, cols, 0.5, rows), f"many rows {rows}x{cols}")
+
+
+def test_encode_capacity_inside_a_vector():
+    """Rows of whole 16-byte units: the compaction stores whole vectors, and none past a capacity that ends inside one."""
+    salr = _salr()
+    w = _random_sparse(6, 1024, 0.7, 31)
+    rb, rv, ro = oracle.encode(w)
+    bitmap = torch.zeros((6, 32), dtype=torch.int32, device=dev())
+    offsets = torch.zeros(7, dtype=torch.int32, device=dev())
+    for cap in (0, 5, 8, 1001, rv.size - 3, rv.size):
+        buf = torch.full((rv.size + 64,), 0x5A5A, dtype=torch.int16, device=dev())
+        salr.salr_encode_bitmap(to_dev_u16(w), bitmap, buf[:cap], offsets)
+        torch.cuda.synchronize()
+        got = to_host_u16(buf)
+        assert np.array_equal(got[:cap], rv[:cap]) and (got[cap:] == 0x5A5A).all(), cap
+        assert np.array_equal(to_host_u32(offsets), ro)

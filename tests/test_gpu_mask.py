@@ -105,3 +105,18 @@ def test_mask_nm_q_proj_2_of_4():
     got = _salr().mask_nm(to_dev_u16(w), 2, 4)
     torch.cuda.synchronize()
     assert np.array_equal(to_host_u16(got).reshape(w.shape), oracle.mask_nm(w, 2, 4))
+
+
+@pytest.mark.parametrize("rows,cols,keep", [(5, 8200, 4100), (3, 14336, 14335), (5, 14336, 1), (6, 14344, 3), (3, 28672, 9000),
+                                            (2, 28664, 0), (2, 11008, 11008), (3, 16384, 8192)])
+def test_mask_rows_long_rows_one_wave_per_row(rows, cols, keep):
+    """The register counts above 8192 columns, at their edges; the search starts from the row's first columns, so rows whose
+    start says nothing about the rest (constant, empty, infinite) as well."""
+    w = wl.gaussian_bf16((rows, cols), 0.02, cols + keep)
+    _check_rows(w, keep, "long rows, gaussian")
+    _check_rows(_few_magnitudes((rows, cols), cols + keep), keep, "long rows, ties")
+    w = w.copy()
+    w[0, :512] = 0x8000
+    w[1, :512] = 0xFF80
+    w[1, 512:] &= 0x80FF
+    _check_rows(w, keep, "long rows, misleading start")
