@@ -95,15 +95,45 @@ __global__ __launch_bounds__(256) void adapter_t_kernel(const uint16_t* __restri
     }
 }
 
-// out = bf16(sum over z of partial[z]), four elements per thread (count % 4 == 0), z in ascending order.
+// out = bf16(sum over z of partial[z]), four elements per thread, in a fixed order; slices are
+// whole float4 apart (splitk_slice).  kZ threads share an
+// output, thread q taking z = q, q + kZ, ..; each has up to eight requests in flight (one after the other, 56 slices of a
+// [256, 32] sum took 15.9 us).
+template <int kZ>
 __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restrict__ partial, int64_t count, int ksplit,
                                                             uint16_t* __restrict__ out) {
-    const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
+    constexpr int kOut = 256 / kZ;   // outputs (of four elements) per workgroup
+    __shared__ float4 sums[kZ > 1 ? 256 : 1];
+    const int64_t slice = splitk_slice(count);
+    const int c = threadIdx.x % kOut, q = threadIdx.x / kOut;
+    const int64_t i = ((int64_t)blockIdx.x * kOut + c) * 4;
+    float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (i < count) {
+        for (int z0 = q; z0 < ksplit; z0 += 8 * kZ) {
+            float4 p[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+                if (z0 + kZ * j < ksplit) p[j] = *reinterpret_cast<const float4*>(partial + (int64_t)(z0 + kZ * j) * slice + i);
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+                if (z0 + kZ * j < ksplit) { s.x += p[j].x; s.y += p[j].y; s.z += p[j].z; s.w += p[j].w; }
+        }
+    }
+    if constexpr (kZ > 1) {
+        sums[threadIdx.x] = s;
+        __syncthreads();
+        if (q > 0) return;
+#pragma unroll
+        for (int j = 1; j < kZ; ++j) {
+            const float4 p = sums[j * kOut + c];
+            s.x += p.x; s.y += p.y; s.z += p.z; s.w += p.w;
+        }
+    }
     if (i >= count) return;
-    float4 s = *reinterpret_cast<const float4*>(partial + i);
-    for (int z = 1; z < ksplit; ++z) {
-        const float4 p = *reinterpret_cast<const float4*>(partial + (int64_t)z * count + i);
-        s.x += p.x; s.y += p.y; s.z += p.z; s.w += p.w;
+    if (i + 4 > count) {   // the last outputs of a count that is no multiple of four
+        const float e[3] = {s.x, s.y, s.z};
+        for (int j = 0; i + j < count; ++j) out[i + j] = f32_to_bf16_rne(e[j]);
+        return;
     }
     uint2 o;
     o.x = (uint32_t)f32_to_bf16_rne(s.x) | ((uint32_t)f32_to_bf16_rne(s.y) << 16);
@@ -112,8 +142,12 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restr
 }
 
 void launch_splitk_reduce(const float* partial, int64_t count, int ksplit, uint16_t* out, hipStream_t stream) {
-    hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)((count / 4 + 255) / 256)), dim3(256), 0, stream, partial, count,
-                       ksplit, out);
+    if (ksplit > 8)
+        hipLaunchKernelGGL(splitk_reduce_kernel<4>, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, stream, partial, count,
+                           ksplit, out);
+    else
+        hipLaunchKernelGGL(splitk_reduce_kernel<1>, dim3((unsigned)((count + 1023) / 1024)), dim3(256), 0, stream, partial, count,
+                           ksplit, out);
 }
 
 // a_t[r][k] = A_cat[k][r] for r < R, 0 for R <= r < Rpad: one thread per k and block of 8 ranks.

@@ -1,0 +1,122 @@
+// T = X * A_cat (Sec. 3.2, first concatenated GEMM) for the large-batch paths: one workgroup's work.
+#pragma once
+
+#include "salr_device.hpp"
+#include "salr_linear_common.hpp"
+
+namespace salr {
+
+typedef short i16x4 __attribute__((ext_vector_type(4)));
+
+// Four rows of a column from a row-major bf16 tile in LDS (gfx950's transposing read): every 16 lanes read four rows of 16
+// elements, lane i the quarter i % 4 of row i / 4 at `p`, and lane i receives column i of those rows.
+__device__ __forceinline__ uint2 lds_read_tr4(const uint16_t* p) {
+    return __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                                         (__attribute__((address_space(3))) i16x4*)(uintptr_t)(__attribute__((address_space(3))) const void*)p));
+}
+
+constexpr int kTaPitch = 40;   // bf16 per row of an A tile [32 k][32 ranks]: 80 bytes, 16-byte aligned, rows spread over the banks
+constexpr int kTxPitch = 72;   // bf16 per row of an X tile [rows][64 k]: 144 bytes, the 16 rows of an operand on different banks
+
+template <int kMT, int kWaves>
+constexpr int adapter_t_lds_bytes() {
+    constexpr int tiles = kWaves * (32 * kTaPitch + 16 * kMT * kTxPitch) * 2, sums = kWaves * kMT * 2 * 256 * 4;
+    return tiles > sums ? tiles : sums;
+}
+
+// Rows 16 kMT rb .. of T, ranks 32 rg .. 32 rg + 31 (columns past R as zeros), bf16 [M, Rpad].  The waves split K among
+// themselves, every kWaves-th step of 64 columns each, and are summed through LDS, so that the result needs no partial sums in
+// memory and no second launch.  X is fetched as whole 128-byte lines (16 rows x 64 bytes per request, the MFMA operand as it
+// is, asks the L2 twice for every line, and with rows a multiple of 4 KB apart all from one channel) and turned into operands
+// through LDS; A_cat's rows go there as they lie and come back transposed.  kDepth steps in flight per wave.
+// R % 8 == 0 (A_cat's rows are whole 16-byte vectors).  `lds`: adapter_t_lds_bytes<kMT, kWaves>().
+template <int kMT, int kWaves, int kDepth>
+__device__ __forceinline__ void adapter_t_block(const uint16_t* __restrict__ x, int64_t M, int64_t K, const uint16_t* __restrict__ a_cat,
+                                                int R, int Rpad, uint16_t* __restrict__ t, int64_t rb, int rg, uint16_t* lds) {
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int i16 = lane & 15, g = lane >> 4;
+    const int64_t steps = (K + 63) >> 6;
+    const int64_t m0 = rb * 16 * kMT;
+    uint16_t* a_tile = lds + wave * (32 * kTaPitch + 16 * kMT * kTxPitch);
+    uint16_t* x_tile = a_tile + 32 * kTaPitch;
+    // X loader: lane l fetches segment l % 8 (16 bytes) of row l / 8 of every eight rows
+    const int xseg = lane & 7;
+    const uint16_t* xrow[2 * kMT];
+#pragma unroll
+    for (int i = 0; i < 2 * kMT; ++i) {
+        const int64_t m = m0 + 8 * i + (lane >> 3);
+        xrow[i] = x + (m < M ? m : M - 1) * K + 8 * xseg;
+    }
+    // A loader: lane l fetches eight ranks from 32 rg + 8 (l % 4) of row l / 4 of every sixteen
+    const int arow = lane >> 2, acol = 32 * rg + 8 * (lane & 3);
+    auto load_a = [&](int64_t k) -> uint4 { return *reinterpret_cast<const uint4*>(a_cat + k * R + (acol < R ? acol : R - 8)); };
+    f32x4 acc[kMT][2];
+#pragma unroll
+    for (int i = 0; i < kMT; ++i) acc[i][0] = acc[i][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int64_t s0 = wave; s0 < steps; s0 += kWaves * kDepth) {
+        uint4 xq[kDepth][2 * kMT], aq[kDepth][4];
+#pragma unroll
+        for (int d = 0; d < kDepth; ++d) {
+            const int64_t s = s0 + kWaves * d;
+            const int64_t k = (s < steps ? s : steps - 1) << 6;   // past the end: the last step again, not used
+            const int64_t half = k + 64 > K ? 32 : 0;             // the last step has 32 columns when K % 64 is 32: its first half twice
+#pragma unroll
+            for (int i = 0; i < 2 * kMT; ++i) xq[d][i] = *reinterpret_cast<const uint4*>(xrow[i] + k - (xseg >= 4 ? half : 0));
+#pragma unroll
+            for (int i = 0; i < 4; ++i) aq[d][i] = load_a(k + arow + 16 * i - (i >= 2 ? half : 0));
+        }
+#pragma unroll
+        for (int d = 0; d < kDepth; ++d) {
+            const int64_t s = s0 + kWaves * d;
+            if (s < steps) {   // wave-uniform
+#pragma unroll
+                for (int i = 0; i < 2 * kMT; ++i)
+                    *reinterpret_cast<uint4*>(x_tile + (8 * i + (lane >> 3)) * kTxPitch + 8 * xseg) = xq[d][i];
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {   // 32 columns each
+                    if (h == 0 || (s << 6) + 32 < K) {   // wave-uniform
+                        *reinterpret_cast<uint4*>(a_tile + arow * kTaPitch + 8 * (lane & 3)) = aq[d][2 * h];
+                        *reinterpret_cast<uint4*>(a_tile + (arow + 16) * kTaPitch + 8 * (lane & 3)) = aq[d][2 * h + 1];
+                        __builtin_amdgcn_wave_barrier();   // LDS executes a wave's accesses in order
+                        const uint16_t* col = a_tile + (8 * g + (i16 >> 2)) * kTaPitch + 4 * (i16 & 3);
+                        bf16x8 xf[kMT];
+#pragma unroll
+                        for (int i = 0; i < kMT; ++i)
+                            xf[i] = *reinterpret_cast<const bf16x8*>(x_tile + (16 * i + i16) * kTxPitch + 32 * h + 8 * g);
+#pragma unroll
+                        for (int rt = 0; rt < 2; ++rt) {
+                            const uint2 lo = lds_read_tr4(col + 16 * rt), hi = lds_read_tr4(col + 4 * kTaPitch + 16 * rt);
+                            const bf16x8 b = as_bf16x8(make_uint4(lo.x, lo.y, hi.x, hi.y));
+#pragma unroll
+                            for (int i = 0; i < kMT; ++i) acc[i][rt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xf[i], b, acc[i][rt], 0, 0, 0);
+                        }
+                        __builtin_amdgcn_wave_barrier();
+                    }
+                }
+            }
+        }
+    }
+    __syncthreads();
+    // accumulator layout: lane holds T[16 i + 4 g + e][16 rt + i16]
+    float* red = reinterpret_cast<float*>(lds);
+#pragma unroll
+    for (int i = 0; i < kMT; ++i)
+#pragma unroll
+        for (int rt = 0; rt < 2; ++rt)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) red[(wave * kMT * 2 + i * 2 + rt) * 256 + e * 64 + lane] = acc[i][rt][e];
+    __syncthreads();
+    for (int idx = tid; idx < kMT * 512; idx += 64 * kWaves) {
+        float s = 0.f;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) s += red[w * kMT * 512 + idx];
+        const int l = idx & 63, e = (idx >> 6) & 3, rt = (idx >> 8) & 1, i = idx >> 9;
+        const int64_t m = m0 + 16 * i + 4 * (l >> 4) + e;
+        const int r = 32 * rg + 16 * rt + (l & 15);
+        if (m < M) t[m * Rpad + r] = r < R ? f32_to_bf16_rne(s) : (uint16_t)0;
+    }
+}
+
+}  // namespace salr

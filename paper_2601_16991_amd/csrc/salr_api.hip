@@ -37,10 +37,10 @@ constexpr int64_t kMaxRank = 256;
 constexpr int64_t kMaxM = 65535LL * 64;           // gridDim.y of the generic kernel
 constexpr int64_t kMaxSvdDim = 65535LL * 32;      // gridDim.y of the transposing kernel
 
-// QSALR calls whose decode stage reads the 4-bit codes itself: the two-stage path (large batches, K % 64 == 0) within the
-// row decode kernel's limits (rows of at most 524288 columns); the workspace is then the plain layer's.
+// QSALR calls whose decode stage reads the 4-bit codes itself: the two-stage path (large batches); the workspace is then the
+// plain layer's.
 bool qsalr_decodes_codes(int64_t M, int64_t K, int64_t N, int64_t nnz) {
-    return nnz > 0 && K > 0 && salr::linear_takes_twostage(M, K, N) && (K / 32 + 15) / 16 <= 1024;
+    return nnz > 0 && K > 0 && salr::linear_takes_twostage(M, K, N);
 }
 
 }  // namespace

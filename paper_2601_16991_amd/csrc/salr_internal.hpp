@@ -95,9 +95,14 @@ constexpr int64_t kStreamMaxM = 64;
 constexpr int kStreamTSlices = 16;
 constexpr int kMaxRankPadded = 256;  // R <= 256: pitch of the T tile the streaming kernels keep in LDS
 
-// Large-batch path: M > kStreamMaxM decodes the weight once into a dense scratch matrix, then runs a dense MFMA
-// GEMM on it (k-steps of 64).
-inline bool uses_twostage(int64_t M, int64_t K) { return M > kStreamMaxM && K >= 64 && K % 64 == 0; }
+// Large-batch path: M > kStreamMaxM decodes the weight once into scratch memory in MFMA operand order, then runs a dense
+// MFMA GEMM on it (k-steps of 64; offsets inside a tile of X are 32-bit).
+inline bool uses_twostage(int64_t M, int64_t K) { return M > kStreamMaxM && K >= 32 && K % 32 == 0 && K <= (1 << 22); }
+// Decoded weight in operand order (salr_gemm.hip): 1 KB blocks of 16 rows x 32 columns, an even number along the columns,
+// and the rank blocks of B_cat (likewise) behind them.
+inline size_t frag_weight_bytes(int64_t K, int64_t N, int64_t R) {
+    return (size_t)((N + 15) / 16) * (size_t)((K + 63) / 64 + (R + 63) / 64) * 2048;
+}
 
 inline size_t round_up_256(size_t b) { return (b + 255) / 256 * 256; }
 
@@ -108,7 +113,26 @@ inline size_t adapter_t_bytes(int64_t M, int64_t R) {
     return R > 0 ? round_up_256((size_t)M * (size_t)adapter_rank_padded(R) * sizeof(uint16_t)) : 0;
 }
 inline size_t adapter_at_bytes(int64_t K, int64_t R) {
-    return R > 0 ? round_up_256((size_t)K * (size_t)adapter_rank_padded(R) * sizeof(uint16_t)) : 0;
+    return R > 0 ? round_up_256((size_t)((K + 63) / 64 * 64) * (size_t)adapter_rank_padded(R) * sizeof(uint16_t)) : 0;
+}
+// Rows of X per block of the large-batch T (salr_adapter_t.hpp), in tiles of 16: two where the blocks are many anyway (each
+// reads its ranks' part of A_cat once).
+inline int adapter_t_row_tiles(int64_t M) { return M >= 1024 ? 2 : 1; }
+// T = X * A_cat of the large-batch paths: one launch that reads X once per 32 ranks and A_cat once per block of rows
+// (launch_adapter_t_direct), or a split-K product on the MFMA stage's kernel, which reads X once but costs a summing pass and
+// A_cat in operand order.  The latter where the former is more than about fifteen microseconds of traffic (70B down_proj at
+// 4096 tokens: 85 us; the transposing pass, tall product and sum before it 129) or a long chain of steps (300 tokens: 8.8 us at
+// K = 4096, 20.6 at 14336; the product and its sum 14), and where A_cat's rows are no whole 16-byte vectors.
+inline bool adapter_t_own_product(int64_t M, int64_t K, int64_t R) {
+    if (R % 8 != 0 || K > 8192) return true;
+    const double groups = (double)((R + 31) / 32), rows = 16.0 * adapter_t_row_tiles(M);
+    return groups * ((double)M * K * 2 + M / rows * 64.0 * K) > 64e6;
+}
+inline int adapter_t_product_ksplit(int64_t M, int64_t K, int64_t Rpad) {
+    const int64_t wgs = (M + 255) / 256 * ((Rpad + 127) / 128), steps = (K + 63) / 64;
+    int64_t ks = (256 + wgs - 1) / wgs;
+    if (ks > steps / 4) ks = steps / 4;
+    return (int)(ks < 1 ? 1 : ks > 64 ? 64 : ks);
 }
 // T = X * A_cat splits K over workgroups (fp32 partials [ksplit, M, Rpad], added up in a fixed order).
 inline int adapter_rows_per_block(int64_t M) { return M >= 4096 ? 256 : 64; }
@@ -132,6 +156,14 @@ inline size_t adapter_partial_bytes(int64_t M, int64_t K, int64_t R) {
 inline size_t twostage_dense_offset(int64_t M, int64_t K, int64_t R) {
     return adapter_t_bytes(M, R) + adapter_at_bytes(K, R) + adapter_partial_bytes(M, K, R);
 }
+inline size_t frag_weight_offset(int64_t M, int64_t K, int64_t R) {   // T first, then what a product of its own needs
+    size_t b = adapter_t_bytes(M, R);
+    if (R > 0 && adapter_t_own_product(M, K, R)) {
+        const int64_t Rpad = adapter_rank_padded(R);
+        b += adapter_at_bytes(K, R) + round_up_256((size_t)adapter_t_product_ksplit(M, K, Rpad) * (size_t)M * (size_t)Rpad * sizeof(float));
+    }
+    return b;
+}
 
 // Split of K over workgroups in the dense stage of the two-stage path: used when the 256 x 128 output tiles are
 // too few for the 256 CUs.  Needs N % 4 == 0 (vector stores of the reducing pass) and an even split of the 64-wide
@@ -143,6 +175,52 @@ inline int dense_ksplit(int64_t M, int64_t K, int64_t N) {
     int s = 1;
     while (s < 8 && tiles * s * 2 <= 256 && steps % (s * 2) == 0 && steps / (s * 2) >= 4) s *= 2;
     return s;
+}
+
+// fp32 elements from one slice of a split contraction's partial sums to the next
+#ifdef __HIPCC__
+__host__ __device__
+#endif
+inline int64_t splitk_slice(int64_t count) { return (count + 3) / 4 * 4; }
+
+// Output tile of the large-batch MFMA stage and its split of the contraction over workgroups (fp32 partial outputs
+// [ksplit, M, N], summed by splitk_reduce_kernel).  Kt = columns of X plus padded ranks.  The choice minimises a model of the
+// stage's time in microseconds.  A tile has the time of a k-step on a CU that is full of its workgroups (per workgroup: what
+// the matrix cores sustain on data at this chip's power), the time of one that is alone (latency, or the same where a CU
+// holds one), and what a workgroup spends outside its loop (first tiles, results; half of it hidden behind the loop of a
+// neighbour on the CU).  A split adds the partial sums' way through memory and one launch.  The figures are fitted to a sweep
+// of 21 layers from 512 to 28672 wide at 130 to 4096 tokens over all tiles and splits, where the choice costs 0.4 % on average
+// and 8 % at worst against the best tile.
+struct GemmPlan {
+    int mt, nt, ksplit;
+};
+inline GemmPlan gemm_plan(int64_t M, int64_t Kt, int64_t N) {
+    struct Tile {
+        int mt, nt, per_cu;
+        double step, alone, outside;
+    };
+    constexpr Tile kTiles[7] = {{256, 256, 1, 1.45, 1.45, 13.8},  {256, 224, 1, 1.32, 1.32, 13.0}, {128, 256, 2, 0.80, 0.81, 7.6},
+                                {128, 128, 2, 0.42, 0.53, 4.6},   {64, 256, 3, 0.45, 0.50, 5.1},   {64, 128, 4, 0.30, 0.44, 3.0},
+                                {64, 64, 4, 0.17, 0.41, 2.5}};
+    const int64_t steps = (Kt + 63) / 64;   // (one more when both parts end in half a step: of no account here)
+    GemmPlan best{64, 64, 1};
+    double best_cost = 1e300;
+    for (const Tile& t : kTiles) {
+        const int64_t tiles = ((M + t.mt - 1) / t.mt) * ((N + t.nt - 1) / t.nt);
+        const double outside = t.outside * (N % 8 != 0 ? 1.65 : 1.0);   // results that leave in pieces
+        for (int ks = 1; ks <= 16 && (ks == 1 || steps / ks >= 3); ks *= 2) {
+            const int64_t on_cu = (tiles * ks + 255) / 256, rounds = (on_cu + t.per_cu - 1) / t.per_cu;
+            const double full = (double)on_cu * t.step, lone = (double)rounds * t.alone;
+            double cost = (full > lone ? full : lone) * (double)((steps + ks - 1) / ks);
+            cost += (t.per_cu == 1 ? (double)rounds : 1.0 + (double)(on_cu - 1) * 0.46) * outside;
+            if (ks > 1) cost += 1.8 + (double)M * (double)N * (8 * ks + 2) * 0.08e-6;
+            if (cost < best_cost) {
+                best_cost = cost;
+                best = {t.mt, t.nt, ks};
+            }
+        }
+    }
+    return best;
 }
 
 // Row-tiled streaming path (one pass over the compressed weight, X shared by the 128 rows of a workgroup): batches of
@@ -225,13 +303,13 @@ inline size_t linear_workspace_bytes_without_table(int64_t M, int64_t K, int64_t
     if (uses_rowtile(M, K, N)) return rowtile_workspace_bytes(M, K, N, R);
     if (M <= kStreamMaxM)
         return R > 0 ? round_up_256((size_t)kStreamTSlices * (size_t)M * (size_t)adapter_rank_padded(R) * sizeof(float)) : 0;
-    size_t b = twostage_dense_offset(M, K, R);
-    if (uses_twostage(M, K)) {
-        b += round_up_256((size_t)N * (size_t)K * sizeof(uint16_t));
-        const int ks = dense_ksplit(M, K, N);
-        if (ks > 1) b += round_up_256((size_t)ks * (size_t)M * (size_t)N * sizeof(float));
-    }
-    return b;
+    if (!uses_twostage(M, K)) return twostage_dense_offset(M, K, R);
+    size_t b = frag_weight_offset(M, K, R) + frag_weight_bytes(K, N, R);
+    const int ks = gemm_plan(M, K + adapter_rank_padded(R), N).ksplit;
+    if (ks > 1) b += round_up_256((size_t)ks * (size_t)splitk_slice(M * N) * sizeof(float));
+    // more than the kernel without a decoded copy is given, by which the two are told apart
+    const size_t lean = twostage_dense_offset(M, K, R) + 256;
+    return b > lean ? b : lean;
 }
 
 // The least the layer runs with: where the preferred path decodes the weight into the workspace (large batches), the
@@ -286,6 +364,9 @@ hipError_t launch_gemm_2of4(const LinearArgs& args, hipStream_t stream, const Ti
 void launch_adapter_partial(const LinearArgs& args, hipStream_t stream);
 // the same into `partial` [kStreamTSlices, M, Rpad] (no slice table)
 void launch_adapter_partial_to(const LinearArgs& args, float* partial, hipStream_t stream);
+// T = X * A_cat in bf16 [M, Rpad] in one launch (see adapter_t_own_product)
+void launch_adapter_t_direct(const uint16_t* x, int64_t M, int64_t K, const uint16_t* a_cat, int R, int Rpad, uint16_t* t,
+                             hipStream_t stream);
 // T = X * A_cat in bf16 [M, Rpad] at the start of the workspace (every path with M > kStreamMaxM)
 void launch_adapter_t(const LinearArgs& args, hipStream_t stream);
 // x [M, K] bf16 times the transpose of a_t [Rpad, K] bf16 (Rpad % 32 == 0, K % 32 == 0), K split over `ksplit`
@@ -306,12 +387,15 @@ void launch_tall_product(const uint16_t* x, int64_t M, int64_t K, const uint16_t
 void launch_adapter_transpose(const uint16_t* a_cat, int64_t K, int R, int Rpad, uint16_t* a_t, hipStream_t stream);
 // out [C, R] = in [R, C]^T (bf16); R <= 65535 * 32
 void launch_transpose_bf16(const uint16_t* in, int64_t R, int64_t C, uint16_t* out, hipStream_t stream);
+// y [M, N] = x [M, K] * W^T (+ t [M, Rpad] * B_cat) with W and B_cat in operand order (salr_gemm.hip)
+void launch_frag_gemm(const uint16_t* x, int64_t M, int64_t K, int64_t N, const uint16_t* wf, const uint16_t* t, int Rpad,
+                      uint16_t* y, float* partial, const TimingEvents& ev, hipStream_t stream);
 // y [M, N] = x [M, K] * wd [N, K]^T (+ t [M, Rpad] * b_cat [R, N], pitch N, when R > 0): the dense MFMA stage with its
 // tile choice; K % 64 == 0; partial holds dense_ksplit(M, K, N) fp32 copies of y when that is > 1
 void launch_dense_stage(const uint16_t* x, int64_t M, int64_t K, int64_t N, const uint16_t* wd, const uint16_t* t,
                         const uint16_t* b_cat, int R, int Rpad, uint16_t* y, float* partial, const TimingEvents& ev,
                         hipStream_t stream);
-// out[i] = bf16(sum over z < ksplit of partial[z * count + i]); count % 4 == 0
+// out[i] = bf16(sum over z < ksplit of partial[z * splitk_slice(count) + i])
 void launch_splitk_reduce(const float* partial, int64_t count, int ksplit, uint16_t* out, hipStream_t stream);
 
 }  // namespace salr

@@ -1,0 +1,93 @@
+"""GPU parity of the large-batch path (decode into MFMA operand order, one dense MFMA stage) at the edges of its tiles, splits
+and layouts, against the fp64 CPU oracle.  Bar: max |Y - Y_ref| <= 1e-2 * max |Y_ref|."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import salr_workloads as wl
+from gpu_util import dev, to_dev_u16, to_dev_u32, y_to_f64
+
+pytestmark = pytest.mark.gpu
+
+REL_TOL = 1e-2
+
+
+def _check(M, K, N, R, density, quantised=False):
+    import paper_2601_16991_amd as salr
+    seed = M + 3 * K + 5 * N + R
+    rng = np.random.default_rng(seed)
+    x = wl.gaussian_bf16((M, K), 1.0, seed)
+    w = wl.gaussian_bf16((N, K), 0.02, seed + 1)
+    w[rng.random((N, K)) >= density] = 0
+    a = wl.gaussian_bf16((K, R), 0.05, seed + 2) if R else None
+    b = wl.gaussian_bf16((R, N), 0.05, seed + 3) if R else None
+    rb, rv, ro = oracle.encode(w)
+    dx, dbm, dro = to_dev_u16(x), to_dev_u32(rb), to_dev_u32(ro)
+    da, db = (to_dev_u16(a), to_dev_u16(b)) if R else (None, None)
+    print(f"[large batch] M{M} K{K} N{N} R{R} density {density} nf4 {quantised}", flush=True)
+    if quantised:
+        codes, scales = salr.nf4_quantize(to_dev_u16(rv))
+        q = salr.nf4_dequantize(codes, scales, rv.size)
+        w = oracle.decode(rb, q.cpu().numpy().view(np.uint16), ro, N, K)
+        y = salr.qsalr_linear(dx, dbm, codes, scales, dro, rv.size, da, db)
+    else:
+        y = salr.linear(dx, dbm, to_dev_u16(rv), dro, da, db)
+    torch.cuda.synchronize()
+    ref = oracle.linear(x, w, a, b)
+    err, scale = float(np.max(np.abs(y_to_f64(y) - ref))), float(np.max(np.abs(ref)))
+    assert err <= REL_TOL * scale, f"{err} > {REL_TOL} * {scale}"
+
+
+# contraction lengths: one half step, half steps after whole ones, pieces of 256 columns and their remainders; outputs that are
+# no multiple of 2, 4, 8; row counts around tile edges; ranks that leave whole, half and several steps of the rank dimension
+@pytest.mark.parametrize("M,K,N,R,density", [
+    (65, 32, 33, 0, 0.5), (129, 96, 17, 5, 0.5), (300, 160, 1, 3, 0.5), (131, 2720, 267, 24, 0.5), (257, 480, 130, 33, 0.3),
+    (200, 224, 1027, 64, 0.9), (1025, 288, 65, 65, 0.5), (130, 64, 2051, 8, 0.02), (513, 1056, 4, 96, 0.5), (70, 992, 255, 0, 1.0)])
+def test_ragged(M, K, N, R, density):
+    _check(M, K, N, R, density)
+
+
+# layers that take each output tile, with and without a split of the contraction
+@pytest.mark.parametrize("M,K,N,R", [
+    (150, 1024, 700, 16),        # 64 x 64
+    (150, 8192, 512, 16),        # 64 x 64 and 64 x 128, split sixteen ways
+    (600, 4096, 1100, 32),       # 64 x 128, split
+    (1100, 512, 2050, 130),      # 128 x 128
+    (520, 2048, 4104, 40),       # 128 x 256
+    (260, 4096, 4096, 32),       # split
+    (2050, 1024, 7300, 8),       # 256-row tiles
+    (1030, 96, 14400, 8)])
+def test_tiles(M, K, N, R):
+    _check(M, K, N, R, 0.5)
+
+
+@pytest.mark.parametrize("M,K,R", [(2100, 8192, 64), (1500, 8224, 130), (4100, 4128, 33)])
+def test_adapter_product_of_its_own(M, K, R):
+    """T = X A_cat large enough for the split-K product on the MFMA stage's kernel."""
+    _check(M, K, 96, R, 0.5)
+
+
+@pytest.mark.parametrize("M,K,N,R,density", [(129, 96, 40, 8, 0.8), (300, 2720, 130, 0, 0.8), (600, 512, 257, 32, 0.5), (129, 288, 64, 8, 1.0)])
+def test_quantised(M, K, N, R, density):
+    _check(M, K, N, R, density, quantised=True)
+
+
+def test_empty_and_full_rows():
+    """Rows without a single value next to full ones (a piece of 256 values spans 33 vectors off a vector boundary)."""
+    import paper_2601_16991_amd as salr
+    M, K, N = 140, 1280, 100
+    x = wl.gaussian_bf16((M, K), 1.0, 5)
+    w = wl.gaussian_bf16((N, K), 0.02, 6)
+    w[::3] = 0
+    w[1::3, :7] = 0
+    rb, rv, ro = oracle.encode(w)
+    y = salr.linear(to_dev_u16(x), to_dev_u32(rb), to_dev_u16(rv), to_dev_u32(ro), None, None)
+    torch.cuda.synchronize()
+    ref = oracle.linear(x, w, None, None)
+    assert float(np.max(np.abs(y_to_f64(y) - ref))) <= REL_TOL * float(np.max(np.abs(ref)))
+    w[:] = 0
+    rb, rv, ro = oracle.encode(w)
+    y = salr.linear(to_dev_u16(x), to_dev_u32(rb), torch.zeros(8, dtype=torch.int16, device=dev())[:0], to_dev_u32(ro), None, None)
+    torch.cuda.synchronize()
+    assert float(np.max(np.abs(y_to_f64(y)))) == 0.0
