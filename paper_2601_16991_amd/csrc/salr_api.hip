@@ -37,13 +37,32 @@ constexpr int64_t kMaxRank = 256;
 constexpr int64_t kMaxM = 65535LL * 64;           // gridDim.y of the generic kernel
 constexpr int64_t kMaxSvdDim = 65535LL * 32;      // gridDim.y of the transposing kernel
 
-// QSALR calls whose decode stage reads the 4-bit codes itself: the two-stage path (large batches); the workspace is then the
-// plain layer's.
+// QSALR calls for which no bf16 copy of the values is planned: the decode stage of the row-major two-stage path reads the 4-bit
+// codes (large batches, K % 64 == 0, rows of at most 524288 columns); the workspace is then the plain layer's.
 bool qsalr_decodes_codes(int64_t M, int64_t K, int64_t N, int64_t nnz) {
-    return nnz > 0 && K > 0 && salr::linear_takes_twostage(M, K, N);
+    return nnz > 0 && K > 0 && salr::linear_takes_twostage(M, K, N) && (K / 32 + 15) / 16 <= 1024;
 }
 
 }  // namespace
+
+namespace salr {
+
+// See salr_internal.hpp: the binding allocates these for calls that bring no workspace, or one of the size the queries tell.
+size_t linear_call_workspace_bytes(bool two_of_four, int64_t M, int64_t K, int64_t N, int64_t R) {
+    const size_t told = two_of_four ? salr_linear_2of4_workspace_bytes(M, K, N, R) : salr_linear_workspace_bytes(M, K, N, R);
+    if (M <= 0 || K <= 0 || N <= 0 || R < 0 || R > kMaxRank || K % 32 != 0) return told;
+    if (two_of_four && (uses_2of4_kernel(M, K, N) || uses_2of4_gemm(M, K, N))) return told;
+    return linear_workspace_bytes_fastest(M, K, N, R);
+}
+
+size_t qsalr_call_workspace_bytes(int64_t M, int64_t K, int64_t N, int64_t R, int64_t nnz) {
+    const size_t told = salr_qsalr_linear_workspace_bytes(M, K, N, R, nnz);
+    if (M <= 0 || K <= 0 || N <= 0 || R < 0 || R > kMaxRank || K % 32 != 0 || nnz <= 0 || linear_nf4_takes(M, K, N, nnz)) return told;
+    const size_t fastest = linear_workspace_bytes_fastest(M, K, N, R);
+    return fastest > told ? fastest : told;
+}
+
+}  // namespace salr
 
 extern "C" {
 
@@ -211,9 +230,10 @@ static salr_status_t linear_entry(const uint16_t* x, int64_t M, int64_t K, int64
     a.y = y;
     a.t = static_cast<uint16_t*>(workspace);
     a.lean = have < need;   // no room for the decoded copy: decode stage and MFMA stage in one kernel
+    a.room = have;
     a.slice_table = slice_table;
     if (codes != nullptr) {   // QSALR on the two-stage path (the caller has checked that this call takes it)
-        if (!salr::linear_takes_twostage(M, K, N) || a.lean) return SALR_ERR_UNSUPPORTED;
+        if (!salr::linear_takes_frag(M, K, N, R, have) && (!salr::linear_takes_twostage(M, K, N) || a.lean)) return SALR_ERR_UNSUPPORTED;
         a.values = nullptr; a.codes = codes; a.scales = scales; a.nnz = nnz;
     }
     if (!slice_table && have >= need && salr::builds_slice_table(M, K, N, R)) {   // none of the caller's: this call's own
@@ -255,7 +275,8 @@ salr_status_t salr_sparse_lowrank_linear_noalloc(const uint16_t* x, int64_t M, i
     if (need > SALR_NOALLOC_SCRATCH_BYTES) return SALR_ERR_CAPACITY;
     void* ws = nullptr;
     if (need > 0 && scratch_of_current_device(&ws) != hipSuccess) return SALR_ERR_HIP;
-    return salr_sparse_lowrank_linear(x, M, K, N, bitmap, values, row_offsets, a_cat, b_cat, R, y, ws, need, stream);
+    return salr_sparse_lowrank_linear(x, M, K, N, bitmap, values, row_offsets, a_cat, b_cat, R, y, ws,
+                                      need > 0 ? SALR_NOALLOC_SCRATCH_BYTES : 0, stream);
 }
 
 salr_status_t salr_nf4_quantize_values(const uint16_t* values, int64_t count, uint8_t* codes, uint16_t* scales, void* stream) {
@@ -310,15 +331,14 @@ salr_status_t salr_qsalr_linear(const uint16_t* x, int64_t M, int64_t K, int64_t
         hipError_t e = salr::launch_linear_nf4(a, codes, scales, nnz, static_cast<hipStream_t>(stream), salr::g_timing_events);
         return e == hipSuccess ? SALR_OK : SALR_ERR_HIP;
     }
-    if (qsalr_decodes_codes(M, K, N, nnz)) {   // large batches: the decode stage reads the codes
-        const size_t lw = salr::linear_workspace_bytes(M, K, N, R);
-        if (!workspace || workspace_bytes < lw) return SALR_ERR_CAPACITY;
+    const size_t planned = K > 0 ? salr_qsalr_linear_workspace_bytes(M, K, N, R, nnz) : salr::qsalr_values_bytes(nnz);
+    if (planned > 0 && (!workspace || workspace_bytes < planned)) return SALR_ERR_CAPACITY;
+    if (qsalr_decodes_codes(M, K, N, nnz) ||   // large batches: the decode stage reads the codes
+        (nnz > 0 && K > 0 && salr::linear_takes_frag(M, K, N, R, workspace_bytes))) {
         return linear_entry(x, M, K, N, bitmap, nullptr, row_offsets, nullptr, a_cat, b_cat, R, y, workspace, workspace_bytes, stream,
                             codes, scales, nnz);
     }
     const size_t vbytes = salr::qsalr_values_bytes(nnz);
-    const size_t need = vbytes + (K > 0 ? salr::linear_workspace_bytes(M, K, N, R) : 0);
-    if (need > 0 && (!workspace || workspace_bytes < need)) return SALR_ERR_CAPACITY;
     uint16_t* values = static_cast<uint16_t*>(workspace);
     if (K > 0 && nnz > 0) {
         hipError_t e = salr::launch_nf4_dequantize(codes, scales, nnz, values, static_cast<hipStream_t>(stream));

@@ -18,6 +18,8 @@ hipError_t launch_encode_index(const uint16_t* w, int64_t rows, int64_t cols, ui
                                uint32_t* nnz_host, hipStream_t stream);
 hipError_t launch_encode_values(const uint16_t* w, int64_t rows, int64_t cols, const uint32_t* bitmap, const uint32_t* row_offsets,
                                 uint16_t* values, int64_t capacity, hipStream_t stream);
+size_t linear_call_workspace_bytes(bool two_of_four, int64_t M, int64_t K, int64_t N, int64_t R);
+size_t qsalr_call_workspace_bytes(int64_t M, int64_t K, int64_t N, int64_t R, int64_t nnz);
 }  // namespace salr
 
 namespace {
@@ -190,8 +192,15 @@ PyObject* py_linear(PyObject*, PyObject* const* v, Py_ssize_t n) {
     }
     Workspace ws;
     ws.given(v[9]);
-    if (v[9] == Py_None && v[8] == Py_None)
-        ws.allocate(form == 2 ? salr_linear_2of4_workspace_bytes(l.M, l.K, l.N, l.R) : salr_linear_workspace_bytes(l.M, l.K, l.N, l.R), x);
+    if (v[8] == Py_None) {
+        // a workspace of the size the query tells, or more, means that memory for a decoded weight is there: where the fastest path
+        // wants a little more the call takes that from the allocator.  Less than the query tells is the caller's choice.
+        const size_t want = salr::linear_call_workspace_bytes(form == 2, l.M, l.K, l.N, l.R);
+        if (v[9] == Py_None ||
+            (ws.bytes < want && ws.bytes >= (form == 2 ? salr_linear_2of4_workspace_bytes(l.M, l.K, l.N, l.R)
+                                                       : salr_linear_workspace_bytes(l.M, l.K, l.N, l.R))))
+            ws.allocate(want, x);
+    }
     void* stream = stream_of(v[10]);
     salr_status_t st;
     {
@@ -227,7 +236,7 @@ PyObject* py_qsalr_linear(PyObject*, PyObject* const* v, Py_ssize_t n) {
     Workspace ws;
     ws.given(v[9]);
     if (v[9] == Py_None && v[8] == Py_None) {
-        const size_t need = salr_qsalr_linear_workspace_bytes(l.M, l.K, l.N, l.R, nnz);
+        const size_t need = salr::qsalr_call_workspace_bytes(l.M, l.K, l.N, l.R, nnz);
         ws.allocate(need < 256 ? 256 : need, x);
     }
     void* stream = stream_of(v[10]);

@@ -482,8 +482,8 @@ hipError_t launch_decode_frags(const LinearArgs& a, uint16_t* wf, uint16_t* af, 
 }
 
 void launch_frag_gemm(const uint16_t* x, int64_t M, int64_t K, int64_t N, const uint16_t* wf, const uint16_t* t, int Rpad,
-                      uint16_t* y, float* partial, const TimingEvents& ev, hipStream_t stream) {
-    const GemmPlan p = gemm_plan(M, K + Rpad, N);
+                      uint16_t* y, float* partial, size_t partial_room, const TimingEvents& ev, hipStream_t stream) {
+    const GemmPlan p = gemm_plan(M, K + Rpad, N, partial_room);
     const int m_tiles = (int)((M + p.mt - 1) / p.mt), n_tiles = (int)((N + p.nt - 1) / p.nt);
     const dim3 grid(gemm_grid(m_tiles * n_tiles * p.ksplit));
 #define SALR_GEMM_P(MI, NI, P)                                                                                                     \
@@ -542,7 +542,7 @@ static void launch_adapter_t_product(const uint16_t* x, int64_t M, int64_t K, co
     launch_splitk_reduce(partial, M * Rpad, ks, t, stream);
 }
 
-hipError_t launch_linear_twostage(const LinearArgs& a, hipStream_t stream, const TimingEvents& ev) {
+hipError_t launch_linear_frag(const LinearArgs& a, hipStream_t stream, const TimingEvents& ev) {
     const int Rpad = (int)adapter_rank_padded(a.R);
     uint16_t* wf = reinterpret_cast<uint16_t*>(reinterpret_cast<char*>(a.t) + frag_weight_offset(a.M, a.K, a.R));
     // T in one launch, or as a product of its own whose operand the decode launch lays out
@@ -553,9 +553,10 @@ hipError_t launch_linear_twostage(const LinearArgs& a, hipStream_t stream, const
     if (e != hipSuccess) return e;
     if (own)
         launch_adapter_t_product(a.x, a.M, a.K, reinterpret_cast<const uint16_t*>(af), Rpad, a.t,
-                                 reinterpret_cast<float*>(af + adapter_at_bytes(a.K, a.R)), stream);
-    float* partial = reinterpret_cast<float*>(reinterpret_cast<char*>(wf) + frag_weight_bytes(a.K, a.N, a.R));
-    launch_frag_gemm(a.x, a.M, a.K, a.N, wf, a.t, Rpad, a.y, partial, ev, stream);
+                                 reinterpret_cast<float*>(af + adapter_frag_bytes(a.K, a.R)), stream);
+    const size_t base = frag_base_bytes(a.M, a.K, a.N, a.R);
+    float* partial = reinterpret_cast<float*>(reinterpret_cast<char*>(a.t) + base);
+    launch_frag_gemm(a.x, a.M, a.K, a.N, wf, a.t, Rpad, a.y, partial, a.room - base, ev, stream);
     return hipGetLastError();
 }
 

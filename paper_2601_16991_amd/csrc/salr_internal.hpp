@@ -57,6 +57,7 @@ struct LinearArgs {
     uint16_t* y;
     uint16_t* t;  // workspace (see linear_workspace_bytes)
     bool lean = false;  // large batches: no room for a decoded copy of the weight, take the fused kernel
+    size_t room = 0;    // bytes of the workspace (large batches: see linear_takes_frag)
     const uint32_t* slice_table = nullptr;  // optional: the layer's slice table (see kSliceTableSlices)
     bool build_table = false;  // slice_table points into the workspace and the adapter pre-kernel fills it in this call
     // QSALR on the large-batch path: `values` is null and the decode stage reads these (nnz values, 4-bit codes)
@@ -96,8 +97,13 @@ constexpr int kStreamTSlices = 16;
 constexpr int kMaxRankPadded = 256;  // R <= 256: pitch of the T tile the streaming kernels keep in LDS
 
 // Large-batch path: M > kStreamMaxM decodes the weight once into scratch memory in MFMA operand order, then runs a dense
-// MFMA GEMM on it (k-steps of 64; offsets inside a tile of X are 32-bit).
-inline bool uses_twostage(int64_t M, int64_t K) { return M > kStreamMaxM && K >= 32 && K % 32 == 0 && K <= (1 << 22); }
+// MFMA GEMM on it (salr_gemm.hip; k-steps of 64, offsets inside a tile of X are 32-bit).  Wherever the call's workspace has room
+// for it: 300 x 2720 x 2731 36 us against 113 on the generic kernel, 2048 x 4096 x 14336 250 against 292 on the next one.
+inline bool uses_frag(int64_t M, int64_t K) { return M > kStreamMaxM && K >= 32 && K % 32 == 0 && K <= (1 << 22); }
+// The same in two stages with a row-major copy (salr_linear_twostage.hip), K % 64 == 0: what salr_linear_workspace_bytes sizes a
+// workspace for.  It needs less room (no rank blocks beside the weight), and is what a call with that much and no more
+// gets where the rank blocks do not fit; half as fast again as the kernel without a decoded copy.
+inline bool uses_twostage(int64_t M, int64_t K) { return M > kStreamMaxM && K >= 64 && K % 64 == 0; }
 // Decoded weight in operand order (salr_gemm.hip): 1 KB blocks of 16 rows x 32 columns, an even number along the columns,
 // and the rank blocks of B_cat (likewise) behind them.
 inline size_t frag_weight_bytes(int64_t K, int64_t N, int64_t R) {
@@ -113,6 +119,10 @@ inline size_t adapter_t_bytes(int64_t M, int64_t R) {
     return R > 0 ? round_up_256((size_t)M * (size_t)adapter_rank_padded(R) * sizeof(uint16_t)) : 0;
 }
 inline size_t adapter_at_bytes(int64_t K, int64_t R) {
+    return R > 0 ? round_up_256((size_t)K * (size_t)adapter_rank_padded(R) * sizeof(uint16_t)) : 0;
+}
+// A_cat^T in operand order (whole k-steps of 64)
+inline size_t adapter_frag_bytes(int64_t K, int64_t R) {
     return R > 0 ? round_up_256((size_t)((K + 63) / 64 * 64) * (size_t)adapter_rank_padded(R) * sizeof(uint16_t)) : 0;
 }
 // Rows of X per block of the large-batch T (salr_adapter_t.hpp), in tiles of 16: two where the blocks are many anyway (each
@@ -160,7 +170,7 @@ inline size_t frag_weight_offset(int64_t M, int64_t K, int64_t R) {   // T first
     size_t b = adapter_t_bytes(M, R);
     if (R > 0 && adapter_t_own_product(M, K, R)) {
         const int64_t Rpad = adapter_rank_padded(R);
-        b += adapter_at_bytes(K, R) + round_up_256((size_t)adapter_t_product_ksplit(M, K, Rpad) * (size_t)M * (size_t)Rpad * sizeof(float));
+        b += adapter_frag_bytes(K, R) + round_up_256((size_t)adapter_t_product_ksplit(M, K, Rpad) * (size_t)M * (size_t)Rpad * sizeof(float));
     }
     return b;
 }
@@ -190,11 +200,14 @@ inline int64_t splitk_slice(int64_t count) { return (count + 3) / 4 * 4; }
 // holds one), and what a workgroup spends outside its loop (first tiles, results; half of it hidden behind the loop of a
 // neighbour on the CU).  A split adds the partial sums' way through memory and one launch.  The figures are fitted to a sweep
 // of 21 layers from 512 to 28672 wide at 130 to 4096 tokens over all tiles and splits, where the choice costs 0.4 % on average
-// and 8 % at worst against the best tile.
+// and 8 % at worst against the best tile.  partial_room: bytes there are for the partial outputs.
 struct GemmPlan {
     int mt, nt, ksplit;
 };
-inline GemmPlan gemm_plan(int64_t M, int64_t Kt, int64_t N) {
+inline size_t gemm_partial_bytes(int64_t M, int64_t N, int ksplit) {
+    return ksplit > 1 ? round_up_256((size_t)ksplit * (size_t)splitk_slice(M * N) * sizeof(float)) : 0;
+}
+inline GemmPlan gemm_plan(int64_t M, int64_t Kt, int64_t N, size_t partial_room = SIZE_MAX) {
     struct Tile {
         int mt, nt, per_cu;
         double step, alone, outside;
@@ -208,7 +221,7 @@ inline GemmPlan gemm_plan(int64_t M, int64_t Kt, int64_t N) {
     for (const Tile& t : kTiles) {
         const int64_t tiles = ((M + t.mt - 1) / t.mt) * ((N + t.nt - 1) / t.nt);
         const double outside = t.outside * (N % 8 != 0 ? 1.65 : 1.0);   // results that leave in pieces
-        for (int ks = 1; ks <= 16 && (ks == 1 || steps / ks >= 3); ks *= 2) {
+        for (int ks = 1; ks <= 16 && (ks == 1 || (steps / ks >= 3 && gemm_partial_bytes(M, N, ks) <= partial_room)); ks *= 2) {
             const int64_t on_cu = (tiles * ks + 255) / 256, rounds = (on_cu + t.per_cu - 1) / t.per_cu;
             const double full = (double)on_cu * t.step, lone = (double)rounds * t.alone;
             double cost = (full > lone ? full : lone) * (double)((steps + ks - 1) / ks);
@@ -303,14 +316,35 @@ inline size_t linear_workspace_bytes_without_table(int64_t M, int64_t K, int64_t
     if (uses_rowtile(M, K, N)) return rowtile_workspace_bytes(M, K, N, R);
     if (M <= kStreamMaxM)
         return R > 0 ? round_up_256((size_t)kStreamTSlices * (size_t)M * (size_t)adapter_rank_padded(R) * sizeof(float)) : 0;
-    if (!uses_twostage(M, K)) return twostage_dense_offset(M, K, R);
-    size_t b = frag_weight_offset(M, K, R) + frag_weight_bytes(K, N, R);
-    const int ks = gemm_plan(M, K + adapter_rank_padded(R), N).ksplit;
-    if (ks > 1) b += round_up_256((size_t)ks * (size_t)splitk_slice(M * N) * sizeof(float));
-    // more than the kernel without a decoded copy is given, by which the two are told apart
-    const size_t lean = twostage_dense_offset(M, K, R) + 256;
-    return b > lean ? b : lean;
+    size_t b = twostage_dense_offset(M, K, R);
+    if (uses_twostage(M, K)) {
+        b += round_up_256((size_t)N * (size_t)K * sizeof(uint16_t));
+        const int ks = dense_ksplit(M, K, N);
+        if (ks > 1) b += round_up_256((size_t)ks * (size_t)M * (size_t)N * sizeof(float));
+    }
+    return b;
 }
+
+// The operand-order path's workspace: T, what a product of its own needs for it, the weight, then the partial outputs of a split
+// contraction as far as there is room (gemm_plan).
+inline size_t frag_base_bytes(int64_t M, int64_t K, int64_t N, int64_t R) {
+    return round_up_256(frag_weight_offset(M, K, R) + frag_weight_bytes(K, N, R));
+}
+inline bool linear_takes_frag(int64_t M, int64_t K, int64_t N, int64_t R, size_t room) {
+    return M > kStreamMaxM && !uses_rowtile(M, K, N) && uses_frag(M, K) && room >= frag_base_bytes(M, K, N, R);
+}
+// Workspace with which the layer is fastest: what is allocated for a call that brings none.
+inline size_t linear_workspace_bytes_fastest(int64_t M, int64_t K, int64_t N, int64_t R) {
+    const size_t told = linear_workspace_bytes(M, K, N, R);
+    if (M <= kStreamMaxM || N <= 0 || uses_rowtile(M, K, N) || !uses_frag(M, K)) return told;
+    const size_t b = frag_base_bytes(M, K, N, R) + gemm_partial_bytes(M, N, gemm_plan(M, K + adapter_rank_padded(R), N).ksplit);
+    return b > told ? b : told;
+}
+
+// The same for a call of the Python binding (two_of_four: salr_sparse_lowrank_linear_2of4), and for one of salr_qsalr_linear; at
+// least what the query functions of the boundary tell.
+size_t linear_call_workspace_bytes(bool two_of_four, int64_t M, int64_t K, int64_t N, int64_t R);
+size_t qsalr_call_workspace_bytes(int64_t M, int64_t K, int64_t N, int64_t R, int64_t nnz);
 
 // The least the layer runs with: where the preferred path decodes the weight into the workspace (large batches), the
 // fused kernel needs the adapter part only.
@@ -354,6 +388,7 @@ hipError_t launch_linear(const LinearArgs& args, hipStream_t stream);
 hipError_t launch_fill_zero(uint16_t* out, int64_t count, hipStream_t stream);
 hipError_t launch_linear_stream(const LinearArgs& args, hipStream_t stream, const TimingEvents& ev);
 hipError_t launch_linear_slice(const LinearArgs& args, hipStream_t stream, const TimingEvents& ev);
+hipError_t launch_linear_frag(const LinearArgs& args, hipStream_t stream, const TimingEvents& ev);
 hipError_t launch_linear_twostage(const LinearArgs& args, hipStream_t stream, const TimingEvents& ev);
 // the same shapes without a decoded copy of the weight: decode stage and MFMA stage in one kernel (K % 64 == 0)
 hipError_t launch_linear_tiled(const LinearArgs& args, hipStream_t stream, const TimingEvents& ev);
@@ -389,7 +424,7 @@ void launch_adapter_transpose(const uint16_t* a_cat, int64_t K, int R, int Rpad,
 void launch_transpose_bf16(const uint16_t* in, int64_t R, int64_t C, uint16_t* out, hipStream_t stream);
 // y [M, N] = x [M, K] * W^T (+ t [M, Rpad] * B_cat) with W and B_cat in operand order (salr_gemm.hip)
 void launch_frag_gemm(const uint16_t* x, int64_t M, int64_t K, int64_t N, const uint16_t* wf, const uint16_t* t, int Rpad,
-                      uint16_t* y, float* partial, const TimingEvents& ev, hipStream_t stream);
+                      uint16_t* y, float* partial, size_t partial_room, const TimingEvents& ev, hipStream_t stream);
 // y [M, N] = x [M, K] * wd [N, K]^T (+ t [M, Rpad] * b_cat [R, N], pitch N, when R > 0): the dense MFMA stage with its
 // tile choice; K % 64 == 0; partial holds dense_ksplit(M, K, N) fp32 copies of y when that is > 1
 void launch_dense_stage(const uint16_t* x, int64_t M, int64_t K, int64_t N, const uint16_t* wd, const uint16_t* t,

@@ -19,7 +19,7 @@
 // map keeps all m-tiles of one n-tile on the same XCD so the compressed rows are fetched into one L2.
 // Every m-tile decodes the weight tile again, and the decode instructions share the SIMDs with the MFMAs: with a
 // workspace for a decoded copy (2 N K bytes) the call decodes once into memory and runs a dense MFMA kernel instead
-// (salr_linear_twostage.hip), which is faster at every M > 64 that was measured.  This kernel is what runs when the
+// (salr_gemm.hip), which is faster at every M > 64 that was measured.  This kernel is what runs when the
 // caller gives the layer no room for that copy: the weight then never exists in dense form outside LDS.
 #include "salr_device.hpp"
 #include "salr_internal.hpp"
