@@ -18,9 +18,14 @@ __device__ __forceinline__ uint2 lds_read_tr4(const uint16_t* p) {
 constexpr int kTaPitch = 40;   // bf16 per row of an A tile [32 k][32 ranks]: 80 bytes, 16-byte aligned, rows spread over the banks
 constexpr int kTxPitch = 72;   // bf16 per row of an X tile [rows][64 k]: 144 bytes, the 16 rows of an operand on different banks
 
-template <int kMT, int kWaves>
+// How the small factor lies: kFactorVec, [K, R] with R % 8 == 0 (rows of whole 16-byte vectors); kFactorAny, [K, R] with any R
+// (element loads); kFactorRanks, [R, K] (B_cat in the backward pass).
+enum FactorLayout { kFactorVec, kFactorAny, kFactorRanks };
+
+template <int kMT, int kWaves, FactorLayout kFactor = kFactorVec>
 constexpr int adapter_t_lds_bytes() {
-    constexpr int tiles = kWaves * (32 * kTaPitch + 16 * kMT * kTxPitch) * 2, sums = kWaves * kMT * 2 * 256 * 4;
+    constexpr int factor = kFactor == kFactorRanks ? 32 * kTxPitch : 32 * kTaPitch;
+    constexpr int tiles = kWaves * (factor + 16 * kMT * kTxPitch) * 2, sums = kWaves * kMT * 2 * 256 * 4;
     return tiles > sums ? tiles : sums;
 }
 
@@ -29,18 +34,21 @@ constexpr int adapter_t_lds_bytes() {
 // memory and no second launch.  X is fetched as whole 128-byte lines (16 rows x 64 bytes per request, the MFMA operand as it
 // is, asks the L2 twice for every line, and with rows a multiple of 4 KB apart all from one channel) and turned into operands
 // through LDS; A_cat's rows go there as they lie and come back transposed.  kDepth steps in flight per wave.
-// R % 8 == 0 (A_cat's rows are whole 16-byte vectors).  `lds`: adapter_t_lds_bytes<kMT, kWaves>().
-template <int kMT, int kWaves, int kDepth>
+// A factor laid out as [R, K] is fetched and turned into operands as X is.  t_t (unless null) receives T transposed, [Rpad, M].
+// `lds`: adapter_t_lds_bytes<kMT, kWaves, kFactor>().
+template <int kMT, int kWaves, int kDepth, FactorLayout kFactor = kFactorVec>
 __device__ __forceinline__ void adapter_t_block(const uint16_t* __restrict__ x, int64_t M, int64_t K, const uint16_t* __restrict__ a_cat,
-                                                int R, int Rpad, uint16_t* __restrict__ t, int64_t rb, int rg, uint16_t* lds) {
+                                                int R, int Rpad, uint16_t* __restrict__ t, int64_t rb, int rg, uint16_t* lds,
+                                                uint16_t* __restrict__ t_t = nullptr) {
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int i16 = lane & 15, g = lane >> 4;
     const int64_t steps = (K + 63) >> 6;
     const int64_t m0 = rb * 16 * kMT;
-    uint16_t* a_tile = lds + wave * (32 * kTaPitch + 16 * kMT * kTxPitch);
-    uint16_t* x_tile = a_tile + 32 * kTaPitch;
+    constexpr int kFactorElems = kFactor == kFactorRanks ? 32 * kTxPitch : 32 * kTaPitch;
+    uint16_t* a_tile = lds + wave * (kFactorElems + 16 * kMT * kTxPitch);
+    uint16_t* x_tile = a_tile + kFactorElems;
     // X loader: lane l fetches segment l % 8 (16 bytes) of row l / 8 of every eight rows
     const int xseg = lane & 7;
     const uint16_t* xrow[2 * kMT];
@@ -51,7 +59,22 @@ __device__ __forceinline__ void adapter_t_block(const uint16_t* __restrict__ x, 
     }
     // A loader: lane l fetches eight ranks from 32 rg + 8 (l % 4) of row l / 4 of every sixteen
     const int arow = lane >> 2, acol = 32 * rg + 8 * (lane & 3);
-    auto load_a = [&](int64_t k) -> uint4 { return *reinterpret_cast<const uint4*>(a_cat + k * R + (acol < R ? acol : R - 8)); };
+    auto load_a = [&](int64_t k) -> uint4 {
+        if constexpr (kFactor == kFactorVec) {
+            return *reinterpret_cast<const uint4*>(a_cat + k * R + (acol < R ? acol : R - 8));
+        } else {   // ranks past R: any value, their columns are stored as zeros
+            uint32_t e[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) e[j] = a_cat[k * R + (acol + j < R ? acol + j : R - 1)];
+            return make_uint4(e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16), e[6] | (e[7] << 16));
+        }
+    };
+    const uint16_t* frow[4];   // kFactorRanks: loaded like X, ranks past R as the last one
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int r = 32 * rg + 8 * i + (lane >> 3);
+        frow[i] = a_cat + (int64_t)(r < R ? r : R - 1) * K + 8 * xseg;
+    }
     f32x4 acc[kMT][2];
 #pragma unroll
     for (int i = 0; i < kMT; ++i) acc[i][0] = acc[i][1] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -65,7 +88,10 @@ __device__ __forceinline__ void adapter_t_block(const uint16_t* __restrict__ x, 
 #pragma unroll
             for (int i = 0; i < 2 * kMT; ++i) xq[d][i] = *reinterpret_cast<const uint4*>(xrow[i] + k - (xseg >= 4 ? half : 0));
 #pragma unroll
-            for (int i = 0; i < 4; ++i) aq[d][i] = load_a(k + arow + 16 * i - (i >= 2 ? half : 0));
+            for (int i = 0; i < 4; ++i) {
+                if constexpr (kFactor == kFactorRanks) aq[d][i] = *reinterpret_cast<const uint4*>(frow[i] + k - (xseg >= 4 ? half : 0));
+                else aq[d][i] = load_a(k + arow + 16 * i - (i >= 2 ? half : 0));
+            }
         }
 #pragma unroll
         for (int d = 0; d < kDepth; ++d) {
@@ -75,10 +101,16 @@ __device__ __forceinline__ void adapter_t_block(const uint16_t* __restrict__ x, 
                 for (int i = 0; i < 2 * kMT; ++i)
                     *reinterpret_cast<uint4*>(x_tile + (8 * i + (lane >> 3)) * kTxPitch + 8 * xseg) = xq[d][i];
 #pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    if constexpr (kFactor == kFactorRanks) *reinterpret_cast<uint4*>(a_tile + (8 * i + (lane >> 3)) * kTxPitch + 8 * xseg) = aq[d][i];
+                }
+#pragma unroll
                 for (int h = 0; h < 2; ++h) {   // 32 columns each
                     if (h == 0 || (s << 6) + 32 < K) {   // wave-uniform
-                        *reinterpret_cast<uint4*>(a_tile + arow * kTaPitch + 8 * (lane & 3)) = aq[d][2 * h];
-                        *reinterpret_cast<uint4*>(a_tile + (arow + 16) * kTaPitch + 8 * (lane & 3)) = aq[d][2 * h + 1];
+                        if constexpr (kFactor != kFactorRanks) {
+                            *reinterpret_cast<uint4*>(a_tile + arow * kTaPitch + 8 * (lane & 3)) = aq[d][2 * h];
+                            *reinterpret_cast<uint4*>(a_tile + (arow + 16) * kTaPitch + 8 * (lane & 3)) = aq[d][2 * h + 1];
+                        }
                         __builtin_amdgcn_wave_barrier();   // LDS executes a wave's accesses in order
                         const uint16_t* col = a_tile + (8 * g + (i16 >> 2)) * kTaPitch + 4 * (i16 & 3);
                         bf16x8 xf[kMT];
@@ -87,8 +119,14 @@ __device__ __forceinline__ void adapter_t_block(const uint16_t* __restrict__ x, 
                             xf[i] = *reinterpret_cast<const bf16x8*>(x_tile + (16 * i + i16) * kTxPitch + 32 * h + 8 * g);
 #pragma unroll
                         for (int rt = 0; rt < 2; ++rt) {
-                            const uint2 lo = lds_read_tr4(col + 16 * rt), hi = lds_read_tr4(col + 4 * kTaPitch + 16 * rt);
-                            const bf16x8 b = as_bf16x8(make_uint4(lo.x, lo.y, hi.x, hi.y));
+                            uint4 bq;
+                            if constexpr (kFactor == kFactorRanks) {
+                                bq = *reinterpret_cast<const uint4*>(a_tile + (16 * rt + i16) * kTxPitch + 32 * h + 8 * g);
+                            } else {
+                                const uint2 lo = lds_read_tr4(col + 16 * rt), hi = lds_read_tr4(col + 4 * kTaPitch + 16 * rt);
+                                bq = make_uint4(lo.x, lo.y, hi.x, hi.y);
+                            }
+                            const bf16x8 b = as_bf16x8(bq);
 #pragma unroll
                             for (int i = 0; i < kMT; ++i) acc[i][rt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xf[i], b, acc[i][rt], 0, 0, 0);
                         }
@@ -115,7 +153,11 @@ __device__ __forceinline__ void adapter_t_block(const uint16_t* __restrict__ x, 
         const int l = idx & 63, e = (idx >> 6) & 3, rt = (idx >> 8) & 1, i = idx >> 9;
         const int64_t m = m0 + 16 * i + 4 * (l >> 4) + e;
         const int r = 32 * rg + 16 * rt + (l & 15);
-        if (m < M) t[m * Rpad + r] = r < R ? f32_to_bf16_rne(s) : (uint16_t)0;
+        if (m < M) {
+            const uint16_t v = r < R ? f32_to_bf16_rne(s) : (uint16_t)0;
+            t[m * Rpad + r] = v;
+            if (t_t != nullptr) t_t[(int64_t)r * M + m] = v;
+        }
     }
 }
 

@@ -400,15 +400,17 @@ hipError_t launch_decode(const uint32_t* bitmap, const uint16_t* values, const u
 }
 
 // ---------------------------------------------------------------------------------------------------
-// Decode into the TRANSPOSED dense matrix, out_t [cols, rows] (the backward pass contracts over the weight's rows and
-// wants them contiguous): the reconstruction rule of Sec. 3.3 as in the kernels above, with the transposition done in
-// LDS on the way out, so that the dense matrix crosses memory once instead of three times (decode, then read and
-// write again to transpose).  cols % 128 == 0, rows % 64 == 0.
-//   workgroup (b, z): rows 64 b .. 64 b + 63 (wave w the 16 rows 16 w ..), chunks [C z / ksl, C (z + 1) / ksl) of the
-//   C = cols / 128 chunks of 128 columns.  Per chunk lane (n = lane%16, g = lane/16) expands byte g of the four bitmap
-//   words of row n, as in the small-batch linear, and writes its 32 values into an LDS tile [128 columns][64 rows];
-//   after a barrier the 256 threads store the tile's rows, 128 bytes each, with 16-byte stores.
+// Decode of the TRANSPOSED weight (the backward pass contracts over the weight's rows) into MFMA operand order, block (f, nb) =
+// columns 16 f .. 16 f + 15 x rows 32 nb .. + 31 as described in salr_gemm.hip, with the rank blocks of A_cat behind those of
+// the weight: the reconstruction rule of Sec. 3.3 as in the kernels above, the transposition done in LDS on the way out, so
+// that the dense matrix crosses memory once.  cols % 32 == 0, rows % 64 == 0.
+//   the first a_wgs workgroups: A_cat's blocks, a 16-byte vector per thread;
+//   workgroup (b, z) of the others: rows 64 b .. 64 b + 63 (wave w the 16 rows 16 w ..), chunks [C z / ksl, C (z + 1) / ksl) of
+//   the C = ceil(cols / 128) chunks of 128 columns.  Per chunk lane (n = lane%16, g = lane/16) expands byte g of the four
+//   bitmap words of row n, as in the small-batch linear, and writes its 32 values into an LDS tile [128 columns][64 rows];
+//   after a barrier the 256 threads store the tile's sixteen blocks, two of them (2 KB) in a row each.
 //   The packed values of the next chunk are in flight while this one is expanded.
+// Bound by memory and by the LDS it transposes through: 4096 x 4096 in 17 us (33 MB out, 19 in).
 // ---------------------------------------------------------------------------------------------------
 constexpr int kDtWaves = 4;
 constexpr int kDtThreads = kDtWaves * 64;
@@ -422,10 +424,29 @@ struct DtStage {
     uint32_t off, nv, vbase;
 };
 
-__global__ __launch_bounds__(kDtThreads) void decode_transposed_kernel(const uint32_t* __restrict__ bitmap,
-                                                                       const uint16_t* __restrict__ values,
-                                                                       const uint32_t* __restrict__ row_offsets, int64_t rows,
-                                                                       int64_t cols, int ksl, uint16_t* __restrict__ out_t) {
+// kVec: rows of the bitmap are whole 16-byte vectors (cols % 128 == 0)
+template <bool kVec>
+__global__ __launch_bounds__(kDtThreads) void decode_transposed_frags_kernel(
+    const uint32_t* __restrict__ bitmap, const uint16_t* __restrict__ values, const uint32_t* __restrict__ row_offsets, int64_t rows,
+    int64_t cols, int ksl, const uint16_t* __restrict__ a_cat, int R, int r_blocks, int a_wgs, uint16_t* __restrict__ wf) {
+    const int64_t out_blocks = rows / 32 + r_blocks, frags = cols / 16;   // blocks per f, number of f
+    if ((int)blockIdx.x < a_wgs) {   // the same for the whole workgroup
+        const int64_t v = (int64_t)blockIdx.x * kDtThreads + threadIdx.x, block = v >> 6;
+        const int l = (int)v & 63, rb = (int)(block % r_blocks);
+        const int64_t f = block / r_blocks;
+        if (f >= frags) return;
+        const uint16_t* arow = a_cat + (16 * f + (l & 15)) * R;
+        uint32_t e[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const int r = 32 * rb + 8 * (l >> 4) + j;
+            const uint32_t q = arow[r < R ? r : R - 1];
+            e[j] = r < R ? q : 0u;
+        }
+        *reinterpret_cast<uint4*>(wf + (f * out_blocks + rows / 32 + rb) * 512 + 8 * l) =
+            make_uint4(e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16), e[6] | (e[7] << 16));
+        return;
+    }
     __shared__ __attribute__((aligned(16))) uint16_t tile[128 * kDtPitch];
     __shared__ __attribute__((aligned(16))) uint32_t slots[kDtWaves * 16 * kDtSlotDwords + 8];
     __shared__ uint32_t lut[kNibbleLutWords];
@@ -434,14 +455,25 @@ __global__ __launch_bounds__(kDtThreads) void decode_transposed_kernel(const uin
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n = lane & 15, g = lane >> 4;
-    const int64_t n0 = (int64_t)blockIdx.x * kDtRows;
+    const int64_t id = (int64_t)blockIdx.x - a_wgs, row_blocks = rows / kDtRows;
+    const int64_t n0 = id % row_blocks * kDtRows;
     const int64_t row = n0 + 16 * wave + n;
     const int64_t row_c = row;   // rows % 64 == 0: every row of the block exists
     const int64_t wpr = cols >> 5;
-    const int64_t chunks = wpr >> 2;
-    const int z = blockIdx.y;
+    const int64_t chunks = (wpr + 3) >> 2;
+    const int z = (int)(id / row_blocks);
     const int64_t c_begin = chunks * z / ksl, c_end = chunks * (z + 1) / ksl;   // the same for the whole workgroup
     const uint32_t* brow = bitmap + row_c * wpr;
+    auto load_chunk = [&](int64_t c) -> uint4 {   // words past the row are empty
+        if constexpr (kVec) return *reinterpret_cast<const uint4*>(brow + c * 4);
+        uint32_t q[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const uint32_t v = brow[4 * c + i < wpr ? 4 * c + i : wpr - 1];
+            q[i] = 4 * c + i < wpr ? v : 0u;
+        }
+        return make_uint4(q[0], q[1], q[2], q[3]);
+    };
     // nonzeros of the row left of the slice: the 4 lanes of a row share the words, 8 loads in flight each
     uint32_t cur = row_offsets[row_c];
     {
@@ -451,7 +483,7 @@ __global__ __launch_bounds__(kDtThreads) void decode_transposed_kernel(const uin
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
                 const int64_t c = c0 + g + 4 * i;
-                q[i] = *reinterpret_cast<const uint4*>(brow + (c < c_begin ? c : 0) * 4);
+                q[i] = load_chunk(c < c_begin ? c : 0);
             }
 #pragma unroll
             for (int i = 0; i < 8; ++i)
@@ -465,7 +497,7 @@ __global__ __launch_bounds__(kDtThreads) void decode_transposed_kernel(const uin
     uint32_t* slot = slots + (wave * 16 + n) * kDtSlotDwords;
     // chunks past the slice read its last chunk and count as empty (no conditional load in the stream)
     auto issue = [&](DtStage& st, int64_t c) {
-        uint4 bm = *reinterpret_cast<const uint4*>(brow + (c < c_end ? c : c_end - 1) * 4);
+        uint4 bm = load_chunk(c < c_end ? c : c_end - 1);
         const uint32_t keep = c < c_end ? 0xFFFFFFFFu : 0u;
         bm.x &= keep; bm.y &= keep; bm.z &= keep; bm.w &= keep;
         st.bm = bm;
@@ -474,8 +506,8 @@ __global__ __launch_bounds__(kDtThreads) void decode_transposed_kernel(const uin
         st.nv = len ? (st.off + len + 7u) >> 3 : 0u;
         st.vbase = cur >> 3;
         const uint32_t last = st.nv ? st.nv - 1u : 0u;
-        // an empty piece reads the bitmap instead (always mapped: cols >= 128 gives every row 16 bytes)
-        const uint4* vb = st.nv ? values128 + st.vbase : reinterpret_cast<const uint4*>(brow);
+        // an empty piece reads the output instead (always mapped, and not used)
+        const uint4* vb = st.nv ? values128 + st.vbase : reinterpret_cast<const uint4*>(wf);
         cur += len;
 #pragma unroll
         for (int i = 0; i < 3; ++i) {
@@ -520,13 +552,15 @@ __global__ __launch_bounds__(kDtThreads) void decode_transposed_kernel(const uin
                 issue(st[i], c + i + 2);
                 // barriers that wait for LDS traffic only: the requests of the next chunks stay in flight
                 asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");   // the tile is complete
-                const int64_t k0 = (c + i) * 128;
+                // vector l of block (f, nb): column 16 f + l % 16, rows 32 nb + 8 (l / 16) ..
+                const int64_t f0 = (c + i) * 8;
 #pragma unroll
                 for (int t = 0; t < 4; ++t) {
                     const int idx = tid + kDtThreads * t;
-                    const int kr = idx >> 3, v = idx & 7;
-                    *reinterpret_cast<uint4*>(out_t + (k0 + kr) * rows + n0 + 8 * v) =
-                        *reinterpret_cast<const uint4*>(tile + kr * kDtPitch + 8 * v);
+                    const int f = idx >> 7, nb = (idx >> 6) & 1, l = idx & 63;
+                    if (f0 + f < frags)
+                        *reinterpret_cast<uint4*>(wf + ((f0 + f) * out_blocks + n0 / 32 + nb) * 512 + 8 * l) =
+                            *reinterpret_cast<const uint4*>(tile + (16 * f + (l & 15)) * kDtPitch + 32 * nb + 8 * (l >> 4));
                 }
                 asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");   // the tile may be overwritten
             }
@@ -534,19 +568,20 @@ __global__ __launch_bounds__(kDtThreads) void decode_transposed_kernel(const uin
     }
 }
 
-bool decode_transposed_takes(int64_t rows, int64_t cols, const void* values, const void* out_t) {
-    return rows > 0 && rows % kDtRows == 0 && cols >= 128 && cols % 128 == 0 && (reinterpret_cast<uintptr_t>(values) & 15u) == 0 &&
-           (reinterpret_cast<uintptr_t>(out_t) & 15u) == 0;
-}
-
-hipError_t launch_decode_transposed(const uint32_t* bitmap, const uint16_t* values, const uint32_t* row_offsets, int64_t rows,
-                                    int64_t cols, uint16_t* out_t, hipStream_t stream) {
-    const int64_t blocks = (rows + kDtRows - 1) / kDtRows, chunks = cols / 128;
+hipError_t launch_decode_transposed_frags(const uint32_t* bitmap, const uint16_t* values, const uint32_t* row_offsets, int64_t rows,
+                                          int64_t cols, const uint16_t* a_cat, int R, uint16_t* wf, hipStream_t stream) {
+    const int64_t blocks = rows / kDtRows, chunks = (cols + 127) / 128;
     int64_t ksl = (1024 + blocks - 1) / blocks;   // about four workgroups per CU
     ksl = ksl < 1 ? 1 : (ksl > chunks ? chunks : ksl);
-    if (ksl > 65535) ksl = 65535;
-    hipLaunchKernelGGL(decode_transposed_kernel, dim3((unsigned)blocks, (unsigned)ksl), dim3(kDtThreads), 0, stream, bitmap, values,
-                       row_offsets, rows, cols, (int)ksl, out_t);
+    const int r_blocks = (R + 63) / 64 * 2;
+    const int64_t a_wgs = (cols / 16 * r_blocks * 64 + kDtThreads - 1) / kDtThreads;
+    const dim3 grid((unsigned)(a_wgs + blocks * ksl));
+    if (cols % 128 == 0)
+        hipLaunchKernelGGL(decode_transposed_frags_kernel<true>, grid, dim3(kDtThreads), 0, stream, bitmap, values, row_offsets, rows, cols,
+                           (int)ksl, a_cat, R, r_blocks, (int)a_wgs, wf);
+    else
+        hipLaunchKernelGGL(decode_transposed_frags_kernel<false>, grid, dim3(kDtThreads), 0, stream, bitmap, values, row_offsets, rows, cols,
+                           (int)ksl, a_cat, R, r_blocks, (int)a_wgs, wf);
     return hipGetLastError();
 }
 

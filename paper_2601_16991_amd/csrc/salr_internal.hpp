@@ -379,10 +379,10 @@ hipError_t launch_linear_nf4(const LinearArgs& args, const uint8_t* codes, const
 bool decode_nf4_takes(int64_t rows, int64_t cols, int64_t nnz, const void* codes, const void* out);
 hipError_t launch_decode_nf4(const uint32_t* bitmap, const uint8_t* codes, const uint16_t* scales, int64_t nnz,
                              const uint32_t* row_offsets, int64_t rows, int64_t cols, uint16_t* out, hipStream_t stream);
-// decode into the transposed dense matrix out_t [cols, rows] (cols a multiple of 128, 16-byte aligned buffers)
-bool decode_transposed_takes(int64_t rows, int64_t cols, const void* values, const void* out_t);
-hipError_t launch_decode_transposed(const uint32_t* bitmap, const uint16_t* values, const uint32_t* row_offsets, int64_t rows,
-                                    int64_t cols, uint16_t* out_t, hipStream_t stream);
+// the transpose of the weight in operand order, the rank blocks of A_cat [cols, R] (null with R == 0) behind it:
+// frag_weight_bytes(rows, cols, R) bytes (rows % 64 == 0, cols % 32 == 0)
+hipError_t launch_decode_transposed_frags(const uint32_t* bitmap, const uint16_t* values, const uint32_t* row_offsets, int64_t rows,
+                                          int64_t cols, const uint16_t* a_cat, int R, uint16_t* wf, hipStream_t stream);
 hipError_t launch_linear(const LinearArgs& args, hipStream_t stream);
 // count bf16 zeros (+0.0) at out
 hipError_t launch_fill_zero(uint16_t* out, int64_t count, hipStream_t stream);
@@ -404,18 +404,37 @@ void launch_adapter_t_direct(const uint16_t* x, int64_t M, int64_t K, const uint
                              hipStream_t stream);
 // T = X * A_cat in bf16 [M, Rpad] at the start of the workspace (every path with M > kStreamMaxM)
 void launch_adapter_t(const LinearArgs& args, hipStream_t stream);
-// x [M, K] bf16 times the transpose of a_t [Rpad, K] bf16 (Rpad % 32 == 0, K % 32 == 0), K split over `ksplit`
-// slices: bf16 t [M, Rpad] (one slice, !keep_fp32) or fp32 partial [ksplit, M, Rpad]
-// Products that contract over the rows of in [M, C] (M % 32 == 0): partial [ksplit][C][Rpad] fp32; tn_ksplit picks the
-// split of M (about four workgroups per CU, at least two steps of 32 rows each)
-inline int tn_ksplit(int64_t C, int64_t M) {
-    const int64_t blocks = (C + 63) / 64, steps = M / 32;
+// The two low-rank intermediates of the backward pass, bf16: job 0 is T' = in [M, C] * factor [R, C]^T, job 1 is T = in [M, C] *
+// factor [C, R]; each [M, Rpad] in t and, unless null, transposed [Rpad, M] in t_t.  A job whose `in` is null is left out.
+// C % 32 == 0.
+struct LowRankJob {
+    const uint16_t* in;
+    const uint16_t* factor;
+    int64_t C;
+    uint16_t* t;
+    uint16_t* t_t;
+};
+void launch_backward_t(const LowRankJob& dy_b, const LowRankJob& x_a, int64_t M, int R, hipStream_t stream);
+// Products that contract over the rows of in [M, C] (M % 32 == 0) against s_t [Rpad, M]: the adapter gradients, bf16, job 0 to
+// out [C, R], job 1 to out [R, C].  A job whose `out` is null is left out.  partial: room for ksplit fp32 slices
+// [C, Rpad] of each job; tn_ksplit picks the split of M (about four workgroups per CU over both jobs, at least two
+// steps of 32 rows each).
+struct RowProductJob {
+    const uint16_t* in;
+    const uint16_t* s_t;
+    int64_t C;
+    uint16_t* out;
+};
+inline int tn_ksplit(int64_t C0, int64_t M, int64_t C1 = 0) {
+    const int64_t blocks = (C0 + 63) / 64 + (C1 + 63) / 64, steps = M / 32;
     int s = 1;
     while (s < 64 && blocks * s * 2 <= 1024 && steps / (s * 2) >= 2) s *= 2;
     return s;
 }
-void launch_tall_tn(const uint16_t* in, int64_t M, int64_t C, const uint16_t* s_t, int Rpad, int ksplit, float* partial,
-                    hipStream_t stream);
+void launch_row_products(const RowProductJob& da, const RowProductJob& db, int64_t M, int R, int ksplit, float* partial,
+                         hipStream_t stream);
+// x [M, K] bf16 times the transpose of a_t [Rpad, K] bf16 (Rpad % 32 == 0, K % 32 == 0), K split over `ksplit`
+// slices: bf16 t [M, Rpad] (one slice, !keep_fp32) or fp32 partial [ksplit, M, Rpad]
 void launch_tall_product(const uint16_t* x, int64_t M, int64_t K, const uint16_t* a_t, int Rpad, int ksplit, uint16_t* t,
                          float* partial, bool keep_fp32, hipStream_t stream);
 // a_t [Rpad, K] = A_cat [K, R]^T, rows R .. Rpad - 1 zero

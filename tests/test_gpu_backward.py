@@ -79,6 +79,20 @@ def test_backward_input_gradient_only(M):
     _close(dx0, oracle.linear_backward(x, dy, w_hat, None, None)[0], f"dX, no adapters, M={M}")
 
 
+@pytest.mark.parametrize("M,K,N,ranks,keep", [(32, 32, 64, (1,), 1.0), (64, 224, 128, (33,), 0.9), (96, 416, 64, (7, 64), 0.05),
+                                             (1056, 160, 192, (12,), 0.5), (1024, 288, 64, (129,), 0.5)])
+def test_backward_edges_of_the_transposed_operand_order(M, K, N, ranks, keep):
+    """Rows that end inside a 128-column chunk, nearly full and nearly empty pieces, rank blocks of one and of several 64-rank
+    steps, ranks that are no whole vectors on one and on two row tiles per workgroup."""
+    x, dy, _, a_cat, b_cat = _problem(M, K, N, ranks, 5000 + M + K)
+    w_hat = oracle.mask_topk_rows(wl.gaussian_bf16((N, K), 0.02, 5001 + K), max(1, int(K * keep)))
+    rx, ra, rb_ = oracle.linear_backward(x, dy, w_hat, a_cat, b_cat)
+    dx, da, db = _run(x, dy, w_hat, a_cat, b_cat)
+    _close(dx, rx, "dX")
+    _close(da, ra, "dA")
+    _close(db, rb_, "dB")
+
+
 def test_backward_adapter_gradients_only():
     x, dy, w_hat, a_cat, b_cat = _problem(128, 256, 192, (24,), 3000)
     dx, da, db = _run(x, dy, w_hat, a_cat, b_cat, need_dx=False)
