@@ -91,3 +91,31 @@ def test_empty_and_full_rows():
     y = salr.linear(to_dev_u16(x), to_dev_u32(rb), torch.zeros(8, dtype=torch.int16, device=dev())[:0], to_dev_u32(ro), None, None)
     torch.cuda.synchronize()
     assert float(np.max(np.abs(y_to_f64(y)))) == 0.0
+
+
+@pytest.mark.parametrize("M,K,N,R", [(130, 256, 4096, 32), (300, 512, 528, 8), (150, 96, 300, 8), (129, 4096, 256, 16), (520, 2048, 4104, 0)])
+def test_every_workspace_size(M, K, N, R):
+    """The least workspace, the one the query tells and one with room for everything: each takes its own path through the
+    boundary, with the same result; bytes behind the size that was given stay as they were."""
+    import paper_2601_16991_amd as salr
+    seed = M + K + N
+    x, w = wl.gaussian_bf16((M, K), 1.0, seed), wl.gaussian_bf16((N, K), 0.02, seed + 1)
+    w[np.random.default_rng(seed).random((N, K)) >= 0.5] = 0
+    a, b = (wl.gaussian_bf16((K, R), 0.05, seed + 2), wl.gaussian_bf16((R, N), 0.05, seed + 3)) if R else (None, None)
+    rb, rv, ro = oracle.encode(w)
+    args = [to_dev_u16(x), to_dev_u32(rb), to_dev_u16(rv), to_dev_u32(ro), None if a is None else to_dev_u16(a),
+            None if b is None else to_dev_u16(b)]
+    ref = oracle.linear(x, w, a, b)
+    told = salr.salr_linear_workspace_bytes(M, K, N, R)
+    for size in (salr.salr_linear_workspace_bytes_min(M, K, N, R), told, 2 * told + 64 * M * N + (4 << 20)):
+        buf = torch.full((size + 4096,), 0x5A, dtype=torch.uint8, device=dev())
+        y = torch.empty((M, N), dtype=torch.int16, device=dev())
+        salr.salr_sparse_lowrank_linear(*args, y, buf[:size] if size else None)
+        torch.cuda.synchronize()
+        err = float(np.max(np.abs(y_to_f64(y) - ref)))
+        print(f"[large batch] M{M} K{K} N{N} R{R} workspace {size}: max|d| {err:.3e}", flush=True)
+        assert err <= REL_TOL * float(np.max(np.abs(ref)))
+        assert bool((buf[size:] == 0x5A).all())
+        y2 = salr.linear(*args, buf[:size] if size else None)
+        torch.cuda.synchronize()
+        assert float(np.max(np.abs(y_to_f64(y2) - ref))) <= REL_TOL * float(np.max(np.abs(ref)))
