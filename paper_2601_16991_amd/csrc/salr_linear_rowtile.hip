@@ -9,12 +9,15 @@
 //                16-byte loads, parked in the wave's LDS slot and expanded by the nibble rule of Sec. 3.3 straight
 //                into the B operand of a 16x16x32 bf16 MFMA;
 //   activations  the chunk's X tile [16 MT rows x 128 columns] is loaded ONCE per workgroup (one 16-byte vector per
-//                thread and 32 rows) S chunks ahead into registers, written to LDS one chunk ahead, and read from
+//                thread and 32 rows) ahead into registers, written to LDS one barrier ahead, and read from
 //                there by all eight waves as the A operand.  A wave of the small-batch kernel pulls all of X through the L2 for its 16 rows; here
 //                128 rows share one copy, so a layer of N rows moves N / 128 copies of X instead of N / 16.
 //                16-byte vectors of a row are stored at index v ^ (row % 16): the operand reads of a wave (16 rows,
 //                the same four vectors each) then cover every LDS bank equally.
-//   one barrier per chunk: it publishes the next X tile and retires the one just read.
+//   one barrier per chunk, or per four chunks up to 16 tokens (X tiles of 4 KB): it publishes the next tiles and retires those
+//                just read.  With the waves in step on every chunk of 16 tokens each waited for the slowest one's weights:
+//                16 x 4096 x 14336 34.7 -> 32.9 us a call, 16 x 8192 x 28672 96 -> 88.  At 17 to 32 tokens two chunks per
+//                barrier were no faster (32 x 4096 x 14336 36.3 both ways, 24 x 3072 x 8192 17.6 -> 18.4).
 //   adapters     slice 0 adds the rank steps after its loop: T = X A_cat (summed from the pre-kernel's split-K partials
 //                and rounded to bf16 once) sits in LDS where the X tiles were; every wave multiplies it with the
 //                B_cat columns of its own rows.
@@ -45,11 +48,8 @@ struct RowStage {
     uint32_t vbase;   // index of its first vector in `values`
 };
 
-// native vector types (a 16-byte and an 8-byte one) that the compiler keeps in registers
+// a native vector type that the compiler keeps in registers
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-template <bool kHalf> struct XUnitType { using type = u32x4; };
-template <> struct XUnitType<true> { using type = u32x2; };
 
 __device__ __forceinline__ uint32_t popc4(const uint4& q) { return __popc(q.x) + __popc(q.y) + __popc(q.z) + __popc(q.w); }
 
@@ -63,7 +63,11 @@ __global__ __launch_bounds__(kRtThreads, MT <= 4 ? 4 : 2) void linear_rowtile_ke
     const uint32_t* __restrict__ slice_table) {
     constexpr int kRows = 16 * MT;                                    // X rows of the tile (M padded)
     constexpr int kXsElems = kRows * kRtChunkCols;                    // bf16 elements of one X tile
-    __shared__ __attribute__((aligned(16))) uint16_t xs[2 * kXsElems];
+    constexpr int kBlock = MT == 1 ? 4 : 1;                           // X tiles per barrier
+    constexpr int kRing = kBlock == 1 ? S : 1;                        // blocks of X tiles in registers
+    constexpr int kRound = S > kBlock ? S : kBlock;                   // chunks per round of the loop
+    static_assert(kRound % S == 0 && kRound % (kBlock * kRing) == 0, "a round is whole rings");
+    __shared__ __attribute__((aligned(16))) uint16_t xs[2 * kBlock * kXsElems];
     __shared__ __attribute__((aligned(16))) uint32_t slots[kRtWaves * 16 * kRtSlotDwords + 8];
     __shared__ uint32_t lut_all[kRtWaves][kNibbleLutWords];  // one copy per wave: filled and used wave-synchronously
 
@@ -99,37 +103,37 @@ __global__ __launch_bounds__(kRtThreads, MT <= 4 ? 4 : 2) void linear_rowtile_ke
 #pragma unroll
     for (int i = 0; i < S; ++i) bmq[i] = load_bitmap_chunk(c_begin + i);
 
-    // ---- X tile loader: every thread moves kXPer units of the tile (16 bytes; 8 bytes with one m-tile, where the
-    // tile has only 256 vectors for 512 threads): unit idx = tid + kRtThreads j belongs to tile row idx / units-per-row
-    using XUnit = typename XUnitType<MT == 1>::type;
-    constexpr int kUnitElems = sizeof(XUnit) / 2;                 // bf16 elements per unit
-    constexpr int kUnitsPerRow = kRtChunkCols / kUnitElems;
-    constexpr int kXPer = kRows * kUnitsPerRow / kRtThreads;     // units per thread
-    static_assert(kXPer * kRtThreads == kRows * kUnitsPerRow, "the threads cover the tile exactly");
+    // ---- X loader: every thread moves kXPer 16-byte units of a block of kBlock tiles
+    constexpr int kXPer = kBlock * kRows * 16 / kRtThreads;
+    static_assert(kXPer * kRtThreads == kBlock * kRows * 16, "the threads cover the block exactly");
     const uint16_t* xsrc[kXPer];
-    int xdst[kXPer];
+    int xdst[kXPer], xtile[kXPer];
 #pragma unroll
     for (int j = 0; j < kXPer; ++j) {
         const int idx = tid + kRtThreads * j;
-        const int r = idx / kUnitsPerRow, e = (idx % kUnitsPerRow) * kUnitElems;   // row, first element of the unit
-        const int v = e >> 3;                                                      // its 16-byte vector
-        xsrc[j] = x + (int64_t)(r < M ? r : M - 1) * K + e;   // rows past M repeat row M-1; never stored
-        xdst[j] = r * kRtChunkCols + 8 * (v ^ (r & 15)) + (e & 7);
+        const int v = idx % 16;
+        xtile[j] = kBlock == 1 ? 0 : idx / (16 * kRows);
+        const int r = idx / 16 - xtile[j] * kRows;
+        xsrc[j] = x + (int64_t)(r < M ? r : M - 1) * K + 8 * v;   // rows past M repeat row M-1; never stored
+        xdst[j] = xtile[j] * kXsElems + r * kRtChunkCols + 8 * (v ^ (r & 15));
     }
-    // tile j of the slice waits in register set j % S from S chunks before it is read until it is written to LDS
-    XUnit xring[S][kXPer];
-    auto load_x = [&](XUnit (&xr)[kXPer], int64_t c) {
-        const int64_t cc = c < c_end ? c : c_end - 1;   // past the slice: reload its last tile (its weights count as zero)
+    // block j of the slice waits in register set j % kRing until it is written to LDS
+    u32x4 xring[kRing][kXPer];
+    auto load_x = [&](u32x4 (&xr)[kXPer], int64_t c) {   // the block that starts at chunk c
 #pragma unroll
-        for (int j = 0; j < kXPer; ++j) xr[j] = *reinterpret_cast<const XUnit*>(xsrc[j] + cc * kRtChunkCols);
+        for (int j = 0; j < kXPer; ++j) {
+            const int64_t ct = kBlock == 1 ? c : c + xtile[j];
+            const int64_t cc = ct < c_end ? ct : c_end - 1;   // past the slice: its last tile (not read)
+            xr[j] = *reinterpret_cast<const u32x4*>(xsrc[j] + cc * kRtChunkCols);
+        }
     };
-    auto store_x = [&](const XUnit (&xr)[kXPer], int buf) {
+    auto store_x = [&](const u32x4 (&xr)[kXPer], int buf) {
 #pragma unroll
-        for (int j = 0; j < kXPer; ++j) *reinterpret_cast<XUnit*>(&xs[buf * kXsElems + xdst[j]]) = xr[j];
+        for (int j = 0; j < kXPer; ++j) *reinterpret_cast<u32x4*>(&xs[buf * kBlock * kXsElems + xdst[j]]) = xr[j];
     };
     if (c_begin < c_end) {
 #pragma unroll
-        for (int d = 0; d < S; ++d) load_x(xring[d], c_begin + d);
+        for (int d = 0; d < kRing; ++d) load_x(xring[d], c_begin + kBlock * d);
     }
 
     // B operand of the first rank step (Sec. 3.2): lane (n, g) holds B_cat[8 g + j][row], j = 0..7
@@ -242,40 +246,50 @@ __global__ __launch_bounds__(kRtThreads, MT <= 4 ? 4 : 2) void linear_rowtile_ke
             bmq[i] = load_bitmap_chunk(c_begin + i + S);
         }
         store_x(xring[0], 0);
-        load_x(xring[0], c_begin + S);
+        load_x(xring[0], c_begin + kBlock * kRing);
         __syncthreads();
         int buf = 0;
         int64_t c = c_begin;
-        // Rounds of S chunks whose prefetches all lie inside the slice run without a condition: with no load of the
+        // Rounds whose prefetches all lie inside the slice run without a condition: with no load of the
         // round conditional the compiler counts the requests younger than the one a wave waits for and leaves them in
         // flight (behind a branch it waits for everything).
-        for (; c + 2 * S <= c_end; c += S) {
+        for (; c + kRound + S <= c_end; c += kRound) {
 #pragma unroll
-            for (int i = 0; i < S; ++i) {
-                consume(st[i], xs + buf * kXsElems);
-                issue(st[i], bmq[i]);
-                bmq[i] = load_bitmap_chunk(c + i + 2 * S);
-                // tile c + i + 1 into the buffer read one chunk ago (all waves are past that barrier)
-                store_x(xring[(i + 1) % S], buf ^ 1);
-                load_x(xring[(i + 1) % S], c + i + 1 + S);
-                __syncthreads();    // publishes tile c + i + 1, retires tile c + i
-                buf ^= 1;
-            }
-        }
-        // the last rounds: nothing is requested past the slice
-        for (; c < c_end; c += S) {
-#pragma unroll
-            for (int i = 0; i < S; ++i) {
-                if (c + i < c_end) {   // the same for the whole workgroup
-                    consume(st[i], xs + buf * kXsElems);
-                    if (c + i + S < c_end) issue(st[i], bmq[i]);
-                    if (c + i + 1 < c_end) store_x(xring[(i + 1) % S], buf ^ 1);
-                    if (c + i + 1 + S < c_end) load_x(xring[(i + 1) % S], c + i + 1 + S);
-                    __syncthreads();
+            for (int i = 0; i < kRound; ++i) {
+                consume(st[i % S], xs + (buf * kBlock + i % kBlock) * kXsElems);
+                issue(st[i % S], bmq[i % S]);
+                bmq[i % S] = load_bitmap_chunk(c + i + 2 * S);
+                if (i % kBlock == kBlock - 1) {
+                    // the next block into the buffer read one block ago (all waves are past that barrier)
+                    u32x4 (&xr)[kXPer] = xring[(i + 1) / kBlock % kRing];
+                    store_x(xr, buf ^ 1);
+                    load_x(xr, c + i + 1 + kBlock * kRing);
+                    __syncthreads();    // publishes the next block, retires this one
                     buf ^= 1;
                 }
             }
         }
+        // the last rounds: nothing is requested past the slice
+        for (; c < c_end; c += kRound) {
+#pragma unroll
+            for (int i = 0; i < kRound; ++i) {
+                if (c + i < c_end) {   // the same for the whole workgroup
+                    consume(st[i % S], xs + (buf * kBlock + i % kBlock) * kXsElems);
+                    if (c + i + S < c_end) {
+                        issue(st[i % S], bmq[i % S]);
+                        if constexpr (kRound > S) bmq[i % S] = load_bitmap_chunk(c + i + 2 * S);   // else these are the last two rounds
+                    }
+                    if (i % kBlock == kBlock - 1 && c + i + 1 < c_end) {
+                        u32x4 (&xr)[kXPer] = xring[(i + 1) / kBlock % kRing];
+                        store_x(xr, buf ^ 1);
+                        if (c + i + 1 + kBlock * kRing < c_end) load_x(xr, c + i + 1 + kBlock * kRing);
+                        __syncthreads();
+                        buf ^= 1;
+                    }
+                }
+            }
+        }
+        __syncthreads();   // the X tiles are retired
     }
 
     // ---- adapter k-steps (Sec. 3.2): A operand = T rows from LDS, B operand = B_cat columns of this wave's rows

@@ -422,3 +422,12 @@ def test_large_batch_calls_back_to_back_share_a_workspace():
     # and against the oracle once
     x, w, a_cat, b_cat = probs[0]
     _assert_close(y_to_f64(ys[0]), oracle.linear(x, w, a_cat, b_cat), "back to back, call 0")
+
+
+@pytest.mark.parametrize("M,K,N,ranks", [(16, 640, 8192, (8,)), (9, 896, 8200, ()), (13, 1152, 8192, (4,)), (16, 128, 8192, (3,)),
+                                        (10, 4096, 8193, (16,))])
+def test_row_tiled_blocks_of_four_tiles(M, K, N, ranks):
+    """9 to 16 tokens on layers of 8192 rows and more: slices of 1, 5, 7 and 9 chunks (a last block of X tiles that is not
+    whole), and K in one slice."""
+    x, w, a_cat, b_cat = _problem(M, K, N, ranks, 9000 + M + K)
+    _assert_close(_run(x, w, a_cat, b_cat), oracle.linear(x, w, a_cat, b_cat), f"blocks M{M} K{K} N{N}")
