@@ -395,6 +395,13 @@ void launch_adapter_t(const LinearArgs& a, hipStream_t stream) {
         launch_splitk_reduce(partial, a.M * Rpad, kStreamTSlices, a.t, stream);
         return;
     }
+    // One launch and no partial sums where X is read once (ranks up to 32).  2:4 calls: 4096 x 2048 x 8192 135.8 -> 127.4 us,
+    // 1500 x 8192 x 8192 178.4 -> 175.3; at rank 64 it reads X twice and 4096 x 4096 x 8192 goes 235 -> 237.5; at 1024 rows and
+    // below the two launches above are level with it.
+    if (Rpad == 32 && !adapter_t_own_product(a.M, a.K, a.R)) {
+        launch_adapter_t_direct(a.x, a.M, a.K, a.a_cat, R, Rpad, a.t, stream);
+        return;
+    }
     launch_adapter_transpose(a.a_cat, a.K, R, Rpad, a_t, stream);
     const int ksplit = adapter_ksplit(a.M, a.K);
     launch_tall_product(a.x, a.M, a.K, a_t, Rpad, ksplit, a.t, partial, false, stream);
