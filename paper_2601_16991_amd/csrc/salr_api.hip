@@ -379,6 +379,7 @@ salr_status_t salr_sparse_lowrank_linear_2of4(const uint16_t* x, int64_t M, int6
     a.a_cat = a_cat; a.b_cat = b_cat; a.R = R;
     a.y = y;
     a.t = static_cast<uint16_t*>(workspace);
+    a.room = workspace ? workspace_bytes : 0;
     hipError_t e = small ? salr::launch_linear_2of4(a, static_cast<hipStream_t>(stream), salr::g_timing_events)
                          : salr::launch_gemm_2of4(a, static_cast<hipStream_t>(stream), salr::g_timing_events);
     return e == hipSuccess ? SALR_OK : SALR_ERR_HIP;

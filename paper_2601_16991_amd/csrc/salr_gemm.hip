@@ -30,6 +30,8 @@ namespace salr {
 
 constexpr int kGemmXcds = 8;
 
+typedef __bf16 bf16x16 __attribute__((ext_vector_type(16)));
+
 // c += a b on the matrix cores, c in the accumulation registers it is in.  Spelled out, because from the builtin the compiler
 // rotates the accumulators through other registers (four copies per MFMA in the loop below).  It does not know the
 // instruction's latency then: frag_gemm_kernel reads the accumulators only behind an s_nop of its own.
@@ -37,7 +39,14 @@ __device__ __forceinline__ void mfma_in_place(f32x4& c, const bf16x8& a, const b
     asm("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
 }
 
-template <int kMI, int kNI, int kWM, int kWN, int kStages, bool kPartial>
+// The same on the sparse matrix cores (a: four of eight columns and their positions, the half of `index` that kHalf names).
+template <int kHalf>
+__device__ __forceinline__ void smfmac_in_place(f32x4& c, const bf16x8& a, const bf16x16& b, uint32_t index) {
+    if constexpr (kHalf == 0) asm("v_smfmac_f32_16x16x64_bf16 %0, %1, %2, %3" : "+a"(c) : "v"(a), "v"(b), "v"(index));
+    else asm("v_smfmac_f32_16x16x64_bf16 %0, %1, %2, %3 abid:1" : "+a"(c) : "v"(a), "v"(b), "v"(index));
+}
+
+template <int kMI, int kNI, int kWM, int kWN, int kStages, bool kPartial, bool kSparse = false>
 __global__ __launch_bounds__(64 * kWM * kWN, 1) void frag_gemm_kernel(
     const uint16_t* __restrict__ x, int64_t M, int64_t K, int64_t N, const uint16_t* wf,
     const uint16_t* __restrict__ t, int Rpad, uint16_t* __restrict__ y, int m_tiles, int n_tiles, int ksplit,
@@ -70,7 +79,8 @@ __global__ __launch_bounds__(64 * kWM * kWN, 1) void frag_gemm_kernel(
 
     // k-steps of 64: x_steps over X (the weight is padded with a zero block when K % 64 is 32), then the ones over T;
     // this workgroup takes [s_begin, s_end)
-    const int x_steps = (int)((K + 63) >> 6), steps = x_steps + ((Rpad + 63) >> 6);
+    // (sparse weight: the steps over X only, T follows after the loop)
+    const int x_steps = (int)((K + 63) >> 6), steps = x_steps + (kSparse ? 0 : (Rpad + 63) >> 6);
     const int64_t blocks = 2 * (int64_t)steps;
     const int s_begin = (int)((int64_t)steps * kz / ksplit), s_end = (int)((int64_t)steps * (kz + 1) / ksplit);
 
@@ -132,48 +142,140 @@ __global__ __launch_bounds__(64 * kWM * kWN, 1) void frag_gemm_kernel(
     // the second half refills stage cur with step s + kStages.  The barrier between the halves publishes the next stage and
     // retires cur.  Requests are spread between the MFMAs (the scheduling fences keep them there): with one wave per SIMD
     // nothing else fills the matrix pipe.
-    bf16x8 w0[kNI], w1[kNI], x0[kMI], x1[kMI];
 #pragma unroll
     for (int p = 0; p < kStages; ++p) {
         const XSource src = x_source(s_begin + p);
 #pragma unroll
         for (int j = 0; j < kXLoads; ++j) fetch_x(src, p, j);
     }
+    if constexpr (!kSparse) {
+        bf16x8 w0[kNI], w1[kNI], x0[kMI], x1[kMI];
 #pragma unroll
-    for (int j = 0; j < kNI; ++j) w0[j] = load_w(s_begin, 0, j);
+        for (int j = 0; j < kNI; ++j) w0[j] = load_w(s_begin, 0, j);
 #pragma unroll
-    for (int j = 0; j < kNI; ++j) w1[j] = load_w(s_begin, 1, j);
-    asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
+        for (int j = 0; j < kNI; ++j) w1[j] = load_w(s_begin, 1, j);
+        asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
 #pragma unroll
-    for (int i = 0; i < kMI; ++i) x0[i] = load_x(0, 0, i);
-    int cur = 0;
-    for (int s = s_begin; s < s_end; ++s) {
-        const int nxt = cur + 1 == kStages ? 0 : cur + 1;
+        for (int i = 0; i < kMI; ++i) x0[i] = load_x(0, 0, i);
+        int cur = 0;
+        for (int s = s_begin; s < s_end; ++s) {
+            const int nxt = cur + 1 == kStages ? 0 : cur + 1;
 #pragma unroll
-        for (int j = 0; j < kNI; ++j) {
+            for (int j = 0; j < kNI; ++j) {
 #pragma unroll
-            for (int q = kMI * j / kNI; q < kMI * (j + 1) / kNI; ++q) x1[q] = load_x(cur, 1, q);
+                for (int q = kMI * j / kNI; q < kMI * (j + 1) / kNI; ++q) x1[q] = load_x(cur, 1, q);
 #pragma unroll
-            for (int i = 0; i < kMI; ++i) mfma_in_place(acc[i][j], w0[j], x0[i]);
-            __builtin_amdgcn_sched_barrier(0);
-            w0[j] = load_w(s + 1, 0, j);
+                for (int i = 0; i < kMI; ++i) mfma_in_place(acc[i][j], w0[j], x0[i]);
+                __builtin_amdgcn_sched_barrier(0);
+                w0[j] = load_w(s + 1, 0, j);
+            }
+            // X of step s + 1 has landed: since its last request (second half of step s - 2) there were three halves' W requests
+            // and kStages - 2 X tiles
+            asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((kStages - 2) * (kXLoads + 2 * kNI) + kNI) : "memory");
+            const XSource src = x_source(s + kStages);
+#pragma unroll
+            for (int j = 0; j < kNI; ++j) {
+#pragma unroll
+                for (int q = kXLoads * j / kNI; q < kXLoads * (j + 1) / kNI; ++q) fetch_x(src, cur, q);
+#pragma unroll
+                for (int q = kMI * j / kNI; q < kMI * (j + 1) / kNI; ++q) x0[q] = load_x(nxt, 0, q);
+#pragma unroll
+                for (int i = 0; i < kMI; ++i) mfma_in_place(acc[i][j], w1[j], x1[i]);
+                __builtin_amdgcn_sched_barrier(0);
+                w1[j] = load_w(s + 1, 1, j);
+            }
+            cur = nxt;
         }
-        // X of step s + 1 has landed: since its last request (second half of step s - 2) there were three halves' W requests
-        // and kStages - 2 X tiles
-        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((kStages - 2) * (kXLoads + 2 * kNI) + kNI) : "memory");
-        const XSource src = x_source(s + kStages);
+    } else {
+        // Sparse weight (256 x 256 and 256 x 224 tiles): one instruction per tile and step of 64 columns, half the steps' matrix time, so W is
+        // requested two steps ahead and X fragments are held for two steps.  A pair of
+        // steps shares its words of positions (low and high half).  Bound by the operands' way from the L2 (64 KB a step and CU):
+        // 2048 x 4096 x 14336 153 us, 167 with W one step ahead, 203 in the kernel that reads the packed format (gemm_2of4_kernel).
+        const int64_t pairs = (steps + 1) / 2, frag = sparse_frag_elems(K, Rpad);
+        auto pair_base = [&](int64_t pr, int j) -> const char* {
+            const int64_t f = f0 + j < f_last ? f0 + j : f_last;
+            return reinterpret_cast<const char*>(wf + f * frag) + (pr < pairs ? pr : pairs - 1) * (kSparsePairElems * 2);
+        };
+        auto load_ws = [&](int step, int j) -> bf16x8 {
+            return *reinterpret_cast<const bf16x8*>(pair_base(step >> 1, j) + (step & 1) * 1024 + lane_bytes);
+        };
+        auto load_index = [&](int step, int j) -> uint32_t {
+            return *reinterpret_cast<const uint32_t*>(pair_base(step >> 1, j) + 2048 + lane * 4);
+        };
+        auto load_xs = [&](int stage, int i) -> bf16x16 {   // columns 16 g .. 16 g + 15 of the step
+            const uint16_t* row = frag_base + stage * (kMT * 64) + 16 * i * 64;
+            const bf16x8 lo = *reinterpret_cast<const bf16x8*>(row + ((2 * g) ^ fsw) * 8), hi = *reinterpret_cast<const bf16x8*>(row + ((2 * g + 1) ^ fsw) * 8);
+            return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15);
+        };
+        bf16x8 wa[kNI], wb[kNI];
+        uint32_t index[kNI], index_next[kNI];
+        bf16x16 xa[kMI], xb[kMI];
 #pragma unroll
-        for (int j = 0; j < kNI; ++j) {
+        for (int j = 0; j < kNI; ++j) wa[j] = load_ws(0, j);
 #pragma unroll
-            for (int q = kXLoads * j / kNI; q < kXLoads * (j + 1) / kNI; ++q) fetch_x(src, cur, q);
+        for (int j = 0; j < kNI; ++j) wb[j] = load_ws(1, j);
 #pragma unroll
-            for (int q = kMI * j / kNI; q < kMI * (j + 1) / kNI; ++q) x0[q] = load_x(nxt, 0, q);
+        for (int j = 0; j < kNI; ++j) index[j] = load_index(0, j);
+        asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
 #pragma unroll
-            for (int i = 0; i < kMI; ++i) mfma_in_place(acc[i][j], w1[j], x1[i]);
-            __builtin_amdgcn_sched_barrier(0);
-            w1[j] = load_w(s + 1, 1, j);
+        for (int i = 0; i < kMI; ++i) xa[i] = load_xs(0, i);
+        int cur = 0;
+        constexpr int kFirst = kNI / 2;   // n-tiles before the barrier
+        auto step = [&](auto half, bf16x8 (&w)[kNI], const bf16x16 (&xc)[kMI], bf16x16 (&xn)[kMI], int s) {
+            constexpr int kHalf = decltype(half)::value;
+            const int nxt = cur + 1 == kStages ? 0 : cur + 1;
+            XSource src{};
+#pragma unroll
+            for (int j = 0; j < kNI; ++j) {
+                if (j == kFirst) {
+                    // X of step s + 1 has landed: since its last request (step s + 1 - kStages) there were at least the W
+                    // requests and X tiles of kStages - 2 steps, those after the barrier of the one before and kFirst of this
+                    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((kStages - 2) * (kXLoads + kNI) + kFirst) : "memory");
+                    src = x_source(s + kStages);
+                }
+                if (j >= kFirst) {
+                    constexpr int kRest = kNI - kFirst;
+                    const int jj = j - kFirst;
+#pragma unroll
+                    for (int q = kXLoads * jj / kRest; q < kXLoads * (jj + 1) / kRest; ++q) fetch_x(src, cur, q);
+#pragma unroll
+                    for (int q = kMI * jj / kRest; q < kMI * (jj + 1) / kRest; ++q) xn[q] = load_xs(nxt, q);
+                }
+#pragma unroll
+                for (int i = 0; i < kMI; ++i) smfmac_in_place<kHalf>(acc[i][j], w[j], xc[i], index[j]);
+                __builtin_amdgcn_sched_barrier(0);
+                w[j] = load_ws(s + 2, j);
+                if constexpr (kHalf == 0) index_next[j] = load_index(s + 2, j);
+                else index[j] = index_next[j];
+            }
+            cur = nxt;
+        };
+        int s = 0;
+        for (; s + 1 < s_end; s += 2) {
+            step(std::integral_constant<int, 0>{}, wa, xa, xb, s);
+            step(std::integral_constant<int, 1>{}, wb, xb, xa, s + 1);
         }
-        cur = nxt;
+        if (s < s_end) step(std::integral_constant<int, 0>{}, wa, xa, xb, s);
+        // T times B_cat: dense instructions on the same accumulators, both operands from memory
+        asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+        const uint16_t* bf = wf + pairs * kSparsePairElems;
+        for (int rb = 0; rb < Rpad / 32; ++rb) {
+            bf16x8 bq[kNI], tq[kMI];
+#pragma unroll
+            for (int j = 0; j < kNI; ++j) {
+                const int64_t f = f0 + j < f_last ? f0 + j : f_last;
+                bq[j] = *reinterpret_cast<const bf16x8*>(bf + f * frag + rb * 512 + lane * 8);
+            }
+#pragma unroll
+            for (int i = 0; i < kMI; ++i) {
+                const int64_t m = m0 + wm * 16 * kMI + 16 * i + i16;
+                tq[i] = *reinterpret_cast<const bf16x8*>(t + (m < M ? m : M - 1) * Rpad + rb * 32 + 8 * g);
+            }
+#pragma unroll
+            for (int j = 0; j < kNI; ++j)
+#pragma unroll
+                for (int i = 0; i < kMI; ++i) mfma_in_place(acc[i][j], bq[j], tq[i]);
+        }
     }
     // no request lands any more, every wave has read its last tile, the last MFMAs have written their results
     asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier\n\ts_nop 15\n\ts_nop 15" ::: "memory");
@@ -558,6 +660,101 @@ hipError_t launch_linear_frag(const LinearArgs& a, hipStream_t stream, const Tim
     float* partial = reinterpret_cast<float*>(reinterpret_cast<char*>(a.t) + base);
     launch_frag_gemm(a.x, a.M, a.K, a.N, wf, a.t, Rpad, a.y, partial, a.room - base, ev, stream);
     return hipGetLastError();
+}
+
+// Sparse operand order of a 2:4-masked weight, B_cat behind it: a permutation of the packed values and the bitmap, no decode.
+// Pair (f, p) is 16 weight rows x 128 columns: for each of its two steps of 64 columns 1 KB of values, lane (n, kb) = lane kb 16 +
+// n holding two sets of four (columns c .. c + 7 and c + 16 .. c + 23 with c = 32 (kb % 2) + 8 (kb / 2)), then a word per lane with
+// the positions of both steps (the index field of v_smfmac_f32_16x16x64_bf16 in the low and the high half; a last single step
+// leaves the second half of its pair unread).  Behind the pairs of an f the rank blocks of B_cat, dense, 32 ranks each.
+// Value offsets are clamped to the stored count: the 2:4 form is the caller's promise.  Bound by memory: 14336 x 4096, 66 MB in
+// and 66 out, 28.7 us.
+__global__ __launch_bounds__(256) void pack_2of4_kernel(const uint32_t* __restrict__ bitmap, const uint16_t* __restrict__ values,
+                                                        const uint32_t* __restrict__ row_offsets, const uint16_t* __restrict__ any16,
+                                                        int64_t N, int64_t K, int split, const uint16_t* __restrict__ b_cat, int R,
+                                                        int Rpad, uint16_t* __restrict__ wf) {
+    const int lane = lane_id(), n = lane & 15, kb = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t frags = (N + 15) / 16, id = (int64_t)blockIdx.x * 4 + wave;
+    const int64_t f = id / split;
+    const int z = (int)(id % split);
+    if (f >= frags) return;   // wave-uniform; the kernel has no barrier
+    const int64_t row = 16 * f + n < N ? 16 * f + n : N - 1;   // rows past N: copies of the last one, their outputs are dropped
+    const int64_t steps = K / 64, pairs = (steps + 1) / 2, frag = sparse_frag_elems(K, Rpad), wpr = K / 32;
+    const int64_t p_begin = pairs * z / split, p_end = pairs * (z + 1) / split;
+    uint16_t* out = wf + f * frag;
+    const uint32_t nnz = row_offsets[N], e_max = nnz >= 8u ? nnz - 8u : 0u;
+    const uint16_t* vsrc = nnz >= 8u ? values : any16;   // (a weight this small cannot meet the precondition)
+    const uint32_t first = row_offsets[row] + 16u * (uint32_t)(kb & 1);
+    const int half = 4 * (kb >> 1), sh = 8 * (kb >> 1);
+    const uint32_t* brow = bitmap + row * wpr + (kb & 1);
+    auto set = [&](int64_t step, uint32_t h) -> uint2 {   // four values of the vector of eight that holds them
+        uint32_t e = first + 32u * (uint32_t)step + 8u * h;
+        e = (e < e_max ? e : e_max) & ~7u;
+        return *reinterpret_cast<const uint2*>(vsrc + e + half);
+    };
+    auto code = [&](uint32_t word) -> uint32_t {
+        const uint32_t cw = index_codes_2of4(word);
+        return ((cw >> sh) & 0xFFu) | ((cw >> (sh + 8)) & 0xFF00u);
+    };
+    constexpr int kAhead = 4;
+    for (int64_t p0 = p_begin; p0 < p_end; p0 += kAhead) {
+        uint2 v[kAhead][4];
+        uint32_t b[kAhead][2];
+#pragma unroll
+        for (int d = 0; d < kAhead; ++d) {
+            const int64_t p = p0 + d < p_end ? p0 + d : p_end - 1;
+            const int64_t s1 = 2 * p + 1 < steps ? 2 * p + 1 : 2 * p;
+            v[d][0] = set(2 * p, 0);
+            v[d][1] = set(2 * p, 1);
+            v[d][2] = set(s1, 0);
+            v[d][3] = set(s1, 1);
+            b[d][0] = brow[4 * p];
+            b[d][1] = brow[2 * s1];
+        }
+#pragma unroll
+        for (int d = 0; d < kAhead; ++d) {
+            if (p0 + d < p_end) {   // wave-uniform
+                uint16_t* to = out + (p0 + d) * kSparsePairElems;
+                *reinterpret_cast<uint4*>(to + 8 * lane) = make_uint4(v[d][0].x, v[d][0].y, v[d][1].x, v[d][1].y);
+                *reinterpret_cast<uint4*>(to + 512 + 8 * lane) = make_uint4(v[d][2].x, v[d][2].y, v[d][3].x, v[d][3].y);
+                *reinterpret_cast<uint32_t*>(to + 1024 + 2 * lane) = code(b[d][0]) | (code(b[d][1]) << 16);
+            }
+        }
+    }
+    for (int rb = z; rb < Rpad / 32; rb += split) {
+        uint32_t e[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const int r = 32 * rb + 8 * kb + j;
+            const uint32_t q = b_cat[(int64_t)(r < R ? r : R - 1) * N + row];
+            e[j] = r < R ? q : 0u;
+        }
+        *reinterpret_cast<uint4*>(out + pairs * kSparsePairElems + rb * 512 + 8 * lane) =
+            make_uint4(e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16), e[6] | (e[7] << 16));
+    }
+}
+
+// y = x W^T + t B_cat on the sparse matrix cores: the weight into sparse operand order at wf (sparse_weight_bytes), then tiles of
+// 256 x 256 or 256 x 224.  K % 64 == 0.
+void launch_sparse_gemm(const LinearArgs& a, uint16_t* wf, bool narrow, const TimingEvents& ev, hipStream_t stream) {
+    const int R = (int)a.R, Rpad = (int)adapter_rank_padded(a.R);
+    const int64_t frags = (a.N + 15) / 16, pairs = (a.K / 64 + 1) / 2;
+    int64_t split = (8192 + frags - 1) / frags;   // about eight waves per SIMD, four pairs at least to a wave
+    if (split > pairs / 4) split = pairs / 4;
+    if (split < 1) split = 1;
+    hipLaunchKernelGGL(pack_2of4_kernel, dim3((unsigned)((frags * split + 3) / 4)), dim3(256), 0, stream, a.bitmap, a.values, a.row_offsets,
+                       a.x, a.N, a.K, (int)split, a.b_cat, R, Rpad, wf);
+    const int nt = narrow ? 224 : 256, m_tiles = (int)((a.M + 255) / 256), n_tiles = (int)((a.N + nt - 1) / nt);
+    const dim3 grid(gemm_grid(m_tiles * n_tiles));
+    float* none = nullptr;
+    const uint16_t* t = a.t;
+#define SALR_SPARSE(NI)                                                                                                              \
+    SALR_LAUNCH((frag_gemm_kernel<8, NI, 2, 2, 3, false, true>), grid, dim3(256), stream, ev, a.x, a.M, a.K, a.N, (const uint16_t*)wf, t, \
+                Rpad, a.y, m_tiles, n_tiles, 1, none)
+    if (narrow) SALR_SPARSE(7);
+    else SALR_SPARSE(8);
+#undef SALR_SPARSE
 }
 
 }  // namespace salr

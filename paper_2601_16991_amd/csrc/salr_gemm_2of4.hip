@@ -2,6 +2,8 @@
 // instruction whose sparse operand is the SALR format as it is (Sec. 3.3: packed values, bitmap), so that there is
 // neither a decode stage nor a dense copy of the weight, and the weight tile in LDS is half as wide as a dense one.
 //
+// From kSparseOrderMinM tokens on the 256-wide tiles run on the weight in sparse operand order instead (salr_gemm.hip).
+//
 //   workgroup   4 waves, output tile 128 (n) x 128 (m), k-step 64 columns; wave (wn, wm) owns 64 x 64 = 4 x 4 tiles
 //               of v_smfmac_f32_16x16x64_bf16 (one instruction per tile and step), D[n][m] (the sparse operand is the
 //               first one, so the weight rows are the rows of D);
@@ -33,14 +35,6 @@ constexpr int kG4Xcds = 8;
 typedef __bf16 bf16x16 __attribute__((ext_vector_type(16)));
 typedef uint32_t g4_u32x4 __attribute__((ext_vector_type(4)));   // native vectors: the compiler keeps arrays of them in registers
 typedef uint32_t g4_u32x2 __attribute__((ext_vector_type(2)));
-
-// per nibble with two set bits at p0 < p1: p0 | p1 << 2 (the index field of the sparse MFMA)
-__device__ __forceinline__ uint32_t g4_index_codes(uint32_t w) {
-    const uint32_t ones = 0x11111111u;
-    const uint32_t b0 = w & ones, b1 = (w >> 1) & ones, b2 = (w >> 2) & ones, b3 = (w >> 3) & ones;
-    const uint32_t n0 = b0 ^ ones, n1 = b1 ^ ones, n2 = b2 ^ ones;
-    return (n0 & b1) | ((n0 & n1) << 1) | ((b3 | n2) << 2) | ((b3 | b2) << 3);
-}
 
 // kWN x kWM waves; a wave owns kNI x kMJ tiles of 16 x 16: output tile 16 kNI kWN (n) x 16 kMJ kWM (m).
 template <int kWN, int kWM, int kNI, int kMJ>
@@ -130,7 +124,7 @@ __global__ __launch_bounds__(64 * kWN * kWM, kWN * kWM <= 4 ? 2 : 1) void gemm_2
                 *reinterpret_cast<g4_u32x2*>(&ws[buf][wdst[j][1]]) = g4_u32x2{wr[j].z, wr[j].w};
             }
         }
-        if (b_loader) bms[buf][2 * brow + bw] = g4_index_codes(br);   // the index fields of the word's four bytes, computed once per tile
+        if (b_loader) bms[buf][2 * brow + bw] = index_codes_2of4(br);   // the index fields of the word's four bytes, computed once per tile
     };
 
     f32x4 acc[kNI][kMJ];
@@ -249,7 +243,13 @@ hipError_t launch_gemm_2of4(const LinearArgs& a, hipStream_t stream, const Timin
     const int64_t m_tiles = (a.M + 255) / 256;
     const int64_t t256 = m_tiles * ((a.N + 255) / 256), t224 = m_tiles * ((a.N + 223) / 224);
     const int64_t cost256 = (t256 + 255) / 256 * 256, cost224 = (t224 + 255) / 256 * 224;
-    if (t256 >= kGemm2of4BigTilesMin && cost224 < cost256) launch_gemm_2of4_t<2, 4, 7, 4>(a, stream, ev);
+    // The weight in sparse operand order first (salr_gemm.hip): a pass over the weight, 0.49 us per million entries, for a matrix
+    // stage a quarter faster, worth it from about 1200 tokens.  2048 x 4096 x 14336 237 -> 197 us, 4096 x 4096 x 8192 239 -> 189,
+    // 3000 x 1024 x 8192 78 -> 73; 1024 x 4096 x 28672 181 -> 203.
+    const size_t offset = twostage_dense_offset(a.M, a.K, a.R);
+    if (t256 >= kGemm2of4BigTilesMin && a.M >= kSparseOrderMinM && a.room >= offset + sparse_weight_bytes(a.K, a.N, a.R))
+        launch_sparse_gemm(a, reinterpret_cast<uint16_t*>(reinterpret_cast<char*>(a.t) + offset), cost224 < cost256, ev, stream);
+    else if (t256 >= kGemm2of4BigTilesMin && cost224 < cost256) launch_gemm_2of4_t<2, 4, 7, 4>(a, stream, ev);
     else if (t256 >= kGemm2of4BigTilesMin) launch_gemm_2of4_t<2, 4, 8, 4>(a, stream, ev);
     else launch_gemm_2of4_t<2, 2, 4, 4>(a, stream, ev);
     return hipGetLastError();

@@ -110,6 +110,18 @@ inline size_t frag_weight_bytes(int64_t K, int64_t N, int64_t R) {
     return (size_t)((N + 15) / 16) * (size_t)((K + 63) / 64 + (R + 63) / 64) * 2048;
 }
 
+// A 2:4-masked weight in sparse operand order (pack_2of4_kernel): pairs of k-steps of 16 rows x 128 columns, 2048 bytes of values
+// and 256 of positions, then the rank blocks of B_cat.
+constexpr int64_t kSparsePairElems = 1152;
+constexpr int64_t kSparseOrderMinM = 1536;   // see launch_gemm_2of4
+#ifdef __HIPCC__
+__host__ __device__
+#endif
+inline int64_t sparse_frag_elems(int64_t K, int64_t Rpad) { return (K / 64 + 1) / 2 * kSparsePairElems + Rpad / 32 * 512; }
+inline size_t sparse_weight_bytes(int64_t K, int64_t N, int64_t R) {
+    return (size_t)((N + 15) / 16) * (size_t)sparse_frag_elems(K, adapter_rank_padded(R)) * 2;
+}
+
 inline size_t round_up_256(size_t b) { return (b + 255) / 256 * 256; }
 
 // Workspace layout of the large-batch paths (M > kStreamMaxM): T [M, Rpad] bf16, the transposed padded adapter
@@ -394,6 +406,7 @@ hipError_t launch_linear_twostage(const LinearArgs& args, hipStream_t stream, co
 hipError_t launch_linear_tiled(const LinearArgs& args, hipStream_t stream, const TimingEvents& ev);
 hipError_t launch_linear_rowtile(const LinearArgs& args, hipStream_t stream, const TimingEvents& ev);
 hipError_t launch_linear_2of4(const LinearArgs& args, hipStream_t stream, const TimingEvents& ev);
+void launch_sparse_gemm(const LinearArgs& args, uint16_t* wf, bool narrow, const TimingEvents& ev, hipStream_t stream);
 hipError_t launch_gemm_2of4(const LinearArgs& args, hipStream_t stream, const TimingEvents& ev);
 // split-K partials of T = X * A_cat (small batches): fp32 [kStreamTSlices, M, Rpad] at the start of the workspace
 void launch_adapter_partial(const LinearArgs& args, hipStream_t stream);

@@ -47,19 +47,6 @@ struct S4Stage {
     s4_u32x4 v0, v1;     // its 16 stored values
 };
 
-// Index bytes of the sparse MFMA for the four bytes of a bitmap word whose nibbles have two set bits each:
-// per nibble, code = p0 | p1 << 2 with p0 < p1 the positions of the set bits.
-__device__ __forceinline__ uint32_t index_codes_2of4(uint32_t w) {
-    const uint32_t ones = 0x11111111u;
-    const uint32_t b0 = w & ones, b1 = (w >> 1) & ones, b2 = (w >> 2) & ones, b3 = (w >> 3) & ones;
-    const uint32_t n0 = b0 ^ ones, n1 = b1 ^ ones, n2 = b2 ^ ones;
-    const uint32_t p0_lo = n0 & b1;        // p0 == 1
-    const uint32_t p0_hi = n0 & n1;        // p0 == 2
-    const uint32_t p1_lo = b3 | n2;        // p1 == 3 or p1 == 1
-    const uint32_t p1_hi = b3 | b2;        // p1 == 3 or p1 == 2
-    return p0_lo | (p0_hi << 1) | (p1_lo << 2) | (p1_hi << 3);
-}
-
 // MT m-tiles of 16 tokens (M <= 16 MT), S chunks in flight per wave.  K % 128 == 0.
 template <int MT, int S>
 __global__ __launch_bounds__(kS4Threads, MT <= 4 ? 4 : 2) void linear_2of4_kernel(

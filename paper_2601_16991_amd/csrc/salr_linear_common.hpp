@@ -68,4 +68,12 @@ __device__ __forceinline__ void slice_table_block(const uint32_t* __restrict__ b
     }
 }
 
+// per nibble with two set bits at p0 < p1: p0 | p1 << 2 (the index field of the sparse MFMA)
+__device__ __forceinline__ uint32_t index_codes_2of4(uint32_t w) {
+    const uint32_t ones = 0x11111111u;
+    const uint32_t b0 = w & ones, b1 = (w >> 1) & ones, b2 = (w >> 2) & ones, b3 = (w >> 3) & ones;
+    const uint32_t n0 = b0 ^ ones, n1 = b1 ^ ones, n2 = b2 ^ ones;
+    return (n0 & b1) | ((n0 & n1) << 1) | ((b3 | n2) << 2) | ((b3 | b2) << 3);
+}
+
 }  // namespace salr

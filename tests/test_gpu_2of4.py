@@ -203,3 +203,12 @@ def test_graph_replays(M, K, N):
         eager = salr.linear_2of4(x_dev, bm, v, rod, a, b)   # eager work between the replays, on another workspace
         torch.cuda.synchronize()
         assert torch.equal(eager.view(torch.int16), y.view(torch.int16)), f"replay {replay} differs from eager"
+
+
+@pytest.mark.parametrize("M,K,N,ranks", [(3500, 192, 3580, (5,)), (3900, 320, 3836, ()), (3585, 448, 3588, (70,)), (3841, 1024, 3844, (8,)),
+                                        (4000, 2112, 3200, (130,))])
+def test_sparse_operand_order(M, K, N, ranks):
+    """256- and 224-wide tiles on the sparse operand order: odd and even numbers of k-steps, fewer steps than stages of the X
+    ring, rank blocks of none to several 32-rank steps, rows and tokens past the last tile."""
+    x, w_hat, a_cat, b_cat = _problem(M, K, N, ranks, 7000 + M + K)
+    _assert_close(_run(x, w_hat, a_cat, b_cat), oracle.linear(x, w_hat, a_cat, b_cat), f"sparse order M{M} K{K} N{N}")
