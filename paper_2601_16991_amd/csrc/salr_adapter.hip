@@ -99,8 +99,8 @@ __global__ __launch_bounds__(256) void adapter_t_kernel(const uint16_t* __restri
 // out = bf16(sum over z of partial[z]), four elements per thread, in a fixed order; slices are
 // whole float4 apart (splitk_slice).  kZ threads share an
 // output, thread q taking z = q, q + kZ, ..; each has up to eight requests in flight (one after the other, 56 slices of a
-// [256, 32] sum took 15.9 us).
-template <int kZ>
+// [256, 32] sum took 15.9 us).  kCount: the number of slices where it is known (0: ksplit), so that no request is conditional.
+template <int kZ, int kCount = 0>
 __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restrict__ partial, int64_t count, int ksplit,
                                                             uint16_t* __restrict__ out) {
     constexpr int kOut = 256 / kZ;   // outputs (of four elements) per workgroup
@@ -110,14 +110,22 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restr
     const int64_t i = ((int64_t)blockIdx.x * kOut + c) * 4;
     float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
     if (i < count) {
-        for (int z0 = q; z0 < ksplit; z0 += 8 * kZ) {
-            float4 p[8];
+        if constexpr (kCount > 0) {
+            float4 p[kCount];
 #pragma unroll
-            for (int j = 0; j < 8; ++j)
-                if (z0 + kZ * j < ksplit) p[j] = *reinterpret_cast<const float4*>(partial + (int64_t)(z0 + kZ * j) * slice + i);
+            for (int z = 0; z < kCount; ++z) p[z] = *reinterpret_cast<const float4*>(partial + z * slice + i);
 #pragma unroll
-            for (int j = 0; j < 8; ++j)
-                if (z0 + kZ * j < ksplit) { s.x += p[j].x; s.y += p[j].y; s.z += p[j].z; s.w += p[j].w; }
+            for (int z = 0; z < kCount; ++z) { s.x += p[z].x; s.y += p[z].y; s.z += p[z].z; s.w += p[z].w; }
+        } else {
+            for (int z0 = q; z0 < ksplit; z0 += 8 * kZ) {
+                float4 p[8];
+#pragma unroll
+                for (int j = 0; j < 8; ++j)
+                    if (z0 + kZ * j < ksplit) p[j] = *reinterpret_cast<const float4*>(partial + (int64_t)(z0 + kZ * j) * slice + i);
+#pragma unroll
+                for (int j = 0; j < 8; ++j)
+                    if (z0 + kZ * j < ksplit) { s.x += p[j].x; s.y += p[j].y; s.z += p[j].z; s.w += p[j].w; }
+            }
         }
     }
     if constexpr (kZ > 1) {
@@ -143,12 +151,15 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restr
 }
 
 void launch_splitk_reduce(const float* partial, int64_t count, int ksplit, uint16_t* out, hipStream_t stream) {
-    if (ksplit > 8)
-        hipLaunchKernelGGL(splitk_reduce_kernel<4>, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, stream, partial, count,
-                           ksplit, out);
-    else
-        hipLaunchKernelGGL(splitk_reduce_kernel<1>, dim3((unsigned)((count + 1023) / 1024)), dim3(256), 0, stream, partial, count,
-                           ksplit, out);
+#define SALR_SUM(OUT, ...) \
+    hipLaunchKernelGGL((splitk_reduce_kernel<__VA_ARGS__>), dim3((unsigned)((count + 4 * (OUT)-1) / (4 * (OUT)))), dim3(256), 0, stream, \
+                       partial, count, ksplit, out)
+    if (ksplit > 8) SALR_SUM(64, 4);
+    else if (ksplit == 2) SALR_SUM(256, 1, 2);   // the splits of the layers' kernels are powers of two
+    else if (ksplit == 4) SALR_SUM(256, 1, 4);
+    else if (ksplit == 8) SALR_SUM(256, 1, 8);
+    else SALR_SUM(256, 1);
+#undef SALR_SUM
 }
 
 // a_t[r][k] = A_cat[k][r] for r < R, 0 for R <= r < Rpad: one thread per k and block of 8 ranks.
