@@ -94,26 +94,32 @@ __global__ __launch_bounds__(64 * kWM * kWN, 1) void frag_gemm_kernel(
         row_off[j] = (uint32_t)(m0 + r < M ? r : M - 1 - m0);
     }
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)Xs;
-    struct XSource {   // where the X tile of a step comes from (uniform) and this lane's place in it
-        const uint16_t* base;
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    struct XSource {   // where the X tile of a step comes from (uniform: a raw buffer of 2 GB) and this lane's place in it, in bytes
+        u32x4 buffer;
         uint32_t pitch, seg;
     };
+    // Second half of a half step: zeros, which a buffer load gives past the buffer's end (the rows of a tile lie below it, see
+    // kFragMaxColumns).  That half is multiplied by a zero block, and other columns of the row in its place would make every output
+    // of the row NaN where one of them is infinite.  Costs nothing; a condition in the k loop 1 to 3 %, per-lane addresses 1 %.
+    constexpr uint32_t kBufferBytes = 0x80000000u, kRawBuffer = 0x00020000u;
     auto x_source = [&](int step) -> XSource {
         const int sc = step < s_end ? step : s_end - 1;   // past the end: reload the last step (unused)
         const bool is_t = sc >= x_steps;
         const int64_t pitch = is_t ? Rpad : K;
         const int k0 = 64 * (is_t ? sc - x_steps : sc);
-        // second half of a half step (multiplied by the zero block, or not at all): any readable place of the row
-        return {(is_t ? t : x) + m0 * pitch + k0, (uint32_t)pitch, (uint32_t)(k0 + 8 * lseg < pitch ? lseg : lseg & 3)};
+        const uint64_t base = reinterpret_cast<uint64_t>((is_t ? t : x) + m0 * pitch + k0);
+        return {u32x4{(uint32_t)base, (uint32_t)(base >> 32) & 0xFFFFu, kBufferBytes, kRawBuffer}, (uint32_t)pitch * 2,
+                k0 + 8 * lseg < pitch ? 16u * lseg : kBufferBytes};
     };
     // Load j of an X tile straight into LDS: lane l lands on the wave's base + 16 l.  Assembly, so that the waits stay under
     // this kernel's control; its memory clobber also keeps the W loads on their side of it, which the wait counts rely on.
     auto fetch_x = [&](const XSource& src, int stage, int j) {
-        const uint32_t voff = (row_off[j] * src.pitch + 8 * src.seg) * 2;
+        const uint32_t voff = row_off[j] * src.pitch + src.seg;
         const uint32_t lds = __builtin_amdgcn_readfirstlane(lds0 + stage * (kMT * 128) + (wave + kWaves * j) * 1024);
-        asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
+        asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds"
                      :
-                     : "v"(voff), "s"(src.base), "s"(lds)
+                     : "v"(voff), "s"(src.buffer), "s"(lds)
                      : "memory", "m0");
     };
 

@@ -247,7 +247,7 @@ hipError_t launch_gemm_2of4(const LinearArgs& a, hipStream_t stream, const Timin
     // stage a quarter faster, worth it from about 1200 tokens.  2048 x 4096 x 14336 237 -> 197 us, 4096 x 4096 x 8192 239 -> 189,
     // 3000 x 1024 x 8192 78 -> 73; 1024 x 4096 x 28672 181 -> 203.
     const size_t offset = twostage_dense_offset(a.M, a.K, a.R);
-    if (t256 >= kGemm2of4BigTilesMin && a.M >= kSparseOrderMinM && a.room >= offset + sparse_weight_bytes(a.K, a.N, a.R))
+    if (t256 >= kGemm2of4BigTilesMin && a.M >= kSparseOrderMinM && a.K <= kFragMaxColumns && a.room >= offset + sparse_weight_bytes(a.K, a.N, a.R))
         launch_sparse_gemm(a, reinterpret_cast<uint16_t*>(reinterpret_cast<char*>(a.t) + offset), cost224 < cost256, ev, stream);
     else if (t256 >= kGemm2of4BigTilesMin && cost224 < cost256) launch_gemm_2of4_t<2, 4, 7, 4>(a, stream, ev);
     else if (t256 >= kGemm2of4BigTilesMin) launch_gemm_2of4_t<2, 4, 8, 4>(a, stream, ev);

@@ -97,9 +97,10 @@ constexpr int kStreamTSlices = 16;
 constexpr int kMaxRankPadded = 256;  // R <= 256: pitch of the T tile the streaming kernels keep in LDS
 
 // Large-batch path: M > kStreamMaxM decodes the weight once into scratch memory in MFMA operand order, then runs a dense
-// MFMA GEMM on it (salr_gemm.hip; k-steps of 64, offsets inside a tile of X are 32-bit).  Wherever the call's workspace has room
+// MFMA GEMM on it (salr_gemm.hip; k-steps of 64, the 256 rows of a tile of X lie within 2 GB).  Wherever the call's workspace has room
 // for it: 300 x 2720 x 2731 36 us against 113 on the generic kernel, 2048 x 4096 x 14336 250 against 292 on the next one.
-inline bool uses_frag(int64_t M, int64_t K) { return M > kStreamMaxM && K >= 32 && K % 32 == 0 && K <= (1 << 22); }
+constexpr int64_t kFragMaxColumns = 1 << 22;
+inline bool uses_frag(int64_t M, int64_t K) { return M > kStreamMaxM && K >= 32 && K % 32 == 0 && K <= kFragMaxColumns; }
 // The same in two stages with a row-major copy (salr_linear_twostage.hip), K % 64 == 0: what salr_linear_workspace_bytes sizes a
 // workspace for.  It needs less room (no rank blocks beside the weight), and is what a call with that much and no more
 // gets where the rank blocks do not fit; half as fast again as the kernel without a decoded copy.

@@ -1,0 +1,90 @@
+"""Infinite activations on the large-batch path: an output is infinite, NaN or finite exactly where the sums of the fp64 CPU oracle
+are.  One infinite entry of X makes infinities where the weights of its column are nonzero and NaN where they are zero (every
+kernel multiplies the zeros of the mask); nothing that a tile, a half step or a padded rank adds may turn those into NaN.  The
+finite outputs keep the usual bar, max |Y - Y_ref| <= 1e-2 * max |Y_ref|."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import salr_workloads as wl
+from gpu_util import to_dev_u16, to_dev_u32, y_to_f64
+
+pytestmark = pytest.mark.gpu
+
+REL_TOL = 1e-2
+INF, NINF = 0x7F80, 0xFF80
+
+
+def _kinds(a):
+    return np.isnan(a) * 3 + np.isposinf(a) + np.isneginf(a) * 2
+
+
+def _compare(got, ref, label):
+    assert np.array_equal(_kinds(got), _kinds(ref)), f"{label}: {int(np.sum(_kinds(got) != _kinds(ref)))} outputs of another kind"
+    fin = np.isfinite(ref)
+    if fin.any():   # (an infinite gradient entry reaches all of dA)
+        assert float(np.max(np.abs(got[fin] - ref[fin]))) <= REL_TOL * float(np.max(np.abs(ref[fin]))), label
+
+
+def _layer(M, K, N, R, seed):
+    """Weight and adapters whose entries in the infinite columns (the last 32) are not negative, so that the infinities of a sum agree."""
+    w = wl.gaussian_bf16((N, K), 0.02, seed + 1)
+    w[np.random.default_rng(seed).random((N, K)) >= 0.5] = 0
+    w[:, -32:] &= 0x7FFF
+    a = wl.gaussian_bf16((K, R), 0.05, seed + 2) if R else None
+    b = wl.gaussian_bf16((R, N), 0.05, seed + 3) & np.uint16(0x7FFF) if R else None
+    if R:
+        a[-32:] &= 0x7FFF
+    x = wl.gaussian_bf16((M, K), 1.0, seed)
+    x[3, K - 30], x[M - 1, K - 3] = INF, NINF
+    return x, w, a, b
+
+
+# contractions that end in half a step, with and without a split; rank dimensions that do (ranks up to 32, and 65 to 96); both
+HALF_STEPS = [(130, 96, 300, 0), (300, 160, 65, 64), (150, 8224, 40, 0), (200, 128, 300, 8), (200, 192, 70, 96), (300, 160, 65, 8),
+              (131, 2720, 267, 24), (1030, 96, 14400, 8), (1100, 544, 2050, 32)]
+
+
+@pytest.mark.parametrize("M,K,N,R", HALF_STEPS)
+def test_linear(M, K, N, R):
+    import paper_2601_16991_amd as salr
+    x, w, a, b = _layer(M, K, N, R, M + K + N + R)
+    rb, rv, ro = oracle.encode(w)
+    print(f"[non-finite] M{M} K{K} N{N} R{R}", flush=True)
+    y = salr.linear(to_dev_u16(x), to_dev_u32(rb), to_dev_u16(rv), to_dev_u32(ro), *((to_dev_u16(a), to_dev_u16(b)) if R else (None, None)))
+    torch.cuda.synchronize()
+    ref = oracle.linear(x, w, a, b)
+    assert np.isinf(ref[3]).any() and np.isinf(ref[M - 1]).any()
+    _compare(y_to_f64(y), ref, "y")
+
+
+def test_quantised():
+    import paper_2601_16991_amd as salr
+    M, K, N, R = 129, 96, 40, 8
+    x, w, a, b = _layer(M, K, N, R, 7)
+    rb, rv, ro = oracle.encode(w)
+    codes, scales = salr.nf4_quantize(to_dev_u16(rv))
+    q = salr.nf4_dequantize(codes, scales, rv.size)
+    print(f"[non-finite] quantised M{M} K{K} N{N} R{R}", flush=True)
+    y = salr.qsalr_linear(to_dev_u16(x), to_dev_u32(rb), codes, scales, to_dev_u32(ro), rv.size, to_dev_u16(a), to_dev_u16(b))
+    torch.cuda.synchronize()
+    _compare(y_to_f64(y), oracle.linear(x, oracle.decode(rb, q.cpu().numpy().view(np.uint16), ro, N, K), a, b), "y")
+
+
+@pytest.mark.parametrize("M,K,N,R", [(160, 256, 128, 8), (192, 288, 192, 96)])
+def test_backward(M, K, N, R):
+    """dX contracts over N (whole steps) and the ranks (half a step here)."""
+    import paper_2601_16991_amd as salr
+    x, w, a, b = _layer(M, K, N, R, M + K)
+    x = wl.gaussian_bf16((M, K), 1.0, 11)
+    a &= 0x7FFF
+    w &= 0x7FFF
+    dy = wl.gaussian_bf16((M, N), 1.0, 12)
+    dy[5, N - 7] = INF
+    rb, rv, ro = oracle.encode(w)
+    print(f"[non-finite] backward M{M} K{K} N{N} R{R}", flush=True)
+    got = salr.linear_backward(to_dev_u16(x), to_dev_u16(dy), to_dev_u32(rb), to_dev_u16(rv), to_dev_u32(ro), to_dev_u16(a), to_dev_u16(b))
+    torch.cuda.synchronize()
+    for name, g, ref in zip(("dx", "da", "db"), got, oracle.linear_backward(x, dy, w, a, b)):
+        _compare(y_to_f64(g), ref, name)
