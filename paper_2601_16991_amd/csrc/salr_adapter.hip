@@ -16,12 +16,13 @@ namespace salr {
 // times the X requests and their L2 traffic, not X, sets the pace), the four waves walk the slice in step.
 // kRT rank tiles of 16 columns per pass over the slice (all of them in one pass up to rank 128); 16x16x32 bf16
 // MFMAs; with more than one slice the fp32 partial results go to partial[z] and splitk_reduce_kernel adds
-// them in a fixed order.  Padding columns come out as exact zeros.  keep_fp32: the caller wants the fp32 sums
+// them in a fixed order.  Padding columns (from `ranks` on) are stored as zeros, which their products with an infinite entry of X
+// are not.  keep_fp32: the caller wants the fp32 sums
 // (the subspace iteration of the residual adapter), so even a single slice goes to partial[0].
 // ---------------------------------------------------------------------------------------------------
 template <int kMB, int kRT, int kDepth>
 __global__ __launch_bounds__(256) void adapter_t_kernel(const uint16_t* __restrict__ x, int64_t M, int64_t K,
-                                                        const uint16_t* __restrict__ a_t, int Rpad, int ksplit,
+                                                        const uint16_t* __restrict__ a_t, int Rpad, int ranks, int ksplit,
                                                         uint16_t* __restrict__ t, float* __restrict__ partial,
                                                         int keep_fp32) {
     const int lane = threadIdx.x & 63;
@@ -87,9 +88,10 @@ __global__ __launch_bounds__(256) void adapter_t_kernel(const uint16_t* __restri
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     const int64_t m = m0 + 16 * mb + 4 * g + e;
+                    const float v = r < ranks ? acc[mb][rt][e] : 0.f;
                     if (m < M && r < Rpad) {
-                        if (ksplit == 1 && !keep_fp32) t[m * Rpad + r] = f32_to_bf16_rne(acc[mb][rt][e]);
-                        else partial[((int64_t)z * M + m) * Rpad + r] = acc[mb][rt][e];
+                        if (ksplit == 1 && !keep_fp32) t[m * Rpad + r] = f32_to_bf16_rne(v);
+                        else partial[((int64_t)z * M + m) * Rpad + r] = v;
                     }
                 }
             }
@@ -100,9 +102,10 @@ __global__ __launch_bounds__(256) void adapter_t_kernel(const uint16_t* __restri
 // whole float4 apart (splitk_slice).  kZ threads share an
 // output, thread q taking z = q, q + kZ, ..; each has up to eight requests in flight (one after the other, 56 slices of a
 // [256, 32] sum took 15.9 us).  kCount: the number of slices where it is known (0: ksplit), so that no request is conditional.
-template <int kZ, int kCount = 0>
+// kPadded: out has rows of `cols` (a multiple of four), of which those from `valid` on are padding and stored as zeros.
+template <int kZ, int kCount = 0, bool kPadded = false>
 __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restrict__ partial, int64_t count, int ksplit,
-                                                            uint16_t* __restrict__ out) {
+                                                            uint16_t* __restrict__ out, int cols, int valid) {
     constexpr int kOut = 256 / kZ;   // outputs (of four elements) per workgroup
     __shared__ float4 sums[kZ > 1 ? 256 : 1];
     const int64_t slice = splitk_slice(count);
@@ -139,6 +142,10 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restr
         }
     }
     if (i >= count) return;
+    if constexpr (kPadded) {
+        const int c0 = (int)(i % cols);
+        s = make_float4(c0 < valid ? s.x : 0.f, c0 + 1 < valid ? s.y : 0.f, c0 + 2 < valid ? s.z : 0.f, c0 + 3 < valid ? s.w : 0.f);
+    }
     if (i + 4 > count) {   // the last outputs of a count that is no multiple of four
         const float e[3] = {s.x, s.y, s.z};
         for (int j = 0; i + j < count; ++j) out[i + j] = f32_to_bf16_rne(e[j]);
@@ -150,11 +157,14 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restr
     *reinterpret_cast<uint2*>(out + i) = o;
 }
 
-void launch_splitk_reduce(const float* partial, int64_t count, int ksplit, uint16_t* out, hipStream_t stream) {
+void launch_splitk_reduce(const float* partial, int64_t count, int ksplit, uint16_t* out, hipStream_t stream, int cols, int valid) {
 #define SALR_SUM(OUT, ...) \
     hipLaunchKernelGGL((splitk_reduce_kernel<__VA_ARGS__>), dim3((unsigned)((count + 4 * (OUT)-1) / (4 * (OUT)))), dim3(256), 0, stream, \
-                       partial, count, ksplit, out)
-    if (ksplit > 8) SALR_SUM(64, 4);
+                       partial, count, ksplit, out, cols, valid)
+    if (valid < cols) {
+        if (ksplit > 8) SALR_SUM(64, 4, 0, true);
+        else SALR_SUM(256, 1, 0, true);
+    } else if (ksplit > 8) SALR_SUM(64, 4);
     else if (ksplit == 2) SALR_SUM(256, 1, 2);   // the splits of the layers' kernels are powers of two
     else if (ksplit == 4) SALR_SUM(256, 1, 4);
     else if (ksplit == 8) SALR_SUM(256, 1, 8);
@@ -371,11 +381,11 @@ void launch_backward_t(const LowRankJob& dy_b, const LowRankJob& x_a, int64_t M,
 
 template <int kMB, int kDepth>
 static void launch_tall_product_rt(int rank_tiles, dim3 grid, hipStream_t stream, const uint16_t* x, int64_t M, int64_t K,
-                                   const uint16_t* a_t, int Rpad, int ksplit, uint16_t* t, float* partial, int keep) {
+                                   const uint16_t* a_t, int Rpad, int ranks, int ksplit, uint16_t* t, float* partial, int keep) {
     switch (rank_tiles) {
 #define SALR_CASE(RT)                                                                                                   \
     case RT:                                                                                                            \
-        hipLaunchKernelGGL((adapter_t_kernel<kMB, RT, kDepth>), grid, dim3(256), 0, stream, x, M, K, a_t, Rpad, ksplit, t, \
+        hipLaunchKernelGGL((adapter_t_kernel<kMB, RT, kDepth>), grid, dim3(256), 0, stream, x, M, K, a_t, Rpad, ranks, ksplit, t, \
                            partial, keep);                                                                              \
         break;
         SALR_CASE(2) SALR_CASE(3) SALR_CASE(4) SALR_CASE(5) SALR_CASE(6) SALR_CASE(7) SALR_CASE(8)
@@ -384,7 +394,7 @@ static void launch_tall_product_rt(int rank_tiles, dim3 grid, hipStream_t stream
     }
 }
 
-void launch_tall_product(const uint16_t* x, int64_t M, int64_t K, const uint16_t* a_t, int Rpad, int ksplit, uint16_t* t,
+void launch_tall_product(const uint16_t* x, int64_t M, int64_t K, const uint16_t* a_t, int Rpad, int ranks, int ksplit, uint16_t* t,
                          float* partial, bool keep_fp32, hipStream_t stream) {
     const int rows = adapter_rows_per_block(M);
     const dim3 grid((unsigned)((M + rows - 1) / rows), (unsigned)ksplit);
@@ -392,8 +402,8 @@ void launch_tall_product(const uint16_t* x, int64_t M, int64_t K, const uint16_t
     const int tiles = Rpad / 16, passes = (tiles + 7) / 8;
     const int rank_tiles = (tiles + passes - 1) / passes;
     const int keep = keep_fp32 ? 1 : 0;
-    if (rows == 256) launch_tall_product_rt<4, 2>(rank_tiles, grid, stream, x, M, K, a_t, Rpad, ksplit, t, partial, keep);
-    else launch_tall_product_rt<1, 4>(rank_tiles, grid, stream, x, M, K, a_t, Rpad, ksplit, t, partial, keep);
+    if (rows == 256) launch_tall_product_rt<4, 2>(rank_tiles, grid, stream, x, M, K, a_t, Rpad, ranks, ksplit, t, partial, keep);
+    else launch_tall_product_rt<1, 4>(rank_tiles, grid, stream, x, M, K, a_t, Rpad, ranks, ksplit, t, partial, keep);
 }
 
 void launch_adapter_t(const LinearArgs& a, hipStream_t stream) {
@@ -415,7 +425,7 @@ void launch_adapter_t(const LinearArgs& a, hipStream_t stream) {
     }
     launch_adapter_transpose(a.a_cat, a.K, R, Rpad, a_t, stream);
     const int ksplit = adapter_ksplit(a.M, a.K);
-    launch_tall_product(a.x, a.M, a.K, a_t, Rpad, ksplit, a.t, partial, false, stream);
+    launch_tall_product(a.x, a.M, a.K, a_t, Rpad, R, ksplit, a.t, partial, false, stream);
     if (ksplit > 1) launch_splitk_reduce(partial, a.M * Rpad, ksplit, a.t, stream);
 }
 

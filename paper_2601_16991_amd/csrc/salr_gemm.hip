@@ -633,9 +633,10 @@ void launch_adapter_t_direct(const uint16_t* x, int64_t M, int64_t K, const uint
 }
 
 // T = X * A_cat as a product with A_cat in operand order (af): 256 rows x all ranks (128 at a time) per workgroup, K split over
-// as many workgroups as the chip holds, fp32 partial sums, their sum to bf16 [M, Rpad].
-static void launch_adapter_t_product(const uint16_t* x, int64_t M, int64_t K, const uint16_t* af, int Rpad, uint16_t* t, float* partial,
-                                     hipStream_t stream) {
+// as many workgroups as the chip holds, fp32 partial sums, their sum to bf16 [M, Rpad] (padding columns as zeros: an infinite
+// entry of X made the products with their zero rows NaN, and those every output of the row).
+static void launch_adapter_t_product(const uint16_t* x, int64_t M, int64_t K, const uint16_t* af, int R, int Rpad, uint16_t* t,
+                                     float* partial, hipStream_t stream) {
     const int m_tiles = (int)((M + 255) / 256), nt = Rpad <= 32 ? 32 : Rpad <= 64 ? 64 : 128, n_tiles = (Rpad + nt - 1) / nt;
     const int ks = adapter_t_product_ksplit(M, K, Rpad);
     const dim3 grid(gemm_grid(m_tiles * n_tiles * ks));
@@ -647,7 +648,7 @@ static void launch_adapter_t_product(const uint16_t* x, int64_t M, int64_t K, co
     else if (nt == 64) SALR_TGEMM(4);
     else SALR_TGEMM(8);
 #undef SALR_TGEMM
-    launch_splitk_reduce(partial, M * Rpad, ks, t, stream);
+    launch_splitk_reduce(partial, M * Rpad, ks, t, stream, Rpad, R);
 }
 
 hipError_t launch_linear_frag(const LinearArgs& a, hipStream_t stream, const TimingEvents& ev) {
@@ -660,7 +661,7 @@ hipError_t launch_linear_frag(const LinearArgs& a, hipStream_t stream, const Tim
     const hipError_t e = launch_decode_frags(a, wf, own ? reinterpret_cast<uint16_t*>(af) : nullptr, stream);
     if (e != hipSuccess) return e;
     if (own)
-        launch_adapter_t_product(a.x, a.M, a.K, reinterpret_cast<const uint16_t*>(af), Rpad, a.t,
+        launch_adapter_t_product(a.x, a.M, a.K, reinterpret_cast<const uint16_t*>(af), (int)a.R, Rpad, a.t,
                                  reinterpret_cast<float*>(af + adapter_frag_bytes(a.K, a.R)), stream);
     const size_t base = frag_base_bytes(a.M, a.K, a.N, a.R);
     float* partial = reinterpret_cast<float*>(reinterpret_cast<char*>(a.t) + base);

@@ -448,8 +448,8 @@ inline int tn_ksplit(int64_t C0, int64_t M, int64_t C1 = 0) {
 void launch_row_products(const RowProductJob& da, const RowProductJob& db, int64_t M, int R, int ksplit, float* partial,
                          hipStream_t stream);
 // x [M, K] bf16 times the transpose of a_t [Rpad, K] bf16 (Rpad % 32 == 0, K % 32 == 0), K split over `ksplit`
-// slices: bf16 t [M, Rpad] (one slice, !keep_fp32) or fp32 partial [ksplit, M, Rpad]
-void launch_tall_product(const uint16_t* x, int64_t M, int64_t K, const uint16_t* a_t, int Rpad, int ksplit, uint16_t* t,
+// slices: bf16 t [M, Rpad] (one slice, !keep_fp32) or fp32 partial [ksplit, M, Rpad]; columns from `ranks` on as zeros
+void launch_tall_product(const uint16_t* x, int64_t M, int64_t K, const uint16_t* a_t, int Rpad, int ranks, int ksplit, uint16_t* t,
                          float* partial, bool keep_fp32, hipStream_t stream);
 // a_t [Rpad, K] = A_cat [K, R]^T, rows R .. Rpad - 1 zero
 void launch_adapter_transpose(const uint16_t* a_cat, int64_t K, int R, int Rpad, uint16_t* a_t, hipStream_t stream);
@@ -463,7 +463,8 @@ void launch_frag_gemm(const uint16_t* x, int64_t M, int64_t K, int64_t N, const 
 void launch_dense_stage(const uint16_t* x, int64_t M, int64_t K, int64_t N, const uint16_t* wd, const uint16_t* t,
                         const uint16_t* b_cat, int R, int Rpad, uint16_t* y, float* partial, const TimingEvents& ev,
                         hipStream_t stream);
-// out[i] = bf16(sum over z < ksplit of partial[z * splitk_slice(count) + i])
-void launch_splitk_reduce(const float* partial, int64_t count, int ksplit, uint16_t* out, hipStream_t stream);
+// out[i] = bf16(sum over z < ksplit of partial[z * splitk_slice(count) + i]); with valid < cols the columns from `valid` on of out's
+// rows of `cols` are zeros instead
+void launch_splitk_reduce(const float* partial, int64_t count, int ksplit, uint16_t* out, hipStream_t stream, int cols = 0, int valid = 0);
 
 }  // namespace salr

@@ -454,7 +454,7 @@ static void run_svd(const uint16_t* e, int64_t N, int64_t K, int r, int l, int i
     float* small_b = small_a + L * L;
 
     auto product = [&](const uint16_t* mat, int64_t rows, int64_t cols, int ks, float* out) {   // out = mat * (bt as fp32)^T
-        launch_tall_product(mat, rows, cols, bt, 2 * L, ks, nullptr, partial, true, stream);
+        launch_tall_product(mat, rows, cols, bt, 2 * L, 2 * L, ks, nullptr, partial, true, stream);
         hipLaunchKernelGGL(fold_reduce_kernel, dim3((unsigned)((rows * (L / 4) + 255) / 256)), dim3(256), 0, stream, partial, rows,
                            L, ks, out);
     };

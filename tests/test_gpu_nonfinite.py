@@ -8,7 +8,7 @@ import torch
 
 import oracle
 import salr_workloads as wl
-from gpu_util import to_dev_u16, to_dev_u32, y_to_f64
+from gpu_util import dev, to_dev_u16, to_dev_u32, y_to_f64
 
 pytestmark = pytest.mark.gpu
 
@@ -46,13 +46,25 @@ HALF_STEPS = [(130, 96, 300, 0), (300, 160, 65, 64), (150, 8224, 40, 0), (200, 1
               (131, 2720, 267, 24), (1030, 96, 14400, 8), (1100, 544, 2050, 32)]
 
 
-@pytest.mark.parametrize("M,K,N,R", HALF_STEPS)
-def test_linear(M, K, N, R):
+# ranks that do not fill the padded ones, on the paths that compute T with A_cat padded by zero rows: the product of its own (ranks
+# that are no multiple of 8, long rows), and the transposing pass of the fused kernel above 1024 tokens (the least workspace)
+PADDED_RANKS = [(200, 128, 300, 5), (200, 128, 300, 61), (1100, 128, 300, 61), (150, 8256, 40, 72), (1100, 1024, 300, 33), (4100, 512, 33, 7)]
+
+
+@pytest.mark.parametrize("M,K,N,R", HALF_STEPS + PADDED_RANKS)
+@pytest.mark.parametrize("least", [False, True])
+def test_linear(M, K, N, R, least):
     import paper_2601_16991_amd as salr
     x, w, a, b = _layer(M, K, N, R, M + K + N + R)
     rb, rv, ro = oracle.encode(w)
-    print(f"[non-finite] M{M} K{K} N{N} R{R}", flush=True)
-    y = salr.linear(to_dev_u16(x), to_dev_u32(rb), to_dev_u16(rv), to_dev_u32(ro), *((to_dev_u16(a), to_dev_u16(b)) if R else (None, None)))
+    print(f"[non-finite] M{M} K{K} N{N} R{R} least workspace {least}", flush=True)
+    y = torch.empty((M, N), dtype=torch.int16, device=dev())
+    size = salr.salr_linear_workspace_bytes_min(M, K, N, R)
+    args = (to_dev_u16(x), to_dev_u32(rb), to_dev_u16(rv), to_dev_u32(ro), *((to_dev_u16(a), to_dev_u16(b)) if R else (None, None)))
+    if least:
+        salr.salr_sparse_lowrank_linear(*args, y, torch.empty(size, dtype=torch.uint8, device=dev()) if size else None)
+    else:
+        y = salr.linear(*args)
     torch.cuda.synchronize()
     ref = oracle.linear(x, w, a, b)
     assert np.isinf(ref[3]).any() and np.isinf(ref[M - 1]).any()
