@@ -1,8 +1,8 @@
 // Magnitude pruning masks (paper Sec. 2: static mask from a magnitude threshold; Sec. 4: the N:M
 // pattern of the inference-throughput comparison).
 //
-// Row mask, rows of up to 28672 columns in whole 16-byte units: mask_rows_wave_kernel below.  Other rows: one workgroup per
-// row keeps the `keep` entries of largest |w|, ties to the lower column.
+// Row mask, rows of up to 14336 columns in whole 16-byte units, and of 20488 to 28672 where there are many:
+// mask_rows_wave_kernel below (see launch_mask_rows).  Other rows: one workgroup per row keeps the `keep` entries of largest |w|, ties to the lower column.
 // The threshold is the largest 15-bit magnitude pattern T with count(|w| >= T) >= keep, found by a
 // two-level radix select: a histogram of the exponent (the top 8 of the 15 bits) locates T's exponent,
 // a histogram of the 7 mantissa bits inside that exponent locates the rest (two passes over the row,
@@ -350,7 +350,21 @@ hipError_t launch_mask_rows(const uint16_t* w, int64_t rows, int64_t cols, int64
     const size_t row_bytes = (size_t)units * sizeof(uint4);
     const bool lds = row_bytes <= (size_t)kMaskLdsBytesMax;
     const bool vec = (cols % kUnit == 0) && (((reinterpret_cast<uintptr_t>(w) | reinterpret_cast<uintptr_t>(out)) & 15u) == 0);
-    if (vec && units <= kWave * 56) {   // the row fits the registers of one wave
+    // A row in the registers of one wave, or a workgroup per row with the row in LDS.  The registers of 28 units a lane leave two
+    // waves on a SIMD (196), those of 56 one (297), too few to cover memory.  Microseconds by rows (1/2 of the entries kept, inputs from
+    // memory), wave form / workgroup form:
+    //   14336 columns   512: 25/27   1024: 29/42                 2048: 39/72     4096: 68/130    8192: 113/-
+    //   16384           512: 41/30   1024: 43/45   1536: 80/67   2048: 82/80     4096: 160/145   8192: 315/275
+    //   20480           512: 50/36   1024: 54/67   1536: 99/84   2048: 103/112   4096: 201/213   8192: 396/397
+    //   22528           512: 54/39   1024: 57/73   1536: 106/91  2048: 111/123   4096: 213/232   8192: 421/437
+    //   24576           512: 57/42   1024: 61/79   1536: 111/100 2048: 117/132   4096: 229/252   8192: 450/470
+    //   25600           512: 59/45   1024: 64/86   1536: 117/125 2048: 123/165   4096: 240/320   8192: 471/622
+    //   28672           512: 65/49   1024: 71/93   1536: 127/137 2048: 135/180   4096: 262/349   8192: 513/681
+    // With 7/10 kept the wave form needs 7 to 10 % more, the other the same.  So 56 units only on rows of more than 20480
+    // columns, where the row in LDS leaves three workgroups on a CU, or two from 24584 on, and the rows are more than those
+    // hold at once.
+    const int64_t held = 256 * (units > kWave * 48 ? 2 : 3);
+    if (vec && (units <= kWave * 28 || (units > kWave * 40 && units <= kWave * 56 && rows > held))) {
         const dim3 wgrid((unsigned)((rows + kMaskWaves - 1) / kMaskWaves));
         if (units <= kWave * 4) hipLaunchKernelGGL((mask_rows_wave_kernel<4>), wgrid, dim3(kMaskThreads), 0, stream, w, rows, cols, keep, out);
         else if (units <= kWave * 8) hipLaunchKernelGGL((mask_rows_wave_kernel<8>), wgrid, dim3(kMaskThreads), 0, stream, w, rows, cols, keep, out);

@@ -130,3 +130,12 @@ def test_mask_of_a_pruned_matrix_is_itself(cols, keep):
     out = salr.mask_rows(torch.from_numpy(w.view(np.int16)).cuda(), keep)
     torch.cuda.synchronize()
     assert np.array_equal(out.cpu().numpy().view(np.uint16), oracle.mask_topk_rows(w, keep))
+
+
+@pytest.mark.parametrize("rows,cols,keep", [(513, 24584, 12292), (514, 28672, 8601), (515, 26000, 25999), (512, 24584, 7000),
+                                            (769, 20488, 10244), (769, 24576, 12288), (768, 24576, 100), (769, 20480, 6000)])
+def test_mask_rows_longest_rows(rows, cols, keep):
+    """From 20488 columns on more rows than the CUs hold workgroups go through the kernel with one wave per row, fewer through
+    the one with a workgroup per row; both sides of each line."""
+    w = np.concatenate([wl.gaussian_bf16((rows - 8, cols), 0.02, cols + keep), _few_magnitudes((8, cols), rows + keep)])
+    _check_rows(w, keep, "longest rows")
