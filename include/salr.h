@@ -124,11 +124,12 @@ salr_status_t salr_decode(const uint32_t* bitmap, const uint16_t* values, const 
 /*
  * Bytes of device workspace salr_sparse_lowrank_linear needs for these sizes (0 is possible).
  * It holds T = X * A_cat and fp32 partial results of contractions that are split over K; for large
- * batches (M > 128, or M > 64 where K is no multiple of 128), where the weight is decoded once per
- * call into a dense scratch matrix that the matrix-core stage then reads, also a transposed copy of
- * A_cat and N * K bf16 elements of decoded weight; for batches of up to 128 tokens with adapters on rows of whole
+ * batches (M > 128, or M > 64 where K is no multiple of 128) also a transposed copy of A_cat and, where K is a multiple
+ * of 64, N * K bf16 elements of weight, which is decoded once per call into scratch memory that the matrix-core stage
+ * then reads; for batches of up to 128 tokens with adapters on rows of whole
  * 128-column chunks, a slice table (64 bytes per weight row, see below) that the call builds for itself beside the
  * first adapter product when it is not handed one.  Nothing in it outlives the call.  Returns 0 for invalid sizes.
+ * For large batches the fastest path can use more: see salr_linear_workspace_bytes_fastest.
  */
 size_t salr_linear_workspace_bytes(int64_t M, int64_t K, int64_t N, int64_t R);
 
@@ -171,6 +172,17 @@ salr_status_t salr_sparse_lowrank_linear_prepared(const uint16_t* x, int64_t M, 
 size_t salr_linear_workspace_bytes_min(int64_t M, int64_t K, int64_t N, int64_t R);
 
 /*
+ * The workspace with which salr_sparse_lowrank_linear (and its _prepared form) is fastest; never less than
+ * salr_linear_workspace_bytes and the same for small batches.  Large batches decode the weight into the order in which
+ * the matrix cores read it, with B_cat behind it and rows in whole blocks of 16, and split the contraction where the
+ * outputs are few; what that takes is about the size above where K is a multiple of 64, a few percent more where N is no
+ * multiple of 16 or the adapters' part is not in it, and 2 N K bytes more where K is not (K % 64 == 32; with the size
+ * above such a layer is decoded anew for every 64 rows of X: 300 x 2720 x 2731 110 us instead of 39, 2048 x 4128 x 14336
+ * 1946 instead of 260).  A call takes the best path that fits what it is given.  Returns 0 for invalid sizes.
+ */
+size_t salr_linear_workspace_bytes_fastest(int64_t M, int64_t K, int64_t N, int64_t R);
+
+/*
  * salr_sparse_lowrank_linear -- the layer of Sec. 3.2 / 3.3:
  *
  *     Y = X * W-hat^T + (X * A_cat) * B_cat
@@ -189,8 +201,8 @@ size_t salr_linear_workspace_bytes_min(int64_t M, int64_t K, int64_t N, int64_t 
  *   b_cat        in   [R, N] bf16; may be NULL iff R == 0
  *   y            out  [M, N] bf16, overwritten
  *   workspace    --   salr_linear_workspace_bytes(M, K, N, R) bytes, 256-byte aligned (at least
- *                     salr_linear_workspace_bytes_min: see there for what the smaller size means); may be NULL
- *                     when that size is 0.  Contents before and after are unspecified.
+ *                     salr_linear_workspace_bytes_min, at best salr_linear_workspace_bytes_fastest: see there for what
+ *                     the other sizes mean); may be NULL when that size is 0.  Contents before and after are unspecified.
  *
  * Constraints: K % 32 == 0 (else SHAPE); R <= 256 (else UNSUPPORTED); M, N < 2^31.
  * K == 0: x, bitmap, values, a_cat may be NULL; Y is written as zeros (both products are empty sums).
@@ -258,19 +270,22 @@ salr_status_t salr_sparse_lowrank_linear_noalloc(const uint16_t* x, int64_t M, i
  *     slice table built per call (64 bytes per weight row).
  *   As an INPUT to salr_qsalr_linear `codes` must be readable up to the next multiple of 16 bytes (vector reads; the
  *   padding is never used).
- *   - Large batches that take the two-stage path (more than 128 tokens, or more than 64 where the row-tiled kernel
- *     does not apply; K % 64 == 0): its decode stage reads the codes; workspace as for the plain layer.
+ *   - Large batches (more than 128 tokens, or more than 64 where the row-tiled kernel does not apply): the decode stage
+ *     reads the codes where K % 64 == 0 (workspace as for the plain layer), and for other K where the workspace has room
+ *     for the decoded weight.
  *   - Otherwise the values are dequantised once per call into the first part of the workspace (2 * nnz bytes,
  *     rounded up), then the layer runs as usual on them.
  * Both compute the same products; where the plain layer would take its small-batch streaming kernels Y is the same
  * bit for bit (finite scales).
- * Workspace: salr_qsalr_linear_workspace_bytes(M, K, N, R, nnz) bytes, 256-byte aligned.
+ * Workspace: salr_qsalr_linear_workspace_bytes(M, K, N, R, nnz) bytes, 256-byte aligned, at best
+ * salr_qsalr_linear_workspace_bytes_fastest (as for the plain layer).
  */
 salr_status_t salr_nf4_quantize_values(const uint16_t* values, int64_t count, uint8_t* codes, uint16_t* scales,
                                        void* stream);
 salr_status_t salr_nf4_dequantize_values(const uint8_t* codes, const uint16_t* scales, int64_t count,
                                          uint16_t* values_out, void* stream);
 size_t salr_qsalr_linear_workspace_bytes(int64_t M, int64_t K, int64_t N, int64_t R, int64_t nnz);
+size_t salr_qsalr_linear_workspace_bytes_fastest(int64_t M, int64_t K, int64_t N, int64_t R, int64_t nnz);
 salr_status_t salr_qsalr_linear(const uint16_t* x, int64_t M, int64_t K, int64_t N, const uint32_t* bitmap,
                                 const uint8_t* codes, const uint16_t* scales, const uint32_t* row_offsets,
                                 int64_t nnz, const uint16_t* a_cat, const uint16_t* b_cat, int64_t R, uint16_t* y,
@@ -293,12 +308,14 @@ salr_status_t salr_qsalr_linear(const uint16_t* x, int64_t M, int64_t K, int64_t
  * by this call (the flag that salr_bitmap_is_2of4 writes lives in device memory, and reading it here would
  * mean a synchronisation, which no entry point of this library performs: the caller reads it once per layer
  * and picks the entry point): on a weight that fails it the result is unspecified (no memory outside the
- * buffers is read or written).  Workspace: salr_linear_2of4_workspace_bytes(M, K, N, R) bytes.
+ * buffers is read or written).  Workspace: salr_linear_2of4_workspace_bytes(M, K, N, R) bytes; on the shapes that are
+ * passed on salr_linear_2of4_workspace_bytes_fastest as for the plain layer.
  * Errors of both: INVALID_ARG, SHAPE, CAPACITY, UNSUPPORTED, HIP as above.
  */
 salr_status_t salr_bitmap_is_2of4(const uint32_t* bitmap, int64_t rows, int64_t cols, uint32_t* result,
                                   void* stream);
 size_t salr_linear_2of4_workspace_bytes(int64_t M, int64_t K, int64_t N, int64_t R);
+size_t salr_linear_2of4_workspace_bytes_fastest(int64_t M, int64_t K, int64_t N, int64_t R);
 salr_status_t salr_sparse_lowrank_linear_2of4(const uint16_t* x, int64_t M, int64_t K, int64_t N,
                                               const uint32_t* bitmap, const uint16_t* values,
                                               const uint32_t* row_offsets, const uint16_t* a_cat,

@@ -58,6 +58,8 @@ def lib() -> ctypes.CDLL:
         L.salr_linear_workspace_bytes.argtypes = [_i64, _i64, _i64, _i64]
         L.salr_linear_workspace_bytes_min.restype = ctypes.c_size_t
         L.salr_linear_workspace_bytes_min.argtypes = [_i64, _i64, _i64, _i64]
+        L.salr_linear_workspace_bytes_fastest.restype = ctypes.c_size_t
+        L.salr_linear_workspace_bytes_fastest.argtypes = [_i64, _i64, _i64, _i64]
         L.salr_sparse_lowrank_linear.restype = ctypes.c_int
         L.salr_sparse_lowrank_linear.argtypes = [_vp, _i64, _i64, _i64, _vp, _vp, _vp, _vp, _vp, _i64, _vp, _vp,
                                                  ctypes.c_size_t, _vp]
@@ -76,6 +78,8 @@ def lib() -> ctypes.CDLL:
         L.salr_nf4_dequantize_values.argtypes = [_vp, _vp, _i64, _vp, _vp]
         L.salr_qsalr_linear_workspace_bytes.restype = ctypes.c_size_t
         L.salr_qsalr_linear_workspace_bytes.argtypes = [_i64, _i64, _i64, _i64, _i64]
+        L.salr_qsalr_linear_workspace_bytes_fastest.restype = ctypes.c_size_t
+        L.salr_qsalr_linear_workspace_bytes_fastest.argtypes = [_i64, _i64, _i64, _i64, _i64]
         L.salr_qsalr_linear.restype = ctypes.c_int
         L.salr_qsalr_linear.argtypes = [_vp, _i64, _i64, _i64, _vp, _vp, _vp, _vp, _i64, _vp, _vp, _i64, _vp, _vp,
                                         ctypes.c_size_t, _vp]
@@ -83,6 +87,8 @@ def lib() -> ctypes.CDLL:
         L.salr_bitmap_is_2of4.argtypes = [_vp, _i64, _i64, _vp, _vp]
         L.salr_linear_2of4_workspace_bytes.restype = ctypes.c_size_t
         L.salr_linear_2of4_workspace_bytes.argtypes = [_i64, _i64, _i64, _i64]
+        L.salr_linear_2of4_workspace_bytes_fastest.restype = ctypes.c_size_t
+        L.salr_linear_2of4_workspace_bytes_fastest.argtypes = [_i64, _i64, _i64, _i64]
         L.salr_sparse_lowrank_linear_2of4.restype = ctypes.c_int
         L.salr_sparse_lowrank_linear_2of4.argtypes = [_vp, _i64, _i64, _i64, _vp, _vp, _vp, _vp, _vp, _i64, _vp, _vp,
                                                       ctypes.c_size_t, _vp]
@@ -199,6 +205,10 @@ def salr_linear_workspace_bytes_min(M: int, K: int, N: int, R: int) -> int:
     return int(lib().salr_linear_workspace_bytes_min(M, K, N, R))
 
 
+def salr_linear_workspace_bytes_fastest(M: int, K: int, N: int, R: int) -> int:
+    return int(lib().salr_linear_workspace_bytes_fastest(M, K, N, R))
+
+
 def salr_sparse_lowrank_linear(x: torch.Tensor, bitmap: torch.Tensor, values: torch.Tensor,
                                row_offsets: torch.Tensor, a_cat: Optional[torch.Tensor],
                                b_cat: Optional[torch.Tensor], y: torch.Tensor,
@@ -250,6 +260,10 @@ def salr_nf4_dequantize_values(codes: torch.Tensor, scales: torch.Tensor, count:
 
 def salr_qsalr_linear_workspace_bytes(M: int, K: int, N: int, R: int, nnz: int) -> int:
     return int(lib().salr_qsalr_linear_workspace_bytes(M, K, N, R, nnz))
+
+
+def salr_qsalr_linear_workspace_bytes_fastest(M: int, K: int, N: int, R: int, nnz: int) -> int:
+    return int(lib().salr_qsalr_linear_workspace_bytes_fastest(M, K, N, R, nnz))
 
 
 def salr_qsalr_linear(x: torch.Tensor, bitmap: torch.Tensor, codes: torch.Tensor, scales: torch.Tensor,
@@ -316,6 +330,10 @@ def salr_bitmap_is_2of4(bitmap: torch.Tensor, result: torch.Tensor, stream=None)
 
 def salr_linear_2of4_workspace_bytes(M: int, K: int, N: int, R: int) -> int:
     return int(lib().salr_linear_2of4_workspace_bytes(M, K, N, R))
+
+
+def salr_linear_2of4_workspace_bytes_fastest(M: int, K: int, N: int, R: int) -> int:
+    return int(lib().salr_linear_2of4_workspace_bytes_fastest(M, K, N, R))
 
 
 def salr_sparse_lowrank_linear_2of4(x: torch.Tensor, bitmap: torch.Tensor, values: torch.Tensor,
@@ -559,4 +577,9 @@ def linear_prepared(x, bitmap, values, row_offsets, slice_table, a_cat, b_cat,
 
 
 def linear(x, bitmap, values, row_offsets, a_cat, b_cat, workspace: Optional[torch.Tensor] = None) -> torch.Tensor:
+    """Y = X What^T + (X A_cat) B_cat, newly allocated.  Where ``workspace`` is None, or holds what salr_linear_workspace_bytes
+    tells but less than salr_linear_workspace_bytes_fastest, one of the fastest size comes from torch's allocator for the
+    length of the call (large batches only; most on layers with K % 64 == 32, whose decoded weight the told size does not
+    contain); where the allocator has no room for it the call runs on what it was given.  With the fastest size nothing but the result is
+    allocated; salr_sparse_lowrank_linear, which takes y, never allocates.  linear_prepared and linear_2of4 alike."""
     return _native().linear(0, x, bitmap, values, row_offsets, None, a_cat, b_cat, None, workspace, None)

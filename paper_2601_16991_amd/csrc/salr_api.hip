@@ -45,25 +45,6 @@ bool qsalr_decodes_codes(int64_t M, int64_t K, int64_t N, int64_t nnz) {
 
 }  // namespace
 
-namespace salr {
-
-// See salr_internal.hpp: the binding allocates these for calls that bring no workspace, or one of the size the queries tell.
-size_t linear_call_workspace_bytes(bool two_of_four, int64_t M, int64_t K, int64_t N, int64_t R) {
-    const size_t told = two_of_four ? salr_linear_2of4_workspace_bytes(M, K, N, R) : salr_linear_workspace_bytes(M, K, N, R);
-    if (M <= 0 || K <= 0 || N <= 0 || R < 0 || R > kMaxRank || K % 32 != 0) return told;
-    if (two_of_four && (uses_2of4_kernel(M, K, N) || uses_2of4_gemm(M, K, N))) return told;
-    return linear_workspace_bytes_fastest(M, K, N, R);
-}
-
-size_t qsalr_call_workspace_bytes(int64_t M, int64_t K, int64_t N, int64_t R, int64_t nnz) {
-    const size_t told = salr_qsalr_linear_workspace_bytes(M, K, N, R, nnz);
-    if (M <= 0 || K <= 0 || N <= 0 || R < 0 || R > kMaxRank || K % 32 != 0 || nnz <= 0 || linear_nf4_takes(M, K, N, nnz)) return told;
-    const size_t fastest = linear_workspace_bytes_fastest(M, K, N, R);
-    return fastest > told ? fastest : told;
-}
-
-}  // namespace salr
-
 extern "C" {
 
 const char* salr_status_string(salr_status_t status) {
@@ -183,6 +164,11 @@ size_t salr_linear_workspace_bytes(int64_t M, int64_t K, int64_t N, int64_t R) {
 size_t salr_linear_workspace_bytes_min(int64_t M, int64_t K, int64_t N, int64_t R) {
     if (M <= 0 || K < 0 || N <= 0 || R < 0 || R > kMaxRank || K % 32 != 0) return 0;
     return salr::linear_workspace_bytes_lean(M, K, N, R);
+}
+
+size_t salr_linear_workspace_bytes_fastest(int64_t M, int64_t K, int64_t N, int64_t R) {
+    if (M <= 0 || K <= 0 || N <= 0 || R < 0 || R > kMaxRank || K % 32 != 0) return salr_linear_workspace_bytes(M, K, N, R);
+    return salr::linear_workspace_bytes_fastest(M, K, N, R);
 }
 
 size_t salr_slice_table_bytes(int64_t N, int64_t K) {
@@ -305,6 +291,13 @@ size_t salr_qsalr_linear_workspace_bytes(int64_t M, int64_t K, int64_t N, int64_
     return salr::qsalr_values_bytes(nnz) + salr::linear_workspace_bytes(M, K, N, R);
 }
 
+size_t salr_qsalr_linear_workspace_bytes_fastest(int64_t M, int64_t K, int64_t N, int64_t R, int64_t nnz) {
+    const size_t told = salr_qsalr_linear_workspace_bytes(M, K, N, R, nnz);
+    if (M <= 0 || K <= 0 || N <= 0 || R < 0 || R > kMaxRank || K % 32 != 0 || nnz <= 0 || salr::linear_nf4_takes(M, K, N, nnz)) return told;
+    const size_t fastest = salr::linear_workspace_bytes_fastest(M, K, N, R);
+    return fastest > told ? fastest : told;
+}
+
 salr_status_t salr_qsalr_linear(const uint16_t* x, int64_t M, int64_t K, int64_t N, const uint32_t* bitmap, const uint8_t* codes,
                                 const uint16_t* scales, const uint32_t* row_offsets, int64_t nnz, const uint16_t* a_cat,
                                 const uint16_t* b_cat, int64_t R, uint16_t* y, void* workspace, size_t workspace_bytes,
@@ -353,6 +346,12 @@ size_t salr_linear_2of4_workspace_bytes(int64_t M, int64_t K, int64_t N, int64_t
     if (M <= 0 || K <= 0 || N <= 0 || R < 0 || R > kMaxRank || K % 32 != 0 || !salr::uses_2of4_kernel(M, K, N)) return general;
     const size_t fast = salr::rowtile_workspace_bytes(M, K, N, R);
     return fast > general ? fast : general;
+}
+
+size_t salr_linear_2of4_workspace_bytes_fastest(int64_t M, int64_t K, int64_t N, int64_t R) {
+    if (M > 0 && K > 0 && N > 0 && (salr::uses_2of4_kernel(M, K, N) || salr::uses_2of4_gemm(M, K, N)))
+        return salr_linear_2of4_workspace_bytes(M, K, N, R);
+    return salr_linear_workspace_bytes_fastest(M, K, N, R);
 }
 
 salr_status_t salr_sparse_lowrank_linear_2of4(const uint16_t* x, int64_t M, int64_t K, int64_t N, const uint32_t* bitmap,

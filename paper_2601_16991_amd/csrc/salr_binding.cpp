@@ -18,8 +18,6 @@ hipError_t launch_encode_index(const uint16_t* w, int64_t rows, int64_t cols, ui
                                uint32_t* nnz_host, hipStream_t stream);
 hipError_t launch_encode_values(const uint16_t* w, int64_t rows, int64_t cols, const uint32_t* bitmap, const uint32_t* row_offsets,
                                 uint16_t* values, int64_t capacity, hipStream_t stream);
-size_t linear_call_workspace_bytes(bool two_of_four, int64_t M, int64_t K, int64_t N, int64_t R);
-size_t qsalr_call_workspace_bytes(int64_t M, int64_t K, int64_t N, int64_t R, int64_t nnz);
 }  // namespace salr
 
 namespace {
@@ -136,6 +134,18 @@ struct Workspace {
         ptr = own.data_ptr();
         bytes = need;
     }
+    // The size with which the call is fastest, unless the caller's is that large.  The call runs without it: where the allocator
+    // has no more, on the caller's workspace or, where that is none, on one of the size the query tells.
+    void fastest(size_t want, size_t told, const at::Tensor& like, bool have_given) {
+        if (have_given && bytes >= want) return;
+        try {
+            allocate(want, like);
+        } catch (const c10::OutOfMemoryError&) {
+            if (have_given) return;
+            if (told >= want) throw;
+            allocate(told, like);
+        }
+    }
 };
 
 // y of the call: the caller's, or a new [M, N] tensor of x's type
@@ -168,8 +178,8 @@ void need_args(Py_ssize_t n, Py_ssize_t want, const char* name) {
     END_HANDLE_TH_ERRORS
 
 // linear(form, x, bitmap, values, row_offsets, slice_table, a_cat, b_cat, y, workspace, stream)
-//   form  0 plain, 1 with the slice table, 2 two-of-four; y None: allocated and returned; workspace None: allocated
-//   when y is, else none
+//   form  0 plain, 1 with the slice table, 2 two-of-four; y None: allocated and returned, and so is a workspace for the length
+//   of the call where the caller's is none or smaller than the fastest path wants
 PyObject* py_linear(PyObject*, PyObject* const* v, Py_ssize_t n) {
     SALR_TRY
     need_args(n, 11, "linear");
@@ -192,14 +202,13 @@ PyObject* py_linear(PyObject*, PyObject* const* v, Py_ssize_t n) {
     }
     Workspace ws;
     ws.given(v[9]);
-    if (v[8] == Py_None) {
-        // a workspace of the size the query tells, or more, means that memory for a decoded weight is there: where the fastest path
-        // wants a little more the call takes that from the allocator.  Less than the query tells is the caller's choice.
-        const size_t want = salr::linear_call_workspace_bytes(form == 2, l.M, l.K, l.N, l.R);
-        if (v[9] == Py_None ||
-            (ws.bytes < want && ws.bytes >= (form == 2 ? salr_linear_2of4_workspace_bytes(l.M, l.K, l.N, l.R)
-                                                       : salr_linear_workspace_bytes(l.M, l.K, l.N, l.R))))
-            ws.allocate(want, x);
+    if (v[8] == Py_None) {   // (a call that brings its y allocates nothing)
+        // Less than the query tells is the caller's choice of the path without a decoded weight.
+        const size_t told = form == 2 ? salr_linear_2of4_workspace_bytes(l.M, l.K, l.N, l.R) : salr_linear_workspace_bytes(l.M, l.K, l.N, l.R);
+        if (v[9] == Py_None || ws.bytes >= told)
+            ws.fastest(form == 2 ? salr_linear_2of4_workspace_bytes_fastest(l.M, l.K, l.N, l.R)
+                                 : salr_linear_workspace_bytes_fastest(l.M, l.K, l.N, l.R),
+                       told, x, v[9] != Py_None);
     }
     void* stream = stream_of(v[10]);
     salr_status_t st;
@@ -236,8 +245,9 @@ PyObject* py_qsalr_linear(PyObject*, PyObject* const* v, Py_ssize_t n) {
     Workspace ws;
     ws.given(v[9]);
     if (v[9] == Py_None && v[8] == Py_None) {
-        const size_t need = salr::qsalr_call_workspace_bytes(l.M, l.K, l.N, l.R, nnz);
-        ws.allocate(need < 256 ? 256 : need, x);
+        const size_t told = salr_qsalr_linear_workspace_bytes(l.M, l.K, l.N, l.R, nnz);
+        const size_t want = salr_qsalr_linear_workspace_bytes_fastest(l.M, l.K, l.N, l.R, nnz);
+        ws.fastest(want < 256 ? 256 : want, told < 256 ? 256 : told, x, false);
     }
     void* stream = stream_of(v[10]);
     salr_status_t st;

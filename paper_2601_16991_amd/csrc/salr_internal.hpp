@@ -346,18 +346,13 @@ inline size_t frag_base_bytes(int64_t M, int64_t K, int64_t N, int64_t R) {
 inline bool linear_takes_frag(int64_t M, int64_t K, int64_t N, int64_t R, size_t room) {
     return M > kStreamMaxM && !uses_rowtile(M, K, N) && uses_frag(M, K) && room >= frag_base_bytes(M, K, N, R);
 }
-// Workspace with which the layer is fastest: what is allocated for a call that brings none.
+// Workspace with which the layer is fastest (salr_linear_workspace_bytes_fastest).
 inline size_t linear_workspace_bytes_fastest(int64_t M, int64_t K, int64_t N, int64_t R) {
     const size_t told = linear_workspace_bytes(M, K, N, R);
     if (M <= kStreamMaxM || N <= 0 || uses_rowtile(M, K, N) || !uses_frag(M, K)) return told;
     const size_t b = frag_base_bytes(M, K, N, R) + gemm_partial_bytes(M, N, gemm_plan(M, K + adapter_rank_padded(R), N).ksplit);
     return b > told ? b : told;
 }
-
-// The same for a call of the Python binding (two_of_four: salr_sparse_lowrank_linear_2of4), and for one of salr_qsalr_linear; at
-// least what the query functions of the boundary tell.
-size_t linear_call_workspace_bytes(bool two_of_four, int64_t M, int64_t K, int64_t N, int64_t R);
-size_t qsalr_call_workspace_bytes(int64_t M, int64_t K, int64_t N, int64_t R, int64_t nnz);
 
 // The least the layer runs with: where the preferred path decodes the weight into the workspace (large batches), the
 // fused kernel needs the adapter part only.

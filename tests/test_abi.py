@@ -156,6 +156,35 @@ def test_workspace_bytes(lib):
         assert lib.salr_linear_workspace_bytes(M, K, N, R) == _expected_workspace(M, K, N, R), (M, K, N, R)
 
 
+def test_fastest_workspace_bytes(lib):
+    """The size with which the layer is fastest: the told one for small batches; for large ones at least T, and the weight in blocks of
+    16 rows x 32 columns (an even number along the row) with B_cat's blocks behind them."""
+    def query(name, *a):
+        f = getattr(lib, name)
+        f.restype = ctypes.c_size_t
+        return f(*[ctypes.c_int64(v) for v in a])
+
+    told, fast = "salr_linear_workspace_bytes", "salr_linear_workspace_bytes_fastest"
+    for M, K, N, R in [(1, 4096, 4096, 32), (64, 4000, 100, 5), (128, 4096, 4096, 32), (16, 512, 512, 0)]:
+        assert query(fast, M, K, N, R) == query(told, M, K, N, R)
+        assert query("salr_linear_2of4_workspace_bytes_fastest", M, K, N, R) == query("salr_linear_2of4_workspace_bytes", M, K, N, R)
+        assert query("salr_qsalr_linear_workspace_bytes_fastest", M, K, N, R, 1000) == query("salr_qsalr_linear_workspace_bytes", M, K, N, R, 1000)
+    for M, K, N, R in [(300, 2720, 2731, 24), (300, 2752, 2731, 24), (512, 4096, 2731, 0), (65, 32, 1, 0), (2048, 4128, 14336, 32), (4096, 28672, 8192, 64)]:
+        rp = (R + 31) // 32 * 32
+        blocks = (N + 15) // 16 * ((K + 63) // 64 + (rp + 63) // 64) * 2048
+        least = query("salr_linear_workspace_bytes_min", M, K, N, R)
+        assert query(fast, M, K, N, R) >= max(query(told, M, K, N, R), blocks + M * rp * 2) and query(told, M, K, N, R) >= least
+        assert query("salr_qsalr_linear_workspace_bytes_fastest", M, K, N, R, N * K // 2) >= query(fast, M, K, N, R)
+        assert query("salr_qsalr_linear_workspace_bytes_fastest", M, K, N, R, N * K // 2) >= query("salr_qsalr_linear_workspace_bytes", M, K, N, R, N * K // 2)
+    # a 2:4 layer: the shapes that are passed on, and those with kernels of their own
+    assert query("salr_linear_2of4_workspace_bytes_fastest", 300, 2720, 2731, 24) == query(fast, 300, 2720, 2731, 24)
+    assert query("salr_linear_2of4_workspace_bytes_fastest", 2048, 4096, 14336, 32) == query("salr_linear_2of4_workspace_bytes", 2048, 4096, 14336, 32)
+    for bad in [(0, 64, 8, 4), (-1, 64, 8, 4), (300, 40, 8, 4), (300, 64, 0, 4), (300, 64, 8, 257), (300, 64, 8, -1)]:
+        assert query(fast, *bad) == 0 and query("salr_linear_2of4_workspace_bytes_fastest", *bad) == 0
+        assert query("salr_qsalr_linear_workspace_bytes_fastest", *bad, 10) == 0
+    assert query("salr_qsalr_linear_workspace_bytes_fastest", 300, 64, 8, 4, -1) == 0
+
+
 def test_host_validation_rejects_before_launch(lib):
     import paper_2601_16991_amd as salr
     fake = 0x1000  # never dereferenced: every call below fails validation first

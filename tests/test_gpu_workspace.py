@@ -1,0 +1,106 @@
+"""Which memory a large-batch call uses: the size that the query for the fastest path tells is all it needs, through the boundary and in
+Python, and a Python call whose caller brings less still runs where torch's allocator has no more to give.  Results against the fp64
+CPU oracle (max |Y - Y_ref| <= 1e-2 * max |Y_ref|); calls on the same path bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import salr_workloads as wl
+from gpu_util import dev, to_dev_u16, to_dev_u32, y_to_f64
+
+pytestmark = pytest.mark.gpu
+
+REL_TOL = 1e-2
+
+
+def _layer(M, K, N, R):
+    seed = M + K + N
+    x, w = wl.gaussian_bf16((M, K), 1.0, seed), wl.gaussian_bf16((N, K), 0.02, seed + 1)
+    w[np.random.default_rng(seed).random((N, K)) >= 0.5] = 0
+    a, b = (wl.gaussian_bf16((K, R), 0.05, seed + 2), wl.gaussian_bf16((R, N), 0.05, seed + 3)) if R else (None, None)
+    rb, rv, ro = oracle.encode(w)
+    args = [to_dev_u16(x), to_dev_u32(rb), to_dev_u16(rv), to_dev_u32(ro), None if a is None else to_dev_u16(a),
+            None if b is None else to_dev_u16(b)]
+    return args, oracle.linear(x, w, a, b), rv.size
+
+
+def _ok(y, ref):
+    return float(np.max(np.abs(y_to_f64(y) - ref))) <= REL_TOL * float(np.max(np.abs(ref)))
+
+
+def _bytes(n):
+    return torch.empty(n, dtype=torch.uint8, device=dev())
+
+
+# rows that end in half a step of 64 columns, outputs that are no multiple of 16, both, neither
+@pytest.mark.parametrize("M,K,N,R", [(300, 2720, 267, 24), (130, 96, 300, 0), (200, 4096, 267, 0), (300, 544, 100, 65), (300, 512, 528, 8)])
+def test_fastest_size_is_enough(M, K, N, R):
+    """Through the boundary it gives what a call without a workspace gives, bit for bit, and nothing behind it is touched; in
+    Python the call then allocates its result and nothing else."""
+    import paper_2601_16991_amd as salr
+    args, ref, nnz = _layer(M, K, N, R)
+    size = salr.salr_linear_workspace_bytes_fastest(M, K, N, R)
+    print(f"[workspace] M{M} K{K} N{N} R{R}: told {salr.salr_linear_workspace_bytes(M, K, N, R)}, fastest {size}", flush=True)
+    alone = salr.linear(*args)
+    buf = torch.full((size + 4096,), 0x5A, dtype=torch.uint8, device=dev())
+    y = torch.empty((M, N), dtype=torch.int16, device=dev())
+    salr.salr_sparse_lowrank_linear(*args, y, buf[:size])
+    torch.cuda.synchronize()
+    assert torch.equal(y, alone) and _ok(y, ref) and bool((buf[size:] == 0x5A).all())
+    before = torch.cuda.memory_stats()["allocation.all.allocated"]
+    y = salr.linear(*args, buf[:size])
+    assert torch.cuda.memory_stats()["allocation.all.allocated"] == before + 1
+    torch.cuda.synchronize()
+    assert torch.equal(y, alone)
+
+
+@pytest.mark.parametrize("M,K,N,R", [(300, 2720, 267, 24), (200, 4096, 267, 0), (300, 544, 100, 8)])
+def test_fastest_size_is_enough_for_four_bit_values(M, K, N, R):
+    import paper_2601_16991_amd as salr
+    args, _, nnz = _layer(M, K, N, R)
+    codes, scales = salr.nf4_quantize(args[2])
+    qargs = [args[0], args[1], codes, scales, args[3], nnz, args[4], args[5]]
+    size = salr.salr_qsalr_linear_workspace_bytes_fastest(M, K, N, R, nnz)
+    print(f"[workspace] quantised M{M} K{K} N{N} R{R}: fastest {size}", flush=True)
+    alone = salr.qsalr_linear(*qargs)
+    buf = torch.full((size + 4096,), 0x5A, dtype=torch.uint8, device=dev())
+    y = torch.empty((M, N), dtype=torch.int16, device=dev())
+    salr.salr_qsalr_linear(*qargs, y, buf[:size])
+    torch.cuda.synchronize()
+    assert torch.equal(y, alone) and bool((buf[size:] == 0x5A).all())
+
+
+@pytest.mark.parametrize("form", ["told", "none", "quantised"])
+def test_runs_where_the_allocator_has_no_more(form):
+    """The decoded weight of this layer takes 34 MB and its split sums more; the allocator may hand out the result and little else (in
+    the last form the told workspace as well, 17 MB of values)."""
+    import paper_2601_16991_amd as salr
+    M, K, N, R = 130, 4128, 4096, 16
+    args, ref, nnz = _layer(M, K, N, R)
+    told = salr.salr_linear_workspace_bytes(M, K, N, R)
+    ws = _bytes(told)
+    if form == "quantised":
+        codes, scales = salr.nf4_quantize(args[2])
+        q = salr.nf4_dequantize(codes, scales, nnz)
+        plain = salr.linear(args[0], args[1], q, *args[3:])   # the same products on the dequantised values
+        del q
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    total = torch.cuda.mem_get_info()[1]
+    more = 26 << 20   # (small allocations come in pieces of 2 and 20 MB)
+    torch.cuda.set_per_process_memory_fraction((torch.cuda.memory_reserved() + more) / total)
+    try:
+        print(f"[workspace] {form} with {more >> 20} MB to allocate", flush=True)
+        if form == "quantised":
+            y = salr.qsalr_linear(args[0], args[1], codes, scales, args[3], nnz, args[4], args[5])
+        else:
+            y = salr.linear(*args, ws if form == "told" else None)
+        torch.cuda.synchronize()
+    finally:
+        torch.cuda.set_per_process_memory_fraction(1.0)
+    if form == "quantised":
+        scale = float(plain.view(torch.bfloat16).float().abs().max())
+        assert float((y.view(torch.bfloat16).float() - plain.view(torch.bfloat16).float()).abs().max()) <= REL_TOL * scale
+    else:
+        assert _ok(y, ref)
