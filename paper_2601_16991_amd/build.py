@@ -57,7 +57,7 @@ def _binding_commands() -> list[list[str]]:
     from torch.utils import cpp_extension as ext
     import torch
     obj = os.path.join(OBJ_DIR, "salr_binding.o")
-    includes = ext.include_paths("cuda") + [sysconfig.get_paths()["include"], os.path.join(ROOT, "include")]
+    includes = ext.include_paths("cuda") + [sysconfig.get_paths()["include"], os.path.join(ROOT, "include"), CSRC]
     cxx = os.environ.get("CXX", "g++")
     compile_ = [cxx, "-O2", "-std=c++17", "-fPIC", "-fvisibility=hidden", "-Wno-attributes", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
                 f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
@@ -67,22 +67,29 @@ def _binding_commands() -> list[list[str]]:
     return [compile_, link]
 
 
-def build(verbose: bool = False, only_changed: bool = False, jobs: int | None = None) -> str:
+def _compile_commands(only_changed: bool) -> tuple[list[list[str]], list[str]]:
+    """Compile lines of everything, or of what is older than its source or any header; and the library's objects."""
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-    os.makedirs(OBJ_DIR, exist_ok=True)
     newest_header = max(os.path.getmtime(h) for h in _headers())
+
+    def needed(obj: str, src: str) -> bool:
+        return not (only_changed and os.path.exists(obj) and os.path.getmtime(obj) > max(os.path.getmtime(src), newest_header))
+
     todo, objects = [], []
+    if needed(os.path.join(OBJ_DIR, "salr_binding.o"), BINDING_SRC):
+        todo.append(_binding_commands()[0])   # the longest one first
     for src in sources():
         obj = os.path.join(OBJ_DIR, os.path.basename(src)[:-4] + ".o")
         objects.append(obj)
-        fresh = os.path.exists(obj) and os.path.getmtime(obj) > max(os.path.getmtime(src), newest_header)
-        if not (only_changed and fresh):
+        if needed(obj, src):
             todo.append([hipcc, *HIPCC_FLAGS, "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-c", "-o", obj, src])
-    compile_binding, link_binding = _binding_commands()
-    obj = os.path.join(OBJ_DIR, "salr_binding.o")
-    header = os.path.join(ROOT, "include", "salr.h")
-    if not (only_changed and os.path.exists(obj) and os.path.getmtime(obj) > max(os.path.getmtime(BINDING_SRC), os.path.getmtime(header))):
-        todo.insert(0, compile_binding)   # the longest one first
+    return todo, objects
+
+
+def build(verbose: bool = False, only_changed: bool = False, jobs: int | None = None) -> str:
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    os.makedirs(OBJ_DIR, exist_ok=True)
+    todo, objects = _compile_commands(only_changed)
     if jobs is None:
         jobs = min(8, max(1, len(os.sched_getaffinity(0))))
     if verbose:
@@ -91,7 +98,9 @@ def build(verbose: bool = False, only_changed: bool = False, jobs: int | None = 
     with ThreadPoolExecutor(max_workers=jobs) as pool:
         outs = list(pool.map(_run, todo))
     link = [hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objects]
-    for cmd in (link, link_binding):
+    # The interpreter's own symbols keep the linker from refusing undefined ones in the binding: load it once, all symbols now.
+    load_binding = [sys.executable, "-c", f"import ctypes, os, torch; ctypes.CDLL({BINDING!r}, mode=os.RTLD_NOW)"]
+    for cmd in (link, _binding_commands()[1], load_binding):
         if verbose:
             print(" ".join(cmd), flush=True)
         outs.append(_run(cmd))

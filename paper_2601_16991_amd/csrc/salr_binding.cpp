@@ -12,13 +12,7 @@
 #include <torch/csrc/autograd/python_variable.h>
 
 #include "salr.h"
-
-namespace salr {   // the two halves of the encoder (see salr_internal.hpp)
-hipError_t launch_encode_index(const uint16_t* w, int64_t rows, int64_t cols, uint32_t* bitmap, uint32_t* row_offsets,
-                               uint32_t* nnz_host, hipStream_t stream);
-hipError_t launch_encode_values(const uint16_t* w, int64_t rows, int64_t cols, const uint32_t* bitmap, const uint32_t* row_offsets,
-                                uint16_t* values, int64_t capacity, hipStream_t stream);
-}  // namespace salr
+#include "salr_internal.hpp"   // the two halves of the encoder
 
 namespace {
 

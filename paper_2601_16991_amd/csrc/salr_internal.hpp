@@ -2,7 +2,9 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
-#include <hip/hip_ext.h>
+#ifdef __HIPCC__
+#include <hip/hip_ext.h>   // (SALR_LAUNCH; not for a host compiler)
+#endif
 #include <stddef.h>
 #include <stdint.h>
 
