@@ -225,8 +225,8 @@ salr_status_t salr_sparse_lowrank_linear(const uint16_t* x, int64_t M, int64_t K
  *
  * Limit: sizes for which neither salr_linear_workspace_bytes(M, K, N, R) nor salr_linear_workspace_bytes_min(M, K, N,
  * R) fits SALR_NOALLOC_SCRATCH_BYTES are refused with SALR_ERR_CAPACITY before anything is enqueued.  Decode-sized
- * batches fit; large batches, whose preferred path decodes the weight into a dense scratch matrix, run the
- * fused kernel of salr_linear_workspace_bytes_min instead as long as their adapter intermediates fit.
+ * batches fit; large batches, whose preferred path decodes the weight into scratch memory, take that path where the array
+ * has room for it and else run the kernel of salr_linear_workspace_bytes_min as long as their adapter intermediates fit.
  * The device that is current when the call is made must be the one `stream` belongs to; the first call on a device
  * looks up that device's copy of the array (no allocation; make it outside a graph capture).
  * All calls on one GPU share that GPU's array: calls that may overlap on one GPU (different streams without
@@ -338,7 +338,8 @@ salr_status_t salr_sparse_lowrank_linear_2of4(const uint16_t* x, int64_t M, int6
  *   bitmap, values, row_offsets, a_cat, b_cat, R   as for salr_sparse_lowrank_linear (the weight is needed for dX only)
  *   dx, da, db   out  any of them may be NULL: that gradient is not computed
  *   workspace    --   at least salr_linear_backward_workspace_bytes(M, K, N, R, dx != NULL, da != NULL || db != NULL)
- *                     bytes, 256-byte aligned (for dX it holds the decoded weight and its transpose, 4 N K bytes)
+ *                     bytes, 256-byte aligned (for dX most of it is 4 N K bytes, of which the call needs half for the
+ *                     transposed weight; split sums of dX take what is over)
  *
  * Constraints: K % 32 == 0 (SHAPE); N % 64 == 0 for dX, N % 32 == 0 with adapters, M % 32 == 0 for dA / dB,
  * R <= 256 (UNSUPPORTED otherwise).  The workspace query returns 0 for sizes the call would refuse.

@@ -244,8 +244,8 @@ hipError_t launch_gemm_2of4(const LinearArgs& a, hipStream_t stream, const Timin
     const int64_t t256 = m_tiles * ((a.N + 255) / 256), t224 = m_tiles * ((a.N + 223) / 224);
     const int64_t cost256 = (t256 + 255) / 256 * 256, cost224 = (t224 + 255) / 256 * 224;
     // The weight in sparse operand order first (salr_gemm.hip): a pass over the weight, 0.49 us per million entries, for a matrix
-    // stage a quarter faster, worth it from about 1200 tokens.  2048 x 4096 x 14336 237 -> 197 us, 4096 x 4096 x 8192 239 -> 189,
-    // 3000 x 1024 x 8192 78 -> 73; 1024 x 4096 x 28672 181 -> 203.
+    // stage a quarter faster.  Calls on the packed format / in operand order, microseconds: 2048 x 4096 x 14336 207 / 182,
+    // 4096 x 4096 x 8192 234 / 184, 3000 x 1024 x 8192 76 / 73, 1500 x 4096 x 14336 194 / 172; 1024 x 4096 x 28672 204 / 226.
     const size_t offset = twostage_dense_offset(a.M, a.K, a.R);
     if (t256 >= kGemm2of4BigTilesMin && a.M >= kSparseOrderMinM && a.K <= kFragMaxColumns && a.room >= offset + sparse_weight_bytes(a.K, a.N, a.R))
         launch_sparse_gemm(a, reinterpret_cast<uint16_t*>(reinterpret_cast<char*>(a.t) + offset), cost224 < cost256, ev, stream);

@@ -100,7 +100,7 @@ constexpr int kMaxRankPadded = 256;  // R <= 256: pitch of the T tile the stream
 
 // Large-batch path: M > kStreamMaxM decodes the weight once into scratch memory in MFMA operand order, then runs a dense
 // MFMA GEMM on it (salr_gemm.hip; k-steps of 64, the 256 rows of a tile of X lie within 2 GB).  Wherever the call's workspace has room
-// for it: 300 x 2720 x 2731 36 us against 113 on the generic kernel, 2048 x 4096 x 14336 250 against 292 on the next one.
+// for it: 300 x 2720 x 2731 39 us against 111 on the generic kernel, 2048 x 4096 x 14336 249 against 284 on the next one.
 constexpr int64_t kFragMaxColumns = 1 << 22;
 inline bool uses_frag(int64_t M, int64_t K) { return M > kStreamMaxM && K >= 32 && K % 32 == 0 && K <= kFragMaxColumns; }
 // The same in two stages with a row-major copy (salr_linear_twostage.hip), K % 64 == 0: what salr_linear_workspace_bytes sizes a
@@ -213,9 +213,12 @@ inline int64_t splitk_slice(int64_t count) { return (count + 3) / 4 * 4; }
 // stage's time in microseconds.  A tile has the time of a k-step on a CU that is full of its workgroups (per workgroup: what
 // the matrix cores sustain on data at this chip's power), the time of one that is alone (latency, or the same where a CU
 // holds one), and what a workgroup spends outside its loop (first tiles, results; half of it hidden behind the loop of a
-// neighbour on the CU).  A split adds the partial sums' way through memory and one launch.  The figures are fitted to a sweep
-// of 21 layers from 512 to 28672 wide at 130 to 4096 tokens over all tiles and splits, where the choice costs 0.4 % on average
-// and 8 % at worst against the best tile.  partial_room: bytes there are for the partial outputs.
+// neighbour on the CU).  A split adds the partial sums' way through memory and one launch.  Against all tiles and splits on 126
+// points (21 layers from 512 to 28672 wide, 130 to 4096 tokens; profiles/linear_large_batch_tile_sweep.txt) the choice is the best
+// at 68 and within 1 % at 79; its stage takes 3.7 % more on average.  The misses: splits of layers of a few million entries at 300
+// to 512 tokens (up to 5 us of stage, -1.5 to +2.3 us of the call), and weights of 235 million entries at 130 and 300 tokens,
+// where it takes rows of 64 or 128 and tiles of 256 are faster (30 to 61 us of a call of 347 to 440).  partial_room: bytes there
+// are for the partial outputs.
 struct GemmPlan {
     int mt, nt, ksplit;
 };

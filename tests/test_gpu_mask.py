@@ -110,7 +110,8 @@ def test_mask_nm_q_proj_2_of_4():
 @pytest.mark.parametrize("rows,cols,keep", [(5, 8200, 4100), (3, 14336, 14335), (5, 14336, 1), (6, 14344, 3), (3, 28672, 9000),
                                             (2, 28664, 0), (2, 11008, 11008), (3, 16384, 8192)])
 def test_mask_rows_long_rows_one_wave_per_row(rows, cols, keep):
-    """The register counts above 8192 columns, at their edges; the search starts from the row's first columns, so rows whose
+    """The register counts above 8192 columns, at their edges (rows of more than 14336 columns are too few here for them and take
+    the workgroup kernel; see test_mask_rows_longest_rows); the search starts from the row's first columns, so rows whose
     start says nothing about the rest (constant, empty, infinite) as well."""
     w = wl.gaussian_bf16((rows, cols), 0.02, cols + keep)
     _check_rows(w, keep, "long rows, gaussian")
