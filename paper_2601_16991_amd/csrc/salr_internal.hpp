@@ -96,6 +96,7 @@ extern thread_local TimingEvents g_timing_events;
 // Small-batch path: M <= kStreamMaxM; T = X * A_cat arrives as kStreamTSlices split-K partials (fp32).
 constexpr int64_t kStreamMaxM = 64;
 constexpr int kStreamTSlices = 16;
+constexpr int kRowtileTSlices = 4;   // at most, see rowtile_plan
 constexpr int kMaxRankPadded = 256;  // R <= 256: pitch of the T tile the streaming kernels keep in LDS
 
 // Large-batch path: M > kStreamMaxM decodes the weight once into scratch memory in MFMA operand order, then runs a dense
@@ -261,6 +262,8 @@ inline GemmPlan gemm_plan(int64_t M, int64_t Kt, int64_t N, size_t partial_room 
 // 45 %), from 9 tokens on where the layer has thousands of rows; below that the small-batch kernel, whose waves
 // run independently of each other, is as fast or faster.
 constexpr int64_t kRowtileMaxM = 128;
+constexpr int kRowtileMaxSplit = 32;
+constexpr int64_t kRowtileMaxColumns = 1 << 22;   // 32-bit offsets into X and a wave's rows of the weight
 inline int rowtile_ksplit(int64_t M, int64_t K, int64_t N) {
     const int64_t tiles = (N + 127) / 128, chunks = K / 128;
     if (N % 4 != 0) return 1;   // the reducing pass stores four outputs per thread
@@ -280,6 +283,50 @@ inline bool uses_rowtile(int64_t M, int64_t K, int64_t N) {
 inline size_t rowtile_t_bytes(int64_t M, int64_t K, int64_t R) {
     if (R <= 0) return 0;
     return round_up_256((size_t)kStreamTSlices * (size_t)M * (size_t)adapter_rank_padded(R) * sizeof(float));
+}
+// T as the launch of the row-tiled kernel itself leaves it, ahead of the partial outputs
+inline size_t rowtile_t_out_bytes(int64_t M, int64_t R) {
+    return R > 0 ? round_up_256((size_t)kRowtileTSlices * (size_t)M * (size_t)adapter_rank_padded(R) * sizeof(float)) : 0;
+}
+// fp32 partial outputs of one slice, rows of whole vectors of four
+inline int64_t rowtile_pitch(int64_t N) { return (N + 3) / 4 * 4; }
+inline size_t rowtile_partial_bytes(int64_t M, int64_t N) { return (size_t)M * (size_t)rowtile_pitch(N) * sizeof(float); }
+// How the row-tiled kernel cuts its work: K over `ksplit` workgroups per 128 rows, and X A_cat over `t_slices` workgroups per 16
+// tokens and 16 ranks of the same launch.  The least of a model of the call's time in microseconds: the launch and the start of a
+// slice, rounds of 256 workgroups, one per CU, the chunks of a slice, the popcounts of the bitmap left of it, and the summing
+// launch, which there is when K is split or there are adapters.  Its figures are those of up to 16, 32, 64 and 128 tokens
+// on 4096 x 14336 (2 slices: 22.4, 24.9, 29.9 and 40 us; 4: 26.7, 29.0, 36.1; 1: 35.1, 38.5, 46.0, 59) and 14336 x 4096.
+// partial: fp32 partial outputs in the workspace.  Without room for one slice's (`room` bytes) T comes from a launch in front and
+// the only slice adds the adapters itself.
+struct RowtilePlan {
+    int ksplit = 1, t_slices = 1;
+    bool partial = false;
+};
+inline RowtilePlan rowtile_plan(int64_t M, int64_t K, int64_t N, int64_t R, size_t room) {
+    const int64_t tiles = (N + 127) / 128, chunks = (K + 127) / 128, t_units = R > 0 ? adapter_rank_padded(R) / 16 * ((M + 15) / 16) : 0;
+    const double step = M <= 16 ? 0.70 : M <= 32 ? 0.85 : M <= 64 ? 1.05 : 1.50;
+    const size_t t_bytes = rowtile_t_out_bytes(M, R), one = rowtile_partial_bytes(M, N);
+    RowtilePlan best;
+    double best_cost = 1e300;
+    for (int ks = 1; ks <= kRowtileMaxSplit && ks <= chunks; ++ks) {
+        const bool partial = ks > 1 || R > 0;
+        if (partial && t_bytes + ks * one > room) break;
+        for (int ts = R > 0 ? kRowtileTSlices : 1; ts >= 1; ts /= 2) {
+            const int64_t rounds = (tiles * ks + t_units * ts + 255) / 256;
+            double main = 5.0 + (double)(rounds * ((chunks + ks - 1) / ks)) * step + (double)(rounds - 1) * 2.5 +
+                          0.07 * (double)(chunks - chunks / ks);
+            const double t = R > 0 ? 3.0 + (double)((K / 32 + 32 * ts - 1) / (32 * ts)) * 1.2 : 0.0;   // eight waves, four steps at a time
+            if (main < t) main = t;
+            const double cost = main + (partial ? 4.5 + (double)ks * (double)M * (double)N * 2e-6 : 0.0);
+            if (cost < best_cost) {
+                best_cost = cost;
+                best.ksplit = ks;
+                best.t_slices = ts;
+                best.partial = partial;
+            }
+        }
+    }
+    return best;
 }
 inline size_t rowtile_workspace_bytes(int64_t M, int64_t K, int64_t N, int64_t R) {
     const int ks = rowtile_ksplit(M, K, N);

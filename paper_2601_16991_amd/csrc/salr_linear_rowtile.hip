@@ -1,307 +1,399 @@
-// Row-tiled streaming path of the SALR linear (paper Sec. 3.2 / 3.3) for layers with many rows and batches of up to
-// 128 tokens: one pass over the compressed weight, like the small-batch kernel, but with the activations shared
-// inside the workgroup instead of every wave fetching its own.
+// Row-tiled streaming path of the SALR linear (paper Sec. 3.2 / 3.3) for batches of up to 128 tokens: one pass over the
+// compressed weight, the activations shared inside a workgroup through LDS.
 //
-// A workgroup owns 128 consecutive rows of What and one slice of K; wave w owns rows 16 w .. 16 w + 15 of the tile
-// for the whole slice.  The waves walk the slice in step, chunk by chunk (128 columns):
-//   weights      as in the small-batch kernel: lane (n = lane%16, g = lane/16) takes byte g of each bitmap word of
-//                row n; the row's packed values of the chunk (one contiguous piece) are fetched S chunks ahead with
-//                16-byte loads, parked in the wave's LDS slot and expanded by the nibble rule of Sec. 3.3 straight
-//                into the B operand of a 16x16x32 bf16 MFMA;
-//   activations  the chunk's X tile [16 MT rows x 128 columns] is loaded ONCE per workgroup (one 16-byte vector per
-//                thread and 32 rows) ahead into registers, written to LDS one barrier ahead, and read from
-//                there by all eight waves as the A operand.  A wave of the small-batch kernel pulls all of X through the L2 for its 16 rows; here
-//                128 rows share one copy, so a layer of N rows moves N / 128 copies of X instead of N / 16.
-//                16-byte vectors of a row are stored at index v ^ (row % 16): the operand reads of a wave (16 rows,
-//                the same four vectors each) then cover every LDS bank equally.
-//   one barrier per chunk, or per four chunks up to 16 tokens (X tiles of 4 KB): it publishes the next tiles and retires those
-//                just read.  With the waves in step on every chunk of 16 tokens each waited for the slowest one's weights:
-//                16 x 4096 x 14336 34.7 -> 32.9 us a call, 16 x 8192 x 28672 96 -> 88.  At 17 to 32 tokens two chunks per
-//                barrier were no faster (32 x 4096 x 14336 36.3 both ways, 24 x 3072 x 8192 17.6 -> 18.4).
-//   adapters     slice 0 adds the rank steps after its loop: T = X A_cat (summed from the pre-kernel's split-K partials
-//                and rounded to bf16 once) sits in LDS where the X tiles were; every wave multiplies it with the
-//                B_cat columns of its own rows.
-//   output       every wave owns its 16 output columns outright: bf16 to y, or fp32 to partial[slice] when K is split
-//                (not enough 128-row tiles to fill the chip twice over), summed in slice order by the reducing pass.
-// Tried and left out: 16 waves per workgroup walking the two halves of K side by side and adding them up through
-// LDS, in place of a split of K over two workgroups per CU.  It saves the reducing launch, but the barrier then
-// holds 16 waves in step, and on the 70B gate/up shape it was 10 to 18 % slower than the split.
+// A workgroup of eight waves has a CU to itself and takes 128 consecutive rows of What and one slice of K; wave w owns rows
+// 16 w .. 16 w + 15 of them for the whole slice.
+//   weights      the wave's own stream (salr_row_stream.hpp): bitmap words four chunks at a time, packed values one unit (a pair of
+//                chunks, or one) ahead in registers, parked in the wave's LDS slot, expanded straight into an MFMA operand.
+//   activations  a panel of X (64 KB: 16 chunks of 16 tokens, 4 of 64) is copied to LDS once per workgroup, the next one on its way
+//                in registers meanwhile.  No barrier inside a panel: the waves drift apart and the requests of one meet the
+//                expansion of another.
+//   adapters     T = X A_cat needs all of K before it can be used, so it belongs to neither side of a split of K: the first
+//                workgroups of the same launch write its split-K partial sums, and the launch that adds up the slices' partial
+//                outputs multiplies T with B_cat and adds that too.  (With a launch of its own in front it cost 4.4 us of the
+//                34.9 us of a 16 x 4096 x 14336 call.)
+// The work is cut so that there is one workgroup per CU and one round of them where that can be (rowtile_plan): a slice starts
+// with two dependent round trips to memory and the popcounts of the bitmap left of it, 4 us, and the longer a slice the less often
+// that is paid.  Two workgroups per CU (half the slice, 128 registers a wave) hide each other's start, but spill: 30.5 us a call.
+//
+// Measured, whole calls at p = .5, rank 32, before (two workgroups per CU, a barrier per chunk or per four, T in a launch of its own)
+// and now: 16 x 4096 x 14336 34.9 -> 22.4 us, 32 tokens 36.3 -> 24.9, 64 tokens 47.7 -> 29.9, 128 tokens 52.8 -> 40; 64 x 14336 x 4096
+// 56.7 -> 35.3; 16 x 8192 x 28672 92 -> 65.  The bytes of the first take 13 us at what a large copy reaches; its loop runs at 4.6 TB/s.
+// Tried and left out: packed values two units ahead instead of one (+6 %); 32 weight rows per wave, which halves the operand
+// reads of X (+18 % at 16 tokens: half as many slices' starts overlap); seven waves, so that 256 instead of 224
+// workgroups share the rows of that layer (level); values fetched as whole 256-byte runs of a row, half as many cycles of the
+// address unit (the transposition into conflict-free LDS columns then meets conflicts of its own).
 #include <hip/hip_ext.h>
+#include <type_traits>
 
-#include "salr_device.hpp"
 #include "salr_internal.hpp"
-#include "salr_linear_common.hpp"
+#include "salr_row_stream.hpp"
 
 namespace salr {
 
 constexpr int kRtWaves = 8;
-constexpr int kRtThreads = kRtWaves * 64;
-constexpr int kRtChunkWords = 4;      // bitmap words per row per chunk
-constexpr int kRtChunkCols = 128;
-constexpr int kRtSlotDwords = 68;     // LDS per row per chunk: 17 vectors of 16 B (128 values + misalignment)
+constexpr int kRtThreads = 64 * kRtWaves;
 
-struct RowStage {
-    uint4 bm;         // the chunk's 4 bitmap words of this lane's row
-    uint4 vq[3];      // this lane's share of the first 12 vectors of the row's packed-value piece
-    uint32_t off;     // element offset of the piece inside its first 16-byte vector
-    uint32_t nv;      // vectors in the piece
-    uint32_t vbase;   // index of its first vector in `values`
+// ---- T = X A_cat, split-K partials: one workgroup sums slice b of K for 16 rows of X and 16 ranks
+template <int W>
+__device__ __forceinline__ void adapter_partial_block(const uint16_t* __restrict__ x, int M, int64_t K,
+                                                      const uint16_t* __restrict__ a_cat, int R, int Rpad, int block, int slices,
+                                                      float* __restrict__ t_partial, float* red, int tid) {
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int i16 = lane & 15, g = lane >> 4;
+    const int rank_tiles = Rpad >> 4;
+    const int b = block % slices, rt = block / slices % rank_tiles, mt = block / (slices * rank_tiles);
+    const int units = (int)(K >> 5);   // k-steps of 32 columns
+    const int u_begin = units * b / slices, u_end = units * (b + 1) / slices;
+    const int r = 16 * rt + i16, m = 16 * mt + i16;
+    const int r_c = r < R ? r : R - 1;   // padding columns read a valid one and are zeroed at the store
+    const uint16_t* xr = x + (int64_t)(m < M ? m : M - 1) * K + 8 * g;
+    constexpr int kBatch = 4;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    for (int u0 = u_begin + wave; u0 < u_end; u0 += W * kBatch) {
+        uint4 aq[kBatch], bq[kBatch];
+#pragma unroll
+        for (int t = 0; t < kBatch; ++t) {
+            const int u = u0 + W * t < u_end ? u0 + W * t : u_end - 1;
+            aq[t] = *reinterpret_cast<const uint4*>(xr + 32 * (int64_t)u);
+            uint32_t e[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) e[j] = a_cat[(32 * (int64_t)u + 8 * g + j) * R + r_c];
+            bq[t] = make_uint4(e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16), e[6] | (e[7] << 16));
+        }
+#pragma unroll
+        for (int t = 0; t < kBatch; ++t)
+            if (u0 + W * t < u_end)   // uniform
+                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(aq[t]), as_bf16x8(bq[t]), acc, 0, 0, 0);
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) red[(wave * 4 + e) * 64 + lane] = acc[e];
+    __syncthreads();
+    for (int i = tid; i < 256; i += 64 * W) {   // lane holds T[16 mt + 4 (lane / 16) + e][16 rt + lane % 16]
+        const int l = i & 63, e = i >> 6;
+        float s = 0.f;
+#pragma unroll
+        for (int w = 0; w < W; ++w) s += red[(w * 4 + e) * 64 + l];
+        const int mm = 16 * mt + 4 * (l >> 4) + e, rr = 16 * rt + (l & 15);
+        if (mm < M) t_partial[((int64_t)b * M + mm) * Rpad + rr] = rr < R ? s : 0.f;
+    }
+}
+
+// four consecutive outputs of row m
+__device__ __forceinline__ void store_four(uint16_t* __restrict__ y, int M, int64_t N, int m, int64_t col, const f32x4& v) {
+    uint16_t* out = y + (int64_t)m * N + col;
+    const uint32_t lo = f32_to_bf16_rne(v[0]) | ((uint32_t)f32_to_bf16_rne(v[1]) << 16);
+    const uint32_t hi = f32_to_bf16_rne(v[2]) | ((uint32_t)f32_to_bf16_rne(v[3]) << 16);
+    if (N % 4 == 0) {
+        if (col < N) *reinterpret_cast<uint2*>(out) = make_uint2(lo, hi);
+    } else {
+        if (col < N) out[0] = (uint16_t)lo;
+        if (col + 1 < N) out[1] = (uint16_t)(lo >> 16);
+        if (col + 2 < N) out[2] = (uint16_t)hi;
+        if (col + 3 < N) out[3] = (uint16_t)(hi >> 16);
+    }
+}
+
+struct RowtileArgs {
+    int t_blocks;        // leading workgroups that compute t_out
+    int tiles, ksplit, t_slices;
+    float* t_out;        // split-K partials of T written by this launch (kRowtileTSlices)
+    const float* t_in;   // or those of an earlier one (kStreamTSlices): slice 0 adds the adapters
+    float* partial;      // [ksplit, M, pitch] fp32, or null: y
+    int64_t pitch;
 };
 
-// a native vector type that the compiler keeps in registers
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ uint32_t popc4(const uint4& q) { return __popc(q.x) + __popc(q.y) + __popc(q.z) + __popc(q.w); }
-
-// MT m-tiles of 16 rows (M <= 16 MT), S chunks of packed values in flight per wave.  K % 128 == 0.  Up to 4 m-tiles
-// the kernel keeps to 128 registers so that two workgroups share a CU and run through each other's barriers.
-template <int MT, int S>
-__global__ __launch_bounds__(kRtThreads, MT <= 4 ? 4 : 2) void linear_rowtile_kernel(
+// MT tiles of sixteen rows of X (M <= 16 MT).  kRagged: K is no multiple of 128.
+template <int MT, bool kRagged>
+__global__ __launch_bounds__(kRtThreads, 2) void linear_rowtile_kernel(
     const uint16_t* __restrict__ x, int M, int64_t K, int64_t N, const uint32_t* __restrict__ bitmap,
-    const uint16_t* __restrict__ values, const uint32_t* __restrict__ row_offsets, const float* __restrict__ t_partial,
-    const uint16_t* __restrict__ b_cat, int R, int Rpad, int ksplit, uint16_t* __restrict__ y, float* __restrict__ y_partial,
-    const uint32_t* __restrict__ slice_table) {
-    constexpr int kRows = 16 * MT;                                    // X rows of the tile (M padded)
-    constexpr int kXsElems = kRows * kRtChunkCols;                    // bf16 elements of one X tile
-    constexpr int kBlock = MT == 1 ? 4 : 1;                           // X tiles per barrier
-    constexpr int kRing = kBlock == 1 ? S : 1;                        // blocks of X tiles in registers
-    constexpr int kRound = S > kBlock ? S : kBlock;                   // chunks per round of the loop
-    static_assert(kRound % S == 0 && kRound % (kBlock * kRing) == 0, "a round is whole rings");
-    __shared__ __attribute__((aligned(16))) uint16_t xs[2 * kBlock * kXsElems];
-    __shared__ __attribute__((aligned(16))) uint32_t slots[kRtWaves * 16 * kRtSlotDwords + 8];
-    __shared__ uint32_t lut_all[kRtWaves][kNibbleLutWords];  // one copy per wave: filled and used wave-synchronously
-
+    const uint16_t* __restrict__ values, const uint32_t* __restrict__ row_offsets, const uint32_t* __restrict__ slice_table,
+    const uint16_t* __restrict__ a_cat, const uint16_t* __restrict__ b_cat, int R, int Rpad, uint16_t* __restrict__ y, RowtileArgs p) {
+    constexpr int kTileBytes = 16 * MT * kChunkColumns * 2;           // X of one chunk
+    constexpr int kPanel = 16 / MT;                                   // chunks of X in LDS
+    constexpr int kPanelBytes = kPanel * kTileBytes;                  // 64 KB
+    constexpr bool kPairs = MT <= 4;                                  // units of two chunks (else there are no registers for them)
+    constexpr int kSlotVectors = kPairs ? 12 : 10, kSlotBytes = slot_bytes(kSlotVectors);
+    __shared__ __attribute__((aligned(256))) char lds[256 + kPanelBytes + kRtWaves * kSlotBytes];
     const int tid = threadIdx.x;
+    if ((int)blockIdx.x < p.t_blocks) {   // the same for the whole workgroup
+        adapter_partial_block<kRtWaves>(x, M, K, a_cat, R, Rpad, (int)blockIdx.x, p.t_slices, p.t_out, reinterpret_cast<float*>(lds), tid);
+        return;
+    }
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n = lane & 15;
     const int g = lane >> 4;
-    const int z = blockIdx.y;
-    const int64_t n0 = (int64_t)blockIdx.x * (16 * kRtWaves) + 16 * wave;
-    const int64_t row = n0 + n;
-    // Rows past N (last workgroup only) are computed as copies of row N-1 and dropped at the store: every wave
-    // takes part in every barrier and no load needs a per-lane predicate.
-    const int64_t row_c = row < N ? row : N - 1;
-    const int64_t wpr = K >> 5;
-    const int64_t chunks_total = wpr / kRtChunkWords;
-    const int64_t c_begin = chunks_total * z / ksplit;          // the same for all waves of the workgroup
-    const int64_t c_end = chunks_total * (z + 1) / ksplit;
-    const uint32_t* brow = bitmap + row_c * wpr;
-    uint32_t* lut = lut_all[wave];
+    const int id = (int)blockIdx.x - p.t_blocks;
+    const int z = id / p.tiles, tile = id - z * p.tiles;
+    const int64_t n0 = ((int64_t)tile * kRtWaves + wave) * 16;
+    const int64_t n0_c = n0 < N ? n0 : N;
+    const int row_bytes = (int)(K >> 3);     // of the bitmap
+    const int chunks = (int)((K + kChunkColumns - 1) / kChunkColumns);
+    const int c_begin = (int)((uint32_t)(chunks * z) / (uint32_t)p.ksplit), c_end = (int)((uint32_t)(chunks * (z + 1)) / (uint32_t)p.ksplit);
 
-    uint32_t cur = row_offsets[row_c];  // element index in `values` of the row's next value
-
-    // Chunks past the slice read its last chunk and count as empty.  No load of the stream is conditional: the
-    // compiler can then count the requests that are younger than the one a wave waits for, and leaves them in flight.
-    auto load_bitmap_chunk = [&](int64_t c) -> uint4 {
-        uint4 q = *reinterpret_cast<const uint4*>(brow + (c < c_end ? c : c_end - 1) * kRtChunkWords);
-        const uint32_t keep = c < c_end ? 0xFFFFFFFFu : 0u;
-        q.x &= keep; q.y &= keep; q.z &= keep; q.w &= keep;
-        return q;
+    // ---- the wave's rows of the weight; rows past N read as empty
+    const Buffer bits = make_buffer(bitmap + n0_c * (K >> 5), (uint64_t)(N - n0_c) * row_bytes);
+    const uint32_t bits_lane = (uint32_t)n * row_bytes;
+    // Chunk c starts at column 128 c, the last one of a row of uneven length at K - 128 and its words that belong to the chunk
+    // before count as empty.  Chunks past the slice read as empty.
+    auto chunk_start = [&](int c) -> int { return kRagged && (c + 1) * kChunkColumns > (int)K ? (int)K - kChunkColumns : c * kChunkColumns; };
+    // Bitmap words of four chunks, chunk c + g to lane (n, g): one request of 64 bytes per row.  (One of 16 bytes per row and chunk,
+    // the same to its four lanes, keeps the address unit busy for 31 ns whatever it fetches, this one for 20, a KB in one
+    // piece for 8.)
+    auto load_quad = [&](int c) -> u32x4 {
+        const int ct = c + g;
+        if constexpr (kRagged) {
+            const int start = chunk_start(ct), over = ct * kChunkColumns - start;
+            u32x4 q = buffer_load4(bits, ct < c_end ? bits_lane + (start >> 3) : kPastBuffer);
+            q.x = over > 0 ? 0u : q.x;
+            q.y = over > 32 ? 0u : q.y;
+            q.z = over > 64 ? 0u : q.z;
+            return q;
+        } else {
+            return buffer_load4(bits, ct < c_end ? bits_lane + 16 * ct : kPastBuffer);
+        }
     };
-    uint4 bmq[S];  // bitmap ring: the chunks that are issued next
-#pragma unroll
-    for (int i = 0; i < S; ++i) bmq[i] = load_bitmap_chunk(c_begin + i);
-
-    // ---- X loader: every thread moves kXPer 16-byte units of a block of kBlock tiles
-    constexpr int kXPer = kBlock * kRows * 16 / kRtThreads;
-    static_assert(kXPer * kRtThreads == kBlock * kRows * 16, "the threads cover the block exactly");
-    const uint16_t* xsrc[kXPer];
-    int xdst[kXPer], xtile[kXPer];
-#pragma unroll
-    for (int j = 0; j < kXPer; ++j) {
-        const int idx = tid + kRtThreads * j;
-        const int v = idx % 16;
-        xtile[j] = kBlock == 1 ? 0 : idx / (16 * kRows);
-        const int r = idx / 16 - xtile[j] * kRows;
-        xsrc[j] = x + (int64_t)(r < M ? r : M - 1) * K + 8 * v;   // rows past M repeat row M-1; never stored
-        xdst[j] = xtile[j] * kXsElems + r * kRtChunkCols + 8 * (v ^ (r & 15));
+    u32x4 quad = load_quad(c_begin);
+    const int64_t row = n0 + n;
+    // Index of the row's first value, or of its value at the last start of a table slice that is not behind this slice's; then the
+    // nonzeros from there on (the four lanes of a row share the words).
+    int walk_begin = 0;
+    uint32_t cur;
+    if (slice_table != nullptr) {
+        const int w = kSliceTableSlices * c_begin / chunks;
+        walk_begin = chunks * w / kSliceTableSlices;
+        cur = slice_table[((row < N ? row : N - 1) * kSliceTableSlices + w) * 2];
+    } else {
+        cur = row_offsets[row < N ? row : N];
     }
-    // block j of the slice waits in register set j % kRing until it is written to LDS
-    u32x4 xring[kRing][kXPer];
-    auto load_x = [&](u32x4 (&xr)[kXPer], int64_t c) {   // the block that starts at chunk c
+    const uint32_t first = row_offsets[n0_c] & ~7u;   // the buffer of the wave's values starts here, in elements
+    const uint32_t total = row_offsets[N];
+    constexpr int kWalk = 8;   // requests of a lane in flight
+    u32x4 left[kWalk];
+    auto walk = [&](int c0) {
+#pragma unroll
+        for (int i = 0; i < kWalk; ++i) {
+            const int c = c0 + g + 4 * i;
+            left[i] = u32x4{0, 0, 0, 0};
+            if (c0 + 4 * i < c_begin) left[i] = buffer_load4(bits, c < c_begin ? bits_lane + 16 * c : kPastBuffer);   // uniform
+        }
+    };
+    walk(walk_begin);
+    u32x4 quad_next = load_quad(c_begin + 4);
+
+    // ---- X: every thread moves eight 16-byte units of a panel
+    constexpr int kXPer = kPanelBytes / 16 / kRtThreads;
+    const Buffer xbuf = make_buffer(x, (uint64_t)M * K * 2);
+    const uint32_t lds0 = lds_address(lds), lut = lds0, xs0 = lds0 + 256;
+    const int xv = tid % 16, xr = tid / 16;   // unit j of the thread is vector xv of row (xr + 32 j) % (16 MT) of tile (xr + 32 j) / (16 MT)
+    // Vector v of a row at place p(v) ^ (row % 16), p the order in which a unit's steps read them: the operand reads of a wave then
+    // meet every bank equally.
+    const uint32_t xplace = kPairs ? xv : ((xv & 6) << 1) | ((xv & 1) << 1) | (xv >> 3);
+    u32x4 xring[kXPer];
+    auto load_x = [&](int c) {   // the panel that starts at chunk c
 #pragma unroll
         for (int j = 0; j < kXPer; ++j) {
-            const int64_t ct = kBlock == 1 ? c : c + xtile[j];
-            const int64_t cc = ct < c_end ? ct : c_end - 1;   // past the slice: its last tile (not read)
-            xr[j] = *reinterpret_cast<const u32x4*>(xsrc[j] + cc * kRtChunkCols);
+            const int t = (xr + 32 * j) / (16 * MT), r = (xr + 32 * j) % (16 * MT), ct = c + t, start = chunk_start(ct);
+            bool in = r < M && ct < c_end;
+            if (kRagged) in = in && 8 * xv >= ct * kChunkColumns - start;
+            xring[j] = buffer_load4(xbuf, in ? ((uint32_t)r * (uint32_t)K + start + 8 * xv) * 2 : kPastBuffer);
         }
     };
-    auto store_x = [&](const u32x4 (&xr)[kXPer], int buf) {
+    auto store_x = [&]() {
 #pragma unroll
-        for (int j = 0; j < kXPer; ++j) *reinterpret_cast<u32x4*>(&xs[buf * kBlock * kXsElems + xdst[j]]) = xr[j];
+        for (int j = 0; j < kXPer; ++j) lds_write(xs0 + (xr + 32 * j) * 256 + 16 * (xplace ^ (xr & 15)), xring[j]);
     };
-    if (c_begin < c_end) {
-#pragma unroll
-        for (int d = 0; d < kRing; ++d) load_x(xring[d], c_begin + kBlock * d);
-    }
+    load_x(c_begin);
 
-    // B operand of the first rank step (Sec. 3.2): lane (n, g) holds B_cat[8 g + j][row], j = 0..7
-    const bool adapters = R > 0 && z == 0;
-    auto load_b_cat = [&](int rs) -> uint4 {
-        const int r0 = rs * 32 + 8 * g;
-        uint32_t e[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {  // rows past R meet the zero padding of T; clamp instead of predicating
-            const int r = r0 + j < R ? r0 + j : R - 1;
-            e[j] = (uint32_t)b_cat[(int64_t)r * N + row_c];
-        }
-        return make_uint4(e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16), e[6] | (e[7] << 16));
-    };
-    uint4 bq0 = make_uint4(0, 0, 0, 0);
-    if (adapters) bq0 = load_b_cat(0);
-
-    if (lane < 16) {
+    if (tid < 16) {
         uint32_t a, b;
-        nibble_lut_entry(lane, a, b);
-        lut[2 * lane] = a;
-        lut[2 * lane + 1] = b;
+        nibble_lut_entry(tid, a, b);
+        lds_write(lut + 8 * tid, u32x2{a, b});
     }
-    __builtin_amdgcn_wave_barrier();
-
-    // ---- nonzeros of the row left of the slice: from the layer's slice table when the call has one and the slice
-    // starts where one of the table's eight does (K split 1, 2, 4 or 8 ways); else the 4 lanes of a row share the words,
-    // 8 loads in flight each
-    if (slice_table != nullptr && kSliceTableSlices % ksplit == 0) {   // the same for the whole grid
-        cur = slice_table[((int64_t)row_c * kSliceTableSlices + z * (kSliceTableSlices / ksplit)) * 2];
-    } else {
-        uint32_t before = 0;
-        for (int64_t c0 = 0; c0 < c_begin; c0 += 32) {
-            uint4 q[8];
+    uint32_t before = 0;
+    for (int c0 = walk_begin; c0 < c_begin; c0 += 4 * kWalk) {
+        if (c0 > walk_begin) walk(c0);
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const int64_t c = c0 + g + 4 * i;
-                q[i] = *reinterpret_cast<const uint4*>(brow + (c < c_begin ? c : 0) * kRtChunkWords);
-            }
-#pragma unroll
-            for (int i = 0; i < 8; ++i) before += (c0 + g + 4 * i < c_begin) ? popc4(q[i]) : 0u;
-        }
-        before += __shfl_xor(before, 16, 64);
-        before += __shfl_xor(before, 32, 64);
-        cur += before;
+        for (int i = 0; i < kWalk; ++i) before = popc4(left[i], before);
     }
+    before += __shfl_xor(before, 16, 64);
+    before += __shfl_xor(before, 32, 64);
+    cur += before;
 
-    const uint4* values128 = reinterpret_cast<const uint4*>(values);
-    uint32_t* slot = slots + (wave * 16 + n) * kRtSlotDwords;
+    const Buffer vals = make_buffer(values + first, 2 * (((uint64_t)total + 7) / 8 * 8 - first));
+    uint32_t at_next = 2 * (cur - first);          // byte address of the row's next value
+    // Lane (n, g) expands half g % 2 of a unit (one of a pair of chunks, or half of a chunk), the bytes g / 2, g / 2 + 2, .. of it: the
+    // lanes that read LDS together are sixteen rows of either half, each with a bank of its own.
+    const int h = g & 1, gh = g >> 1;
+    const uint32_t slot = xs0 + kPanelBytes + wave * kSlotBytes + 64 * h + 4 * n;
+    const uint32_t shift[2] = {8u * gh, 8u * gh + 16u}, below[2] = {(1u << shift[0]) - 1u, (1u << shift[1]) - 1u};
+    const uint32_t xrow = xs0 + n * 256;
 
     f32x4 acc[MT];
 #pragma unroll
     for (int i = 0; i < MT; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    // Request the first 12 vectors of the chunk's piece.  Lanes whose vector lies past the piece re-read its last
-    // vector (never used); an empty piece reads the start of X instead (always mapped).
-    auto issue = [&](RowStage& st, const uint4 bm) {
-        st.bm = bm;
-        const uint32_t len = popc4(bm);
-        st.off = cur & 7u;
-        st.nv = len ? (st.off + len + 7u) >> 3 : 0u;
-        st.vbase = cur >> 3;
-        const uint32_t last = st.nv ? st.nv - 1u : 0u;
-        const uint4* vb = st.nv ? values128 + st.vbase : reinterpret_cast<const uint4*>(x);
-        cur += len;
+    struct Stage {
+        u32x4 v[kSlotVectors / 2];   // vectors gh, gh + 2, .. of the lane's piece
+        uint32_t at;                 // its byte address, from the buffer's start
+        bool more, over;             // any lane's piece has more than 8 / more than 12 vectors (wave-uniform)
+    };
+    constexpr int kAlways = kPairs ? 4 : 3;
+    // Request the pieces of a unit whose lengths are `len` values: those of half 0, then those of half 1.
+    auto issue = [&](Stage& st, uint32_t len) {
+        uint32_t l0 = len, l1 = len;
+        swap_odd_even_groups(l0, l1);   // of half 0 and of half 1, to all lanes of the row
+        st.at = at_next + (h ? 2 * l0 : 0u);
+        at_next += 2 * (l0 + l1);
+        const uint32_t need = (st.at & 15u) + 2 * len, first_vector = (st.at & ~15u) + 16 * gh;
+        st.more = __builtin_amdgcn_ballot_w64(need > 32 * kAlways) != 0;
+        st.over = __builtin_amdgcn_ballot_w64(need > 16 * kSlotVectors) != 0;
 #pragma unroll
-        for (int i = 0; i < 3; ++i) {
-            const uint32_t v = g + 4 * i;
-            st.vq[i] = vb[v < last ? v : last];
+        for (int i = 0; i < kAlways; ++i) st.v[i] = buffer_load4(vals, first_vector + 32 * i);
+        if (st.more)
+#pragma unroll
+            for (int i = kAlways; i < kSlotVectors / 2; ++i) st.v[i] = buffer_load4(vals, first_vector + 32 * i);
+    };
+    auto park = [&](const Stage& st) {
+#pragma unroll
+        for (int i = 0; i < kSlotVectors / 2; ++i) {
+            if (i == kAlways && !st.more) break;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) lds_write(slot + 512 * gh + 1024 * i + 128 * j, st.v[i][j]);
         }
     };
-
-    // Park the piece in LDS, expand the 4 byte masks of this lane, multiply with the X tile.
-    auto consume = [&](const RowStage& st, const uint16_t* xt) {
+    // Expand the lane's kWords words, whose values start at element `count` of the parked piece, and multiply.
+    auto expand = [&](auto words_of, auto count_of, uint32_t count, uint32_t x_operand) {
+        constexpr int kWords = decltype(count_of)::value;
+        __builtin_amdgcn_wave_barrier();   // LDS executes a wave's accesses in order: the parked values land first
+        ByteWindow w = read_byte_window(words_of(0), below[0], shift[0], count, slot, lut);
 #pragma unroll
-        for (int i = 0; i < 3; ++i) *reinterpret_cast<uint4*>(slot + 4 * (g + 4 * i)) = st.vq[i];
-        if (st.nv > 12u) {   // a piece of more than ~89 values (rare at the sparsities of the paper): fetch the rest now
+        for (int s = 0; s < 2 * kWords; ++s) {
+            u32x4 aq[MT];
 #pragma unroll
-            for (int i = 3; i < 5; ++i) {
-                const uint32_t v = g + 4 * i;
-                if (v < 17u) *reinterpret_cast<uint4*>(slot + 4 * v) = values128[st.vbase + (v < st.nv - 1u ? v : st.nv - 1u)];
+            for (int mt = 0; mt < MT; ++mt) aq[mt] = lds_read<u32x4>((x_operand ^ ((kPairs ? 32 : 64) * s)) + 4096 * mt);
+            ByteWindow next;
+            if (s + 1 < 2 * kWords) {
+                if (s % 2 == 1) count = __popc(words_of(s / 2)) + count;
+                next = read_byte_window(words_of((s + 1) / 2), below[(s + 1) % 2], shift[(s + 1) % 2], count, slot, lut);
             }
-        }
-        __builtin_amdgcn_wave_barrier();  // LDS executes a wave's accesses in order: writes above land first
-        const uint32_t words[kRtChunkWords] = {st.bm.x, st.bm.y, st.bm.z, st.bm.w};
-        uint32_t c_local = st.off;
+            __builtin_amdgcn_sched_barrier(0);
+            const bf16x8 b = expand_window(w);
 #pragma unroll
-        for (int s = 0; s < kRtChunkWords; ++s) {
-            const uint32_t word = words[s];
-            const uint32_t m8 = (word >> (8 * g)) & 0xFFu;
-            const uint32_t cb = c_local + __popc(word & ((1u << (8 * g)) - 1u));
-            const uint4 wq = expand_byte(slot, lut, cb, m8);
-            c_local += __popc(word);
-            const bf16x8 b = as_bf16x8(wq);
-            const int vx = 8 * ((4 * s + g) ^ n);   // where vector 4 s + g of rows n, 16 + n, .. sits
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt) {
-                const uint4 aq = *reinterpret_cast<const uint4*>(xt + (16 * mt + n) * kRtChunkCols + vx);
-                acc[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(aq), b, acc[mt], 0, 0, 0);
-            }
+            for (int mt = 0; mt < MT; ++mt)
+                acc[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b, __builtin_bit_cast(bf16x8, aq[mt]), acc[mt], 0, 0, 0);
+            if (s + 1 < 2 * kWords) w = next;
+            __builtin_amdgcn_sched_barrier(0);
         }
-        __builtin_amdgcn_wave_barrier();  // reads above are issued before the next chunk overwrites the slot
+        __builtin_amdgcn_wave_barrier();   // reads above are issued before the slots are written again
     };
 
-    if (c_begin < c_end) {
-        RowStage st[S];
+    // Units of U words per lane: 4 = a pair of chunks, one per half; 2 = one chunk.  A round is four chunks.
+    auto stream = [&](auto unit_words) {
+        constexpr int U = decltype(unit_words)::value, kUnits = U == 4 ? 2 : 4, kUnitChunks = 4 / kUnits;
+        uint32_t words[kUnits][U], words_next[kUnits][U];
+        auto spread = [&](u32x4 q, uint32_t (&w)[kUnits][U]) {
+            if constexpr (U == 4) {
 #pragma unroll
-        for (int i = 0; i < S; ++i) {
-            issue(st[i], bmq[i]);
-            bmq[i] = load_bitmap_chunk(c_begin + i + S);
-        }
-        store_x(xring[0], 0);
-        load_x(xring[0], c_begin + kBlock * kRing);
-        __syncthreads();
-        int buf = 0;
-        int64_t c = c_begin;
-        // Rounds whose prefetches all lie inside the slice run without a condition: with no load of the
-        // round conditional the compiler counts the requests younger than the one a wave waits for and leaves them in
-        // flight (behind a branch it waits for everything).
-        for (; c + kRound + S <= c_end; c += kRound) {
-#pragma unroll
-            for (int i = 0; i < kRound; ++i) {
-                consume(st[i % S], xs + (buf * kBlock + i % kBlock) * kXsElems);
-                issue(st[i % S], bmq[i % S]);
-                bmq[i % S] = load_bitmap_chunk(c + i + 2 * S);
-                if (i % kBlock == kBlock - 1) {
-                    // the next block into the buffer read one block ago (all waves are past that barrier)
-                    u32x4 (&xr)[kXPer] = xring[(i + 1) / kBlock % kRing];
-                    store_x(xr, buf ^ 1);
-                    load_x(xr, c + i + 1 + kBlock * kRing);
-                    __syncthreads();    // publishes the next block, retires this one
-                    buf ^= 1;
-                }
+                for (int i = 0; i < 4; ++i) spread_halves(q[i], w[0][i], w[1][i]);
+            } else {
+                uint32_t a0 = q[0], b0 = q[2], a1 = q[1], b1 = q[3];
+                swap_odd_even_groups(a0, b0);
+                swap_odd_even_groups(a1, b1);
+                spread_halves(a0, w[0][0], w[2][0]);
+                spread_halves(b0, w[1][0], w[3][0]);
+                spread_halves(a1, w[0][1], w[2][1]);
+                spread_halves(b1, w[1][1], w[3][1]);
             }
-        }
-        // the last rounds: nothing is requested past the slice
-        for (; c < c_end; c += kRound) {
+        };
+        auto length = [&](const uint32_t (&w)[U]) -> uint32_t {
+            uint32_t l = 0;
 #pragma unroll
-            for (int i = 0; i < kRound; ++i) {
-                if (c + i < c_end) {   // the same for the whole workgroup
-                    consume(st[i % S], xs + (buf * kBlock + i % kBlock) * kXsElems);
-                    if (c + i + S < c_end) {
-                        issue(st[i % S], bmq[i % S]);
-                        if constexpr (kRound > S) bmq[i % S] = load_bitmap_chunk(c + i + 2 * S);   // else these are the last two rounds
-                    }
-                    if (i % kBlock == kBlock - 1 && c + i + 1 < c_end) {
-                        u32x4 (&xr)[kXPer] = xring[(i + 1) / kBlock % kRing];
-                        store_x(xr, buf ^ 1);
-                        if (c + i + 1 + kBlock * kRing < c_end) load_x(xr, c + i + 1 + kBlock * kRing);
+            for (int i = 0; i < U; ++i) l = __popc(w[i]) + l;
+            return l;
+        };
+        // LDS place of the lane's X vector of step 0 in the unit's first tile (the other steps' differ in two or three bits)
+        const uint32_t x_lane = xrow + (U == 4 ? h * kTileBytes + 16 * (gh ^ n) : 16 * ((kPairs ? 8 * h + gh : 2 * gh + h) ^ n));
+        Stage st;
+        spread(quad, words);
+        quad = quad_next;
+        issue(st, length(words[0]));
+        for (int c0 = c_begin; c0 < c_end; c0 += kPanel) {
+            if (c0 > c_begin) __syncthreads();   // the panel before has been read by all waves
+            store_x();
+            if (kPanel < 4 || c0 + kPanel < c_end) load_x(c0 + kPanel);   // (past the slice: zeros)
+            __syncthreads();
+#pragma unroll 1
+            for (int c = c0; c < c0 + kPanel && c < c_end; c += 4) {
+#pragma unroll
+                for (int u = 0; u < kUnits; ++u) {
+                    if (u > 0 && c + u * kUnitChunks >= c_end) break;   // uniform
+                    if (kPanel < 4 && u > 0 && u * kUnitChunks % kPanel == 0) {   // (a round is more than one panel)
                         __syncthreads();
-                        buf ^= 1;
+                        store_x();
+                        if (c + (u * kUnitChunks / kPanel + 1) * kPanel < c_end) load_x(c + (u * kUnitChunks / kPanel + 1) * kPanel);
+                        __syncthreads();
+                    }
+                    const uint32_t at = st.at;
+                    const bool over = U == 4 && st.over;
+                    if (!over) park(st);
+                    if (u + 1 < kUnits) issue(st, length(words[u + 1]));
+                    else {
+                        spread(quad, words_next);
+                        quad = load_quad(c + 8);
+                        if (c + 4 < c_end) issue(st, length(words_next[0]));   // uniform
+                    }
+                    const uint32_t x_operand = x_lane + ((c - c0) + u * kUnitChunks) % kPanel * kTileBytes;
+                    if (U == 4 && over) {   // a piece of more than 89 values or so: fetched now, half of it at a time
+                        uint32_t from = at;
+#pragma unroll 1
+                        for (int k = 0; k < 2; ++k) {
+                            const uint32_t w0 = k ? words[u][U - 2] : words[u][0], w1 = k ? words[u][U - 1] : words[u][1];
+#pragma unroll 1
+                            for (int i = 0; i < 5; ++i) {
+                                const u32x4 v = buffer_load4(vals, (from & ~15u) + 16 * gh + 32 * i);
+#pragma unroll
+                                for (int j = 0; j < 4; ++j) lds_write(slot + 512 * gh + 1024 * i + 128 * j, v[j]);
+                            }
+                            expand([&](int i) { return i == 0 ? w0 : w1; }, std::integral_constant<int, 2>{}, (from & 15u) >> 1,
+                                   x_operand ^ (128 * k));
+                            from += 2 * (__popc(w0) + __popc(w1));
+                        }
+                    } else {
+                        expand([&](int i) { return words[u][i]; }, std::integral_constant<int, U>{}, (at & 15u) >> 1, x_operand);
                     }
                 }
+#pragma unroll
+                for (int u = 0; u < kUnits; ++u)
+#pragma unroll
+                    for (int i = 0; i < U; ++i) words[u][i] = words_next[u][i];
             }
+            if (kPanel < 4) c0 += 4 - kPanel;
         }
-        __syncthreads();   // the X tiles are retired
+    };
+    // Rows of more than about 56 % nonzeros would not fit the stages by the pair of chunks.
+    if constexpr (!kPairs) stream(std::integral_constant<int, 2>{});
+    else {
+    const uint32_t rows_here = n0 + 16 < N ? 16u : (uint32_t)(N - n0_c);
+    if ((uint64_t)(row_offsets[n0_c + rows_here] - row_offsets[n0_c]) * 16 <= (uint64_t)rows_here * (uint64_t)K * 9)
+        stream(std::integral_constant<int, 4>{});
+    else
+        stream(std::integral_constant<int, 2>{});
     }
 
-    // ---- adapter k-steps (Sec. 3.2): A operand = T rows from LDS, B operand = B_cat columns of this wave's rows
-    if (adapters) {   // the same for the whole workgroup
-        uint16_t* t_lds = xs;   // [M][Rpad]; the X tiles are retired (last barrier of the loop)
-        const int groups = M * (Rpad >> 2);  // float4 groups of T
+    // ---- adapters from an earlier launch's T (slice 0)
+    if (p.t_in != nullptr && z == 0) {
+        __syncthreads();   // the X panel is retired
+        uint16_t* t_lds = reinterpret_cast<uint16_t*>(lds + 256);   // [M][Rpad]
+        const int groups = M * (Rpad >> 2);
         for (int i = tid; i < groups; i += kRtThreads) {
             float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
-            const float4* p = reinterpret_cast<const float4*>(t_partial) + i;
+            const float4* q = reinterpret_cast<const float4*>(p.t_in) + i;
 #pragma unroll
             for (int sl = 0; sl < kStreamTSlices; ++sl) {
-                const float4 v = p[(int64_t)sl * groups];
+                const float4 v = q[(int64_t)sl * groups];
                 sum.x += v.x; sum.y += v.y; sum.z += v.z; sum.w += v.w;
             }
             uint2 o;
@@ -311,50 +403,142 @@ __global__ __launch_bounds__(kRtThreads, MT <= 4 ? 4 : 2) void linear_rowtile_ke
         }
         __syncthreads();
         for (int rs = 0; rs < (Rpad >> 5); ++rs) {
-            const uint4 bq = rs == 0 ? bq0 : load_b_cat(rs);
+            uint32_t e[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {   // rows past R meet the zero padding of T; clamp instead of predicating
+                const int k = rs * 32 + 8 * g + j;
+                e[j] = (uint32_t)b_cat[(int64_t)(k < R ? k : R - 1) * N + (row < N ? row : N - 1)];
+            }
+            const uint4 bq = make_uint4(e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16), e[6] | (e[7] << 16));
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt) {
                 const int m = 16 * mt + n;
                 const uint4 aq = *reinterpret_cast<const uint4*>(&t_lds[(m < M ? m : M - 1) * Rpad + rs * 32 + 8 * g]);
-                acc[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(aq), as_bf16x8(bq), acc[mt], 0, 0, 0);
+                acc[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(bq), as_bf16x8(aq), acc[mt], 0, 0, 0);
             }
         }
     }
 
-    // ---- store: lane holds column `row`, rows 16 mt + 4 g + e
-    if (row < N) {
+    // ---- store: lane holds row 16 mt + lane % 16 of Y, columns n0 + 4 g .. + 3
+    const int64_t col = n0 + 4 * g;
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int m = 16 * mt + 4 * g + e;
-                if (m < M) {
-                    if (ksplit == 1) y[(int64_t)m * N + row] = f32_to_bf16_rne(acc[mt][e]);
-                    else y_partial[((int64_t)z * M + m) * N + row] = acc[mt][e];
-                }
-            }
+    for (int mt = 0; mt < MT; ++mt) {
+        const int m = 16 * mt + n;
+        if (m >= M) continue;
+        if (p.partial != nullptr) {
+            if (col < p.pitch) *reinterpret_cast<f32x4*>(p.partial + ((int64_t)z * M + m) * p.pitch + col) = acc[mt];
+        } else {
+            store_four(y, M, N, m, col, acc[mt]);
+        }
     }
 }
 
-template <int MT, int S>
-static void launch_rowtile_t(const LinearArgs& a, const float* t_partial, int ksplit, float* y_partial, hipStream_t stream,
-                             const TimingEvents& ev) {
-    const dim3 grid((unsigned)((a.N + 16 * kRtWaves - 1) / (16 * kRtWaves)), (unsigned)ksplit);
-    SALR_LAUNCH((linear_rowtile_kernel<MT, S>), grid, dim3(kRtThreads), stream, ev, a.x, (int)a.M, a.K, a.N, a.bitmap, a.values,
-                a.row_offsets, t_partial, a.b_cat, (int)a.R, (int)adapter_rank_padded(a.R), ksplit, a.y, y_partial, a.slice_table);
+// y = sum of the slices' partial outputs + T B_cat
+__global__ __launch_bounds__(256) void rowtile_finish_kernel(const float* __restrict__ partial, int ksplit, int M, int64_t N,
+                                                             int64_t pitch, const float* __restrict__ t_partial, int t_slices,
+                                                             const uint16_t* __restrict__ b_cat, int R, int Rpad,
+                                                             uint16_t* __restrict__ y) {
+    constexpr int kTPitch = kMaxRankPadded + 8;
+    __shared__ __attribute__((aligned(16))) uint16_t t_lds[16 * kTPitch];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int i16 = lane & 15, g = lane >> 4;
+    const int64_t n0 = (int64_t)blockIdx.x * 64 + 16 * wave;
+    const int m0 = 16 * (int)blockIdx.y, m = m0 + i16;
+    const int64_t col = n0 + 4 * g;
+    const bool live = m < M && col < pitch;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    const float* src = partial + (int64_t)(m < M ? m : M - 1) * pitch + (col < pitch ? col : 0);
+    const int64_t slice = (int64_t)M * pitch;
+    const int64_t n_c = n0 + i16 < N ? n0 + i16 : N - 1;
+    auto load_b = [&](int rs) -> uint4 {
+        uint32_t e[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const int r = rs * 32 + 8 * g + j;
+            e[j] = (uint32_t)b_cat[(int64_t)(r < R ? r : R - 1) * N + n_c];
+        }
+        return make_uint4(e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16), e[6] | (e[7] << 16));
+    };
+    uint4 b0 = make_uint4(0, 0, 0, 0);
+    if (R > 0) {
+        b0 = load_b(0);
+        const int rows = M - m0 < 16 ? M - m0 : 16, per_row = Rpad >> 2;
+        const int64_t t_slice = (int64_t)M * per_row;
+        for (int i = tid; i < 16 * per_row; i += 256) {
+            const int r = i / per_row, c = i - r * per_row;
+            const float4* q = reinterpret_cast<const float4*>(t_partial) + (int64_t)(m0 + (r < rows ? r : rows - 1)) * per_row + c;
+            float4 v[kRowtileTSlices], sum = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+            for (int sl = 0; sl < kRowtileTSlices; ++sl)
+                if (sl < t_slices) v[sl] = q[sl * t_slice];
+#pragma unroll
+            for (int sl = 0; sl < kRowtileTSlices; ++sl)
+                if (sl < t_slices) { sum.x += v[sl].x; sum.y += v[sl].y; sum.z += v[sl].z; sum.w += v[sl].w; }
+            uint2 o;
+            o.x = (uint32_t)f32_to_bf16_rne(sum.x) | ((uint32_t)f32_to_bf16_rne(sum.y) << 16);
+            o.y = (uint32_t)f32_to_bf16_rne(sum.z) | ((uint32_t)f32_to_bf16_rne(sum.w) << 16);
+            *reinterpret_cast<uint2*>(&t_lds[r * kTPitch + 4 * c]) = o;
+        }
+    }
+    for (int z0 = 0; z0 < ksplit; z0 += 8) {
+        f32x4 v[8];
+#pragma unroll
+        for (int z = 0; z < 8; ++z)
+            if (z0 + z < ksplit) v[z] = *reinterpret_cast<const f32x4*>(src + (z0 + z) * slice);
+#pragma unroll
+        for (int z = 0; z < 8; ++z)
+            if (z0 + z < ksplit) acc += v[z];
+    }
+    if (R > 0) {
+        __syncthreads();
+        for (int rs = 0; rs < (Rpad >> 5); ++rs) {
+            const uint4 bq = rs == 0 ? b0 : load_b(rs);
+            const uint4 tq = *reinterpret_cast<const uint4*>(&t_lds[i16 * kTPitch + rs * 32 + 8 * g]);
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(bq), as_bf16x8(tq), acc, 0, 0, 0);
+        }
+    }
+    if (!live) return;
+    store_four(y, M, N, m, col, acc);
+}
+
+template <int MT>
+static void launch_rowtile_t(const LinearArgs& a, RowtileArgs p, hipStream_t stream, const TimingEvents& ev) {
+    p.tiles = (int)((a.N + 16 * kRtWaves - 1) / (16 * kRtWaves));
+    const dim3 grid((unsigned)(p.t_blocks + p.tiles * p.ksplit));
+    const int R = (int)a.R, Rpad = (int)adapter_rank_padded(a.R);
+    if (a.K % kChunkColumns == 0)
+        SALR_LAUNCH((linear_rowtile_kernel<MT, false>), grid, dim3(kRtThreads), stream, ev, a.x, (int)a.M, a.K, a.N, a.bitmap, a.values,
+                    a.row_offsets, a.slice_table, a.a_cat, a.b_cat, R, Rpad, a.y, p);
+    else
+        SALR_LAUNCH((linear_rowtile_kernel<MT, true>), grid, dim3(kRtThreads), stream, ev, a.x, (int)a.M, a.K, a.N, a.bitmap, a.values,
+                    a.row_offsets, a.slice_table, a.a_cat, a.b_cat, R, Rpad, a.y, p);
 }
 
 hipError_t launch_linear_rowtile(const LinearArgs& a, hipStream_t stream, const TimingEvents& ev) {
-    const int ksplit = rowtile_ksplit(a.M, a.K, a.N);
     char* base = reinterpret_cast<char*>(a.t);
-    const float* t_partial = reinterpret_cast<const float*>(base);
-    if (a.R > 0) launch_adapter_partial(a, stream);   // split-K partials of T, summed inside the kernel
-    float* y_partial = reinterpret_cast<float*>(base + rowtile_t_bytes(a.M, a.K, a.R));
-    if (a.M <= 16) launch_rowtile_t<1, 2>(a, t_partial, ksplit, y_partial, stream, ev);
-    else if (a.M <= 32) launch_rowtile_t<2, 2>(a, t_partial, ksplit, y_partial, stream, ev);
-    else if (a.M <= 64) launch_rowtile_t<4, 2>(a, t_partial, ksplit, y_partial, stream, ev);
-    else launch_rowtile_t<8, 2>(a, t_partial, ksplit, y_partial, stream, ev);
-    if (ksplit > 1) launch_splitk_reduce(y_partial, a.M * a.N, ksplit, a.y, stream);
+    const int Rpad = (int)adapter_rank_padded(a.R);
+    // No more of the workspace than the query tells: the same split, and so the same bits, whatever the caller brings beyond it.
+    const RowtilePlan plan = rowtile_plan(a.M, a.K, a.N, a.R, linear_workspace_bytes(a.M, a.K, a.N, a.R));
+    RowtileArgs p;
+    p.pitch = rowtile_pitch(a.N);
+    p.ksplit = plan.ksplit;
+    p.t_slices = plan.t_slices;
+    p.t_out = reinterpret_cast<float*>(base);
+    p.partial = plan.partial ? reinterpret_cast<float*>(base + rowtile_t_out_bytes(a.M, a.R)) : nullptr;
+    const bool t_first = a.R > 0 && !plan.partial;
+    p.t_in = t_first ? p.t_out : nullptr;
+    p.t_blocks = a.R > 0 && !t_first ? plan.t_slices * (Rpad / 16) * (int)((a.M + 15) / 16) : 0;
+    if (t_first) launch_adapter_partial_to(a, p.t_out, stream);
+    LinearArgs b = a;
+    if (a.build_table) b.slice_table = nullptr;   // (room for one; the bitmap left of a slice is read by the kernel itself)
+    if (a.M <= 16) launch_rowtile_t<1>(b, p, stream, ev);
+    else if (a.M <= 32) launch_rowtile_t<2>(b, p, stream, ev);
+    else if (a.M <= 64) launch_rowtile_t<4>(b, p, stream, ev);
+    else launch_rowtile_t<8>(b, p, stream, ev);
+    if (p.partial != nullptr)
+        hipLaunchKernelGGL(rowtile_finish_kernel, dim3((unsigned)((a.N + 63) / 64), (unsigned)((a.M + 15) / 16)), dim3(256), 0, stream, p.partial,
+                           plan.ksplit, (int)a.M, a.N, p.pitch, p.t_out, plan.t_slices, a.b_cat, (int)a.R, Rpad, a.y);
     return hipGetLastError();
 }
 

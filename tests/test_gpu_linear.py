@@ -431,3 +431,17 @@ def test_row_tiled_blocks_of_four_tiles(M, K, N, ranks):
     whole), and K in one slice."""
     x, w, a_cat, b_cat = _problem(M, K, N, ranks, 9000 + M + K)
     _assert_close(_run(x, w, a_cat, b_cat), oracle.linear(x, w, a_cat, b_cat), f"blocks M{M} K{K} N{N}")
+
+
+@pytest.mark.parametrize("M,K,N,ranks", [(16, 2304, 8196, (8,)), (9, 128, 8200, ()), (32, 640, 260, (16, 16)), (64, 2048, 260, (5,)),
+                                         (65, 896, 132, ()), (128, 4224, 388, (33,))])
+def test_row_tiled_uneven_rows(M, K, N, ranks):
+    """Rows whose values lie in a few full chunks among empty ones: pieces longer than what a wave requests ahead next to pieces of
+    no value at all, rows without any, a slice of every length from one chunk to a panel of X and more."""
+    x, w, a_cat, b_cat = _problem(M, K, N, ranks, 9400 + M + K, density=1.0, std_ab=0.05)
+    rng = np.random.default_rng(K)
+    keep = np.repeat(rng.random((N, K // 64)) < 0.4, 64, axis=1)
+    keep[::7, : K // 2] = False
+    keep[3] = False
+    w[~keep] = 0
+    _assert_close(_run(x, w, a_cat, b_cat), oracle.linear(x, w, a_cat, b_cat), f"uneven M{M} K{K} N{N}")
