@@ -43,6 +43,16 @@ bool qsalr_decodes_codes(int64_t M, int64_t K, int64_t N, int64_t nnz) {
     return nnz > 0 && K > 0 && salr::linear_takes_twostage(M, K, N) && (K / 32 + 15) / 16 <= 1024;
 }
 
+// QSALR calls of up to 128 tokens whose plain layer takes the row-tiled kernel: that kernel on the codes, with room for its partial
+// outputs.  Up to 16 tokens on many rows the vector ALUs set the pace (dequantising is twice the work of expanding), so not where its
+// workgroups leave CUs idle or slices are short (us a call, small-batch kernel / this one at 20 % sparsity: 3 x 3968 x 16473 36.9 / 44.5,
+// 1 x 2688 x 20791 30.8 / 35.9, 9 x 768 x 9088 12.7 / 14.9; 16 x 4096 x 14336 39.2 / 34.7; fewer rows: 16 x 10880 x 974 33.4 / 20.9,
+// 17 x 5696 x 4549 64.2 / 23.0).
+bool qsalr_takes_rowtile(int64_t M, int64_t K, int64_t N, int64_t R, int64_t nnz) {
+    if (M > salr::kRowtileMaxM || nnz <= 0 || K <= 0 || !(salr::uses_rowtile(M, K, N) || salr::rowtile_wide(M, K, N, R))) return false;
+    return M > 16 || N < 8192 || (K >= 2048 && salr::rowtile_fill(M, K, N, R) >= 0.75);
+}
+
 }  // namespace
 
 extern "C" {
@@ -293,7 +303,12 @@ size_t salr_qsalr_linear_workspace_bytes(int64_t M, int64_t K, int64_t N, int64_
 
 size_t salr_qsalr_linear_workspace_bytes_fastest(int64_t M, int64_t K, int64_t N, int64_t R, int64_t nnz) {
     const size_t told = salr_qsalr_linear_workspace_bytes(M, K, N, R, nnz);
-    if (M <= 0 || K <= 0 || N <= 0 || R < 0 || R > kMaxRank || K % 32 != 0 || nnz <= 0 || salr::linear_nf4_takes(M, K, N, nnz)) return told;
+    if (M <= 0 || K <= 0 || N <= 0 || R < 0 || R > kMaxRank || K % 32 != 0 || nnz <= 0) return told;
+    if (qsalr_takes_rowtile(M, K, N, R, nnz)) {
+        const size_t b = salr::rowtile_bytes(M, K, N, R);
+        return b > told ? b : told;
+    }
+    if (salr::linear_nf4_takes(M, K, N, nnz)) return told;
     const size_t fastest = salr::linear_workspace_bytes_fastest(M, K, N, R);
     return fastest > told ? fastest : told;
 }
@@ -308,6 +323,23 @@ salr_status_t salr_qsalr_linear(const uint16_t* x, int64_t M, int64_t K, int64_t
     if (K % 32 != 0) return SALR_ERR_SHAPE;
     if (nnz > (int64_t)0xFFFFFFFFLL || (K > 0 && nnz > N * K)) return SALR_ERR_SHAPE;
     if (R > kMaxRank) return SALR_ERR_UNSUPPORTED;
+    if (qsalr_takes_rowtile(M, K, N, R, nnz) && workspace_bytes >= salr::rowtile_bytes(M, K, N, R) &&
+        workspace_bytes >= salr_qsalr_linear_workspace_bytes(M, K, N, R, nnz)) {
+        if (!y || !x || !bitmap || !row_offsets) return SALR_ERR_INVALID_ARG;
+        if (R > 0 && (!a_cat || !b_cat)) return SALR_ERR_INVALID_ARG;
+        if (N > kMaxRows || K > kMaxCols) return SALR_ERR_SHAPE;
+        if (!workspace && workspace_bytes > 0) return SALR_ERR_CAPACITY;
+        salr::LinearArgs a;
+        a.x = x; a.M = M; a.K = K; a.N = N;
+        a.bitmap = bitmap; a.values = nullptr; a.row_offsets = row_offsets;
+        a.a_cat = a_cat; a.b_cat = b_cat; a.R = R;
+        a.y = y;
+        a.t = static_cast<uint16_t*>(workspace);
+        a.room = workspace_bytes;
+        a.codes = codes; a.scales = scales; a.nnz = nnz;
+        hipError_t e = salr::launch_linear_rowtile(a, static_cast<hipStream_t>(stream), salr::g_timing_events);
+        return e == hipSuccess ? SALR_OK : SALR_ERR_HIP;
+    }
     if (salr::linear_nf4_takes(M, K, N, nnz)) {   // small batches: the kernel that reads the codes itself
         if (!y || !x || !bitmap || !row_offsets) return SALR_ERR_INVALID_ARG;
         if (R > 0 && (!a_cat || !b_cat)) return SALR_ERR_INVALID_ARG;

@@ -306,26 +306,41 @@ inline RowtilePlan rowtile_plan(int64_t M, int64_t K, int64_t N, int64_t R, size
     const int64_t tiles = (N + 127) / 128, chunks = (K + 127) / 128, t_units = R > 0 ? adapter_rank_padded(R) / 16 * ((M + 15) / 16) : 0;
     const double step = M <= 16 ? 0.70 : M <= 32 ? 0.85 : M <= 64 ? 1.05 : 1.50;
     const size_t t_bytes = rowtile_t_out_bytes(M, R), one = rowtile_partial_bytes(M, N);
+    const int64_t most = chunks < kRowtileMaxSplit ? chunks : kRowtileMaxSplit;
     RowtilePlan best;
     double best_cost = 1e300;
-    for (int ks = 1; ks <= kRowtileMaxSplit && ks <= chunks; ++ks) {
-        const bool partial = ks > 1 || R > 0;
-        if (partial && t_bytes + ks * one > room) break;
-        for (int ts = R > 0 ? kRowtileTSlices : 1; ts >= 1; ts /= 2) {
+    for (int ts = R > 0 ? kRowtileTSlices : 1; ts >= 1; ts /= 2)
+        for (int64_t filled = 1; filled <= 4; ++filled) {   // the finest split that fits so many rounds
+            int64_t ks = (256 * filled - t_units * ts) / tiles;
+            ks = ks < 1 ? 1 : ks > most ? most : ks;
+            if (t_bytes + ks * one > room) ks = room > t_bytes ? (int64_t)((room - t_bytes) / one) : 0;
+            if (ks < 1) {
+                if (R > 0) continue;
+                ks = 1;
+            }
+            const int64_t per_slice = (chunks + ks - 1) / ks;
+            ks = (chunks + per_slice - 1) / per_slice;   // (no more slices than that length needs)
+            const bool partial = ks > 1 || R > 0;
             const int64_t rounds = (tiles * ks + t_units * ts + 255) / 256;
-            double main = 5.0 + (double)(rounds * ((chunks + ks - 1) / ks)) * step + (double)(rounds - 1) * 2.5 +
+            double main = 5.0 + (double)(rounds * per_slice) * step + (double)(rounds - 1) * 2.5 +
                           0.07 * (double)(chunks - chunks / ks);
             const double t = R > 0 ? 3.0 + (double)((K / 32 + 32 * ts - 1) / (32 * ts)) * 1.2 : 0.0;   // eight waves, four steps at a time
             if (main < t) main = t;
             const double cost = main + (partial ? 4.5 + (double)ks * (double)M * (double)N * 2e-6 : 0.0);
             if (cost < best_cost) {
                 best_cost = cost;
-                best.ksplit = ks;
+                best.ksplit = (int)ks;
                 best.t_slices = ts;
                 best.partial = partial;
             }
+            if (R == 0 && filled == 1 && best.ksplit > 1) {   // one slice writes y itself
+                const double alone = 5.0 + (double)((tiles + 255) / 256 * chunks) * step + (double)((tiles + 255) / 256 - 1) * 2.5;
+                if (alone < best_cost) {
+                    best_cost = alone;
+                    best = RowtilePlan();
+                }
+            }
         }
-    }
     return best;
 }
 inline size_t rowtile_workspace_bytes(int64_t M, int64_t K, int64_t N, int64_t R) {
@@ -390,6 +405,38 @@ inline size_t linear_workspace_bytes_without_table(int64_t M, int64_t K, int64_t
     return b;
 }
 
+// The same kernel beyond those shapes (any K that is a multiple of 32, any N, fewer tokens), where the call's workspace has room for
+// its partial outputs (salr_linear_workspace_bytes_fastest).  The line to the small-batch kernel, which takes what is left of
+// up to 64 tokens, lies where the two meet: that one wants no launch to sum up, so it wins where a layer is a few microseconds of
+// work (us a call, it / this kernel: 1 x 4096 x 4096 12.1 / 14.6, 2 x 1024 x 1914 8.7 / 12.2, 13 x 1536 x 3072 6.2 / 9.2,
+// 32 x 512 x 1536 10.3 / 13.1), this one on larger layers and long rows (2 x 2560 x 26583 27.6 / 23.8, 3 x 7616 x 1792
+// 22.6 / 15.3, 16 x 7168 x 6932 36.6 / 25.9, 15 x 19936 x 512 47.7 / 22.3, 19 x 3904 x 13712 51.8 / 24.3) and from 33 tokens on
+// (59 x 3008 x 16384 79.7 / 34.3; 99 x 7648 x 12288 140 / 59 against the decoding path).
+inline bool rowtile_wide(int64_t M, int64_t K, int64_t N, int64_t R) {
+    if (M > kRowtileMaxM || K < 128 || K % 32 != 0 || K > kRowtileMaxColumns || N < 128) return false;
+    if (M <= 8 && K > 24576 && N > 4096) return false;   // 1 x 28672 x 8192: 83.5 in the long-row kernel, 92 here (three slices on 192 CUs)
+    if (M > 32) return true;
+    if (M > 16) return K >= 1024 || N >= 8192;
+    return N * K >= (18 << 20) || N >= 16384 || K >= (R > 0 ? 5376 : 8192);
+}
+// What either kind of call uses: no more than the told size where that one has always had the kernel, so that the split, and with
+// it every bit of the result, does not depend on what a caller brings beyond it.
+inline RowtilePlan rowtile_plan_of(int64_t M, int64_t K, int64_t N, int64_t R) {
+    return rowtile_plan(M, K, N, R, uses_rowtile(M, K, N) ? linear_workspace_bytes(M, K, N, R) : SIZE_MAX);
+}
+inline size_t rowtile_bytes(int64_t M, int64_t K, int64_t N, int64_t R) {
+    const RowtilePlan p = rowtile_plan_of(M, K, N, R);
+    return p.partial ? round_up_256(rowtile_t_out_bytes(M, R) + (size_t)p.ksplit * rowtile_partial_bytes(M, N)) : rowtile_t_bytes(M, K, R);
+}
+// share of the CUs that a single round of workgroups gives work; 0 where there are more rounds
+inline double rowtile_fill(int64_t M, int64_t K, int64_t N, int64_t R) {
+    const int64_t wgs = (N + 127) / 128 * rowtile_plan_of(M, K, N, R).ksplit;
+    return wgs <= 256 ? (double)wgs / 256.0 : 0.0;
+}
+inline bool linear_takes_rowtile(int64_t M, int64_t K, int64_t N, int64_t R, size_t room) {
+    return uses_rowtile(M, K, N) || (rowtile_wide(M, K, N, R) && room >= rowtile_bytes(M, K, N, R));
+}
+
 // The operand-order path's workspace: T, what a product of its own needs for it, the weight, then the partial outputs of a split
 // contraction as far as there is room (gemm_plan).
 inline size_t frag_base_bytes(int64_t M, int64_t K, int64_t N, int64_t R) {
@@ -401,7 +448,12 @@ inline bool linear_takes_frag(int64_t M, int64_t K, int64_t N, int64_t R, size_t
 // Workspace with which the layer is fastest (salr_linear_workspace_bytes_fastest).
 inline size_t linear_workspace_bytes_fastest(int64_t M, int64_t K, int64_t N, int64_t R) {
     const size_t told = linear_workspace_bytes(M, K, N, R);
-    if (M <= kStreamMaxM || N <= 0 || uses_rowtile(M, K, N) || !uses_frag(M, K)) return told;
+    if (N <= 0 || uses_rowtile(M, K, N)) return told;
+    if (rowtile_wide(M, K, N, R)) {
+        const size_t b = rowtile_bytes(M, K, N, R);
+        return b > told ? b : told;
+    }
+    if (M <= kStreamMaxM || !uses_frag(M, K)) return told;
     const size_t b = frag_base_bytes(M, K, N, R) + gemm_partial_bytes(M, N, gemm_plan(M, K + adapter_rank_padded(R), N).ksplit);
     return b > told ? b : told;
 }

@@ -169,7 +169,8 @@ thread_local TimingEvents g_timing_events;
 
 hipError_t launch_linear(const LinearArgs& a, hipStream_t stream) {
     if (a.M == 0 || a.N == 0) return hipSuccess;
-    if (uses_rowtile(a.M, a.K, a.N)) return launch_linear_rowtile(a, stream, g_timing_events);
+    // (4-bit values come here for the large-batch path only; there are no `values` then)
+    if (a.codes == nullptr && linear_takes_rowtile(a.M, a.K, a.N, a.R, a.room)) return launch_linear_rowtile(a, stream, g_timing_events);
     if (linear_slice_takes(a.M, a.K, a.N)) return launch_linear_slice(a, stream, g_timing_events);
     if (a.M <= kStreamMaxM) return launch_linear_stream(a, stream, g_timing_events);
     if (linear_takes_frag(a.M, a.K, a.N, a.R, a.room)) return launch_linear_frag(a, stream, g_timing_events);

@@ -3,8 +3,9 @@
 //
 // A workgroup of eight waves has a CU to itself and takes 128 consecutive rows of What and one slice of K; wave w owns rows
 // 16 w .. 16 w + 15 of them for the whole slice.
-//   weights      the wave's own stream (salr_row_stream.hpp): bitmap words four chunks at a time, packed values one unit (a pair of
-//                chunks, or one) ahead in registers, parked in the wave's LDS slot, expanded straight into an MFMA operand.
+//   weights      the wave's own stream (salr_row_stream.hpp): bitmap words four chunks at a time, packed values (or their 4-bit codes
+//                and block scales, dequantised on the way into LDS) one unit ahead in registers, parked in the wave's LDS slot,
+//                expanded straight into an MFMA operand.  A unit is a pair of chunks, one from 65 tokens on.
 //   activations  a panel of X (64 KB: 16 chunks of 16 tokens, 4 of 64) is copied to LDS once per workgroup, the next one on its way
 //                in registers meanwhile.  No barrier inside a panel: the waves drift apart and the requests of one meet the
 //                expansion of another.
@@ -24,9 +25,9 @@
 // workgroups share the rows of that layer (level); values fetched as whole 256-byte runs of a row, half as many cycles of the
 // address unit (the transposition into conflict-free LDS columns then meets conflicts of its own).
 #include <hip/hip_ext.h>
-#include <type_traits>
 
 #include "salr_internal.hpp"
+#include "salr_nf4.hpp"
 #include "salr_row_stream.hpp"
 
 namespace salr {
@@ -105,17 +106,20 @@ struct RowtileArgs {
 };
 
 // MT tiles of sixteen rows of X (M <= 16 MT).  kRagged: K is no multiple of 128.
-template <int MT, bool kRagged>
+// kCodes: the packed values as 4-bit codes and block scales (`values` points at the codes).
+template <int MT, bool kRagged, bool kCodes>
 __global__ __launch_bounds__(kRtThreads, 2) void linear_rowtile_kernel(
     const uint16_t* __restrict__ x, int M, int64_t K, int64_t N, const uint32_t* __restrict__ bitmap,
-    const uint16_t* __restrict__ values, const uint32_t* __restrict__ row_offsets, const uint32_t* __restrict__ slice_table,
-    const uint16_t* __restrict__ a_cat, const uint16_t* __restrict__ b_cat, int R, int Rpad, uint16_t* __restrict__ y, RowtileArgs p) {
+    const void* __restrict__ values, const uint16_t* __restrict__ scales, const uint32_t* __restrict__ row_offsets,
+    const uint32_t* __restrict__ slice_table, const uint16_t* __restrict__ a_cat, const uint16_t* __restrict__ b_cat, int R, int Rpad,
+    uint16_t* __restrict__ y, RowtileArgs p) {
     constexpr int kTileBytes = 16 * MT * kChunkColumns * 2;           // X of one chunk
     constexpr int kPanel = 16 / MT;                                   // chunks of X in LDS
     constexpr int kPanelBytes = kPanel * kTileBytes;                  // 64 KB
     constexpr bool kPairs = MT <= 4;                                  // units of two chunks (else there are no registers for them)
-    constexpr int kSlotVectors = kPairs ? 12 : 10, kSlotBytes = slot_bytes(kSlotVectors);
-    __shared__ __attribute__((aligned(256))) char lds[256 + kPanelBytes + kRtWaves * kSlotBytes];
+    // vectors of a half's piece that starts anywhere in its first one: 128 or 64 values by 8, or codes by 32
+    constexpr int kVectors = kCodes ? (kPairs ? 5 : 3) : (kPairs ? 17 : 9), kSlotBytes = slot_bytes(kCodes ? 4 * kVectors : kVectors + 1);
+    __shared__ __attribute__((aligned(256))) char lds[256 + kPanelBytes + kRtWaves * kSlotBytes];   // tables, X, values
     const int tid = threadIdx.x;
     if ((int)blockIdx.x < p.t_blocks) {   // the same for the whole workgroup
         adapter_partial_block<kRtWaves>(x, M, K, a_cat, R, Rpad, (int)blockIdx.x, p.t_slices, p.t_out, reinterpret_cast<float*>(lds), tid);
@@ -168,7 +172,7 @@ __global__ __launch_bounds__(kRtThreads, 2) void linear_rowtile_kernel(
     } else {
         cur = row_offsets[row < N ? row : N];
     }
-    const uint32_t first = row_offsets[n0_c] & ~7u;   // the buffer of the wave's values starts here, in elements
+    const uint32_t first = row_offsets[n0_c] & (kCodes ? ~63u : ~7u);   // the buffer of the wave's values starts here, in elements
     const uint32_t total = row_offsets[N];
     constexpr int kWalk = 8;   // requests of a lane in flight
     u32x4 left[kWalk];
@@ -211,6 +215,7 @@ __global__ __launch_bounds__(kRtThreads, 2) void linear_rowtile_kernel(
         uint32_t a, b;
         nibble_lut_entry(tid, a, b);
         lds_write(lut + 8 * tid, u32x2{a, b});
+        if constexpr (kCodes) reinterpret_cast<float*>(lds + 128)[tid] = kNf4Levels[tid];
     }
     uint32_t before = 0;
     for (int c0 = walk_begin; c0 < c_begin; c0 += 4 * kWalk) {
@@ -222,165 +227,164 @@ __global__ __launch_bounds__(kRtThreads, 2) void linear_rowtile_kernel(
     before += __shfl_xor(before, 32, 64);
     cur += before;
 
-    const Buffer vals = make_buffer(values + first, 2 * (((uint64_t)total + 7) / 8 * 8 - first));
-    uint32_t at_next = 2 * (cur - first);          // byte address of the row's next value
+    const uint64_t left_over = (uint64_t)total - first;   // values from the buffer's start on; whole vectors of them are readable
+    const Buffer vals = kCodes ? make_buffer(static_cast<const uint8_t*>(values) + first / 2, (left_over + 31) / 32 * 16)
+                               : make_buffer(static_cast<const uint16_t*>(values) + first, (left_over + 7) / 8 * 16);
+    const Buffer scale_buffer = make_buffer(kCodes ? scales + first / 64 : scales, kCodes ? (left_over + 63) / 64 * 2 : 0);
+    uint32_t at_next = cur - first;                // the row's next value
     // Lane (n, g) expands half g % 2 of a unit (one of a pair of chunks, or half of a chunk), the bytes g / 2, g / 2 + 2, .. of it: the
     // lanes that read LDS together are sixteen rows of either half, each with a bank of its own.
     const int h = g & 1, gh = g >> 1;
     const uint32_t slot = xs0 + kPanelBytes + wave * kSlotBytes + 64 * h + 4 * n;
     const uint32_t shift[2] = {8u * gh, 8u * gh + 16u}, below[2] = {(1u << shift[0]) - 1u, (1u << shift[1]) - 1u};
-    const uint32_t xrow = xs0 + n * 256;
 
     f32x4 acc[MT];
 #pragma unroll
     for (int i = 0; i < MT; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
 
+    // A lane asks for vectors gh, gh + 2, .. of its piece: always the first few, further ones where any lane of the wave needs them
+    // (at 50 % nonzeros the second lot nearly always, at 30 % never).
+    constexpr int kLoads = (kVectors + 1) / 2, kFirst = kCodes ? kLoads - 1 : kPairs ? 4 : 3, kSecond = kCodes || !kPairs ? kLoads : 6;
+    constexpr uint32_t kPerVector = kCodes ? 32 : 8;
     struct Stage {
-        u32x4 v[kSlotVectors / 2];   // vectors gh, gh + 2, .. of the lane's piece
-        uint32_t at;                 // its byte address, from the buffer's start
-        bool more, over;             // any lane's piece has more than 8 / more than 12 vectors (wave-uniform)
+        u32x4 v[kLoads];
+        uint32_t scale[kCodes ? kLoads : 1];
+        uint32_t at;         // the piece's first value
+        bool more, most;     // (wave-uniform)
     };
-    constexpr int kAlways = kPairs ? 4 : 3;
+    auto request = [&](Stage& st, int i) {
+        const uint32_t v = st.at / kPerVector + gh + 2 * i;
+        st.v[i] = buffer_load4(vals, 16 * v);
+        // a vector of 32 codes lies in one block of 64 values
+        if constexpr (kCodes) st.scale[i] = __builtin_amdgcn_raw_buffer_load_b16(scale_buffer, (int)(v / 2 * 2), 0, 0);
+    };
     // Request the pieces of a unit whose lengths are `len` values: those of half 0, then those of half 1.
     auto issue = [&](Stage& st, uint32_t len) {
         uint32_t l0 = len, l1 = len;
         swap_odd_even_groups(l0, l1);   // of half 0 and of half 1, to all lanes of the row
-        st.at = at_next + (h ? 2 * l0 : 0u);
-        at_next += 2 * (l0 + l1);
-        const uint32_t need = (st.at & 15u) + 2 * len, first_vector = (st.at & ~15u) + 16 * gh;
-        st.more = __builtin_amdgcn_ballot_w64(need > 32 * kAlways) != 0;
-        st.over = __builtin_amdgcn_ballot_w64(need > 16 * kSlotVectors) != 0;
+        st.at = at_next + (h ? l0 : 0u);
+        at_next += l0 + l1;
+        const uint32_t need = st.at % kPerVector + len;
+        st.more = __builtin_amdgcn_ballot_w64(need > 2 * kPerVector * kFirst) != 0;
+        st.most = kSecond < kLoads && __builtin_amdgcn_ballot_w64(need > 2 * kPerVector * kSecond) != 0;
 #pragma unroll
-        for (int i = 0; i < kAlways; ++i) st.v[i] = buffer_load4(vals, first_vector + 32 * i);
+        for (int i = 0; i < kFirst; ++i) request(st, i);
         if (st.more)
 #pragma unroll
-            for (int i = kAlways; i < kSlotVectors / 2; ++i) st.v[i] = buffer_load4(vals, first_vector + 32 * i);
+            for (int i = kFirst; i < kSecond; ++i) request(st, i);
+        if (st.most)
+#pragma unroll
+            for (int i = kSecond; i < kLoads; ++i) request(st, i);
     };
     auto park = [&](const Stage& st) {
 #pragma unroll
-        for (int i = 0; i < kSlotVectors / 2; ++i) {
-            if (i == kAlways && !st.more) break;
+        for (int i = 0; i < kLoads; ++i) {
+            if (i == kFirst && !st.more) break;
+            if (i == kSecond && !st.most) break;
+            if constexpr (kCodes) {
+                if (i == kLoads - 1 && gh != 0) break;   // an odd number of vectors: the last is the other lane's
+                const float scale = __uint_as_float(st.scale[i] << 16);
 #pragma unroll
-            for (int j = 0; j < 4; ++j) lds_write(slot + 512 * gh + 1024 * i + 128 * j, st.v[i][j]);
+                for (int j = 0; j < 4; ++j) {
+                    const uint4 d = nf4_decode8(st.v[i][j], scale, reinterpret_cast<const float*>(lds + 128));
+                    const uint32_t to = slot + 2048 * gh + 4096 * i + 512 * j;
+                    lds_write(to, d.x);
+                    lds_write(to + 128, d.y);
+                    lds_write(to + 256, d.z);
+                    lds_write(to + 384, d.w);
+                }
+            } else {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) lds_write(slot + 512 * gh + 1024 * i + 128 * j, st.v[i][j]);
+            }
         }
     };
-    // Expand the lane's kWords words, whose values start at element `count` of the parked piece, and multiply.
-    auto expand = [&](auto words_of, auto count_of, uint32_t count, uint32_t x_operand) {
-        constexpr int kWords = decltype(count_of)::value;
+    // Expand the lane's words, whose values start at element `count` of the parked piece, and multiply.
+    auto expand = [&](const auto& words, uint32_t count, uint32_t x_operand) {
+        constexpr int kSteps = 2 * (int)(sizeof(words) / sizeof(words[0]));
         __builtin_amdgcn_wave_barrier();   // LDS executes a wave's accesses in order: the parked values land first
-        ByteWindow w = read_byte_window(words_of(0), below[0], shift[0], count, slot, lut);
+        ByteWindow w = read_byte_window(words[0], below[0], shift[0], count, slot, lut);
 #pragma unroll
-        for (int s = 0; s < 2 * kWords; ++s) {
+        for (int s = 0; s < kSteps; ++s) {
             u32x4 aq[MT];
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt) aq[mt] = lds_read<u32x4>((x_operand ^ ((kPairs ? 32 : 64) * s)) + 4096 * mt);
             ByteWindow next;
-            if (s + 1 < 2 * kWords) {
-                if (s % 2 == 1) count = __popc(words_of(s / 2)) + count;
-                next = read_byte_window(words_of((s + 1) / 2), below[(s + 1) % 2], shift[(s + 1) % 2], count, slot, lut);
+            if (s + 1 < kSteps) {
+                if (s % 2 == 1) count = __popc(words[s / 2]) + count;
+                next = read_byte_window(words[(s + 1) / 2], below[(s + 1) % 2], shift[(s + 1) % 2], count, slot, lut);
             }
             __builtin_amdgcn_sched_barrier(0);
             const bf16x8 b = expand_window(w);
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt)
                 acc[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b, __builtin_bit_cast(bf16x8, aq[mt]), acc[mt], 0, 0, 0);
-            if (s + 1 < 2 * kWords) w = next;
+            if (s + 1 < kSteps) w = next;
             __builtin_amdgcn_sched_barrier(0);
         }
         __builtin_amdgcn_wave_barrier();   // reads above are issued before the slots are written again
     };
 
-    // Units of U words per lane: 4 = a pair of chunks, one per half; 2 = one chunk.  A round is four chunks.
-    auto stream = [&](auto unit_words) {
-        constexpr int U = decltype(unit_words)::value, kUnits = U == 4 ? 2 : 4, kUnitChunks = 4 / kUnits;
-        uint32_t words[kUnits][U], words_next[kUnits][U];
-        auto spread = [&](u32x4 q, uint32_t (&w)[kUnits][U]) {
-            if constexpr (U == 4) {
+    // A unit is U words per lane, a round four chunks.
+    constexpr int U = kPairs ? 4 : 2, kUnits = kPairs ? 2 : 4, kUnitChunks = 4 / kUnits;
+    uint32_t words[kUnits][U], words_next[kUnits][U];
+    auto spread = [&](u32x4 q, uint32_t (&w)[kUnits][U]) {   // to the lanes that expand them
+        if constexpr (kPairs) {
 #pragma unroll
-                for (int i = 0; i < 4; ++i) spread_halves(q[i], w[0][i], w[1][i]);
-            } else {
-                uint32_t a0 = q[0], b0 = q[2], a1 = q[1], b1 = q[3];
-                swap_odd_even_groups(a0, b0);
-                swap_odd_even_groups(a1, b1);
-                spread_halves(a0, w[0][0], w[2][0]);
-                spread_halves(b0, w[1][0], w[3][0]);
-                spread_halves(a1, w[0][1], w[2][1]);
-                spread_halves(b1, w[1][1], w[3][1]);
-            }
-        };
-        auto length = [&](const uint32_t (&w)[U]) -> uint32_t {
-            uint32_t l = 0;
-#pragma unroll
-            for (int i = 0; i < U; ++i) l = __popc(w[i]) + l;
-            return l;
-        };
-        // LDS place of the lane's X vector of step 0 in the unit's first tile (the other steps' differ in two or three bits)
-        const uint32_t x_lane = xrow + (U == 4 ? h * kTileBytes + 16 * (gh ^ n) : 16 * ((kPairs ? 8 * h + gh : 2 * gh + h) ^ n));
-        Stage st;
-        spread(quad, words);
-        quad = quad_next;
-        issue(st, length(words[0]));
-        for (int c0 = c_begin; c0 < c_end; c0 += kPanel) {
-            if (c0 > c_begin) __syncthreads();   // the panel before has been read by all waves
-            store_x();
-            if (kPanel < 4 || c0 + kPanel < c_end) load_x(c0 + kPanel);   // (past the slice: zeros)
-            __syncthreads();
-#pragma unroll 1
-            for (int c = c0; c < c0 + kPanel && c < c_end; c += 4) {
-#pragma unroll
-                for (int u = 0; u < kUnits; ++u) {
-                    if (u > 0 && c + u * kUnitChunks >= c_end) break;   // uniform
-                    if (kPanel < 4 && u > 0 && u * kUnitChunks % kPanel == 0) {   // (a round is more than one panel)
-                        __syncthreads();
-                        store_x();
-                        if (c + (u * kUnitChunks / kPanel + 1) * kPanel < c_end) load_x(c + (u * kUnitChunks / kPanel + 1) * kPanel);
-                        __syncthreads();
-                    }
-                    const uint32_t at = st.at;
-                    const bool over = U == 4 && st.over;
-                    if (!over) park(st);
-                    if (u + 1 < kUnits) issue(st, length(words[u + 1]));
-                    else {
-                        spread(quad, words_next);
-                        quad = load_quad(c + 8);
-                        if (c + 4 < c_end) issue(st, length(words_next[0]));   // uniform
-                    }
-                    const uint32_t x_operand = x_lane + ((c - c0) + u * kUnitChunks) % kPanel * kTileBytes;
-                    if (U == 4 && over) {   // a piece of more than 89 values or so: fetched now, half of it at a time
-                        uint32_t from = at;
-#pragma unroll 1
-                        for (int k = 0; k < 2; ++k) {
-                            const uint32_t w0 = k ? words[u][U - 2] : words[u][0], w1 = k ? words[u][U - 1] : words[u][1];
-#pragma unroll 1
-                            for (int i = 0; i < 5; ++i) {
-                                const u32x4 v = buffer_load4(vals, (from & ~15u) + 16 * gh + 32 * i);
-#pragma unroll
-                                for (int j = 0; j < 4; ++j) lds_write(slot + 512 * gh + 1024 * i + 128 * j, v[j]);
-                            }
-                            expand([&](int i) { return i == 0 ? w0 : w1; }, std::integral_constant<int, 2>{}, (from & 15u) >> 1,
-                                   x_operand ^ (128 * k));
-                            from += 2 * (__popc(w0) + __popc(w1));
-                        }
-                    } else {
-                        expand([&](int i) { return words[u][i]; }, std::integral_constant<int, U>{}, (at & 15u) >> 1, x_operand);
-                    }
-                }
-#pragma unroll
-                for (int u = 0; u < kUnits; ++u)
-#pragma unroll
-                    for (int i = 0; i < U; ++i) words[u][i] = words_next[u][i];
-            }
-            if (kPanel < 4) c0 += 4 - kPanel;
+            for (int i = 0; i < 4; ++i) spread_halves(q[i], w[0][i], w[1][i]);
+        } else {
+            uint32_t a0 = q[0], b0 = q[2], a1 = q[1], b1 = q[3];
+            swap_odd_even_groups(a0, b0);
+            swap_odd_even_groups(a1, b1);
+            spread_halves(a0, w[0][0], w[2][0]);
+            spread_halves(b0, w[1][0], w[3][0]);
+            spread_halves(a1, w[0][1], w[2][1]);
+            spread_halves(b1, w[1][1], w[3][1]);
         }
     };
-    // Rows of more than about 56 % nonzeros would not fit the stages by the pair of chunks.
-    if constexpr (!kPairs) stream(std::integral_constant<int, 2>{});
-    else {
-    const uint32_t rows_here = n0 + 16 < N ? 16u : (uint32_t)(N - n0_c);
-    if ((uint64_t)(row_offsets[n0_c + rows_here] - row_offsets[n0_c]) * 16 <= (uint64_t)rows_here * (uint64_t)K * 9)
-        stream(std::integral_constant<int, 4>{});
-    else
-        stream(std::integral_constant<int, 2>{});
+    auto length = [&](const uint32_t (&w)[U]) -> uint32_t {
+        uint32_t l = 0;
+#pragma unroll
+        for (int i = 0; i < U; ++i) l = __popc(w[i]) + l;
+        return l;
+    };
+    // LDS place of the lane's X vector of step 0 in the unit's first tile (the other steps' differ in two or three bits)
+    const uint32_t x_lane = xs0 + n * 256 + (kPairs ? h * kTileBytes + 16 * (gh ^ n) : 16 * ((2 * gh + h) ^ n));
+    Stage st;
+    spread(quad, words);
+    quad = quad_next;
+    issue(st, length(words[0]));
+    for (int c0 = c_begin; c0 < c_end; c0 += kPanel < 4 ? 4 : kPanel) {
+        if (c0 > c_begin) __syncthreads();   // the panel before has been read by all waves
+        store_x();
+        if (kPanel < 4 || c0 + kPanel < c_end) load_x(c0 + kPanel);   // (past the slice: zeros)
+        __syncthreads();
+#pragma unroll 1
+        for (int c = c0; c < c_end && c < c0 + (kPanel < 4 ? 4 : kPanel); c += 4) {
+#pragma unroll
+            for (int u = 0; u < kUnits; ++u) {
+                if (u > 0 && c + u * kUnitChunks >= c_end) break;   // uniform
+                if (kPanel < 4 && u > 0 && u * kUnitChunks % kPanel == 0) {   // (a round is more than one panel)
+                    __syncthreads();
+                    store_x();
+                    load_x(c + u * kUnitChunks + kPanel);
+                    __syncthreads();
+                }
+                const uint32_t start = st.at % kPerVector;
+                park(st);
+                if (u + 1 < kUnits) issue(st, length(words[u + 1]));
+                else {
+                    spread(quad, words_next);
+                    quad = load_quad(c + 8);
+                    if (c + 4 < c_end) issue(st, length(words_next[0]));   // uniform
+                }
+                expand(words[u], start, x_lane + (c - c0 + u * kUnitChunks) % kPanel * kTileBytes);
+            }
+#pragma unroll
+            for (int u = 0; u < kUnits; ++u)
+#pragma unroll
+                for (int i = 0; i < U; ++i) words[u][i] = words_next[u][i];
+        }
     }
 
     // ---- adapters from an earlier launch's T (slice 0)
@@ -507,19 +511,19 @@ static void launch_rowtile_t(const LinearArgs& a, RowtileArgs p, hipStream_t str
     p.tiles = (int)((a.N + 16 * kRtWaves - 1) / (16 * kRtWaves));
     const dim3 grid((unsigned)(p.t_blocks + p.tiles * p.ksplit));
     const int R = (int)a.R, Rpad = (int)adapter_rank_padded(a.R);
-    if (a.K % kChunkColumns == 0)
-        SALR_LAUNCH((linear_rowtile_kernel<MT, false>), grid, dim3(kRtThreads), stream, ev, a.x, (int)a.M, a.K, a.N, a.bitmap, a.values,
-                    a.row_offsets, a.slice_table, a.a_cat, a.b_cat, R, Rpad, a.y, p);
-    else
-        SALR_LAUNCH((linear_rowtile_kernel<MT, true>), grid, dim3(kRtThreads), stream, ev, a.x, (int)a.M, a.K, a.N, a.bitmap, a.values,
-                    a.row_offsets, a.slice_table, a.a_cat, a.b_cat, R, Rpad, a.y, p);
+    const bool ragged = a.K % kChunkColumns != 0;
+    auto go = [&](auto kernel, const void* values) {
+        SALR_LAUNCH(kernel, grid, dim3(kRtThreads), stream, ev, a.x, (int)a.M, a.K, a.N, a.bitmap, values, a.scales, a.row_offsets, a.slice_table,
+                    a.a_cat, a.b_cat, R, Rpad, a.y, p);
+    };
+    if (a.codes != nullptr) ragged ? go(linear_rowtile_kernel<MT, true, true>, a.codes) : go(linear_rowtile_kernel<MT, false, true>, a.codes);
+    else ragged ? go(linear_rowtile_kernel<MT, true, false>, a.values) : go(linear_rowtile_kernel<MT, false, false>, a.values);
 }
 
 hipError_t launch_linear_rowtile(const LinearArgs& a, hipStream_t stream, const TimingEvents& ev) {
     char* base = reinterpret_cast<char*>(a.t);
     const int Rpad = (int)adapter_rank_padded(a.R);
-    // No more of the workspace than the query tells: the same split, and so the same bits, whatever the caller brings beyond it.
-    const RowtilePlan plan = rowtile_plan(a.M, a.K, a.N, a.R, linear_workspace_bytes(a.M, a.K, a.N, a.R));
+    const RowtilePlan plan = rowtile_plan_of(a.M, a.K, a.N, a.R);
     RowtileArgs p;
     p.pitch = rowtile_pitch(a.N);
     p.ksplit = plan.ksplit;

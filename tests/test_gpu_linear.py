@@ -445,3 +445,21 @@ def test_row_tiled_uneven_rows(M, K, N, ranks):
     keep[3] = False
     w[~keep] = 0
     _assert_close(_run(x, w, a_cat, b_cat), oracle.linear(x, w, a_cat, b_cat), f"uneven M{M} K{K} N{N}")
+
+
+# any K that is a multiple of 32 (the last chunk of a row overlaps the one before), any N, one token and up: K of one chunk and less
+# than half of one more, of several panels of X, N past the last whole tile, density on either side of what a pair of chunks holds
+@pytest.mark.parametrize("M,K,N,ranks,density", [
+    (1, 5408, 131, (8,), 0.5), (16, 6112, 1000, (16, 16), 0.7), (5, 16416, 130, (), 0.5), (8, 2080, 9001, (3,), 0.55),
+    (17, 1056, 261, (8,), 0.5), (32, 3040, 515, (), 0.9), (33, 160, 130, (33,), 0.5), (64, 2208, 387, (8,), 0.2),
+    (65, 992, 200, (5,), 0.5), (128, 2720, 133, (40, 60), 0.6), (100, 128, 130, (), 1.0), (3, 8224, 2300, (16,), 0.5),
+])
+def test_row_tiled_any_width(M, K, N, ranks, density):
+    x, w, a_cat, b_cat = _problem(M, K, N, ranks, 9600 + M + K, density=density, std_ab=0.05)
+    x[:, K - 40] = 0x7F80   # an infinite entry where the last two chunks overlap: met once, by its own weight
+    w[:, K - 40] = 0x3C00
+    w[1, K - 40] = 0
+    y, ref = _run(x, w, a_cat, b_cat), oracle.linear(x, w, a_cat, b_cat)
+    assert np.array_equal(np.isnan(y), np.isnan(ref)) and np.array_equal(np.isinf(y), np.isinf(ref))
+    x[:, K - 40] = 0x3F80
+    _assert_close(_run(x, w, a_cat, b_cat), oracle.linear(x, w, a_cat, b_cat), f"any width M{M} K{K} N{N}")

@@ -176,3 +176,25 @@ def test_qsalr_fused_against_oracle_and_block_borders():
     scale = float(np.max(np.abs(y_ref)))
     print(f"[qsalr fused, block borders] max|d|={err:.3e} scale={scale:.3e}", flush=True)
     assert err <= 1e-2 * scale
+
+
+@pytest.mark.parametrize("M,K,N,R,permille", [(1, 6144, 130, 8, 200), (16, 5408, 200, 0, 0), (17, 1120, 387, 24, 500), (33, 256, 131, 8, 200),
+                                              (64, 2336, 260, 40, 950), (9, 4096, 8200, 8, 200)])
+def test_qsalr_row_tiled(M, K, N, R, permille):
+    """The row-tiled kernel on the codes (pieces that start at every code of a vector, rows of uneven width, full and nearly empty
+    rows) against the oracle on the dequantised weight."""
+    salr = _salr()
+    w = wl.gaussian_bf16((N, K), 0.02, 700 + M)
+    w_hat = oracle.mask_topk_rows(w, K - K * permille // 1000) if permille else w.copy()
+    w_hat[2, : K // 2] = 0
+    x = wl.gaussian_bf16((M, K), 1.0, 701 + M)
+    a_cat, b_cat = (wl.gaussian_bf16((K, R), 0.05, 702), wl.gaussian_bf16((R, N), 0.05, 703)) if R else (None, None)
+    rb, rv, ro = oracle.encode(w_hat)
+    nnz = int(ro[-1])
+    codes_ref, scales_ref = oracle.nf4_quantize(rv)
+    y_ref = oracle.linear(x, oracle.decode(rb, oracle.nf4_dequantize(codes_ref, scales_ref, nnz), ro, N, K), a_cat, b_cat)
+    codes, scales = salr.nf4_quantize(to_dev_u16(rv))
+    y = salr.qsalr_linear(to_dev_u16(x), to_dev_u32(rb), codes, scales, to_dev_u32(ro), nnz, None if a_cat is None else to_dev_u16(a_cat),
+                          None if b_cat is None else to_dev_u16(b_cat))
+    torch.cuda.synchronize()
+    assert float(np.max(np.abs(y_to_f64(y) - y_ref))) <= 1e-2 * float(np.max(np.abs(y_ref)))
