@@ -2,10 +2,12 @@
 #pragma once
 
 #include "salr_device.hpp"
+#include "salr_internal.hpp"
 #include "salr_linear_common.hpp"
 
 namespace salr {
 
+typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));   // (kept in registers; HIP's uint4 in an array is not)
 typedef short i16x4 __attribute__((ext_vector_type(4)));
 
 // Four rows of a column from a row-major bf16 tile in LDS (gfx950's transposing read): every 16 lanes read four rows of 16
@@ -59,14 +61,14 @@ __device__ __forceinline__ void adapter_t_block(const uint16_t* __restrict__ x, 
     }
     // A loader: lane l fetches eight ranks from 32 rg + 8 (l % 4) of row l / 4 of every sixteen
     const int arow = lane >> 2, acol = 32 * rg + 8 * (lane & 3);
-    auto load_a = [&](int64_t k) -> uint4 {
+    auto load_a = [&](int64_t k) -> u32x4_t {
         if constexpr (kFactor == kFactorVec) {
-            return *reinterpret_cast<const uint4*>(a_cat + k * R + (acol < R ? acol : R - 8));
+            return *reinterpret_cast<const u32x4_t*>(a_cat + k * R + (acol < R ? acol : R - 8));
         } else {   // ranks past R: any value, their columns are stored as zeros
             uint32_t e[8];
 #pragma unroll
             for (int j = 0; j < 8; ++j) e[j] = a_cat[k * R + (acol + j < R ? acol + j : R - 1)];
-            return make_uint4(e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16), e[6] | (e[7] << 16));
+            return u32x4_t{e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16), e[6] | (e[7] << 16)};
         }
     };
     const uint16_t* frow[4];   // kFactorRanks: loaded like X, ranks past R as the last one
@@ -78,62 +80,64 @@ __device__ __forceinline__ void adapter_t_block(const uint16_t* __restrict__ x, 
     f32x4 acc[kMT][2];
 #pragma unroll
     for (int i = 0; i < kMT; ++i) acc[i][0] = acc[i][1] = f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int64_t s0 = wave; s0 < steps; s0 += kWaves * kDepth) {
-        uint4 xq[kDepth][2 * kMT], aq[kDepth][4];
+    u32x4_t xq[kDepth][2 * kMT], aq[kDepth][4];
+    auto request = [&](int d, int64_t s) {
+        const int64_t k = (s < steps ? s : steps - 1) << 6;   // past the end: the last step again, not used
+        const int64_t half = k + 64 > K ? 32 : 0;             // the last step has 32 columns when K % 64 is 32: its first half twice
 #pragma unroll
-        for (int d = 0; d < kDepth; ++d) {
-            const int64_t s = s0 + kWaves * d;
-            const int64_t k = (s < steps ? s : steps - 1) << 6;   // past the end: the last step again, not used
-            const int64_t half = k + 64 > K ? 32 : 0;             // the last step has 32 columns when K % 64 is 32: its first half twice
+        for (int i = 0; i < 2 * kMT; ++i) xq[d][i] = *reinterpret_cast<const u32x4_t*>(xrow[i] + k - (xseg >= 4 ? half : 0));
 #pragma unroll
-            for (int i = 0; i < 2 * kMT; ++i) xq[d][i] = *reinterpret_cast<const uint4*>(xrow[i] + k - (xseg >= 4 ? half : 0));
+        for (int i = 0; i < 4; ++i) {
+            if constexpr (kFactor == kFactorRanks) aq[d][i] = *reinterpret_cast<const u32x4_t*>(frow[i] + k - (xseg >= 4 ? half : 0));
+            else aq[d][i] = load_a(k + arow + 16 * i - (i >= 2 ? half : 0));
+        }
+    };
+    auto multiply = [&](int d, int64_t s) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                if constexpr (kFactor == kFactorRanks) aq[d][i] = *reinterpret_cast<const uint4*>(frow[i] + k - (xseg >= 4 ? half : 0));
-                else aq[d][i] = load_a(k + arow + 16 * i - (i >= 2 ? half : 0));
-            }
+        for (int i = 0; i < 2 * kMT; ++i) *reinterpret_cast<u32x4_t*>(x_tile + (8 * i + (lane >> 3)) * kTxPitch + 8 * xseg) = xq[d][i];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if constexpr (kFactor == kFactorRanks) *reinterpret_cast<u32x4_t*>(a_tile + (8 * i + (lane >> 3)) * kTxPitch + 8 * xseg) = aq[d][i];
         }
 #pragma unroll
+        for (int h = 0; h < 2; ++h) {   // 32 columns each
+            if (h == 0 || (s << 6) + 32 < K) {   // wave-uniform
+                if constexpr (kFactor != kFactorRanks) {
+                    *reinterpret_cast<u32x4_t*>(a_tile + arow * kTaPitch + 8 * (lane & 3)) = aq[d][2 * h];
+                    *reinterpret_cast<u32x4_t*>(a_tile + (arow + 16) * kTaPitch + 8 * (lane & 3)) = aq[d][2 * h + 1];
+                }
+                __builtin_amdgcn_wave_barrier();   // LDS executes a wave's accesses in order
+                const uint16_t* col = a_tile + (8 * g + (i16 >> 2)) * kTaPitch + 4 * (i16 & 3);
+                bf16x8 xf[kMT];
+#pragma unroll
+                for (int i = 0; i < kMT; ++i)
+                    xf[i] = *reinterpret_cast<const bf16x8*>(x_tile + (16 * i + i16) * kTxPitch + 32 * h + 8 * g);
+#pragma unroll
+                for (int rt = 0; rt < 2; ++rt) {
+                    uint4 bq;
+                    if constexpr (kFactor == kFactorRanks) {
+                        bq = *reinterpret_cast<const uint4*>(a_tile + (16 * rt + i16) * kTxPitch + 32 * h + 8 * g);
+                    } else {
+                        const uint2 lo = lds_read_tr4(col + 16 * rt), hi = lds_read_tr4(col + 4 * kTaPitch + 16 * rt);
+                        bq = make_uint4(lo.x, lo.y, hi.x, hi.y);
+                    }
+                    const bf16x8 b = as_bf16x8(bq);
+#pragma unroll
+                    for (int i = 0; i < kMT; ++i) acc[i][rt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xf[i], b, acc[i][rt], 0, 0, 0);
+                }
+                __builtin_amdgcn_wave_barrier();
+            }
+        }
+    };
+    // a ring: a step is requested again as soon as its registers are free, kDepth steps ahead
+#pragma unroll
+    for (int d = 0; d < kDepth; ++d) request(d, wave + kWaves * d);
+    for (int64_t s0 = wave; s0 < steps; s0 += kWaves * kDepth) {
+#pragma unroll
         for (int d = 0; d < kDepth; ++d) {
             const int64_t s = s0 + kWaves * d;
-            if (s < steps) {   // wave-uniform
-#pragma unroll
-                for (int i = 0; i < 2 * kMT; ++i)
-                    *reinterpret_cast<uint4*>(x_tile + (8 * i + (lane >> 3)) * kTxPitch + 8 * xseg) = xq[d][i];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    if constexpr (kFactor == kFactorRanks) *reinterpret_cast<uint4*>(a_tile + (8 * i + (lane >> 3)) * kTxPitch + 8 * xseg) = aq[d][i];
-                }
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {   // 32 columns each
-                    if (h == 0 || (s << 6) + 32 < K) {   // wave-uniform
-                        if constexpr (kFactor != kFactorRanks) {
-                            *reinterpret_cast<uint4*>(a_tile + arow * kTaPitch + 8 * (lane & 3)) = aq[d][2 * h];
-                            *reinterpret_cast<uint4*>(a_tile + (arow + 16) * kTaPitch + 8 * (lane & 3)) = aq[d][2 * h + 1];
-                        }
-                        __builtin_amdgcn_wave_barrier();   // LDS executes a wave's accesses in order
-                        const uint16_t* col = a_tile + (8 * g + (i16 >> 2)) * kTaPitch + 4 * (i16 & 3);
-                        bf16x8 xf[kMT];
-#pragma unroll
-                        for (int i = 0; i < kMT; ++i)
-                            xf[i] = *reinterpret_cast<const bf16x8*>(x_tile + (16 * i + i16) * kTxPitch + 32 * h + 8 * g);
-#pragma unroll
-                        for (int rt = 0; rt < 2; ++rt) {
-                            uint4 bq;
-                            if constexpr (kFactor == kFactorRanks) {
-                                bq = *reinterpret_cast<const uint4*>(a_tile + (16 * rt + i16) * kTxPitch + 32 * h + 8 * g);
-                            } else {
-                                const uint2 lo = lds_read_tr4(col + 16 * rt), hi = lds_read_tr4(col + 4 * kTaPitch + 16 * rt);
-                                bq = make_uint4(lo.x, lo.y, hi.x, hi.y);
-                            }
-                            const bf16x8 b = as_bf16x8(bq);
-#pragma unroll
-                            for (int i = 0; i < kMT; ++i) acc[i][rt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xf[i], b, acc[i][rt], 0, 0, 0);
-                        }
-                        __builtin_amdgcn_wave_barrier();
-                    }
-                }
-            }
+            if (s < steps) multiply(d, s);   // wave-uniform
+            request(d, s + kWaves * kDepth);
         }
     }
     __syncthreads();
@@ -159,6 +163,20 @@ __device__ __forceinline__ void adapter_t_block(const uint16_t* __restrict__ x, 
             if (t_t != nullptr) t_t[(int64_t)r * M + m] = v;
         }
     }
+}
+
+// Workgroup `block` of T = X * A_cat (R % 8 == 0) by workgroups of kWaves waves: 32 rows of X each where the blocks are many anyway
+// (adapter_t_row_tiles), 16 else, and 32 ranks.
+inline int adapter_t_blocks(int64_t M, int Rpad) {
+    const int rows = 16 * adapter_t_row_tiles(M);
+    return (int)((M + rows - 1) / rows) * (Rpad / 32);
+}
+template <int kWaves>
+__device__ __forceinline__ void adapter_t_block_of(const uint16_t* __restrict__ x, int64_t M, int64_t K, const uint16_t* __restrict__ a_cat, int R,
+                                                   int Rpad, uint16_t* __restrict__ t, int block, uint16_t* lds) {
+    const int groups = Rpad >> 5;
+    if (M >= kAdapterWideM) adapter_t_block<2, kWaves, 2>(x, M, K, a_cat, R, Rpad, t, block / groups, block % groups, lds);
+    else adapter_t_block<1, kWaves, 3>(x, M, K, a_cat, R, Rpad, t, block / groups, block % groups, lds);
 }
 
 }  // namespace salr

@@ -79,14 +79,16 @@ hipError_t launch_linear_backward(const uint16_t* x, const uint16_t* dy, int64_t
     char* ws = static_cast<char*>(workspace);
     auto at = [&](size_t offset) { return reinterpret_cast<uint16_t*>(ws + offset); };
 
-    if (R > 0) {   // T' is needed by dX and dA, T by dB
-        const LowRankJob none{nullptr, nullptr, 0, nullptr, nullptr};
-        const LowRankJob dy_b{dy, b_cat, N, at(p.off_tp), da != nullptr ? at(p.off_tp_t) : nullptr};
-        const LowRankJob x_a{x, a_cat, K, at(p.off_tt), db != nullptr ? at(p.off_tt_t) : nullptr};
-        launch_backward_t(want_dx || da != nullptr ? dy_b : none, db != nullptr ? x_a : none, M, R, stream);
-    }
+    // T' is needed by dX and dA, T by dB: in the launch that decodes the weight where there is one
+    const LowRankJob none{nullptr, nullptr, 0, nullptr, nullptr};
+    LowRankJob dy_b = none, x_a = none;
+    if (R > 0 && (want_dx || da != nullptr)) dy_b = {dy, b_cat, N, at(p.off_tp), da != nullptr ? at(p.off_tp_t) : nullptr};
+    if (R > 0 && db != nullptr) x_a = {x, a_cat, K, at(p.off_tt), at(p.off_tt_t)};
+    const bool with_decode = want_dx && R % 8 == 0;
+    if (R > 0 && !with_decode) launch_backward_t(dy_b, x_a, M, R, stream);
     if (want_dx) {
-        const hipError_t e = launch_decode_transposed_frags(bitmap, values, row_offsets, N, K, a_cat, R, at(p.off_wf), stream);
+        const hipError_t e = launch_decode_transposed_frags(bitmap, values, row_offsets, N, K, a_cat, R, at(p.off_wf), with_decode ? dy_b : none,
+                                                            with_decode ? x_a : none, M, stream);
         if (e != hipSuccess) return e;
         const TimingEvents none;
         launch_frag_gemm(dy, M, N, K, at(p.off_wf), at(p.off_tp), p.Rpad, dx, reinterpret_cast<float*>(ws + p.off_ypart), p.y_room, none,

@@ -9,6 +9,7 @@
 // dense matrix (2 B/element) against bitmap + values (1/8 + 2(1-p) B/element).
 #include "salr_device.hpp"
 #include "salr_internal.hpp"
+#include "salr_adapter_t.hpp"
 #include "salr_linear_common.hpp"
 #include "salr_nf4.hpp"
 
@@ -404,7 +405,10 @@ hipError_t launch_decode(const uint32_t* bitmap, const uint16_t* values, const u
 // columns 16 f .. 16 f + 15 x rows 32 nb .. + 31 as described in salr_gemm.hip, with the rank blocks of A_cat behind those of
 // the weight: the reconstruction rule of Sec. 3.3 as in the kernels above, the transposition done in LDS on the way out, so
 // that the dense matrix crosses memory once.  cols % 32 == 0, rows % 64 == 0.
-//   the first a_wgs workgroups: A_cat's blocks, a 16-byte vector per thread;
+//   the first t_wgs workgroups: the low-rank intermediates T' = dY B_cat^T and T = X A_cat of the same call (R % 8 == 0), a chain of
+//   round trips that has nothing to do with the weight (in a launch of their own: 2048 x 4096 x 4096 111.6 us a call, now 107.7;
+//   544 x 2400 x 15552 136 and 125);
+//   the next a_wgs: A_cat's blocks, a 16-byte vector per thread;
 //   workgroup (b, z) of the others: rows 64 b .. 64 b + 63 (wave w the 16 rows 16 w ..), chunks [C z / ksl, C (z + 1) / ksl) of
 //   the C = ceil(cols / 128) chunks of 128 columns.  Per chunk lane (n = lane%16, g = lane/16) expands byte g of the four
 //   bitmap words of row n, as in the small-batch linear, and writes its 32 values into an LDS tile [128 columns][64 rows];
@@ -426,12 +430,26 @@ struct DtStage {
 
 // kVec: rows of the bitmap are whole 16-byte vectors (cols % 128 == 0)
 template <bool kVec>
-__global__ __launch_bounds__(kDtThreads) void decode_transposed_frags_kernel(
+__global__ __launch_bounds__(kDtThreads, 4) void decode_transposed_frags_kernel(
     const uint32_t* __restrict__ bitmap, const uint16_t* __restrict__ values, const uint32_t* __restrict__ row_offsets, int64_t rows,
-    int64_t cols, int ksl, const uint16_t* __restrict__ a_cat, int R, int r_blocks, int a_wgs, uint16_t* __restrict__ wf) {
+    int64_t cols, int ksl, const uint16_t* __restrict__ a_cat, int R, int r_blocks, int a_wgs, uint16_t* __restrict__ wf, LowRankJob dy_b,
+    LowRankJob x_a, int64_t M, int dy_wgs, int t_wgs) {
+    // a tile on its way out, and the waves' values; or the tiles of the low-rank intermediates
+    constexpr int kTileElems = 128 * kDtPitch;
+    __shared__ __attribute__((aligned(16))) uint16_t tile[kTileElems + 2 * (kDtWaves * 16 * kDtSlotDwords + 8)];
+    static_assert(sizeof(tile) >= adapter_t_lds_bytes<1, kDtWaves, kFactorRanks>() && sizeof(tile) >= adapter_t_lds_bytes<1, kDtWaves>(), "room");
+    if ((int)blockIdx.x < t_wgs) {   // the same for the whole workgroup
+        const int Rpad = (R + 31) / 32 * 32, groups = Rpad >> 5, id = (int)blockIdx.x;
+        if (id < dy_wgs)
+            adapter_t_block<1, kDtWaves, 2, kFactorRanks>(dy_b.in, M, dy_b.C, dy_b.factor, R, Rpad, dy_b.t, id / groups, id % groups, tile, dy_b.t_t);
+        else
+            adapter_t_block<1, kDtWaves, 2>(x_a.in, M, x_a.C, x_a.factor, R, Rpad, x_a.t, (id - dy_wgs) / groups, (id - dy_wgs) % groups, tile, x_a.t_t);
+        return;
+    }
+    const int wg = (int)blockIdx.x - t_wgs;
     const int64_t out_blocks = rows / 32 + r_blocks, frags = cols / 16;   // blocks per f, number of f
-    if ((int)blockIdx.x < a_wgs) {   // the same for the whole workgroup
-        const int64_t v = (int64_t)blockIdx.x * kDtThreads + threadIdx.x, block = v >> 6;
+    if (wg < a_wgs) {
+        const int64_t v = (int64_t)wg * kDtThreads + threadIdx.x, block = v >> 6;
         const int l = (int)v & 63, rb = (int)(block % r_blocks);
         const int64_t f = block / r_blocks;
         if (f >= frags) return;
@@ -447,15 +465,14 @@ __global__ __launch_bounds__(kDtThreads) void decode_transposed_frags_kernel(
             make_uint4(e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16), e[6] | (e[7] << 16));
         return;
     }
-    __shared__ __attribute__((aligned(16))) uint16_t tile[128 * kDtPitch];
-    __shared__ __attribute__((aligned(16))) uint32_t slots[kDtWaves * 16 * kDtSlotDwords + 8];
+    uint32_t* slots = reinterpret_cast<uint32_t*>(tile + kTileElems);
     __shared__ uint32_t lut[kNibbleLutWords];
     nibble_lut_init(lut);
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n = lane & 15, g = lane >> 4;
-    const int64_t id = (int64_t)blockIdx.x - a_wgs, row_blocks = rows / kDtRows;
+    const int64_t id = (int64_t)wg - a_wgs, row_blocks = rows / kDtRows;
     const int64_t n0 = id % row_blocks * kDtRows;
     const int64_t row = n0 + 16 * wave + n;
     const int64_t row_c = row;   // rows % 64 == 0: every row of the block exists
@@ -569,19 +586,22 @@ __global__ __launch_bounds__(kDtThreads) void decode_transposed_frags_kernel(
 }
 
 hipError_t launch_decode_transposed_frags(const uint32_t* bitmap, const uint16_t* values, const uint32_t* row_offsets, int64_t rows,
-                                          int64_t cols, const uint16_t* a_cat, int R, uint16_t* wf, hipStream_t stream) {
+                                          int64_t cols, const uint16_t* a_cat, int R, uint16_t* wf, const LowRankJob& dy_b,
+                                          const LowRankJob& x_a, int64_t M, hipStream_t stream) {
     const int64_t blocks = rows / kDtRows, chunks = (cols + 127) / 128;
     int64_t ksl = (1024 + blocks - 1) / blocks;   // about four workgroups per CU
     ksl = ksl < 1 ? 1 : (ksl > chunks ? chunks : ksl);
     const int r_blocks = (R + 63) / 64 * 2;
     const int64_t a_wgs = (cols / 16 * r_blocks * 64 + kDtThreads - 1) / kDtThreads;
-    const dim3 grid((unsigned)(a_wgs + blocks * ksl));
+    const int t_job = (int)((M + 15) / 16) * ((R + 31) / 32);   // workgroups of sixteen rows and 32 ranks
+    const int dy_wgs = dy_b.in != nullptr ? t_job : 0, t_wgs = dy_wgs + (x_a.in != nullptr ? t_job : 0);
+    const dim3 grid((unsigned)(t_wgs + a_wgs + blocks * ksl));
     if (cols % 128 == 0)
         hipLaunchKernelGGL(decode_transposed_frags_kernel<true>, grid, dim3(kDtThreads), 0, stream, bitmap, values, row_offsets, rows, cols,
-                           (int)ksl, a_cat, R, r_blocks, (int)a_wgs, wf);
+                           (int)ksl, a_cat, R, r_blocks, (int)a_wgs, wf, dy_b, x_a, M, dy_wgs, t_wgs);
     else
         hipLaunchKernelGGL(decode_transposed_frags_kernel<false>, grid, dim3(kDtThreads), 0, stream, bitmap, values, row_offsets, rows, cols,
-                           (int)ksl, a_cat, R, r_blocks, (int)a_wgs, wf);
+                           (int)ksl, a_cat, R, r_blocks, (int)a_wgs, wf, dy_b, x_a, M, dy_wgs, t_wgs);
     return hipGetLastError();
 }
 

@@ -395,9 +395,15 @@ __global__ __launch_bounds__(kDfWaves * 64) void decode_frag_kernel(const uint32
                                                                    int ksl, const uint16_t* __restrict__ b_cat, int R, int Rpad,
                                                                    const uint16_t* __restrict__ scales, uint32_t scale_last,
                                                                    uint16_t* wf, int a_blocks, const uint16_t* __restrict__ a_cat,
-                                                                   uint16_t* __restrict__ af) {
+                                                                   uint16_t* __restrict__ af, int t_blocks, const uint16_t* __restrict__ x,
+                                                                   int64_t M, uint16_t* __restrict__ t) {
     __shared__ __attribute__((aligned(16))) uint32_t slots[kDfWaves][16 * kDfPitch];
-    if ((int)blockIdx.x < a_blocks) {   // the same for the whole workgroup
+    if ((int)blockIdx.x < t_blocks) {   // the same for the whole workgroup
+        static_assert(sizeof(slots) >= adapter_t_lds_bytes<2, kDfWaves>() && sizeof(slots) >= adapter_t_lds_bytes<1, kDfWaves>(), "room for T's tiles");
+        adapter_t_block_of<kDfWaves>(x, M, K, a_cat, R, Rpad, t, (int)blockIdx.x, reinterpret_cast<uint16_t*>(slots));
+        return;
+    }
+    if ((int)blockIdx.x < a_blocks) {
         adapter_frags_block(a_cat, K, R, Rpad, (int)blockIdx.x * kDfWaves + (threadIdx.x >> 6), a_blocks * kDfWaves, af);
         return;
     }
@@ -410,7 +416,7 @@ __global__ __launch_bounds__(kDfWaves * 64) void decode_frag_kernel(const uint32
     const int lane = lane_id();
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n = lane & 15, g = lane >> 4;
-    const int64_t frags = (N + 15) >> 4, id = (int64_t)blockIdx.x - a_blocks;
+    const int64_t frags = (N + 15) >> 4, id = (int64_t)blockIdx.x - a_blocks - t_blocks;   // (at most one of the two)
     const int64_t f = id % frags;
     const int z = (int)(id / frags) * kDfWaves + wave;
     const int64_t row = 16 * f + n < N ? 16 * f + n : N - 1;   // rows past N: copies of the last one, their outputs are dropped
@@ -561,8 +567,11 @@ __global__ __launch_bounds__(kDfWaves * 64) void decode_frag_kernel(const uint32
     }
 }
 
-// af: A_cat in operand order, too (null: not wanted)
-hipError_t launch_decode_frags(const LinearArgs& a, uint16_t* wf, uint16_t* af, hipStream_t stream) {
+// af: A_cat in operand order, too (null: not wanted); t: T = X A_cat, too, in the launch's first workgroups (null: not wanted; only where
+// adapter_t_beside, and not both).  The two have nothing to do with each other, T is a chain of round trips on a few CUs and
+// the decode pass fills the memory system: 300 x 2720 x 2731 38.6 -> 32.4 us a call, 2048 x 4096 x 14336
+// 252 -> 244.
+hipError_t launch_decode_frags(const LinearArgs& a, uint16_t* wf, uint16_t* af, uint16_t* t, hipStream_t stream) {
     const int R = (int)a.R, Rpad = (int)adapter_rank_padded(a.R);
     const int64_t frags = (a.N + 15) / 16, pieces = (a.K + 255) / 256;
     // one round of the four workgroups that fit a CU, more only where the rows are many; two pieces at least to a wave
@@ -571,12 +580,13 @@ hipError_t launch_decode_frags(const LinearArgs& a, uint16_t* wf, uint16_t* af, 
     if (split < 1) split = 1;
     const int64_t ksl = split * kDfWaves;
     const int a_blocks = af != nullptr ? (int)((a.K + 32 * kDfWaves - 1) / (32 * kDfWaves)) : 0;
-    const dim3 grid((unsigned)(a_blocks + frags * split)), block(kDfWaves * 64);
+    const int t_blocks = t != nullptr ? adapter_t_blocks(a.M, Rpad) : 0;
+    const dim3 grid((unsigned)(t_blocks + a_blocks + frags * split)), block(kDfWaves * 64);
     const uint16_t* src = a.codes != nullptr ? reinterpret_cast<const uint16_t*>(a.codes) : a.values;
     const uint32_t scale_last = a.codes != nullptr ? (uint32_t)((a.nnz + kNf4Block - 1) / kNf4Block - 1) : 0u;
 #define SALR_DECODE(PAIR, NF4) \
     hipLaunchKernelGGL((decode_frag_kernel<PAIR, NF4>), grid, block, 0, stream, a.bitmap, src, a.row_offsets, a.N, a.K, (int)ksl, \
-                       a.b_cat, R, Rpad, a.scales, scale_last, wf, a_blocks, a.a_cat, af)
+                       a.b_cat, R, Rpad, a.scales, scale_last, wf, a_blocks, a.a_cat, af, t_blocks, a.x, a.M, t)
     const bool pair = a.K % 64 == 0;
     if (a.codes != nullptr) {
         if (pair) SALR_DECODE(true, true);
@@ -654,11 +664,10 @@ static void launch_adapter_t_product(const uint16_t* x, int64_t M, int64_t K, co
 hipError_t launch_linear_frag(const LinearArgs& a, hipStream_t stream, const TimingEvents& ev) {
     const int Rpad = (int)adapter_rank_padded(a.R);
     uint16_t* wf = reinterpret_cast<uint16_t*>(reinterpret_cast<char*>(a.t) + frag_weight_offset(a.M, a.K, a.R));
-    // T in one launch, or as a product of its own whose operand the decode launch lays out
+    // T beside the decode pass, or as a product of its own whose operand that pass lays out
     char* af = reinterpret_cast<char*>(a.t) + adapter_t_bytes(a.M, a.R);
-    const bool own = a.R > 0 && adapter_t_own_product(a.M, a.K, a.R);
-    if (a.R > 0 && !own) launch_adapter_t_direct(a.x, a.M, a.K, a.a_cat, (int)a.R, Rpad, a.t, stream);
-    const hipError_t e = launch_decode_frags(a, wf, own ? reinterpret_cast<uint16_t*>(af) : nullptr, stream);
+    const bool own = a.R > 0 && !adapter_t_beside(a.K, a.R);
+    const hipError_t e = launch_decode_frags(a, wf, own ? reinterpret_cast<uint16_t*>(af) : nullptr, a.R > 0 && !own ? a.t : nullptr, stream);
     if (e != hipSuccess) return e;
     if (own)
         launch_adapter_t_product(a.x, a.M, a.K, reinterpret_cast<const uint16_t*>(af), (int)a.R, Rpad, a.t,
@@ -674,15 +683,23 @@ hipError_t launch_linear_frag(const LinearArgs& a, hipStream_t stream, const Tim
 // n holding two sets of four (columns c .. c + 7 and c + 16 .. c + 23 with c = 32 (kb % 2) + 8 (kb / 2)), then a word per lane with
 // the positions of both steps (the index field of v_smfmac_f32_16x16x64_bf16 in the low and the high half; a last single step
 // leaves the second half of its pair unread).  Behind the pairs of an f the rank blocks of B_cat, dense, 32 ranks each.
+// The first t_blocks workgroups compute T = X A_cat meanwhile (any16 = X; 16 rows and 32 ranks each).
 // Value offsets are clamped to the stored count: the 2:4 form is the caller's promise.  Bound by memory: 14336 x 4096, 66 MB in
 // and 66 out, 28.7 us.
 __global__ __launch_bounds__(256) void pack_2of4_kernel(const uint32_t* __restrict__ bitmap, const uint16_t* __restrict__ values,
                                                         const uint32_t* __restrict__ row_offsets, const uint16_t* __restrict__ any16,
                                                         int64_t N, int64_t K, int split, const uint16_t* __restrict__ b_cat, int R,
-                                                        int Rpad, uint16_t* __restrict__ wf) {
+                                                        int Rpad, uint16_t* __restrict__ wf, int t_blocks, int64_t M,
+                                                        const uint16_t* __restrict__ a_cat, uint16_t* __restrict__ t) {
+    if ((int)blockIdx.x < t_blocks) {   // the same for the whole workgroup
+        __shared__ __attribute__((aligned(16))) uint16_t lds[adapter_t_lds_bytes<1, 4>() / 2];
+        const int groups = Rpad >> 5;
+        adapter_t_block<1, 4, 2>(any16, M, K, a_cat, R, Rpad, t, (int)blockIdx.x / groups, (int)blockIdx.x % groups, lds);
+        return;
+    }
     const int lane = lane_id(), n = lane & 15, kb = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t frags = (N + 15) / 16, id = (int64_t)blockIdx.x * 4 + wave;
+    const int64_t frags = (N + 15) / 16, id = ((int64_t)blockIdx.x - t_blocks) * 4 + wave;
     const int64_t f = id / split;
     const int z = (int)(id % split);
     if (f >= frags) return;   // wave-uniform; the kernel has no barrier
@@ -743,15 +760,16 @@ __global__ __launch_bounds__(256) void pack_2of4_kernel(const uint32_t* __restri
 }
 
 // y = x W^T + t B_cat on the sparse matrix cores: the weight into sparse operand order at wf (sparse_weight_bytes), then tiles of
-// 256 x 256 or 256 x 224.  K % 64 == 0.
-void launch_sparse_gemm(const LinearArgs& a, uint16_t* wf, bool narrow, const TimingEvents& ev, hipStream_t stream) {
+// 256 x 256 or 256 x 224.  K % 64 == 0.  with_t: T first, beside the permutation (adapter_t_beside).
+void launch_sparse_gemm(const LinearArgs& a, uint16_t* wf, bool narrow, bool with_t, const TimingEvents& ev, hipStream_t stream) {
     const int R = (int)a.R, Rpad = (int)adapter_rank_padded(a.R);
     const int64_t frags = (a.N + 15) / 16, pairs = (a.K / 64 + 1) / 2;
     int64_t split = (8192 + frags - 1) / frags;   // about eight waves per SIMD, four pairs at least to a wave
     if (split > pairs / 4) split = pairs / 4;
     if (split < 1) split = 1;
-    hipLaunchKernelGGL(pack_2of4_kernel, dim3((unsigned)((frags * split + 3) / 4)), dim3(256), 0, stream, a.bitmap, a.values, a.row_offsets,
-                       a.x, a.N, a.K, (int)split, a.b_cat, R, Rpad, wf);
+    const int t_blocks = with_t ? (int)((a.M + 15) / 16) * (Rpad / 32) : 0;
+    hipLaunchKernelGGL(pack_2of4_kernel, dim3((unsigned)(t_blocks + (frags * split + 3) / 4)), dim3(256), 0, stream, a.bitmap, a.values,
+                       a.row_offsets, a.x, a.N, a.K, (int)split, a.b_cat, R, Rpad, wf, t_blocks, a.M, a.a_cat, a.t);
     const int nt = narrow ? 224 : 256, m_tiles = (int)((a.M + 255) / 256), n_tiles = (int)((a.N + nt - 1) / nt);
     const dim3 grid(gemm_grid(m_tiles * n_tiles));
     float* none = nullptr;

@@ -237,7 +237,6 @@ static void launch_gemm_2of4_t(const LinearArgs& a, hipStream_t stream, const Ti
 }
 
 hipError_t launch_gemm_2of4(const LinearArgs& a, hipStream_t stream, const TimingEvents& ev) {
-    if (a.R > 0) launch_adapter_t(a, stream);   // T = X A_cat, bf16 [M, Rpad], at the start of the workspace
     // 256 x 256 tiles (8 waves, one workgroup per CU) where they fill the chip, else 128 x 128 (4 waves, two per CU);
     // 224 rows instead of 256 where that needs less time in whole rounds of the 256 CUs (a round costs its tile width)
     const int64_t m_tiles = (a.M + 255) / 256;
@@ -247,8 +246,13 @@ hipError_t launch_gemm_2of4(const LinearArgs& a, hipStream_t stream, const Timin
     // stage a quarter faster.  Calls on the packed format / in operand order, microseconds: 2048 x 4096 x 14336 207 / 182,
     // 4096 x 4096 x 8192 234 / 184, 3000 x 1024 x 8192 76 / 73, 1500 x 4096 x 14336 194 / 172; 1024 x 4096 x 28672 204 / 226.
     const size_t offset = twostage_dense_offset(a.M, a.K, a.R);
-    if (t256 >= kGemm2of4BigTilesMin && a.M >= kSparseOrderMinM && a.K <= kFragMaxColumns && a.room >= offset + sparse_weight_bytes(a.K, a.N, a.R))
-        launch_sparse_gemm(a, reinterpret_cast<uint16_t*>(reinterpret_cast<char*>(a.t) + offset), cost224 < cost256, ev, stream);
+    const bool sparse = t256 >= kGemm2of4BigTilesMin && a.M >= kSparseOrderMinM && a.K <= kFragMaxColumns &&
+                        a.room >= offset + sparse_weight_bytes(a.K, a.N, a.R);
+    // T = X A_cat, bf16 [M, Rpad], at the start of the workspace: beside the pass over the weight where there is one
+    const bool with_t = sparse && adapter_t_beside(a.K, a.R);
+    if (a.R > 0 && !with_t) launch_adapter_t(a, stream);
+    if (sparse)
+        launch_sparse_gemm(a, reinterpret_cast<uint16_t*>(reinterpret_cast<char*>(a.t) + offset), cost224 < cost256, with_t, ev, stream);
     else if (t256 >= kGemm2of4BigTilesMin && cost224 < cost256) launch_gemm_2of4_t<2, 4, 7, 4>(a, stream, ev);
     else if (t256 >= kGemm2of4BigTilesMin) launch_gemm_2of4_t<2, 4, 8, 4>(a, stream, ev);
     else launch_gemm_2of4_t<2, 2, 4, 4>(a, stream, ev);

@@ -143,7 +143,8 @@ inline size_t adapter_frag_bytes(int64_t K, int64_t R) {
 }
 // Rows of X per block of the large-batch T (salr_adapter_t.hpp), in tiles of 16: two where the blocks are many anyway (each
 // reads its ranks' part of A_cat once).
-inline int adapter_t_row_tiles(int64_t M) { return M >= 1024 ? 2 : 1; }
+constexpr int64_t kAdapterWideM = 1024;
+inline int adapter_t_row_tiles(int64_t M) { return M >= kAdapterWideM ? 2 : 1; }
 // T = X * A_cat of the large-batch paths: one launch that reads X once per 32 ranks and A_cat once per block of rows
 // (launch_adapter_t_direct), or a split-K product on the MFMA stage's kernel, which reads X once but costs a summing pass and
 // A_cat in operand order.  The latter where the former is more than about fifteen microseconds of traffic (70B down_proj at
@@ -154,6 +155,11 @@ inline bool adapter_t_own_product(int64_t M, int64_t K, int64_t R) {
     const double groups = (double)((R + 31) / 32), rows = 16.0 * adapter_t_row_tiles(M);
     return groups * ((double)M * K * 2 + M / rows * 64.0 * K) > 64e6;
 }
+// Where a pass over the weight runs first anyway (large batches), T is computed by workgroups of that launch: a chain of steps on a few
+// CUs beside a pass that fills the memory system.  Longer rows take the product above (us a call, beside / product: 300 x 8192 x 600 at
+// rank 64 75.0 / 84.7, 657 x 4736 x 768 at rank 128 37.1 / 51.3, 4096 x 8192 x 8192 at rank 64 465 / 472; 1024 x 14336 x 4096 180 / 170,
+// 200 x 28672 x 1024 97 / 77).
+inline bool adapter_t_beside(int64_t K, int64_t R) { return R > 0 && R % 8 == 0 && K <= 8192; }
 inline int adapter_t_product_ksplit(int64_t M, int64_t K, int64_t Rpad) {
     const int64_t wgs = (M + 255) / 256 * ((Rpad + 127) / 128), steps = (K + 63) / 64;
     int64_t ks = (256 + wgs - 1) / wgs;
@@ -491,10 +497,6 @@ hipError_t launch_linear_nf4(const LinearArgs& args, const uint8_t* codes, const
 bool decode_nf4_takes(int64_t rows, int64_t cols, int64_t nnz, const void* codes, const void* out);
 hipError_t launch_decode_nf4(const uint32_t* bitmap, const uint8_t* codes, const uint16_t* scales, int64_t nnz,
                              const uint32_t* row_offsets, int64_t rows, int64_t cols, uint16_t* out, hipStream_t stream);
-// the transpose of the weight in operand order, the rank blocks of A_cat [cols, R] (null with R == 0) behind it:
-// frag_weight_bytes(rows, cols, R) bytes (rows % 64 == 0, cols % 32 == 0)
-hipError_t launch_decode_transposed_frags(const uint32_t* bitmap, const uint16_t* values, const uint32_t* row_offsets, int64_t rows,
-                                          int64_t cols, const uint16_t* a_cat, int R, uint16_t* wf, hipStream_t stream);
 hipError_t launch_linear(const LinearArgs& args, hipStream_t stream);
 // count bf16 zeros (+0.0) at out
 hipError_t launch_fill_zero(uint16_t* out, int64_t count, hipStream_t stream);
@@ -506,7 +508,7 @@ hipError_t launch_linear_twostage(const LinearArgs& args, hipStream_t stream, co
 hipError_t launch_linear_tiled(const LinearArgs& args, hipStream_t stream, const TimingEvents& ev);
 hipError_t launch_linear_rowtile(const LinearArgs& args, hipStream_t stream, const TimingEvents& ev);
 hipError_t launch_linear_2of4(const LinearArgs& args, hipStream_t stream, const TimingEvents& ev);
-void launch_sparse_gemm(const LinearArgs& args, uint16_t* wf, bool narrow, const TimingEvents& ev, hipStream_t stream);
+void launch_sparse_gemm(const LinearArgs& args, uint16_t* wf, bool narrow, bool with_t, const TimingEvents& ev, hipStream_t stream);
 hipError_t launch_gemm_2of4(const LinearArgs& args, hipStream_t stream, const TimingEvents& ev);
 // split-K partials of T = X * A_cat (small batches): fp32 [kStreamTSlices, M, Rpad] at the start of the workspace
 void launch_adapter_partial(const LinearArgs& args, hipStream_t stream);
@@ -528,6 +530,11 @@ struct LowRankJob {
     uint16_t* t_t;
 };
 void launch_backward_t(const LowRankJob& dy_b, const LowRankJob& x_a, int64_t M, int R, hipStream_t stream);
+// the transpose of the weight in operand order, the rank blocks of A_cat [cols, R] (null with R == 0) behind it:
+// frag_weight_bytes(rows, cols, R) bytes (rows % 64 == 0, cols % 32 == 0); the two jobs (see launch_backward_t; R % 8 == 0) in the same launch
+hipError_t launch_decode_transposed_frags(const uint32_t* bitmap, const uint16_t* values, const uint32_t* row_offsets, int64_t rows,
+                                          int64_t cols, const uint16_t* a_cat, int R, uint16_t* wf, const LowRankJob& dy_b,
+                                          const LowRankJob& x_a, int64_t M, hipStream_t stream);
 // Products that contract over the rows of in [M, C] (M % 32 == 0) against s_t [Rpad, M]: the adapter gradients, bf16, job 0 to
 // out [C, R], job 1 to out [R, C].  A job whose `out` is null is left out.  partial: room for ksplit fp32 slices
 // [C, Rpad] of each job; tn_ksplit picks the split of M (about four workgroups per CU over both jobs, at least two
