@@ -41,8 +41,8 @@ def test_mask_rows_tie_heavy(rows, cols, keep):
     (5, 8, 0), (5, 8, 8), (6, 64, 1), (3, 4096, 4096), (7, 4096, 0), (9, 8192, 4000), (5, 2056, 2055), (1, 520, 13),
     (4, 1024, 512), (6, 3072, 77)])
 def test_mask_rows_one_wave_per_row(rows, cols, keep):
-    """Rows of up to 8192 columns in whole 8-column units go through the kernel that keeps a row in the registers of
-    one wave (four rows per workgroup): row counts that are not multiples of four, the extreme `keep` values, ties."""
+    """Rows of up to 7168 columns in whole 8-column units are kept in the registers of one wave (four rows per workgroup): row
+    counts that are not multiples of four, the extreme `keep` values, ties."""
     _check_rows(_few_magnitudes((rows, cols), rows * 77 + cols), keep, "wave kernel, ties")
     _check_rows(wl.gaussian_bf16((rows, cols), 0.02, cols + keep + 1), keep, "wave kernel, gaussian")
 
@@ -110,8 +110,7 @@ def test_mask_nm_q_proj_2_of_4():
 @pytest.mark.parametrize("rows,cols,keep", [(5, 8200, 4100), (3, 14336, 14335), (5, 14336, 1), (6, 14344, 3), (3, 28672, 9000),
                                             (2, 28664, 0), (2, 11008, 11008), (3, 16384, 8192)])
 def test_mask_rows_long_rows_one_wave_per_row(rows, cols, keep):
-    """The register counts above 8192 columns, at their edges (rows of more than 14336 columns are too few here for them and take
-    the workgroup kernel; see test_mask_rows_longest_rows); the search starts from the row's first columns, so rows whose
+    """Rows above 7168 columns, spread over two waves or four; the search starts from the row's first columns, so rows whose
     start says nothing about the rest (constant, empty, infinite) as well."""
     w = wl.gaussian_bf16((rows, cols), 0.02, cols + keep)
     _check_rows(w, keep, "long rows, gaussian")
@@ -136,7 +135,17 @@ def test_mask_of_a_pruned_matrix_is_itself(cols, keep):
 @pytest.mark.parametrize("rows,cols,keep", [(513, 24584, 12292), (514, 28672, 8601), (515, 26000, 25999), (512, 24584, 7000),
                                             (769, 20488, 10244), (769, 24576, 12288), (768, 24576, 100), (769, 20480, 6000)])
 def test_mask_rows_longest_rows(rows, cols, keep):
-    """From 20488 columns on more rows than the CUs hold workgroups go through the kernel with one wave per row, fewer through
-    the one with a workgroup per row; both sides of each line."""
+    """Rows of up to 28672 columns, four waves each, in numbers around what the CUs hold at once."""
     w = np.concatenate([wl.gaussian_bf16((rows - 8, cols), 0.02, cols + keep), _few_magnitudes((8, cols), rows + keep)])
     _check_rows(w, keep, "longest rows")
+
+
+@pytest.mark.parametrize("cols", [504, 512, 520, 1032, 1536, 2056, 3072, 3080, 5120, 6144, 6152, 7168, 7176, 9224, 14336, 14344, 18432,
+                                  28672, 28680, 40968, 57344, 57352])
+def test_mask_rows_round_edges(cols):
+    """A wave takes a row in rounds of 512 columns, a compiled-in number of them, and a row has one to eight waves: widths at the edges
+    of all of these.  Ties that run out inside a round, at a round's end and at a wave's."""
+    w = np.concatenate([wl.gaussian_bf16((5, cols), 0.02, cols), _few_magnitudes((2, cols), cols + 1), np.full((2, cols), 0xBF80, np.uint16)])
+    w[-1, ::3] = 0x0000
+    for keep in sorted({cols // 2, min(cols, 512), cols - cols // 4, min(cols, 7168), cols - 1}):
+        _check_rows(w, keep, "round edges")
