@@ -137,3 +137,9 @@ def test_encode_capacity_inside_a_vector():
         got = to_host_u16(buf)
         assert np.array_equal(got[:cap], rv[:cap]) and (got[cap:] == 0x5A5A).all(), cap
         assert np.array_equal(to_host_u32(offsets), ro)
+
+
+@pytest.mark.parametrize("rows", [3, 255, 257, 4095, 4096, 4097, 32767, 32768, 32770, 65539])
+def test_codec_row_offsets_of_many_rows(rows):
+    """The running sum over the rows takes 4096 or 32768 of them a round, four to a load: row counts at those edges."""
+    _check_codec(_random_sparse(rows, 9, 0.6, rows), "row sums")
