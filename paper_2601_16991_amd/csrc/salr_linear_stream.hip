@@ -22,6 +22,7 @@
 #include "salr_device.hpp"
 #include "salr_internal.hpp"
 #include "salr_linear_common.hpp"
+#include "salr_row_stream.hpp"
 
 namespace salr {
 
@@ -39,18 +40,93 @@ struct StreamStage {
     uint32_t nv;                        // vectors in the piece
 };
 
+// ---- T = X A_cat in every workgroup, for layers whose A_cat is a few KB (see stream_owns_t): one launch instead of two, which is what
+// such a call's time is.  The requests for X and A_cat go out with the first of the weight's, the product is formed while the
+// packed values are on their way.
+// The partials are those of adapter_partial_kernel, summed in the same order, so T has the same bits: the steps of 32 columns of
+// a slice are sums of their own, added up in order, and the slices in order.  A wave takes two of the kStreamTSlices slices; its
+// rows of A_cat lie side by side, so they come as whole vectors and are read back transposed from its staging slots.
+constexpr int kOwnTK = 1024;                        // columns at most: four steps a wave
+constexpr int kOwnTSteps = kOwnTK / 32 / 8;
+constexpr int kOwnTRank = 32;
+constexpr int kOwnTBytes = 4096;                    // of A_cat at most that a wave's steps read: four vectors a lane
+typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+
+struct OwnT {
+    u32x4_t a[kOwnTBytes / 1024];
+    uint4 x[kOwnTSteps];
+    int u_begin, u_mid, u_end;   // steps of the wave's first slice and its second
+};
+
+__device__ __forceinline__ void own_t_request(OwnT& o, const uint16_t* __restrict__ x, int M, int64_t K,
+                                              const uint16_t* __restrict__ a_cat, int R, int wave, int lane) {
+    const int units = (int)(K >> 5), i16 = lane & 15, g = lane >> 4;
+    static_assert(kStreamTSlices == 16 && kOwnTBytes <= kStreamRows * kSlotDwords * 4);
+    o.u_begin = units * wave >> 3;
+    o.u_mid = units * (2 * wave + 1) >> 4;
+    o.u_end = units * (wave + 1) >> 3;
+    const Buffer piece = make_buffer(a_cat + (int64_t)o.u_begin * 32 * R, (uint64_t)(o.u_end - o.u_begin) * 64 * R);
+#pragma unroll
+    for (int i = 0; i < (int)(sizeof(o.a) / 16); ++i) o.a[i] = buffer_load4(piece, 16u * lane + 1024u * i);
+    const int m = i16 < M ? i16 : M - 1;
+#pragma unroll
+    for (int t = 0; t < kOwnTSteps; ++t) {
+        const int u = o.u_begin + t < units ? o.u_begin + t : units - 1;   // steps past the slices are dropped
+        o.x[t] = *reinterpret_cast<const uint4*>(x + (int64_t)m * K + 32 * u + 8 * g);
+    }
+}
+
+// partials: [rank tile][slice][16 rows][16 columns]; slots: 4 KB of this wave's
+__device__ __forceinline__ void own_t_partials(const OwnT& o, int R, int Rpad, uint32_t* slots, float* partials, int wave, int lane) {
+    const int i16 = lane & 15, g = lane >> 4;
+#pragma unroll
+    for (int i = 0; i < (int)(sizeof(o.a) / 16); ++i) *reinterpret_cast<u32x4_t*>(slots + 4 * lane + 256 * i) = o.a[i];
+    __builtin_amdgcn_wave_barrier();   // LDS executes a wave's accesses in order
+    const uint16_t* rows = reinterpret_cast<const uint16_t*>(slots);
+#pragma unroll
+    for (int rt = 0; rt < kOwnTRank / 16; ++rt) {
+        if (16 * rt >= Rpad) break;    // uniform
+        const int r = 16 * rt + i16, r_c = r < R ? r : R - 1;   // padded columns read a valid one and become zeros below
+        f32x4 product[kOwnTSteps];
+#pragma unroll
+        for (int t = 0; t < kOwnTSteps; ++t) {
+            product[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+            if (o.u_begin + t >= o.u_end) break;   // uniform
+            uint32_t e[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) e[j] = rows[(32 * t + 8 * g + j) * R + r_c];
+            const uint4 b = make_uint4(e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16), e[6] | (e[7] << 16));
+            product[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(o.x[t]), as_bf16x8(b), product[t], 0, 0, 0);
+        }
+        f32x4 first = {0.f, 0.f, 0.f, 0.f}, second = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int t = 0; t < kOwnTSteps; ++t) {
+            if (o.u_begin + t < o.u_mid) first += product[t];
+            else if (o.u_begin + t < o.u_end) second += product[t];
+        }
+        float* p = partials + (rt * kStreamTSlices + 2 * wave) * 256 + 64 * g + i16;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            p[16 * q] = r < R ? first[q] : 0.f;
+            p[256 + 16 * q] = r < R ? second[q] : 0.f;
+        }
+    }
+    __builtin_amdgcn_wave_barrier();   // the slots are free again
+}
+
 // MT m-tiles of 16 rows, NW waves per workgroup, S chunks in flight per wave.
 // kOwnPrefix: every wave popcounts the bitmap words left of its slice itself (short rows), so the
 // workgroup needs no barrier before the stream starts; otherwise the waves exchange slice counts.
 // kTable: the cursors come ready-made from the layer's slice table (salr_build_slice_table: for every row and each of
 // the 8 wave slices the index of the slice's first value and the most nonzeros any chunk of it holds): one 8-byte
 // request in place of the row offset, the rest of the slice's bitmap and the words left of it, and no barrier.
-template <int MT, int NW, int S, bool kVecBitmap, bool kOwnPrefix, bool kTable = false>
+// kOwnT: every workgroup computes T itself instead of reading the pre-kernel's partials (see stream_owns_t).
+template <int MT, int NW, int S, bool kVecBitmap, bool kOwnPrefix, bool kTable = false, bool kOwnT = false>
 __global__ __launch_bounds__(NW * 64, (S == 2 && MT == 1) ? 4 : 1) void linear_stream_kernel(
     const uint16_t* __restrict__ x, int M, int64_t K, int64_t N, const uint32_t* __restrict__ bitmap,
     const uint16_t* __restrict__ values, const uint32_t* __restrict__ row_offsets,
     const float* __restrict__ t_partial, const uint16_t* __restrict__ b_cat, int R, int Rpad,
-    uint16_t* __restrict__ y, const uint32_t* __restrict__ slice_table) {
+    uint16_t* __restrict__ y, const uint32_t* __restrict__ slice_table, const uint16_t* __restrict__ a_cat) {
     static_assert(!kTable || NW == kSliceTableSlices, "the table holds one entry per wave slice");
     constexpr int kThreads = NW * 64;
     constexpr int kStageDwords = NW * kStreamRows * kSlotDwords + 8;
@@ -114,7 +190,15 @@ __global__ __launch_bounds__(NW * 64, (S == 2 && MT == 1) ? 4 : 1) void linear_s
     // B operand of this wave's rank step (Sec. 3.2): lane (n, g) holds B_cat[32*wave + 8g + j][row], j = 0..7
     const bool has_rank_step = R > 0 && wave * 32 < Rpad;
     uint4 bq = make_uint4(0, 0, 0, 0);
-    if (has_rank_step) {
+    uint32_t late[8];   // kOwnT: packed where they are used (no constants here: the packing would move up to the loads and wait)
+    if constexpr (kOwnT) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) late[j] = (uint32_t)lane;
+        if (has_rank_step) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) late[j] = (uint32_t)b_cat[(int64_t)(8 * g + j < R ? 8 * g + j : R - 1) * N + row_c];
+        }
+    } else if (has_rank_step) {
         const int r0 = wave * 32 + 8 * g;
         uint32_t e[8];
 #pragma unroll
@@ -125,8 +209,11 @@ __global__ __launch_bounds__(NW * 64, (S == 2 && MT == 1) ? 4 : 1) void linear_s
         bq = make_uint4(e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16), e[6] | (e[7] << 16));
     }
 
+    __shared__ float own_t[kOwnT ? kOwnTRank / 16 * kStreamTSlices * 256 : 1];
+    OwnT own;
+    if constexpr (kOwnT) own_t_request(own, x, M, K, a_cat, R, wave, lane);
     // T = sum of the pre-kernel's split-K partials, rounded once to bf16, kept in LDS
-    if (R > 0) {
+    if (R > 0 && !kOwnT) {
         const int groups = M * (Rpad >> 2);  // float4 groups of T
         for (int i = tid; i < groups; i += kThreads) {
             float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -171,14 +258,15 @@ __global__ __launch_bounds__(NW * 64, (S == 2 && MT == 1) ? 4 : 1) void linear_s
         if constexpr (kOwnPrefix) {
             // nonzeros left of the slice: at most 7 chunks per lane (rows of <= 32 chunks), all in flight at once
             uint32_t before = 0;
-            uint4 left[7];  // no branches: chunks past the slice start re-read chunk 0 and are dropped
+            constexpr int kLeft = kOwnT ? kOwnTK / 512 : 7;
+            uint4 left[kLeft];  // no branches: chunks past the slice start re-read chunk 0 and are dropped
 #pragma unroll
-            for (int i = 0; i < 7; ++i) {
+            for (int i = 0; i < kLeft; ++i) {
                 const int64_t c = g + 4 * i;
                 left[i] = *reinterpret_cast<const uint4*>(brow + (c < c_begin ? c : 0) * kChunkWords);
             }
 #pragma unroll
-            for (int i = 0; i < 7; ++i) {
+            for (int i = 0; i < kLeft; ++i) {
                 const uint32_t cnt = __popc(left[i].x) + __popc(left[i].y) + __popc(left[i].z) + __popc(left[i].w);
                 before += (g + 4 * i < c_begin) ? cnt : 0u;
             }
@@ -284,7 +372,24 @@ __global__ __launch_bounds__(NW * 64, (S == 2 && MT == 1) ? 4 : 1) void linear_s
     };
 
     const int64_t n_chunks = c_end - c_begin;
-    if (n_chunks == S && !dense_slice) {
+    if constexpr (kOwnT) {
+        // one chunk at most: its requests, T behind them, and one wait
+        static_assert(kOwnTK <= 128 * NW && MT == 1);
+        StreamStage<MT, kMaxVecPerLane> st;
+        if (n_chunks > 0) issue(st, bmq[0], c_begin);   // wave-uniform
+        own_t_partials(own, R, Rpad, smem + wave * kStreamRows * kSlotDwords, own_t, wave, lane);
+        __syncthreads();
+        {
+            const int i = tid & 255, rt = tid >> 8;
+            if (16 * rt < Rpad) {
+                float sum = 0.f;
+#pragma unroll
+                for (int b = 0; b < kStreamTSlices; ++b) sum += own_t[(rt * kStreamTSlices + b) * 256 + i];
+                t_lds[(i >> 4) * kMaxRankPadded + 16 * rt + (i & 15)] = f32_to_bf16_rne(sum);
+            }
+        }
+        if (n_chunks > 0) consume(st);
+    } else if (n_chunks == S && !dense_slice) {
         // the whole slice is in flight at once: straight-line code, each chunk waits for its own data only
         StreamStage<MT, 3> st[S];
 #pragma unroll
@@ -331,6 +436,8 @@ __global__ __launch_bounds__(NW * 64, (S == 2 && MT == 1) ? 4 : 1) void linear_s
 
     // ---- adapter k-step of this wave (Sec. 3.2): A operand = T rows from LDS, B operand = bq
     if (has_rank_step) {
+        if constexpr (kOwnT)
+            bq = make_uint4(late[0] | (late[1] << 16), late[2] | (late[3] << 16), late[4] | (late[5] << 16), late[6] | (late[7] << 16));
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
             const int m = 16 * mt + n;
@@ -465,29 +572,48 @@ void launch_adapter_partial_to(const LinearArgs& a, float* partial, hipStream_t 
     launch_adapter_partial_impl(a, partial, false, stream);
 }
 
+// Whether the small-batch kernel computes T itself: up to 16 tokens, A_cat of up to 32 KB on rows that are one chunk per wave at most,
+// and fewer row groups than two per CU (the other variant has no registers for it).  Both ways, us a call (pre-kernel / here):
+// 16 x 512 x 512 rank 16 7.7 / 5.8, 1 x 512 x 1000 7.7 / 5.6, 16 x 1024 x 4096 rank 16 8.7 / 7.3, 16 x 512 x 8000 rank 32 11.0 / 9.1.
+// Reading A_cat costs a workgroup 0.3 us per 32 KB; twice that, in columns or rank, takes more of the staging slots than a wave has.
+static bool stream_owns_t(int64_t M, int64_t K, int64_t R) {
+    return R > 0 && R <= kOwnTRank && M <= 16 && K % 128 == 0 && K <= kOwnTK && (K / 32 + 7) / 8 * 64 * R <= kOwnTBytes;
+}
+
 template <int MT, int NW, int S>
 static void launch_stream_t(const LinearArgs& a, hipStream_t stream, const TimingEvents& ev) {
     const int R = (int)a.R, Rpad = (int)adapter_rank_padded(a.R);
     float* t_partial = reinterpret_cast<float*>(a.t);
+    const unsigned grid = (unsigned)((a.N + kStreamRows - 1) / kStreamRows);
+    if constexpr (MT == 1 && S > 2) {
+        if (stream_owns_t(a.M, a.K, R)) {
+            if (a.slice_table != nullptr && !a.build_table)
+                SALR_LAUNCH((linear_stream_kernel<MT, NW, S, true, false, true, true>), dim3(grid), dim3(NW * 64), stream, ev, a.x, (int)a.M,
+                            a.K, a.N, a.bitmap, a.values, a.row_offsets, nullptr, a.b_cat, R, Rpad, a.y, a.slice_table, a.a_cat);
+            else
+                SALR_LAUNCH((linear_stream_kernel<MT, NW, S, true, true, false, true>), dim3(grid), dim3(NW * 64), stream, ev, a.x, (int)a.M,
+                            a.K, a.N, a.bitmap, a.values, a.row_offsets, nullptr, a.b_cat, R, Rpad, a.y, nullptr, a.a_cat);
+            return;
+        }
+    }
     if (R > 0) launch_adapter_partial(a, stream);
     // the optional events take the kernel's own begin/end timestamps (null events = plain launch)
-    const unsigned grid = (unsigned)((a.N + kStreamRows - 1) / kStreamRows);
     const int64_t wpr = a.K / 32;
     const uint32_t* no_table = nullptr;
     if (a.slice_table != nullptr && wpr % kChunkWords == 0)   // prepared layer: cursors from its slice table
         SALR_LAUNCH((linear_stream_kernel<MT, NW, S, true, false, true>), dim3(grid), dim3(NW * 64), stream, ev, a.x, (int)a.M,
-                    a.K, a.N, a.bitmap, a.values, a.row_offsets, (const float*)t_partial, a.b_cat, R, Rpad, a.y, a.slice_table);
+                    a.K, a.N, a.bitmap, a.values, a.row_offsets, (const float*)t_partial, a.b_cat, R, Rpad, a.y, a.slice_table, a.a_cat);
     else if (wpr % kChunkWords != 0)  // bitmap rows are not multiples of 16 bytes: scalar bitmap loads
         SALR_LAUNCH((linear_stream_kernel<MT, NW, S, false, false>), dim3(grid), dim3(NW * 64), stream, ev, a.x, (int)a.M, a.K,
-                    a.N, a.bitmap, a.values, a.row_offsets, (const float*)t_partial, a.b_cat, R, Rpad, a.y, no_table);
+                    a.N, a.bitmap, a.values, a.row_offsets, (const float*)t_partial, a.b_cat, R, Rpad, a.y, no_table, a.a_cat);
     else if (wpr / kChunkWords <= 32 && S != 2)  // short rows and one workgroup per CU: barrier-free start (two workgroups
                                                  // per CU hide each other's barrier, and the bitmap words left of a slice,
                                                  // which every wave would fetch again, are a third of the L2 reads)
         SALR_LAUNCH((linear_stream_kernel<MT, NW, S, true, true>), dim3(grid), dim3(NW * 64), stream, ev, a.x, (int)a.M, a.K,
-                    a.N, a.bitmap, a.values, a.row_offsets, (const float*)t_partial, a.b_cat, R, Rpad, a.y, no_table);
+                    a.N, a.bitmap, a.values, a.row_offsets, (const float*)t_partial, a.b_cat, R, Rpad, a.y, no_table, a.a_cat);
     else
         SALR_LAUNCH((linear_stream_kernel<MT, NW, S, true, false>), dim3(grid), dim3(NW * 64), stream, ev, a.x, (int)a.M, a.K,
-                    a.N, a.bitmap, a.values, a.row_offsets, (const float*)t_partial, a.b_cat, R, Rpad, a.y, no_table);
+                    a.N, a.bitmap, a.values, a.row_offsets, (const float*)t_partial, a.b_cat, R, Rpad, a.y, no_table, a.a_cat);
 }
 
 hipError_t launch_linear_stream(const LinearArgs& a, hipStream_t stream, const TimingEvents& ev) {

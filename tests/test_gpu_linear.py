@@ -463,3 +463,16 @@ def test_row_tiled_any_width(M, K, N, ranks, density):
     assert np.array_equal(np.isnan(y), np.isnan(ref)) and np.array_equal(np.isinf(y), np.isinf(ref))
     x[:, K - 40] = 0x3F80
     _assert_close(_run(x, w, a_cat, b_cat), oracle.linear(x, w, a_cat, b_cat), f"any width M{M} K{K} N{N}")
+
+
+@pytest.mark.parametrize("M,K,N,ranks,density", [
+    (1, 128, 20, [1], 0.5), (16, 128, 500, [32], 0.9), (5, 256, 33, [3, 4], 0.5), (16, 384, 100, [16], 0.3), (13, 512, 512, [8, 8], 0.5),
+    (16, 512, 2000, [16, 16], 0.5), (2, 512, 1023, [17], 0.95), (16, 640, 77, [21], 0.5), (16, 640, 77, [25], 0.5), (7, 896, 300, [18], 0.7),
+    (16, 1024, 1024, [16], 0.5), (1, 1024, 8191, [15], 0.5), (16, 1024, 16, [16], 0.0)])
+def test_small_layers_with_their_adapters_in_one_kernel(M, K, N, ranks, density):
+    """Up to 16 tokens, 1024 columns and 4 KB of A_cat a wave the small-batch kernel forms X A_cat itself: the fewest and the most
+    columns, ranks on both sides of a tile of 16, waves without a chunk, rows that fill no tile.  The term alone as well."""
+    x, w, a_cat, b_cat = _problem(M, K, N, ranks, 5100 + M + K + N, density=density, std_ab=0.05)
+    _assert_close(_run(x, w, a_cat, b_cat), oracle.linear(x, w, a_cat, b_cat), f"one kernel M{M} K{K} N{N} R{sum(ranks)}")
+    w[:, 1:] = 0
+    _assert_close(_run(x, w, a_cat, b_cat), oracle.linear(x, w, a_cat, b_cat), f"one kernel, adapters alone M{M} K{K} N{N} R{sum(ranks)}")
