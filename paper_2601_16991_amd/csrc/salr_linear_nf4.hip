@@ -21,6 +21,7 @@
 #include "salr_internal.hpp"
 #include "salr_linear_common.hpp"
 #include "salr_nf4.hpp"
+#include "salr_row_stream.hpp"
 
 namespace salr {
 
@@ -31,6 +32,7 @@ constexpr int kQSlotDwords = 84;      // LDS per row per chunk: 160 bf16 (five v
                                       // dwords that the expansion may read past them; 84 n mod 64 are 16 different
                                       // multiples of 4, so the rows of a wave start in different banks
 constexpr int kQLevelWords = 16;
+constexpr int kQRowScales = 12;       // blocks that four chunks of a row's values may touch (ten), in whole requests of four lanes
 
 template <int MT>
 struct NfStage {
@@ -42,8 +44,8 @@ struct NfStage {
     uint32_t off;                    // nibble offset of the piece inside its first vector (0..31)
 };
 
-// MT m-tiles of 16 rows, S chunks in flight per wave.  K % 128 == 0, nnz > 0.
-template <int MT, int S>
+// MT m-tiles of 16 rows, S chunks in flight per wave.  K % 128 == 0, nnz > 0.  kShort: no slice has more than S chunks.
+template <int MT, int S, bool kShort>
 __global__ __launch_bounds__(kQWaves * 64, (S == 2 && MT == 1) ? 4 : 1) void linear_nf4_kernel(
     const uint16_t* __restrict__ x, int M, int64_t K, int64_t N, const uint32_t* __restrict__ bitmap,
     const uint8_t* __restrict__ codes, const uint16_t* __restrict__ scales, uint32_t scale_last,
@@ -60,6 +62,7 @@ __global__ __launch_bounds__(kQWaves * 64, (S == 2 && MT == 1) ? 4 : 1) void lin
     __shared__ __attribute__((aligned(16))) uint16_t t_lds[kTRows * kMaxRankPadded];  // T = X * A_cat, bf16
     __shared__ uint32_t lut_all[NW][kNibbleLutWords];   // one copy per wave: filled and used wave-synchronously
     __shared__ float level_all[NW][kQLevelWords];
+    __shared__ uint16_t scale_all[kShort ? NW : 1][kQRows * kQRowScales];
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -74,6 +77,7 @@ __global__ __launch_bounds__(kQWaves * 64, (S == 2 && MT == 1) ? 4 : 1) void lin
     const int64_t c_end = chunks_total * (wave + 1) / NW;
     uint32_t* lut = lut_all[wave];
     float* levels = level_all[wave];
+    uint16_t* my_scales = scale_all[kShort ? wave : 0];
     // Rows past N (last workgroup only) are computed as copies of row N-1 and dropped at the store.
     const int64_t row_c = row < N ? row : N - 1;
     const uint32_t* brow = bitmap + row_c * wpr;
@@ -87,8 +91,24 @@ __global__ __launch_bounds__(kQWaves * 64, (S == 2 && MT == 1) ? 4 : 1) void lin
         return q;
     };
     uint4 bmq[S];  // bitmap ring: chunks [c, c + S) ahead of the stages
+    // Slices of at most S chunks: one request for their bitmap, as in the bf16 kernel, and their scales by row, read back from LDS.
+    // (One scale per vector of codes, from sixteen rows each, keeps the address unit busier than the codes do.)  4096 x 4096 at 20 %
+    // sparsity: one token 15.1 -> 13.8 us with its pre-kernel, 16 tokens 17.5 -> 17.0; 8000 x 2048 at 50 %, 12 tokens: 19.6 -> 18.2.
+    const uint32_t block0 = cur / kNf4Block;
+    uint32_t row_scale[kQRowScales / 4];
+    u32x4 quad = {0, 0, 0, 0};
+    if constexpr (kShort) {
+        static_assert(S == 4);
+        if (c_begin + g < c_end) quad = *reinterpret_cast<const u32x4*>(brow + (c_begin + g) * kQChunkWords);
 #pragma unroll
-    for (int i = 0; i < S; ++i) bmq[i] = load_bitmap_chunk(c_begin + i);
+        for (int i = 0; i < kQRowScales / 4; ++i) {
+            const uint32_t blk = block0 + g + 4 * i;
+            row_scale[i] = scales[blk < scale_last ? blk : scale_last];
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < S; ++i) bmq[i] = load_bitmap_chunk(c_begin + i);
+    }
 
     // B operand of this wave's rank step (Sec. 3.2): lane (n, g) holds B_cat[32*wave + 8g + j][row], j = 0..7
     const bool has_rank_step = R > 0 && wave * 32 < Rpad;
@@ -132,6 +152,15 @@ __global__ __launch_bounds__(kQWaves * 64, (S == 2 && MT == 1) ? 4 : 1) void lin
     }
     __builtin_amdgcn_wave_barrier();
 
+    if constexpr (kShort) {
+#pragma unroll
+        for (int i = 0; i < kQRowScales / 4; ++i) my_scales[n * kQRowScales + g + 4 * i] = (uint16_t)row_scale[i];
+        u32x4 w[4];
+        spread_chunks(quad, w);
+#pragma unroll
+        for (int i = 0; i < S; ++i) bmq[i] = make_uint4(w[i].x, w[i].y, w[i].z, w[i].w);
+    }
+
     const uint4* codes128 = reinterpret_cast<const uint4*>(codes);
     uint32_t* slot = smem + (wave * kQRows + n) * kQSlotDwords;
 
@@ -162,8 +191,13 @@ __global__ __launch_bounds__(kQWaves * 64, (S == 2 && MT == 1) ? 4 : 1) void lin
         st.cq = vb[v_mine];
         st.c4 = reinterpret_cast<const uint32_t*>(vb + v_fifth)[g];
         const uint32_t blk = (vbase + v_mine) >> 1, blk4 = (vbase + v_fifth) >> 1;   // 64 values = two vectors per block
-        st.sc = scales[blk < scale_last ? blk : scale_last];
-        st.sc4 = scales[blk4 < scale_last ? blk4 : scale_last];
+        if constexpr (kShort) {   // their places in the row's
+            st.sc = blk - block0;
+            st.sc4 = blk4 - block0;
+        } else {
+            st.sc = scales[blk < scale_last ? blk : scale_last];
+            st.sc4 = scales[blk4 < scale_last ? blk4 : scale_last];
+        }
         cur += len;
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
@@ -177,7 +211,9 @@ __global__ __launch_bounds__(kQWaves * 64, (S == 2 && MT == 1) ? 4 : 1) void lin
 
     // Dequantise this lane's codes into the row's slot, expand the 4 byte masks of this lane, run the MFMAs.
     auto consume = [&](const NfStage<MT>& st) {
-        const float sa = __uint_as_float(st.sc << 16), s4 = __uint_as_float(st.sc4 << 16);   // bf16 -> fp32
+        const uint32_t bits = kShort ? my_scales[n * kQRowScales + st.sc] : st.sc;
+        const uint32_t bits4 = kShort ? my_scales[n * kQRowScales + st.sc4] : st.sc4;
+        const float sa = __uint_as_float(bits << 16), s4 = __uint_as_float(bits4 << 16);   // bf16 -> fp32
         uint4* slot4 = reinterpret_cast<uint4*>(slot);
         slot4[4 * g + 0] = nf4_decode8(st.cq.x, sa, levels);   // values 32 g .. 32 g + 31 of the slot
         slot4[4 * g + 1] = nf4_decode8(st.cq.y, sa, levels);
@@ -210,6 +246,14 @@ __global__ __launch_bounds__(kQWaves * 64, (S == 2 && MT == 1) ? 4 : 1) void lin
         for (int i = 0; i < S; ++i) issue(st[i], bmq[i], c_begin + i);
 #pragma unroll
         for (int i = 0; i < S; ++i) consume(st[i]);
+    } else if constexpr (kShort) {
+        NfStage<MT> st[S - 1];
+#pragma unroll
+        for (int i = 0; i < S - 1; ++i)
+            if (i < n_chunks) issue(st[i], bmq[i], c_begin + i);   // wave-uniform conditions
+#pragma unroll
+        for (int i = 0; i < S - 1; ++i)
+            if (i < n_chunks) consume(st[i]);
     } else if (n_chunks > 0) {
         NfStage<MT> st[S];
 #pragma unroll
@@ -275,13 +319,13 @@ size_t linear_nf4_workspace_bytes(int64_t M, int64_t N, int64_t R) {
     return linear_nf4_table_offset(M, R) + round_up_256(slice_table_bytes(N));
 }
 
-template <int MT, int S>
+template <int MT, int S, bool kShort = false>
 static void launch_nf4_t(const LinearArgs& a, const uint8_t* codes, const uint16_t* scales, int64_t nnz, hipStream_t stream,
                          const TimingEvents& ev) {
     const int R = (int)a.R, Rpad = (int)adapter_rank_padded(a.R);
     const unsigned grid = (unsigned)((a.N + kQRows - 1) / kQRows);
     const uint32_t scale_last = (uint32_t)((nnz + 63) / 64 - 1);
-    SALR_LAUNCH((linear_nf4_kernel<MT, S>), dim3(grid), dim3(kQWaves * 64), stream, ev, a.x, (int)a.M, a.K, a.N, a.bitmap, codes,
+    SALR_LAUNCH((linear_nf4_kernel<MT, S, kShort>), dim3(grid), dim3(kQWaves * 64), stream, ev, a.x, (int)a.M, a.K, a.N, a.bitmap, codes,
                 scales, scale_last, a.slice_table, reinterpret_cast<const float*>(a.t), a.b_cat, R, Rpad, a.y);
 }
 
@@ -298,6 +342,7 @@ hipError_t launch_linear_nf4(const LinearArgs& a_in, const uint8_t* codes, const
     }
     const bool many_groups = (a.N + kQRows - 1) / kQRows >= 2 * 256;
     if (a.M <= 16 && many_groups) launch_nf4_t<1, 2>(a, codes, scales, nnz, stream, ev);
+    else if (a.M <= 16 && a.K <= 4 * kQWaves * kQChunkWords * 32) launch_nf4_t<1, 4, true>(a, codes, scales, nnz, stream, ev);
     else if (a.M <= 16) launch_nf4_t<1, 4>(a, codes, scales, nnz, stream, ev);
     else if (a.M <= 32) launch_nf4_t<2, 3>(a, codes, scales, nnz, stream, ev);
     else launch_nf4_t<4, 2>(a, codes, scales, nnz, stream, ev);

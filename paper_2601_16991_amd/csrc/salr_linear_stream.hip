@@ -183,9 +183,27 @@ __global__ __launch_bounds__(NW * 64, (S == 2 && MT == 1) ? 4 : 1) void linear_s
         return q;
     };
 
+    // With four chunks in flight their bitmap comes as one request of 64 bytes a row, chunk c + g to lane (n, g), and goes to the
+    // other lanes in registers.  (A request a chunk, the same 16 bytes a row to four lanes, keeps the address unit busy for 31 ns
+    // each, this one for 20: 4096 x 4096, one token, 13.7 -> 13.2 us with its pre-kernel, 3000 x 5248 16.4 -> 15.4.)
+    constexpr bool kQuads = S == 4 && kVecBitmap;
+    auto load_quad = [&](int64_t c) -> u32x4 {
+        u32x4 q = {0, 0, 0, 0};
+        if (c + g < c_end) q = *reinterpret_cast<const u32x4*>(brow + (c + g) * kChunkWords);
+        return q;
+    };
     uint4 bmq[S];  // bitmap ring: chunks [c, c + S) ahead of the stages
+    auto spread_quad = [&](u32x4 q) {
+        u32x4 w[4];
+        spread_chunks(q, w);
 #pragma unroll
-    for (int i = 0; i < S; ++i) bmq[i] = load_bitmap_chunk(c_begin + i);
+        for (int i = 0; i < S && i < 4; ++i) bmq[i] = make_uint4(w[i].x, w[i].y, w[i].z, w[i].w);
+    };
+    u32x4 quad = {0, 0, 0, 0};
+    if constexpr (kQuads) quad = load_quad(c_begin);
+    else
+#pragma unroll
+        for (int i = 0; i < S; ++i) bmq[i] = load_bitmap_chunk(c_begin + i);
 
     // B operand of this wave's rank step (Sec. 3.2): lane (n, g) holds B_cat[32*wave + 8g + j][row], j = 0..7
     const bool has_rank_step = R > 0 && wave * 32 < Rpad;
@@ -238,6 +256,11 @@ __global__ __launch_bounds__(NW * 64, (S == 2 && MT == 1) ? 4 : 1) void linear_s
         lut[2 * lane + 1] = b;
     }
     __builtin_amdgcn_wave_barrier();
+
+    if constexpr (kQuads) {
+        spread_quad(quad);
+        if (!kOwnT && c_begin + S < c_end) quad = load_quad(c_begin + S);   // (uniform, as below)
+    }
 
     // ---- pre-pass: nonzeros of this wave's slice per row.  The first S chunks are already in
     // registers (all 4 lanes of a row hold them); the 4 lanes split the rest.
@@ -402,8 +425,12 @@ __global__ __launch_bounds__(NW * 64, (S == 2 && MT == 1) ? 4 : 1) void linear_s
         for (int i = 0; i < S; ++i) {
             if (c_begin + i < c_end) {
                 issue(st[i], bmq[i], c_begin + i);
-                bmq[i] = load_bitmap_chunk(c_begin + i + S);
+                if constexpr (!kQuads) bmq[i] = load_bitmap_chunk(c_begin + i + S);
             }
+        }
+        if (kQuads && c_begin + S < c_end) {
+            spread_quad(quad);
+            quad = load_quad(c_begin + 2 * S);
         }
         for (int64_t c = c_begin; c < c_end; c += S) {
 #pragma unroll
@@ -411,8 +438,12 @@ __global__ __launch_bounds__(NW * 64, (S == 2 && MT == 1) ? 4 : 1) void linear_s
                 if (c + i < c_end) consume(st[i]);  // wave-uniform conditions
                 if (c + i + S < c_end) {
                     issue(st[i], bmq[i], c + i + S);
-                    bmq[i] = load_bitmap_chunk(c + i + 2 * S);
+                    if constexpr (!kQuads) bmq[i] = load_bitmap_chunk(c + i + 2 * S);
                 }
+            }
+            if (kQuads && c + 2 * S < c_end) {
+                spread_quad(quad);
+                quad = load_quad(c + 3 * S);
             }
         }
     } else if (n_chunks > 0) {

@@ -116,4 +116,20 @@ __device__ __forceinline__ void spread_halves(uint32_t x, uint32_t& lo, uint32_t
     hi = p[1];
 }
 
+// Sixteen rows' bitmap words of four chunks, chunk g with lane (n, g), to all four lanes of the row: w[chunk][word].
+__device__ __forceinline__ void spread_chunks(u32x4 q, u32x4 (&w)[4]) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        uint32_t a, b;
+        spread_halves(q[i], a, b);   // [x0 x1 x0 x1], [x2 x3 x2 x3]
+        uint32_t a1 = a, b1 = b;
+        swap_odd_even_groups(a, a1);
+        swap_odd_even_groups(b, b1);
+        w[0][i] = a;
+        w[1][i] = a1;
+        w[2][i] = b;
+        w[3][i] = b1;
+    }
+}
+
 }  // namespace salr

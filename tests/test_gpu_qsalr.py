@@ -198,3 +198,21 @@ def test_qsalr_row_tiled(M, K, N, R, permille):
                           None if b_cat is None else to_dev_u16(b_cat))
     torch.cuda.synchronize()
     assert float(np.max(np.abs(y_to_f64(y) - y_ref))) <= 1e-2 * float(np.max(np.abs(y_ref)))
+
+
+@pytest.mark.parametrize("M,K,N,permille", [(1, 4096, 50, 0), (16, 4096, 33, 10), (2, 2944, 100, 500), (16, 1920, 17, 0), (5, 4224, 40, 0),
+                                            (1, 4096, 16, 990)])
+def test_qsalr_slices_with_scales_by_row(M, K, N, permille):
+    """Up to 4096 columns a wave reads its slice's scales by row: full rows, whose slices touch ten blocks of 64 values, nearly empty
+    ones, one to four chunks a wave, and the first width past it.  Bit for bit the plain call on the dequantised values."""
+    salr = _salr()
+    w = wl.gaussian_bf16((N, K), 0.02, 800 + M + K)
+    w_hat = oracle.mask_topk_rows(w, K - K * permille // 1000) if permille else w.copy()
+    w_hat[1, :: 3] = 0       # pieces start at every place of a block
+    rb, rv, ro = oracle.encode(w_hat)
+    codes, scales = salr.nf4_quantize(to_dev_u16(rv))
+    x, rbd, rod = to_dev_u16(wl.gaussian_bf16((M, K), 1.0, 801)), to_dev_u32(rb), to_dev_u32(ro)
+    y = salr.qsalr_linear(x, rbd, codes, scales, rod, int(ro[-1]), None, None)
+    y2 = _plain_on_dequantised(salr, x, rbd, codes, scales, rod, int(ro[-1]), None, None)
+    torch.cuda.synchronize()
+    assert np.array_equal(to_host_u16(y), to_host_u16(y2))
