@@ -18,34 +18,50 @@ namespace salr {
 constexpr int kCodecThreads = 256;             // 4 waves
 constexpr int kChunkValuesMax = kCodecThreads * kUnit;  // packed values one step can own
 
-template <bool kVec>
-__global__ __launch_bounds__(kCodecThreads) void encode_count_kernel(const uint16_t* __restrict__ w,
+constexpr int kDecWaves = kCodecThreads / kWave;
+
+// Rows of up to 4096 columns (eight groups of 512), where they are many, go a wave each: a workgroup per row is mostly the start of it
+// then, with waves that have no group and barriers for the rest.  Workgroup / wave per row, us to encode and to decode: 26496 x 1408
+// 63 + 31 / 52 + 19, 12788 x 512 31.6 + 12.2 / 27.0 + 5.9, 3000 x 768 19.3 + 5.1 / 18.7 + 4.2, 8842 x 3072 42.2 + 17.0 / 41.6 + 15.3,
+// 20000 x 4096 81.4 + 40.3 / 78.2 + 39.7; 4324 x 7040 43.9 + 17.3 / 44.9 + 16.9, 600 x 3072 17.6 + 4.3 / 19.7 + 4.7.
+static bool wave_per_row(int64_t rows, int64_t cols) { return cols <= 4096 && rows > 2048; }
+
+// kWaveRow: a wave per row.
+template <bool kVec, bool kWaveRow>
+__global__ __launch_bounds__(kCodecThreads) void encode_count_kernel(const uint16_t* __restrict__ w, int64_t rows,
                                                                      int64_t cols, int64_t wpr,
                                                                      uint32_t* __restrict__ bitmap,
                                                                      uint32_t* __restrict__ row_offsets) {
-    __shared__ uint32_t scratch[kCodecThreads / kWave];
-    const int64_t n = blockIdx.x;
+    __shared__ uint32_t scratch[kDecWaves];
+    const int lane = lane_id();
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int64_t n = kWaveRow ? (int64_t)blockIdx.x * kDecWaves + wave : (int64_t)blockIdx.x;
+    if (n >= rows) return;   // only with kWaveRow: nothing below synchronises across waves then
     const uint16_t* row = w + n * cols;
     const int64_t units = wpr * 4;  // whole words: pad bytes are produced as zeros
     uint32_t count = 0;
-    for (int64_t base = 0; base < units; base += kCodecThreads) {
-        const int64_t u = base + threadIdx.x;
+    for (int64_t base = 0; base < units; base += kWaveRow ? kWave : kCodecThreads) {
+        const int64_t u = base + (kWaveRow ? lane : (int)threadIdx.x);
         const uint32_t m = nonzero_mask8(load_unit<kVec>(row, cols, u));
         count += __popc(m);
-        // four neighbouring lanes hold the four bytes of one word
-        const uint32_t b1 = __shfl_down(m, 1, kWave);
-        const uint32_t b2 = __shfl_down(m, 2, kWave);
-        const uint32_t b3 = __shfl_down(m, 3, kWave);
-        if ((threadIdx.x & 3) == 0 && u < units) bitmap[n * wpr + (u >> 2)] = m | (b1 << 8) | (b2 << 16) | (b3 << 24);
+        // four neighbouring lanes hold the four bytes of one word, the first of them collects it (quad_perm 1, 2, 3)
+        const uint32_t b1 = __builtin_amdgcn_update_dpp(0u, m, 0x01, 0xf, 0xf, false);
+        const uint32_t b2 = __builtin_amdgcn_update_dpp(0u, m, 0x02, 0xf, 0xf, false);
+        const uint32_t b3 = __builtin_amdgcn_update_dpp(0u, m, 0x03, 0xf, 0xf, false);
+        if ((lane & 3) == 0 && u < units) bitmap[n * wpr + (u >> 2)] = m | (b1 << 8) | (b2 << 16) | (b3 << 24);
     }
-#pragma unroll
-    for (int d = kWave / 2; d > 0; d >>= 1) count += __shfl_down(count, d, kWave);
-    if (lane_id() == 0) scratch[threadIdx.x / kWave] = count;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        uint32_t s = 0;
-        for (int i = 0; i < kCodecThreads / kWave; ++i) s += scratch[i];
-        row_offsets[n + 1] = s;  // the scan turns counts into offsets in place
+    count = last_lane(wave_inclusive_scan(count));
+    // the scan over the rows turns counts into offsets in place
+    if constexpr (kWaveRow) {
+        if (lane == 0) row_offsets[n + 1] = count;
+    } else {
+        if (lane == 0) scratch[wave] = count;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            uint32_t s = 0;
+            for (int i = 0; i < kDecWaves; ++i) s += scratch[i];
+            row_offsets[n + 1] = s;
+        }
     }
 }
 
@@ -149,7 +165,6 @@ __global__ __launch_bounds__(kCodecThreads) void encode_compact_kernel(const uin
     }
 }
 
-constexpr int kDecWaves = kCodecThreads / kWave;
 constexpr int kDecMaxGroups = 1024;   // rows up to 524288 columns
 
 // prefix[g] = nonzeros of a bitmap row before group g of 16 words (512 columns), prefix[groups] = all of them; the whole
@@ -184,15 +199,19 @@ __device__ __forceinline__ void group_prefix(const uint32_t* brow, int64_t wpr, 
 // wave scan of the byte popcounts, the nonzeros dropped into the wave's LDS slot at their place in the output's 16-byte
 // vectors, whole vectors stored as such, the ragged ends of the piece as single values.  Bound by memory: 4096 x 14336 at
 // 50 %, 176 MB: 43.6 us with a block scan per 2048 columns and a two-byte store per value, now 36.
-__global__ __launch_bounds__(kCodecThreads) void encode_compact_rows_kernel(const uint16_t* __restrict__ w, int64_t cols, int64_t wpr,
+// kWaveRow: short rows, a wave per row that takes its groups in order, each where the one before ends; no pass over the bitmap, no barrier.
+template <bool kWaveRow>
+__global__ __launch_bounds__(kCodecThreads) void encode_compact_rows_kernel(const uint16_t* __restrict__ w, int64_t rows, int64_t cols, int64_t wpr,
                                                                             const uint32_t* __restrict__ bitmap,
                                                                             const uint32_t* __restrict__ row_offsets,
                                                                             uint16_t* __restrict__ values, int64_t capacity) {
-    __shared__ uint32_t prefix[kDecMaxGroups + 1];
+    __shared__ uint32_t prefix[kWaveRow ? 1 : kDecMaxGroups + 1];
     __shared__ __attribute__((aligned(16))) uint16_t slot[kDecWaves][65 * 8];
     const int lane = lane_id();
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const int64_t n = blockIdx.x;
+    const int64_t n = kWaveRow ? (int64_t)blockIdx.x * kDecWaves + wave : (int64_t)blockIdx.x;
+    if (n >= rows) return;   // only with kWaveRow: nothing below synchronises across waves then
+    constexpr int kStep = kWaveRow ? 1 : kDecWaves;
     const uint32_t* brow = bitmap + n * wpr;
     const int groups = (int)((wpr + 15) / 16);
     const uint16_t* row = w + n * cols;
@@ -206,17 +225,19 @@ __global__ __launch_bounds__(kCodecThreads) void encode_compact_rows_kernel(cons
         return *reinterpret_cast<const uint4*>(row + uc * kUnit);
     };
     uint32_t m;
-    uint4 q = load_group(wave, m);
-    group_prefix(brow, wpr, groups, prefix);
-    const uint32_t row_start = row_offsets[n];
+    uint4 q = load_group(kWaveRow ? 0 : wave, m);
+    if constexpr (!kWaveRow) group_prefix(brow, wpr, groups, prefix);
+    uint32_t row_start = row_offsets[n];
     uint16_t* my_slot = slot[wave];
     const uint32_t cap = capacity < 0xFFFFFFFFLL ? (uint32_t)capacity : 0xFFFFFFFFu;
-    for (int g = wave; g < groups; g += kDecWaves) {
+    for (int g = kWaveRow ? 0 : wave; g < groups; g += kStep) {
         uint32_t m_next;
-        const uint4 next = load_group(g + kDecWaves, m_next);
-        const uint32_t cursor = row_start + prefix[g], total = prefix[g + 1] - prefix[g];
+        const uint4 next = load_group(g + kStep, m_next);
+        const uint32_t incl = wave_inclusive_scan(__popc(m));
+        const uint32_t cursor = kWaveRow ? row_start : row_start + prefix[g], total = last_lane(incl);
+        if constexpr (kWaveRow) row_start += total;
         const uint32_t first = cursor & 7u;   // position of the piece's first value in its first output vector
-        uint32_t at = first + wave_inclusive_scan(__popc(m)) - __popc(m);
+        uint32_t at = first + incl - __popc(m);
 #pragma unroll
         for (int j = 0; j < kUnit; ++j) {
             if ((m >> j) & 1u) my_slot[at] = (uint16_t)unit_elem(q, j);
@@ -300,24 +321,38 @@ __global__ __launch_bounds__(kCodecThreads) void decode_kernel(const uint32_t* _
 // kNf4 (QSALR, paper Sec. 4): `values` are the 4-bit codes, eight to a dword where the bf16 kernel has a 16-byte vector of
 // eight values; a lane dequantises its dword (all eight codes lie in one scale block of 64) on the way into the slot,
 // and everything after that is the same.  scale_last: index of the last scale.
-template <bool kNf4>
+// kWaveRow: short rows, a wave per row (see encode_compact_rows_kernel).
+template <bool kNf4, bool kWaveRow>
 __global__ __launch_bounds__(kCodecThreads) void decode_rows_kernel(const uint32_t* __restrict__ bitmap,
                                                                     const uint16_t* __restrict__ values,
-                                                                    const uint32_t* __restrict__ row_offsets, int64_t cols,
+                                                                    const uint32_t* __restrict__ row_offsets, int64_t rows, int64_t cols,
                                                                     int64_t wpr, uint16_t* __restrict__ out,
                                                                     const uint16_t* __restrict__ scales, uint32_t scale_last) {
-    __shared__ uint32_t prefix[kDecMaxGroups + 1];
-    __shared__ float levels[16];
-    if (kNf4 && threadIdx.x < 16) levels[threadIdx.x] = kNf4Levels[threadIdx.x];
+    __shared__ uint32_t prefix[kWaveRow ? 1 : kDecMaxGroups + 1];
+    __shared__ float levels_all[kWaveRow ? kDecWaves : 1][16];
     __shared__ __attribute__((aligned(16))) uint32_t slot[kDecWaves][65 * 4 + 8];
-    __shared__ uint32_t lut[kNibbleLutWords];
-    nibble_lut_init(lut);
+    __shared__ uint32_t lut_all[kWaveRow ? kDecWaves : 1][kNibbleLutWords];
     const int lane = lane_id();
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const int64_t n = blockIdx.x;
+    uint32_t* lut = lut_all[kWaveRow ? wave : 0];
+    float* levels = levels_all[kWaveRow ? wave : 0];
+    if (kNf4 && (kWaveRow ? lane : (int)threadIdx.x) < 16) levels[lane] = kNf4Levels[lane];
+    if constexpr (kWaveRow) {   // tables of its own for each wave
+        if (lane < 16) {
+            uint32_t a, b;
+            nibble_lut_entry(lane, a, b);
+            lut[2 * lane] = a;
+            lut[2 * lane + 1] = b;
+        }
+        __builtin_amdgcn_wave_barrier();   // LDS executes a wave's accesses in order
+    } else {
+        nibble_lut_init(lut);
+    }
+    const int64_t n = kWaveRow ? (int64_t)blockIdx.x * kDecWaves + wave : (int64_t)blockIdx.x;
+    if (n >= rows) return;   // only with kWaveRow: nothing below synchronises across waves then
     const uint32_t* brow = bitmap + n * wpr;
     const int groups = (int)((wpr + 15) / 16);
-    group_prefix(brow, wpr, groups, prefix);   // ---- pass 1
+    if constexpr (!kWaveRow) group_prefix(brow, wpr, groups, prefix);   // ---- pass 1
     // ---- pass 2
     const uint8_t* mask_bytes = reinterpret_cast<const uint8_t*>(brow);
     const uint4* values128 = reinterpret_cast<const uint4*>(values);
@@ -338,14 +373,27 @@ __global__ __launch_bounds__(kCodecThreads) void decode_rows_kernel(const uint32
     };
     uint16_t* row_out = out + n * cols;
     const int64_t units = (cols + kUnit - 1) / kUnit;
-    const uint32_t row_start = row_offsets[n];
+    uint32_t row_start = row_offsets[n];
     uint32_t* my_slot = slot[wave];
-    auto group_loads = [&](int g, uint32_t& m, uint4& v, uint32_t& off, uint32_t& nv, uint32_t& vbase) {
+    auto load_mask = [&](int g) -> uint32_t {
         const int64_t u = 64 * (int64_t)g + lane;
-        m = (g < groups && u < units) ? mask_bytes[u] : 0u;
-        const uint32_t gi = g < groups ? g : groups - 1;
-        const uint32_t cursor = row_start + prefix[gi];
-        const uint32_t total = g < groups ? prefix[gi + 1] - prefix[gi] : 0u;
+        return (g < groups && u < units) ? mask_bytes[u] : 0u;
+    };
+    uint32_t ahead = kWaveRow ? load_mask(0) : 0u;   // the mask of the group whose values are asked for next
+    auto group_loads = [&](int g, uint32_t& m, uint4& v, uint32_t& off, uint32_t& nv, uint32_t& vbase) {
+        uint32_t cursor, total;
+        if constexpr (kWaveRow) {
+            m = ahead;
+            ahead = load_mask(g + 1);
+            cursor = row_start;
+            total = last_lane(wave_inclusive_scan(__popc(m)));
+            row_start += total;
+        } else {
+            m = load_mask(g);
+            const uint32_t gi = g < groups ? g : groups - 1;
+            cursor = row_start + prefix[gi];
+            total = g < groups ? prefix[gi + 1] - prefix[gi] : 0u;
+        }
         off = cursor & 7u;
         nv = total ? (off + total + 7u) >> 3 : 0u;
         // lanes past the piece repeat its last vector (clamped, not predicated); an empty piece loads nothing new
@@ -355,11 +403,12 @@ __global__ __launch_bounds__(kCodecThreads) void decode_rows_kernel(const uint32
     };
     uint32_t m, off, nv, vbase;
     uint4 v;
-    group_loads(wave, m, v, off, nv, vbase);
-    for (int g = wave; g < groups; g += kDecWaves) {
+    constexpr int kStep = kWaveRow ? 1 : kDecWaves;
+    group_loads(kWaveRow ? 0 : wave, m, v, off, nv, vbase);
+    for (int g = kWaveRow ? 0 : wave; g < groups; g += kStep) {
         uint32_t m2, off2, nv2, vbase2;
         uint4 v2;
-        group_loads(g + kDecWaves, m2, v2, off2, nv2, vbase2);   // next group of this wave, in flight while this one expands
+        group_loads(g + kStep, m2, v2, off2, nv2, vbase2);   // next group of this wave, in flight while this one expands
         const uint32_t incl = wave_inclusive_scan(__popc(m));
         if ((uint32_t)lane < nv) reinterpret_cast<uint4*>(my_slot)[lane] = ready(v);
         // a full group that starts off a vector boundary spans 65 vectors: the last one is fetched on the spot
@@ -373,6 +422,16 @@ __global__ __launch_bounds__(kCodecThreads) void decode_rows_kernel(const uint32
     }
 }
 
+template <bool kNf4>
+static void launch_decode_rows(const uint32_t* bitmap, const uint16_t* values, const uint32_t* row_offsets, int64_t rows, int64_t cols,
+                               uint16_t* out, const uint16_t* scales, uint32_t scale_last, hipStream_t stream) {
+    const int64_t wpr = (cols + 31) / 32;
+    const bool wave_row = wave_per_row(rows, cols);
+    const dim3 grid((unsigned)(wave_row ? (rows + kDecWaves - 1) / kDecWaves : rows)), block(kCodecThreads);
+    if (wave_row) hipLaunchKernelGGL((decode_rows_kernel<kNf4, true>), grid, block, 0, stream, bitmap, values, row_offsets, rows, cols, wpr, out, scales, scale_last);
+    else hipLaunchKernelGGL((decode_rows_kernel<kNf4, false>), grid, block, 0, stream, bitmap, values, row_offsets, rows, cols, wpr, out, scales, scale_last);
+}
+
 static bool vec_ok(const void* p, int64_t cols);
 
 // QSALR: decode from the 4-bit codes straight into the dense matrix (no bf16 copy of the values in between)
@@ -384,10 +443,8 @@ bool decode_nf4_takes(int64_t rows, int64_t cols, int64_t nnz, const void* codes
 
 hipError_t launch_decode_nf4(const uint32_t* bitmap, const uint8_t* codes, const uint16_t* scales, int64_t nnz,
                              const uint32_t* row_offsets, int64_t rows, int64_t cols, uint16_t* out, hipStream_t stream) {
-    const int64_t wpr = (cols + 31) / 32;
-    hipLaunchKernelGGL(decode_rows_kernel<true>, dim3((unsigned)rows), dim3(kCodecThreads), 0, stream, bitmap,
-                       reinterpret_cast<const uint16_t*>(codes), row_offsets, cols, wpr, out, scales,
-                       (uint32_t)((nnz + kNf4Block - 1) / kNf4Block - 1));
+    launch_decode_rows<true>(bitmap, reinterpret_cast<const uint16_t*>(codes), row_offsets, rows, cols, out, scales,
+                             (uint32_t)((nnz + kNf4Block - 1) / kNf4Block - 1), stream);
     return hipGetLastError();
 }
 
@@ -399,8 +456,11 @@ hipError_t launch_encode_index(const uint16_t* w, int64_t rows, int64_t cols, ui
                                unsigned long long* nnz_host, hipStream_t stream) {
     const int64_t wpr = (cols + 31) / 32;
     if (rows > 0) {
-        if (vec_ok(w, cols)) hipLaunchKernelGGL(encode_count_kernel<true>, dim3((unsigned)rows), dim3(kCodecThreads), 0, stream, w, cols, wpr, bitmap, row_offsets);
-        else hipLaunchKernelGGL(encode_count_kernel<false>, dim3((unsigned)rows), dim3(kCodecThreads), 0, stream, w, cols, wpr, bitmap, row_offsets);
+        const bool wave_row = wave_per_row(rows, cols);
+        const dim3 grid((unsigned)(wave_row ? (rows + kDecWaves - 1) / kDecWaves : rows)), block(kCodecThreads);
+        auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, stream, w, rows, cols, wpr, bitmap, row_offsets); };
+        if (vec_ok(w, cols)) wave_row ? go(encode_count_kernel<true, true>) : go(encode_count_kernel<true, false>);
+        else wave_row ? go(encode_count_kernel<false, true>) : go(encode_count_kernel<false, false>);
     }
     // one vector a wave as far as that is one round (4096 rows 4.1 us), else eight (6016 rows 6.6, 26496 rows 6.5)
     if (rows <= 4 * kScanThreads) hipLaunchKernelGGL((row_scan_kernel<1>), dim3(1), dim3(kScanThreads), 0, stream, row_offsets, rows, nnz_host);
@@ -412,9 +472,12 @@ hipError_t launch_encode_values(const uint16_t* w, int64_t rows, int64_t cols, c
                                 uint16_t* values, int64_t capacity, hipStream_t stream) {
     if (values == nullptr || rows == 0 || cols == 0) return hipSuccess;
     const int64_t wpr = (cols + 31) / 32;
-    if (vec_ok(w, cols) && vec_ok(values, kUnit) && (wpr + 15) / 16 <= kDecMaxGroups)
-        hipLaunchKernelGGL(encode_compact_rows_kernel, dim3((unsigned)rows), dim3(kCodecThreads), 0, stream, w, cols, wpr, bitmap, row_offsets, values, capacity);
-    else if (vec_ok(w, cols))
+    if (vec_ok(w, cols) && vec_ok(values, kUnit) && (wpr + 15) / 16 <= kDecMaxGroups) {
+        if (wave_per_row(rows, cols))
+            hipLaunchKernelGGL(encode_compact_rows_kernel<true>, dim3((unsigned)((rows + kDecWaves - 1) / kDecWaves)), dim3(kCodecThreads), 0, stream, w, rows, cols, wpr, bitmap, row_offsets, values, capacity);
+        else
+            hipLaunchKernelGGL(encode_compact_rows_kernel<false>, dim3((unsigned)rows), dim3(kCodecThreads), 0, stream, w, rows, cols, wpr, bitmap, row_offsets, values, capacity);
+    } else if (vec_ok(w, cols))
         hipLaunchKernelGGL(encode_compact_kernel<true>, dim3((unsigned)rows), dim3(kCodecThreads), 0, stream, w, cols, row_offsets, values, capacity);
     else
         hipLaunchKernelGGL(encode_compact_kernel<false>, dim3((unsigned)rows), dim3(kCodecThreads), 0, stream, w, cols, row_offsets, values, capacity);
@@ -432,8 +495,7 @@ hipError_t launch_decode(const uint32_t* bitmap, const uint16_t* values, const u
     if (rows == 0 || cols == 0) return hipSuccess;
     const int64_t wpr = (cols + 31) / 32;
     if (vec_ok(out, cols) && (wpr + 15) / 16 <= kDecMaxGroups && (reinterpret_cast<uintptr_t>(values) & 15u) == 0)
-        hipLaunchKernelGGL(decode_rows_kernel<false>, dim3((unsigned)rows), dim3(kCodecThreads), 0, stream, bitmap, values,
-                           row_offsets, cols, wpr, out, (const uint16_t*)nullptr, 0u);
+        launch_decode_rows<false>(bitmap, values, row_offsets, rows, cols, out, nullptr, 0u, stream);
     else if (vec_ok(out, cols))
         hipLaunchKernelGGL(decode_kernel<true>, dim3((unsigned)rows), dim3(kCodecThreads), 0, stream, bitmap, values, row_offsets, rows, cols, wpr, out);
     else

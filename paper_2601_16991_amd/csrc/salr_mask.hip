@@ -148,18 +148,8 @@ __device__ __forceinline__ void for_rounds(F&& f) {
     }
 }
 
-// Inclusive scan over the wave, without LDS; the last lane's is the sum.
-__device__ __forceinline__ uint32_t wave_scan(uint32_t x) {
-    x += __builtin_amdgcn_update_dpp(0u, x, 0x111, 0xf, 0xf, false);   // row_shr 1, 2, 4, 8: a scan of each 16 lanes
-    x += __builtin_amdgcn_update_dpp(0u, x, 0x112, 0xf, 0xf, false);
-    x += __builtin_amdgcn_update_dpp(0u, x, 0x114, 0xf, 0xf, false);
-    x += __builtin_amdgcn_update_dpp(0u, x, 0x118, 0xf, 0xf, false);
-    x += __builtin_amdgcn_update_dpp(0u, x, 0x142, 0xa, 0xf, false);   // row_bcast 15, then 31: the sums of the rows before
-    x += __builtin_amdgcn_update_dpp(0u, x, 0x143, 0xc, 0xf, false);
-    return x;
-}
-__device__ __forceinline__ uint32_t last_lane(uint32_t x) { return (uint32_t)__builtin_amdgcn_readlane((int)x, kWave - 1); }
-__device__ __forceinline__ uint32_t wave_total(uint32_t x) { return last_lane(wave_scan(x)); }
+// Sum over the wave, in every lane.
+__device__ __forceinline__ uint32_t wave_total(uint32_t x) { return last_lane(wave_inclusive_scan(x)); }
 
 constexpr uint32_t kTop = 0x80008000u;   // the top bit of both entries of a dword
 constexpr uint32_t kOnes = 0x00010001u;
@@ -401,7 +391,7 @@ __global__ __launch_bounds__(kW == 1 ? kMaskThreads : kW * kWave) void mask_rows
                 uint32_t tied = 0;   // a bit per entry
 #pragma unroll
                 for (int j = 0; j < kUnit; ++j) tied |= (uint32_t)(((e[j >> 1] >> (16 * (j & 1))) & 0x7FFFu) == T) << j;
-                uint32_t rank = ties + wave_scan(__popc(tied)) - __popc(tied);
+                uint32_t rank = ties + wave_inclusive_scan(__popc(tied)) - __popc(tied);
                 u32x4 o = {0, 0, 0, 0};
 #pragma unroll
                 for (int j = 0; j < kUnit; ++j) {

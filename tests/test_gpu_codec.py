@@ -143,3 +143,15 @@ def test_encode_capacity_inside_a_vector():
 def test_codec_row_offsets_of_many_rows(rows):
     """The running sum over the rows takes 4096 or 32768 of them a round, four to a load: row counts at those edges."""
     _check_codec(_random_sparse(rows, 9, 0.6, rows), "row sums")
+
+
+@pytest.mark.parametrize("rows,cols", [(2048, 512), (2049, 512), (2050, 8), (2051, 520), (2049, 1032), (2052, 4096), (2049, 4104), (2053, 37),
+                                       (2049, 4090)])
+def test_codec_wave_per_row(rows, cols):
+    """More than 2048 rows of up to 4096 columns go a wave each: both sides of each line, rows that fill no group or workgroup, full and
+    empty rows, and widths without whole vectors."""
+    w = _random_sparse(rows, cols, 0.5, rows + cols)
+    w[5] = 0x3F80
+    w[6] = 0
+    w[-1] = 0x3F80
+    _check_codec(w, "wave per row")
