@@ -129,15 +129,24 @@ __device__ __forceinline__ void adapter_t_block(const uint16_t* __restrict__ x, 
             }
         }
     };
-    // a ring: a step is requested again as soon as its registers are free, kDepth steps ahead
+    if constexpr (kFactor == kFactorAny) {   // element loads are packed, and so waited for, where they are asked for: kDepth steps at once
+        for (int64_t s0 = wave; s0 < steps; s0 += kWaves * kDepth) {
 #pragma unroll
-    for (int d = 0; d < kDepth; ++d) request(d, wave + kWaves * d);
-    for (int64_t s0 = wave; s0 < steps; s0 += kWaves * kDepth) {
+            for (int d = 0; d < kDepth; ++d) request(d, s0 + kWaves * d);
 #pragma unroll
-        for (int d = 0; d < kDepth; ++d) {
-            const int64_t s = s0 + kWaves * d;
-            if (s < steps) multiply(d, s);   // wave-uniform
-            request(d, s + kWaves * kDepth);
+            for (int d = 0; d < kDepth; ++d)
+                if (s0 + kWaves * d < steps) multiply(d, s0 + kWaves * d);   // wave-uniform
+        }
+    } else {   // a ring: a step is requested again as soon as its registers are free, kDepth steps ahead
+#pragma unroll
+        for (int d = 0; d < kDepth; ++d) request(d, wave + kWaves * d);
+        for (int64_t s0 = wave; s0 < steps; s0 += kWaves * kDepth) {
+#pragma unroll
+            for (int d = 0; d < kDepth; ++d) {
+                const int64_t s = s0 + kWaves * d;
+                if (s < steps) multiply(d, s);   // wave-uniform
+                request(d, s + kWaves * kDepth);
+            }
         }
     }
     __syncthreads();

@@ -333,19 +333,6 @@ PyObject* py_mask(PyObject*, PyObject* const* v, Py_ssize_t n) {
     SALR_CATCH
 }
 
-// Wait until a kernel queued on the stream has written *word (pinned memory, 0 before).  Polled, because the wake-up of a stream
-// synchronisation leaves the GPU idle 5 us longer.  The stream is asked about every millisecond, so that a failed launch ends the
-// wait; asked every few microseconds, the question itself cost 8 us.
-hipError_t wait_for(const volatile unsigned long long* word, hipStream_t stream) {
-    for (uint32_t i = 1; *word == 0; ++i) {
-        __builtin_ia32_pause();
-        if (i % 65536 != 0) continue;
-        const hipError_t e = hipStreamQuery(stream);
-        if (e != hipErrorNotReady) return e == hipSuccess ? hipStreamSynchronize(stream) : e;
-    }
-    return hipSuccess;
-}
-
 // encode(w) -> (bitmap, values, row_offsets).  `values` can only be sized once the nonzeros are counted: the encoder's
 // first half leaves their number in pinned memory, the host waits for it once, and the second half follows.
 PyObject* py_encode(PyObject*, PyObject* w_o) {
@@ -358,19 +345,17 @@ PyObject* py_encode(PyObject*, PyObject* w_o) {
     if (rows > 0x7FFFFFFFLL || cols > 0x7FFFFFFFLL - 31 || (cols > 0 && rows > 0xFFFFFFFFLL / cols)) check(SALR_ERR_SHAPE, "salr_encode_bitmap");
     at::Tensor bitmap = empty_on({rows, (cols + 31) / 32}, at::kInt, w), offsets = empty_on({rows + 1}, at::kInt, w);
     uint32_t *bp = device_ptr<uint32_t>(bitmap, kU32, "bitmap"), *rp = device_ptr<uint32_t>(offsets, kU32, "row_offsets");
-    at::Tensor count = at::empty({1}, at::TensorOptions().dtype(at::kLong).pinned_memory(true));
-    volatile unsigned long long* total = static_cast<unsigned long long*>(count.data_ptr());
-    *total = 0;
+    at::Tensor count = at::empty({1}, at::TensorOptions().dtype(at::kInt).pinned_memory(true));
+    uint32_t* nnz_host = static_cast<uint32_t*>(count.data_ptr());
     hipStream_t stream = static_cast<hipStream_t>(stream_of(Py_None));
     hipError_t e;
     {
         Gil release;
-        e = salr::launch_encode_index(wp, rows, cols, bp, rp, static_cast<unsigned long long*>(count.data_ptr()), stream);
-        if (e == hipSuccess) e = wait_for(total, stream);
-        if (e != hipSuccess) (void)hipStreamSynchronize(stream);   // nothing may still write to `count`
+        e = salr::launch_encode_index(wp, rows, cols, bp, rp, nnz_host, stream);
+        if (e == hipSuccess) e = hipStreamSynchronize(stream);
     }
     check(e == hipSuccess ? SALR_OK : SALR_ERR_HIP, "salr_encode_bitmap");
-    const int64_t nnz = (int64_t)(*total & 0xFFFFFFFFull);
+    const int64_t nnz = *static_cast<volatile uint32_t*>(nnz_host);
     at::Tensor values = values_alloc(nnz, w);
     e = nnz > 0 ? salr::launch_encode_values(wp, rows, cols, bp, rp, static_cast<uint16_t*>(values.data_ptr()), nnz, stream) : hipSuccess;
     check(e == hipSuccess ? SALR_OK : SALR_ERR_HIP, "salr_encode_bitmap");
