@@ -68,12 +68,12 @@ __global__ __launch_bounds__(kCodecThreads) void encode_count_kernel(const uint1
 constexpr int kScanThreads = 1024;
 
 // row_offsets[1..rows] holds per-row counts on entry and inclusive prefix sums on exit; [0] = 0.  *nnz_host (pinned host memory,
-// may be null): the total, and 1 in the upper half, which a waiting host may poll.  One workgroup, bound by the latency of its
+// may be null) gets the total as well.  One workgroup, bound by the latency of its
 // rounds: a wave takes 256 * kVectors consecutive rows a round, all its loads (1 KB each) in flight (with eight consecutive rows a
 // thread, 26496 rows took 25.8 us and 4096 5.7; now 6.5 and 4.1).
 template <int kVectors>
 __global__ __launch_bounds__(kScanThreads) void row_scan_kernel(uint32_t* __restrict__ row_offsets, int64_t rows,
-                                                                unsigned long long* __restrict__ nnz_host) {
+                                                                uint32_t* __restrict__ nnz_host) {
     __shared__ uint32_t wave_sums[2][kScanThreads / kWave];
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4), aligned(4)));
     const int lane = lane_id();
@@ -132,7 +132,7 @@ __global__ __launch_bounds__(kScanThreads) void row_scan_kernel(uint32_t* __rest
     }
     if (threadIdx.x == 0) {
         row_offsets[0] = 0;
-        if (nnz_host != nullptr) __hip_atomic_store(nnz_host, 1ull << 32 | carry, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        if (nnz_host != nullptr) *nnz_host = carry;
     }
 }
 
@@ -453,7 +453,7 @@ static bool vec_ok(const void* p, int64_t cols) {
 }
 
 hipError_t launch_encode_index(const uint16_t* w, int64_t rows, int64_t cols, uint32_t* bitmap, uint32_t* row_offsets,
-                               unsigned long long* nnz_host, hipStream_t stream) {
+                               uint32_t* nnz_host, hipStream_t stream) {
     const int64_t wpr = (cols + 31) / 32;
     if (rows > 0) {
         const bool wave_row = wave_per_row(rows, cols);

@@ -14,9 +14,9 @@ hipError_t launch_encode(const uint16_t* w, int64_t rows, int64_t cols, uint32_t
                          int64_t capacity, uint32_t* row_offsets, hipStream_t stream);
 
 // The two halves of it, for a caller that sizes `values` in between: bitmap and row offsets (the total also to *nnz_host,
-// pinned host memory, with 1 in the upper half, unless null), then the packed values.
+// pinned host memory, unless null), then the packed values.
 hipError_t launch_encode_index(const uint16_t* w, int64_t rows, int64_t cols, uint32_t* bitmap, uint32_t* row_offsets,
-                               unsigned long long* nnz_host, hipStream_t stream);
+                               uint32_t* nnz_host, hipStream_t stream);
 hipError_t launch_encode_values(const uint16_t* w, int64_t rows, int64_t cols, const uint32_t* bitmap, const uint32_t* row_offsets,
                                 uint16_t* values, int64_t capacity, hipStream_t stream);
 
