@@ -129,7 +129,7 @@ salr_status_t salr_decode(const uint32_t* bitmap, const uint16_t* values, const 
  * then reads; for batches of up to 128 tokens with adapters on rows of whole
  * 128-column chunks, a slice table (64 bytes per weight row, see below) that the call builds for itself beside the
  * first adapter product when it is not handed one.  Nothing in it outlives the call.  Returns 0 for invalid sizes.
- * For large batches the fastest path can use more: see salr_linear_workspace_bytes_fastest.
+ * The fastest path can use more: see salr_linear_workspace_bytes_fastest.
  */
 size_t salr_linear_workspace_bytes(int64_t M, int64_t K, int64_t N, int64_t R);
 
@@ -173,7 +173,9 @@ size_t salr_linear_workspace_bytes_min(int64_t M, int64_t K, int64_t N, int64_t 
 
 /*
  * The workspace with which salr_sparse_lowrank_linear (and its _prepared form) is fastest; never less than
- * salr_linear_workspace_bytes and the same for small batches.  Large batches decode the weight into the order in which
+ * salr_linear_workspace_bytes.  Up to 128 tokens layers of more than a few MB go through a kernel that shares X between
+ * the 128 rows of a workgroup and splits K, if there is room for its fp32 partial outputs (16 x 7168 x 6932 37 us on the size
+ * above, 26 with room; 99 x 7648 x 12288 140 and 59).  Large batches decode the weight into the order in which
  * the matrix cores read it, with B_cat behind it and rows in whole blocks of 16, and split the contraction where the
  * outputs are few; what that takes is about the size above where K is a multiple of 64, a few percent more where N is no
  * multiple of 16 or the adapters' part is not in it, and 2 N K bytes more where K is not (K % 64 == 32; with the size
@@ -264,6 +266,8 @@ salr_status_t salr_sparse_lowrank_linear_noalloc(const uint16_t* x, int64_t M, i
  * salr_qsalr_linear is salr_sparse_lowrank_linear on such a weight: Y = X * W-hat'^T + (X * A_cat) * B_cat with
  * W-hat' = decode(bitmap, dequantised values); arguments, rounding and errors otherwise as there.  nnz =
  * row_offsets[N], which the caller knows from encoding (host value).
+ *   - Up to 128 tokens, where the plain layer has its row-tiled kernel and the workspace the room for it
+ *     (salr_qsalr_linear_workspace_bytes_fastest), that kernel reads the codes.
  *   - Up to 64 tokens on rows of whole 128-column chunks (K % 128 == 0, nnz > 0) one kernel reads bitmap, codes and
  *     scales and dequantises inside its decode stage: the weight crosses the memory system at 1 + 4.25 (1 - p) bits
  *     per element and no bf16 copy of the values exists.  Workspace: the layer's partial sums of X * A_cat and a

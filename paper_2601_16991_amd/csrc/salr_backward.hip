@@ -3,13 +3,14 @@
 //     dX = dY What + (dY B_cat^T) A_cat^T        [M, K]
 //     dA = X^T (dY B_cat^T)                      [K, R]
 //     dB = (X A_cat)^T dY                        [R, N]
-// Five launches (six where the matrix stage splits its contraction; fewer where not all gradients are asked for):
-//     T' = dY B_cat^T and T = X A_cat, both as they are [M, Rpad] and transposed (backward_t_kernel);
-//     the transposed weight in MFMA operand order, A_cat's rank blocks behind it (decode_transposed_frags_kernel);
+// Four launches (five where the matrix stage splits its contraction; fewer where not all gradients are asked for):
+//     the transposed weight in MFMA operand order, A_cat's rank blocks behind it (decode_transposed_frags_kernel), and in the same
+//     launch's first workgroups T' = dY B_cat^T and T = X A_cat, both as they are [M, Rpad] and transposed (a launch of their own,
+//     backward_t_kernel, where the weight is not wanted or R is no multiple of 8);
 //     dX: the large-batch matrix stage on dY and that weight, T' riding along as its adapter steps (salr_gemm.hip);
 //     dA, dB: products that contract over the rows of X and dY against T'^T and T^T (tall_tn_kernel) and their sums over slices.
-// As in the forward pass T and T' are rounded to bf16 once; sums are fp32; outputs bf16.  The sixteen slices of T and T' interleave
-// (every sixteenth step of 64 columns), so a sum can differ from one over contiguous slices in its last bits, and where it sits on
+// As in the forward pass T and T' are rounded to bf16 once; sums are fp32; outputs bf16.  The slices of T and T', one
+// per wave, interleave (every n-th step of 64 columns to a wave), so a sum can differ from one over contiguous slices in its last bits, and where it sits on
 // a rounding boundary by one bf16 step: about 2e-4 of dA and dB in the 2-norm against such a sum; against fp64 both are off by
 // 2.35e-3, the two roundings.
 #include "salr_device.hpp"

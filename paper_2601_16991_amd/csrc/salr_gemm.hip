@@ -624,22 +624,19 @@ void launch_frag_gemm(const uint16_t* x, int64_t M, int64_t K, int64_t N, const 
     if (p.ksplit > 1) launch_splitk_reduce(partial, M * N, p.ksplit, y, stream);
 }
 
-// T = X * A_cat straight to bf16 [M, Rpad] in one launch: sixteen waves per 16 or 32 rows and 32 ranks.
-template <int kMT, int kDepth>
+// T = X * A_cat straight to bf16 [M, Rpad] in one launch (more than kAdapterSmallM rows): sixteen waves per 32 rows and 32 ranks.
 __global__ __launch_bounds__(1024) void adapter_t_direct_kernel(const uint16_t* __restrict__ x, int64_t M, int64_t K,
                                                                 const uint16_t* __restrict__ a_cat, int R, int Rpad,
                                                                 uint16_t* __restrict__ t) {
-    __shared__ __attribute__((aligned(16))) uint16_t lds[adapter_t_lds_bytes<kMT, 16>() / 2];
+    __shared__ __attribute__((aligned(16))) uint16_t lds[adapter_t_lds_bytes<2, 16>() / 2];
     const int groups = Rpad >> 5;
-    adapter_t_block<kMT, 16, kDepth>(x, M, K, a_cat, R, Rpad, t, blockIdx.x / groups, (int)blockIdx.x % groups, lds);
+    adapter_t_block<2, 16, 2>(x, M, K, a_cat, R, Rpad, t, blockIdx.x / groups, (int)blockIdx.x % groups, lds);
 }
 
 void launch_adapter_t_direct(const uint16_t* x, int64_t M, int64_t K, const uint16_t* a_cat, int R, int Rpad, uint16_t* t,
                              hipStream_t stream) {
-    const int rows = 16 * adapter_t_row_tiles(M);
-    const dim3 grid((unsigned)((M + rows - 1) / rows * (Rpad / 32)));
-    if (rows == 32) hipLaunchKernelGGL((adapter_t_direct_kernel<2, 2>), grid, dim3(1024), 0, stream, x, M, K, a_cat, R, Rpad, t);
-    else hipLaunchKernelGGL((adapter_t_direct_kernel<1, 3>), grid, dim3(1024), 0, stream, x, M, K, a_cat, R, Rpad, t);
+    const dim3 grid((unsigned)((M + 31) / 32 * (Rpad / 32)));
+    hipLaunchKernelGGL(adapter_t_direct_kernel, grid, dim3(1024), 0, stream, x, M, K, a_cat, R, Rpad, t);
 }
 
 // T = X * A_cat as a product with A_cat in operand order (af): 256 rows x all ranks (128 at a time) per workgroup, K split over
