@@ -332,15 +332,15 @@ inline RowtilePlan rowtile_plan(int64_t M, int64_t K, int64_t N, int64_t R, size
                           0.07 * (double)(chunks - chunks / ks);
             const double t = R > 0 ? 3.0 + (double)((K / 32 + 32 * ts - 1) / (32 * ts)) * 1.2 : 0.0;   // eight waves, four steps at a time
             if (main < t) main = t;
-            const double cost = main + (partial ? 4.5 + (double)ks * (double)M * (double)N * 2e-6 : 0.0);
+            const double cost = main + (partial ? 3.7 + (double)ks * (double)M * (double)N * 2e-6 : 0.0);
             if (cost < best_cost) {
                 best_cost = cost;
                 best.ksplit = (int)ks;
                 best.t_slices = ts;
                 best.partial = partial;
             }
-            if (R == 0 && filled == 1 && best.ksplit > 1) {   // one slice writes y itself
-                const double alone = 5.0 + (double)((tiles + 255) / 256 * chunks) * step + (double)((tiles + 255) / 256 - 1) * 2.5;
+            if (R == 0 && filled == 1 && best.ksplit > 1) {   // one slice writes y itself (whole rows measured 0.84 us a chunk)
+                const double alone = 5.0 + (double)((tiles + 255) / 256 * chunks) * step * 1.2 + (double)((tiles + 255) / 256 - 1) * 2.5;
                 if (alone < best_cost) {
                     best_cost = alone;
                     best = RowtilePlan();
@@ -423,6 +423,9 @@ inline bool rowtile_wide(int64_t M, int64_t K, int64_t N, int64_t R) {
     if (M <= 8 && K > 24576 && N > 4096) return false;   // 1 x 28672 x 8192: 83.5 in the long-row kernel, 92 here (three slices on 192 CUs)
     if (M > 32) return true;
     if (M > 16) return K >= 1024 || N >= 8192;
+    // without adapters that kernel is one launch and this one two: 2 x 2048 x 9300 10.8 / 13.0, 2 x 1856 x 11293 12.1 / 15.3,
+    // 2 x 2560 x 9300 16.2 / 15.0; 16 x 2048 x 9300 19.4 / 13.5
+    if (R == 0 && M <= 8 && K <= 2048 && N < 16384) return false;
     return N * K >= (18 << 20) || N >= 16384 || K >= (R > 0 ? 5376 : 8192);
 }
 // What either kind of call uses: no more than the told size where that one has always had the kernel, so that the split, and with
