@@ -120,8 +120,9 @@ __device__ __forceinline__ void own_t_partials(const OwnT& o, int R, int Rpad, u
 // kTable: the cursors come ready-made from the layer's slice table (salr_build_slice_table: for every row and each of
 // the 8 wave slices the index of the slice's first value and the most nonzeros any chunk of it holds): one 8-byte
 // request in place of the row offset, the rest of the slice's bitmap and the words left of it, and no barrier.
+// kQuads: the bitmap of four chunks in one request.
 // kOwnT: every workgroup computes T itself instead of reading the pre-kernel's partials (see stream_owns_t).
-template <int MT, int NW, int S, bool kVecBitmap, bool kOwnPrefix, bool kTable = false, bool kOwnT = false>
+template <int MT, int NW, int S, bool kVecBitmap, bool kOwnPrefix, bool kTable = false, bool kOwnT = false, bool kQuads = false>
 __global__ __launch_bounds__(NW * 64, (S == 2 && MT == 1) ? 4 : 1) void linear_stream_kernel(
     const uint16_t* __restrict__ x, int M, int64_t K, int64_t N, const uint32_t* __restrict__ bitmap,
     const uint16_t* __restrict__ values, const uint32_t* __restrict__ row_offsets,
@@ -183,10 +184,10 @@ __global__ __launch_bounds__(NW * 64, (S == 2 && MT == 1) ? 4 : 1) void linear_s
         return q;
     };
 
-    // With four chunks in flight their bitmap comes as one request of 64 bytes a row, chunk c + g to lane (n, g), and goes to the
+    // kQuads: the bitmap of the four chunks in flight comes as one request of 64 bytes a row, chunk c + g to lane (n, g), and goes to the
     // other lanes in registers.  (A request a chunk, the same 16 bytes a row to four lanes, keeps the address unit busy for 31 ns
     // each, this one for 20: 4096 x 4096, one token, 13.7 -> 13.2 us with its pre-kernel, 3000 x 5248 16.4 -> 15.4.)
-    constexpr bool kQuads = S == 4 && kVecBitmap;
+    static_assert(!kQuads || (S == 4 && kVecBitmap));
     auto load_quad = [&](int64_t c) -> u32x4 {
         u32x4 q = {0, 0, 0, 0};
         if (c + g < c_end) q = *reinterpret_cast<const u32x4*>(brow + (c + g) * kChunkWords);
@@ -611,12 +612,12 @@ static bool stream_owns_t(int64_t M, int64_t K, int64_t R) {
     return R > 0 && R <= kOwnTRank && M <= 16 && K % 128 == 0 && K <= kOwnTK && (K / 32 + 7) / 8 * 64 * R <= kOwnTBytes;
 }
 
-template <int MT, int NW, int S>
+template <int MT, int NW, int S, bool kQ = false>
 static void launch_stream_t(const LinearArgs& a, hipStream_t stream, const TimingEvents& ev) {
     const int R = (int)a.R, Rpad = (int)adapter_rank_padded(a.R);
     float* t_partial = reinterpret_cast<float*>(a.t);
     const unsigned grid = (unsigned)((a.N + kStreamRows - 1) / kStreamRows);
-    if constexpr (MT == 1 && S > 2) {
+    if constexpr (MT == 1 && S > 2 && !kQ) {
         if (stream_owns_t(a.M, a.K, R)) {
             if (a.slice_table != nullptr && !a.build_table)
                 SALR_LAUNCH((linear_stream_kernel<MT, NW, S, true, false, true, true>), dim3(grid), dim3(NW * 64), stream, ev, a.x, (int)a.M,
@@ -632,7 +633,7 @@ static void launch_stream_t(const LinearArgs& a, hipStream_t stream, const Timin
     const int64_t wpr = a.K / 32;
     const uint32_t* no_table = nullptr;
     if (a.slice_table != nullptr && wpr % kChunkWords == 0)   // prepared layer: cursors from its slice table
-        SALR_LAUNCH((linear_stream_kernel<MT, NW, S, true, false, true>), dim3(grid), dim3(NW * 64), stream, ev, a.x, (int)a.M,
+        SALR_LAUNCH((linear_stream_kernel<MT, NW, S, true, false, true, false, kQ>), dim3(grid), dim3(NW * 64), stream, ev, a.x, (int)a.M,
                     a.K, a.N, a.bitmap, a.values, a.row_offsets, (const float*)t_partial, a.b_cat, R, Rpad, a.y, a.slice_table, a.a_cat);
     else if (wpr % kChunkWords != 0)  // bitmap rows are not multiples of 16 bytes: scalar bitmap loads
         SALR_LAUNCH((linear_stream_kernel<MT, NW, S, false, false>), dim3(grid), dim3(NW * 64), stream, ev, a.x, (int)a.M, a.K,
@@ -640,10 +641,10 @@ static void launch_stream_t(const LinearArgs& a, hipStream_t stream, const Timin
     else if (wpr / kChunkWords <= 32 && S != 2)  // short rows and one workgroup per CU: barrier-free start (two workgroups
                                                  // per CU hide each other's barrier, and the bitmap words left of a slice,
                                                  // which every wave would fetch again, are a third of the L2 reads)
-        SALR_LAUNCH((linear_stream_kernel<MT, NW, S, true, true>), dim3(grid), dim3(NW * 64), stream, ev, a.x, (int)a.M, a.K,
+        SALR_LAUNCH((linear_stream_kernel<MT, NW, S, true, true, false, false, kQ>), dim3(grid), dim3(NW * 64), stream, ev, a.x, (int)a.M, a.K,
                     a.N, a.bitmap, a.values, a.row_offsets, (const float*)t_partial, a.b_cat, R, Rpad, a.y, no_table, a.a_cat);
     else
-        SALR_LAUNCH((linear_stream_kernel<MT, NW, S, true, false>), dim3(grid), dim3(NW * 64), stream, ev, a.x, (int)a.M, a.K,
+        SALR_LAUNCH((linear_stream_kernel<MT, NW, S, true, false, false, false, kQ>), dim3(grid), dim3(NW * 64), stream, ev, a.x, (int)a.M, a.K,
                     a.N, a.bitmap, a.values, a.row_offsets, (const float*)t_partial, a.b_cat, R, Rpad, a.y, no_table, a.a_cat);
 }
 
@@ -653,6 +654,7 @@ hipError_t launch_linear_stream(const LinearArgs& a, hipStream_t stream, const T
     // workgroups share a CU, so one group's start-up and reduction overlap the other's stream.
     const bool many_groups = (a.N + kStreamRows - 1) / kStreamRows >= 2 * 256;
     if (a.M <= 16 && many_groups) launch_stream_t<1, NW, 2>(a, stream, ev);
+    else if (a.M <= 16 && a.K > 2 * NW * kChunkWords * 32) launch_stream_t<1, NW, 4, true>(a, stream, ev);   // (three chunks a wave and more: two come faster one by one)
     else if (a.M <= 16) launch_stream_t<1, NW, 4>(a, stream, ev);
     else if (a.M <= 32) launch_stream_t<2, NW, 3>(a, stream, ev);
     else launch_stream_t<4, NW, 2>(a, stream, ev);
