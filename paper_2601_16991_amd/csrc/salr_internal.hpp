@@ -422,8 +422,11 @@ inline bool rowtile_wide(int64_t M, int64_t K, int64_t N, int64_t R) {
     if (M > kRowtileMaxM || K < 128 || K % 32 != 0 || K > kRowtileMaxColumns || N < 128) return false;
     if (M <= 8 && K > 24576 && N > 4096) return false;   // 1 x 28672 x 8192: 83.5 in the long-row kernel, 92 here (three slices on 192 CUs)
     if (M > 32) return true;
+    // without adapters that kernel is one launch and this one two: 24 x 1024 x 4000 6.4 / 10.2, 17 x 2560 x 3500 9.8 / 12.2,
+    // 24 x 1152 x 7800 12.6 / 11.8, 17 x 4096 x 1000 12.5 / 13.9, 17 x 4096 x 1500 13.4 / 12.5, 24 x 2560 x 5000 18.7 / 12.6
+    if (M > 16 && R == 0) return K >= (N >= 1500 ? 4096 : 5376) || N >= 7168 || N * K >= (12 << 20);
     if (M > 16) return K >= 1024 || N >= 8192;
-    // without adapters that kernel is one launch and this one two: 2 x 2048 x 9300 10.8 / 13.0, 2 x 1856 x 11293 12.1 / 15.3,
+    // as there: 2 x 2048 x 9300 10.8 / 13.0, 2 x 1856 x 11293 12.1 / 15.3,
     // 2 x 2560 x 9300 16.2 / 15.0; 16 x 2048 x 9300 19.4 / 13.5
     if (R == 0 && M <= 8 && K <= 2048 && N < 16384) return false;
     return N * K >= (18 << 20) || N >= 16384 || K >= (R > 0 ? 5376 : 8192);
