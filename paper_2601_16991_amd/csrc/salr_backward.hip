@@ -6,7 +6,7 @@
 // Four launches (five where the matrix stage splits its contraction; fewer where not all gradients are asked for):
 //     the transposed weight in MFMA operand order, A_cat's rank blocks behind it (decode_transposed_frags_kernel), and in the same
 //     launch's first workgroups T' = dY B_cat^T and T = X A_cat, both as they are [M, Rpad] and transposed (a launch of their own,
-//     backward_t_kernel, where the weight is not wanted or R is no multiple of 8);
+//     backward_t_kernel, where the weight is not wanted, R is no multiple of 8 or the chains are long and many);
 //     dX: the large-batch matrix stage on dY and that weight, T' riding along as its adapter steps (salr_gemm.hip);
 //     dA, dB: products that contract over the rows of X and dY against T'^T and T^T (tall_tn_kernel) and their sums over slices.
 // As in the forward pass T and T' are rounded to bf16 once; sums are fp32; outputs bf16.  The slices of T and T', one
@@ -85,7 +85,12 @@ hipError_t launch_linear_backward(const uint16_t* x, const uint16_t* dy, int64_t
     LowRankJob dy_b = none, x_a = none;
     if (R > 0 && (want_dx || da != nullptr)) dy_b = {dy, b_cat, N, at(p.off_tp), da != nullptr ? at(p.off_tp_t) : nullptr};
     if (R > 0 && db != nullptr) x_a = {x, a_cat, K, at(p.off_tt), at(p.off_tt_t)};
-    const bool with_decode = want_dx && R % 8 == 0;
+    // (A launch of their own, four times the waves to a chain of steps, where the chains are long and there are many of them for the
+    // weight's size.  Own launch / in the decode launch, us a call: 3392 x 19072 x 576 rank 64 263 / 275, 4096 x 8192 x 512 rank 128
+    // 215 / 223, 4096 x 10240 x 1024 rank 64 197 / 203; 3392 x 6144 x 1024 rank 128 196 / 192, 2048 x 1024 x 10240 rank 64 126 / 115,
+    // 2048 x 4096 x 14336 rank 32 313 / 287.)
+    const bool short_chains = K <= 6144 && N <= 6144, few = M * (K + N) * ((p.Rpad + 31) / 32) <= 6 * N * K;
+    const bool with_decode = want_dx && R % 8 == 0 && (short_chains || few);
     if (R > 0 && !with_decode) launch_backward_t(dy_b, x_a, M, R, stream);
     if (want_dx) {
         const hipError_t e = launch_decode_transposed_frags(bitmap, values, row_offsets, N, K, a_cat, R, at(p.off_wf), with_decode ? dy_b : none,
