@@ -115,7 +115,7 @@ __global__ __launch_bounds__(kScanThreads) void row_scan_kernel(uint32_t* __rest
             before += i < wave ? s : 0u;
             carry += s;
         }
-        parity ^= 1;   // the other half was read before this round's barrier
+        parity ^= 1;   // the other half was read before this turn's barrier
 #pragma unroll
         for (int j = 0; j < kVectors; ++j) {
             const int64_t r = r0 + j * (4 * kWave);
