@@ -431,14 +431,22 @@ inline bool rowtile_wide(int64_t M, int64_t K, int64_t N, int64_t R) {
     if (R == 0 && M <= 8 && K <= 2048 && N < 16384) return false;
     return N * K >= (18 << 20) || N >= 16384 || K >= (R > 0 ? 5376 : 8192);
 }
-// What either kind of call uses: no more than the told size where that one has always had the kernel, so that the split, and with
-// it every bit of the result, does not depend on what a caller brings beyond it.
+// Whether the told size is all that the kernel ever uses: where that one has always had it with a split of K, so that the split, and
+// with it every bit of the result, does not depend on what a caller brings beyond it.  (N % 4 != 0: the told size has no room for
+// a split, the fastest one has: 64 x 4096 x 14335 at rank 32 52.3 us without, 33.3 with (14336: 31.7), 16 x 8192 x 8193 61.8 / 32.6;
+// 4-bit values, 37 x 17536 x 10315: 273 / 106, the small-batch kernel 170.)
+inline bool rowtile_on_told_size(int64_t M, int64_t K, int64_t N) { return uses_rowtile(M, K, N) && N % 4 == 0; }
 inline RowtilePlan rowtile_plan_of(int64_t M, int64_t K, int64_t N, int64_t R) {
-    return rowtile_plan(M, K, N, R, uses_rowtile(M, K, N) ? linear_workspace_bytes(M, K, N, R) : SIZE_MAX);
+    return rowtile_plan(M, K, N, R, rowtile_on_told_size(M, K, N) ? linear_workspace_bytes(M, K, N, R) : SIZE_MAX);
 }
 inline size_t rowtile_bytes(int64_t M, int64_t K, int64_t N, int64_t R) {
     const RowtilePlan p = rowtile_plan_of(M, K, N, R);
     return p.partial ? round_up_256(rowtile_t_out_bytes(M, R) + (size_t)p.ksplit * rowtile_partial_bytes(M, N)) : rowtile_t_bytes(M, K, R);
+}
+// The plan of a call that brings `room` bytes: the one above, or the one that fits the told size.
+inline RowtilePlan rowtile_plan_in(int64_t M, int64_t K, int64_t N, int64_t R, size_t room) {
+    if (rowtile_on_told_size(M, K, N) || room >= rowtile_bytes(M, K, N, R)) return rowtile_plan_of(M, K, N, R);
+    return rowtile_plan(M, K, N, R, linear_workspace_bytes(M, K, N, R));
 }
 // share of the CUs that a single round of workgroups gives work; 0 where there are more rounds
 inline double rowtile_fill(int64_t M, int64_t K, int64_t N, int64_t R) {
@@ -460,8 +468,8 @@ inline bool linear_takes_frag(int64_t M, int64_t K, int64_t N, int64_t R, size_t
 // Workspace with which the layer is fastest (salr_linear_workspace_bytes_fastest).
 inline size_t linear_workspace_bytes_fastest(int64_t M, int64_t K, int64_t N, int64_t R) {
     const size_t told = linear_workspace_bytes(M, K, N, R);
-    if (N <= 0 || uses_rowtile(M, K, N)) return told;
-    if (rowtile_wide(M, K, N, R)) {
+    if (N <= 0 || rowtile_on_told_size(M, K, N)) return told;
+    if (uses_rowtile(M, K, N) || rowtile_wide(M, K, N, R)) {
         const size_t b = rowtile_bytes(M, K, N, R);
         return b > told ? b : told;
     }

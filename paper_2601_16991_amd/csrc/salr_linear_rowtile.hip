@@ -553,7 +553,7 @@ static void launch_rowtile_t(const LinearArgs& a, RowtileArgs p, hipStream_t str
 hipError_t launch_linear_rowtile(const LinearArgs& a, hipStream_t stream, const TimingEvents& ev) {
     char* base = reinterpret_cast<char*>(a.t);
     const int Rpad = (int)adapter_rank_padded(a.R);
-    const RowtilePlan plan = rowtile_plan_of(a.M, a.K, a.N, a.R);
+    const RowtilePlan plan = rowtile_plan_in(a.M, a.K, a.N, a.R, a.room);
     RowtileArgs p;
     p.pitch = rowtile_pitch(a.N);
     p.ksplit = plan.ksplit;

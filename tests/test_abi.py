@@ -185,6 +185,18 @@ def test_fastest_workspace_bytes(lib):
     assert query("salr_qsalr_linear_workspace_bytes_fastest", 300, 64, 8, 4, -1) == 0
 
 
+@pytest.mark.parametrize("M,K,N,R", [(64, 4096, 14335, 32), (16, 4096, 8193, 0), (48, 14336, 8195, 32), (9, 1024, 8201, 64), (128, 8192, 10306, 128)])
+def test_fastest_workspace_splits_layers_of_uneven_rows(lib, M, K, N, R):
+    """A layer whose N is no multiple of 4 is split over K like its neighbour: the told size has no room for that, the fastest size
+    has, for T in four slices and two slices of fp32 outputs at least (rows padded to whole vectors of four)."""
+    fast = lib.salr_linear_workspace_bytes_fastest
+    fast.restype, fast.argtypes = ctypes.c_size_t, [ctypes.c_int64] * 4
+    pitch, t = (N + 3) // 4 * 4, _r256(4 * M * ((R + 31) // 32 * 32) * 4)
+    assert fast(M, K, N, R) >= t + 2 * M * pitch * 4 > lib.salr_linear_workspace_bytes(M, K, N, R)
+    slices, even = (fast(M, K, N, R) - t) // (M * pitch * 4), (lib.salr_linear_workspace_bytes(M, K, pitch, R) - t) // (M * pitch * 4)
+    assert 2 <= slices <= max(even, 2), "no finer than the neighbour's room allows"
+
+
 def test_host_validation_rejects_before_launch(lib):
     import paper_2601_16991_amd as salr
     fake = 0x1000  # never dereferenced: every call below fails validation first

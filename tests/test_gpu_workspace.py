@@ -1,4 +1,4 @@
-"""Which memory a large-batch call uses: the size that the query for the fastest path tells is all it needs, through the boundary and in
+"""Which memory a call uses: the size that the query for the fastest path tells is all it needs, through the boundary and in
 Python, and a Python call whose caller brings less still runs where torch's allocator has no more to give.  Results against the fp64
 CPU oracle (max |Y - Y_ref| <= 1e-2 * max |Y_ref|); calls on the same path bit for bit."""
 import numpy as np
@@ -69,6 +69,27 @@ def test_fastest_size_is_enough_for_four_bit_values(M, K, N, R):
     salr.salr_qsalr_linear(*qargs, y, buf[:size])
     torch.cuda.synchronize()
     assert torch.equal(y, alone) and bool((buf[size:] == 0x5A).all())
+
+
+# N no multiple of 4 on many rows: split over K with the fastest size only
+@pytest.mark.parametrize("M,K,N,R", [(16, 1152, 8193, 8), (40, 640, 8195, 33), (65, 512, 8198, 0)])
+@pytest.mark.parametrize("size_of", ["salr_linear_workspace_bytes", "salr_linear_workspace_bytes_fastest"])
+def test_row_tiled_calls_stay_inside_their_workspace(M, K, N, R, size_of):
+    """At either size: close to the oracle, nothing behind the workspace touched, and what it held before of no account."""
+    import paper_2601_16991_amd as salr
+    args, ref, _ = _layer(M, K, N, R)
+    size = getattr(salr, size_of)(M, K, N, R)
+    print(f"[workspace] M{M} K{K} N{N} R{R}: {size_of} {size}", flush=True)
+    buf = torch.full((size + 4096,), 0x5A, dtype=torch.uint8, device=dev())
+    y = torch.empty((M, N), dtype=torch.int16, device=dev())
+    salr.salr_sparse_lowrank_linear(*args, y, buf[:size] if size else None)
+    torch.cuda.synchronize()
+    assert _ok(y, ref) and bool((buf[size:] == 0x5A).all())
+    buf[:size] = 0xFF   # NaN as fp32 and as bf16
+    again = torch.empty_like(y)
+    salr.salr_sparse_lowrank_linear(*args, again, buf[:size] if size else None)
+    torch.cuda.synchronize()
+    assert torch.equal(again, y)
 
 
 @pytest.mark.parametrize("form", ["told", "none", "quantised"])
