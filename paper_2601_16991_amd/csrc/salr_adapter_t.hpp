@@ -24,6 +24,12 @@ constexpr int kTxPitch = 72;   // bf16 per row of an X tile [rows][64 k]: 144 by
 // (element loads); kFactorRanks, [R, K] (B_cat in the backward pass).
 enum FactorLayout { kFactorVec, kFactorAny, kFactorRanks };
 
+// T's sum over K is cut into so many interleaved slices, every sixteenth step of 64 columns each, whatever the number of waves that
+// share them: the slices are fp32 sums of their own, added up in order, so a call's T has the same bits in every launch that
+// computes it.  (Four slices on the four waves of a decode launch moved dA and dB of 2048 x 4096 x 4096 by 1.6e-4 and were no faster:
+// 99.8 us then, 100.0 with sixteen; 2048 x 4096 x 14336 239.9 and 237.3.)
+constexpr int kAdapterSlices = 16;
+
 template <int kMT, int kWaves, FactorLayout kFactor = kFactorVec>
 constexpr int adapter_t_lds_bytes() {
     constexpr int factor = kFactor == kFactorRanks ? 32 * kTxPitch : 32 * kTaPitch;
@@ -32,7 +38,7 @@ constexpr int adapter_t_lds_bytes() {
 }
 
 // Rows 16 kMT rb .. of T, ranks 32 rg .. 32 rg + 31 (columns past R as zeros), bf16 [M, Rpad].  The waves split K among
-// themselves, every kWaves-th step of 64 columns each, and are summed through LDS, so that the result needs no partial sums in
+// themselves, kAdapterSlices / kWaves slices each, which are summed through LDS, so that the result needs no partial sums in
 // memory and no second launch.  X is fetched as whole 128-byte lines (16 rows x 64 bytes per request, the MFMA operand as it
 // is, asks the L2 twice for every line, and with rows a multiple of 4 KB apart all from one channel) and turned into operands
 // through LDS; A_cat's rows go there as they lie and come back transposed.  kDepth steps in flight per wave.
@@ -77,9 +83,13 @@ __device__ __forceinline__ void adapter_t_block(const uint16_t* __restrict__ x, 
         const int r = 32 * rg + 8 * i + (lane >> 3);
         frow[i] = a_cat + (int64_t)(r < R ? r : R - 1) * K + 8 * xseg;
     }
-    f32x4 acc[kMT][2];
+    constexpr int kOwn = kAdapterSlices / kWaves;   // slices of a wave: step j of it is one of slice wave + kWaves * (j % kOwn)
+    static_assert(kOwn * kWaves == kAdapterSlices, "whole slices to a wave");
+    f32x4 acc[kOwn][kMT][2];
 #pragma unroll
-    for (int i = 0; i < kMT; ++i) acc[i][0] = acc[i][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int o = 0; o < kOwn; ++o)
+#pragma unroll
+        for (int i = 0; i < kMT; ++i) acc[o][i][0] = acc[o][i][1] = f32x4{0.f, 0.f, 0.f, 0.f};
     u32x4_t xq[kDepth][2 * kMT], aq[kDepth][4];
     auto request = [&](int d, int64_t s) {
         const int64_t k = (s < steps ? s : steps - 1) << 6;   // past the end: the last step again, not used
@@ -92,7 +102,7 @@ __device__ __forceinline__ void adapter_t_block(const uint16_t* __restrict__ x, 
             else aq[d][i] = load_a(k + arow + 16 * i - (i >= 2 ? half : 0));
         }
     };
-    auto multiply = [&](int d, int64_t s) {
+    auto multiply = [&](int o, int d, int64_t s) {
 #pragma unroll
         for (int i = 0; i < 2 * kMT; ++i) *reinterpret_cast<u32x4_t*>(x_tile + (8 * i + (lane >> 3)) * kTxPitch + 8 * xseg) = xq[d][i];
 #pragma unroll
@@ -123,69 +133,83 @@ __device__ __forceinline__ void adapter_t_block(const uint16_t* __restrict__ x, 
                     }
                     const bf16x8 b = as_bf16x8(bq);
 #pragma unroll
-                    for (int i = 0; i < kMT; ++i) acc[i][rt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xf[i], b, acc[i][rt], 0, 0, 0);
+                    for (int i = 0; i < kMT; ++i) acc[o][i][rt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xf[i], b, acc[o][i][rt], 0, 0, 0);
                 }
                 __builtin_amdgcn_wave_barrier();
             }
         }
     };
+    constexpr int kRound = kDepth > kOwn ? kDepth : kOwn;   // steps after which slice and registers are the same again
+    static_assert(kRound % kDepth == 0 && kRound % kOwn == 0, "a round is whole turns of both");
     if constexpr (kFactor == kFactorAny) {   // element loads are packed, and so waited for, where they are asked for: kDepth steps at once
-        for (int64_t s0 = wave; s0 < steps; s0 += kWaves * kDepth) {
+        for (int64_t s0 = wave; s0 < steps; s0 += kWaves * kRound) {
 #pragma unroll
-            for (int d = 0; d < kDepth; ++d) request(d, s0 + kWaves * d);
+            for (int j = 0; j < kRound; j += kDepth) {
 #pragma unroll
-            for (int d = 0; d < kDepth; ++d)
-                if (s0 + kWaves * d < steps) multiply(d, s0 + kWaves * d);   // wave-uniform
+                for (int d = 0; d < kDepth; ++d) request(d, s0 + kWaves * (j + d));
+#pragma unroll
+                for (int d = 0; d < kDepth; ++d)
+                    if (s0 + kWaves * (j + d) < steps) multiply((j + d) % kOwn, d, s0 + kWaves * (j + d));   // wave-uniform
+            }
         }
     } else {   // a ring: a step is requested again as soon as its registers are free, kDepth steps ahead
 #pragma unroll
         for (int d = 0; d < kDepth; ++d) request(d, wave + kWaves * d);
-        for (int64_t s0 = wave; s0 < steps; s0 += kWaves * kDepth) {
+        for (int64_t s0 = wave; s0 < steps; s0 += kWaves * kRound) {
 #pragma unroll
-            for (int d = 0; d < kDepth; ++d) {
-                const int64_t s = s0 + kWaves * d;
-                if (s < steps) multiply(d, s);   // wave-uniform
-                request(d, s + kWaves * kDepth);
+            for (int j = 0; j < kRound; ++j) {
+                const int64_t s = s0 + kWaves * j;
+                if (s < steps) multiply(j % kOwn, j % kDepth, s);   // wave-uniform
+                request(j % kDepth, s + kWaves * kDepth);
             }
         }
     }
-    __syncthreads();
-    // accumulator layout: lane holds T[16 i + 4 g + e][16 rt + i16]
+    // accumulator layout: lane holds T[16 i + 4 g + e][16 rt + i16].  kWaves slices at a time go through LDS and are added in order.
     float* red = reinterpret_cast<float*>(lds);
+    constexpr int kSums = kMT * 512 / (64 * kWaves) > 0 ? kMT * 512 / (64 * kWaves) : 1;   // of a thread
+    float sum[kSums];
 #pragma unroll
-    for (int i = 0; i < kMT; ++i)
+    for (int j = 0; j < kSums; ++j) sum[j] = 0.f;
 #pragma unroll
-        for (int rt = 0; rt < 2; ++rt)
+    for (int o = 0; o < kOwn; ++o) {
+        __syncthreads();   // the tiles, or the slices before, have been read
 #pragma unroll
-            for (int e = 0; e < 4; ++e) red[(wave * kMT * 2 + i * 2 + rt) * 256 + e * 64 + lane] = acc[i][rt][e];
-    __syncthreads();
-    for (int idx = tid; idx < kMT * 512; idx += 64 * kWaves) {
-        float s = 0.f;
+        for (int i = 0; i < kMT; ++i)
 #pragma unroll
-        for (int w = 0; w < kWaves; ++w) s += red[w * kMT * 512 + idx];
+            for (int rt = 0; rt < 2; ++rt)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) red[(wave * kMT * 2 + i * 2 + rt) * 256 + e * 64 + lane] = acc[o][i][rt][e];
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < kSums; ++j) {
+            const int idx = tid + 64 * kWaves * j;
+            if (idx < kMT * 512)
+#pragma unroll
+                for (int w = 0; w < kWaves; ++w) sum[j] += red[w * kMT * 512 + idx];
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < kSums; ++j) {
+        const int idx = tid + 64 * kWaves * j;
         const int l = idx & 63, e = (idx >> 6) & 3, rt = (idx >> 8) & 1, i = idx >> 9;
         const int64_t m = m0 + 16 * i + 4 * (l >> 4) + e;
         const int r = 32 * rg + 16 * rt + (l & 15);
-        if (m < M) {
-            const uint16_t v = r < R ? f32_to_bf16_rne(s) : (uint16_t)0;
+        if (idx < kMT * 512 && m < M) {
+            const uint16_t v = r < R ? f32_to_bf16_rne(sum[j]) : (uint16_t)0;
             t[m * Rpad + r] = v;
             if (t_t != nullptr) t_t[(int64_t)r * M + m] = v;
         }
     }
 }
 
-// Workgroup `block` of T = X * A_cat (R % 8 == 0) by workgroups of kWaves waves: 32 rows of X each where the blocks are many anyway
-// (adapter_t_row_tiles), 16 else, and 32 ranks.
-inline int adapter_t_blocks(int64_t M, int Rpad) {
-    const int rows = 16 * adapter_t_row_tiles(M);
-    return (int)((M + rows - 1) / rows) * (Rpad / 32);
-}
+// Workgroup `block` of T = X * A_cat (R % 8 == 0) beside a pass over the weight, by workgroups of kWaves waves: 16 rows of X and 32 ranks
+// each (32 rows of sums of four slices each would take the registers of two more workgroups of that pass).
+inline int adapter_t_blocks(int64_t M, int Rpad) { return (int)((M + 15) / 16) * (Rpad / 32); }
 template <int kWaves>
 __device__ __forceinline__ void adapter_t_block_of(const uint16_t* __restrict__ x, int64_t M, int64_t K, const uint16_t* __restrict__ a_cat, int R,
                                                    int Rpad, uint16_t* __restrict__ t, int block, uint16_t* lds) {
     const int groups = Rpad >> 5;
-    if (M >= kAdapterWideM) adapter_t_block<2, kWaves, 2>(x, M, K, a_cat, R, Rpad, t, block / groups, block % groups, lds);
-    else adapter_t_block<1, kWaves, 3>(x, M, K, a_cat, R, Rpad, t, block / groups, block % groups, lds);
+    adapter_t_block<1, kWaves, 2>(x, M, K, a_cat, R, Rpad, t, block / groups, block % groups, lds);
 }
 
 }  // namespace salr

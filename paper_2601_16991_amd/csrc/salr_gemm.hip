@@ -389,7 +389,7 @@ constexpr int kDfPitch = 140;         // dwords of LDS per row: 33 vectors of 16
 constexpr int kDfAhead = 3;           // vectors per lane and row half fetched ahead: pieces of up to 24 vectors (~70 % dense)
 
 template <bool kPair, bool kNf4>
-__global__ __launch_bounds__(kDfWaves * 64) void decode_frag_kernel(const uint32_t* __restrict__ bitmap,
+__global__ __launch_bounds__(kDfWaves * 64, 4) void decode_frag_kernel(const uint32_t* __restrict__ bitmap,
                                                                    const uint16_t* __restrict__ values,
                                                                    const uint32_t* __restrict__ row_offsets, int64_t N, int64_t K,
                                                                    int ksl, const uint16_t* __restrict__ b_cat, int R, int Rpad,
@@ -399,7 +399,7 @@ __global__ __launch_bounds__(kDfWaves * 64) void decode_frag_kernel(const uint32
                                                                    int64_t M, uint16_t* __restrict__ t) {
     __shared__ __attribute__((aligned(16))) uint32_t slots[kDfWaves][16 * kDfPitch];
     if ((int)blockIdx.x < t_blocks) {   // the same for the whole workgroup
-        static_assert(sizeof(slots) >= adapter_t_lds_bytes<2, kDfWaves>() && sizeof(slots) >= adapter_t_lds_bytes<1, kDfWaves>(), "room for T's tiles");
+        static_assert(sizeof(slots) >= adapter_t_lds_bytes<1, kDfWaves>(), "room for T's tiles");
         adapter_t_block_of<kDfWaves>(x, M, K, a_cat, R, Rpad, t, (int)blockIdx.x, reinterpret_cast<uint16_t*>(slots));
         return;
     }
@@ -683,15 +683,14 @@ hipError_t launch_linear_frag(const LinearArgs& a, hipStream_t stream, const Tim
 // The first t_blocks workgroups compute T = X A_cat meanwhile (any16 = X; 16 rows and 32 ranks each).
 // Value offsets are clamped to the stored count: the 2:4 form is the caller's promise.  Bound by memory: 14336 x 4096, 66 MB in
 // and 66 out, 28.7 us.
-__global__ __launch_bounds__(256) void pack_2of4_kernel(const uint32_t* __restrict__ bitmap, const uint16_t* __restrict__ values,
+__global__ __launch_bounds__(256, 5) void pack_2of4_kernel(const uint32_t* __restrict__ bitmap, const uint16_t* __restrict__ values,
                                                         const uint32_t* __restrict__ row_offsets, const uint16_t* __restrict__ any16,
                                                         int64_t N, int64_t K, int split, const uint16_t* __restrict__ b_cat, int R,
                                                         int Rpad, uint16_t* __restrict__ wf, int t_blocks, int64_t M,
                                                         const uint16_t* __restrict__ a_cat, uint16_t* __restrict__ t) {
     if ((int)blockIdx.x < t_blocks) {   // the same for the whole workgroup
         __shared__ __attribute__((aligned(16))) uint16_t lds[adapter_t_lds_bytes<1, 4>() / 2];
-        const int groups = Rpad >> 5;
-        adapter_t_block<1, 4, 2>(any16, M, K, a_cat, R, Rpad, t, (int)blockIdx.x / groups, (int)blockIdx.x % groups, lds);
+        adapter_t_block_of<4>(any16, M, K, a_cat, R, Rpad, t, (int)blockIdx.x, lds);
         return;
     }
     const int lane = lane_id(), n = lane & 15, kb = lane >> 4;
@@ -764,7 +763,7 @@ void launch_sparse_gemm(const LinearArgs& a, uint16_t* wf, bool narrow, bool wit
     int64_t split = (8192 + frags - 1) / frags;   // about eight waves per SIMD, four pairs at least to a wave
     if (split > pairs / 4) split = pairs / 4;
     if (split < 1) split = 1;
-    const int t_blocks = with_t ? (int)((a.M + 15) / 16) * (Rpad / 32) : 0;
+    const int t_blocks = with_t ? adapter_t_blocks(a.M, Rpad) : 0;
     hipLaunchKernelGGL(pack_2of4_kernel, dim3((unsigned)(t_blocks + (frags * split + 3) / 4)), dim3(256), 0, stream, a.bitmap, a.values,
                        a.row_offsets, a.x, a.N, a.K, (int)split, a.b_cat, R, Rpad, wf, t_blocks, a.M, a.a_cat, a.t);
     const int nt = narrow ? 224 : 256, m_tiles = (int)((a.M + 255) / 256), n_tiles = (int)((a.N + nt - 1) / nt);

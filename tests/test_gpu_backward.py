@@ -93,6 +93,28 @@ def test_backward_edges_of_the_transposed_operand_order(M, K, N, ranks, keep):
     _close(db, rb_, "dB")
 
 
+@pytest.mark.parametrize("M,R", [(64, 8), (96, 40), (64, 12), (1056, 16)])
+def test_backward_sums_of_the_low_rank_products(M, R):
+    """T' and T are sixteen fp32 sums over every sixteenth step of 64 columns, added up in order, in whichever launch they are formed:
+    2^24 and -2^24 sixteen steps apart cancel in a sum of their own and leave the 1 of another one, which a sum that takes
+    every fourth or eighth step would lose to the 2^24 before it."""
+    C = 1088
+    rows, factor = np.zeros((M, C), np.float32), np.zeros((C, R), np.float32)
+    rows[:, 0], rows[:, 256], rows[:, 1024] = 4096.0, 1.0, -4096.0
+    factor[0], factor[256], factor[1024] = 4096.0, 1.0, 4096.0
+    one_row = np.zeros((M, C), np.float32)
+    one_row[M - 1, 5] = 1.0
+    w_hat = np.zeros((C, C), np.uint16)
+    w_hat[7, 3] = 0x3F80   # met by zeros only
+    bf = wl.f32_to_bf16_bits
+    a = np.full((C, R), 1.0 / 64, np.float32)
+    dx, da, _ = _run(bf(one_row), bf(rows), w_hat, bf(a), bf(np.ascontiguousarray(factor.T)))
+    assert np.array_equal(dx, np.full((M, C), R / 64))
+    assert np.array_equal(da[5], np.ones(R)) and np.count_nonzero(da) == R
+    _, _, db = _run(bf(rows), bf(one_row), w_hat, bf(factor), bf(np.zeros((R, C), np.float32)))
+    assert np.array_equal(db[:, 5], np.ones(R)) and np.count_nonzero(db) == R
+
+
 def test_backward_adapter_gradients_only():
     x, dy, w_hat, a_cat, b_cat = _problem(128, 256, 192, (24,), 3000)
     dx, da, db = _run(x, dy, w_hat, a_cat, b_cat, need_dx=False)

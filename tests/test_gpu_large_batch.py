@@ -68,6 +68,31 @@ def test_adapter_product_of_its_own(M, K, R):
     _check(M, K, 96, R, 0.5)
 
 
+@pytest.mark.parametrize("M,N,R,form", [(130, 96, 8, "linear"), (1040, 80, 40, "linear"), (300, 64, 96, "qsalr"), (2048, 6144, 40, "2of4")])
+def test_sums_of_the_adapter_product(M, N, R, form):
+    """T = X A_cat beside the pass over the weight: sixteen fp32 sums over every sixteenth step of 64 columns, added up in order.  2^24
+    and -2^24 sixteen steps apart cancel in a sum of their own and leave the 1 of another one, which a sum that takes every
+    fourth step would lose to the 2^24 before it."""
+    import paper_2601_16991_amd as salr
+    K = 1088
+    x, a, b = np.zeros((M, K), np.float32), np.zeros((K, R), np.float32), np.zeros((R, N), np.float32)
+    x[:, 0], x[:, 256], x[:, 1024] = 4096.0, 1.0, -4096.0
+    a[0], a[256], a[1024] = 4096.0, 1.0, 4096.0
+    b[:] = (1 + np.arange(N) % 7) / 8
+    w = np.zeros((N, K), np.uint16)
+    w[:, 1::4] = w[:, 2::4] = 0x3F80   # met by zeros only
+    rb, rv, ro = oracle.encode(w)
+    bf = wl.f32_to_bf16_bits
+    dx, dbm, dv, dro, da, db = to_dev_u16(bf(x)), to_dev_u32(rb), to_dev_u16(rv), to_dev_u32(ro), to_dev_u16(bf(a)), to_dev_u16(bf(b))
+    if form == "qsalr":
+        codes, scales = salr.nf4_quantize(dv)
+        y = salr.qsalr_linear(dx, dbm, codes, scales, dro, rv.size, da, db)
+    else:
+        y = (salr.linear_2of4 if form == "2of4" else salr.linear)(dx, dbm, dv, dro, da, db)
+    torch.cuda.synchronize()
+    assert np.array_equal(y_to_f64(y), np.repeat(b[:1].astype(np.float64) * R, M, axis=0))
+
+
 @pytest.mark.parametrize("M,K,N,R,density", [(129, 96, 40, 8, 0.8), (300, 2720, 130, 0, 0.8), (600, 512, 257, 32, 0.5), (129, 288, 64, 8, 1.0)])
 def test_quantised(M, K, N, R, density):
     _check(M, K, N, R, density, quantised=True)
