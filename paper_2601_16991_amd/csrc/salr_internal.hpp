@@ -281,7 +281,7 @@ inline int rowtile_ksplit(int64_t M, int64_t K, int64_t N) {
 }
 inline bool rowtile_possible(int64_t M, int64_t K) { return M <= kRowtileMaxM && K >= 128 && K % 128 == 0; }
 inline bool uses_rowtile(int64_t M, int64_t K, int64_t N) {
-    if (!rowtile_possible(M, K)) return false;
+    if (!rowtile_possible(M, K) || K > kRowtileMaxColumns) return false;   // (longer rows: the paths with 64-bit offsets)
     if (N % 4 != 0 && N < 64 * 128) return false;   // K cannot be split and the row tiles are few
     return M > 32 || (M > 8 && N >= 8192);
 }

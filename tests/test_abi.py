@@ -197,6 +197,32 @@ def test_fastest_workspace_splits_layers_of_uneven_rows(lib, M, K, N, R):
     assert 2 <= slices <= max(even, 2), "no finer than the neighbour's room allows"
 
 
+@pytest.mark.parametrize("M,N,R", [(16, 8192, 32), (64, 4096, 8), (33, 512, 0), (128, 4096, 8), (100, 260, 0)])
+def test_row_tiled_kernel_ends_where_its_offsets_do(lib, M, N, R):
+    """The row-tiled kernel keeps 32-bit byte offsets into X and the rows of a wave, so rows of more than 2^22 columns are planned for
+    the paths that have 64-bit ones: the small-batch kernel (the partial sums of T and a slice table) up to 64 tokens, a decoded
+    weight above, at the told size and at the fastest, for 4-bit values too."""
+    def query(name, *args):
+        fn = getattr(lib, name)
+        fn.restype, fn.argtypes = ctypes.c_size_t, [ctypes.c_int64] * len(args)
+        return fn(*args)
+
+    Rpad = (R + 31) // 32 * 32
+    t = _r256(16 * M * Rpad * 4)
+    for K in ((1 << 22) + 128, 1 << 24, 1 << 25, 1 << 28):
+        told = query("salr_linear_workspace_bytes", M, K, N, R)
+        if M <= 64:
+            assert told == (t + _r256(N * 64) if R else 0)
+            assert query("salr_linear_workspace_bytes_fastest", M, K, N, R) == told
+        else:
+            assert told >= 2 * N * K
+        nnz = min(N * K // 4, (1 << 32) - 1)
+        assert (query("salr_qsalr_linear_workspace_bytes_fastest", M, K, N, R, nnz) ==
+                query("salr_qsalr_linear_workspace_bytes", M, K, N, R, nnz))
+    at_the_bound = query("salr_linear_workspace_bytes", M, 1 << 22, N, R)   # partial outputs of several slices
+    assert at_the_bound >= t + 2 * M * N * 4
+
+
 def test_host_validation_rejects_before_launch(lib):
     import paper_2601_16991_amd as salr
     fake = 0x1000  # never dereferenced: every call below fails validation first
