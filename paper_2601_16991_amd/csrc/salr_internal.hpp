@@ -188,9 +188,9 @@ inline size_t adapter_partial_bytes(int64_t M, int64_t K, int64_t R) {
 inline size_t twostage_dense_offset(int64_t M, int64_t K, int64_t R) {
     return adapter_t_bytes(M, R) + adapter_at_bytes(K, R) + adapter_partial_bytes(M, K, R);
 }
-inline size_t frag_weight_offset(int64_t M, int64_t K, int64_t R) {   // T first, then what a product of its own needs
+inline size_t frag_weight_offset(int64_t M, int64_t K, int64_t R) {   // T first, then what a product of its own needs (launch_linear_frag)
     size_t b = adapter_t_bytes(M, R);
-    if (R > 0 && adapter_t_own_product(M, K, R)) {
+    if (R > 0 && !adapter_t_beside(K, R)) {
         const int64_t Rpad = adapter_rank_padded(R);
         b += adapter_frag_bytes(K, R) + round_up_256((size_t)adapter_t_product_ksplit(M, K, Rpad) * (size_t)M * (size_t)Rpad * sizeof(float));
     }

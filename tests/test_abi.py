@@ -185,6 +185,31 @@ def test_fastest_workspace_bytes(lib):
     assert query("salr_qsalr_linear_workspace_bytes_fastest", 300, 64, 8, 4, -1) == 0
 
 
+def _product_room(M, K, R):
+    """Room of a product X A_cat of its own: A_cat in operand order, and the fp32 sums of its slices of K."""
+    rp, steps = (R + 31) // 32 * 32, (K + 63) // 64
+    slices = min(max(min(-(-256 // ((M + 255) // 256 * ((rp + 127) // 128))), steps // 4), 1), 64)
+    return _r256(steps * 64 * rp * 2) + _r256(slices * M * rp * 4)
+
+
+def _operand_order_bytes(M, K, N, R):
+    """T, and the weight in operand order with B_cat's blocks behind it."""
+    rp = (R + 31) // 32 * 32
+    return _r256(M * rp * 2) + _r256((N + 15) // 16 * ((K + 63) // 64 + (R + 63) // 64) * 2048)
+
+
+@pytest.mark.parametrize("M,K,N,R,product", [(1000, 4096, 4096, 128, False), (4096, 4096, 8192, 64, False), (700, 4096, 30000, 128, False),
+                                             (1000, 4096, 4096, 127, True), (4096, 14336, 8192, 32, True), (600, 8224, 28000, 8, True)])
+def test_fastest_workspace_of_the_low_rank_product(lib, M, K, N, R, product):
+    """The fastest size holds what a product for T = X A_cat of its own needs only where there is one: a layer whose contraction is not split
+    is told that and the weight, or the told size where that is larger."""
+    fast, told = lib.salr_linear_workspace_bytes_fastest, lib.salr_linear_workspace_bytes
+    for f in (fast, told):
+        f.restype, f.argtypes = ctypes.c_size_t, [ctypes.c_int64] * 4
+    need = _operand_order_bytes(M, K, N, R) + (_product_room(M, K, R) if product else 0)
+    assert fast(M, K, N, R) == max(need, told(M, K, N, R))
+
+
 @pytest.mark.parametrize("M,K,N,R", [(64, 4096, 14335, 32), (16, 4096, 8193, 0), (48, 14336, 8195, 32), (9, 1024, 8201, 64), (128, 8192, 10306, 128)])
 def test_fastest_workspace_splits_layers_of_uneven_rows(lib, M, K, N, R):
     """A layer whose N is no multiple of 4 is split over K like its neighbour: the told size has no room for that, the fastest size
