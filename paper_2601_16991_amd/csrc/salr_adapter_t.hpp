@@ -26,9 +26,11 @@ enum FactorLayout { kFactorVec, kFactorAny, kFactorRanks };
 
 // T's sum over K is cut into so many interleaved slices, every sixteenth step of 64 columns each, whatever the number of waves that
 // share them: the slices are fp32 sums of their own, added up in order, so a call's T has the same bits in every launch that
-// computes it.  (Four slices on the four waves of a decode launch moved dA and dB of 2048 x 4096 x 4096 by 1.6e-4 and were no faster:
-// 99.8 us then, 100.0 with sixteen; 2048 x 4096 x 14336 239.9 and 237.3.)
+// computes it.  (Four slices on the four waves of a decode launch moved dA and dB of 2048 x 4096 x 4096 by 1.6e-4.)
+// A wave of fewer than sixteen takes several slices.  With 16 rows it keeps their sums side by side, its steps in the order of the columns;
+// with 32 rows, whose four sums would take the registers of two more workgroups on a CU, it finishes one slice after the other.
 constexpr int kAdapterSlices = 16;
+constexpr bool adapter_t_one_by_one(int kMT, int kWaves) { return kMT > 1 && kWaves < kAdapterSlices; }
 
 template <int kMT, int kWaves, FactorLayout kFactor = kFactorVec>
 constexpr int adapter_t_lds_bytes() {
@@ -83,13 +85,18 @@ __device__ __forceinline__ void adapter_t_block(const uint16_t* __restrict__ x, 
         const int r = 32 * rg + 8 * i + (lane >> 3);
         frow[i] = a_cat + (int64_t)(r < R ? r : R - 1) * K + 8 * xseg;
     }
-    constexpr int kOwn = kAdapterSlices / kWaves;   // slices of a wave: step j of it is one of slice wave + kWaves * (j % kOwn)
+    constexpr int kOwn = kAdapterSlices / kWaves;   // slices of a wave: wave, wave + kWaves, ..
     static_assert(kOwn * kWaves == kAdapterSlices, "whole slices to a wave");
-    f32x4 acc[kOwn][kMT][2];
+    constexpr bool kOneByOne = adapter_t_one_by_one(kMT, kWaves);
+    constexpr int kHeld = kOneByOne ? 1 : kOwn;     // sums held at a time
+    f32x4 acc[kHeld][kMT][2];
+    auto clear = [&]() {
 #pragma unroll
-    for (int o = 0; o < kOwn; ++o)
+        for (int o = 0; o < kHeld; ++o)
 #pragma unroll
-        for (int i = 0; i < kMT; ++i) acc[o][i][0] = acc[o][i][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int i = 0; i < kMT; ++i) acc[o][i][0] = acc[o][i][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+    };
+    clear();
     u32x4_t xq[kDepth][2 * kMT], aq[kDepth][4];
     auto request = [&](int d, int64_t s) {
         const int64_t k = (s < steps ? s : steps - 1) << 6;   // past the end: the last step again, not used
@@ -139,39 +146,14 @@ __device__ __forceinline__ void adapter_t_block(const uint16_t* __restrict__ x, 
             }
         }
     };
-    constexpr int kRound = kDepth > kOwn ? kDepth : kOwn;   // steps after which slice and registers are the same again
-    static_assert(kRound % kDepth == 0 && kRound % kOwn == 0, "a round is whole turns of both");
-    if constexpr (kFactor == kFactorAny) {   // element loads are packed, and so waited for, where they are asked for: kDepth steps at once
-        for (int64_t s0 = wave; s0 < steps; s0 += kWaves * kRound) {
-#pragma unroll
-            for (int j = 0; j < kRound; j += kDepth) {
-#pragma unroll
-                for (int d = 0; d < kDepth; ++d) request(d, s0 + kWaves * (j + d));
-#pragma unroll
-                for (int d = 0; d < kDepth; ++d)
-                    if (s0 + kWaves * (j + d) < steps) multiply((j + d) % kOwn, d, s0 + kWaves * (j + d));   // wave-uniform
-            }
-        }
-    } else {   // a ring: a step is requested again as soon as its registers are free, kDepth steps ahead
-#pragma unroll
-        for (int d = 0; d < kDepth; ++d) request(d, wave + kWaves * d);
-        for (int64_t s0 = wave; s0 < steps; s0 += kWaves * kRound) {
-#pragma unroll
-            for (int j = 0; j < kRound; ++j) {
-                const int64_t s = s0 + kWaves * j;
-                if (s < steps) multiply(j % kOwn, j % kDepth, s);   // wave-uniform
-                request(j % kDepth, s + kWaves * kDepth);
-            }
-        }
-    }
-    // accumulator layout: lane holds T[16 i + 4 g + e][16 rt + i16].  kWaves slices at a time go through LDS and are added in order.
+    // Accumulator layout: lane holds T[16 i + 4 g + e][16 rt + i16].  A slice of each wave at a time goes through LDS, which the tiles leave
+    // to them, and they are added in order.
     float* red = reinterpret_cast<float*>(lds);
     constexpr int kSums = kMT * 512 / (64 * kWaves) > 0 ? kMT * 512 / (64 * kWaves) : 1;   // of a thread
     float sum[kSums];
 #pragma unroll
     for (int j = 0; j < kSums; ++j) sum[j] = 0.f;
-#pragma unroll
-    for (int o = 0; o < kOwn; ++o) {
+    auto add_up = [&](int o) {
         __syncthreads();   // the tiles, or the slices before, have been read
 #pragma unroll
         for (int i = 0; i < kMT; ++i)
@@ -187,6 +169,69 @@ __device__ __forceinline__ void adapter_t_block(const uint16_t* __restrict__ x, 
 #pragma unroll
                 for (int w = 0; w < kWaves; ++w) sum[j] += red[w * kMT * 512 + idx];
         }
+    };
+    if constexpr (kOneByOne) {   // a ring over the steps of all the wave's slices, in the order of the slices
+        static_assert(kFactor != kFactorAny);
+        int asked = 0;                      // slice and step of the next request; past the last: steps
+        int64_t ask = wave;
+        auto advance = [&]() {
+            ask += kAdapterSlices;
+            if (ask >= steps) {             // wave-uniform
+                ++asked;
+                ask = asked < kOwn ? wave + kWaves * asked : steps;   // (a slice without steps: so are the ones behind it)
+            }
+        };
+#pragma unroll
+        for (int d = 0; d < kDepth; ++d) {
+            request(d, ask);
+            advance();
+        }
+        int turn = 0;
+#pragma unroll 1
+        for (int o = 0; o < kOwn; ++o) {
+#pragma unroll 1
+            for (int64_t s = wave + kWaves * o; s < steps; s += kAdapterSlices) {
+#pragma unroll
+                for (int d = 0; d < kDepth; ++d)
+                    if (turn == d) {        // wave-uniform
+                        multiply(0, d, s);
+                        request(d, ask);
+                    }
+                advance();
+                turn = turn + 1 == kDepth ? 0 : turn + 1;
+            }
+            add_up(0);
+            clear();
+            __syncthreads();   // the sums have been read
+        }
+    } else {
+        constexpr int kRound = kDepth > kOwn ? kDepth : kOwn;   // steps after which slice and registers are the same again
+        static_assert(kRound % kDepth == 0 && kRound % kOwn == 0, "a round is whole turns of both");
+        if constexpr (kFactor == kFactorAny) {   // element loads are packed, and so waited for, where they are asked for: kDepth steps at once
+            for (int64_t s0 = wave; s0 < steps; s0 += kWaves * kRound) {
+#pragma unroll
+                for (int j = 0; j < kRound; j += kDepth) {
+#pragma unroll
+                    for (int d = 0; d < kDepth; ++d) request(d, s0 + kWaves * (j + d));
+#pragma unroll
+                    for (int d = 0; d < kDepth; ++d)
+                        if (s0 + kWaves * (j + d) < steps) multiply((j + d) % kOwn, d, s0 + kWaves * (j + d));   // wave-uniform
+                }
+            }
+        } else {   // a ring: a step is requested again as soon as its registers are free, kDepth steps ahead
+#pragma unroll
+            for (int d = 0; d < kDepth; ++d) request(d, wave + kWaves * d);
+            for (int64_t s0 = wave; s0 < steps; s0 += kWaves * kRound) {
+#pragma unroll
+                for (int j = 0; j < kRound; ++j) {
+                    const int64_t s = s0 + kWaves * j;
+                    if (s < steps) multiply(j % kOwn, j % kDepth, s);   // wave-uniform
+                    request(j % kDepth, s + kWaves * kDepth);
+                }
+            }
+        }
+#pragma unroll
+        for (int o = 0; o < kOwn; ++o) add_up(o);
     }
 #pragma unroll
     for (int j = 0; j < kSums; ++j) {
@@ -203,13 +248,24 @@ __device__ __forceinline__ void adapter_t_block(const uint16_t* __restrict__ x, 
 }
 
 // Workgroup `block` of T = X * A_cat (R % 8 == 0) beside a pass over the weight, by workgroups of kWaves waves: 16 rows of X and 32 ranks
-// each (32 rows of sums of four slices each would take the registers of two more workgroups of that pass).
-inline int adapter_t_blocks(int64_t M, int Rpad) { return (int)((M + 15) / 16) * (Rpad / 32); }
-template <int kWaves>
+// each, or 32 rows where kWide, there are kAdapterWideM and more, and blocks of 16 rows would be more than one a CU.  (16 / 32 rows, us a
+// call: 256 blocks 1024 x 8192 x 1024 rank 128 52.4 / 55.2, 4096 x 4096 x 512 rank 32 41.6 / 45.9; 512 blocks 2048 x 4096 x 512 rank 128
+// 40.9 / 39.4, 1024 x 8192 x 1024 rank 256 64.2 / 58.9; 1024 blocks 4096 x 8192 x 512 rank 128 104 / 89.)
+template <bool kWide>
+__host__ __device__ inline bool adapter_t_wide(int64_t M, int Rpad) {
+    return kWide && M >= kAdapterWideM && (M + 15) / 16 * (Rpad >> 5) > 256;
+}
+template <bool kWide>
+inline int adapter_t_blocks(int64_t M, int Rpad) {
+    const int rows = adapter_t_wide<kWide>(M, Rpad) ? 32 : 16;
+    return (int)((M + rows - 1) / rows) * (Rpad / 32);
+}
+template <int kWaves, bool kWide>
 __device__ __forceinline__ void adapter_t_block_of(const uint16_t* __restrict__ x, int64_t M, int64_t K, const uint16_t* __restrict__ a_cat, int R,
                                                    int Rpad, uint16_t* __restrict__ t, int block, uint16_t* lds) {
     const int groups = Rpad >> 5;
-    adapter_t_block<1, kWaves, 2>(x, M, K, a_cat, R, Rpad, t, block / groups, block % groups, lds);
+    if (adapter_t_wide<kWide>(M, Rpad)) adapter_t_block<2, kWaves, 2>(x, M, K, a_cat, R, Rpad, t, block / groups, block % groups, lds);
+    else adapter_t_block<1, kWaves, 2>(x, M, K, a_cat, R, Rpad, t, block / groups, block % groups, lds);
 }
 
 }  // namespace salr

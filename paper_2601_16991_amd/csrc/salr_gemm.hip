@@ -399,8 +399,8 @@ __global__ __launch_bounds__(kDfWaves * 64, 4) void decode_frag_kernel(const uin
                                                                    int64_t M, uint16_t* __restrict__ t) {
     __shared__ __attribute__((aligned(16))) uint32_t slots[kDfWaves][16 * kDfPitch];
     if ((int)blockIdx.x < t_blocks) {   // the same for the whole workgroup
-        static_assert(sizeof(slots) >= adapter_t_lds_bytes<1, kDfWaves>(), "room for T's tiles");
-        adapter_t_block_of<kDfWaves>(x, M, K, a_cat, R, Rpad, t, (int)blockIdx.x, reinterpret_cast<uint16_t*>(slots));
+        static_assert(sizeof(slots) >= adapter_t_lds_bytes<2, kDfWaves>() && sizeof(slots) >= adapter_t_lds_bytes<1, kDfWaves>(), "room for T's tiles");
+        adapter_t_block_of<kDfWaves, true>(x, M, K, a_cat, R, Rpad, t, (int)blockIdx.x, reinterpret_cast<uint16_t*>(slots));
         return;
     }
     if ((int)blockIdx.x < a_blocks) {
@@ -580,7 +580,7 @@ hipError_t launch_decode_frags(const LinearArgs& a, uint16_t* wf, uint16_t* af, 
     if (split < 1) split = 1;
     const int64_t ksl = split * kDfWaves;
     const int a_blocks = af != nullptr ? (int)((a.K + 32 * kDfWaves - 1) / (32 * kDfWaves)) : 0;
-    const int t_blocks = t != nullptr ? adapter_t_blocks(a.M, Rpad) : 0;
+    const int t_blocks = t != nullptr ? adapter_t_blocks<true>(a.M, Rpad) : 0;
     const dim3 grid((unsigned)(t_blocks + a_blocks + frags * split)), block(kDfWaves * 64);
     const uint16_t* src = a.codes != nullptr ? reinterpret_cast<const uint16_t*>(a.codes) : a.values;
     const uint32_t scale_last = a.codes != nullptr ? (uint32_t)((a.nnz + kNf4Block - 1) / kNf4Block - 1) : 0u;
@@ -690,7 +690,7 @@ __global__ __launch_bounds__(256, 5) void pack_2of4_kernel(const uint32_t* __res
                                                         const uint16_t* __restrict__ a_cat, uint16_t* __restrict__ t) {
     if ((int)blockIdx.x < t_blocks) {   // the same for the whole workgroup
         __shared__ __attribute__((aligned(16))) uint16_t lds[adapter_t_lds_bytes<1, 4>() / 2];
-        adapter_t_block_of<4>(any16, M, K, a_cat, R, Rpad, t, (int)blockIdx.x, lds);
+        adapter_t_block_of<4, false>(any16, M, K, a_cat, R, Rpad, t, (int)blockIdx.x, lds);
         return;
     }
     const int lane = lane_id(), n = lane & 15, kb = lane >> 4;
@@ -763,7 +763,7 @@ void launch_sparse_gemm(const LinearArgs& a, uint16_t* wf, bool narrow, bool wit
     int64_t split = (8192 + frags - 1) / frags;   // about eight waves per SIMD, four pairs at least to a wave
     if (split > pairs / 4) split = pairs / 4;
     if (split < 1) split = 1;
-    const int t_blocks = with_t ? adapter_t_blocks(a.M, Rpad) : 0;
+    const int t_blocks = with_t ? adapter_t_blocks<false>(a.M, Rpad) : 0;
     hipLaunchKernelGGL(pack_2of4_kernel, dim3((unsigned)(t_blocks + (frags * split + 3) / 4)), dim3(256), 0, stream, a.bitmap, a.values,
                        a.row_offsets, a.x, a.N, a.K, (int)split, a.b_cat, R, Rpad, wf, t_blocks, a.M, a.a_cat, a.t);
     const int nt = narrow ? 224 : 256, m_tiles = (int)((a.M + 255) / 256), n_tiles = (int)((a.N + nt - 1) / nt);

@@ -68,7 +68,14 @@ def test_adapter_product_of_its_own(M, K, R):
     _check(M, K, 96, R, 0.5)
 
 
-@pytest.mark.parametrize("M,N,R,form", [(130, 96, 8, "linear"), (1040, 80, 40, "linear"), (300, 64, 96, "qsalr"), (2048, 6144, 40, "2of4")])
+# fewer steps of 64 columns than waves or slices, half steps, more steps than two rounds of the slices
+@pytest.mark.parametrize("M,K,R", [(2100, 32, 72), (2050, 160, 96), (1030, 224, 256), (1360, 1056, 128), (4100, 2144, 40)])
+def test_adapter_product_in_blocks_of_32_rows(M, K, R):
+    """T = X A_cat beside the pass over the weight where blocks of 16 rows of X and 32 ranks would be more than one a CU."""
+    _check(M, K, 80, R, 0.5)
+
+
+@pytest.mark.parametrize("M,N,R,form", [(130, 96, 8, "linear"), (1040, 80, 40, "linear"), (2100, 64, 72, "linear"), (300, 64, 96, "qsalr"), (2048, 6144, 40, "2of4")])
 def test_sums_of_the_adapter_product(M, N, R, form):
     """T = X A_cat beside the pass over the weight: sixteen fp32 sums over every sixteenth step of 64 columns, added up in order.  2^24
     and -2^24 sixteen steps apart cancel in a sum of their own and leave the 1 of another one, which a sum that takes every
