@@ -663,7 +663,7 @@ hipError_t launch_linear_frag(const LinearArgs& a, hipStream_t stream, const Tim
     uint16_t* wf = reinterpret_cast<uint16_t*>(reinterpret_cast<char*>(a.t) + frag_weight_offset(a.M, a.K, a.R));
     // T beside the decode pass, or as a product of its own whose operand that pass lays out
     char* af = reinterpret_cast<char*>(a.t) + adapter_t_bytes(a.M, a.R);
-    const bool own = a.R > 0 && !adapter_t_beside(a.K, a.R);
+    const bool own = a.R > 0 && !adapter_t_beside(a.M, a.K, a.R);
     const hipError_t e = launch_decode_frags(a, wf, own ? reinterpret_cast<uint16_t*>(af) : nullptr, a.R > 0 && !own ? a.t : nullptr, stream);
     if (e != hipSuccess) return e;
     if (own)
@@ -756,7 +756,7 @@ __global__ __launch_bounds__(256, 5) void pack_2of4_kernel(const uint32_t* __res
 }
 
 // y = x W^T + t B_cat on the sparse matrix cores: the weight into sparse operand order at wf (sparse_weight_bytes), then tiles of
-// 256 x 256 or 256 x 224.  K % 64 == 0.  with_t: T first, beside the permutation (adapter_t_beside).
+// 256 x 256 or 256 x 224.  K % 64 == 0.  with_t: T first, beside the permutation (adapter_t_in_pass).
 void launch_sparse_gemm(const LinearArgs& a, uint16_t* wf, bool narrow, bool with_t, const TimingEvents& ev, hipStream_t stream) {
     const int R = (int)a.R, Rpad = (int)adapter_rank_padded(a.R);
     const int64_t frags = (a.N + 15) / 16, pairs = (a.K / 64 + 1) / 2;

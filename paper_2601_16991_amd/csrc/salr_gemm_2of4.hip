@@ -249,7 +249,7 @@ hipError_t launch_gemm_2of4(const LinearArgs& a, hipStream_t stream, const Timin
     const bool sparse = t256 >= kGemm2of4BigTilesMin && a.M >= kSparseOrderMinM && a.K <= kFragMaxColumns &&
                         a.room >= offset + sparse_weight_bytes(a.K, a.N, a.R);
     // T = X A_cat, bf16 [M, Rpad], at the start of the workspace: beside the pass over the weight where there is one
-    const bool with_t = sparse && adapter_t_beside(a.K, a.R);
+    const bool with_t = sparse && adapter_t_in_pass(a.K, a.R);
     if (a.R > 0 && !with_t) launch_adapter_t(a, stream);
     if (sparse)
         launch_sparse_gemm(a, reinterpret_cast<uint16_t*>(reinterpret_cast<char*>(a.t) + offset), cost224 < cost256, with_t, ev, stream);

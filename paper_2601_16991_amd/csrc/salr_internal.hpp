@@ -159,7 +159,14 @@ inline bool adapter_t_own_product(int64_t M, int64_t K, int64_t R) {
 // CUs beside a pass that fills the memory system.  Longer rows take the product above (us a call, beside / product: 300 x 8192 x 600 at
 // rank 64 75.0 / 84.7, 657 x 4736 x 768 at rank 128 37.1 / 51.3, 4096 x 8192 x 8192 at rank 64 465 / 472; 1024 x 14336 x 4096 180 / 170,
 // 200 x 28672 x 1024 97 / 77).
-inline bool adapter_t_beside(int64_t K, int64_t R) { return R > 0 && R % 8 == 0 && K <= 8192; }
+inline bool adapter_t_in_pass(int64_t K, int64_t R) { return R > 0 && R % 8 == 0 && K <= 8192; }
+// Each 32 ranks read X again, so many tokens at many ranks take the product, which reads it once (beside / product, N = 640: 2048 x 4096
+// rank 256 58.4 / 76.1, 4096 x 8192 rank 64 87.0 / 88.6, 3072 x 6144 rank 192 84.9 / 93.4; 4096 x 6144 rank 160 98.4 / 93.9,
+// 4096 x 8192 rank 160 124 / 108, rank 256 149 / 112; N = 4096: 302 / 273).  The pass over a 2:4-masked weight keeps it: 4096 x 8192 x 3072
+// rank 256 253 / 276 against the transposing launches that path has otherwise.
+inline bool adapter_t_beside(int64_t M, int64_t K, int64_t R) {
+    return adapter_t_in_pass(K, R) && (R + 31) / 32 * M * K <= 120000000;
+}
 inline int adapter_t_product_ksplit(int64_t M, int64_t K, int64_t Rpad) {
     const int64_t wgs = (M + 255) / 256 * ((Rpad + 127) / 128), steps = (K + 63) / 64;
     int64_t ks = (256 + wgs - 1) / wgs;
@@ -190,7 +197,7 @@ inline size_t twostage_dense_offset(int64_t M, int64_t K, int64_t R) {
 }
 inline size_t frag_weight_offset(int64_t M, int64_t K, int64_t R) {   // T first, then what a product of its own needs (launch_linear_frag)
     size_t b = adapter_t_bytes(M, R);
-    if (R > 0 && !adapter_t_beside(K, R)) {
+    if (R > 0 && !adapter_t_beside(M, K, R)) {
         const int64_t Rpad = adapter_rank_padded(R);
         b += adapter_frag_bytes(K, R) + round_up_256((size_t)adapter_t_product_ksplit(M, K, Rpad) * (size_t)M * (size_t)Rpad * sizeof(float));
     }

@@ -199,7 +199,8 @@ def _operand_order_bytes(M, K, N, R):
 
 
 @pytest.mark.parametrize("M,K,N,R,product", [(1000, 4096, 4096, 128, False), (4096, 4096, 8192, 64, False), (700, 4096, 30000, 128, False),
-                                             (1000, 4096, 4096, 127, True), (4096, 14336, 8192, 32, True), (600, 8224, 28000, 8, True)])
+                                             (1000, 4096, 4096, 127, True), (4096, 14336, 8192, 32, True), (600, 8224, 28000, 8, True),
+                                             (3662, 8192, 14336, 128, False), (3663, 8192, 14336, 128, True), (4096, 8192, 8192, 128, True), (4096, 4096, 14336, 256, True)])
 def test_fastest_workspace_of_the_low_rank_product(lib, M, K, N, R, product):
     """The fastest size holds what a product for T = X A_cat of its own needs only where there is one: a layer whose contraction is not split
     is told that and the weight, or the told size where that is larger."""

@@ -62,7 +62,8 @@ def test_tiles(M, K, N, R):
     _check(M, K, N, R, 0.5)
 
 
-@pytest.mark.parametrize("M,K,R", [(2100, 8192, 64), (1500, 8224, 130), (4100, 4128, 33)])
+@pytest.mark.parametrize("M,K,R", [(2100, 8192, 64), (1500, 8224, 130), (4100, 4128, 33),
+                                   (3662, 8192, 128), (3663, 8192, 128)])   # the last two: either side of the line to T beside the pass over the weight
 def test_adapter_product_of_its_own(M, K, R):
     """T = X A_cat large enough for the split-K product on the MFMA stage's kernel."""
     _check(M, K, 96, R, 0.5)
