@@ -314,6 +314,8 @@ inline size_t rowtile_partial_bytes(int64_t M, int64_t N) { return (size_t)M * (
 struct RowtilePlan {
     int ksplit = 1, t_slices = 1;
     bool partial = false;
+    double cost = 1e300;   // microseconds by that model
+    int64_t chunks = 0;    // that a CU goes through, one workgroup after the other
 };
 inline RowtilePlan rowtile_plan(int64_t M, int64_t K, int64_t N, int64_t R, size_t room) {
     const int64_t tiles = (N + 127) / 128, chunks = (K + 127) / 128, t_units = R > 0 ? adapter_rank_padded(R) / 16 * ((M + 15) / 16) : 0;
@@ -321,7 +323,6 @@ inline RowtilePlan rowtile_plan(int64_t M, int64_t K, int64_t N, int64_t R, size
     const size_t t_bytes = rowtile_t_out_bytes(M, R), one = rowtile_partial_bytes(M, N);
     const int64_t most = chunks < kRowtileMaxSplit ? chunks : kRowtileMaxSplit;
     RowtilePlan best;
-    double best_cost = 1e300;
     for (int ts = R > 0 ? kRowtileTSlices : 1; ts >= 1; ts /= 2)
         for (int64_t filled = 1; filled <= 4; ++filled) {   // the finest split that fits so many rounds
             int64_t ks = (256 * filled - t_units * ts) / tiles;
@@ -340,20 +341,26 @@ inline RowtilePlan rowtile_plan(int64_t M, int64_t K, int64_t N, int64_t R, size
             const double t = R > 0 ? 3.0 + (double)((K / 32 + 32 * ts - 1) / (32 * ts)) * 1.2 : 0.0;   // eight waves, four steps at a time
             if (main < t) main = t;
             const double cost = main + (partial ? 3.7 + (double)ks * (double)M * (double)N * 2e-6 : 0.0);
-            if (cost < best_cost) {
-                best_cost = cost;
+            if (cost < best.cost) {
+                best.cost = cost;
                 best.ksplit = (int)ks;
                 best.t_slices = ts;
                 best.partial = partial;
+                best.chunks = rounds * per_slice;
             }
             if (R == 0 && filled == 1 && best.ksplit > 1) {   // one slice writes y itself (whole rows measured 0.84 us a chunk)
                 const double alone = 5.0 + (double)((tiles + 255) / 256 * chunks) * step * 1.2 + (double)((tiles + 255) / 256 - 1) * 2.5;
-                if (alone < best_cost) {
-                    best_cost = alone;
+                if (alone < best.cost) {
                     best = RowtilePlan();
+                    best.cost = alone;
+                    best.chunks = (tiles + 255) / 256 * chunks;
                 }
             }
         }
+    if (best.cost == 1e300) {   // one slice, T from a launch in front (4.4 us)
+        best.chunks = (tiles + 255) / 256 * chunks;
+        best.cost = 9.4 + (double)best.chunks * step + (double)((tiles + 255) / 256 - 1) * 2.5;
+    }
     return best;
 }
 inline size_t rowtile_workspace_bytes(int64_t M, int64_t K, int64_t N, int64_t R) {
@@ -418,25 +425,39 @@ inline size_t linear_workspace_bytes_without_table(int64_t M, int64_t K, int64_t
     return b;
 }
 
+// Time of a call of up to 64 tokens in the small-batch kernels (the long-row kernel where it takes the shape), microseconds, the weight
+// coming from memory: rounds of workgroups of 16 rows, one per CU (two beside each other up to 16 tokens from 512 on, which
+// share its time), the chunks of the longest of a workgroup's eight slices, and T's launch in front.  Fitted, with rowtile_plan's model as
+// it is, on 2015 calls of 1 to 64 tokens, 128 to 28672 wide, rank 0 to 128, 30 to 70 % zeros, with and without a table, timed in
+// both kernels: the cheaper price is the faster kernel or within 3 % of it in all but 39 of them (at worst 1.21 times its time; the
+// thresholds on K, N and R that stood here: 115, 1.94 times, small layers of 33 to 64 tokens and rows in one round at 30 % zeros).
+inline double stream_price(int64_t M, int64_t K, int64_t N, int64_t R) {
+    const int64_t groups = (N + 15) / 16, chunks = ((K + 127) / 128 + 7) / 8, m_tiles = (M + 15) / 16;
+    const bool pairs = M <= 16 && groups >= 512, long_rows = linear_slice_takes(M, K, N);
+    double chunk = (M <= 16 ? 1.44 : M <= 32 ? 1.84 : 2.94) + 0.38 * (double)M / 16.0;
+    if (pairs) chunk *= 2.37;
+    if (K % 128 != 0 && M <= 32) chunk *= 1.17;
+    if (long_rows) chunk *= 0.87;
+    // (pairs: half of what the last round leaves idle is won back)
+    const double rounds = pairs ? 0.5 * ((double)((groups + 511) / 512) + (double)groups / 512.0) : (double)((groups + 255) / 256);
+    const double t = R > 0 ? 3.11 + 0.28 * (double)(m_tiles * ((R + 31) / 32)) : 0.0;
+    return 1.04 + (long_rows ? 1.0 : 0.0) + t + rounds * (1.16 + chunk * (double)chunks);
+}
 // The same kernel beyond those shapes (any K that is a multiple of 32, any N, fewer tokens), where the call's workspace has room for
-// its partial outputs (salr_linear_workspace_bytes_fastest).  The line to the small-batch kernel, which takes what is left of
-// up to 64 tokens, lies where the two meet: that one wants no launch to sum up, so it wins where a layer is a few microseconds of
-// work (us a call, it / this kernel: 1 x 4096 x 4096 12.1 / 14.6, 2 x 1024 x 1914 8.7 / 12.2, 13 x 1536 x 3072 6.2 / 9.2,
-// 32 x 512 x 1536 10.3 / 13.1), this one on larger layers and long rows (2 x 2560 x 26583 27.6 / 23.8, 3 x 7616 x 1792
-// 22.6 / 15.3, 16 x 7168 x 6932 36.6 / 25.9, 15 x 19936 x 512 47.7 / 22.3, 19 x 3904 x 13712 51.8 / 24.3) and from 33 tokens on
-// (59 x 3008 x 16384 79.7 / 34.3; 99 x 7648 x 12288 140 / 59 against the decoding path).
-inline bool rowtile_wide(int64_t M, int64_t K, int64_t N, int64_t R) {
+// its partial outputs (salr_linear_workspace_bytes_fastest) and it has the lower price; from 65 tokens on wherever it can (99 x 7648 x
+// 12288 140 us on the decoding path, 59 here).  Layers of a few microseconds stay with the small-batch kernel, which wants no launch to
+// sum up, whatever the models say of them (us a call, it / this kernel: 1 x 4096 x 4096 12.1 / 14.6, 13 x 1536 x 3072 6.2 / 9.2; larger
+// ones: 2 x 2560 x 26583 27.6 / 23.8, 3 x 7616 x 1792 22.6 / 15.3, 16 x 7168 x 6932 36.6 / 25.9, 59 x 3008 x 16384 79.7 / 34.3).
+inline bool rowtile_can(int64_t M, int64_t K, int64_t N) {
     if (M > kRowtileMaxM || K < 128 || K % 32 != 0 || K > kRowtileMaxColumns || N < 128) return false;
-    if (M <= 8 && K > 24576 && N > 4096) return false;   // 1 x 28672 x 8192: 83.5 in the long-row kernel, 92 here (three slices on 192 CUs)
-    if (M > 32) return true;
-    // without adapters that kernel is one launch and this one two: 24 x 1024 x 4000 6.4 / 10.2, 17 x 2560 x 3500 9.8 / 12.2,
-    // 24 x 1152 x 7800 12.6 / 11.8, 17 x 4096 x 1000 12.5 / 13.9, 17 x 4096 x 1500 13.4 / 12.5, 24 x 2560 x 5000 18.7 / 12.6
-    if (M > 16 && R == 0) return K >= (N >= 1500 ? 4096 : 5376) || N >= 7168 || N * K >= (12 << 20);
-    if (M > 16) return K >= 1024 || N >= 8192;
-    // as there: 2 x 2048 x 9300 10.8 / 13.0, 2 x 1856 x 11293 12.1 / 15.3,
-    // 2 x 2560 x 9300 16.2 / 15.0; 16 x 2048 x 9300 19.4 / 13.5
-    if (R == 0 && M <= 8 && K <= 2048 && N < 16384) return false;
-    return N * K >= (18 << 20) || N >= 16384 || K >= (R > 0 ? 5376 : 8192);
+    return !(M <= 8 && K > 24576 && N > 4096);   // 1 x 28672 x 8192: 83.5 in the long-row kernel, 92 here (three slices on 192 CUs)
+}
+inline bool rowtile_wide(int64_t M, int64_t K, int64_t N, int64_t R) {
+    if (!rowtile_can(M, K, N)) return false;
+    if (M > kStreamMaxM) return true;
+    if (M <= 16 && !(N * K >= (18 << 20) || N >= 16384 || K >= 5376)) return false;
+    if (M > 16 && M <= 32 && !(K >= 1024 || N >= 8192)) return false;
+    return rowtile_plan(M, K, N, R, SIZE_MAX).cost < stream_price(M, K, N, R);
 }
 // Whether the told size is all that the kernel ever uses: where that one has always had it with a split of K, so that the split, and
 // with it every bit of the result, does not depend on what a caller brings beyond it.  (N % 4 != 0: the told size has no room for

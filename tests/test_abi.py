@@ -211,6 +211,31 @@ def test_fastest_workspace_of_the_low_rank_product(lib, M, K, N, R, product):
     assert fast(M, K, N, R) == max(need, told(M, K, N, R))
 
 
+@pytest.mark.parametrize("M,K,N,R,row_tiled", [
+    (48, 1024, 2366, 0, False), (33, 512, 3837, 0, False), (64, 512, 3159, 0, False), (8, 8192, 2558, 0, False), (8, 8192, 3582, 0, False),
+    (1, 6528, 2907, 0, False), (17, 4736, 3443, 0, False), (24, 1792, 2155, 32, False), (24, 1152, 2857, 16, False),
+    (16, 7168, 6932, 32, True), (3, 7616, 1792, 32, True), (59, 3008, 16384, 32, True), (8, 8192, 8118, 0, True),
+    (32, 9600, 656, 0, True), (99, 7648, 12288, 64, True)])
+def test_fastest_workspace_takes_the_faster_kernel(lib, M, K, N, R, row_tiled):
+    """Up to 64 tokens the fastest size holds the row-tiled kernel's partial outputs only where that kernel is ahead of the small-batch
+    kernel, which needs no more than the told size: layers of a few microseconds, and rows in one round of its workgroups, are not."""
+    fast = lib.salr_linear_workspace_bytes_fastest
+    fast.restype, fast.argtypes = ctypes.c_size_t, [ctypes.c_int64] * 4
+    told = lib.salr_linear_workspace_bytes(M, K, N, R)
+    assert fast(M, K, N, R) > told if row_tiled else fast(M, K, N, R) == told
+
+
+@pytest.mark.parametrize("M,K,N,R,row_tiled", [
+    (33, 896, 1260, 16, False), (48, 768, 1872, 64, False), (48, 1536, 1324, 32, False), (64, 1152, 2032, 0, False), (33, 384, 3712, 0, False),
+    (16, 10880, 974, 32, True), (64, 4096, 14336, 32, True)])
+def test_fastest_workspace_of_four_bit_values_takes_the_faster_kernel(lib, M, K, N, R, row_tiled):
+    told, fast = lib.salr_qsalr_linear_workspace_bytes, lib.salr_qsalr_linear_workspace_bytes_fastest
+    for f in (told, fast):
+        f.restype, f.argtypes = ctypes.c_size_t, [ctypes.c_int64] * 5
+    nnz = N * (K - K // 5)
+    assert fast(M, K, N, R, nnz) > told(M, K, N, R, nnz) if row_tiled else fast(M, K, N, R, nnz) == told(M, K, N, R, nnz)
+
+
 @pytest.mark.parametrize("M,K,N,R", [(64, 4096, 14335, 32), (16, 4096, 8193, 0), (48, 14336, 8195, 32), (9, 1024, 8201, 64), (128, 8192, 10306, 128)])
 def test_fastest_workspace_splits_layers_of_uneven_rows(lib, M, K, N, R):
     """A layer whose N is no multiple of 4 is split over K like its neighbour: the told size has no room for that, the fastest size
