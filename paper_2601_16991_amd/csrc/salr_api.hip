@@ -43,31 +43,17 @@ bool qsalr_decodes_codes(int64_t M, int64_t K, int64_t N, int64_t nnz) {
     return nnz > 0 && K > 0 && salr::linear_takes_twostage(M, K, N) && (K / 32 + 15) / 16 <= 1024;
 }
 
-// Times of a call of 17 to 64 tokens in the small-batch kernel on the codes and in the row-tiled one, microseconds, after stream_price and
-// rowtile_plan and fitted as the former is, on 418 calls: the cheaper price is the faster kernel or within 3 % of it in all but 5.
-double nf4_price(int64_t M, int64_t K, int64_t N, int64_t R) {
-    const int64_t rounds = ((N + 15) / 16 + 255) / 256, chunks = (K / 128 + 7) / 8, m_tiles = (M + 15) / 16;
-    const double chunk = (M <= 32 ? 1.99 : 2.35) + 0.49 * (double)M / 16.0;
-    const double t = R > 0 ? 2.11 + 0.19 * (double)(m_tiles * ((R + 31) / 32)) : 0.0;
-    return 2.2 + t + (double)rounds * (1.87 + chunk * (double)chunks);
-}
-double rowtile_price_of_codes(int64_t M, int64_t K, int64_t N, int64_t R) {
-    const salr::RowtilePlan p = salr::rowtile_plan_of(M, K, N, R);
-    return p.cost + (M <= 32 ? 0.84 + 0.18 * (double)p.chunks : 0.31 + 0.36 * (double)p.chunks);
-}
-
-// QSALR calls of up to 128 tokens that take the row-tiled kernel on the codes, with room for its partial outputs.  Rows that are no whole
-// chunks and more than 64 tokens have no other kernel that reads codes.  From 17 to 64 tokens the lower price
-// (small-batch kernel / this one: 33 x 896 x 1260 10.5 / 19.9, 48 x 1536 x 1324 14.2 / 17.3; 17 x 5696 x 4549 64.2 / 23.0).  Up to 16 tokens
-// on many rows the vector ALUs set the pace (dequantising is twice the work of expanding), so not where its workgroups leave CUs idle
-// or slices are short (at 20 % sparsity: 3 x 3968 x 16473 36.9 / 44.5, 1 x 2688 x 20791 30.8 / 35.9, 9 x 768 x 9088 12.7 / 14.9; 16 x 4096 x
-// 14336 39.2 / 34.7), and on fewer where there is work for more than one launch (16 x 10880 x 974 33.4 / 20.9).
+// QSALR calls of up to 128 tokens that take the row-tiled kernel on the codes, with room for its partial outputs.  More than 64
+// tokens have no other kernel that reads codes; fewer take the small-batch kernel on layers of a few microseconds and the lower price on
+// others (us a call, that kernel / this one: 33 x 896 x 1260 10.5 / 19.9, 1 x 8192 x 8192 32 / 41, 16 x 2048 x 8192 14.6 / 16.5; 16 x 4096 x
+// 14336 36.4 / 30.7, 1 x 13824 x 5120 61 / 36, 17 x 5696 x 4549 64 / 23).  Rows that are no whole chunks have this kernel or none.
 bool qsalr_takes_rowtile(int64_t M, int64_t K, int64_t N, int64_t R, int64_t nnz) {
     if (nnz <= 0 || K <= 0 || !(salr::uses_rowtile(M, K, N) || salr::rowtile_can(M, K, N))) return false;
     if (M > salr::kStreamMaxM) return true;
-    if (M > 16) return K % 128 != 0 || rowtile_price_of_codes(M, K, N, R) < nf4_price(M, K, N, R);
-    const bool large = N * K >= (18 << 20) || N >= 16384 || K >= (R > 0 ? 5376 : 8192) || salr::uses_rowtile(M, K, N);
-    return large && (N < 8192 || (K >= 2048 && salr::rowtile_fill(M, K, N, R) >= 0.75));
+    const bool large = M > 32 || (M > 16 ? K >= 1024 || N >= 8192 : N * K >= (18 << 20) || N >= 16384 || K >= (R > 0 ? 5376 : 8192));
+    if (!large || K % 128 != 0) return large;
+    return salr::rowtile_price(salr::kPricesOfCodes, salr::rowtile_plan_of(M, K, N, R), M, R) <
+           salr::small_batch_price(salr::kPricesOfCodes, true, M, K, N, R);
 }
 
 }  // namespace

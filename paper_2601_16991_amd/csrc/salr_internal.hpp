@@ -425,23 +425,39 @@ inline size_t linear_workspace_bytes_without_table(int64_t M, int64_t K, int64_t
     return b;
 }
 
-// Time of a call of up to 64 tokens in the small-batch kernels (the long-row kernel where it takes the shape), microseconds, the weight
-// coming from memory: rounds of workgroups of 16 rows, one per CU (two beside each other up to 16 tokens from 512 on, which
-// share its time), the chunks of the longest of a workgroup's eight slices, and T's launch in front.  Fitted, with rowtile_plan's model as
-// it is, on 2015 calls of 1 to 64 tokens, 128 to 28672 wide, rank 0 to 128, 30 to 70 % zeros, with and without a table, timed in
-// both kernels: the cheaper price is the faster kernel or within 3 % of it in all but 39 of them (at worst 1.21 times its time; the
-// thresholds on K, N and R that stood here: 115, 1.94 times, small layers of 33 to 64 tokens and rows in one round at 30 % zeros).
-inline double stream_price(int64_t M, int64_t K, int64_t N, int64_t R) {
+// Times of a call of up to 64 tokens in the small-batch kernels (the long-row kernel where it takes the shape) and in the row-tiled one,
+// microseconds, the weight coming from memory.  Small-batch: T's launch in front, then rounds of workgroups of 16 rows, one per CU (up to
+// 16 tokens from 512 workgroups on two beside each other, which share its time), each as long as the chunks of the longest of its eight
+// slices.  Row-tiled: the plan's own cost, corrected for what the ranks cost the summing launch and for its chunks.
+struct SmallBatchPrices {
+    double call, t, t_rank;          // launch; T, and its 32 ranks of 16 tokens
+    double round, chunk[3], token;   // a round, a chunk up to 16, 32 and 64 tokens, and what 16 tokens add to it
+    double bank;                     // that, where rows of X are a multiple of 4 KB apart
+    double pairs, ragged;            // factors of a chunk: two workgroups on a CU; rows of X and bitmap that are no whole chunks, up to 32 tokens
+    double long_call, long_chunk;    // the long-row kernel
+    double tiled, tiled_rank, tiled_chunk[3];
+};
+// Fitted, with rowtile_plan's model as it is, on 3571 calls of 1 to 64 tokens on layers 128 to 28672 wide, rank 0 to 128, 30 to 70 % zeros,
+// with and without a table, timed in both kernels: with these prices 30 calls are more than 3 % slower than before the row-tiled kernel
+// took any of them, at most by 1.21 (with thresholds on K, N and R: 172, at most by 1.92).
+constexpr SmallBatchPrices kPrices = {0.82, 2.71, 0.39, 1.45, {1.29, 1.53, 2.39}, 0.44, 1.69, 1.9, 1.26, 3.4, 0.76, -0.71, 0.54, {-0.11, -0.27, -0.13}};
+// The same on 4-bit values, 1281 calls: 18, at most by 1.13 (thresholds: 80, by 2.02).
+constexpr SmallBatchPrices kPricesOfCodes = {0.53, 2.31, 0.5, 2.7, {2.04, 2.07, 2.77}, 0.28, 1.62, 1.3, 1.0, 0.0, 1.0, -0.55, 1.02, {0.41, 0.09, 0.34}};
+
+inline double small_batch_price(const SmallBatchPrices& c, bool codes, int64_t M, int64_t K, int64_t N, int64_t R) {
     const int64_t groups = (N + 15) / 16, chunks = ((K + 127) / 128 + 7) / 8, m_tiles = (M + 15) / 16;
-    const bool pairs = M <= 16 && groups >= 512, long_rows = linear_slice_takes(M, K, N);
-    double chunk = (M <= 16 ? 1.44 : M <= 32 ? 1.84 : 2.94) + 0.38 * (double)M / 16.0;
-    if (pairs) chunk *= 2.37;
-    if (K % 128 != 0 && M <= 32) chunk *= 1.17;
-    if (long_rows) chunk *= 0.87;
+    const bool pairs = M <= 16 && groups >= 512, long_rows = !codes && linear_slice_takes(M, K, N);
+    double chunk = c.chunk[M <= 16 ? 0 : M <= 32 ? 1 : 2] + c.token * (double)M / 16.0 * (K % 2048 == 0 ? c.bank : 1.0);
+    if (pairs) chunk *= c.pairs;
+    if (K % 128 != 0 && M <= 32) chunk *= c.ragged;
+    if (long_rows) chunk *= c.long_chunk;
     // (pairs: half of what the last round leaves idle is won back)
     const double rounds = pairs ? 0.5 * ((double)((groups + 511) / 512) + (double)groups / 512.0) : (double)((groups + 255) / 256);
-    const double t = R > 0 ? 3.11 + 0.28 * (double)(m_tiles * ((R + 31) / 32)) : 0.0;
-    return 1.04 + (long_rows ? 1.0 : 0.0) + t + rounds * (1.16 + chunk * (double)chunks);
+    const double t = R > 0 ? c.t + c.t_rank * (double)(m_tiles * ((R + 31) / 32)) : 0.0;
+    return c.call + (long_rows ? c.long_call : 0.0) + t + rounds * (c.round + chunk * (double)chunks);
+}
+inline double rowtile_price(const SmallBatchPrices& c, const RowtilePlan& p, int64_t M, int64_t R) {
+    return p.cost + c.tiled + c.tiled_rank * (double)((R + 31) / 32) + c.tiled_chunk[M <= 16 ? 0 : M <= 32 ? 1 : 2] * (double)p.chunks;
 }
 // The same kernel beyond those shapes (any K that is a multiple of 32, any N, fewer tokens), where the call's workspace has room for
 // its partial outputs (salr_linear_workspace_bytes_fastest) and it has the lower price; from 65 tokens on wherever it can (99 x 7648 x
@@ -456,8 +472,9 @@ inline bool rowtile_wide(int64_t M, int64_t K, int64_t N, int64_t R) {
     if (!rowtile_can(M, K, N)) return false;
     if (M > kStreamMaxM) return true;
     if (M <= 16 && !(N * K >= (18 << 20) || N >= 16384 || K >= 5376)) return false;
+    if (M <= 16 && R > 0) return true;   // (T's launch in front costs the small-batch kernel as much as the sum this one: it was ahead by more than 3 % in 5 of 326)
     if (M > 16 && M <= 32 && !(K >= 1024 || N >= 8192)) return false;
-    return rowtile_plan(M, K, N, R, SIZE_MAX).cost < stream_price(M, K, N, R);
+    return rowtile_price(kPrices, rowtile_plan(M, K, N, R, SIZE_MAX), M, R) < small_batch_price(kPrices, false, M, K, N, R);
 }
 // Whether the told size is all that the kernel ever uses: where that one has always had it with a split of K, so that the split, and
 // with it every bit of the result, does not depend on what a caller brings beyond it.  (N % 4 != 0: the told size has no room for
@@ -475,11 +492,6 @@ inline size_t rowtile_bytes(int64_t M, int64_t K, int64_t N, int64_t R) {
 inline RowtilePlan rowtile_plan_in(int64_t M, int64_t K, int64_t N, int64_t R, size_t room) {
     if (rowtile_on_told_size(M, K, N) || room >= rowtile_bytes(M, K, N, R)) return rowtile_plan_of(M, K, N, R);
     return rowtile_plan(M, K, N, R, linear_workspace_bytes(M, K, N, R));
-}
-// share of the CUs that a single round of workgroups gives work; 0 where there are more rounds
-inline double rowtile_fill(int64_t M, int64_t K, int64_t N, int64_t R) {
-    const int64_t wgs = (N + 127) / 128 * rowtile_plan_of(M, K, N, R).ksplit;
-    return wgs <= 256 ? (double)wgs / 256.0 : 0.0;
 }
 inline bool linear_takes_rowtile(int64_t M, int64_t K, int64_t N, int64_t R, size_t room) {
     return uses_rowtile(M, K, N) || (rowtile_wide(M, K, N, R) && room >= rowtile_bytes(M, K, N, R));
