@@ -235,7 +235,8 @@ static salr_status_t linear_entry(const uint16_t* x, int64_t M, int64_t K, int64
         if (!salr::linear_takes_frag(M, K, N, R, have) && (!salr::linear_takes_twostage(M, K, N) || a.lean)) return SALR_ERR_UNSUPPORTED;
         a.values = nullptr; a.codes = codes; a.scales = scales; a.nnz = nnz;
     }
-    if (!slice_table && have >= need && salr::builds_slice_table(M, K, N, R)) {   // none of the caller's: this call's own
+    if (!slice_table && have >= need && salr::reserves_slice_table(M, K, N, R) &&
+        !salr::linear_takes_rowtile(M, K, N, R, have)) {   // none of the caller's: this call's own
         a.slice_table = reinterpret_cast<const uint32_t*>(static_cast<char*>(workspace) +
                                                           salr::linear_workspace_bytes_without_table(M, K, N, R));
         a.build_table = true;

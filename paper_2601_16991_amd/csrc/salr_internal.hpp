@@ -268,19 +268,18 @@ inline GemmPlan gemm_plan(int64_t M, int64_t Kt, int64_t N, size_t partial_room 
     return best;
 }
 
-// Row-tiled streaming path (one pass over the compressed weight, X shared by the 128 rows of a workgroup): batches of
-// 9 to 128 tokens on layers whose rows come in whole 128-column chunks.  K is split over workgroups when the
-// 128-row tiles alone would leave most of the chip idle; the fp32 partial outputs [ksplit, M, N] follow T in the
-// workspace.  Measured against the other paths on the Llama-3 shapes: ahead from 33 tokens on everywhere (by 15 to
-// 45 %), from 9 tokens on where the layer has thousands of rows; below that the small-batch kernel, whose waves
-// run independently of each other, is as fast or faster.
+// Row-tiled streaming path (one pass over the compressed weight, X shared by the 128 rows of a workgroup) on the size that
+// salr_linear_workspace_bytes tells: batches of 33 to 128 tokens, and of 9 to 32 on layers of 8192 rows and more, whose rows come in
+// whole 128-column chunks.  rowtile_ksplit is the split of K that this size has room for, fp32 partial outputs [ksplit, M, N] behind T;
+// the 2:4 kernel, of which two workgroups share a CU, splits so.  The row-tiled kernel has one workgroup a CU and its own plan
+// (rowtile_plan) within the same bytes; its other shapes and what they need are rowtile_wide's.
 constexpr int64_t kRowtileMaxM = 128;
 constexpr int kRowtileMaxSplit = 32;
 constexpr int64_t kRowtileMaxColumns = 1 << 22;   // 32-bit offsets into X and a wave's rows of the weight
 inline int rowtile_ksplit(int64_t M, int64_t K, int64_t N) {
     const int64_t tiles = (N + 127) / 128, chunks = K / 128;
     if (N % 4 != 0) return 1;   // the reducing pass stores four outputs per thread
-    // up to 64 tokens two workgroups share a CU (and hide each other's barriers), above that one fills it
+    // (2:4 kernel:) up to 64 tokens two workgroups share a CU and hide each other's barriers, above that one fills it
     const int64_t enough = M <= 64 ? 448 : 224;
     int s = 1;
     while (s < 16 && tiles * s < enough && chunks / (s * 2) >= 4) s *= 2;
@@ -368,8 +367,8 @@ inline size_t rowtile_workspace_bytes(int64_t M, int64_t K, int64_t N, int64_t R
     return rowtile_t_bytes(M, K, R) + (ks > 1 ? round_up_256((size_t)ks * (size_t)M * (size_t)N * sizeof(float)) : 0);
 }
 
-// The linear on 2:4-masked weights (sparse matrix-core instructions, no decode stage): same tiling, K split and
-// workspace as the row-tiled path; other shapes go through launch_linear.
+// The linear on 2:4-masked weights (sparse matrix-core instructions, no decode stage): tiles of 128 rows, rowtile_ksplit and its
+// workspace; other shapes go through launch_linear.
 inline bool uses_2of4_kernel(int64_t M, int64_t K, int64_t N) {
     return rowtile_possible(M, K) && !(N % 4 != 0 && N < 64 * 128);
 }
@@ -394,12 +393,12 @@ bool linear_slice_takes(int64_t M, int64_t K, int64_t N);
 inline bool linear_takes_twostage(int64_t M, int64_t K, int64_t N) {
     return M > kStreamMaxM && !uses_rowtile(M, K, N) && uses_twostage(M, K);
 }
-// A call without a slice table of the caller's builds one for itself where the adapter pre-kernel runs anyway (R > 0)
-// and a kernel that gains more from it than the build costs follows: the small-batch streaming kernel on rows of whole
-// chunks, and the row-tiled kernel when its split of K starts where table slices do.  (The long-row kernel reads a
-// caller's table but gains less from it than reading the bitmap a second time costs: 70B down_proj M = 1, kernel +
-// pre-kernel 87.3 us without, 89.3 us with.)  The table sits behind the rest of the workspace.
-inline bool builds_slice_table(int64_t M, int64_t K, int64_t N, int64_t R) {
+// Where the told size has room for a slice table behind the rest of the workspace.  A call without a table of the caller's builds
+// one there where the small-batch streaming kernel runs on rows of whole chunks behind a launch for T (R > 0), which builds it on the
+// side.  (The long-row kernel reads a caller's table but gains less from it than reading the bitmap a second time costs: 70B
+// down_proj M = 1, kernel + launch for T 87.3 us without, 89.3 us with.)  The row-tiled kernel reads the bitmap left of its slices
+// itself; its calls have these bytes so that the size a caller was told stays what it was, as room for partial outputs.
+inline bool reserves_slice_table(int64_t M, int64_t K, int64_t N, int64_t R) {
     if (R <= 0 || M <= 0 || N <= 0 || K < 128 || K % 128 != 0) return false;
     if (uses_rowtile(M, K, N)) return kSliceTableSlices % rowtile_ksplit(M, K, N) == 0;
     if (linear_slice_takes(M, K, N)) return false;
@@ -409,7 +408,7 @@ inline size_t linear_workspace_bytes_without_table(int64_t M, int64_t K, int64_t
 // Workspace the linear needs: the small-batch path keeps fp32 split-K partials of T; the others see above.
 inline size_t linear_workspace_bytes(int64_t M, int64_t K, int64_t N, int64_t R) {
     const size_t b = linear_workspace_bytes_without_table(M, K, N, R);
-    return builds_slice_table(M, K, N, R) ? b + round_up_256(slice_table_bytes(N)) : b;
+    return reserves_slice_table(M, K, N, R) ? b + round_up_256(slice_table_bytes(N)) : b;
 }
 inline size_t linear_workspace_bytes_without_table(int64_t M, int64_t K, int64_t N, int64_t R) {
     if (M <= 0 || N <= 0) return 0;

@@ -564,12 +564,10 @@ hipError_t launch_linear_rowtile(const LinearArgs& a, hipStream_t stream, const 
     p.t_in = t_first ? p.t_out : nullptr;
     p.t_blocks = a.R > 0 && !t_first ? plan.t_slices * (Rpad / 16) * (int)((a.M + 15) / 16) : 0;
     if (t_first) launch_adapter_partial_to(a, p.t_out, stream);
-    LinearArgs b = a;
-    if (a.build_table) b.slice_table = nullptr;   // (room for one; the bitmap left of a slice is read by the kernel itself)
-    if (a.M <= 16) launch_rowtile_t<1>(b, p, stream, ev);
-    else if (a.M <= 32) launch_rowtile_t<2>(b, p, stream, ev);
-    else if (a.M <= 64) launch_rowtile_t<4>(b, p, stream, ev);
-    else launch_rowtile_t<8>(b, p, stream, ev);
+    if (a.M <= 16) launch_rowtile_t<1>(a, p, stream, ev);
+    else if (a.M <= 32) launch_rowtile_t<2>(a, p, stream, ev);
+    else if (a.M <= 64) launch_rowtile_t<4>(a, p, stream, ev);
+    else launch_rowtile_t<8>(a, p, stream, ev);
     if (p.partial != nullptr)
         hipLaunchKernelGGL(plan.ksplit <= 4 ? rowtile_finish_kernel<4> : rowtile_finish_kernel<8>, dim3((unsigned)((a.N + 63) / 64), (unsigned)((a.M + 15) / 16)), dim3(256), 0, stream, p.partial,
                            plan.ksplit, (int)a.M, a.N, p.pitch, p.t_out, plan.t_slices, a.b_cat, (int)a.R, Rpad, a.y);
