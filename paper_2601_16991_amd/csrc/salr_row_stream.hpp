@@ -37,9 +37,6 @@ __device__ __forceinline__ Buffer make_buffer(const void* p, uint64_t bytes) {
 __device__ __forceinline__ u32x4 buffer_load4(Buffer b, uint32_t lane_offset, uint32_t offset = 0) {
     return __builtin_amdgcn_raw_buffer_load_b128(b, (int)lane_offset, (int)offset, 0);
 }
-__device__ __forceinline__ uint32_t buffer_load1(Buffer b, uint32_t lane_offset, uint32_t offset = 0) {
-    return __builtin_amdgcn_raw_buffer_load_b32(b, (int)lane_offset, (int)offset, 0);
-}
 
 // ---- LDS by byte address
 __device__ __forceinline__ uint32_t lds_address(const void* p) {
