@@ -5,7 +5,8 @@
 //   2. row_scan_kernel       one workgroup: counts -> row_offsets (exclusive prefix, in place)
 //   3. encode_compact_rows_kernel (encode_compact_kernel where rows do not allow 16-byte loads)
 //                            one workgroup per row: order-preserving compaction of the nonzeros
-// Decoding is one launch, one workgroup per row.  All of it is integer/bit work; the traffic is the
+// Decoding is one launch, one workgroup per row.  Where short rows are many, launches that go by rows give each a wave instead
+// (kWaveRow).  All of it is integer/bit work; the traffic is the
 // dense matrix (2 B/element) against bitmap + values (1/8 + 2(1-p) B/element).
 #include "salr_device.hpp"
 #include "salr_internal.hpp"

@@ -32,7 +32,7 @@ constexpr int kQSlotDwords = 84;      // LDS per row per chunk: 160 bf16 (five v
                                       // dwords that the expansion may read past them; 84 n mod 64 are 16 different
                                       // multiples of 4, so the rows of a wave start in different banks
 constexpr int kQLevelWords = 16;
-constexpr int kQRowScales = 12;       // blocks that four chunks of a row's values may touch (ten), in whole requests of four lanes
+constexpr int kQRowScales = 12;       // blocks that four chunks of a row's values may touch (512 values: nine), in whole requests of four lanes
 
 template <int MT>
 struct NfStage {

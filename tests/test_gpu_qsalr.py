@@ -203,7 +203,7 @@ def test_qsalr_row_tiled(M, K, N, R, permille):
 @pytest.mark.parametrize("M,K,N,permille", [(1, 4096, 50, 0), (16, 4096, 33, 10), (2, 2944, 100, 500), (16, 1920, 17, 0), (5, 4224, 40, 0),
                                             (1, 4096, 16, 990)])
 def test_qsalr_slices_with_scales_by_row(M, K, N, permille):
-    """Up to 4096 columns a wave reads its slice's scales by row: full rows, whose slices touch ten blocks of 64 values, nearly empty
+    """Up to 4096 columns a wave reads its slice's scales by row: full rows, whose slices touch up to nine blocks of 64 values, nearly empty
     ones, one to four chunks a wave, and the first width past it.  Bit for bit the plain call on the dequantised values."""
     salr = _salr()
     w = wl.gaussian_bf16((N, K), 0.02, 800 + M + K)
