@@ -456,13 +456,31 @@ def test_row_tiled_uneven_rows(M, K, N, ranks):
 ])
 def test_row_tiled_any_width(M, K, N, ranks, density):
     x, w, a_cat, b_cat = _problem(M, K, N, ranks, 9600 + M + K, density=density, std_ab=0.05)
-    x[:, K - 40] = 0x7F80   # an infinite entry where the last two chunks overlap: met once, by its own weight
+    x[:, K - 40] = 0x7F80   # (adapters make most outputs NaN; without them see the test below)
     w[:, K - 40] = 0x3C00
     w[1, K - 40] = 0
     y, ref = _run(x, w, a_cat, b_cat), oracle.linear(x, w, a_cat, b_cat)
     assert np.array_equal(np.isnan(y), np.isnan(ref)) and np.array_equal(np.isinf(y), np.isinf(ref))
     x[:, K - 40] = 0x3F80
     _assert_close(_run(x, w, a_cat, b_cat), oracle.linear(x, w, a_cat, b_cat), f"any width M{M} K{K} N{N}")
+
+
+@pytest.mark.parametrize("M,K,N", [(M, K + tail, 131) for M, K in ((1, 9088), (14, 9088), (32, 9088), (50, 9088), (65, 256), (128, 1024)) for tail in (32, 64, 96)])
+def test_row_tiled_overlap_of_the_last_chunks(M, K, N):
+    """A row that is no multiple of 128 columns ends in a chunk that overlaps the one before.  The first and the last column of the
+    overlap are infinite in X, one in even and one in odd tokens: an output is infinite where the weight there is not zero and
+    NaN where it is, and no entry is met a second time by the zeros that stand for the chunk before."""
+    salr = _salr()
+    assert salr.salr_linear_workspace_bytes_fastest(M, K, N, 0) >= 2 * M * (N + 1) * 4, "the row-tiled kernel with K split"
+    x, w, _, _ = _problem(M, K, N, (), 9800 + M + K)
+    first, last = K - 128, K // 128 * 128 - 1
+    w[:, [first, last]] &= 0x7FFF
+    x[::2, first], x[1::2, last] = 0x7F80, 0xFF80
+    kinds = lambda a: np.isnan(a) * 3 + np.isposinf(a) + np.isneginf(a) * 2
+    y, ref = _run(x, w, None, None), oracle.linear(x, w, None, None)
+    assert np.array_equal(kinds(y), kinds(ref)) and np.isinf(ref).any(axis=1).all()
+    x[::2, first], x[1::2, last] = 0x4400, 0xC400   # 512: by far the largest entries, met once
+    _assert_close(_run(x, w, None, None), oracle.linear(x, w, None, None), f"overlap M{M} K{K} N{N}")
 
 
 @pytest.mark.parametrize("M,K,N,ranks,density", [

@@ -71,8 +71,13 @@ def test_fastest_size_is_enough_for_four_bit_values(M, K, N, R):
     assert torch.equal(y, alone) and bool((buf[size:] == 0x5A).all())
 
 
-# N no multiple of 4 on many rows: split over K with the fastest size only
-@pytest.mark.parametrize("M,K,N,R", [(16, 1152, 8193, 8), (40, 640, 8195, 33), (65, 512, 8198, 0)])
+# N no multiple of 4 on many rows: split over K with the fastest size only; rows of no whole chunks, where the told size is for other
+# kernels; the plan within the told size, with T in the same launch and (17 x 512 x 8320) without room for that
+ROW_TILED = [(16, 1152, 8193, 8), (40, 640, 8195, 33), (65, 512, 8198, 0), (5, 5408, 1131, 8), (20, 9120, 333, 24), (100, 992, 133, 5),
+             (64, 2048, 260, 5), (128, 4224, 388, 33), (17, 512, 8320, 16)]
+
+
+@pytest.mark.parametrize("M,K,N,R", ROW_TILED)
 @pytest.mark.parametrize("size_of", ["salr_linear_workspace_bytes", "salr_linear_workspace_bytes_fastest"])
 def test_row_tiled_calls_stay_inside_their_workspace(M, K, N, R, size_of):
     """At either size: close to the oracle, nothing behind the workspace touched, and what it held before of no account."""
@@ -88,6 +93,30 @@ def test_row_tiled_calls_stay_inside_their_workspace(M, K, N, R, size_of):
     buf[:size] = 0xFF   # NaN as fp32 and as bf16
     again = torch.empty_like(y)
     salr.salr_sparse_lowrank_linear(*args, again, buf[:size] if size else None)
+    torch.cuda.synchronize()
+    assert torch.equal(again, y)
+
+
+# (65 to 128 tokens: at the told size the values are dequantised first)
+@pytest.mark.parametrize("M,K,N,R", ROW_TILED + [(66, 160, 130, 0), (96, 4096, 515, 16), (128, 1152, 2050, 40)])
+@pytest.mark.parametrize("size_of", ["salr_qsalr_linear_workspace_bytes", "salr_qsalr_linear_workspace_bytes_fastest"])
+def test_row_tiled_calls_on_four_bit_values_stay_inside_their_workspace(M, K, N, R, size_of):
+    import paper_2601_16991_amd as salr
+    args, _, nnz = _layer(M, K, N, R)
+    codes, scales = salr.nf4_quantize(args[2])
+    w = oracle.decode(args[1].cpu().numpy().view(np.uint32), salr.nf4_dequantize(codes, scales, nnz).cpu().numpy().view(np.uint16)[:nnz],
+                      args[3].cpu().numpy().view(np.uint32), N, K)
+    ref = oracle.linear(args[0].cpu().numpy().view(np.uint16), w, *(None if t is None else t.cpu().numpy().view(np.uint16) for t in args[4:]))
+    size = getattr(salr, size_of)(M, K, N, R, nnz)
+    print(f"[workspace] quantised M{M} K{K} N{N} R{R}: {size_of} {size}", flush=True)
+    buf = torch.full((size + 4096,), 0x5A, dtype=torch.uint8, device=dev())
+    y, again = (torch.empty((M, N), dtype=torch.int16, device=dev()) for _ in range(2))
+    qargs = (args[0], args[1], codes, scales, args[3], nnz, args[4], args[5])
+    salr.salr_qsalr_linear(*qargs, y, buf[:size] if size else None)
+    torch.cuda.synchronize()
+    assert _ok(y, ref) and bool((buf[size:] == 0x5A).all())
+    buf[:size] = 0xFF   # NaN as fp32 and as bf16
+    salr.salr_qsalr_linear(*qargs, again, buf[:size] if size else None)
     torch.cuda.synchronize()
     assert torch.equal(again, y)
 
