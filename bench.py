@@ -127,6 +127,14 @@ class Layer:
         return [self.w_hat.view(torch.bfloat16).clone() for _ in range(n)]
 
 
+def workspace_query(two_of_four, lean):
+    """The query whose size a call is given: the one for the fastest path, which salr.linear takes by itself."""
+    import paper_2601_16991_amd as salr
+    if lean:
+        return salr.salr_linear_workspace_bytes_min
+    return salr.salr_linear_2of4_workspace_bytes_fastest if two_of_four else salr.salr_linear_workspace_bytes_fastest
+
+
 def time_linear(layer, M, steps, warmup, events=False, two_of_four=False, lean=False, prepared=False):
     """(ms per step by wall clock, list of per-launch kernel ms from HIP events or None).  two_of_four: the call is
     salr_sparse_lowrank_linear_2of4 (the layer must be 2:4-masked).  lean: the call gets the least workspace it accepts
@@ -140,9 +148,7 @@ def time_linear(layer, M, steps, warmup, events=False, two_of_four=False, lean=F
     dev = torch.device("cuda:0")
     x = torch.from_numpy(wl.activations(cfg, M).view(np.int16)).to(dev)
     y = torch.empty((M, cfg.N), dtype=torch.int16, device=dev)
-    ws_fn = salr.salr_linear_2of4_workspace_bytes if two_of_four else salr.salr_linear_workspace_bytes
-    if lean:
-        ws_fn = salr.salr_linear_workspace_bytes_min
+    ws_fn = workspace_query(two_of_four, lean)
     ws = torch.empty(max(ws_fn(M, cfg.K, cfg.N, layer.R), 256), dtype=torch.uint8, device=dev)[:max(ws_fn(M, cfg.K, cfg.N, layer.R), 1)]
 
     tables = layer.tables() if prepared else [None] * len(layer.enc)
@@ -345,7 +351,6 @@ def config_row(layer, M, steps, warmup, two_of_four=False, lean=False, prepared=
     flops above (2:4 rows: dense-equivalent flops; the sparse instructions execute half of them).  prepared: the call
     with the layer's slice table (64 more bytes per weight row, counted)."""
     import numpy as np
-    import paper_2601_16991_amd as salr
     import salr_workloads as wl
     cfg = layer.cfg
     w_ms, k_ms = time_linear(layer, M, steps, warmup, events=True, two_of_four=two_of_four, lean=lean, prepared=prepared)
@@ -353,9 +358,7 @@ def config_row(layer, M, steps, warmup, two_of_four=False, lean=False, prepared=
     k = float(np.mean(k_ms))
     nbytes = wl.algorithmic_bytes(M, cfg.K, cfg.N, layer.R, layer.nnz) + (64 * cfg.N if prepared else 0)
     fl = wl.algorithmic_flops(M, cfg.K, cfg.N, layer.R)
-    ws_fn = salr.salr_linear_2of4_workspace_bytes if two_of_four else salr.salr_linear_workspace_bytes
-    if lean:
-        ws_fn = salr.salr_linear_workspace_bytes_min
+    ws_fn = workspace_query(two_of_four, lean)
     row = {"ms_per_step": round(w_ms, 6), "kernel_avg_us": round(k * 1e3, 2), "dense_gemm_ms": round(d_ms, 6),
            "speedup_vs_dense_gemm": round(d_ms / w_ms, 3), "workspace_bytes": int(ws_fn(M, cfg.K, cfg.N, layer.R))}
     if M <= 128:
@@ -455,7 +458,7 @@ def time_qsalr(cfg, Ms, steps):
     for M in Ms:
         x = torch.from_numpy(wl.activations(cfg, M).view(np.int16)).to(dev)
         y = torch.empty((M, cfg.N), dtype=torch.int16, device=dev)
-        ws_bytes = salr.salr_qsalr_linear_workspace_bytes(M, cfg.K, cfg.N, layer.R, nnz)
+        ws_bytes = salr.salr_qsalr_linear_workspace_bytes_fastest(M, cfg.K, cfg.N, layer.R, nnz)
         ws = torch.empty(max(ws_bytes, 256), dtype=torch.uint8, device=dev)
         calls = [salr.PreparedQsalrLinear(x, b, c, sc, o, nnz, layer.a_cat, layer.b_cat, y, ws) for (b, c, sc, o) in copies]
         n_steps = steps if M > 64 else 10 * steps

@@ -579,7 +579,8 @@ def linear_prepared(x, bitmap, values, row_offsets, slice_table, a_cat, b_cat,
 def linear(x, bitmap, values, row_offsets, a_cat, b_cat, workspace: Optional[torch.Tensor] = None) -> torch.Tensor:
     """Y = X What^T + (X A_cat) B_cat, newly allocated.  Where ``workspace`` is None, or holds what salr_linear_workspace_bytes
     tells but less than salr_linear_workspace_bytes_fastest, one of the fastest size comes from torch's allocator for the
-    length of the call (large batches only; most on layers with K % 64 == 32, whose decoded weight the told size does not
-    contain); where the allocator has no room for it the call runs on what it was given.  With the fastest size nothing but the result is
+    length of the call and the workspace that was handed over stays unused (large batches, most on layers with K % 64 == 32, whose
+    decoded weight the told size does not contain; and up to 128 tokens where workgroups of 128 weight rows are faster and need
+    room for partial outputs); where the allocator has no room for it the call runs on what it was given.  With the fastest size nothing but the result is
     allocated; salr_sparse_lowrank_linear, which takes y, never allocates.  linear_prepared and linear_2of4 alike."""
     return _native().linear(0, x, bitmap, values, row_offsets, None, a_cat, b_cat, None, workspace, None)
