@@ -236,6 +236,17 @@ def test_fastest_workspace_of_four_bit_values_takes_the_faster_kernel(lib, M, K,
     assert fast(M, K, N, R, nnz) > told(M, K, N, R, nnz) if row_tiled else fast(M, K, N, R, nnz) == told(M, K, N, R, nnz)
 
 
+@pytest.mark.parametrize("M,K,N,R", [(16, 19840, 3200, 64), (12, 21120, 3968, 128), (8, 25472, 3456, 128), (8, 8192, 2432, 128)])
+def test_row_tiled_plan_leaves_workgroups_for_the_adapter_product(lib, M, K, N, R):
+    """Long rows at high ranks: the split of K that the fastest size is for leaves two workgroups of the first 256 to every 16 ranks and 16 tokens
+    of T, whose sum over all of K in one workgroup takes longer than the weight."""
+    fast = lib.salr_linear_workspace_bytes_fastest
+    fast.restype, fast.argtypes = ctypes.c_size_t, [ctypes.c_int64] * 4
+    rp = (R + 31) // 32 * 32
+    slices = (fast(M, K, N, R) - _r256(4 * M * rp * 4)) // (M * N * 4)
+    assert 1 < slices and slices * ((N + 127) // 128) + 2 * (rp // 16) * ((M + 15) // 16) <= 256
+
+
 @pytest.mark.parametrize("M,K,N,R", [(64, 4096, 14335, 32), (16, 4096, 8193, 0), (48, 14336, 8195, 32), (9, 1024, 8201, 64), (128, 8192, 10306, 128)])
 def test_fastest_workspace_splits_layers_of_uneven_rows(lib, M, K, N, R):
     """A layer whose N is no multiple of 4 is split over K like its neighbour: the told size has no room for that, the fastest size
