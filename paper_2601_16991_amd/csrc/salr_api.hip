@@ -52,8 +52,10 @@ bool qsalr_takes_rowtile(int64_t M, int64_t K, int64_t N, int64_t R, int64_t nnz
     if (M > salr::kStreamMaxM) return true;
     const bool large = M > 32 || (M > 16 ? K >= 1024 || N >= 8192 : N * K >= (18 << 20) || N >= 16384 || K >= (R > 0 ? 5376 : 8192));
     if (!large || K % 128 != 0) return large;
-    return salr::rowtile_price(salr::kPricesOfCodes, salr::rowtile_plan_of(M, K, N, R), M, R) <
-           salr::small_batch_price(salr::kPricesOfCodes, true, M, K, N, R);
+    const salr::SmallBatchPrices& prices = M <= 16 ? salr::kPricesOfFewCodes : salr::kPricesOfCodes;
+    const double nonzeros = (double)nnz / ((double)N * (double)K);
+    return salr::rowtile_price(prices, salr::rowtile_plan_of(M, K, N, R), M, R, nonzeros) <
+           salr::small_batch_price(prices, true, M, K, N, R, nonzeros);
 }
 
 }  // namespace

@@ -236,6 +236,17 @@ def test_fastest_workspace_of_four_bit_values_takes_the_faster_kernel(lib, M, K,
     assert fast(M, K, N, R, nnz) > told(M, K, N, R, nnz) if row_tiled else fast(M, K, N, R, nnz) == told(M, K, N, R, nnz)
 
 
+@pytest.mark.parametrize("M,K,N,R", [(8, 4096, 19622, 32), (12, 5888, 11682, 8), (4, 8192, 12021, 64), (4, 14336, 12032, 128)])
+def test_fastest_workspace_of_four_bit_values_knows_how_many_there_are(lib, M, K, N, R):
+    """Nearly full rows cost the row-tiled kernel a second lot of requests a chunk: few tokens stay with the small-batch kernel there."""
+    told, fast = lib.salr_qsalr_linear_workspace_bytes, lib.salr_qsalr_linear_workspace_bytes_fastest
+    for f in (told, fast):
+        f.restype, f.argtypes = ctypes.c_size_t, [ctypes.c_int64] * 5
+    thin, full = N * K // 2, N * K * 4 // 5
+    assert fast(M, K, N, R, thin) > told(M, K, N, R, thin)
+    assert fast(M, K, N, R, full) == told(M, K, N, R, full)
+
+
 @pytest.mark.parametrize("M,K,N,R", [(16, 19840, 3200, 64), (12, 21120, 3968, 128), (8, 25472, 3456, 128), (8, 8192, 2432, 128)])
 def test_row_tiled_plan_leaves_workgroups_for_the_adapter_product(lib, M, K, N, R):
     """Long rows at high ranks: the split of K that the fastest size is for leaves two workgroups of the first 256 to every 16 ranks and 16 tokens
