@@ -306,9 +306,10 @@ inline size_t rowtile_partial_bytes(int64_t M, int64_t N) { return (size_t)M * (
 // How the row-tiled kernel cuts its work: K over `ksplit` workgroups per 128 rows, and X A_cat over `t_slices` workgroups per 16
 // tokens and 16 ranks of the same launch.  The least of a model of the call's time in microseconds: the launch and the start of a
 // slice, rounds of 256 workgroups, one per CU, the chunks of a slice, the popcounts of the bitmap left of it, and the summing
-// launch, which there is when K is split or there are adapters.  A step of T's sum, four of 32 columns for each of eight waves, is 1.7 us (measured 1.7
-// for one token, 2.1 for 16): long rows get several slices of T rather than one more of the weight (16 x 19840 x 3200: one slice of T and ten of the
-// weight at rank 64 52.1 us, two and nine at rank 128 37.9, the small-batch kernel 42.9).  Its other figures are those of up to 16, 32, 64 and 128 tokens
+// launch, which there is when K is split or there are adapters.  A step of T's sum, four of 32 columns for each of eight waves, is 1.7 us above 32 ranks, whose rows of
+// A_cat a workgroup reads in 32 bytes each: long rows get several slices of T rather than one more of the weight (16 x 19840 x 3200 rank 64: one slice of
+// T and ten of the weight 52.4 us, two and nine 36.3, the small-batch kernel 43.5).  Up to 32 ranks 1.2: with 1.7 16 of 598 calls of 17 to 64 tokens
+// lose more than 3 % (64 x 6176 x 2432 rank 16 18.3 -> 20.8) and 4 gain as much; above 32 4 and 40 of 574.  Its other figures are those of up to 16, 32, 64 and 128 tokens
 // on 4096 x 14336 (2 slices: 22.4, 24.9, 29.9 and 40 us; 4: 26.7, 29.0, 36.1; 1: 35.1, 38.5, 46.0, 59) and 14336 x 4096.
 // partial: fp32 partial outputs in the workspace.  Without room for one slice's (`room` bytes) T comes from a launch in front and
 // the only slice adds the adapters itself.
@@ -339,7 +340,7 @@ inline RowtilePlan rowtile_plan(int64_t M, int64_t K, int64_t N, int64_t R, size
             const int64_t rounds = (tiles * ks + t_units * ts + 255) / 256;
             double main = 5.0 + (double)(rounds * per_slice) * step + (double)(rounds - 1) * 2.5 +
                           0.07 * (double)(chunks - chunks / ks);
-            const double t = R > 0 ? 3.0 + (double)((K / 32 + 32 * ts - 1) / (32 * ts)) * 1.7 : 0.0;   // eight waves, four steps at a time
+            const double t = R > 0 ? 3.0 + (double)((K / 32 + 32 * ts - 1) / (32 * ts)) * (R > 32 ? 1.7 : 1.2) : 0.0;   // eight waves, four steps at a time
             if (main < t) main = t;
             const double cost = main + (partial ? 3.7 + (double)ks * (double)M * (double)N * 2e-6 : 0.0);
             if (cost < best.cost) {
@@ -486,7 +487,9 @@ inline bool rowtile_wide(int64_t M, int64_t K, int64_t N, int64_t R) {
     if (!rowtile_can(M, K, N)) return false;
     if (M > kStreamMaxM) return true;
     if (M <= 16 && !(N * K >= (18 << 20) || N >= 16384 || K >= 5376)) return false;
-    if (M <= 16 && R > 0) return true;   // (T's launch in front costs the small-batch kernel as much as the sum this one: it was ahead by more than 3 % in 5 of 326)
+    // T's launch in front costs the small-batch kernel as much as the sum this one: it was ahead by more than 3 % in 211 of 9119 calls without a
+    // table.  The prices would find half of them, but a caller's table gains this kernel more (1 x 14336 x 4096 27.1 us without, 22.5 with).
+    if (M <= 16 && R > 0) return true;
     if (M > 16 && M <= 32 && !(K >= 1024 || N >= 8192)) return false;
     return rowtile_price(kPrices, rowtile_plan(M, K, N, R, SIZE_MAX), M, R) < small_batch_price(kPrices, false, M, K, N, R);
 }
