@@ -359,9 +359,13 @@ inline RowtilePlan rowtile_plan(int64_t M, int64_t K, int64_t N, int64_t R, size
                 }
             }
         }
-    if (best.cost == 1e300) {   // one slice, T from a launch in front (4.4 us)
+    // One slice, T from a launch in front (4.4 us): where there is no room for partial outputs, and on layers that the told size has no room to split
+    // where short rows make the partial outputs cost more than they save (128 x 2048 x 25851 rank 256 81.5 us with three slices, 68.3 so).
+    const double t_first = 9.4 + (double)((tiles + 255) / 256 * chunks) * step + (double)((tiles + 255) / 256 - 1) * 2.5;
+    if (best.cost == 1e300 || (R > 0 && N % 4 != 0 && uses_rowtile(M, K, N) && t_first < best.cost)) {
+        best = RowtilePlan();
         best.chunks = (tiles + 255) / 256 * chunks;
-        best.cost = 9.4 + (double)best.chunks * step + (double)((tiles + 255) / 256 - 1) * 2.5;
+        best.cost = t_first;
     }
     return best;
 }

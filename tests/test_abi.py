@@ -247,6 +247,13 @@ def test_fastest_workspace_of_four_bit_values_knows_how_many_there_are(lib, M, K
     assert fast(M, K, N, R, full) == told(M, K, N, R, full)
 
 
+@pytest.mark.parametrize("M,K,N,R", [(128, 2048, 25851, 256), (96, 2432, 28167, 256), (64, 2432, 28167, 256), (128, 6784, 26302, 128)])
+def test_fastest_workspace_splits_no_layer_of_few_columns_and_many_uneven_rows(lib, M, K, N, R):
+    fast = lib.salr_linear_workspace_bytes_fastest
+    fast.restype, fast.argtypes = ctypes.c_size_t, [ctypes.c_int64] * 4
+    assert fast(M, K, N, R) == lib.salr_linear_workspace_bytes(M, K, N, R)
+
+
 @pytest.mark.parametrize("M,K,N,R", [(16, 19840, 3200, 64), (12, 21120, 3968, 128), (8, 25472, 3456, 128), (8, 8192, 2432, 128)])
 def test_row_tiled_plan_leaves_workgroups_for_the_adapter_product(lib, M, K, N, R):
     """Long rows at high ranks: the split of K that the fastest size is for leaves two workgroups of the first 256 to every 16 ranks and 16 tokens
