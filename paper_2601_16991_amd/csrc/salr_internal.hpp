@@ -444,20 +444,22 @@ struct SmallBatchPrices {
     double tiled, tiled_rank, tiled_chunk[3];
     double tiled_full;               // what a chunk costs more whose 4-bit values outgrow the vectors that are asked for first
     double density, pair_round;      // what a chunk costs more from 0 to 100 % nonzeros (0 at 50 %), and a round of two workgroups on a CU
+    double later_round;              // what a round after the first costs more, from 17 tokens on
 };
 // Fitted, with rowtile_plan's model as it is, on 3571 calls of 1 to 64 tokens on layers 128 to 28672 wide, rank 0 to 128, 30 to 70 % zeros,
 // with and without a table, timed in both kernels: with these prices 30 calls are more than 3 % slower than before the row-tiled kernel
-// took any of them, at most by 1.21 (with thresholds on K, N and R: 172, at most by 1.92).
-constexpr SmallBatchPrices kPrices = {0.82, 2.71, 0.39, 1.45, {1.29, 1.53, 2.39}, 0.44, 1.69, 1.9, 1.26, 3.4, 0.76, -0.71, 0.54, {-0.11, -0.27, -0.13}, 0.0, 0.0, 0.0};
+// took any of them, at most by 1.21 (with thresholds on K, N and R: 172, at most by 1.92).  later_round from 14.1 us of 32 x 1024 x 7680 rank 16
+// (10.9 row-tiled) against 9.3 in one round (1024 x 3500).
+constexpr SmallBatchPrices kPrices = {0.82, 2.71, 0.39, 1.45, {1.29, 1.53, 2.39}, 0.44, 1.69, 1.9, 1.26, 3.4, 0.76, -0.71, 0.54, {-0.11, -0.27, -0.13}, 0.0, 0.0, 0.0, 1.0};
 // The same on 4-bit values of 17 to 64 tokens: of 15678 calls on full layers and thin ones 22 are more than 3 % slower than in the
 // small-batch kernel, at most by 1.11 (thresholds: 80 of 1281, by 2.02).
-constexpr SmallBatchPrices kPricesOfCodes = {0.53, 2.31, 0.5, 2.7, {2.04, 2.07, 2.77}, 0.28, 1.62, 1.3, 1.0, 0.0, 1.0, -0.55, 1.02, {0.41, 0.09, 0.34}, 0.0, 0.0, 0.0};
+constexpr SmallBatchPrices kPricesOfCodes = {0.53, 2.31, 0.5, 2.7, {2.04, 2.07, 2.77}, 0.28, 1.62, 1.3, 1.0, 0.0, 1.0, -0.55, 1.02, {0.41, 0.09, 0.34}, 0.0, 0.0, 0.0, 0.0};
 // And of up to 16, where the share of nonzeros decides: a row-tiled lane asks for two vectors of 32 codes at once, four cover a
 // row's piece of 128 columns if its values and its place in the first vector come to 128 at most: nearly always at 70 % nonzeros, hardly ever
 // at 80 %.  Two of the small-batch kernel's workgroups share a CU, and what counts is how many of them one CU gets (12 tokens, 80 %, us a
 // call, it / row-tiled: 8192 x 12115, three a CU, 53.5 / 59.5; 9600 x 12912, four a CU, 81.9 / 72.1).  Of 15555 calls at 30 to 100 % 64 are more than 3 % slower than in the small-batch
 // kernel, at most by 1.16; without these terms 178, by 1.19 (1 x 8192 x 20000 at 80 % 82.4 us instead of 73.6).
-constexpr SmallBatchPrices kPricesOfFewCodes = {0.53, 2.31, 0.5, 2.7, {1.97, 0.0, 0.0}, 0.42, 1.62, 1.41, 1.0, 0.0, 1.0, -3.44, 0.86, {0.46, 0.0, 0.0}, 0.43, 0.55, 0.52};
+constexpr SmallBatchPrices kPricesOfFewCodes = {0.53, 2.31, 0.5, 2.7, {1.97, 0.0, 0.0}, 0.42, 1.62, 1.41, 1.0, 0.0, 1.0, -3.44, 0.86, {0.46, 0.0, 0.0}, 0.43, 0.55, 0.52, 0.0};
 
 inline double small_batch_price(const SmallBatchPrices& c, bool codes, int64_t M, int64_t K, int64_t N, int64_t R, double nonzeros = 0.5) {
     const int64_t groups = (N + 15) / 16, chunks = ((K + 127) / 128 + 7) / 8, m_tiles = (M + 15) / 16;
@@ -471,7 +473,8 @@ inline double small_batch_price(const SmallBatchPrices& c, bool codes, int64_t M
     const double per_cu = (double)((groups + 255) / 256);
     const double rounds = !pairs ? per_cu : codes ? 0.5 * per_cu : 0.5 * ((double)((groups + 511) / 512) + (double)groups / 512.0);
     const double t = R > 0 ? c.t + c.t_rank * (double)(m_tiles * ((R + 31) / 32)) : 0.0;
-    return c.call + (long_rows ? c.long_call : 0.0) + t + rounds * (c.round + (pairs ? c.pair_round : 0.0) + chunk * (double)chunks);
+    const double later = M > 16 ? c.later_round * (rounds - 1.0) : 0.0;
+    return c.call + (long_rows ? c.long_call : 0.0) + t + later + rounds * (c.round + (pairs ? c.pair_round : 0.0) + chunk * (double)chunks);
 }
 inline double rowtile_price(const SmallBatchPrices& c, const RowtilePlan& p, int64_t M, int64_t R, double nonzeros = 0.5) {
     const double full = nonzeros <= 0.7 ? 0.0 : nonzeros >= 0.8 ? 1.0 : (nonzeros - 0.7) * 10.0;   // share of the chunks that pay tiled_full

@@ -215,7 +215,7 @@ def test_fastest_workspace_of_the_low_rank_product(lib, M, K, N, R, product):
     (48, 1024, 2366, 0, False), (33, 512, 3837, 0, False), (64, 512, 3159, 0, False), (8, 8192, 2558, 0, False), (8, 8192, 3582, 0, False),
     (1, 6528, 2907, 0, False), (17, 4736, 3443, 0, False), (24, 1792, 2155, 32, False), (24, 1152, 2857, 16, False),
     (16, 7168, 6932, 32, True), (3, 7616, 1792, 32, True), (59, 3008, 16384, 32, True), (8, 8192, 8118, 0, True),
-    (32, 9600, 656, 0, True), (99, 7648, 12288, 64, True)])
+    (32, 9600, 656, 0, True), (99, 7648, 12288, 64, True), (32, 1024, 7680, 16, True), (24, 1024, 8064, 16, True)])
 def test_fastest_workspace_takes_the_faster_kernel(lib, M, K, N, R, row_tiled):
     """Up to 64 tokens the fastest size holds the row-tiled kernel's partial outputs only where that kernel is ahead of the small-batch
     kernel, which needs no more than the told size: layers of a few microseconds, and rows in one round of its workgroups, are not."""
