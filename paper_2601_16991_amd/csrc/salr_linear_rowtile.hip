@@ -18,8 +18,8 @@
 // that is paid.  Two workgroups per CU (half the slice, 128 registers a wave) hide each other's start, but spill: 30.5 us a call.
 //
 // Measured, whole calls at p = .5, rank 32, before (two workgroups per CU, a barrier per chunk or per four, T in a launch of its own)
-// and now: 16 x 4096 x 14336 34.9 -> 22.4 us, 32 tokens 36.3 -> 24.9, 64 tokens 47.7 -> 29.9, 128 tokens 52.8 -> 40; 64 x 14336 x 4096
-// 56.7 -> 35.3; 16 x 8192 x 28672 92 -> 65.  The bytes of the first take 13 us at what a large copy reaches; its loop runs at 4.6 TB/s.
+// and now: 16 x 4096 x 14336 34.2 -> 24.4 us, 32 tokens 37.5 -> 26.1, 64 tokens 46.4 -> 30.3, 128 tokens 53.8 -> 40.6; 64 x 14336 x 4096
+// 56.3 -> 33.9; 16 x 8192 x 28672 101 -> 70.  The bytes of the first take 13 us at what a large copy reaches; its loop runs at 4.1 TB/s.
 // Tried and left out: packed values two units ahead instead of one (+6 %); 32 weight rows per wave, which halves the operand
 // reads of X (+18 % at 16 tokens: half as many slices' starts overlap); seven waves, so that 256 instead of 224
 // workgroups share the rows of that layer (level); values fetched as whole 256-byte runs of a row, half as many cycles of the
