@@ -54,7 +54,7 @@ bool qsalr_takes_rowtile(int64_t M, int64_t K, int64_t N, int64_t R, int64_t nnz
     if (!large || K % 128 != 0) return large;
     const salr::SmallBatchPrices& prices = M <= 16 ? salr::kPricesOfFewCodes : salr::kPricesOfCodes;
     const double nonzeros = (double)nnz / ((double)N * (double)K);
-    return salr::rowtile_price(prices, salr::rowtile_plan_of(M, K, N, R), M, R, nonzeros) <
+    return salr::rowtile_price(prices, salr::rowtile_plan_of(M, K, N, R, true), M, R, nonzeros) <
            salr::small_batch_price(prices, true, M, K, N, R, nonzeros);
 }
 
@@ -311,7 +311,7 @@ size_t salr_qsalr_linear_workspace_bytes_fastest(int64_t M, int64_t K, int64_t N
     const size_t told = salr_qsalr_linear_workspace_bytes(M, K, N, R, nnz);
     if (M <= 0 || K <= 0 || N <= 0 || R < 0 || R > kMaxRank || K % 32 != 0 || nnz <= 0) return told;
     if (qsalr_takes_rowtile(M, K, N, R, nnz)) {
-        const size_t b = salr::rowtile_bytes(M, K, N, R);
+        const size_t b = salr::rowtile_bytes_fastest(M, K, N, R);
         return b > told ? b : told;
     }
     if (salr::linear_nf4_takes(M, K, N, nnz)) return told;

@@ -315,11 +315,27 @@ inline size_t rowtile_partial_bytes(int64_t M, int64_t N) { return (size_t)M * (
 // the only slice adds the adapters itself.
 struct RowtilePlan {
     int ksplit = 1, t_slices = 1;
-    bool partial = false;
+    int parts = 1;           // of a slice, one beside the other in a workgroup of 128 / parts rows
+    bool partial = false;    // fp32 partial outputs
+    bool one_launch = false; // the adapters are added in the launch itself, from T as its first workgroups leave it
     double cost = 1e300;   // microseconds by that model
     int64_t chunks = 0;    // that a CU goes through, one workgroup after the other
 };
-inline RowtilePlan rowtile_plan(int64_t M, int64_t K, int64_t N, int64_t R, size_t room) {
+// Parts of K in a workgroup (1, 2, 4: 128, 64, 32 rows) instead of slices over workgroups, where that many row tiles and T's workgroups are one
+// round: no partial outputs and no launch that sums them, but every workgroup copies all of X to LDS, in shorter panels with as many more
+// barriers (part_step: what that adds to a chunk), and from 33 tokens on four parts' panels would hold half a unit.  Below kOneLaunchTiles row tiles
+// too few CUs take part, whatever the model says.  us a call, slices / parts: 16 x 4096 x 14336 rank 32 23.2 / 21.8 (2), 8 x 2048 x 14336 14.4 / 12.5 (2),
+// 16 x 4096 x 7168 16.0 / 13.9 (4), 64 x 4096 x 28672 51.2 / 47.2 (1), 64 x 2048 x 14336 19.9 / 17.6 (2); left with slices:
+// 64 x 8192 x 14336 51.0 / 54.0 (2), 16 x 3072 x 8192 14.4 / 15.3 (2), 24 x 8192 x 7168 26.3 / 29.2 (4).  Of 220 random calls of 1 to 128 tokens on
+// layers 512 to 16384 columns by 3000 to 28672 rows the rule makes 4 slower by more than 2 %, at most by 6, the geometric mean 1.035.
+constexpr int64_t kOneLaunchTiles = 130;
+inline double part_step(int64_t M, int q) {
+    if (q == 1) return 0.0;
+    if (M <= 16) return q == 2 ? 0.10 : 0.24;
+    if (M <= 32) return q == 2 ? 0.12 : 0.40;
+    return M <= 64 ? 0.42 : 0.55;
+}
+inline RowtilePlan rowtile_plan(int64_t M, int64_t K, int64_t N, int64_t R, size_t room, bool slices_only = false) {
     const int64_t tiles = (N + 127) / 128, chunks = (K + 127) / 128, t_units = R > 0 ? adapter_rank_padded(R) / 16 * ((M + 15) / 16) : 0;
     const double step = M <= 16 ? 0.70 : M <= 32 ? 0.85 : M <= 64 ? 1.05 : 1.50;
     const size_t t_bytes = rowtile_t_out_bytes(M, R), one = rowtile_partial_bytes(M, N);
@@ -346,9 +362,31 @@ inline RowtilePlan rowtile_plan(int64_t M, int64_t K, int64_t N, int64_t R, size
             if (cost < best.cost) {
                 best.cost = cost;
                 best.ksplit = (int)ks;
+                best.parts = 1;
+                best.one_launch = false;
                 best.t_slices = ts;
                 best.partial = partial;
                 best.chunks = rounds * per_slice;
+            }
+            // One slice, the parts of a workgroup added up in LDS, T handed over inside the launch.
+            for (int q = R > 0 ? 1 : 2; !slices_only && filled == 1 && q <= (M <= 32 ? 4 : 2); q *= 2) {
+                const int64_t row_tiles = (N * q + 127) / 128, per_part = (chunks + q - 1) / q;
+                if (row_tiles < kOneLaunchTiles || row_tiles + t_units * ts > 256 || chunks < 4 * q || t_bytes + one > room) continue;
+                double alone = 5.0 + (double)per_part * (step + part_step(M, q)) + 0.07 * (double)(chunks - chunks / q);
+                if (R > 0) {   // T's workgroups meet in a knockout, the last sums its slices and hands it out
+                    double handed = t + 5.5 + 0.35e-3 * (double)(M * adapter_rank_padded(R));
+                    for (int64_t blocks = t_units * ts; blocks > 8; blocks = (blocks + 1) / 2) handed += 0.5;
+                    if (alone < handed) alone = handed;
+                }
+                alone += 1.5;
+                if (alone < best.cost) {
+                    best.cost = alone;
+                    best.ksplit = 1;
+                    best.parts = q;
+                    best.t_slices = ts;
+                    best.partial = best.one_launch = R > 0;
+                    best.chunks = per_part;
+                }
             }
             if (R == 0 && filled == 1 && best.ksplit > 1) {   // one slice writes y itself (whole rows measured 0.84 us a chunk)
                 const double alone = 5.0 + (double)((tiles + 255) / 256 * chunks) * step * 1.2 + (double)((tiles + 255) / 256 - 1) * 2.5;
@@ -369,6 +407,14 @@ inline RowtilePlan rowtile_plan(int64_t M, int64_t K, int64_t N, int64_t R, size
     }
     return best;
 }
+// What a call whose row-tiled launch adds the adapters itself (RowtilePlan::one_launch) has behind its one slice of partial outputs: T,
+// and the words of salr_handover.hpp.  Without room for it the summing launch does that.
+inline size_t rowtile_pair_bytes(int64_t M, int64_t N, int64_t R, const RowtilePlan& p) {
+    if (!p.one_launch) return 0;
+    const int64_t Rpad = adapter_rank_padded(R), pairs = (N + 127) / 128 * 8, t_blocks = p.t_slices * (Rpad / 16) * ((M + 15) / 16);
+    return round_up_256((size_t)M * (size_t)Rpad * sizeof(uint16_t)) + (size_t)(pairs + t_blocks) * sizeof(uint64_t);
+}
+uint64_t next_handover_tag();   // 64 bits that no other call of the process has
 inline size_t rowtile_workspace_bytes(int64_t M, int64_t K, int64_t N, int64_t R) {
     const int ks = rowtile_ksplit(M, K, N);
     return rowtile_t_bytes(M, K, R) + (ks > 1 ? round_up_256((size_t)ks * (size_t)M * (size_t)N * sizeof(float)) : 0);
@@ -476,6 +522,7 @@ inline double small_batch_price(const SmallBatchPrices& c, bool codes, int64_t M
     const double later = M > 16 ? c.later_round * (rounds - 1.0) : 0.0;
     return c.call + (long_rows ? c.long_call : 0.0) + t + later + rounds * (c.round + (pairs ? c.pair_round : 0.0) + chunk * (double)chunks);
 }
+// p: a plan of slices over workgroups, which the prices were fitted on.  (Where parts in one launch are faster still, so is the call.)
 inline double rowtile_price(const SmallBatchPrices& c, const RowtilePlan& p, int64_t M, int64_t R, double nonzeros = 0.5) {
     const double full = nonzeros <= 0.7 ? 0.0 : nonzeros >= 0.8 ? 1.0 : (nonzeros - 0.7) * 10.0;   // share of the chunks that pay tiled_full
     return p.cost + c.tiled + c.tiled_rank * (double)((R + 31) / 32) +
@@ -498,19 +545,28 @@ inline bool rowtile_wide(int64_t M, int64_t K, int64_t N, int64_t R) {
     // table.  The prices would find half of them, but a caller's table gains this kernel more (1 x 14336 x 4096 27.1 us without, 22.5 with).
     if (M <= 16 && R > 0) return true;
     if (M > 16 && M <= 32 && !(K >= 1024 || N >= 8192)) return false;
-    return rowtile_price(kPrices, rowtile_plan(M, K, N, R, SIZE_MAX), M, R) < small_batch_price(kPrices, false, M, K, N, R);
+    return rowtile_price(kPrices, rowtile_plan(M, K, N, R, SIZE_MAX, true), M, R) < small_batch_price(kPrices, false, M, K, N, R);
 }
 // Whether the told size is all that the kernel ever uses: where that one has always had it with a split of K, so that the split, and
 // with it every bit of the result, does not depend on what a caller brings beyond it.  (N % 4 != 0: the told size has no room for
 // a split, the fastest one has: 64 x 4096 x 14335 at rank 32 52.3 us without, 33.3 with (14336: 31.7), 16 x 8192 x 8193 61.8 / 32.6;
 // 4-bit values, 37 x 17536 x 10315: 273 / 106, the small-batch kernel 170.)
 inline bool rowtile_on_told_size(int64_t M, int64_t K, int64_t N) { return uses_rowtile(M, K, N) && N % 4 == 0; }
-inline RowtilePlan rowtile_plan_of(int64_t M, int64_t K, int64_t N, int64_t R) {
-    return rowtile_plan(M, K, N, R, rowtile_on_told_size(M, K, N) ? linear_workspace_bytes(M, K, N, R) : SIZE_MAX);
+inline RowtilePlan rowtile_plan_of(int64_t M, int64_t K, int64_t N, int64_t R, bool slices_only = false) {
+    return rowtile_plan(M, K, N, R, rowtile_on_told_size(M, K, N) ? linear_workspace_bytes(M, K, N, R) : SIZE_MAX, slices_only);
 }
-inline size_t rowtile_bytes(int64_t M, int64_t K, int64_t N, int64_t R) {
-    const RowtilePlan p = rowtile_plan_of(M, K, N, R);
+inline size_t rowtile_plan_bytes(int64_t M, int64_t K, int64_t N, int64_t R, const RowtilePlan& p) {
     return p.partial ? round_up_256(rowtile_t_out_bytes(M, R) + (size_t)p.ksplit * rowtile_partial_bytes(M, N)) : rowtile_t_bytes(M, K, R);
+}
+// With this much a call of rowtile_wide's shapes goes through the kernel: what its slices need, parts in one launch or not.
+inline size_t rowtile_bytes(int64_t M, int64_t K, int64_t N, int64_t R) {
+    const size_t slices = rowtile_plan_bytes(M, K, N, R, rowtile_plan_of(M, K, N, R, true)), b = rowtile_plan_bytes(M, K, N, R, rowtile_plan_of(M, K, N, R));
+    return slices > b ? slices : b;
+}
+inline size_t rowtile_bytes_fastest(int64_t M, int64_t K, int64_t N, int64_t R) {   // with room for T to be handed over
+    const RowtilePlan p = rowtile_plan_of(M, K, N, R);
+    const size_t least = rowtile_bytes(M, K, N, R), b = rowtile_plan_bytes(M, K, N, R, p) + rowtile_pair_bytes(M, N, R, p);
+    return b > least ? b : least;
 }
 // The plan of a call that brings `room` bytes: the one above, or the one that fits the told size.
 inline RowtilePlan rowtile_plan_in(int64_t M, int64_t K, int64_t N, int64_t R, size_t room) {
@@ -534,7 +590,7 @@ inline size_t linear_workspace_bytes_fastest(int64_t M, int64_t K, int64_t N, in
     const size_t told = linear_workspace_bytes(M, K, N, R);
     if (N <= 0 || rowtile_on_told_size(M, K, N)) return told;
     if (uses_rowtile(M, K, N) || rowtile_wide(M, K, N, R)) {
-        const size_t b = rowtile_bytes(M, K, N, R);
+        const size_t b = rowtile_bytes_fastest(M, K, N, R);
         return b > told ? b : told;
     }
     if (M <= kStreamMaxM || !uses_frag(M, K)) return told;

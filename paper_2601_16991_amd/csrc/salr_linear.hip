@@ -5,6 +5,9 @@
 //                           tile into LDS per k-step, bf16 MFMA, adapters as extra k-steps
 #include <hip/hip_ext.h>
 
+#include <atomic>
+#include <chrono>
+
 #include "salr_device.hpp"
 #include "salr_internal.hpp"
 #include "salr_linear_common.hpp"
@@ -166,6 +169,17 @@ hipError_t launch_fill_zero(uint16_t* out, int64_t count, hipStream_t stream) {
 }
 
 thread_local TimingEvents g_timing_events;
+
+// Bijective mixing (splitmix64's finaliser) of a counter that starts from the clock: tags do not repeat within a process, and are not the
+// small numbers or floats that a workspace may hold.
+uint64_t next_handover_tag() {
+    static std::atomic<uint64_t> calls{(uint64_t)std::chrono::steady_clock::now().time_since_epoch().count()};
+    uint64_t v = calls.fetch_add(1, std::memory_order_relaxed) * 0x9E3779B97F4A7C15ull;
+    v = (v ^ (v >> 30)) * 0xBF58476D1CE4E5B9ull;
+    v = (v ^ (v >> 27)) * 0x94D049BB133111EBull;
+    v ^= v >> 31;
+    return v != 0 ? v : 1;   // 0: a clear word
+}
 
 hipError_t launch_linear(const LinearArgs& a, hipStream_t stream) {
     if (a.M == 0 || a.N == 0) return hipSuccess;

@@ -13,19 +13,28 @@
 //                workgroups of the same launch write its split-K partial sums, and the launch that adds up the slices' partial
 //                outputs multiplies T with B_cat and adds that too.  (With a launch of its own in front it cost 4.4 us of the
 //                34.9 us of a 16 x 4096 x 14336 call.)
+// Where the row tiles alone fill a round of the CUs (rowtile_plan), K is not split over workgroups: 128, 64 or 32 rows a workgroup, the
+// waves on one, two or four parts of K beside each other (Q), added up in LDS.  T, formed 3 to 7 us into the launch, is then handed over
+// inside it (salr_handover.hpp) and there is no second launch, which costs 4.6 us: 16 x 4096 x 14336 23.9 -> 22.0 us a layer,
+// 16 x 4096 x 7168 16.0 -> 13.9, 8 x 2048 x 14336 14.4 -> 12.5, 64 x 4096 x 28672 51.2 -> 47.2.  A part's panels of X are that much shorter,
+// and every barrier costs the waves their lead: 16 x 4096 x 14336 would take 21.2 without any.
 // The work is cut so that there is one workgroup per CU and one round of them where that can be (rowtile_plan): a slice starts
 // with two dependent round trips to memory and the popcounts of the bitmap left of it, 4 us, and the longer a slice the less often
 // that is paid.  Two workgroups per CU (half the slice, 128 registers a wave) hide each other's start, but spill: 30.5 us a call.
 //
-// Measured, whole calls at p = .5, rank 32, before (two workgroups per CU, a barrier per chunk or per four, T in a launch of its own)
-// and now: 16 x 4096 x 14336 34.2 -> 24.4 us, 32 tokens 37.5 -> 26.1, 64 tokens 46.4 -> 30.3, 128 tokens 53.8 -> 40.6; 64 x 14336 x 4096
+// Measured with slices over workgroups, whole calls at p = .5, rank 32, before (two workgroups per CU, a barrier per chunk or per four, T in a
+// launch of its own) and so: 16 x 4096 x 14336 34.2 -> 24.4 us, 32 tokens 37.5 -> 26.1, 64 tokens 46.4 -> 30.3, 128 tokens 53.8 -> 40.6; 64 x 14336 x 4096
 // 56.3 -> 33.9; 16 x 8192 x 28672 101 -> 70.  The bytes of the first take 13 us at what a large copy reaches; its loop runs at 4.1 TB/s.
 // Tried and left out: packed values two units ahead instead of one (+6 %); 32 weight rows per wave, which halves the operand
 // reads of X (+18 % at 16 tokens: half as many slices' starts overlap); seven waves, so that 256 instead of 224
-// workgroups share the rows of that layer (level); values fetched as whole 256-byte runs of a row, half as many cycles of the
+// workgroups share the rows of that layer (level); twelve waves on three parts (25.9 us); the partial outputs of slices added up inside the
+// launch by whoever comes last (23.2 to 24.5 us, 14336 x 4096 24.4 to 33: see salr_handover.hpp); values fetched as whole 256-byte runs of a row, half as many cycles of the
 // address unit (the transposition into conflict-free LDS columns then meets conflicts of its own).
 #include <hip/hip_ext.h>
 
+#include <type_traits>
+
+#include "salr_handover.hpp"
 #include "salr_internal.hpp"
 #include "salr_nf4.hpp"
 #include "salr_row_stream.hpp"
@@ -77,7 +86,8 @@ __device__ __forceinline__ void adapter_partial_block(const uint16_t* __restrict
 #pragma unroll
         for (int w = 0; w < W; ++w) s += red[(w * 4 + e) * 64 + l];
         const int mm = 16 * mt + 4 * (l >> 4) + e, rr = 16 * rt + (l & 15);
-        if (mm < M) t_partial[((int64_t)b * M + mm) * Rpad + rr] = rr < R ? s : 0.f;
+        if (mm < M)   // (read by another workgroup of this launch)
+            __hip_atomic_store(t_partial + ((int64_t)b * M + mm) * Rpad + rr, rr < R ? s : 0.f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
 
@@ -103,19 +113,128 @@ struct RowtileArgs {
     const float* t_in;   // or those of an earlier one (kStreamTSlices): slice 0 adds the adapters
     float* partial;      // [ksplit, M, pitch] fp32, or null: y
     int64_t pitch;
+    uint64_t* words;     // one slice that adds the adapters in this launch (salr_handover.hpp): a pair per sixteen rows, then t_blocks.  Or null
+    uint16_t* t_sum;     // there: T, bf16 [M, Rpad]
+    uint64_t tag;
+    int polls;
 };
 
+// T B_cat for the sixteen rows of a wave, T past the caches
+template <int MT>
+struct RowtileAdapters {
+    const uint16_t* b_cat;
+    int M, R, Rpad, n, g;
+    int64_t N, n0;
+    Buffer t_sum;
+    uint32_t e[8];   // B_cat and T of a rank step
+    u32x4 tq[MT];
+
+    __device__ __forceinline__ RowtileAdapters(const RowtileArgs& p, int64_t row0, int M_, int64_t N_, const uint16_t* b, int R_, int Rpad_, int lane)
+        : b_cat(b), M(M_), R(R_), Rpad(Rpad_), n(lane & 15), g(lane >> 4), N(N_), n0(row0), t_sum(make_buffer(p.t_sum, (uint64_t)M_ * Rpad_ * 2)) {}
+    __device__ __forceinline__ void load_b(int rs) {
+        const int64_t n_c = n0 + n < N ? n0 + n : N - 1;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {   // ranks past R meet the zero padding of T
+            const int r = rs * 32 + 8 * g + j;
+            e[j] = (uint32_t)b_cat[(int64_t)(r < R ? r : R - 1) * N + n_c];
+        }
+    }
+    __device__ __forceinline__ void load_t(int rs) {
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) {
+            const int m = 16 * mt + n;
+            tq[mt] = shared_load4(t_sum, (uint32_t)((m < M ? m : M - 1) * Rpad + rs * 32 + 8 * g) * 2);
+        }
+    }
+    // B_cat and T of the first rank step have been asked for
+    __device__ __forceinline__ void add(f32x4 (&acc)[MT]) {
+        for (int rs = 0; rs < (Rpad >> 5); ++rs) {
+            if (rs > 0) {
+                load_b(rs);
+                load_t(rs);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            const uint4 bq = make_uint4(e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16), e[6] | (e[7] << 16));
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+                acc[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(bq), __builtin_bit_cast(bf16x8, tq[mt]), acc[mt], 0, 0, 0);
+        }
+    }
+};
+
+// A wave's sums of X What^T in memory, for the case that T comes after them: element (m, column) as in a slice's partial outputs
+template <int MT>
+__device__ __forceinline__ void rowtile_sums(const RowtileArgs& p, int64_t n0, int M, int lane, bool store, f32x4 (&acc)[MT]) {
+    const Buffer partial = make_buffer(p.partial, (uint64_t)M * p.pitch * 4);
+    const int n = lane & 15;
+    const int64_t col = n0 + 4 * (lane >> 4);
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+        const int m = 16 * mt + n;
+        const uint32_t at = m < M && col < p.pitch ? (uint32_t)(m * p.pitch + col) * 4 : kPastBuffer;   // (stores past the buffer are dropped)
+        if (store) shared_store4(partial, at, __builtin_bit_cast(u32x4, acc[mt]));
+        else acc[mt] = __builtin_bit_cast(f32x4, shared_load4(partial, at));
+    }
+}
+
+template <int MT>
+__device__ __forceinline__ void rowtile_store(uint16_t* __restrict__ y, int64_t n0, int M, int64_t N, int lane, const f32x4 (&acc)[MT]) {
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+        if (16 * mt + (lane & 15) < M) store_four(y, M, N, 16 * mt + (lane & 15), n0 + 4 * (lane >> 4), acc[mt]);
+}
+
+// T's workgroups have met, this one came last: T from its partial sums, then T's side of every wave's pair.  Waves that came before T
+// have left their sums to it.
+template <int MT, int kGroups>
+__device__ __forceinline__ void rowtile_hand_out_t(const RowtileArgs& p, int M, int64_t N, const uint16_t* __restrict__ b_cat, int R, int Rpad,
+                                                   uint16_t* __restrict__ y, int tid) {
+    const int groups = M * (Rpad >> 2);
+    const Buffer parts = make_buffer(p.t_out, (uint64_t)p.t_slices * groups * 16), t_sum = make_buffer(p.t_sum, (uint64_t)groups * 8);
+    for (int i = tid; i < groups; i += kRtThreads) {
+        f32x4 v[kRowtileTSlices], sum = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int sl = 0; sl < kRowtileTSlices; ++sl)
+            v[sl] = __builtin_bit_cast(f32x4, shared_load4(parts, 16u * (uint32_t)((sl < p.t_slices ? sl : 0) * groups + i)));
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int sl = 0; sl < kRowtileTSlices; ++sl)
+            if (sl < p.t_slices) sum += v[sl];
+        shared_store2(t_sum, 8u * (uint32_t)i, u32x2{(uint32_t)f32_to_bf16_rne(sum[0]) | ((uint32_t)f32_to_bf16_rne(sum[1]) << 16),
+                                                     (uint32_t)f32_to_bf16_rne(sum[2]) | ((uint32_t)f32_to_bf16_rne(sum[3]) << 16)});
+    }
+    stores_done();
+    __syncthreads();
+    const int lane = tid & 63, pairs = p.tiles * kGroups;
+    for (int base = __builtin_amdgcn_readfirstlane(tid & ~63); base < pairs; base += kRtThreads) {
+        const bool second = base + lane < pairs && meet(p.words + base + lane, p.tag);
+        for (uint64_t left = __builtin_amdgcn_ballot_w64(second); left != 0; left &= left - 1) {   // uniform
+            const int64_t n0 = (int64_t)(base + __builtin_ctzll(left)) * 16;
+            RowtileAdapters<MT> adapters(p, n0, M, N, b_cat, R, Rpad, lane);
+            f32x4 acc[MT];
+            rowtile_sums<MT>(p, n0, M, lane, false, acc);
+            adapters.load_b(0);
+            adapters.load_t(0);
+            adapters.add(acc);
+            rowtile_store<MT>(y, n0, M, N, lane, acc);
+        }
+    }
+}
+
 // MT tiles of sixteen rows of X (M <= 16 MT).  kRagged: K is no multiple of 128.
+// Q: the waves of a workgroup share 128 / Q rows, each sixteen of them on one of Q parts of the slice of K, and are added up through LDS.
+// kOneLaunch: the only slice, which adds the adapters where p.words is set.
 // kCodes: the packed values as 4-bit codes and block scales (`values` points at the codes).
-template <int MT, bool kRagged, bool kCodes>
+template <int MT, bool kRagged, bool kCodes, int Q, bool kOneLaunch>
 __global__ __launch_bounds__(kRtThreads, 2) void linear_rowtile_kernel(
     const uint16_t* __restrict__ x, int M, int64_t K, int64_t N, const uint32_t* __restrict__ bitmap,
     const void* __restrict__ values, const uint16_t* __restrict__ scales, const uint32_t* __restrict__ row_offsets,
     const uint32_t* __restrict__ slice_table, const uint16_t* __restrict__ a_cat, const uint16_t* __restrict__ b_cat, int R, int Rpad,
     uint16_t* __restrict__ y, RowtileArgs p) {
     constexpr int kTileBytes = 16 * MT * kChunkColumns * 2;           // X of one chunk
-    constexpr int kPanel = 16 / MT;                                   // chunks of X in LDS
-    constexpr int kPanelBytes = kPanel * kTileBytes;                  // 64 KB
+    constexpr int kGroups = kRtWaves / Q;                             // of sixteen rows
+    constexpr int kPartPanel = 16 / MT / Q;                           // chunks of X in LDS, of each part
+    constexpr int kPanelBytes = Q * kPartPanel * kTileBytes;          // 64 KB
     constexpr bool kPairs = MT <= 4;                                  // units of two chunks (else there are no registers for them)
     // vectors of a half's piece that starts anywhere in its first one: 128 or 64 values by 8, or codes by 32
     constexpr int kVectors = kCodes ? (kPairs ? 5 : 3) : (kPairs ? 17 : 9), kSlotBytes = slot_bytes(kCodes ? 4 * kVectors : kVectors + 1);
@@ -123,6 +242,13 @@ __global__ __launch_bounds__(kRtThreads, 2) void linear_rowtile_kernel(
     const int tid = threadIdx.x;
     if ((int)blockIdx.x < p.t_blocks) {   // the same for the whole workgroup
         adapter_partial_block<kRtWaves>(x, M, K, a_cat, R, Rpad, (int)blockIdx.x, p.t_slices, p.t_out, reinterpret_cast<float*>(lds), tid);
+        if (!kOneLaunch || p.words == nullptr) return;
+        stores_done();
+        __syncthreads();   // (the sums in LDS have been read, too)
+        int* last = reinterpret_cast<int*>(lds);
+        if (tid == 0) *last = knockout(p.words + (int64_t)p.tiles * kGroups, (int)blockIdx.x, p.t_blocks, p.tag);
+        __syncthreads();
+        if (*last != 0) rowtile_hand_out_t<MT, kGroups>(p, M, N, b_cat, R, Rpad, y, tid);
         return;
     }
     const int lane = tid & 63;
@@ -131,11 +257,15 @@ __global__ __launch_bounds__(kRtThreads, 2) void linear_rowtile_kernel(
     const int g = lane >> 4;
     const int id = (int)blockIdx.x - p.t_blocks;
     const int z = id / p.tiles, tile = id - z * p.tiles;
-    const int64_t n0 = ((int64_t)tile * kRtWaves + wave) * 16;
+    const int part = wave / kGroups;
+    const int64_t n0 = ((int64_t)tile * kGroups + wave % kGroups) * 16;
     const int64_t n0_c = n0 < N ? n0 : N;
     const int row_bytes = (int)(K >> 3);     // of the bitmap
     const int chunks = (int)((K + kChunkColumns - 1) / kChunkColumns);
-    const int c_begin = (int)((uint32_t)(chunks * z) / (uint32_t)p.ksplit), c_end = (int)((uint32_t)(chunks * (z + 1)) / (uint32_t)p.ksplit);
+    const int part_of_all = z * Q + part;
+    const int c_begin = (int)((uint32_t)(chunks * part_of_all) / (uint32_t)(p.ksplit * Q));
+    const int c_end = (int)((uint32_t)(chunks * (part_of_all + 1)) / (uint32_t)(p.ksplit * Q));
+    const int length_of_all = (chunks + p.ksplit * Q - 1) / (p.ksplit * Q);   // the longest part's: every wave goes through as many
 
     // ---- the wave's rows of the weight; rows past N read as empty
     const Buffer bits = make_buffer(bitmap + n0_c * (K >> 5), (uint64_t)(N - n0_c) * row_bytes);
@@ -187,19 +317,20 @@ __global__ __launch_bounds__(kRtThreads, 2) void linear_rowtile_kernel(
     walk(walk_begin);
     u32x4 quad_next = load_quad(c_begin + 4);
 
-    // ---- X: every thread moves eight 16-byte units of a panel
-    constexpr int kXPer = kPanelBytes / 16 / kRtThreads;
+    // ---- X: the waves of a part move its chunks of a panel
+    constexpr int kXRows = 4 * kGroups, kXPer = kPartPanel * 16 * MT / kXRows;   // rows at a time, 16-byte units of a thread
     const Buffer xbuf = make_buffer(x, (uint64_t)M * K * 2);
     const uint32_t lds0 = lds_address(lds), lut = lds0, xs0 = lds0 + 256;
-    const int xv = tid % 16, xr = tid / 16;   // unit j of the thread is vector xv of row (xr + 32 j) % (16 MT) of tile (xr + 32 j) / (16 MT)
+    const int xv = tid & 15, xr = (tid & (16 * kXRows - 1)) >> 4;   // unit j of the thread is vector xv of row (xr + kXRows j) % (16 MT) of chunk (xr + kXRows j) / (16 MT)
     // Vector v of a row at place p(v) ^ (row % 16), p the order in which a unit's steps read them: the operand reads of a wave then
     // meet every bank equally.
     const uint32_t xplace = kPairs ? xv : ((xv & 6) << 1) | ((xv & 1) << 1) | (xv >> 3);
     u32x4 xring[kXPer];
-    auto load_x = [&](int c) {   // the panel that starts at chunk c
+    const uint32_t x_part = xs0 + (uint32_t)part * kPartPanel * kTileBytes;
+    auto load_x = [&](int i) {   // the panel that starts i chunks on
 #pragma unroll
         for (int j = 0; j < kXPer; ++j) {
-            const int t = (xr + 32 * j) / (16 * MT), r = (xr + 32 * j) % (16 * MT), ct = c + t, start = chunk_start(ct);
+            const int t = (xr + kXRows * j) / (16 * MT), r = (xr + kXRows * j) % (16 * MT), ct = c_begin + i + t, start = chunk_start(ct);
             bool in = r < M && ct < c_end;
             if (kRagged) in = in && 8 * xv >= ct * kChunkColumns - start;
             xring[j] = buffer_load4(xbuf, in ? ((uint32_t)r * (uint32_t)K + start + 8 * xv) * 2 : kPastBuffer);
@@ -207,9 +338,9 @@ __global__ __launch_bounds__(kRtThreads, 2) void linear_rowtile_kernel(
     };
     auto store_x = [&]() {
 #pragma unroll
-        for (int j = 0; j < kXPer; ++j) lds_write(xs0 + (xr + 32 * j) * 256 + 16 * (xplace ^ (xr & 15)), xring[j]);
+        for (int j = 0; j < kXPer; ++j) lds_write(x_part + (xr + kXRows * j) * 256 + 16 * (xplace ^ ((xr + kXRows * j) & 15)), xring[j]);
     };
-    load_x(c_begin);
+    load_x(0);
 
     if (tid < 16) {
         uint32_t a, b;
@@ -349,25 +480,30 @@ __global__ __launch_bounds__(kRtThreads, 2) void linear_rowtile_kernel(
         return l;
     };
     // LDS place of the lane's X vector of step 0 in the unit's first tile (the other steps' differ in two or three bits)
-    const uint32_t x_lane = xs0 + n * 256 + (kPairs ? h * kTileBytes + 16 * (gh ^ n) : 16 * ((2 * gh + h) ^ n));
+    const uint32_t x_lane = x_part + n * 256 + (kPairs ? h * kTileBytes + 16 * (gh ^ n) : 16 * ((2 * gh + h) ^ n));
     Stage st;
     spread(quad, words);
     quad = quad_next;
     issue(st, length(words[0]));
-    for (int c0 = c_begin; c0 < c_end; c0 += kPanel < 4 ? 4 : kPanel) {
-        if (c0 > c_begin) __syncthreads();   // the panel before has been read by all waves
+    // Whether T is there and what of B_cat it meets: asked for before the last unit is multiplied.
+    RowtileAdapters<MT> adapters(p, n0, M, N, b_cat, R, Rpad, lane);
+    uint64_t* pair = p.words + (int64_t)tile * kGroups + wave % kGroups;
+    uint64_t pair_word = 0;
+    constexpr int kTurn = kPartPanel < 4 ? 4 : kPartPanel;
+    for (int i0 = 0; i0 < length_of_all; i0 += kTurn) {
+        if (i0 > 0) __syncthreads();   // the panel before has been read by all waves
         store_x();
-        if (kPanel < 4 || c0 + kPanel < c_end) load_x(c0 + kPanel);   // (past the slice: zeros)
+        if (kPartPanel < 4 || i0 + kPartPanel < length_of_all) load_x(i0 + kPartPanel);   // (past the slice: zeros)
         __syncthreads();
 #pragma unroll 1
-        for (int c = c0; c < c_end && c < c0 + (kPanel < 4 ? 4 : kPanel); c += 4) {
+        for (int i = i0; i < length_of_all && i < i0 + kTurn; i += 4) {
 #pragma unroll
             for (int u = 0; u < kUnits; ++u) {
-                if (u > 0 && c + u * kUnitChunks >= c_end) break;   // uniform
-                if (kPanel < 4 && u > 0 && u * kUnitChunks % kPanel == 0) {   // (a round is more than one panel)
+                if (u > 0 && i + u * kUnitChunks >= length_of_all) break;   // uniform
+                if (kPartPanel < 4 && u > 0 && u * kUnitChunks % kPartPanel == 0) {   // (a round is more than one panel)
                     __syncthreads();
                     store_x();
-                    load_x(c + u * kUnitChunks + kPanel);
+                    load_x(i + u * kUnitChunks + kPartPanel);
                     __syncthreads();
                 }
                 const uint32_t start = st.at % kPerVector;
@@ -375,20 +511,37 @@ __global__ __launch_bounds__(kRtThreads, 2) void linear_rowtile_kernel(
                 if (u + 1 < kUnits) issue(st, length(words[u + 1]));
                 else {
                     spread(quad, words_next);
-                    quad = load_quad(c + 8);
-                    if (c + 4 < c_end) issue(st, length(words_next[0]));   // uniform
+                    quad = load_quad(c_begin + i + 8);
+                    if (i + 4 < length_of_all) issue(st, length(words_next[0]));   // uniform
                 }
-                expand(words[u], start, x_lane + (c - c0 + u * kUnitChunks) % kPanel * kTileBytes);
+                if (i + (u + 1) * kUnitChunks >= length_of_all && kOneLaunch && p.words != nullptr) {   // uniform
+                    pair_word = look_at(pair);
+                    adapters.load_b(0);
+                }
+                expand(words[u], start, x_lane + (i - i0 + u * kUnitChunks) % kPartPanel * kTileBytes);
             }
 #pragma unroll
             for (int u = 0; u < kUnits; ++u)
 #pragma unroll
-                for (int i = 0; i < U; ++i) words[u][i] = words_next[u][i];
+                for (int j = 0; j < U; ++j) words[u][j] = words_next[u][j];
         }
+    }
+    if constexpr (Q > 1) {   // the parts' sums, in order
+        __syncthreads();     // the X panel is retired
+        const uint32_t place = xs0 + (uint32_t)(wave % kGroups) * MT * 1024 + 16 * lane;
+        if (part > 0)
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) lds_write(place + (part - 1) * kGroups * MT * 1024 + 1024 * mt, acc[mt]);
+        __syncthreads();
+        if (part > 0) return;
+#pragma unroll
+        for (int q = 0; q + 1 < Q; ++q)
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) acc[mt] += lds_read<f32x4>(place + q * kGroups * MT * 1024 + 1024 * mt);
     }
 
     // ---- adapters from an earlier launch's T (slice 0)
-    if (p.t_in != nullptr && z == 0) {
+    if (!kOneLaunch && p.t_in != nullptr && z == 0) {
         __syncthreads();   // the X panel is retired
         uint16_t* t_lds = reinterpret_cast<uint16_t*>(lds + 256);   // [M][Rpad]
         const int groups = M * (Rpad >> 2);
@@ -425,15 +578,34 @@ __global__ __launch_bounds__(kRtThreads, 2) void linear_rowtile_kernel(
 
     // ---- store: lane holds row 16 mt + lane % 16 of Y, columns n0 + 4 g .. + 3
     const int64_t col = n0 + 4 * g;
+    if (kOneLaunch && p.words != nullptr) {
+        bool t_there = __builtin_amdgcn_ballot_w64(pair_word == p.tag) != 0;   // (the same in all lanes)
+        if (t_there) {
+            if (lane == 0) leave_clear(pair);
+        } else {
+            // T is formed within the first 6 to 12 us of the launch.  Where it is not there yet, it soon will be, and its last
+            // workgroup would have all rows to finish: wait a little, but not without end.
+            rowtile_sums<MT>(p, n0, M, lane, true, acc);
+            stores_done();
+            if (lane == 0) {
+                for (int i = 0; i < p.polls && look_at(pair) != p.tag; ++i) __builtin_amdgcn_s_sleep(1);
+                t_there = meet(pair, p.tag);
+            }
+            if (__builtin_amdgcn_ballot_w64(t_there) == 0) return;
+        }
+        adapters.load_t(0);
+        adapters.add(acc);
+        rowtile_store<MT>(y, n0, M, N, lane, acc);
+        return;
+    }
+    if (p.partial == nullptr) {
+        rowtile_store<MT>(y, n0, M, N, lane, acc);
+        return;
+    }
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
         const int m = 16 * mt + n;
-        if (m >= M) continue;
-        if (p.partial != nullptr) {
-            if (col < p.pitch) *reinterpret_cast<f32x4*>(p.partial + ((int64_t)z * M + m) * p.pitch + col) = acc[mt];
-        } else {
-            store_four(y, M, N, m, col, acc[mt]);
-        }
+        if (m < M && col < p.pitch) *reinterpret_cast<f32x4*>(p.partial + ((int64_t)z * M + m) * p.pitch + col) = acc[mt];
     }
 }
 
@@ -536,9 +708,8 @@ __global__ __launch_bounds__(256, kBatch == 4 ? 8 : 4) void rowtile_finish_kerne
     store_four(y, M, N, m, col, acc);
 }
 
-template <int MT>
+template <int MT, int Q, bool kOne>
 static void launch_rowtile_t(const LinearArgs& a, RowtileArgs p, hipStream_t stream, const TimingEvents& ev) {
-    p.tiles = (int)((a.N + 16 * kRtWaves - 1) / (16 * kRtWaves));
     const dim3 grid((unsigned)(p.t_blocks + p.tiles * p.ksplit));
     const int R = (int)a.R, Rpad = (int)adapter_rank_padded(a.R);
     const bool ragged = a.K % kChunkColumns != 0;
@@ -546,9 +717,15 @@ static void launch_rowtile_t(const LinearArgs& a, RowtileArgs p, hipStream_t str
         SALR_LAUNCH(kernel, grid, dim3(kRtThreads), stream, ev, a.x, (int)a.M, a.K, a.N, a.bitmap, values, a.scales, a.row_offsets, a.slice_table,
                     a.a_cat, a.b_cat, R, Rpad, a.y, p);
     };
-    if (a.codes != nullptr) ragged ? go(linear_rowtile_kernel<MT, true, true>, a.codes) : go(linear_rowtile_kernel<MT, false, true>, a.codes);
-    else ragged ? go(linear_rowtile_kernel<MT, true, false>, a.values) : go(linear_rowtile_kernel<MT, false, false>, a.values);
+    if (a.codes != nullptr) ragged ? go(linear_rowtile_kernel<MT, true, true, Q, kOne>, a.codes) : go(linear_rowtile_kernel<MT, false, true, Q, kOne>, a.codes);
+    else ragged ? go(linear_rowtile_kernel<MT, true, false, Q, kOne>, a.values) : go(linear_rowtile_kernel<MT, false, false, Q, kOne>, a.values);
 }
+
+// How often the kernel looks for T at the end before it leaves its sums to it, a quarter of a microsecond each.  For tests: this host thread's
+// next calls, 0 to not wait at all.
+constexpr int kHandoverPolls = 64;
+static thread_local int g_handover_polls = kHandoverPolls;
+extern "C" void salr_set_handover_polls(int polls) { g_handover_polls = polls >= 0 && polls < kHandoverPolls ? polls : kHandoverPolls; }
 
 hipError_t launch_linear_rowtile(const LinearArgs& a, hipStream_t stream, const TimingEvents& ev) {
     char* base = reinterpret_cast<char*>(a.t);
@@ -564,11 +741,28 @@ hipError_t launch_linear_rowtile(const LinearArgs& a, hipStream_t stream, const 
     p.t_in = t_first ? p.t_out : nullptr;
     p.t_blocks = a.R > 0 && !t_first ? plan.t_slices * (Rpad / 16) * (int)((a.M + 15) / 16) : 0;
     if (t_first) launch_adapter_partial_to(a, p.t_out, stream);
-    if (a.M <= 16) launch_rowtile_t<1>(a, p, stream, ev);
-    else if (a.M <= 32) launch_rowtile_t<2>(a, p, stream, ev);
-    else if (a.M <= 64) launch_rowtile_t<4>(a, p, stream, ev);
-    else launch_rowtile_t<8>(a, p, stream, ev);
-    if (p.partial != nullptr)
+    const int rows = 16 * kRtWaves / plan.parts;
+    p.tiles = (int)((a.N + rows - 1) / rows);
+    p.words = nullptr;
+    p.t_sum = nullptr;
+    p.polls = g_handover_polls;
+    const size_t before = rowtile_t_out_bytes(a.M, a.R) + (size_t)plan.ksplit * rowtile_partial_bytes(a.M, a.N), t_sum_bytes = round_up_256((size_t)a.M * Rpad * 2);
+    if (plan.one_launch && a.room >= round_up_256(before) + rowtile_pair_bytes(a.M, a.N, a.R, plan)) {
+        p.t_sum = reinterpret_cast<uint16_t*>(base + round_up_256(before));
+        p.words = reinterpret_cast<uint64_t*>(base + round_up_256(before) + t_sum_bytes);
+        p.tag = next_handover_tag();
+    }
+    auto go = [&](auto mt) {
+        if (plan.parts == 2) launch_rowtile_t<mt, 2, true>(a, p, stream, ev);
+        else if (p.words != nullptr && plan.parts == 1) launch_rowtile_t<mt, 1, true>(a, p, stream, ev);
+        else if (plan.parts == 1) launch_rowtile_t<mt, 1, false>(a, p, stream, ev);
+        else if constexpr (mt <= 2) launch_rowtile_t<mt, 4, true>(a, p, stream, ev);
+    };
+    if (a.M <= 16) go(std::integral_constant<int, 1>());
+    else if (a.M <= 32) go(std::integral_constant<int, 2>());
+    else if (a.M <= 64) go(std::integral_constant<int, 4>());
+    else go(std::integral_constant<int, 8>());
+    if (p.partial != nullptr && p.words == nullptr)
         hipLaunchKernelGGL(plan.ksplit <= 4 ? rowtile_finish_kernel<4> : rowtile_finish_kernel<8>, dim3((unsigned)((a.N + 63) / 64), (unsigned)((a.M + 15) / 16)), dim3(256), 0, stream, p.partial,
                            plan.ksplit, (int)a.M, a.N, p.pitch, p.t_out, plan.t_slices, a.b_cat, (int)a.R, Rpad, a.y);
     return hipGetLastError();
