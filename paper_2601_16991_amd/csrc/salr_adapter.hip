@@ -4,6 +4,7 @@
 #include "salr_device.hpp"
 #include "salr_internal.hpp"
 #include "salr_linear_common.hpp"
+#include "salr_row_products.hpp"
 
 namespace salr {
 
@@ -190,156 +191,24 @@ void launch_adapter_transpose(const uint16_t* a_cat, int64_t K, int R, int Rpad,
                        Rpad, a_t);
 }
 
-// ---------------------------------------------------------------------------------------------------
-// Products that contract over the ROWS of a large row-major matrix (the adapter gradients of the backward pass,
-// dA = X^T T' and dB^T = dY^T T, in one launch): partial[z][c][r] = sum over the rows m of slice z of in[m][c] * s_t[r][m],
-// with in [M, C] bf16 and the small factor given transposed, s_t [Rpad, M].  The large matrix is read once, row-wise and
-// coalesced, and transposed on the way into the MFMA operand: no transposed copy of it in memory.
-//   workgroup (b, z): columns 64 b .. 64 b + 63 (wave w the 16 columns 16 w ..), row slice z (whole steps of 32 rows);
-//   kTnBatch steps at a time the 256 threads copy tiles [32 rows x 64 columns] into one half of the LDS buffers, the requests
-//   of the next batch in flight while this one is multiplied (a step is 4 KB, and what bounds the kernel is requests in
-//   flight: with one step ahead 2048 rows x 4096 columns took 8.2 us, 2 TB/s); the LDS' transposing read hands lane (i, g)
-//   in[8 g .. 8 g + 7][16 w + i] as the A operand of 16x16x32 bf16 MFMAs, the B operand s_t[16 rt + i][8 g ..] is a plain
-//   16-byte load; kRT rank tiles per pass over the slice.  Padding columns of Rpad come out as zeros (s_t is zero there).
-// M % 32 == 0, C % 8 == 0.
-// ---------------------------------------------------------------------------------------------------
-constexpr int kTnPitch = 64 + 8;   // bf16 elements per tile row
-constexpr int kTnBatch = 4;
-
 template <int kRT>
-__global__ __launch_bounds__(256, kRT <= 2 ? 4 : 2) void tall_tn_kernel(const uint16_t* __restrict__ in0, const uint16_t* __restrict__ s_t0, int64_t C0,
-                                                      const uint16_t* __restrict__ in1, const uint16_t* __restrict__ s_t1, int64_t C1,
-                                                      int64_t M, int Rpad, int ksplit, float* __restrict__ partial0) {
-    __shared__ __attribute__((aligned(16))) uint16_t tile[2][kTnBatch][32 * kTnPitch];
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int i16 = lane & 15, g = lane >> 4;
-    const int blocks0 = (int)((C0 + 63) / 64);
-    const bool first = (int)blockIdx.x < blocks0;   // the same for the whole workgroup
-    const uint16_t* in = first ? in0 : in1;
-    const uint16_t* s_t = first ? s_t0 : s_t1;
-    const int64_t C = first ? C0 : C1;
-    float* partial = partial0 + (first ? 0 : (int64_t)ksplit * C0 * Rpad);
-    const int64_t c0 = (int64_t)((int)blockIdx.x - (first ? 0 : blocks0)) * 64;
-    const int z = blockIdx.y;
-    const int64_t steps = M >> 5;
-    const int64_t s_begin = steps * z / ksplit, s_end = steps * (z + 1) / ksplit;   // never empty: ksplit <= steps
-    // this thread's 16 bytes of a tile: row tid / 8, columns 8 (tid % 8) ..; past C a vector of other columns (never stored)
-    const int trow = tid >> 3, tvec = tid & 7;
-    const int64_t cv = c0 + 8 * tvec + 8 <= C ? c0 + 8 * tvec : C - 8;
-    auto load_tile = [&](int64_t s) -> uint4 {   // past the slice: its last step again, not used
-        return *reinterpret_cast<const uint4*>(in + (((s < s_end ? s : s_end - 1) << 5) + trow) * C + cv);
-    };
-    for (int rb = 0; rb < Rpad; rb += 16 * kRT) {
-        f32x4 acc[kRT];
-#pragma unroll
-        for (int rt = 0; rt < kRT; ++rt) acc[rt] = f32x4{0.f, 0.f, 0.f, 0.f};
-        const uint16_t* srow[kRT];
-#pragma unroll
-        for (int rt = 0; rt < kRT; ++rt) {
-            const int r = rb + 16 * rt + i16;
-            srow[rt] = s_t + (int64_t)(r < Rpad ? r : Rpad - 1) * M + 8 * g;
-        }
-        uint4 next[kTnBatch];
-#pragma unroll
-        for (int d = 0; d < kTnBatch; ++d) next[d] = load_tile(s_begin + d);
-        int buf = 0;
-        for (int64_t s = s_begin; s < s_end; s += kTnBatch) {
-            uint4 bq[kTnBatch][kRT];
-#pragma unroll
-            for (int d = 0; d < kTnBatch; ++d) {
-                const int64_t sc = s + d < s_end ? s + d : s_end - 1;
-#pragma unroll
-                for (int rt = 0; rt < kRT; ++rt) bq[d][rt] = *reinterpret_cast<const uint4*>(srow[rt] + (sc << 5));
-            }
-#pragma unroll
-            for (int d = 0; d < kTnBatch; ++d) *reinterpret_cast<uint4*>(&tile[buf][d][trow * kTnPitch + 8 * tvec]) = next[d];
-            if (s + kTnBatch < s_end) {
-#pragma unroll
-                for (int d = 0; d < kTnBatch; ++d) next[d] = load_tile(s + kTnBatch + d);
-            }
-            __syncthreads();   // the tiles are complete; the buffers written two batches ago have been read by everyone
-#pragma unroll
-            for (int d = 0; d < kTnBatch; ++d) {
-                if (s + d < s_end) {   // the same for the whole workgroup
-                    const uint16_t* col = &tile[buf][d][(8 * g + (i16 >> 2)) * kTnPitch + 16 * wave + 4 * (i16 & 3)];
-                    const uint2 lo = lds_read_tr4(col), hi = lds_read_tr4(col + 4 * kTnPitch);
-                    const bf16x8 aq = as_bf16x8(make_uint4(lo.x, lo.y, hi.x, hi.y));
-#pragma unroll
-                    for (int rt = 0; rt < kRT; ++rt) acc[rt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aq, as_bf16x8(bq[d][rt]), acc[rt], 0, 0, 0);
-                }
-            }
-            buf ^= 1;
-        }
-        __syncthreads();   // before the next pass writes buffer 0 again
-        // accumulator layout of the 16x16 MFMA: lane holds column lane % 16 (rank), rows 4 (lane / 16) + e (matrix column)
-#pragma unroll
-        for (int rt = 0; rt < kRT; ++rt) {
-            const int r = rb + 16 * rt + i16;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int64_t c = c0 + 16 * wave + 4 * g + e;
-                if (c < C && r < Rpad) partial[((int64_t)z * C + c) * Rpad + r] = acc[rt][e];
-            }
-        }
-    }
+__global__ __launch_bounds__(256, kRT <= 2 ? 4 : 2) void tall_tn_kernel(RowProducts p) {
+    __shared__ __attribute__((aligned(16))) uint16_t lds[kTnLdsBytes / 2];
+    tall_tn_block<kRT>(p, (int)blockIdx.x, (int)blockIdx.y, lds);
 }
 
-// The sums over the slices of tall_tn_kernel, 32 matrix columns per workgroup: read along the ranks, as they lie, and through LDS
-// into out0 [C0, R] and out1 [R, C1] (read in the order of the outputs, dB's sums came one 128-byte line per value: 7.4 us a
-// gradient on 4096 columns of rank 32, 16 slices).
-constexpr int kRpCols = 32;
-
-__global__ __launch_bounds__(256) void row_products_reduce_kernel(const float* __restrict__ partial0, int64_t C0, int64_t C1, int Rpad,
-                                                                  int ksplit, int R, uint16_t* __restrict__ out0,
-                                                                  uint16_t* __restrict__ out1) {
-    __shared__ float sums[kRpCols][kMaxRankPadded + 1];
-    const int blocks0 = (int)((C0 + kRpCols - 1) / kRpCols);
-    const bool first = (int)blockIdx.x < blocks0;   // the same for the whole workgroup
-    const int64_t C = first ? C0 : C1;
-    const float* partial = partial0 + (first ? 0 : (int64_t)ksplit * C0 * Rpad);
-    const int64_t c0 = (int64_t)((int)blockIdx.x - (first ? 0 : blocks0)) * kRpCols;
-    const int cols = C - c0 < kRpCols ? (int)(C - c0) : kRpCols;
-    const int quads = Rpad >> 2;
-    for (int i = threadIdx.x; i < cols * quads; i += 256) {
-        const float* p = partial + c0 * Rpad + 4 * i;
-        float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
-        for (int z0 = 0; z0 < ksplit; z0 += 8) {
-            float4 q[8];
-#pragma unroll
-            for (int j = 0; j < 8; ++j)
-                if (z0 + j < ksplit) q[j] = *reinterpret_cast<const float4*>(p + (int64_t)(z0 + j) * C * Rpad);
-#pragma unroll
-            for (int j = 0; j < 8; ++j)
-                if (z0 + j < ksplit) { s.x += q[j].x; s.y += q[j].y; s.z += q[j].z; s.w += q[j].w; }
-        }
-        float* to = &sums[i / quads][4 * (i % quads)];
-        to[0] = s.x; to[1] = s.y; to[2] = s.z; to[3] = s.w;
-    }
-    __syncthreads();
-    if (first) {
-        for (int i = threadIdx.x; i < cols * R; i += 256) out0[c0 * R + i] = f32_to_bf16_rne(sums[i / R][i % R]);
-    } else {
-        for (int i = threadIdx.x; i < kRpCols * R; i += 256) {
-            const int c = i % kRpCols, r = i / kRpCols;
-            if (c < cols) out1[r * C + c0 + c] = f32_to_bf16_rne(sums[c][r]);
-        }
-    }
+__global__ __launch_bounds__(256) void row_products_reduce_kernel(RowProducts p) {
+    __shared__ __attribute__((aligned(16))) float sums[kRpCols * kRpPitch];
+    const int blocks0 = (int)((p.C[0] + kRpCols - 1) / kRpCols), job = (int)blockIdx.x < blocks0 ? 0 : 1;
+    row_products_sum<false>(p, job, (int64_t)((int)blockIdx.x - (job == 0 ? 0 : blocks0)) * kRpCols, sums);
 }
 
-void launch_row_products(const RowProductJob& da, const RowProductJob& db, int64_t M, int R, int ksplit, float* partial,
-                         hipStream_t stream) {
-    const int Rpad = (int)adapter_rank_padded(R);
-    const int64_t C0 = da.out != nullptr ? da.C : 0, C1 = db.out != nullptr ? db.C : 0;
-    const dim3 grid((unsigned)((C0 + 63) / 64 + (C1 + 63) / 64), (unsigned)ksplit);
-#define SALR_TN(RT) \
-    hipLaunchKernelGGL(tall_tn_kernel<RT>, grid, dim3(256), 0, stream, da.in, da.s_t, C0, db.in, db.s_t, C1, M, Rpad, ksplit, partial)
-    if (Rpad % 64 == 0) SALR_TN(4);
-    else SALR_TN(2);
-#undef SALR_TN
-    hipLaunchKernelGGL(row_products_reduce_kernel, dim3((unsigned)((C0 + kRpCols - 1) / kRpCols + (C1 + kRpCols - 1) / kRpCols)), dim3(256), 0,
-                       stream, partial, C0, C1, Rpad, ksplit, R, da.out, db.out);
+void launch_row_products(const RowProducts& p, hipStream_t stream) {
+    const dim3 grid((unsigned)(row_product_blocks(p.C[0]) + row_product_blocks(p.C[1])), (unsigned)p.ksplit);
+    if (p.Rpad % 64 == 0) hipLaunchKernelGGL(tall_tn_kernel<4>, grid, dim3(256), 0, stream, p);
+    else hipLaunchKernelGGL(tall_tn_kernel<2>, grid, dim3(256), 0, stream, p);
+    hipLaunchKernelGGL(row_products_reduce_kernel, dim3((unsigned)((p.C[0] + kRpCols - 1) / kRpCols + (p.C[1] + kRpCols - 1) / kRpCols)), dim3(256),
+                       0, stream, p);
 }
 
 // T' = dY B_cat^T and T = X A_cat of the backward pass in one launch (salr_adapter_t.hpp), sixteen waves per 16 or 32 rows and 32

@@ -3,12 +3,14 @@
 //     dX = dY What + (dY B_cat^T) A_cat^T        [M, K]
 //     dA = X^T (dY B_cat^T)                      [K, R]
 //     dB = (X A_cat)^T dY                        [R, N]
-// Four launches (five where the matrix stage splits its contraction; fewer where not all gradients are asked for):
+// Two launches (three where the matrix stage splits its contraction), or four:
 //     the transposed weight in MFMA operand order, A_cat's rank blocks behind it (decode_transposed_frags_kernel), and in the same
 //     launch's first workgroups T' = dY B_cat^T and T = X A_cat, both as they are [M, Rpad] and transposed (a launch of their own,
 //     backward_t_kernel, where the weight is not wanted, R is no multiple of 8 or the chains are long and many);
 //     dX: the large-batch matrix stage on dY and that weight, T' riding along as its adapter steps (salr_gemm.hip);
-//     dA, dB: products that contract over the rows of X and dY against T'^T and T^T (tall_tn_kernel) and their sums over slices.
+//     dA, dB: products that contract over the rows of X and dY against T'^T and T^T (salr_row_products.hpp), in workgroups beside the matrix
+//     stage's where those leave room on a CU and the stage is long enough (gradients_beside in salr_gemm.hip), or in a launch of their own
+//     and one that sums their slices.
 // As in the forward pass T and T' are rounded to bf16 once; sums are fp32; outputs bf16.  The sixteen slices of T and T' interleave
 // (every sixteenth step of 64 columns, whichever launch forms them), so a sum can differ from one over contiguous slices in its last
 // bits, and where it sits on a rounding boundary by one bf16 step: about 2e-4 of dA and dB in the 2-norm against such a sum;
@@ -21,7 +23,8 @@ namespace salr {
 
 struct BackwardPlan {
     int Rpad, ks_tn;
-    size_t off_wf, off_tp, off_tt, off_tp_t, off_tt_t, off_tn, off_ypart, y_room, total;
+    size_t off_wf, off_tp, off_tt, off_tp_t, off_tt_t, off_tn, off_words, off_ypart, y_room, total;
+    bool words;   // there is room for the gradients' slices to meet
 };
 
 // What the call tells its callers to bring: the sizes of two dense copies of the weight, row-padded factors, the intermediates in
@@ -58,6 +61,9 @@ static BackwardPlan backward_plan(int64_t M, int64_t K, int64_t N, int64_t R, bo
         p.off_tp_t = take(grads ? t_bytes : 0);
         p.off_tt_t = take(grads ? t_bytes : 0);
         p.off_tn = take(grads ? (size_t)p.ks_tn * (K + N) * p.Rpad * sizeof(float) : 0);
+        const size_t words = grads && want_dx ? (size_t)((K + 63) / 64 + (N + 63) / 64) * p.ks_tn * sizeof(uint64_t) : 0;
+        p.words = words > 0 && o + round_up_256(words) <= room;
+        p.off_words = take(p.words ? words : 0);
         p.off_ypart = o;
         if (o <= room || p.ks_tn == 1) break;
     }
@@ -92,17 +98,21 @@ hipError_t launch_linear_backward(const uint16_t* x, const uint16_t* dy, int64_t
     const bool short_chains = K <= 6144 && N <= 6144, few = M * (K + N) * ((p.Rpad + 31) / 32) <= 6 * N * K;
     const bool with_decode = want_dx && R % 8 == 0 && (short_chains || few);
     if (R > 0 && !with_decode) launch_backward_t(dy_b, x_a, M, R, stream);
+    RowProducts products{{x, dy}, {at(p.off_tp_t), at(p.off_tt_t)}, {da != nullptr ? K : 0, db != nullptr ? N : 0}, {da, db}, M, R, p.Rpad, p.ks_tn,
+                         reinterpret_cast<float*>(ws + p.off_tn), reinterpret_cast<uint64_t*>(ws + p.off_words), p.words ? next_handover_tag() : 0};
+    bool gradients_done = false;
     if (want_dx) {
         const hipError_t e = launch_decode_transposed_frags(bitmap, values, row_offsets, N, K, a_cat, R, at(p.off_wf), with_decode ? dy_b : none,
                                                             with_decode ? x_a : none, M, stream);
         if (e != hipSuccess) return e;
         const TimingEvents none;
-        launch_frag_gemm(dy, M, N, K, at(p.off_wf), at(p.off_tp), p.Rpad, dx, reinterpret_cast<float*>(ws + p.off_ypart), p.y_room, none,
-                         stream);
+        gradients_done = launch_frag_gemm(dy, M, N, K, at(p.off_wf), at(p.off_tp), p.Rpad, dx, reinterpret_cast<float*>(ws + p.off_ypart), p.y_room,
+                                          none, stream, p.words ? &products : nullptr);
     }
-    if (want_dadb && R > 0)
-        launch_row_products({x, at(p.off_tp_t), K, da}, {dy, at(p.off_tt_t), N, db}, M, R, p.ks_tn, reinterpret_cast<float*>(ws + p.off_tn),
-                            stream);
+    if (want_dadb && R > 0 && !gradients_done) {
+        products.words = nullptr;
+        launch_row_products(products, stream);
+    }
     return hipGetLastError();
 }
 

@@ -25,6 +25,7 @@
 #include "salr_internal.hpp"
 #include "salr_linear_common.hpp"
 #include "salr_nf4.hpp"
+#include "salr_row_products.hpp"
 
 namespace salr {
 
@@ -46,20 +47,25 @@ __device__ __forceinline__ void smfmac_in_place(f32x4& c, const bf16x8& a, const
     else asm("v_smfmac_f32_16x16x64_bf16 %0, %1, %2, %3 abid:1" : "+a"(c) : "v"(a), "v"(b), "v"(index));
 }
 
-template <int kMI, int kNI, int kWM, int kWN, int kStages, bool kPartial, bool kSparse = false>
-__global__ __launch_bounds__(64 * kWM * kWN, 1) void frag_gemm_kernel(
+// LDS of a workgroup: the ring of X tiles, then sixteen output rows per wave on their way out (see the store)
+template <int kMI, int kNI, int kWM, int kWN, int kStages, bool kPartial>
+constexpr int frag_gemm_lds_bytes() {
+    constexpr int kElem = kPartial ? 4 : 2, kOut = kWM * kWN * 16 * (16 * kNI + 32 / kElem) * kElem, kTiles = kStages * 16 * kMI * kWM * 128;
+    return kTiles > kOut ? kTiles : kOut;
+}
+
+template <int kMI, int kNI, int kWM, int kWN, int kStages, bool kPartial, bool kSparse>
+__device__ __forceinline__ void frag_gemm_block(
     const uint16_t* __restrict__ x, int64_t M, int64_t K, int64_t N, const uint16_t* wf,
     const uint16_t* __restrict__ t, int Rpad, uint16_t* __restrict__ y, int m_tiles, int n_tiles, int ksplit,
-    float* __restrict__ partial) {
+    float* __restrict__ partial, uint16_t* Xs) {
     constexpr int kWaves = kWM * kWN;
     constexpr int kMT = 16 * kMI * kWM, kNT = 16 * kNI * kWN;
     constexpr int kXLoads = kMT / (8 * kWaves);   // LDS loads per wave and k-step, eight rows each
     static_assert(kMT % (8 * kWaves) == 0 && kNT % 32 == 0, "tile/wave shape");
     typedef typename std::conditional<kPartial, float, uint16_t>::type out_t;
-    // sixteen output rows per wave on their way out (see the store)
-    constexpr int kCols = 16 * kNI, kVec = 16 / sizeof(out_t), kPitch = kCols + 2 * kVec, kOutBytes = kWaves * 16 * kPitch * sizeof(out_t);
-    constexpr int kTileBytes = kStages * kMT * 128;
-    __shared__ __attribute__((aligned(16))) uint16_t Xs[(kTileBytes > kOutBytes ? kTileBytes : kOutBytes) / 2];
+    constexpr int kCols = 16 * kNI, kVec = 16 / sizeof(out_t), kPitch = kCols + 2 * kVec;
+    static_assert(frag_gemm_lds_bytes<kMI, kNI, kWM, kWN, kStages, kPartial>() >= kWaves * 16 * kPitch * (int)sizeof(out_t), "room for the results");
 
     // Consecutive workgroup ids land on different XCDs, each with an L2 of its own: XCD c takes the c-th eighth of the work,
     // ordered so that workgroups running side by side on it share operands: K slice, then blocks of eight m-tiles, then n,
@@ -359,6 +365,33 @@ __global__ __launch_bounds__(64 * kWM * kWN, 1) void frag_gemm_kernel(
     }
 }
 
+template <int kMI, int kNI, int kWM, int kWN, int kStages, bool kPartial, bool kSparse = false>
+__global__ __launch_bounds__(64 * kWM * kWN, 1) void frag_gemm_kernel(
+    const uint16_t* __restrict__ x, int64_t M, int64_t K, int64_t N, const uint16_t* wf,
+    const uint16_t* __restrict__ t, int Rpad, uint16_t* __restrict__ y, int m_tiles, int n_tiles, int ksplit,
+    float* __restrict__ partial) {
+    __shared__ __attribute__((aligned(16))) uint16_t lds[frag_gemm_lds_bytes<kMI, kNI, kWM, kWN, kStages, kPartial>() / 2];
+    frag_gemm_block<kMI, kNI, kWM, kWN, kStages, kPartial, kSparse>(x, M, K, N, wf, t, Rpad, y, m_tiles, n_tiles, ksplit, partial, lds);
+}
+
+// The same with the adapter gradients of a backward pass beside it (salr_row_products.hpp), on tiles of which two workgroups fit a CU: workgroups
+// behind the stage's `gemm_blocks`, so that they take what room the CUs have left.  The stage keeps the matrix cores busy and those stream X and dY.
+// 2048 x 4096 x 4096 rank 32: 99.4 us a step with two launches behind the stage (12.5 and 4.9 us), 89.4 so.
+template <int kMI, int kNI, bool kPartial, int kRT>
+__global__ __launch_bounds__(256, 2) void frag_gemm_gradients_kernel(
+    const uint16_t* __restrict__ x, int64_t M, int64_t K, int64_t N, const uint16_t* wf,
+    const uint16_t* __restrict__ t, int Rpad, uint16_t* __restrict__ y, int m_tiles, int n_tiles, int ksplit,
+    float* __restrict__ partial, int gemm_blocks, RowProducts products) {
+    constexpr int kBytes = frag_gemm_lds_bytes<kMI, kNI, 2, 2, 3, kPartial>();
+    __shared__ __attribute__((aligned(16))) uint16_t lds[(kBytes > kTnLdsBytes ? kBytes : kTnLdsBytes) / 2];
+    if ((int)blockIdx.x < gemm_blocks) {   // the same for the whole workgroup
+        frag_gemm_block<kMI, kNI, 2, 2, 3, kPartial, false>(x, M, K, N, wf, t, Rpad, y, m_tiles, n_tiles, ksplit, partial, lds);
+        return;
+    }
+    const int id = (int)blockIdx.x - gemm_blocks, blocks = row_product_blocks(products.C[0]) + row_product_blocks(products.C[1]);
+    tall_tn_block<kRT>(products, id % blocks, id / blocks, lds);
+}
+
 static unsigned gemm_grid(int workgroups) { return (unsigned)((workgroups + kGemmXcds - 1) / kGemmXcds * kGemmXcds); }
 
 // A_cat^T in operand order: block (f, kb) = ranks 16 f .. 16 f + 15 (rows past R as zeros) x columns 32 kb .. + 31; an even
@@ -599,11 +632,53 @@ hipError_t launch_decode_frags(const LinearArgs& a, uint16_t* wf, uint16_t* af, 
     return hipGetLastError();
 }
 
-void launch_frag_gemm(const uint16_t* x, int64_t M, int64_t K, int64_t N, const uint16_t* wf, const uint16_t* t, int Rpad,
-                      uint16_t* y, float* partial, size_t partial_room, const TimingEvents& ev, hipStream_t stream) {
+// Slices of the rows at most where the gradients are beside the stage: whoever sums them reads them all.  (With the 32 of a launch of their
+// own 2272 x 1216 x 640 at rank 32 went 33 -> 41 us; with eight 29.)
+constexpr int kBesideSlices = 8;
+// Whether they are: where the stage is long enough to hide them, by what they read at 3 TB/s and what the stage multiplies at 1100 TFLOP/s, and
+// up to 96 ranks, from where on their workgroups' passes are several.  Of 200 drawn steps (128 to 4096 tokens, ranks 8 to 96) one is 1 %
+// slower so, the geometric mean 1.13 faster; at rank 128 0.86 (448 x 5248 x 640) to 1.10 (608 x 2688 x 13440).
+static bool gradients_beside(int64_t M, int64_t K, int64_t N, const RowProducts& p) {
+    const double gradients = (double)M * (double)(p.C[0] + p.C[1]) * 2.0 * (p.Rpad / 32) / 3e6, stage = 2.0 * (double)M * (double)N * (double)K / 1.1e9;
+    return p.Rpad <= 96 && (gradients < 20.0 || gradients < 0.85 * stage);
+}
+
+bool launch_frag_gemm(const uint16_t* x, int64_t M, int64_t K, int64_t N, const uint16_t* wf, const uint16_t* t, int Rpad,
+                      uint16_t* y, float* partial, size_t partial_room, const TimingEvents& ev, hipStream_t stream, const RowProducts* beside) {
     const GemmPlan p = gemm_plan(M, K + Rpad, N, partial_room);
     const int m_tiles = (int)((M + p.mt - 1) / p.mt), n_tiles = (int)((N + p.nt - 1) / p.nt);
     const dim3 grid(gemm_grid(m_tiles * n_tiles * p.ksplit));
+    // (mt, nt: two of the stage's workgroups fit a CU up to 128 x 256; four rank tiles a pass have the registers up to 128 x 128)
+    const bool four = Rpad % 64 == 0 && p.mt * p.nt <= 128 * 128;
+    if (beside != nullptr && p.mt <= 128 && gradients_beside(M, K, N, *beside)) {
+        RowProducts products = *beside;
+        if (products.ksplit > kBesideSlices) products.ksplit = kBesideSlices;
+        const int blocks = (row_product_blocks(products.C[0]) + row_product_blocks(products.C[1])) * products.ksplit;
+        const dim3 all(grid.x + (unsigned)blocks);
+#define SALR_TN_P(MI, NI, P, RT)                                                                                                                \
+    hipLaunchKernelGGL((frag_gemm_gradients_kernel<MI, NI, P, RT>), all, dim3(256), 0, stream, x, M, K, N, wf, t, Rpad, y, m_tiles, n_tiles, \
+                       p.ksplit, partial, (int)grid.x, products)
+#define SALR_TN(MI, NI, RT)                          \
+    do {                                             \
+        if (p.ksplit > 1) SALR_TN_P(MI, NI, true, RT); \
+        else SALR_TN_P(MI, NI, false, RT);           \
+    } while (0)
+#define SALR_TN24(MI, NI)           \
+    do {                            \
+        if (four) SALR_TN(MI, NI, 4); \
+        else SALR_TN(MI, NI, 2);    \
+    } while (0)
+        if (p.mt == 128 && p.nt == 256) SALR_TN(4, 8, 2);
+        else if (p.mt == 128) SALR_TN24(4, 4);
+        else if (p.nt == 256) SALR_TN24(2, 8);
+        else if (p.nt == 128) SALR_TN24(2, 4);
+        else SALR_TN24(2, 2);
+#undef SALR_TN24
+#undef SALR_TN
+#undef SALR_TN_P
+        if (p.ksplit > 1) launch_splitk_reduce(partial, M * N, p.ksplit, y, stream);
+        return true;
+    }
 #define SALR_GEMM_P(MI, NI, P)                                                                                                     \
     SALR_LAUNCH((frag_gemm_kernel<MI, NI, 2, 2, 3, P>), grid, dim3(256), stream, ev, x, M, K, N, wf, t, Rpad, y, m_tiles, n_tiles, \
                 p.ksplit, partial)
@@ -622,6 +697,7 @@ void launch_frag_gemm(const uint16_t* x, int64_t M, int64_t K, int64_t N, const 
 #undef SALR_GEMM
 #undef SALR_GEMM_P
     if (p.ksplit > 1) launch_splitk_reduce(partial, M * N, p.ksplit, y, stream);
+    return false;
 }
 
 // T = X * A_cat straight to bf16 [M, Rpad] in one launch (more than kAdapterSmallM rows): sixteen waves per 32 rows and 32 ranks.
@@ -671,7 +747,7 @@ hipError_t launch_linear_frag(const LinearArgs& a, hipStream_t stream, const Tim
                                  reinterpret_cast<float*>(af + adapter_frag_bytes(a.K, a.R)), stream);
     const size_t base = frag_base_bytes(a.M, a.K, a.N, a.R);
     float* partial = reinterpret_cast<float*>(reinterpret_cast<char*>(a.t) + base);
-    launch_frag_gemm(a.x, a.M, a.K, a.N, wf, a.t, Rpad, a.y, partial, a.room - base, ev, stream);
+    launch_frag_gemm(a.x, a.M, a.K, a.N, wf, a.t, Rpad, a.y, partial, a.room - base, ev, stream, nullptr);
     return hipGetLastError();
 }
 

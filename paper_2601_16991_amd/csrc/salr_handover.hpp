@@ -12,8 +12,9 @@
 //            launch in front).  Whoever finds the tag clears the word: a captured launch, whose tag is the same on every
 //            replay, starts from clear words.
 //   knockout of many: in pairs, the one that finds the tag goes on to the next round.
-// Sums of a split contraction handed over so were no faster than a launch that adds them up: under load a store's acknowledgement,
-// an exchange and a load are 1 us each, one after the other (16 x 4096 x 14336, two slices: 23.2 us against 23.9).
+// At the end of a launch sums of a split contraction handed over so were no faster than a launch that adds them up: under load a store's
+// acknowledgement, an exchange and a load are 1 us each, one after the other (16 x 4096 x 14336, two slices: 23.2 us against 23.9).
+// Beside something longer they cost nothing (the backward pass's gradients).
 #pragma once
 
 #include "salr_device.hpp"
@@ -27,6 +28,13 @@ __device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)
 
 __device__ __forceinline__ u32x4 shared_load4(Buffer b, uint32_t offset) {
     return __builtin_amdgcn_raw_buffer_load_b128(b, (int)offset, 0, kAgentScope);
+}
+__device__ __forceinline__ u32x4 shared_load4(const void* p) {   // (where 32-bit offsets do not reach)
+    u32x4 v;
+    const uint64_t* q = static_cast<const uint64_t*>(p);
+    const uint64_t lo = __hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), hi = __hip_atomic_load(q + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    v[0] = (uint32_t)lo; v[1] = (uint32_t)(lo >> 32); v[2] = (uint32_t)hi; v[3] = (uint32_t)(hi >> 32);
+    return v;
 }
 __device__ __forceinline__ void shared_store4(Buffer b, uint32_t offset, u32x4 v) {
     __builtin_amdgcn_raw_buffer_store_b128(v, b, (int)offset, 0, kAgentScope);

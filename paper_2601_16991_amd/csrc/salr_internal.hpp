@@ -670,14 +670,19 @@ hipError_t launch_decode_transposed_frags(const uint32_t* bitmap, const uint16_t
                                           int64_t cols, const uint16_t* a_cat, int R, uint16_t* wf, const LowRankJob& dy_b,
                                           const LowRankJob& x_a, int64_t M, hipStream_t stream);
 // Products that contract over the rows of in [M, C] (M % 32 == 0) against s_t [Rpad, M]: the adapter gradients, bf16, job 0 to
-// out [C, R], job 1 to out [R, C].  A job whose `out` is null is left out.  partial: room for ksplit fp32 slices
+// out [C, R], job 1 to out [R, C].  A job that is not wanted has C = 0.  partial: room for ksplit fp32 slices
 // [C, Rpad] of each job; tn_ksplit picks the split of M (about four workgroups per CU over both jobs, at least two
-// steps of 32 rows each).
-struct RowProductJob {
-    const uint16_t* in;
-    const uint16_t* s_t;
-    int64_t C;
-    uint16_t* out;
+// steps of 32 rows each).  words: ksplit per 64 columns of each job, for slices that are summed in the launch that forms them, or null.
+struct RowProducts {
+    const uint16_t* in[2];
+    const uint16_t* s_t[2];
+    int64_t C[2];
+    uint16_t* out[2];
+    int64_t M;
+    int R, Rpad, ksplit;
+    float* partial;
+    uint64_t* words;
+    uint64_t tag;
 };
 inline int tn_ksplit(int64_t C0, int64_t M, int64_t C1 = 0) {
     const int64_t blocks = (C0 + 63) / 64 + (C1 + 63) / 64, steps = M / 32;
@@ -685,8 +690,7 @@ inline int tn_ksplit(int64_t C0, int64_t M, int64_t C1 = 0) {
     while (s < 64 && blocks * s * 2 <= 1024 && steps / (s * 2) >= 2) s *= 2;
     return s;
 }
-void launch_row_products(const RowProductJob& da, const RowProductJob& db, int64_t M, int R, int ksplit, float* partial,
-                         hipStream_t stream);
+void launch_row_products(const RowProducts& products, hipStream_t stream);   // words == nullptr
 // x [M, K] bf16 times the transpose of a_t [Rpad, K] bf16 (Rpad % 32 == 0, K % 32 == 0), K split over `ksplit`
 // slices: bf16 t [M, Rpad] (one slice, !keep_fp32) or fp32 partial [ksplit, M, Rpad]; columns from `ranks` on as zeros
 void launch_tall_product(const uint16_t* x, int64_t M, int64_t K, const uint16_t* a_t, int Rpad, int ranks, int ksplit, uint16_t* t,
@@ -695,9 +699,10 @@ void launch_tall_product(const uint16_t* x, int64_t M, int64_t K, const uint16_t
 void launch_adapter_transpose(const uint16_t* a_cat, int64_t K, int R, int Rpad, uint16_t* a_t, hipStream_t stream);
 // out [C, R] = in [R, C]^T (bf16); R <= 65535 * 32
 void launch_transpose_bf16(const uint16_t* in, int64_t R, int64_t C, uint16_t* out, hipStream_t stream);
-// y [M, N] = x [M, K] * W^T (+ t [M, Rpad] * B_cat) with W and B_cat in operand order (salr_gemm.hip)
-void launch_frag_gemm(const uint16_t* x, int64_t M, int64_t K, int64_t N, const uint16_t* wf, const uint16_t* t, int Rpad,
-                      uint16_t* y, float* partial, size_t partial_room, const TimingEvents& ev, hipStream_t stream);
+// y [M, N] = x [M, K] * W^T (+ t [M, Rpad] * B_cat) with W and B_cat in operand order (salr_gemm.hip).  beside (or null; words set): products
+// to be formed in the same launch where two of its workgroups fit a CU; whether they were.
+bool launch_frag_gemm(const uint16_t* x, int64_t M, int64_t K, int64_t N, const uint16_t* wf, const uint16_t* t, int Rpad,
+                      uint16_t* y, float* partial, size_t partial_room, const TimingEvents& ev, hipStream_t stream, const RowProducts* beside);
 // y [M, N] = x [M, K] * wd [N, K]^T (+ t [M, Rpad] * b_cat [R, N], pitch N, when R > 0): the dense MFMA stage with its
 // tile choice; K % 64 == 0; partial holds dense_ksplit(M, K, N) fp32 copies of y when that is > 1
 void launch_dense_stage(const uint16_t* x, int64_t M, int64_t K, int64_t N, const uint16_t* wd, const uint16_t* t,
