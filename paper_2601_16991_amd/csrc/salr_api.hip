@@ -358,6 +358,7 @@ salr_status_t salr_qsalr_linear(const uint16_t* x, int64_t M, int64_t K, int64_t
         a.a_cat = a_cat; a.b_cat = b_cat; a.R = R;
         a.y = y;
         a.t = static_cast<uint16_t*>(workspace);
+        a.room = workspace_bytes;
         a.slice_table = reinterpret_cast<const uint32_t*>(static_cast<char*>(workspace) + salr::linear_nf4_table_offset(M, R));
         hipError_t e = salr::launch_linear_nf4(a, codes, scales, nnz, static_cast<hipStream_t>(stream), salr::g_timing_events);
         return e == hipSuccess ? SALR_OK : SALR_ERR_HIP;

@@ -415,6 +415,36 @@ inline size_t rowtile_pair_bytes(int64_t M, int64_t N, int64_t R, const RowtileP
     return round_up_256((size_t)M * (size_t)Rpad * sizeof(uint16_t)) + (size_t)(pairs + t_blocks) * sizeof(uint64_t);
 }
 uint64_t next_handover_tag();   // 64 bits that no other call of the process has
+int handover_polls();           // looks before a workgroup does without what it waits for (salr_set_handover_polls)
+
+// T handed over inside a small-batch kernel's launch (salr_shared_t.hpp): one word per slice of T, 32 ranks and workgroup behind the sums.
+struct SharedT {
+    uint64_t* words = nullptr;
+    uint64_t tag = 0;
+    int polls = 0;
+};
+constexpr int64_t kSharedMaxRank = 128;
+inline int64_t shared_t_blocks(int64_t R) { return kStreamTSlices * (adapter_rank_padded(R) / 32); }
+inline size_t shared_t_sums_bytes(int64_t M, int64_t R) {
+    return round_up_256((size_t)kStreamTSlices * (size_t)M * (size_t)adapter_rank_padded(R) * sizeof(float));
+}
+inline size_t shared_t_bytes(int64_t M, int64_t N, int64_t R) {
+    return shared_t_sums_bytes(M, R) + (size_t)shared_t_blocks(R) * (size_t)((N + 15) / 16) * sizeof(uint64_t);
+}
+// Up to 16 tokens on fewer row groups than two a CU (the kernels' variant of one workgroup a CU), A_cat in rows of whole vectors, and as
+// many workgroups as T has slices.
+inline bool shares_t(int64_t M, int64_t K, int64_t N, int64_t R) {
+    return R > 0 && R % 8 == 0 && R <= kSharedMaxRank && M <= 16 && K % 128 == 0 && K <= 8192 && (N + 15) / 16 < 2 * 256 &&
+           (N + 15) / 16 >= shared_t_blocks(R);
+}
+inline SharedT shared_t_of(const LinearArgs& a, size_t room) {
+    SharedT p;
+    if (!shares_t(a.M, a.K, a.N, a.R) || room < shared_t_bytes(a.M, a.N, a.R)) return p;
+    p.words = reinterpret_cast<uint64_t*>(reinterpret_cast<char*>(a.t) + shared_t_sums_bytes(a.M, a.R));
+    p.tag = next_handover_tag();
+    p.polls = handover_polls();
+    return p;
+}
 inline size_t rowtile_workspace_bytes(int64_t M, int64_t K, int64_t N, int64_t R) {
     const int ks = rowtile_ksplit(M, K, N);
     return rowtile_t_bytes(M, K, R) + (ks > 1 ? round_up_256((size_t)ks * (size_t)M * (size_t)N * sizeof(float)) : 0);

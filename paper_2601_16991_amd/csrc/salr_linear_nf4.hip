@@ -22,6 +22,7 @@
 #include "salr_linear_common.hpp"
 #include "salr_nf4.hpp"
 #include "salr_row_stream.hpp"
+#include "salr_shared_t.hpp"
 
 namespace salr {
 
@@ -45,12 +46,15 @@ struct NfStage {
 };
 
 // MT m-tiles of 16 rows, S chunks in flight per wave.  K % 128 == 0, nnz > 0.  kShort: no slice has more than S chunks.
-template <int MT, int S, bool kShort>
+// kAlone: no launch in front.  Each wave counts the bitmap words left of its slice in place of a table, and T (if any) comes from the first
+// workgroups (salr_shared_t.hpp).
+template <int MT, int S, bool kShort, bool kAlone>
 __global__ __launch_bounds__(kQWaves * 64, (S == 2 && MT == 1) ? 4 : 1) void linear_nf4_kernel(
     const uint16_t* __restrict__ x, int M, int64_t K, int64_t N, const uint32_t* __restrict__ bitmap,
     const uint8_t* __restrict__ codes, const uint16_t* __restrict__ scales, uint32_t scale_last,
-    const uint32_t* __restrict__ slice_table, const float* __restrict__ t_partial, const uint16_t* __restrict__ b_cat,
-    int R, int Rpad, uint16_t* __restrict__ y) {
+    const uint32_t* __restrict__ slice_table, const uint32_t* __restrict__ row_offsets, float* t_partial, const uint16_t* __restrict__ a_cat,
+    const uint16_t* __restrict__ b_cat, int R, int Rpad, uint16_t* __restrict__ y, SharedT shared) {
+    static_assert(!kAlone || (kShort && MT == 1 && kQWaves == kShareWaves && kShareTileBytes <= kQRows * kQSlotDwords * 4));
     static_assert(kQWaves == kSliceTableSlices, "the table holds one entry per wave slice");
     constexpr int NW = kQWaves;
     constexpr int kThreads = NW * 64;
@@ -83,7 +87,7 @@ __global__ __launch_bounds__(kQWaves * 64, (S == 2 && MT == 1) ? 4 : 1) void lin
     const uint32_t* brow = bitmap + row_c * wpr;
 
     // index in the packed values of the first value of this wave's slice of the row
-    uint32_t cur = slice_table[((int64_t)row_c * kSliceTableSlices + wave) * 2];
+    uint32_t cur = kAlone ? row_offsets[row_c] : slice_table[((int64_t)row_c * kSliceTableSlices + wave) * 2];
 
     auto load_bitmap_chunk = [&](int64_t c) -> uint4 {
         uint4 q = make_uint4(0, 0, 0, 0);
@@ -94,17 +98,30 @@ __global__ __launch_bounds__(kQWaves * 64, (S == 2 && MT == 1) ? 4 : 1) void lin
     // Slices of at most S chunks: one request for their bitmap, as in the bf16 kernel, and their scales by row, read back from LDS.
     // (One scale per vector of codes, from sixteen rows each, keeps the address unit busier than the codes do.)  4096 x 4096 at 20 %
     // sparsity: one token 15.1 -> 13.8 us with its pre-kernel, 16 tokens 17.5 -> 17.0; 8000 x 2048 at 50 %, 12 tokens: 19.6 -> 18.2.
-    const uint32_t block0 = cur / kNf4Block;
+    uint32_t block0 = cur / kNf4Block;
     uint32_t row_scale[kQRowScales / 4];
     u32x4 quad = {0, 0, 0, 0};
     if constexpr (kShort) {
         static_assert(S == 4);
         if (c_begin + g < c_end) quad = *reinterpret_cast<const u32x4*>(brow + (c_begin + g) * kQChunkWords);
+    }
+    auto load_scales = [&]() {
 #pragma unroll
         for (int i = 0; i < kQRowScales / 4; ++i) {
             const uint32_t blk = block0 + g + 4 * i;
             row_scale[i] = scales[blk < scale_last ? blk : scale_last];
         }
+    };
+    constexpr int kLeft = S * kQWaves / 4 - 1;   // requests of a lane for the words left of the last slice
+    uint4 left[kAlone ? kLeft : 1];
+    if constexpr (kAlone) {   // chunks past the slice start re-read chunk 0 and are dropped
+#pragma unroll
+        for (int i = 0; i < kLeft; ++i) {
+            const int64_t c = g + 4 * i;
+            left[i] = *reinterpret_cast<const uint4*>(brow + (c < c_begin ? c : 0) * kQChunkWords);
+        }
+    } else if constexpr (kShort) {
+        load_scales();
     } else {
 #pragma unroll
         for (int i = 0; i < S; ++i) bmq[i] = load_bitmap_chunk(c_begin + i);
@@ -125,7 +142,7 @@ __global__ __launch_bounds__(kQWaves * 64, (S == 2 && MT == 1) ? 4 : 1) void lin
     }
 
     // T = sum of the pre-kernel's split-K partials, rounded once to bf16, kept in LDS
-    if (R > 0) {
+    if (R > 0 && !kAlone) {
         const int groups = M * (Rpad >> 2);  // float4 groups of T
         for (int i = tid; i < groups; i += kThreads) {
             float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -143,6 +160,31 @@ __global__ __launch_bounds__(kQWaves * 64, (S == 2 && MT == 1) ? 4 : 1) void lin
         }
     }
 
+    const bool forms_t = kAlone && R > 0 && (int)blockIdx.x < kStreamTSlices * (Rpad >> 5);   // the same for the whole workgroup
+    if constexpr (kAlone) {
+        static_assert(sizeof(t_lds) >= kShareRedBytes);
+        if (forms_t) {
+            shared_t_products(x, M, K, a_cat, R, (int)blockIdx.x, reinterpret_cast<uint16_t*>(smem + wave * kQRows * kQSlotDwords),
+                              reinterpret_cast<float*>(t_lds), wave, lane);
+            __syncthreads();
+        }
+        uint32_t before = 0;
+#pragma unroll
+        for (int i = 0; i < kLeft; ++i)
+            before += g + 4 * i < c_begin ? __popc(left[i].x) + __popc(left[i].y) + __popc(left[i].z) + __popc(left[i].w) : 0u;
+        before += __shfl_xor(before, 16, 64);
+        before += __shfl_xor(before, 32, 64);
+        cur += before;
+        block0 = cur / kNf4Block;
+        load_scales();
+    }
+    // behind the first requests of the stream, whose way is as long as that of the sums
+    auto hand_out = [&]() {
+        if constexpr (kAlone)
+            if (forms_t && wave == 0)
+                shared_t_hand_out(shared, t_partial, M, R, Rpad, (int)blockIdx.x, (int)gridDim.x, reinterpret_cast<const float*>(t_lds), lane);
+    };
+
     if (lane < 16) {
         uint32_t a, b;
         nibble_lut_entry(lane, a, b);
@@ -152,9 +194,12 @@ __global__ __launch_bounds__(kQWaves * 64, (S == 2 && MT == 1) ? 4 : 1) void lin
     }
     __builtin_amdgcn_wave_barrier();
 
-    if constexpr (kShort) {
+    auto park_scales = [&]() {
 #pragma unroll
         for (int i = 0; i < kQRowScales / 4; ++i) my_scales[n * kQRowScales + g + 4 * i] = (uint16_t)row_scale[i];
+    };
+    if constexpr (kShort) {
+        if (!kAlone) park_scales();   // (else they are on their way)
         u32x4 w[4];
         spread_chunks(quad, w);
 #pragma unroll
@@ -239,18 +284,27 @@ __global__ __launch_bounds__(kQWaves * 64, (S == 2 && MT == 1) ? 4 : 1) void lin
     };
 
     const int64_t n_chunks = c_end - c_begin;
+    SharedTReader t_reader(shared, t_partial, M, R > 0 ? Rpad : 0, (int)gridDim.x, (int)blockIdx.x, wave, lane);   // (no ranks: nothing to look at)
     if (n_chunks == S) {
         // the whole slice is in flight at once: straight-line code, each chunk waits for its own data only
         NfStage<MT> st[S];
 #pragma unroll
         for (int i = 0; i < S; ++i) issue(st[i], bmq[i], c_begin + i);
+        if (kAlone) park_scales();
+        hand_out();
 #pragma unroll
-        for (int i = 0; i < S; ++i) consume(st[i]);
+        for (int i = 0; i < S; ++i) {
+            if (kAlone && i == S - 2) t_reader.look();
+            if (kAlone && i == S - 1 && t_reader.check()) t_reader.request();   // (uniform)
+            consume(st[i]);
+        }
     } else if constexpr (kShort) {
         NfStage<MT> st[S - 1];
 #pragma unroll
         for (int i = 0; i < S - 1; ++i)
             if (i < n_chunks) issue(st[i], bmq[i], c_begin + i);   // wave-uniform conditions
+        if (kAlone) park_scales();
+        hand_out();
 #pragma unroll
         for (int i = 0; i < S - 1; ++i)
             if (i < n_chunks) consume(st[i]);
@@ -275,7 +329,23 @@ __global__ __launch_bounds__(kQWaves * 64, (S == 2 && MT == 1) ? 4 : 1) void lin
         }
     }
 
+    __shared__ uint32_t t_missing[kAlone ? NW : 1];
+    if constexpr (kAlone) {
+        const bool fetched = t_reader.finish(shared, t_lds, Rpad);
+        if (lane == 0) t_missing[wave] = fetched ? 0u : 1u;
+    }
+
     __syncthreads();  // every wave is done with its staging slots; T in LDS is complete
+
+    if constexpr (kAlone) {
+        uint32_t missing = 0;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) missing |= t_missing[w];
+        missing = __builtin_amdgcn_readfirstlane(missing);   // (the same in all lanes)
+        if (wave == 0) t_reader.leave(missing == 0);
+        if (missing != 0)
+            shared_t_alone(x, M, K, a_cat, R, Rpad, reinterpret_cast<uint16_t*>(smem + wave * kQRows * kQSlotDwords), t_lds, tid, wave, lane);
+    }
 
     // ---- adapter k-step of this wave (Sec. 3.2): A operand = T rows from LDS, B operand = bq
     if (has_rank_step) {
@@ -319,20 +389,27 @@ size_t linear_nf4_workspace_bytes(int64_t M, int64_t N, int64_t R) {
     return linear_nf4_table_offset(M, R) + round_up_256(slice_table_bytes(N));
 }
 
-template <int MT, int S, bool kShort = false>
+template <int MT, int S, bool kShort = false, bool kAlone = false>
 static void launch_nf4_t(const LinearArgs& a, const uint8_t* codes, const uint16_t* scales, int64_t nnz, hipStream_t stream,
-                         const TimingEvents& ev) {
+                         const TimingEvents& ev, const SharedT& shared = SharedT()) {
     const int R = (int)a.R, Rpad = (int)adapter_rank_padded(a.R);
     const unsigned grid = (unsigned)((a.N + kQRows - 1) / kQRows);
     const uint32_t scale_last = (uint32_t)((nnz + 63) / 64 - 1);
-    SALR_LAUNCH((linear_nf4_kernel<MT, S, kShort>), dim3(grid), dim3(kQWaves * 64), stream, ev, a.x, (int)a.M, a.K, a.N, a.bitmap, codes,
-                scales, scale_last, a.slice_table, reinterpret_cast<const float*>(a.t), a.b_cat, R, Rpad, a.y);
+    SALR_LAUNCH((linear_nf4_kernel<MT, S, kShort, kAlone>), dim3(grid), dim3(kQWaves * 64), stream, ev, a.x, (int)a.M, a.K, a.N, a.bitmap, codes,
+                scales, scale_last, a.slice_table, a.row_offsets, reinterpret_cast<float*>(a.t), a.a_cat, a.b_cat, R, Rpad, a.y, shared);
 }
 
 // a.t: the partials of T (R > 0), a.slice_table: room for the table (built here), a.values unused.
 hipError_t launch_linear_nf4(const LinearArgs& a_in, const uint8_t* codes, const uint16_t* scales, int64_t nnz,
                              hipStream_t stream, const TimingEvents& ev) {
     LinearArgs a = a_in;
+    const bool many_groups = (a.N + kQRows - 1) / kQRows >= 2 * 256;
+    const bool short_slices = a.M <= 16 && !many_groups && a.K <= 4 * kQWaves * kQChunkWords * 32;
+    const SharedT shared = shared_t_of(a, a.room);
+    if (short_slices && (a.R == 0 || shared.words != nullptr)) {
+        launch_nf4_t<1, 4, true, true>(a, codes, scales, nnz, stream, ev, shared);
+        return hipGetLastError();
+    }
     if (a.R > 0) {   // the adapter pre-kernel builds the table in its extra workgroups
         a.build_table = true;
         launch_adapter_partial(a, stream);
@@ -340,9 +417,8 @@ hipError_t launch_linear_nf4(const LinearArgs& a_in, const uint8_t* codes, const
         hipError_t e = launch_build_slice_table(a.bitmap, a.row_offsets, a.N, a.K, const_cast<uint32_t*>(a.slice_table), stream);
         if (e != hipSuccess) return e;
     }
-    const bool many_groups = (a.N + kQRows - 1) / kQRows >= 2 * 256;
     if (a.M <= 16 && many_groups) launch_nf4_t<1, 2>(a, codes, scales, nnz, stream, ev);
-    else if (a.M <= 16 && a.K <= 4 * kQWaves * kQChunkWords * 32) launch_nf4_t<1, 4, true>(a, codes, scales, nnz, stream, ev);
+    else if (short_slices) launch_nf4_t<1, 4, true>(a, codes, scales, nnz, stream, ev);
     else if (a.M <= 16) launch_nf4_t<1, 4>(a, codes, scales, nnz, stream, ev);
     else if (a.M <= 32) launch_nf4_t<2, 3>(a, codes, scales, nnz, stream, ev);
     else launch_nf4_t<4, 2>(a, codes, scales, nnz, stream, ev);

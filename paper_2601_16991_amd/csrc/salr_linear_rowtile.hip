@@ -721,10 +721,11 @@ static void launch_rowtile_t(const LinearArgs& a, RowtileArgs p, hipStream_t str
     else ragged ? go(linear_rowtile_kernel<MT, true, false, Q, kOne>, a.values) : go(linear_rowtile_kernel<MT, false, false, Q, kOne>, a.values);
 }
 
-// How often the kernel looks for T at the end before it leaves its sums to it, a quarter of a microsecond each.  For tests: this host thread's
-// next calls, 0 to not wait at all.
+// How often a kernel looks for T at the end before it leaves its sums to it (or, salr_shared_t.hpp, forms T itself), a quarter of a
+// microsecond each.  For tests: this host thread's next calls, 0 to not wait at all.
 constexpr int kHandoverPolls = 64;
 static thread_local int g_handover_polls = kHandoverPolls;
+int handover_polls() { return g_handover_polls; }
 extern "C" void salr_set_handover_polls(int polls) { g_handover_polls = polls >= 0 && polls < kHandoverPolls ? polls : kHandoverPolls; }
 
 hipError_t launch_linear_rowtile(const LinearArgs& a, hipStream_t stream, const TimingEvents& ev) {

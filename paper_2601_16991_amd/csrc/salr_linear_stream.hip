@@ -23,6 +23,7 @@
 #include "salr_internal.hpp"
 #include "salr_linear_common.hpp"
 #include "salr_row_stream.hpp"
+#include "salr_shared_t.hpp"
 
 namespace salr {
 
@@ -122,12 +123,14 @@ __device__ __forceinline__ void own_t_partials(const OwnT& o, int R, int Rpad, u
 // request in place of the row offset, the rest of the slice's bitmap and the words left of it, and no barrier.
 // kQuads: the bitmap of four chunks in one request.
 // kOwnT: every workgroup computes T itself instead of reading the pre-kernel's partials (see stream_owns_t).
-template <int MT, int NW, int S, bool kVecBitmap, bool kOwnPrefix, bool kTable = false, bool kOwnT = false, bool kQuads = false>
+// kShareT: the first workgroups form T's partials for all (salr_shared_t.hpp).
+template <int MT, int NW, int S, bool kVecBitmap, bool kOwnPrefix, bool kTable = false, bool kOwnT = false, bool kQuads = false, bool kShareT = false>
 __global__ __launch_bounds__(NW * 64, (S == 2 && MT == 1) ? 4 : 1) void linear_stream_kernel(
     const uint16_t* __restrict__ x, int M, int64_t K, int64_t N, const uint32_t* __restrict__ bitmap,
     const uint16_t* __restrict__ values, const uint32_t* __restrict__ row_offsets,
-    const float* __restrict__ t_partial, const uint16_t* __restrict__ b_cat, int R, int Rpad,
-    uint16_t* __restrict__ y, const uint32_t* __restrict__ slice_table, const uint16_t* __restrict__ a_cat) {
+    float* t_partial, const uint16_t* __restrict__ b_cat, int R, int Rpad,
+    uint16_t* __restrict__ y, const uint32_t* __restrict__ slice_table, const uint16_t* __restrict__ a_cat, SharedT shared) {
+    static_assert(!kShareT || (MT == 1 && NW == kShareWaves && !kOwnT && kShareTileBytes <= kStreamRows * kSlotDwords * 4));
     static_assert(!kTable || NW == kSliceTableSlices, "the table holds one entry per wave slice");
     constexpr int kThreads = NW * 64;
     constexpr int kStageDwords = NW * kStreamRows * kSlotDwords + 8;
@@ -232,7 +235,7 @@ __global__ __launch_bounds__(NW * 64, (S == 2 && MT == 1) ? 4 : 1) void linear_s
     OwnT own;
     if constexpr (kOwnT) own_t_request(own, x, M, K, a_cat, R, wave, lane);
     // T = sum of the pre-kernel's split-K partials, rounded once to bf16, kept in LDS
-    if (R > 0 && !kOwnT) {
+    if (R > 0 && !kOwnT && !kShareT) {
         const int groups = M * (Rpad >> 2);  // float4 groups of T
         for (int i = tid; i < groups; i += kThreads) {
             float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -249,6 +252,22 @@ __global__ __launch_bounds__(NW * 64, (S == 2 && MT == 1) ? 4 : 1) void linear_s
             *reinterpret_cast<uint2*>(&t_lds[m * kMaxRankPadded + 4 * r4]) = o;
         }
     }
+
+    const bool forms_t = kShareT && (int)blockIdx.x < kStreamTSlices * (Rpad >> 5);   // the same for the whole workgroup
+    if constexpr (kShareT) {
+        static_assert(sizeof(t_lds) >= kShareRedBytes);
+        if (forms_t) {
+            shared_t_products(x, M, K, a_cat, R, (int)blockIdx.x, reinterpret_cast<uint16_t*>(smem + wave * kStreamRows * kSlotDwords),
+                              reinterpret_cast<float*>(t_lds), wave, lane);
+            __syncthreads();
+        }
+    }
+    // behind the first requests of the stream, whose way is as long as that of the sums
+    auto hand_out = [&]() {
+        if constexpr (kShareT)
+            if (forms_t && wave == 0)
+                shared_t_hand_out(shared, t_partial, M, R, Rpad, (int)blockIdx.x, (int)gridDim.x, reinterpret_cast<const float*>(t_lds), lane);
+    };
 
     if (lane < 16) {
         uint32_t a, b;
@@ -396,6 +415,8 @@ __global__ __launch_bounds__(NW * 64, (S == 2 && MT == 1) ? 4 : 1) void linear_s
     };
 
     const int64_t n_chunks = c_end - c_begin;
+    SharedTReader t_reader(shared, t_partial, M, Rpad, (int)gridDim.x, (int)blockIdx.x, wave, lane);
+    if (n_chunks == 0) hand_out();
     if constexpr (kOwnT) {
         // one chunk at most: its requests, T behind them, and one wait
         static_assert(kOwnTK <= 128 * NW && MT == 1);
@@ -418,8 +439,13 @@ __global__ __launch_bounds__(NW * 64, (S == 2 && MT == 1) ? 4 : 1) void linear_s
         StreamStage<MT, 3> st[S];
 #pragma unroll
         for (int i = 0; i < S; ++i) issue(st[i], bmq[i], c_begin + i);
+        hand_out();
 #pragma unroll
-        for (int i = 0; i < S; ++i) consume(st[i]);
+        for (int i = 0; i < S; ++i) {
+            if (kShareT && i == S - 2) t_reader.look();
+            if (kShareT && i == S - 1 && t_reader.check()) t_reader.request();   // (uniform)
+            consume(st[i]);
+        }
     } else if (n_chunks > 0 && !dense_slice) {
         StreamStage<MT, 3> st[S];
 #pragma unroll
@@ -433,6 +459,7 @@ __global__ __launch_bounds__(NW * 64, (S == 2 && MT == 1) ? 4 : 1) void linear_s
             spread_quad(quad);
             quad = load_quad(c_begin + 2 * S);
         }
+        hand_out();
         for (int64_t c = c_begin; c < c_end; c += S) {
 #pragma unroll
             for (int i = 0; i < S; ++i) {
@@ -456,6 +483,7 @@ __global__ __launch_bounds__(NW * 64, (S == 2 && MT == 1) ? 4 : 1) void linear_s
             bm_next = (c + 1 - c_begin < S) ? bmq[(c + 1 - c_begin) % S] : load_bitmap_chunk(c + 1);
         };
         step(da, c_begin);
+        hand_out();
         for (int64_t c = c_begin; c < c_end; c += 2) {
             if (c + 1 < c_end) step(db, c + 1);
             consume(da);
@@ -464,7 +492,23 @@ __global__ __launch_bounds__(NW * 64, (S == 2 && MT == 1) ? 4 : 1) void linear_s
         }
     }
 
+    __shared__ uint32_t t_missing[kShareT ? NW : 1];
+    if constexpr (kShareT) {
+        const bool fetched = t_reader.finish(shared, t_lds, Rpad);
+        if (lane == 0) t_missing[wave] = fetched ? 0u : 1u;
+    }
+
     __syncthreads();  // every wave is done with its staging slots; T in LDS is complete
+
+    if constexpr (kShareT) {
+        uint32_t missing = 0;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) missing |= t_missing[w];
+        missing = __builtin_amdgcn_readfirstlane(missing);   // (the same in all lanes)
+        if (wave == 0) t_reader.leave(missing == 0);
+        if (missing != 0)
+            shared_t_alone(x, M, K, a_cat, R, Rpad, reinterpret_cast<uint16_t*>(smem + wave * kStreamRows * kSlotDwords), t_lds, tid, wave, lane);
+    }
 
     // ---- adapter k-step of this wave (Sec. 3.2): A operand = T rows from LDS, B operand = bq
     if (has_rank_step) {
@@ -621,10 +665,24 @@ static void launch_stream_t(const LinearArgs& a, hipStream_t stream, const Timin
         if (stream_owns_t(a.M, a.K, R)) {
             if (a.slice_table != nullptr && !a.build_table)
                 SALR_LAUNCH((linear_stream_kernel<MT, NW, S, true, false, true, true>), dim3(grid), dim3(NW * 64), stream, ev, a.x, (int)a.M,
-                            a.K, a.N, a.bitmap, a.values, a.row_offsets, nullptr, a.b_cat, R, Rpad, a.y, a.slice_table, a.a_cat);
+                            a.K, a.N, a.bitmap, a.values, a.row_offsets, nullptr, a.b_cat, R, Rpad, a.y, a.slice_table, a.a_cat, SharedT());
             else
                 SALR_LAUNCH((linear_stream_kernel<MT, NW, S, true, true, false, true>), dim3(grid), dim3(NW * 64), stream, ev, a.x, (int)a.M,
-                            a.K, a.N, a.bitmap, a.values, a.row_offsets, nullptr, a.b_cat, R, Rpad, a.y, nullptr, a.a_cat);
+                            a.K, a.N, a.bitmap, a.values, a.row_offsets, nullptr, a.b_cat, R, Rpad, a.y, nullptr, a.a_cat, SharedT());
+            return;
+        }
+    }
+    if constexpr (MT == 1 && S > 2) {
+        const SharedT shared = shared_t_of(a, a.room);
+        if (shared.words != nullptr) {
+            auto go = [&](auto kernel, const uint32_t* table) {
+                SALR_LAUNCH(kernel, dim3(grid), dim3(NW * 64), stream, ev, a.x, (int)a.M, a.K, a.N, a.bitmap, a.values, a.row_offsets,
+                            t_partial, a.b_cat, R, Rpad, a.y, table, a.a_cat, shared);
+            };
+            // (a caller's table; without one there is no launch in front to build it in)
+            if (a.slice_table != nullptr && !a.build_table) go(linear_stream_kernel<MT, NW, S, true, false, true, false, kQ, true>, a.slice_table);
+            else if (!kQ || a.K <= 32 * kChunkWords * 32) go(linear_stream_kernel<MT, NW, S, true, true, false, false, kQ, true>, nullptr);
+            else if constexpr (kQ) go(linear_stream_kernel<MT, NW, S, true, false, false, false, kQ, true>, nullptr);
             return;
         }
     }
@@ -634,10 +692,10 @@ static void launch_stream_t(const LinearArgs& a, hipStream_t stream, const Timin
     const uint32_t* no_table = nullptr;
     if (a.slice_table != nullptr && wpr % kChunkWords == 0)   // prepared layer: cursors from its slice table
         SALR_LAUNCH((linear_stream_kernel<MT, NW, S, true, false, true, false, kQ>), dim3(grid), dim3(NW * 64), stream, ev, a.x, (int)a.M,
-                    a.K, a.N, a.bitmap, a.values, a.row_offsets, (const float*)t_partial, a.b_cat, R, Rpad, a.y, a.slice_table, a.a_cat);
+                    a.K, a.N, a.bitmap, a.values, a.row_offsets, t_partial, a.b_cat, R, Rpad, a.y, a.slice_table, a.a_cat, SharedT());
     else if (wpr % kChunkWords != 0)  // bitmap rows are not multiples of 16 bytes: scalar bitmap loads
         SALR_LAUNCH((linear_stream_kernel<MT, NW, S, false, false>), dim3(grid), dim3(NW * 64), stream, ev, a.x, (int)a.M, a.K,
-                    a.N, a.bitmap, a.values, a.row_offsets, (const float*)t_partial, a.b_cat, R, Rpad, a.y, no_table, a.a_cat);
+                    a.N, a.bitmap, a.values, a.row_offsets, t_partial, a.b_cat, R, Rpad, a.y, no_table, a.a_cat, SharedT());
     else {
         constexpr bool kTwoChunks = MT == 1 && S > 2 && !kQ;   // of a wave at most: its longer rows go to the variant with kQ
         // Short rows and one workgroup per CU: barrier-free start (two workgroups per CU hide each other's barrier, and the bitmap
@@ -645,13 +703,13 @@ static void launch_stream_t(const LinearArgs& a, hipStream_t stream, const Timin
         if constexpr (S != 2) {
             if (kTwoChunks || wpr / kChunkWords <= 32) {
                 SALR_LAUNCH((linear_stream_kernel<MT, NW, S, true, true, false, false, kQ>), dim3(grid), dim3(NW * 64), stream, ev, a.x, (int)a.M,
-                            a.K, a.N, a.bitmap, a.values, a.row_offsets, (const float*)t_partial, a.b_cat, R, Rpad, a.y, no_table, a.a_cat);
+                            a.K, a.N, a.bitmap, a.values, a.row_offsets, t_partial, a.b_cat, R, Rpad, a.y, no_table, a.a_cat, SharedT());
                 return;
             }
         }
         if constexpr (!kTwoChunks)
             SALR_LAUNCH((linear_stream_kernel<MT, NW, S, true, false, false, false, kQ>), dim3(grid), dim3(NW * 64), stream, ev, a.x, (int)a.M,
-                        a.K, a.N, a.bitmap, a.values, a.row_offsets, (const float*)t_partial, a.b_cat, R, Rpad, a.y, no_table, a.a_cat);
+                        a.K, a.N, a.bitmap, a.values, a.row_offsets, t_partial, a.b_cat, R, Rpad, a.y, no_table, a.a_cat, SharedT());
     }
 }
 
