@@ -422,8 +422,9 @@ struct SharedT {
     uint64_t* words = nullptr;
     uint64_t tag = 0;
     int polls = 0;
+    int extra = 0;   // leading workgroups that form T and nothing else
 };
-constexpr int64_t kSharedMaxRank = 128;
+constexpr int64_t kSharedMaxRank = 128, kSharedMaxColumns = 8192;
 inline int64_t shared_t_blocks(int64_t R) { return kStreamTSlices * (adapter_rank_padded(R) / 32); }
 inline size_t shared_t_sums_bytes(int64_t M, int64_t R) {
     return round_up_256((size_t)kStreamTSlices * (size_t)M * (size_t)adapter_rank_padded(R) * sizeof(float));
@@ -432,17 +433,21 @@ inline size_t shared_t_bytes(int64_t M, int64_t N, int64_t R) {
     return shared_t_sums_bytes(M, R) + (size_t)shared_t_blocks(R) * (size_t)((N + 15) / 16) * sizeof(uint64_t);
 }
 // Up to 16 tokens on fewer row groups than two a CU (the kernels' variant of one workgroup a CU), A_cat in rows of whole vectors, and as
-// many workgroups as T has slices.
+// many workgroups as T has slices (SharedT::extra: of their own, where they all are one round).  us a call, T from a launch in front / so:
+// 4096 x 4096 rank 32 one token 13.2 / 11.1 (4-bit values 13.8 / 11.6), 16 tokens 15.0 / 12.8 (4-bit 15.7 / 13.8; rank 64 15.8 / 13.9);
+// 16 x 2048 x 4096 10.5 / 8.8; own workgroups: 8 x 4096 x 1024 11.4 / 8.6, 16 x 4096 x 2048 rank 128 15.0 / 12.5 (14.9 where half of the
+// workgroups form T beside their own work).  2:4 masks: 16 x 4096 x 4096 14.6 / 13.4, 16 x 4096 x 1024 rank 16 12.7 / 10.2.
 inline bool shares_t(int64_t M, int64_t K, int64_t N, int64_t R) {
-    return R > 0 && R % 8 == 0 && R <= kSharedMaxRank && M <= 16 && K % 128 == 0 && K <= 8192 && (N + 15) / 16 < 2 * 256 &&
-           (N + 15) / 16 >= shared_t_blocks(R);
+    return R > 0 && R % 8 == 0 && R <= kSharedMaxRank && M <= 16 && K % 128 == 0 && K <= kSharedMaxColumns && (N + 15) / 16 < 2 * 256 &&
+           ((N + 15) / 16 >= shared_t_blocks(R) || (N + 15) / 16 + shared_t_blocks(R) <= 256);
 }
 inline SharedT shared_t_of(const LinearArgs& a, size_t room) {
     SharedT p;
-    if (!shares_t(a.M, a.K, a.N, a.R) || room < shared_t_bytes(a.M, a.N, a.R)) return p;
+    if (!shares_t(a.M, a.K, a.N, a.R) || room < shared_t_bytes(a.M, a.N, a.R) || (uintptr_t)a.a_cat % 16 != 0) return p;
     p.words = reinterpret_cast<uint64_t*>(reinterpret_cast<char*>(a.t) + shared_t_sums_bytes(a.M, a.R));
     p.tag = next_handover_tag();
     p.polls = handover_polls();
+    if ((a.N + 15) / 16 + shared_t_blocks(a.R) <= 256) p.extra = (int)shared_t_blocks(a.R);
     return p;
 }
 inline size_t rowtile_workspace_bytes(int64_t M, int64_t K, int64_t N, int64_t R) {

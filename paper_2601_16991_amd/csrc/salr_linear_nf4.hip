@@ -46,8 +46,9 @@ struct NfStage {
 };
 
 // MT m-tiles of 16 rows, S chunks in flight per wave.  K % 128 == 0, nnz > 0.  kShort: no slice has more than S chunks.
-// kAlone: no launch in front.  Each wave counts the bitmap words left of its slice in place of a table, and T (if any) comes from the first
-// workgroups (salr_shared_t.hpp).
+// kAlone: no launch in front.  The waves exchange the counts of their slices in place of a table (reading the words left of a slice again takes
+// the address unit as long as the words themselves: 16 tokens 15.6 us, so 14.7), and T (if any) comes from the launch's first workgroups
+// (salr_shared_t.hpp).
 template <int MT, int S, bool kShort, bool kAlone>
 __global__ __launch_bounds__(kQWaves * 64, (S == 2 && MT == 1) ? 4 : 1) void linear_nf4_kernel(
     const uint16_t* __restrict__ x, int M, int64_t K, int64_t N, const uint32_t* __restrict__ bitmap,
@@ -66,6 +67,7 @@ __global__ __launch_bounds__(kQWaves * 64, (S == 2 && MT == 1) ? 4 : 1) void lin
     __shared__ __attribute__((aligned(16))) uint16_t t_lds[kTRows * kMaxRankPadded];  // T = X * A_cat, bf16
     __shared__ uint32_t lut_all[NW][kNibbleLutWords];   // one copy per wave: filled and used wave-synchronously
     __shared__ float level_all[NW][kQLevelWords];
+    __shared__ uint32_t slice_count[kAlone ? NW : 1][kQRows];
     __shared__ uint16_t scale_all[kShort ? NW : 1][kQRows * kQRowScales];
 
     const int tid = threadIdx.x;
@@ -73,7 +75,16 @@ __global__ __launch_bounds__(kQWaves * 64, (S == 2 && MT == 1) ? 4 : 1) void lin
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n = lane & 15;
     const int g = lane >> 4;
-    const int64_t n0 = (int64_t)blockIdx.x * kQRows;
+    const int group = (int)blockIdx.x - (kAlone ? shared.extra : 0);   // of 16 rows
+    if constexpr (kAlone) {
+        static_assert(sizeof(t_lds) >= kShareRedBytes);
+        if (group < 0) {   // the same for the whole workgroup
+            shared_t_workgroup(shared, x, M, K, a_cat, R, Rpad, t_partial, reinterpret_cast<uint16_t*>(smem + wave * kQRows * kQSlotDwords),
+                               reinterpret_cast<float*>(t_lds), wave, lane);
+            return;
+        }
+    }
+    const int64_t n0 = (int64_t)group * kQRows;
     const int64_t row = n0 + n;
     const int64_t wpr = K >> 5;
     const int64_t chunks_total = wpr / kQChunkWords;
@@ -112,15 +123,7 @@ __global__ __launch_bounds__(kQWaves * 64, (S == 2 && MT == 1) ? 4 : 1) void lin
             row_scale[i] = scales[blk < scale_last ? blk : scale_last];
         }
     };
-    constexpr int kLeft = S * kQWaves / 4 - 1;   // requests of a lane for the words left of the last slice
-    uint4 left[kAlone ? kLeft : 1];
-    if constexpr (kAlone) {   // chunks past the slice start re-read chunk 0 and are dropped
-#pragma unroll
-        for (int i = 0; i < kLeft; ++i) {
-            const int64_t c = g + 4 * i;
-            left[i] = *reinterpret_cast<const uint4*>(brow + (c < c_begin ? c : 0) * kQChunkWords);
-        }
-    } else if constexpr (kShort) {
+    if constexpr (!kAlone && kShort) {
         load_scales();
     } else {
 #pragma unroll
@@ -160,29 +163,36 @@ __global__ __launch_bounds__(kQWaves * 64, (S == 2 && MT == 1) ? 4 : 1) void lin
         }
     }
 
-    const bool forms_t = kAlone && R > 0 && (int)blockIdx.x < kStreamTSlices * (Rpad >> 5);   // the same for the whole workgroup
+    const bool forms_t = kAlone && R > 0 && shared.extra == 0 && group < kStreamTSlices * (Rpad >> 5);   // the same for the whole workgroup
     if constexpr (kAlone) {
-        static_assert(sizeof(t_lds) >= kShareRedBytes);
-        if (forms_t) {
-            shared_t_products(x, M, K, a_cat, R, (int)blockIdx.x, reinterpret_cast<uint16_t*>(smem + wave * kQRows * kQSlotDwords),
-                              reinterpret_cast<float*>(t_lds), wave, lane);
-            __syncthreads();
-        }
+        SharedTProducts t_products;
+        if (forms_t) t_products.request(x, M, K, a_cat, R, group, wave, lane);
+        uint32_t mine = __popc(quad.x) + __popc(quad.y) + __popc(quad.z) + __popc(quad.w);
+        mine += __shfl_xor(mine, 16, 64);
+        mine += __shfl_xor(mine, 32, 64);
+        if (g == 0) slice_count[wave][n] = mine;
+        if (forms_t)
+            t_products.multiply(reinterpret_cast<uint16_t*>(smem + wave * kQRows * kQSlotDwords), reinterpret_cast<float*>(t_lds), wave, lane);
+        __syncthreads();
         uint32_t before = 0;
 #pragma unroll
-        for (int i = 0; i < kLeft; ++i)
-            before += g + 4 * i < c_begin ? __popc(left[i].x) + __popc(left[i].y) + __popc(left[i].z) + __popc(left[i].w) : 0u;
-        before += __shfl_xor(before, 16, 64);
-        before += __shfl_xor(before, 32, 64);
+        for (int w = 0; w + 1 < NW; ++w) before += w < wave ? slice_count[w][n] : 0u;
         cur += before;
         block0 = cur / kNf4Block;
         load_scales();
     }
     // behind the first requests of the stream, whose way is as long as that of the sums
-    auto hand_out = [&]() {
+    auto start_hand_out = [&](SharedTHandOut& t_out) {
         if constexpr (kAlone)
-            if (forms_t && wave == 0)
-                shared_t_hand_out(shared, t_partial, M, R, Rpad, (int)blockIdx.x, (int)gridDim.x, reinterpret_cast<const float*>(t_lds), lane);
+            if (forms_t && wave == 0) t_out.start(shared, t_partial, M, R, Rpad, group, (int)gridDim.x, reinterpret_cast<const float*>(t_lds), lane);
+    };
+    auto finish_hand_out = [&](SharedTHandOut& t_out) {
+        if (kAlone && forms_t && wave == 0) t_out.finish(shared);
+    };
+    auto hand_out = [&]() {
+        SharedTHandOut t_out;
+        start_hand_out(t_out);
+        finish_hand_out(t_out);
     };
 
     if (lane < 16) {
@@ -284,20 +294,22 @@ __global__ __launch_bounds__(kQWaves * 64, (S == 2 && MT == 1) ? 4 : 1) void lin
     };
 
     const int64_t n_chunks = c_end - c_begin;
-    SharedTReader t_reader(shared, t_partial, M, R > 0 ? Rpad : 0, (int)gridDim.x, (int)blockIdx.x, wave, lane);   // (no ranks: nothing to look at)
+    SharedTReader t_reader(shared, t_partial, M, R > 0 ? Rpad : 0, (int)gridDim.x - shared.extra, group, wave, lane);   // (no ranks: nothing to look at)
     if (n_chunks == S) {
         // the whole slice is in flight at once: straight-line code, each chunk waits for its own data only
         NfStage<MT> st[S];
 #pragma unroll
         for (int i = 0; i < S; ++i) issue(st[i], bmq[i], c_begin + i);
         if (kAlone) park_scales();
-        hand_out();
+        SharedTHandOut t_out;
+        start_hand_out(t_out);
 #pragma unroll
         for (int i = 0; i < S; ++i) {
             if (kAlone && i == S - 2) t_reader.look();
             if (kAlone && i == S - 1 && t_reader.check()) t_reader.request();   // (uniform)
             consume(st[i]);
         }
+        finish_hand_out(t_out);
     } else if constexpr (kShort) {
         NfStage<MT> st[S - 1];
 #pragma unroll
@@ -393,7 +405,7 @@ template <int MT, int S, bool kShort = false, bool kAlone = false>
 static void launch_nf4_t(const LinearArgs& a, const uint8_t* codes, const uint16_t* scales, int64_t nnz, hipStream_t stream,
                          const TimingEvents& ev, const SharedT& shared = SharedT()) {
     const int R = (int)a.R, Rpad = (int)adapter_rank_padded(a.R);
-    const unsigned grid = (unsigned)((a.N + kQRows - 1) / kQRows);
+    const unsigned grid = (unsigned)((a.N + kQRows - 1) / kQRows) + shared.extra;
     const uint32_t scale_last = (uint32_t)((nnz + 63) / 64 - 1);
     SALR_LAUNCH((linear_nf4_kernel<MT, S, kShort, kAlone>), dim3(grid), dim3(kQWaves * 64), stream, ev, a.x, (int)a.M, a.K, a.N, a.bitmap, codes,
                 scales, scale_last, a.slice_table, a.row_offsets, reinterpret_cast<float*>(a.t), a.a_cat, a.b_cat, R, Rpad, a.y, shared);

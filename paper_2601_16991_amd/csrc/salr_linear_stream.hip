@@ -16,7 +16,7 @@
 //   epilogue       accumulators of the NW waves are summed through LDS, rounded to bf16, stored.
 //
 // The row cursor into `values` at the start of a wave's slice is the row offset plus the popcount of
-// the row's earlier bitmap words; a short pre-pass over the workgroup's bitmap rows computes it.
+// the row's earlier bitmap words; the waves exchange the counts of their slices for it, or a table holds it.
 #include <hip/hip_ext.h>
 
 #include "salr_device.hpp"
@@ -116,8 +116,10 @@ __device__ __forceinline__ void own_t_partials(const OwnT& o, int R, int Rpad, u
 }
 
 // MT m-tiles of 16 rows, NW waves per workgroup, S chunks in flight per wave.
-// kOwnPrefix: every wave popcounts the bitmap words left of its slice itself (short rows), so the
-// workgroup needs no barrier before the stream starts; otherwise the waves exchange slice counts.
+// kOwnPrefix: every wave popcounts the bitmap words left of its slice itself (kOwnT's rows of a chunk a wave), so the workgroup needs no
+// barrier before the stream starts; otherwise the waves exchange slice counts.  (On longer rows the words that are read again keep the
+// address unit busier than the barrier costs: 16 x 2048 x 4096 10.2 -> 9.3 us, 8 x 4096 x 1024 9.5 -> 8.6; one token on 4096 x 4096 the other
+// way round by 3 %.)
 // kTable: the cursors come ready-made from the layer's slice table (salr_build_slice_table: for every row and each of
 // the 8 wave slices the index of the slice's first value and the most nonzeros any chunk of it holds): one 8-byte
 // request in place of the row offset, the rest of the slice's bitmap and the words left of it, and no barrier.
@@ -130,7 +132,7 @@ __global__ __launch_bounds__(NW * 64, (S == 2 && MT == 1) ? 4 : 1) void linear_s
     const uint16_t* __restrict__ values, const uint32_t* __restrict__ row_offsets,
     float* t_partial, const uint16_t* __restrict__ b_cat, int R, int Rpad,
     uint16_t* __restrict__ y, const uint32_t* __restrict__ slice_table, const uint16_t* __restrict__ a_cat, SharedT shared) {
-    static_assert(!kShareT || (MT == 1 && NW == kShareWaves && !kOwnT && kShareTileBytes <= kStreamRows * kSlotDwords * 4));
+    static_assert(!kShareT || (!kOwnPrefix && MT == 1 && NW == kShareWaves && !kOwnT && kShareTileBytes <= kStreamRows * kSlotDwords * 4));
     static_assert(!kTable || NW == kSliceTableSlices, "the table holds one entry per wave slice");
     constexpr int kThreads = NW * 64;
     constexpr int kStageDwords = NW * kStreamRows * kSlotDwords + 8;
@@ -147,7 +149,16 @@ __global__ __launch_bounds__(NW * 64, (S == 2 && MT == 1) ? 4 : 1) void linear_s
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // scalar: conditions on it branch uniformly
     const int n = lane & 15;
     const int g = lane >> 4;
-    const int64_t n0 = (int64_t)blockIdx.x * kStreamRows;
+    const int group = (int)blockIdx.x - (kShareT ? shared.extra : 0);   // of 16 rows
+    if constexpr (kShareT) {
+        static_assert(sizeof(t_lds) >= kShareRedBytes);
+        if (group < 0) {   // the same for the whole workgroup
+            shared_t_workgroup(shared, x, M, K, a_cat, R, Rpad, t_partial, reinterpret_cast<uint16_t*>(smem + wave * kStreamRows * kSlotDwords),
+                               reinterpret_cast<float*>(t_lds), wave, lane);
+            return;
+        }
+    }
+    const int64_t n0 = (int64_t)group * kStreamRows;
     const int64_t row = n0 + n;
     const bool row_ok = row < N;
     const int64_t wpr = K >> 5;
@@ -253,20 +264,22 @@ __global__ __launch_bounds__(NW * 64, (S == 2 && MT == 1) ? 4 : 1) void linear_s
         }
     }
 
-    const bool forms_t = kShareT && (int)blockIdx.x < kStreamTSlices * (Rpad >> 5);   // the same for the whole workgroup
-    if constexpr (kShareT) {
-        static_assert(sizeof(t_lds) >= kShareRedBytes);
-        if (forms_t) {
-            shared_t_products(x, M, K, a_cat, R, (int)blockIdx.x, reinterpret_cast<uint16_t*>(smem + wave * kStreamRows * kSlotDwords),
-                              reinterpret_cast<float*>(t_lds), wave, lane);
-            __syncthreads();
-        }
-    }
+    const bool forms_t = kShareT && shared.extra == 0 && group < kStreamTSlices * (Rpad >> 5);   // the same for the whole workgroup
+    SharedTProducts t_products;
+    if constexpr (kShareT)
+        if (forms_t) t_products.request(x, M, K, a_cat, R, group, wave, lane);
     // behind the first requests of the stream, whose way is as long as that of the sums
-    auto hand_out = [&]() {
+    auto start_hand_out = [&](SharedTHandOut& t_out) {
         if constexpr (kShareT)
-            if (forms_t && wave == 0)
-                shared_t_hand_out(shared, t_partial, M, R, Rpad, (int)blockIdx.x, (int)gridDim.x, reinterpret_cast<const float*>(t_lds), lane);
+            if (forms_t && wave == 0) t_out.start(shared, t_partial, M, R, Rpad, group, (int)gridDim.x, reinterpret_cast<const float*>(t_lds), lane);
+    };
+    auto finish_hand_out = [&](SharedTHandOut& t_out) {
+        if (kShareT && forms_t && wave == 0) t_out.finish(shared);
+    };
+    auto hand_out = [&]() {
+        SharedTHandOut t_out;
+        start_hand_out(t_out);
+        finish_hand_out(t_out);
     };
 
     if (lane < 16) {
@@ -299,9 +312,10 @@ __global__ __launch_bounds__(NW * 64, (S == 2 && MT == 1) ? 4 : 1) void linear_s
             longest = len > longest ? len : longest;
         }
         if constexpr (kOwnPrefix) {
-            // nonzeros left of the slice: at most 7 chunks per lane (rows of <= 32 chunks), all in flight at once
+            // nonzeros left of the slice: at most two chunks per lane, in flight at once
             uint32_t before = 0;
-            constexpr int kLeft = kOwnT ? kOwnTK / 512 : 7;
+            static_assert(kOwnT);
+            constexpr int kLeft = kOwnTK / 512;
             uint4 left[kLeft];  // no branches: chunks past the slice start re-read chunk 0 and are dropped
 #pragma unroll
             for (int i = 0; i < kLeft; ++i) {
@@ -320,6 +334,12 @@ __global__ __launch_bounds__(NW * 64, (S == 2 && MT == 1) ? 4 : 1) void linear_s
             tail += __shfl_xor(tail, 16, 64);
             tail += __shfl_xor(tail, 32, 64);
             if (g == 0) slice_count[wave][n] = head + tail;
+        }
+    }
+    if constexpr (kShareT) {
+        if (forms_t) {
+            t_products.multiply(reinterpret_cast<uint16_t*>(smem + wave * kStreamRows * kSlotDwords), reinterpret_cast<float*>(t_lds), wave, lane);
+            if (kTable) __syncthreads();
         }
     }
     if constexpr (!kOwnPrefix && !kTable) {
@@ -415,7 +435,7 @@ __global__ __launch_bounds__(NW * 64, (S == 2 && MT == 1) ? 4 : 1) void linear_s
     };
 
     const int64_t n_chunks = c_end - c_begin;
-    SharedTReader t_reader(shared, t_partial, M, Rpad, (int)gridDim.x, (int)blockIdx.x, wave, lane);
+    SharedTReader t_reader(shared, t_partial, M, Rpad, (int)gridDim.x - shared.extra, group, wave, lane);
     if (n_chunks == 0) hand_out();
     if constexpr (kOwnT) {
         // one chunk at most: its requests, T behind them, and one wait
@@ -439,13 +459,15 @@ __global__ __launch_bounds__(NW * 64, (S == 2 && MT == 1) ? 4 : 1) void linear_s
         StreamStage<MT, 3> st[S];
 #pragma unroll
         for (int i = 0; i < S; ++i) issue(st[i], bmq[i], c_begin + i);
-        hand_out();
+        SharedTHandOut t_out;
+        start_hand_out(t_out);
 #pragma unroll
         for (int i = 0; i < S; ++i) {
             if (kShareT && i == S - 2) t_reader.look();
             if (kShareT && i == S - 1 && t_reader.check()) t_reader.request();   // (uniform)
             consume(st[i]);
         }
+        finish_hand_out(t_out);
     } else if (n_chunks > 0 && !dense_slice) {
         StreamStage<MT, 3> st[S];
 #pragma unroll
@@ -676,13 +698,12 @@ static void launch_stream_t(const LinearArgs& a, hipStream_t stream, const Timin
         const SharedT shared = shared_t_of(a, a.room);
         if (shared.words != nullptr) {
             auto go = [&](auto kernel, const uint32_t* table) {
-                SALR_LAUNCH(kernel, dim3(grid), dim3(NW * 64), stream, ev, a.x, (int)a.M, a.K, a.N, a.bitmap, a.values, a.row_offsets,
+                SALR_LAUNCH(kernel, dim3(grid + shared.extra), dim3(NW * 64), stream, ev, a.x, (int)a.M, a.K, a.N, a.bitmap, a.values, a.row_offsets,
                             t_partial, a.b_cat, R, Rpad, a.y, table, a.a_cat, shared);
             };
             // (a caller's table; without one there is no launch in front to build it in)
             if (a.slice_table != nullptr && !a.build_table) go(linear_stream_kernel<MT, NW, S, true, false, true, false, kQ, true>, a.slice_table);
-            else if (!kQ || a.K <= 32 * kChunkWords * 32) go(linear_stream_kernel<MT, NW, S, true, true, false, false, kQ, true>, nullptr);
-            else if constexpr (kQ) go(linear_stream_kernel<MT, NW, S, true, false, false, false, kQ, true>, nullptr);
+            else go(linear_stream_kernel<MT, NW, S, true, false, false, false, kQ, true>, nullptr);
             return;
         }
     }
@@ -696,21 +717,9 @@ static void launch_stream_t(const LinearArgs& a, hipStream_t stream, const Timin
     else if (wpr % kChunkWords != 0)  // bitmap rows are not multiples of 16 bytes: scalar bitmap loads
         SALR_LAUNCH((linear_stream_kernel<MT, NW, S, false, false>), dim3(grid), dim3(NW * 64), stream, ev, a.x, (int)a.M, a.K,
                     a.N, a.bitmap, a.values, a.row_offsets, t_partial, a.b_cat, R, Rpad, a.y, no_table, a.a_cat, SharedT());
-    else {
-        constexpr bool kTwoChunks = MT == 1 && S > 2 && !kQ;   // of a wave at most: its longer rows go to the variant with kQ
-        // Short rows and one workgroup per CU: barrier-free start (two workgroups per CU hide each other's barrier, and the bitmap
-        // words left of a slice, which every wave would fetch again, are a third of the L2 reads).
-        if constexpr (S != 2) {
-            if (kTwoChunks || wpr / kChunkWords <= 32) {
-                SALR_LAUNCH((linear_stream_kernel<MT, NW, S, true, true, false, false, kQ>), dim3(grid), dim3(NW * 64), stream, ev, a.x, (int)a.M,
-                            a.K, a.N, a.bitmap, a.values, a.row_offsets, t_partial, a.b_cat, R, Rpad, a.y, no_table, a.a_cat, SharedT());
-                return;
-            }
-        }
-        if constexpr (!kTwoChunks)
-            SALR_LAUNCH((linear_stream_kernel<MT, NW, S, true, false, false, false, kQ>), dim3(grid), dim3(NW * 64), stream, ev, a.x, (int)a.M,
-                        a.K, a.N, a.bitmap, a.values, a.row_offsets, t_partial, a.b_cat, R, Rpad, a.y, no_table, a.a_cat, SharedT());
-    }
+    else   // (no ranks: with any there is a table)
+        SALR_LAUNCH((linear_stream_kernel<MT, NW, S, true, false, false, false, kQ>), dim3(grid), dim3(NW * 64), stream, ev, a.x, (int)a.M,
+                    a.K, a.N, a.bitmap, a.values, a.row_offsets, t_partial, a.b_cat, R, Rpad, a.y, no_table, a.a_cat, SharedT());
 }
 
 hipError_t launch_linear_stream(const LinearArgs& a, hipStream_t stream, const TimingEvents& ev) {

@@ -2,7 +2,7 @@
 //
 // A launch for T in front costs the small-batch kernels 4 us of 12 to 16, whatever it does.  Their own workgroups, one a CU, need T only at
 // their end, 8 us after their start, so the first kStreamTSlices * Rpad / 32 of them each form the product over one slice of K for 32 ranks
-// beside their own start (two requests a step of 32 columns) and leave it to all.
+// beside their own start (two requests a step of 32 columns) and leave it to all.  Where CUs would be idle, workgroups of their own do.
 //   partial sums   kStreamTSlices fp32 slices, the same sums in the same order as adapter_partial_kernel's: T has the same bits
 //   words          one per slice and workgroup (salr_handover.hpp): a slice's workgroup meets every workgroup's word once its sums have
 //                  reached memory.  A workgroup that finds the tag in all of its words at the end reads the sums and clears the words; one that
@@ -19,78 +19,113 @@
 namespace salr {
 
 constexpr int kShareWaves = 8;
-constexpr int kShareBatch = 4;                                  // steps of a wave in flight
-constexpr int kShareTileBytes = kShareBatch * 1024;             // of a wave
+constexpr int kShareSteps = (int)(kSharedMaxColumns / 32 / kStreamTSlices / 4);   // of a wave at most
+constexpr int kShareTileBytes = kShareSteps * 1024;             // of a wave
 constexpr int kShareRedBytes = kShareWaves * 256 * 4;
 constexpr int kShareMaxPairs = kSharedMaxRank / 32;
 
-// The sums of slice `block` % kStreamTSlices for ranks 32 (block / kStreamTSlices) .. + 31, as accumulators of eight waves in `red`
-// [8][4][64]: waves 0 to 3 the first sixteen ranks, every fourth step each, waves 4 to 7 the others.  R % 8 == 0.  tiles:
-// kShareTileBytes of this wave.
-__device__ __forceinline__ void shared_t_products(const uint16_t* __restrict__ x, int M, int64_t K, const uint16_t* __restrict__ a_cat, int R,
-                                                  int block, uint16_t* tiles, float* red, int wave, int lane) {
-    const int i16 = lane & 15, g = lane >> 4;
-    const int b = block % kStreamTSlices, rt = 2 * (block / kStreamTSlices) + (wave >> 2);
-    const int units = (int)(K >> 5), u_begin = units * b / kStreamTSlices, u_end = units * (b + 1) / kStreamTSlices;
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    if (16 * rt < R) {   // uniform
-        const uint16_t* xr = x + (int64_t)(i16 < M ? i16 : M - 1) * K + 8 * g;
+// The sums of slice `block` % kStreamTSlices for ranks 32 (block / kStreamTSlices) .. + 31: waves 0 to 3 the first sixteen ranks, every fourth
+// step each, waves 4 to 7 the others.  R % 8 == 0.
+struct SharedTProducts {
+    uint4 a[kShareSteps], x[kShareSteps];
+    int first, end;   // steps of 32 columns of this wave: first, first + 4, ..
+
+    __device__ __forceinline__ void request(const uint16_t* __restrict__ x_in, int M, int64_t K, const uint16_t* __restrict__ a_cat, int R, int block,
+                                            int wave, int lane) {
+        const int i16 = lane & 15, g = lane >> 4;
+        const int b = block % kStreamTSlices, rt = 2 * (block / kStreamTSlices) + (wave >> 2), units = (int)(K >> 5);
+        first = units * b / kStreamTSlices + (wave & 3);
+        end = 16 * rt < R ? units * (b + 1) / kStreamTSlices : 0;   // (ranks past R: nothing)
+        const uint16_t* xr = x_in + (int64_t)(i16 < M ? i16 : M - 1) * K + 8 * g;
         // sixteen ranks of 32 rows of A_cat: 16 bytes a lane, row lane / 2 (ranks past R read valid ones and are dropped)
         const int r0 = 16 * rt + 8 * (lane & 1);
         const uint16_t* ar = a_cat + (int64_t)(lane >> 1) * R + (r0 < R ? r0 : R - 8);
-        for (int u0 = u_begin + (wave & 3); u0 < u_end; u0 += 4 * kShareBatch) {
-            uint4 aq[kShareBatch], xq[kShareBatch];
 #pragma unroll
-            for (int t = 0; t < kShareBatch; ++t) {
-                const int u = u0 + 4 * t < u_end ? u0 + 4 * t : u_end - 1;
-                aq[t] = *reinterpret_cast<const uint4*>(ar + (int64_t)u * 32 * R);
-                xq[t] = *reinterpret_cast<const uint4*>(xr + 32 * (int64_t)u);
+        for (int t = 0; t < kShareSteps; ++t) {
+            a[t] = x[t] = make_uint4(0, 0, 0, 0);
+            if (first + 4 * t < end) {   // uniform
+                a[t] = *reinterpret_cast<const uint4*>(ar + (int64_t)(first + 4 * t) * 32 * R);
+                x[t] = *reinterpret_cast<const uint4*>(xr + 32 * (int64_t)(first + 4 * t));
             }
-#pragma unroll
-            for (int t = 0; t < kShareBatch; ++t) *reinterpret_cast<uint4*>(tiles + 512 * t + 8 * lane) = aq[t];
-            __builtin_amdgcn_wave_barrier();   // LDS executes a wave's accesses in order
-#pragma unroll
-            for (int t = 0; t < kShareBatch; ++t)
-                if (u0 + 4 * t < u_end) {   // uniform
-                    const uint16_t* col = tiles + 512 * t + (8 * g + (i16 >> 2)) * 16 + 4 * (i16 & 3);
-                    const uint2 lo = lds_read_tr4(col), hi = lds_read_tr4(col + 64);
-                    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(xq[t]), as_bf16x8(make_uint4(lo.x, lo.y, hi.x, hi.y)), acc, 0, 0, 0);
-                }
-            __builtin_amdgcn_wave_barrier();
         }
     }
+    // As accumulators of eight waves in `red` [8][4][64].  tiles: kShareTileBytes of this wave.
+    __device__ __forceinline__ void multiply(uint16_t* tiles, float* red, int wave, int lane) {
+        const int i16 = lane & 15, g = lane >> 4;
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int e = 0; e < 4; ++e) red[(wave * 4 + e) * 64 + lane] = acc[e];
-}
-
-// One wave leaves what shared_t_products has formed to all workgroups: sums [slice][M][Rpad].
-__device__ __forceinline__ void shared_t_hand_out(const SharedT& p, float* sums, int M, int R, int Rpad, int block, int workgroups, const float* red,
-                                                  int lane) {
-    const int b = block % kStreamTSlices, rp = block / kStreamTSlices;
-    const Buffer out = make_buffer(sums, (uint64_t)kStreamTSlices * M * Rpad * 4);
+        for (int t = 0; t < kShareSteps; ++t) *reinterpret_cast<uint4*>(tiles + 512 * t + 8 * lane) = a[t];
+        __builtin_amdgcn_wave_barrier();   // LDS executes a wave's accesses in order
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {   // four ranks of a token each
-        const int q = lane + 64 * i, m = q >> 3, rt = (q >> 2) & 1, col = 4 * (q & 3), r = 32 * rp + 16 * rt + col;
-        f32x4 s = {0.f, 0.f, 0.f, 0.f};
+        for (int t = 0; t < kShareSteps; ++t)
+            if (first + 4 * t < end) {     // uniform
+                const uint16_t* col = tiles + 512 * t + (8 * g + (i16 >> 2)) * 16 + 4 * (i16 & 3);
+                const uint2 lo = lds_read_tr4(col), hi = lds_read_tr4(col + 64);
+                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(x[t]), as_bf16x8(make_uint4(lo.x, lo.y, hi.x, hi.y)), acc, 0, 0, 0);
+            }
+        __builtin_amdgcn_wave_barrier();
 #pragma unroll
-        for (int w = 0; w < 4; ++w) s += *reinterpret_cast<const f32x4*>(red + ((4 * rt + w) * 4 + (m & 3)) * 64 + 16 * (m >> 2) + col);
-        if (r >= R) s = f32x4{0.f, 0.f, 0.f, 0.f};   // (R % 8 == 0: all four or none)
-        shared_store4(out, m < M ? (uint32_t)((b * M + m) * Rpad + r) * 4 : kPastBuffer, __builtin_bit_cast(u32x4, s));
+        for (int e = 0; e < 4; ++e) red[(wave * 4 + e) * 64 + lane] = acc[e];
     }
-    stores_done();
-    uint64_t* words = p.words + (int64_t)block * workgroups;
-    constexpr int kAtOnce = 4;
-    for (int c0 = lane; c0 < workgroups; c0 += 64 * kAtOnce) {
-        uint64_t before[kAtOnce];
+};
+
+// One wave leaves what the waves have formed to all workgroups: sums [slice][M][Rpad], then the words.  What the last words held, which only
+// matters where a workgroup has given up, is looked at by finish(), so that the wave goes on with its stream meanwhile.
+struct SharedTHandOut {
+    static constexpr int kAtOnce = 4;
+    uint64_t before[kAtOnce];
+    uint64_t* last;   // the words of the last exchanges, this lane's every 64th
+
+    __device__ __forceinline__ void exchange(const SharedT& p, int left) {
 #pragma unroll
         for (int i = 0; i < kAtOnce; ++i) {
             before[i] = 0;
-            if (c0 + 64 * i < workgroups)
-                before[i] = __hip_atomic_exchange(words + c0 + 64 * i, p.tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (64 * i < left) before[i] = __hip_atomic_exchange(last + 64 * i, p.tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
+    }
+    __device__ __forceinline__ void start(const SharedT& p, float* sums, int M, int R, int Rpad, int block, int workgroups, const float* red, int lane) {
+        const int b = block % kStreamTSlices, rp = block / kStreamTSlices;
+        const Buffer out = make_buffer(sums, (uint64_t)kStreamTSlices * M * Rpad * 4);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {   // four ranks of a token each
+            const int q = lane + 64 * i, m = q >> 3, rt = (q >> 2) & 1, col = 4 * (q & 3), r = 32 * rp + 16 * rt + col;
+            f32x4 s = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int w = 0; w < 4; ++w) s += *reinterpret_cast<const f32x4*>(red + ((4 * rt + w) * 4 + (m & 3)) * 64 + 16 * (m >> 2) + col);
+            if (r >= R) s = f32x4{0.f, 0.f, 0.f, 0.f};   // (R % 8 == 0: all four or none)
+            shared_store4(out, m < M ? (uint32_t)((b * M + m) * Rpad + r) * 4 : kPastBuffer, __builtin_bit_cast(u32x4, s));
+        }
+        stores_done();
+        last = p.words + (int64_t)block * workgroups + lane;
+        int left = workgroups - lane;
+        exchange(p, left);
+        while (workgroups > 64 * kAtOnce) {   // (uniform)
+            finish(p);
+            last += 64 * kAtOnce;
+            left -= 64 * kAtOnce;
+            workgroups -= 64 * kAtOnce;
+            exchange(p, left);
+        }
+    }
+    __device__ __forceinline__ void finish(const SharedT& p) {
 #pragma unroll
         for (int i = 0; i < kAtOnce; ++i)
-            if (before[i] == p.tag) leave_clear(words + c0 + 64 * i);   // that workgroup has formed T itself
+            if (before[i] == p.tag) leave_clear(last + 64 * i);   // that workgroup has formed T itself
+    }
+};
+
+// A workgroup that does nothing else
+__device__ __forceinline__ void shared_t_workgroup(const SharedT& p, const uint16_t* __restrict__ x, int M, int64_t K,
+                                                   const uint16_t* __restrict__ a_cat, int R, int Rpad, float* sums, uint16_t* tiles, float* red,
+                                                   int wave, int lane) {
+    SharedTProducts products;
+    products.request(x, M, K, a_cat, R, (int)blockIdx.x, wave, lane);
+    products.multiply(tiles, red, wave, lane);
+    __syncthreads();
+    if (wave == 0) {
+        SharedTHandOut out;
+        out.start(p, sums, M, R, Rpad, (int)blockIdx.x, (int)gridDim.x - p.extra, red, lane);
+        out.finish(p);
     }
 }
 
@@ -171,7 +206,9 @@ __device__ __forceinline__ void shared_t_alone(const uint16_t* __restrict__ x, i
 #pragma unroll 1
             for (int b = 0; b < kStreamTSlices; ++b) {
                 __syncthreads();
-                shared_t_products(x, M, K, a_cat, R, rp * kStreamTSlices + b, tiles, red, wave, lane);
+                SharedTProducts products;
+                products.request(x, M, K, a_cat, R, rp * kStreamTSlices + b, wave, lane);
+                products.multiply(tiles, red, wave, lane);
                 __syncthreads();
                 float s = 0.f;
 #pragma unroll

@@ -69,6 +69,9 @@ def test_close_to_the_oracle_whoever_forms_t(kind, M, K, N, R, density):
     y = _call(kind, args, M, K, N, R, extra)
     assert float(np.max(np.abs(y_to_f64(y) - ref))) <= REL_TOL * float(np.max(np.abs(ref)))
     assert torch.equal(_call(kind, args, M, K, N, R, extra, 0xFF), y)   # what the workspace held before is of no account
+    # A_cat that starts inside a vector: a launch in front
+    off = torch.empty(K * R + 1, dtype=args[4].dtype, device=dev())[1:].view(K, R).copy_(args[4])
+    assert torch.equal(_call(kind, [*args[:4], off, args[5]], M, K, N, R, extra), y)
     salr.lib().salr_set_handover_polls(0)   # workgroups that do not find T at once form it themselves
     try:
         for _ in range(3):
