@@ -29,6 +29,7 @@
 #include "salr_device.hpp"
 #include "salr_internal.hpp"
 #include "salr_linear_common.hpp"
+#include "salr_shared_t.hpp"
 
 namespace salr {
 
@@ -256,7 +257,8 @@ __global__ __launch_bounds__(kS4Threads, MT <= 4 ? 4 : 2) void linear_2of4_kerne
 // no barrier in the stream, no split of K over workgroups and no reducing launch.  Per chunk a lane (n, g) loads
 // bitmap word g and its 16 stored values of row n (4 + 32 bytes) and, as lane (m, g) of the dense operand, the 32
 // activations X[m][32 g .. 32 g + 31] of the chunk (64 contiguous bytes, from the L2); S chunks are in flight.
-// Wave w applies rank step w of the adapters (T summed from the pre-kernel's partials into LDS).
+// Wave w applies rank step w of the adapters (T summed from the pre-kernel's partials into LDS, or, kShareT, from those that the first
+// workgroups of the launch leave, salr_shared_t.hpp).
 // ---------------------------------------------------------------------------------------------------
 template <int MT>
 struct S4WaveStage {
@@ -265,11 +267,12 @@ struct S4WaveStage {
     s4_u32x4 xq[4 * MT];   // xq[4 mt + s]: X[16 mt + m][32 g + 8 s .. + 7] of the chunk
 };
 
-template <int MT, int S>
+template <int MT, int S, bool kShareT>
 __global__ __launch_bounds__(kS4Threads, 4) void linear_2of4_stream_kernel(
     const uint16_t* __restrict__ x, int M, int64_t K, int64_t N, const uint32_t* __restrict__ bitmap,
-    const uint16_t* __restrict__ values, const uint32_t* __restrict__ row_offsets, const float* __restrict__ t_partial,
-    const uint16_t* __restrict__ b_cat, int R, int Rpad, uint16_t* __restrict__ y) {
+    const uint16_t* __restrict__ values, const uint32_t* __restrict__ row_offsets, float* t_partial,
+    const uint16_t* __restrict__ a_cat, const uint16_t* __restrict__ b_cat, int R, int Rpad, uint16_t* __restrict__ y, SharedT shared) {
+    static_assert(!kShareT || (MT == 1 && kS4Waves == kShareWaves));
     constexpr int kTRows = 16 * MT;
     __shared__ __attribute__((aligned(16))) float red[kS4Waves * MT * 256];
     __shared__ __attribute__((aligned(16))) uint16_t t_lds[kTRows * kMaxRankPadded];
@@ -279,7 +282,17 @@ __global__ __launch_bounds__(kS4Threads, 4) void linear_2of4_stream_kernel(
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n = lane & 15;
     const int g = lane >> 4;
-    const int64_t n0 = (int64_t)blockIdx.x * 16;
+    const int group = (int)blockIdx.x - (kShareT ? shared.extra : 0);   // of 16 rows
+    __shared__ __attribute__((aligned(16))) uint16_t t_tiles[kShareT ? kS4Waves * kShareTileBytes / 2 : 8];
+    uint16_t* tiles = t_tiles + (kShareT ? wave * kShareTileBytes / 2 : 0);
+    if constexpr (kShareT) {
+        static_assert(sizeof(t_lds) >= kShareRedBytes);
+        if (group < 0) {   // the same for the whole workgroup
+            shared_t_workgroup(shared, x, M, K, a_cat, R, Rpad, t_partial, tiles, reinterpret_cast<float*>(t_lds), wave, lane);
+            return;
+        }
+    }
+    const int64_t n0 = (int64_t)group * 16;
     const int64_t row_c = n0 + n < N ? n0 + n : N - 1;   // rows past N are copies of row N-1, dropped at the store
     const int64_t wpr = K >> 5;
     const int64_t chunks_total = wpr >> 2;
@@ -327,7 +340,7 @@ __global__ __launch_bounds__(kS4Threads, 4) void linear_2of4_stream_kernel(
     }
 
     // T = sum of the pre-kernel's split-K partials, rounded once to bf16, kept in LDS
-    if (R > 0) {
+    if (R > 0 && !kShareT) {
         const int groups = M * (Rpad >> 2);  // float4 groups of T
         for (int i = tid; i < groups; i += kS4Threads) {
             float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -344,6 +357,24 @@ __global__ __launch_bounds__(kS4Threads, 4) void linear_2of4_stream_kernel(
             *reinterpret_cast<uint2*>(&t_lds[m * kMaxRankPadded + 4 * r4]) = o;
         }
     }
+
+    const bool forms_t = kShareT && shared.extra == 0 && group < kStreamTSlices * (Rpad >> 5);   // the same for the whole workgroup
+    if constexpr (kShareT)
+        if (forms_t) {
+            SharedTProducts products;
+            products.request(x, M, K, a_cat, R, group, wave, lane);
+            products.multiply(tiles, reinterpret_cast<float*>(t_lds), wave, lane);
+            __syncthreads();
+        }
+    auto hand_out = [&]() {   // behind the first requests of the stream, whose way is as long as that of the sums
+        if constexpr (kShareT)
+            if (forms_t && wave == 0) {
+                SharedTHandOut t_out;
+                t_out.start(shared, t_partial, M, R, Rpad, group, (int)gridDim.x, reinterpret_cast<const float*>(t_lds), lane);
+                t_out.finish(shared);
+            }
+    };
+    SharedTReader t_reader(shared, t_partial, M, Rpad, (int)gridDim.x - shared.extra, group, wave, lane);
 
     f32x4 acc[MT];
 #pragma unroll
@@ -364,10 +395,12 @@ __global__ __launch_bounds__(kS4Threads, 4) void linear_2of4_stream_kernel(
         }
     };
 
+    if (c_begin >= c_end) hand_out();
     if (c_begin < c_end) {
         S4WaveStage<MT> st[S];
 #pragma unroll
         for (int i = 0; i < S; ++i) issue(st[i], c_begin + i);   // (chunks past the slice are loaded and dropped)
+        hand_out();
         int64_t c = c_begin;
         for (; c + 2 * S <= c_end; c += S) {   // rounds without a condition, see the row-tiled kernel below
 #pragma unroll
@@ -376,6 +409,7 @@ __global__ __launch_bounds__(kS4Threads, 4) void linear_2of4_stream_kernel(
                 issue(st[i], c + i + S);
             }
         }
+        if (kShareT) t_reader.look();
         for (; c < c_end; c += S) {
 #pragma unroll
             for (int i = 0; i < S; ++i) {
@@ -385,7 +419,23 @@ __global__ __launch_bounds__(kS4Threads, 4) void linear_2of4_stream_kernel(
         }
     }
 
+    __shared__ uint32_t t_missing[kShareT ? kS4Waves : 1];
+    if constexpr (kShareT) {
+        if (t_reader.check()) t_reader.request();   // (uniform)
+        const bool fetched = t_reader.finish(shared, t_lds, Rpad);
+        if (lane == 0) t_missing[wave] = fetched ? 0u : 1u;
+    }
+
     __syncthreads();  // T in LDS is complete
+
+    if constexpr (kShareT) {
+        uint32_t missing = 0;
+#pragma unroll
+        for (int w = 0; w < kS4Waves; ++w) missing |= t_missing[w];
+        missing = __builtin_amdgcn_readfirstlane(missing);   // (the same in all lanes)
+        if (wave == 0) t_reader.leave(missing == 0);
+        if (missing != 0) shared_t_alone(x, M, K, a_cat, R, Rpad, tiles, t_lds, tid, wave, lane);
+    }
 
     // ---- adapter k-step of this wave (Sec. 3.2): first operand = B_cat columns, second = T rows from LDS
     if (has_rank_step) {
@@ -415,10 +465,19 @@ __global__ __launch_bounds__(kS4Threads, 4) void linear_2of4_stream_kernel(
 }
 
 template <int MT, int S>
-static void launch_2of4_stream_t(const LinearArgs& a, const float* t_partial, hipStream_t stream, const TimingEvents& ev) {
-    const dim3 grid((unsigned)((a.N + 15) / 16));
-    SALR_LAUNCH((linear_2of4_stream_kernel<MT, S>), grid, dim3(kS4Threads), stream, ev, a.x, (int)a.M, a.K, a.N, a.bitmap,
-                a.values, a.row_offsets, t_partial, a.b_cat, (int)a.R, (int)adapter_rank_padded(a.R), a.y);
+static void launch_2of4_stream_t(const LinearArgs& a, float* t_partial, hipStream_t stream, const TimingEvents& ev) {
+    const SharedT shared = shared_t_of(a, a.room);
+    const dim3 grid((unsigned)((a.N + 15) / 16 + shared.extra));
+    auto go = [&](auto kernel) {
+        SALR_LAUNCH(kernel, grid, dim3(kS4Threads), stream, ev, a.x, (int)a.M, a.K, a.N, a.bitmap, a.values, a.row_offsets, t_partial, a.a_cat,
+                    a.b_cat, (int)a.R, (int)adapter_rank_padded(a.R), a.y, shared);
+    };
+    if (shared.words != nullptr) {
+        go(linear_2of4_stream_kernel<MT, S, true>);
+        return;
+    }
+    if (a.R > 0) launch_adapter_partial(a, stream);   // split-K partials of T, summed inside the kernel
+    go(linear_2of4_stream_kernel<MT, S, false>);
 }
 
 template <int MT, int S>
@@ -432,8 +491,7 @@ static void launch_2of4_t(const LinearArgs& a, const float* t_partial, int kspli
 hipError_t launch_linear_2of4(const LinearArgs& a, hipStream_t stream, const TimingEvents& ev) {
     const int ksplit = rowtile_ksplit(a.M, a.K, a.N);
     char* base = reinterpret_cast<char*>(a.t);
-    const float* t_partial = reinterpret_cast<const float*>(base);
-    if (a.R > 0) launch_adapter_partial(a, stream);   // split-K partials of T, summed inside the kernel
+    float* t_partial = reinterpret_cast<float*>(base);
     float* y_partial = reinterpret_cast<float*>(base + rowtile_t_bytes(a.M, a.K, a.R));
     // Up to 16 tokens the barrier-free kernel is ahead where the call is short (layers of up to 2^25 elements: no
     // reducing launch, no split of K) and, on any layer, up to 4 tokens (little X to pull through the L2 per workgroup);
@@ -442,6 +500,7 @@ hipError_t launch_linear_2of4(const LinearArgs& a, hipStream_t stream, const Tim
         launch_2of4_stream_t<1, 4>(a, t_partial, stream, ev);
         return hipGetLastError();
     }
+    if (a.R > 0) launch_adapter_partial(a, stream);
     if (a.M <= 16) launch_2of4_t<1, 4>(a, t_partial, ksplit, y_partial, stream, ev);
     else if (a.M <= 32) launch_2of4_t<2, 4>(a, t_partial, ksplit, y_partial, stream, ev);
     else if (a.M <= 64) launch_2of4_t<4, 2>(a, t_partial, ksplit, y_partial, stream, ev);
