@@ -312,13 +312,12 @@ __global__ __launch_bounds__(kRtThreads, 2) void linear_rowtile_kernel(
     u32x4 left[4][kWalk];
     auto walk = [&](int c0) {
 #pragma unroll
-        for (int i = 0; i < kWalk; ++i)
+        for (int i = 0; i < kWalk; ++i) {
+            if (c0 + 16 * i >= c_begin) break;   // uniform
+            const int c = c0 + 16 * i + n;
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int c = c0 + 16 * i + n;
-                left[r][i] = u32x4{0, 0, 0, 0};
-                if (c0 + 16 * i < c_begin) left[r][i] = buffer_load4(bits, c < c_begin ? (uint32_t)((4 * r + g) * row_bytes + 16 * c) : kPastBuffer);   // uniform
-            }
+            for (int r = 0; r < 4; ++r) left[r][i] = buffer_load4(bits, c < c_begin ? (uint32_t)((4 * r + g) * row_bytes + 16 * c) : kPastBuffer);
+        }
     };
     walk(walk_begin);
     u32x4 quad_next = load_quad(c_begin + 4);
@@ -359,19 +358,23 @@ __global__ __launch_bounds__(kRtThreads, 2) void linear_rowtile_kernel(
         for (int c0 = walk_begin; c0 < c_begin; c0 += 16 * kWalk) {
             if (c0 > walk_begin) walk(c0);
 #pragma unroll
-            for (int i = 0; i < kWalk; ++i)
+            for (int i = 0; i < kWalk; ++i) {
+                if (c0 + 16 * i >= c_begin) break;   // uniform (short rows: counting what is not there was 0.5 us of a call)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) before[r] = popc4(left[r][i], before[r]);
+            }
         }
-        uint32_t mine = 0;
+        // (in registers, by rotations of 16 lanes, and one exchange: as 20 exchanges through LDS they were slower on short rows)
+        uint32_t held = 0;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-#pragma unroll
-            for (int o = 1; o < 16; o <<= 1) before[r] += __shfl_xor(before[r], o, 64);
-            const uint32_t of_row = __shfl(before[r], 16 * (n & 3), 64);
-            mine = n >> 2 == r ? of_row : mine;
+            before[r] += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)before[r], 0x128, 0xF, 0xF, false);   // row_ror:8, 4, 2, 1
+            before[r] += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)before[r], 0x124, 0xF, 0xF, false);
+            before[r] += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)before[r], 0x122, 0xF, 0xF, false);
+            before[r] += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)before[r], 0x121, 0xF, 0xF, false);
+            held = n >> 2 == r ? before[r] : held;
         }
-        cur += mine;
+        cur += __shfl(held, 16 * (n & 3) + (n & 12), 64);   // row n = 4 (n / 4) + n % 4
     }
 
     const uint64_t left_over = (uint64_t)total - first;   // values from the buffer's start on; whole vectors of them are readable
