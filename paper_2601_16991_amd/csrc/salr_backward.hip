@@ -98,8 +98,9 @@ hipError_t launch_linear_backward(const uint16_t* x, const uint16_t* dy, int64_t
     const bool short_chains = K <= 6144 && N <= 6144, few = M * (K + N) * ((p.Rpad + 31) / 32) <= 6 * N * K;
     const bool with_decode = want_dx && R % 8 == 0 && (short_chains || few);
     if (R > 0 && !with_decode) launch_backward_t(dy_b, x_a, M, R, stream);
+    const bool beside = p.words && handover_aligned(workspace);
     RowProducts products{{x, dy}, {at(p.off_tp_t), at(p.off_tt_t)}, {da != nullptr ? K : 0, db != nullptr ? N : 0}, {da, db}, M, R, p.Rpad, p.ks_tn,
-                         reinterpret_cast<float*>(ws + p.off_tn), reinterpret_cast<uint64_t*>(ws + p.off_words), p.words ? next_handover_tag() : 0};
+                         reinterpret_cast<float*>(ws + p.off_tn), reinterpret_cast<uint64_t*>(ws + p.off_words), beside ? next_handover_tag() : 0};
     bool gradients_done = false;
     if (want_dx) {
         const hipError_t e = launch_decode_transposed_frags(bitmap, values, row_offsets, N, K, a_cat, R, at(p.off_wf), with_decode ? dy_b : none,
@@ -107,7 +108,7 @@ hipError_t launch_linear_backward(const uint16_t* x, const uint16_t* dy, int64_t
         if (e != hipSuccess) return e;
         const TimingEvents none;
         gradients_done = launch_frag_gemm(dy, M, N, K, at(p.off_wf), at(p.off_tp), p.Rpad, dx, reinterpret_cast<float*>(ws + p.off_ypart), p.y_room,
-                                          none, stream, p.words ? &products : nullptr);
+                                          none, stream, beside ? &products : nullptr);
     }
     if (want_dadb && R > 0 && !gradients_done) {
         products.words = nullptr;

@@ -415,6 +415,9 @@ inline size_t rowtile_pair_bytes(int64_t M, int64_t N, int64_t R, const RowtileP
     return round_up_256((size_t)M * (size_t)Rpad * sizeof(uint16_t)) + (size_t)(pairs + t_blocks) * sizeof(uint64_t);
 }
 uint64_t next_handover_tag();   // 64 bits that no other call of the process has
+// The words are exchanged 64 bits at a time, which an address that is no multiple of 8 does not allow.  A call whose workspace starts inside a
+// vector, against what it is told to bring, has its launches in front and behind.
+inline bool handover_aligned(const void* workspace) { return (uintptr_t)workspace % 16 == 0; }
 int handover_polls();           // looks before a workgroup does without what it waits for (salr_set_handover_polls)
 
 // T handed over inside a small-batch kernel's launch (salr_shared_t.hpp): one word per slice of T, 32 ranks and workgroup behind the sums.
@@ -443,7 +446,7 @@ inline bool shares_t(int64_t M, int64_t K, int64_t N, int64_t R) {
 }
 inline SharedT shared_t_of(const LinearArgs& a, size_t room) {
     SharedT p;
-    if (!shares_t(a.M, a.K, a.N, a.R) || room < shared_t_bytes(a.M, a.N, a.R) || (uintptr_t)a.a_cat % 16 != 0) return p;
+    if (!shares_t(a.M, a.K, a.N, a.R) || room < shared_t_bytes(a.M, a.N, a.R) || (uintptr_t)a.a_cat % 16 != 0 || !handover_aligned(a.t)) return p;
     p.words = reinterpret_cast<uint64_t*>(reinterpret_cast<char*>(a.t) + shared_t_sums_bytes(a.M, a.R));
     p.tag = next_handover_tag();
     p.polls = handover_polls();

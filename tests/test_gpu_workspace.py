@@ -121,6 +121,52 @@ def test_row_tiled_calls_on_four_bit_values_stay_inside_their_workspace(M, K, N,
     assert torch.equal(again, y)
 
 
+# the small-batch kernels with T from workgroups beside their own work and from workgroups of their own, the row-tiled kernel in one launch, and
+# the gradients beside the matrix stage
+@pytest.mark.parametrize("kind,M,K,N,R", [("plain", 16, 1024, 4096, 32), ("plain", 5, 2048, 241, 8), ("prepared", 3, 2048, 1025, 64), ("codes", 16, 1024, 4096, 32),
+                                          ("2of4", 16, 1024, 4096, 32), ("plain", 24, 1120, 8384, 8), ("codes", 33, 1024, 8320, 16), ("backward", 96, 160, 192, 40)])
+@pytest.mark.parametrize("start", [4, 8])
+def test_workspaces_that_start_inside_a_vector(kind, M, K, N, R, start):
+    """A workspace is told to be aligned to 256 bytes, and one that is not ran slowly and still does: nothing in it is exchanged 64 bits at a
+    time.  The same bits (of the backward pass: dX, the gradients being cut into other slices)."""
+    import paper_2601_16991_amd as salr
+    args, ref, nnz = _layer(M, K, N, R)
+    extra = []
+    if kind == "2of4":
+        w = oracle.mask_nm(wl.gaussian_bf16((N, K), 0.02, 1), 2, 4)
+        args[1:4] = [f(v) for f, v in zip((to_dev_u32, to_dev_u16, to_dev_u32), oracle.encode(w))]
+    elif kind == "prepared":
+        extra = [salr.build_slice_table(args[1], args[3], K)]
+    elif kind == "codes":
+        args[2:3], extra = salr.nf4_quantize(args[2]), [nnz]
+    elif kind == "backward":
+        dy = to_dev_u16(wl.gaussian_bf16((M, N), 1.0, 9))
+    call = {"plain": salr.salr_sparse_lowrank_linear, "prepared": salr.salr_sparse_lowrank_linear_prepared, "codes": salr.salr_qsalr_linear,
+            "2of4": salr.salr_sparse_lowrank_linear_2of4, "backward": salr.salr_sparse_lowrank_linear_backward}[kind]
+    size = (salr.salr_linear_backward_workspace_bytes(M, K, N, R, True, True) if kind == "backward" else
+            salr.salr_qsalr_linear_workspace_bytes_fastest(M, K, N, R, nnz) if kind == "codes" else
+            salr.salr_linear_2of4_workspace_bytes(M, K, N, R) if kind == "2of4" else salr.salr_linear_workspace_bytes_fastest(M, K, N, R))
+    out = []
+    for at in (0, start):
+        print(f"[workspace] {kind} M{M} K{K} N{N} R{R}: {size} bytes from {at} on", flush=True)
+        buf = torch.full((size + 4096,), 0x5A, dtype=torch.uint8, device=dev())
+        y = torch.empty((M, K if kind == "backward" else N), dtype=torch.int16, device=dev())
+        grads = [torch.empty((K, R), dtype=torch.int16, device=dev()), torch.empty((R, N), dtype=torch.int16, device=dev())]
+        if kind == "backward":
+            call(args[0], dy, *args[1:], y, *grads, buf[at:at + size])
+        else:
+            call(*args[:-2], *extra, *args[-2:], y, buf[at:at + size])
+        torch.cuda.synchronize()
+        assert bool((buf[:at] == 0x5A).all()) and bool((buf[at + size:] == 0x5A).all())
+        out.append((y, *(g.view(torch.bfloat16).float() for g in grads)))
+    assert torch.equal(out[0][0], out[1][0])
+    if kind == "backward":
+        for g, h in zip(out[0][1:], out[1][1:]):
+            assert float((g - h).abs().max()) <= 2.0 ** -7 * float(g.abs().max())
+    elif kind in ("plain", "prepared"):
+        assert _ok(out[1][0], ref)
+
+
 @pytest.mark.parametrize("form", ["told", "none", "quantised"])
 def test_runs_where_the_allocator_has_no_more(form):
     """The decoded weight of this layer takes 34 MB and its split sums more; the allocator may hand out the result and little else (in
