@@ -374,7 +374,6 @@ __global__ __launch_bounds__(kS4Threads, 4) void linear_2of4_stream_kernel(
                 t_out.finish(shared);
             }
     };
-    SharedTReader t_reader(shared, t_partial, M, Rpad, (int)gridDim.x - shared.extra, group, wave, lane);
 
     f32x4 acc[MT];
 #pragma unroll
@@ -395,27 +394,30 @@ __global__ __launch_bounds__(kS4Threads, 4) void linear_2of4_stream_kernel(
         }
     };
 
-    if (c_begin >= c_end) hand_out();
+    S4WaveStage<MT> st[S];
+    int64_t c = c_begin;
     if (c_begin < c_end) {
-        S4WaveStage<MT> st[S];
 #pragma unroll
         for (int i = 0; i < S; ++i) issue(st[i], c_begin + i);   // (chunks past the slice are loaded and dropped)
-        hand_out();
-        int64_t c = c_begin;
-        for (; c + 2 * S <= c_end; c += S) {   // rounds without a condition, see the row-tiled kernel below
+    }
+    hand_out();
+    for (; c + 2 * S <= c_end; c += S) {   // rounds without a condition, see the row-tiled kernel below
 #pragma unroll
-            for (int i = 0; i < S; ++i) {
-                consume(st[i]);
-                issue(st[i], c + i + S);
-            }
+        for (int i = 0; i < S; ++i) {
+            consume(st[i]);
+            issue(st[i], c + i + S);
         }
-        if (kShareT) t_reader.look();
-        for (; c < c_end; c += S) {
+    }
+    // (Here and not in front of the stream, tokens past M not clamped below, addresses of shared_t_alone's own: with all of that kept through
+    // the stream five registers were spilled.  us a call with / without: 4096 x 4096 rank 32 16 tokens 11.9 / 11.1, one 9.8 / 9.0; 4096 x 1024
+    // 10.1 / 9.4 and 8.0 / 6.6.)
+    SharedTReader t_reader(shared, t_partial, M, Rpad, (int)gridDim.x - shared.extra, group, wave, lane);
+    if (kShareT) t_reader.look();
+    for (; c < c_end; c += S) {
 #pragma unroll
-            for (int i = 0; i < S; ++i) {
-                if (c + i < c_end) consume(st[i]);   // wave-uniform conditions
-                if (c + i + S < c_end) issue(st[i], c + i + S);
-            }
+        for (int i = 0; i < S; ++i) {
+            if (c + i < c_end) consume(st[i]);   // wave-uniform conditions
+            if (c + i + S < c_end) issue(st[i], c + i + S);
         }
     }
 
@@ -434,7 +436,10 @@ __global__ __launch_bounds__(kS4Threads, 4) void linear_2of4_stream_kernel(
         for (int w = 0; w < kS4Waves; ++w) missing |= t_missing[w];
         missing = __builtin_amdgcn_readfirstlane(missing);   // (the same in all lanes)
         if (wave == 0) t_reader.leave(missing == 0);
-        if (missing != 0) shared_t_alone(x, M, K, a_cat, R, Rpad, tiles, t_lds, tid, wave, lane);
+        // (addresses of X that are not the first request's, which would be kept through the stream)
+        int tokens = M;
+        asm("" : "+s"(tokens));
+        if (missing != 0) shared_t_alone(x, tokens, K, a_cat, R, Rpad, tiles, t_lds, tid, wave, lane);
     }
 
     // ---- adapter k-step of this wave (Sec. 3.2): first operand = B_cat columns, second = T rows from LDS
@@ -442,7 +447,7 @@ __global__ __launch_bounds__(kS4Threads, 4) void linear_2of4_stream_kernel(
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
             const int m = 16 * mt + n;
-            const uint4 tq = *reinterpret_cast<const uint4*>(&t_lds[(m < M ? m : M - 1) * kMaxRankPadded + wave * 32 + 8 * g]);
+            const uint4 tq = *reinterpret_cast<const uint4*>(&t_lds[m * kMaxRankPadded + wave * 32 + 8 * g]);   // (past M: never stored)
             acc[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(bq), as_bf16x8(tq), acc[mt], 0, 0, 0);
         }
     }
