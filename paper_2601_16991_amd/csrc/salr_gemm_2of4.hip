@@ -191,11 +191,12 @@ __global__ __launch_bounds__(64 * kWN * kWM, kWN * kWM <= 4 ? 2 : 1) void gemm_2
                 const int64_t nc = n < N ? n : N - 1;
                 uint32_t e[8];
 #pragma unroll
-                for (int j = 0; j < 8; ++j) {  // rows past R meet the zero padding of T; clamp instead of predicating
+                for (int j = 0; j < 8; ++j) {  // (past R: dropped below)
                     const int r = rs * 32 + 8 * kb + j;
                     e[j] = (uint32_t)b_cat[(int64_t)(r < R ? r : R - 1) * N + nc];
                 }
-                bq[i] = g4_u32x4{e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16), e[6] | (e[7] << 16)};
+                bq[i] = __builtin_bit_cast(g4_u32x4, ranks_below(make_uint4(e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16), e[6] | (e[7] << 16)),
+                                                                 rs * 32 + 8 * kb, R));
             }
 #pragma unroll
             for (int j = 0; j < kMJ; ++j) {

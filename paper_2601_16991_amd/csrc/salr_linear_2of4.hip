@@ -122,7 +122,7 @@ __global__ __launch_bounds__(kS4Threads, MT <= 4 ? 4 : 2) void linear_2of4_kerne
         const int r0 = rs * 32 + 8 * g;
         uint32_t e[8];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {  // rows past R meet the zero padding of T; clamp instead of predicating
+        for (int j = 0; j < 8; ++j) {  // clamp instead of predicating; ranks_below drops those past R
             const int r = r0 + j < R ? r0 + j : R - 1;
             e[j] = (uint32_t)b_cat[(int64_t)r * N + row_c];
         }
@@ -215,7 +215,7 @@ __global__ __launch_bounds__(kS4Threads, MT <= 4 ? 4 : 2) void linear_2of4_kerne
         }
         __syncthreads();
         for (int rs = 0; rs < (Rpad >> 5); ++rs) {
-            const uint4 bq = rs == 0 ? bq0 : load_b_cat(rs);
+            const uint4 bq = ranks_below(rs == 0 ? bq0 : load_b_cat(rs), rs * 32 + 8 * g, R);
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt) {
                 const int m = 16 * mt + n;
@@ -332,7 +332,7 @@ __global__ __launch_bounds__(kS4Threads, 4) void linear_2of4_stream_kernel(
         const int r0 = wave * 32 + 8 * g;
         uint32_t e[8];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {  // rows past R meet the zero padding of T; clamp instead of predicating
+        for (int j = 0; j < 8; ++j) {  // clamp instead of predicating; ranks_below drops those past R
             const int r = r0 + j < R ? r0 + j : R - 1;
             e[j] = (uint32_t)b_cat[(int64_t)r * N + row_c];
         }
@@ -444,6 +444,7 @@ __global__ __launch_bounds__(kS4Threads, 4) void linear_2of4_stream_kernel(
 
     // ---- adapter k-step of this wave (Sec. 3.2): first operand = B_cat columns, second = T rows from LDS
     if (has_rank_step) {
+        bq = ranks_below(bq, wave * 32 + 8 * g, R);
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
             const int m = 16 * mt + n;

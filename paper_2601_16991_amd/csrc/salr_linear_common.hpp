@@ -17,6 +17,21 @@ __device__ __forceinline__ float bf16_bits_to_f32(uint32_t b) { return __uint_as
 
 __device__ __forceinline__ bf16x8 as_bf16x8(const uint4& q) { return __builtin_bit_cast(bf16x8, q); }
 
+// Eight ranks of B_cat from rank r0 on, as an MFMA operand, without those that fill the padded ones: they are read from the last rank and meet
+// zeros of T, but an infinite entry would make NaN of that.  At the operand's use and only where R is no multiple of 32, which is the same for
+// the whole launch: where the loads are packed it made the small-batch kernels wait for them (4096 x 4096, 16 tokens, 4 to 13 % of a call).
+__device__ __forceinline__ uint4 ranks_below(uint4 b, int r0, int R) {
+    if (R % 32 != 0) {
+        asm volatile("" : "+v"(r0));   // (here: what follows is not worked out ahead and kept through a stream)
+        const int n = R - r0;
+        b.x = n > 1 ? b.x : n > 0 ? b.x & 0xFFFFu : 0u;
+        b.y = n > 3 ? b.y : n > 2 ? b.y & 0xFFFFu : 0u;
+        b.z = n > 5 ? b.z : n > 4 ? b.z & 0xFFFFu : 0u;
+        b.w = n > 7 ? b.w : n > 6 ? b.w & 0xFFFFu : 0u;
+    }
+    return b;
+}
+
 // One block of 256 threads builds the slice-table entries of 32 rows (see kSliceTableSlices in salr_internal.hpp):
 // eight lanes per row, one per slice; a lane walks the chunks of its slice (16 bytes = 128 columns a load, four loads
 // in flight), then an exclusive scan over the row's eight lanes turns slice counts into value indices.  Used by

@@ -137,7 +137,7 @@ __global__ __launch_bounds__(kQWaves * 64, (S == 2 && MT == 1) ? 4 : 1) void lin
         const int r0 = wave * 32 + 8 * g;
         uint32_t e[8];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {  // rows past R meet the zero padding of T; clamp instead of predicating
+        for (int j = 0; j < 8; ++j) {  // clamp instead of predicating; ranks_below drops those past R
             const int r = r0 + j < R ? r0 + j : R - 1;
             e[j] = (uint32_t)b_cat[(int64_t)r * N + row_c];
         }
@@ -361,6 +361,7 @@ __global__ __launch_bounds__(kQWaves * 64, (S == 2 && MT == 1) ? 4 : 1) void lin
 
     // ---- adapter k-step of this wave (Sec. 3.2): A operand = T rows from LDS, B operand = bq
     if (has_rank_step) {
+        bq = ranks_below(bq, wave * 32 + 8 * g, R);
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
             const int m = 16 * mt + n;

@@ -134,7 +134,7 @@ struct RowtileAdapters {
     __device__ __forceinline__ void load_b(int rs) {
         const int64_t n_c = n0 + n < N ? n0 + n : N - 1;
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {   // ranks past R meet the zero padding of T
+        for (int j = 0; j < 8; ++j) {   // (past R: dropped by ranks_below)
             const int r = rs * 32 + 8 * g + j;
             e[j] = (uint32_t)b_cat[(int64_t)(r < R ? r : R - 1) * N + n_c];
         }
@@ -154,7 +154,7 @@ struct RowtileAdapters {
                 load_t(rs);
             }
             __builtin_amdgcn_sched_barrier(0);
-            const uint4 bq = make_uint4(e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16), e[6] | (e[7] << 16));
+            const uint4 bq = ranks_below(make_uint4(e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16), e[6] | (e[7] << 16)), rs * 32 + 8 * g, R);
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt)
                 acc[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(bq), __builtin_bit_cast(bf16x8, tq[mt]), acc[mt], 0, 0, 0);
@@ -581,11 +581,11 @@ __global__ __launch_bounds__(kRtThreads, 2) void linear_rowtile_kernel(
         for (int rs = 0; rs < (Rpad >> 5); ++rs) {
             uint32_t e[8];
 #pragma unroll
-            for (int j = 0; j < 8; ++j) {   // rows past R meet the zero padding of T; clamp instead of predicating
+            for (int j = 0; j < 8; ++j) {   // (past R: dropped by ranks_below)
                 const int k = rs * 32 + 8 * g + j;
                 e[j] = (uint32_t)b_cat[(int64_t)(k < R ? k : R - 1) * N + (row < N ? row : N - 1)];
             }
-            const uint4 bq = make_uint4(e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16), e[6] | (e[7] << 16));
+            const uint4 bq = ranks_below(make_uint4(e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16), e[6] | (e[7] << 16)), rs * 32 + 8 * g, R);
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt) {
                 const int m = 16 * mt + n;
@@ -718,7 +718,7 @@ __global__ __launch_bounds__(256, kBatch == 4 ? 8 : 4) void rowtile_finish_kerne
         __syncthreads();
         for (int rs = 0; rs < (Rpad >> 5); ++rs) {
             if (rs > 0) load_b(rs);
-            const uint4 bq = make_uint4(e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16), e[6] | (e[7] << 16));
+            const uint4 bq = ranks_below(make_uint4(e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16), e[6] | (e[7] << 16)), rs * 32 + 8 * g, R);
             const uint4 tq = *reinterpret_cast<const uint4*>(&t_lds[i16 * kTPitch + rs * 32 + 8 * g]);
             acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(bq), as_bf16x8(tq), acc, 0, 0, 0);
         }

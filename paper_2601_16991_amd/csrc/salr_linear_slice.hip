@@ -98,7 +98,7 @@ __global__ __launch_bounds__(kSlThreads, 1) void linear_slice_kernel(
         const int r0 = wave * 32 + 8 * g;
         uint32_t e[8];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {  // rows past R meet the zero padding of T; clamp instead of predicating
+        for (int j = 0; j < 8; ++j) {  // clamp instead of predicating; ranks_below drops those past R
             const int r = r0 + j < R ? r0 + j : R - 1;
             e[j] = (uint32_t)b_cat[(int64_t)r * N + row_c];
         }
@@ -242,7 +242,7 @@ __global__ __launch_bounds__(kSlThreads, 1) void linear_slice_kernel(
     // ---- adapter k-step of this wave (Sec. 3.2): A operand = T rows from LDS, B operand = bq
     if (has_rank_step) {
         const uint4 aq = *reinterpret_cast<const uint4*>(&t_lds[(n < M ? n : M - 1) * kMaxRankPadded + wave * 32 + 8 * g]);
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(aq), as_bf16x8(bq), acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(aq), as_bf16x8(ranks_below(bq, wave * 32 + 8 * g, R)), acc, 0, 0, 0);
     }
 
     // ---- reduce the waves' accumulators and store

@@ -235,7 +235,7 @@ __global__ __launch_bounds__(NW * 64, (S == 2 && MT == 1) ? 4 : 1) void linear_s
         const int r0 = wave * 32 + 8 * g;
         uint32_t e[8];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {  // rows past R meet the zero padding of T; clamp instead of predicating
+        for (int j = 0; j < 8; ++j) {  // clamp instead of predicating; ranks_below drops those past R
             const int r = r0 + j < R ? r0 + j : R - 1;
             e[j] = (uint32_t)b_cat[(int64_t)r * N + row_c];
         }
@@ -453,6 +453,12 @@ __global__ __launch_bounds__(NW * 64, (S == 2 && MT == 1) ? 4 : 1) void linear_s
                 t_lds[(i >> 4) * kMaxRankPadded + 16 * rt + (i & 15)] = f32_to_bf16_rne(sum);
             }
         }
+        if (has_rank_step) {   // while the values, requested after these, are still on their way
+#pragma unroll
+            for (int j = 0; j < 8; ++j) asm volatile("" : "+v"(late[j]));
+            bq = make_uint4(late[0] | (late[1] << 16), late[2] | (late[3] << 16), late[4] | (late[5] << 16), late[6] | (late[7] << 16));
+            bq = ranks_below(bq, 8 * g, R);
+        }
         if (n_chunks > 0) consume(st);
     } else if (n_chunks == S && !dense_slice) {
         // the whole slice is in flight at once: straight-line code, each chunk waits for its own data only
@@ -534,8 +540,7 @@ __global__ __launch_bounds__(NW * 64, (S == 2 && MT == 1) ? 4 : 1) void linear_s
 
     // ---- adapter k-step of this wave (Sec. 3.2): A operand = T rows from LDS, B operand = bq
     if (has_rank_step) {
-        if constexpr (kOwnT)
-            bq = make_uint4(late[0] | (late[1] << 16), late[2] | (late[3] << 16), late[4] | (late[5] << 16), late[6] | (late[7] << 16));
+        if constexpr (!kOwnT) bq = ranks_below(bq, wave * 32 + 8 * g, R);
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
             const int m = 16 * mt + n;

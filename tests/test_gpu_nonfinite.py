@@ -1,4 +1,4 @@
-"""Infinite activations on the large-batch path: an output is infinite, NaN or finite exactly where the sums of the fp64 CPU oracle
+"""Infinite activations and adapters: an output is infinite, NaN or finite exactly where the sums of the fp64 CPU oracle
 are.  One infinite entry of X makes infinities where the weights of its column are nonzero and NaN where they are zero (every
 kernel multiplies the zeros of the mask); nothing that a tile, a half step or a padded rank adds may turn those into NaN.  The
 finite outputs keep the usual bar, max |Y - Y_ref| <= 1e-2 * max |Y_ref|."""
@@ -68,6 +68,61 @@ def test_linear(M, K, N, R, least):
     torch.cuda.synchronize()
     ref = oracle.linear(x, w, a, b)
     assert np.isinf(ref[3]).any() and np.isinf(ref[M - 1]).any()
+    _compare(y_to_f64(y), ref, "y")
+
+
+# T formed by every workgroup, by the first of them beside their own work, by workgroups of their own, in a launch in front (rank 12);
+# long rows; row tiles with a split, in one launch of one, two and four parts, without adapters in parts; large batches and, under
+# 2:4, both of their kernels.  Ranks that do not fill the padded ones.
+CALLS = [(5, 512, 300, 5), (16, 1152, 4096, 24), (3, 2048, 500, 40), (16, 2048, 500, 12), (4, 12416, 160, 5), (20, 2048, 600, 7), (40, 1120, 2100, 33),
+         (100, 1120, 300, 5), (16, 4096, 6000, 24), (24, 1120, 8384, 8), (128, 576, 16640, 40), (16, 1024, 8320, 0), (200, 128, 300, 20),
+         (1024, 128, 3072, 40), (1536, 128, 2048, 40)]
+
+
+def _places(kind, K, R):
+    """Of a 2:4 weight the zeros are not multiplied: X stays finite there.  Its calls and those with a table want rows of whole chunks."""
+    if kind in ("2of4", "prepared") and K % 128:
+        return []
+    return (["x"] if kind != "2of4" else []) + (["a", "b"] if R else [])
+
+
+@pytest.mark.parametrize("kind,M,K,N,R,where", [(kind, M, K, N, R, where) for M, K, N, R in CALLS for kind in ("plain", "prepared", "codes", "2of4")
+                                                for where in _places(kind, K, R)])
+def test_every_path(kind, M, K, N, R, where):
+    """An infinite entry of X, of A_cat, or of B_cat in its last rank, which those that fill the padded ones must not meet."""
+    import paper_2601_16991_amd as salr
+    w = wl.gaussian_bf16((N, K), 0.02, M + K)
+    if kind == "2of4":
+        w = oracle.mask_nm(w, 2, 4)
+    else:
+        w[np.random.default_rng(M + K).random((N, K)) >= 0.5] = 0
+    x = wl.gaussian_bf16((M, K), 1.0, M + N)
+    a, b = (wl.gaussian_bf16((K, R), 0.05, 1), wl.gaussian_bf16((R, N), 0.05, 2)) if R else (None, None)
+    if where == "x":
+        w[:, K - 20] &= 0x7FFF
+        if R:
+            a[K - 20] &= 0x7FFF
+            b &= 0x7FFF
+        x[M - 1, K - 20] = NINF
+    elif where == "a":
+        a[K // 2, R - 1] = INF
+    else:
+        b[R - 1, N - 1], b[R - 1, N // 2] = INF, NINF
+    rb, rv, ro = oracle.encode(w)
+    args = [to_dev_u16(x), to_dev_u32(rb), to_dev_u16(rv), to_dev_u32(ro)]
+    ab = [to_dev_u16(a), to_dev_u16(b)] if R else [None, None]
+    print(f"[non-finite] {kind} M{M} K{K} N{N} R{R}: {where}", flush=True)
+    if kind == "codes":
+        codes, scales = salr.nf4_quantize(args[2])
+        w = oracle.decode(rb, salr.nf4_dequantize(codes, scales, rv.size).cpu().numpy().view(np.uint16)[:rv.size], ro, N, K)
+        y = salr.qsalr_linear(args[0], args[1], codes, scales, args[3], rv.size, *ab)
+    elif kind == "prepared":
+        y = salr.linear_prepared(*args, salr.build_slice_table(args[1], args[3], K), *ab)
+    else:
+        y = (salr.linear if kind == "plain" else salr.linear_2of4)(*args, *ab)
+    torch.cuda.synchronize()
+    ref = oracle.linear(x, w, a, b)
+    assert not np.isfinite(ref).all()
     _compare(y_to_f64(y), ref, "y")
 
 
