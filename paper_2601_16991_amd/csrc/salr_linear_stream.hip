@@ -116,23 +116,24 @@ __device__ __forceinline__ void own_t_partials(const OwnT& o, int R, int Rpad, u
 }
 
 // MT m-tiles of 16 rows, NW waves per workgroup, S chunks in flight per wave.
-// kOwnPrefix: every wave popcounts the bitmap words left of its slice itself (kOwnT's rows of a chunk a wave), so the workgroup needs no
-// barrier before the stream starts; otherwise the waves exchange slice counts.  (On longer rows the words that are read again keep the
-// address unit busier than the barrier costs: 16 x 2048 x 4096 10.2 -> 9.3 us, 8 x 4096 x 1024 9.5 -> 8.6; one token on 4096 x 4096 the other
-// way round by 3 %.)
+// Where a slice's values start the waves find by exchanging the counts of their slices.  (Each reading the words left of its own again, with no
+// barrier before the stream, keeps the address unit busier than the barrier costs.  us a call without adapters, read again / exchanged:
+// 4096 x 4096 one token 9.4 / 9.1, 16 tokens 10.7 / 10.4, 32 tokens 14.9 / 14.4; 2048 x 4096 6.5 / 5.8 and 7.6 / 6.8, 2048 x 2048 32 tokens 9.3 / 8.5,
+// 1024 x 4096 32 tokens 6.8 / 5.9, 2048 x 7168 16 tokens 13.8 / 12.0; level at 512 columns.)
 // kTable: the cursors come ready-made from the layer's slice table (salr_build_slice_table: for every row and each of
 // the 8 wave slices the index of the slice's first value and the most nonzeros any chunk of it holds): one 8-byte
 // request in place of the row offset, the rest of the slice's bitmap and the words left of it, and no barrier.
 // kQuads: the bitmap of four chunks in one request.
-// kOwnT: every workgroup computes T itself instead of reading the pre-kernel's partials (see stream_owns_t).
+// kOwnT: every workgroup computes T itself instead of reading the pre-kernel's partials (see stream_owns_t).  Its rows are a chunk a wave: there
+// the waves count what is left of their slices.
 // kShareT: the first workgroups form T's partials for all (salr_shared_t.hpp).
-template <int MT, int NW, int S, bool kVecBitmap, bool kOwnPrefix, bool kTable = false, bool kOwnT = false, bool kQuads = false, bool kShareT = false>
+template <int MT, int NW, int S, bool kVecBitmap, bool kTable = false, bool kOwnT = false, bool kQuads = false, bool kShareT = false>
 __global__ __launch_bounds__(NW * 64, (S == 2 && MT == 1) ? 4 : 1) void linear_stream_kernel(
     const uint16_t* __restrict__ x, int M, int64_t K, int64_t N, const uint32_t* __restrict__ bitmap,
     const uint16_t* __restrict__ values, const uint32_t* __restrict__ row_offsets,
     float* t_partial, const uint16_t* __restrict__ b_cat, int R, int Rpad,
     uint16_t* __restrict__ y, const uint32_t* __restrict__ slice_table, const uint16_t* __restrict__ a_cat, SharedT shared) {
-    static_assert(!kShareT || (!kOwnPrefix && MT == 1 && NW == kShareWaves && !kOwnT && kShareTileBytes <= kStreamRows * kSlotDwords * 4));
+    static_assert(!kShareT || (MT == 1 && NW == kShareWaves && !kOwnT && kShareTileBytes <= kStreamRows * kSlotDwords * 4));
     static_assert(!kTable || NW == kSliceTableSlices, "the table holds one entry per wave slice");
     constexpr int kThreads = NW * 64;
     constexpr int kStageDwords = NW * kStreamRows * kSlotDwords + 8;
@@ -311,10 +312,9 @@ __global__ __launch_bounds__(NW * 64, (S == 2 && MT == 1) ? 4 : 1) void linear_s
             tail += len;
             longest = len > longest ? len : longest;
         }
-        if constexpr (kOwnPrefix) {
+        if constexpr (kOwnT) {
             // nonzeros left of the slice: at most two chunks per lane, in flight at once
             uint32_t before = 0;
-            static_assert(kOwnT);
             constexpr int kLeft = kOwnTK / 512;
             uint4 left[kLeft];  // no branches: chunks past the slice start re-read chunk 0 and are dropped
 #pragma unroll
@@ -342,7 +342,7 @@ __global__ __launch_bounds__(NW * 64, (S == 2 && MT == 1) ? 4 : 1) void linear_s
             if (kTable) __syncthreads();
         }
     }
-    if constexpr (!kOwnPrefix && !kTable) {
+    if constexpr (!kOwnT && !kTable) {
         __syncthreads();
         for (int w = 0; w < wave; ++w) cur += slice_count[w][n];
     }
@@ -691,10 +691,10 @@ static void launch_stream_t(const LinearArgs& a, hipStream_t stream, const Timin
     if constexpr (MT == 1 && S > 2 && !kQ) {
         if (stream_owns_t(a.M, a.K, R)) {
             if (a.slice_table != nullptr && !a.build_table)
-                SALR_LAUNCH((linear_stream_kernel<MT, NW, S, true, false, true, true>), dim3(grid), dim3(NW * 64), stream, ev, a.x, (int)a.M,
+                SALR_LAUNCH((linear_stream_kernel<MT, NW, S, true, true, true>), dim3(grid), dim3(NW * 64), stream, ev, a.x, (int)a.M,
                             a.K, a.N, a.bitmap, a.values, a.row_offsets, nullptr, a.b_cat, R, Rpad, a.y, a.slice_table, a.a_cat, SharedT());
             else
-                SALR_LAUNCH((linear_stream_kernel<MT, NW, S, true, true, false, true>), dim3(grid), dim3(NW * 64), stream, ev, a.x, (int)a.M,
+                SALR_LAUNCH((linear_stream_kernel<MT, NW, S, true, false, true>), dim3(grid), dim3(NW * 64), stream, ev, a.x, (int)a.M,
                             a.K, a.N, a.bitmap, a.values, a.row_offsets, nullptr, a.b_cat, R, Rpad, a.y, nullptr, a.a_cat, SharedT());
             return;
         }
@@ -707,8 +707,8 @@ static void launch_stream_t(const LinearArgs& a, hipStream_t stream, const Timin
                             t_partial, a.b_cat, R, Rpad, a.y, table, a.a_cat, shared);
             };
             // (a caller's table; without one there is no launch in front to build it in)
-            if (a.slice_table != nullptr && !a.build_table) go(linear_stream_kernel<MT, NW, S, true, false, true, false, kQ, true>, a.slice_table);
-            else go(linear_stream_kernel<MT, NW, S, true, false, false, false, kQ, true>, nullptr);
+            if (a.slice_table != nullptr && !a.build_table) go(linear_stream_kernel<MT, NW, S, true, true, false, kQ, true>, a.slice_table);
+            else go(linear_stream_kernel<MT, NW, S, true, false, false, kQ, true>, nullptr);
             return;
         }
     }
@@ -717,13 +717,13 @@ static void launch_stream_t(const LinearArgs& a, hipStream_t stream, const Timin
     const int64_t wpr = a.K / 32;
     const uint32_t* no_table = nullptr;
     if (a.slice_table != nullptr && wpr % kChunkWords == 0)   // prepared layer: cursors from its slice table
-        SALR_LAUNCH((linear_stream_kernel<MT, NW, S, true, false, true, false, kQ>), dim3(grid), dim3(NW * 64), stream, ev, a.x, (int)a.M,
+        SALR_LAUNCH((linear_stream_kernel<MT, NW, S, true, true, false, kQ>), dim3(grid), dim3(NW * 64), stream, ev, a.x, (int)a.M,
                     a.K, a.N, a.bitmap, a.values, a.row_offsets, t_partial, a.b_cat, R, Rpad, a.y, a.slice_table, a.a_cat, SharedT());
     else if (wpr % kChunkWords != 0)  // bitmap rows are not multiples of 16 bytes: scalar bitmap loads
-        SALR_LAUNCH((linear_stream_kernel<MT, NW, S, false, false>), dim3(grid), dim3(NW * 64), stream, ev, a.x, (int)a.M, a.K,
+        SALR_LAUNCH((linear_stream_kernel<MT, NW, S, false>), dim3(grid), dim3(NW * 64), stream, ev, a.x, (int)a.M, a.K,
                     a.N, a.bitmap, a.values, a.row_offsets, t_partial, a.b_cat, R, Rpad, a.y, no_table, a.a_cat, SharedT());
     else   // (no ranks: with any there is a table)
-        SALR_LAUNCH((linear_stream_kernel<MT, NW, S, true, false, false, false, kQ>), dim3(grid), dim3(NW * 64), stream, ev, a.x, (int)a.M,
+        SALR_LAUNCH((linear_stream_kernel<MT, NW, S, true, false, false, kQ>), dim3(grid), dim3(NW * 64), stream, ev, a.x, (int)a.M,
                     a.K, a.N, a.bitmap, a.values, a.row_offsets, t_partial, a.b_cat, R, Rpad, a.y, no_table, a.a_cat, SharedT());
 }
 
