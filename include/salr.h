@@ -427,6 +427,13 @@ salr_status_t salr_concat_adapters(const uint16_t* const* a_list, const uint16_t
  */
 void salr_set_kernel_timing_events(void* start_event, void* stop_event);
 
+/*
+ * Test hook (not part of the method): how often a kernel looks, a quarter of a microsecond apart, for what other workgroups of
+ * its launch hand over (T = X * A_cat, of up to 128 tokens) before it does without: with 0 this host thread's next calls do not
+ * wait at all, with a negative number they wait as they do by default (64 looks).  Results are the same bit for bit.
+ */
+void salr_set_handover_polls(int polls);
+
 #ifdef __cplusplus
 }
 #endif

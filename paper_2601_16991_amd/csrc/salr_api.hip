@@ -43,21 +43,6 @@ bool qsalr_decodes_codes(int64_t M, int64_t K, int64_t N, int64_t nnz) {
     return nnz > 0 && K > 0 && salr::linear_takes_twostage(M, K, N) && (K / 32 + 15) / 16 <= 1024;
 }
 
-// QSALR calls of up to 128 tokens that take the row-tiled kernel on the codes, with room for its partial outputs.  More than 64
-// tokens have no other kernel that reads codes; fewer take the small-batch kernel on layers of a few microseconds and the lower price on
-// others (us a call, that kernel / this one: 33 x 896 x 1260 10.5 / 19.9, 1 x 8192 x 8192 32 / 41, 16 x 2048 x 8192 14.6 / 16.5; 16 x 4096 x
-// 14336 36.4 / 30.7, 1 x 13824 x 5120 61 / 36, 17 x 5696 x 4549 64 / 23).  Rows that are no whole chunks have this kernel or none.
-bool qsalr_takes_rowtile(int64_t M, int64_t K, int64_t N, int64_t R, int64_t nnz) {
-    if (nnz <= 0 || K <= 0 || !(salr::uses_rowtile(M, K, N) || salr::rowtile_can(M, K, N))) return false;
-    if (M > salr::kStreamMaxM) return true;
-    const bool large = M > 32 || (M > 16 ? K >= 1024 || N >= 8192 : N * K >= (18 << 20) || N >= 16384 || K >= (R > 0 ? 5376 : 8192));
-    if (!large || K % 128 != 0) return large;
-    const salr::SmallBatchPrices& prices = M <= 16 ? salr::kPricesOfFewCodes : salr::kPricesOfCodes;
-    const double nonzeros = (double)nnz / ((double)N * (double)K);
-    return salr::rowtile_price(prices, salr::rowtile_plan_of(M, K, N, R, true), M, R, nonzeros) <
-           salr::small_batch_price(prices, true, M, K, N, R, nonzeros);
-}
-
 }  // namespace
 
 extern "C" {
@@ -310,7 +295,7 @@ size_t salr_qsalr_linear_workspace_bytes(int64_t M, int64_t K, int64_t N, int64_
 size_t salr_qsalr_linear_workspace_bytes_fastest(int64_t M, int64_t K, int64_t N, int64_t R, int64_t nnz) {
     const size_t told = salr_qsalr_linear_workspace_bytes(M, K, N, R, nnz);
     if (M <= 0 || K <= 0 || N <= 0 || R < 0 || R > kMaxRank || K % 32 != 0 || nnz <= 0) return told;
-    if (qsalr_takes_rowtile(M, K, N, R, nnz)) {
+    if (salr::qsalr_takes_rowtile(M, K, N, R, nnz)) {
         const size_t b = salr::rowtile_bytes_fastest(M, K, N, R);
         return b > told ? b : told;
     }
@@ -329,7 +314,7 @@ salr_status_t salr_qsalr_linear(const uint16_t* x, int64_t M, int64_t K, int64_t
     if (K % 32 != 0) return SALR_ERR_SHAPE;
     if (nnz > (int64_t)0xFFFFFFFFLL || (K > 0 && nnz > N * K)) return SALR_ERR_SHAPE;
     if (R > kMaxRank) return SALR_ERR_UNSUPPORTED;
-    if (qsalr_takes_rowtile(M, K, N, R, nnz) && workspace_bytes >= salr::rowtile_bytes(M, K, N, R) &&
+    if (salr::qsalr_takes_rowtile(M, K, N, R, nnz) && workspace_bytes >= salr::rowtile_bytes(M, K, N, R) &&
         workspace_bytes >= salr_qsalr_linear_workspace_bytes(M, K, N, R, nnz)) {
         if (!y || !x || !bitmap || !row_offsets) return SALR_ERR_INVALID_ARG;
         if (R > 0 && (!a_cat || !b_cat)) return SALR_ERR_INVALID_ARG;

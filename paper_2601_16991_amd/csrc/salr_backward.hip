@@ -9,15 +9,13 @@
 //     backward_t_kernel, where the weight is not wanted, R is no multiple of 8 or the chains are long and many);
 //     dX: the large-batch matrix stage on dY and that weight, T' riding along as its adapter steps (salr_gemm.hip);
 //     dA, dB: products that contract over the rows of X and dY against T'^T and T^T (salr_row_products.hpp), in workgroups beside the matrix
-//     stage's where those leave room on a CU and the stage is long enough (gradients_beside in salr_gemm.hip), or in a launch of their own
+//     stage's where those leave room on a CU and the stage is long enough (gradients_beside), or in a launch of their own
 //     and one that sums their slices.
 // As in the forward pass T and T' are rounded to bf16 once; sums are fp32; outputs bf16.  The sixteen slices of T and T' interleave
 // (every sixteenth step of 64 columns, whichever launch forms them), so a sum can differ from one over contiguous slices in its last
 // bits, and where it sits on a rounding boundary by one bf16 step: about 2e-4 of dA and dB in the 2-norm against such a sum;
 // against fp64 both are off by 2.35e-3, the two roundings.
-#include "salr_device.hpp"
 #include "salr_internal.hpp"
-#include "salr_linear_common.hpp"
 
 namespace salr {
 

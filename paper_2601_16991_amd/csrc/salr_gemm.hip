@@ -632,17 +632,6 @@ hipError_t launch_decode_frags(const LinearArgs& a, uint16_t* wf, uint16_t* af, 
     return hipGetLastError();
 }
 
-// Slices of the rows at most where the gradients are beside the stage: whoever sums them reads them all.  (With the 32 of a launch of their
-// own 2272 x 1216 x 640 at rank 32 went 33 -> 41 us; with eight 29.)
-constexpr int kBesideSlices = 8;
-// Whether they are: where the stage is long enough to hide them, by what they read at 3 TB/s and what the stage multiplies at 1100 TFLOP/s, and
-// up to 96 ranks, from where on their workgroups' passes are several.  Of 200 drawn steps (128 to 4096 tokens, ranks 8 to 96) one is 1 %
-// slower so, the geometric mean 1.13 faster; at rank 128 0.86 (448 x 5248 x 640) to 1.10 (608 x 2688 x 13440).
-static bool gradients_beside(int64_t M, int64_t K, int64_t N, const RowProducts& p) {
-    const double gradients = (double)M * (double)(p.C[0] + p.C[1]) * 2.0 * (p.Rpad / 32) / 3e6, stage = 2.0 * (double)M * (double)N * (double)K / 1.1e9;
-    return p.Rpad <= 96 && (gradients < 20.0 || gradients < 0.85 * stage);
-}
-
 bool launch_frag_gemm(const uint16_t* x, int64_t M, int64_t K, int64_t N, const uint16_t* wf, const uint16_t* t, int Rpad,
                       uint16_t* y, float* partial, size_t partial_room, const TimingEvents& ev, hipStream_t stream, const RowProducts* beside) {
     const GemmPlan p = gemm_plan(M, K + Rpad, N, partial_room);
@@ -650,7 +639,7 @@ bool launch_frag_gemm(const uint16_t* x, int64_t M, int64_t K, int64_t N, const 
     const dim3 grid(gemm_grid(m_tiles * n_tiles * p.ksplit));
     // (mt, nt: two of the stage's workgroups fit a CU up to 128 x 256; four rank tiles a pass have the registers up to 128 x 128)
     const bool four = Rpad % 64 == 0 && p.mt * p.nt <= 128 * 128;
-    if (beside != nullptr && p.mt <= 128 && gradients_beside(M, K, N, *beside)) {
+    if (beside != nullptr && gradients_beside(M, K, N, p.mt, *beside)) {
         RowProducts products = *beside;
         if (products.ksplit > kBesideSlices) products.ksplit = kBesideSlices;
         const int blocks = (row_product_blocks(products.C[0]) + row_product_blocks(products.C[1])) * products.ksplit;

@@ -463,6 +463,11 @@ inline size_t rowtile_workspace_bytes(int64_t M, int64_t K, int64_t N, int64_t R
 inline bool uses_2of4_kernel(int64_t M, int64_t K, int64_t N) {
     return rowtile_possible(M, K) && !(N % 4 != 0 && N < 64 * 128);
 }
+// The barrier-free one of its kernels: up to 16 tokens it is ahead where the call is short (layers of up to 2^25 elements: no reducing launch, no
+// split of K) and, on any layer, up to 4 tokens (little X to pull through the L2 per workgroup); measured on the Llama-3 shapes.
+inline bool uses_2of4_stream(int64_t M, int64_t K, int64_t N) {
+    return uses_2of4_kernel(M, K, N) && M <= 16 && (M <= 4 || N * K <= (int64_t(1) << 25));
+}
 // above 128 tokens: a tiled GEMM on the sparse MFMA (k-steps of 64 columns, four outputs per store); its workspace is
 // the T part of the large-batch layout, which the general call's workspace contains
 // Taken where its tiles fill the chip without crowding it (measured on the Llama-3 shapes: 14 to 32 % ahead of the
@@ -611,8 +616,27 @@ inline RowtilePlan rowtile_plan_in(int64_t M, int64_t K, int64_t N, int64_t R, s
     if (rowtile_on_told_size(M, K, N) || room >= rowtile_bytes(M, K, N, R)) return rowtile_plan_of(M, K, N, R);
     return rowtile_plan(M, K, N, R, linear_workspace_bytes(M, K, N, R));
 }
+// Whether its launch hands T over and adds the adapters itself: where the plan has it so, with room for the words behind the rest.
+inline bool rowtile_hands_over(int64_t M, int64_t K, int64_t N, int64_t R, const RowtilePlan& p, size_t room) {
+    return p.one_launch && room >= rowtile_plan_bytes(M, K, N, R, p) + rowtile_pair_bytes(M, N, R, p);
+}
 inline bool linear_takes_rowtile(int64_t M, int64_t K, int64_t N, int64_t R, size_t room) {
     return uses_rowtile(M, K, N) || (rowtile_wide(M, K, N, R) && room >= rowtile_bytes(M, K, N, R));
+}
+
+// QSALR calls of up to 128 tokens that take the row-tiled kernel on the codes, with room for its partial outputs.  More than 64
+// tokens have no other kernel that reads codes; fewer take the small-batch kernel on layers of a few microseconds and the lower price on
+// others (us a call, that kernel / this one: 33 x 896 x 1260 10.5 / 19.9, 1 x 8192 x 8192 32 / 41, 16 x 2048 x 8192 14.6 / 16.5; 16 x 4096 x
+// 14336 36.4 / 30.7, 1 x 13824 x 5120 61 / 36, 17 x 5696 x 4549 64 / 23).  Rows that are no whole chunks have this kernel or none.
+inline bool qsalr_takes_rowtile(int64_t M, int64_t K, int64_t N, int64_t R, int64_t nnz) {
+    if (nnz <= 0 || K <= 0 || !(uses_rowtile(M, K, N) || rowtile_can(M, K, N))) return false;
+    if (M > kStreamMaxM) return true;
+    const bool large = M > 32 || (M > 16 ? K >= 1024 || N >= 8192 : N * K >= (18 << 20) || N >= 16384 || K >= (R > 0 ? 5376 : 8192));
+    if (!large || K % 128 != 0) return large;
+    const SmallBatchPrices& prices = M <= 16 ? kPricesOfFewCodes : kPricesOfCodes;
+    const double nonzeros = (double)nnz / ((double)N * (double)K);
+    return rowtile_price(prices, rowtile_plan_of(M, K, N, R, true), M, R, nonzeros) <
+           small_batch_price(prices, true, M, K, N, R, nonzeros);
 }
 
 // The operand-order path's workspace: T, what a product of its own needs for it, the weight, then the partial outputs of a split
@@ -722,6 +746,16 @@ struct RowProducts {
     uint64_t* words;
     uint64_t tag;
 };
+// Slices of the rows at most where the gradients are beside the stage: whoever sums them reads them all.  (With the 32 of a launch of their
+// own 2272 x 1216 x 640 at rank 32 went 33 -> 41 us; with eight 29.)
+constexpr int kBesideSlices = 8;
+// Whether they are: on tiles of the stage (of stage_rows rows) of which two fit a CU, where the stage is long enough to hide them, by what
+// they read at 3 TB/s and what the stage multiplies at 1100 TFLOP/s, and up to 96 ranks, from where on their workgroups' passes are several.  Of 200 drawn steps (128 to 4096 tokens, ranks 8 to 96) one is 1 %
+// slower so, the geometric mean 1.13 faster; at rank 128 0.86 (448 x 5248 x 640) to 1.10 (608 x 2688 x 13440).
+inline bool gradients_beside(int64_t M, int64_t K, int64_t N, int stage_rows, const RowProducts& p) {
+    const double gradients = (double)M * (double)(p.C[0] + p.C[1]) * 2.0 * (p.Rpad / 32) / 3e6, stage = 2.0 * (double)M * (double)N * (double)K / 1.1e9;
+    return stage_rows <= 128 && p.Rpad <= 96 && (gradients < 20.0 || gradients < 0.85 * stage);
+}
 inline int tn_ksplit(int64_t C0, int64_t M, int64_t C1 = 0) {
     const int64_t blocks = (C0 + 63) / 64 + (C1 + 63) / 64, steps = M / 32;
     int s = 1;

@@ -499,10 +499,7 @@ hipError_t launch_linear_2of4(const LinearArgs& a, hipStream_t stream, const Tim
     char* base = reinterpret_cast<char*>(a.t);
     float* t_partial = reinterpret_cast<float*>(base);
     float* y_partial = reinterpret_cast<float*>(base + rowtile_t_bytes(a.M, a.K, a.R));
-    // Up to 16 tokens the barrier-free kernel is ahead where the call is short (layers of up to 2^25 elements: no
-    // reducing launch, no split of K) and, on any layer, up to 4 tokens (little X to pull through the L2 per workgroup);
-    // measured on the Llama-3 shapes.
-    if (a.M <= 16 && (a.M <= 4 || a.N * a.K <= (int64_t(1) << 25))) {
+    if (uses_2of4_stream(a.M, a.K, a.N)) {
         launch_2of4_stream_t<1, 4>(a, t_partial, stream, ev);
         return hipGetLastError();
     }

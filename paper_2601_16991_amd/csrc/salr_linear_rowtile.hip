@@ -766,10 +766,10 @@ hipError_t launch_linear_rowtile(const LinearArgs& a, hipStream_t stream, const 
     p.words = nullptr;
     p.t_sum = nullptr;
     p.polls = g_handover_polls;
-    const size_t before = rowtile_t_out_bytes(a.M, a.R) + (size_t)plan.ksplit * rowtile_partial_bytes(a.M, a.N), t_sum_bytes = round_up_256((size_t)a.M * Rpad * 2);
-    if (plan.one_launch && handover_aligned(base) && a.room >= round_up_256(before) + rowtile_pair_bytes(a.M, a.N, a.R, plan)) {
-        p.t_sum = reinterpret_cast<uint16_t*>(base + round_up_256(before));
-        p.words = reinterpret_cast<uint64_t*>(base + round_up_256(before) + t_sum_bytes);
+    if (handover_aligned(base) && rowtile_hands_over(a.M, a.K, a.N, a.R, plan, a.room)) {
+        char* t_sum = base + rowtile_plan_bytes(a.M, a.K, a.N, a.R, plan);
+        p.t_sum = reinterpret_cast<uint16_t*>(t_sum);
+        p.words = reinterpret_cast<uint64_t*>(t_sum + round_up_256((size_t)a.M * Rpad * sizeof(uint16_t)));
         p.tag = next_handover_tag();
     }
     auto go = [&](auto mt) {

@@ -27,10 +27,18 @@ def _out(*shape):
     return torch.full(shape, 0x7FC0, dtype=torch.int16, device=dev())
 
 
-# one step of 32 rows and a few, one to eight slices; 64-column blocks that end early; two and four rank tiles a pass, two passes;
-# stages of 64 and 128 rows, split and whole
-@pytest.mark.parametrize("M,K,N,R", [(32, 96, 64, 8), (64, 32, 128, 16), (96, 160, 192, 40), (256, 416, 320, 96), (512, 1056, 576, 64),
-                                     (480, 2048, 1024, 32), (544, 2080, 2112, 8), (1024, 2048, 2048, 72)])
+# M, K, N, R and the stage of dX that the gradients are beside (tests/test_routes.py holds them to it): its tile and its split of the contraction.  One step
+# of 32 rows and a few, one to eight slices of them; 64-column blocks that end early; two and four rank tiles a pass, two passes
+BESIDE = [(32, 96, 64, 8, 64, 64, 1), (64, 32, 128, 16, 64, 64, 1), (96, 160, 192, 40, 64, 64, 1), (256, 416, 320, 96, 64, 64, 1),
+          (512, 1056, 576, 64, 64, 64, 1), (480, 2048, 1024, 32, 64, 64, 1), (544, 2080, 2112, 8, 64, 64, 1), (1024, 2048, 2048, 72, 64, 64, 1),
+          (32, 32, 1408, 64, 64, 64, 4), (256, 256, 4096, 8, 64, 64, 16), (416, 2496, 64, 40, 64, 128, 1), (2048, 1024, 1024, 32, 64, 128, 1),
+          (32, 2208, 1536, 64, 64, 128, 8), (512, 512, 8192, 32, 64, 128, 8), (1568, 2464, 512, 40, 64, 256, 1), (2048, 2048, 1024, 32, 64, 256, 1),
+          (160, 1088, 9216, 64, 64, 256, 16), (512, 2048, 4096, 32, 64, 256, 4), (1120, 1856, 192, 64, 128, 128, 1), (1632, 1280, 128, 96, 128, 128, 1),
+          (96, 1088, 6656, 40, 128, 128, 16), (96, 2112, 3328, 8, 128, 128, 8), (2144, 7328, 128, 8, 128, 256, 1), (2048, 4096, 4096, 32, 128, 256, 1),
+          (1504, 352, 15872, 32, 128, 256, 8)]
+
+
+@pytest.mark.parametrize("M,K,N,R", [c[:4] for c in BESIDE])
 def test_same_gradients_beside_the_stage_and_alone(M, K, N, R):
     import paper_2601_16991_amd as salr
     host, args = _layer(M, K, N, R)

@@ -72,8 +72,8 @@ def test_linear(M, K, N, R, least):
 
 
 # T formed by every workgroup, by the first of them beside their own work, by workgroups of their own, in a launch in front (rank 12);
-# long rows; row tiles with a split, in one launch of one, two and four parts, without adapters in parts; large batches and, under
-# 2:4, both of their kernels.  Ranks that do not fill the padded ones.
+# row tiles with a split, in one launch of one, two and four parts, without adapters in parts; large batches and, under 2:4, both of their
+# kernels.  On the told workspace long rows and 17 to 64 tokens have kernels of their own.  Ranks that do not fill the padded ones.
 CALLS = [(5, 512, 300, 5), (16, 1152, 4096, 24), (3, 2048, 500, 40), (16, 2048, 500, 12), (4, 12416, 160, 5), (20, 2048, 600, 7), (40, 1120, 2100, 33),
          (100, 1120, 300, 5), (16, 4096, 6000, 24), (24, 1120, 8384, 8), (128, 576, 16640, 40), (16, 1024, 8320, 0), (200, 128, 300, 20),
          (1024, 128, 3072, 40), (1536, 128, 2048, 40)]
@@ -115,15 +115,20 @@ def test_every_path(kind, M, K, N, R, where):
     if kind == "codes":
         codes, scales = salr.nf4_quantize(args[2])
         w = oracle.decode(rb, salr.nf4_dequantize(codes, scales, rv.size).cpu().numpy().view(np.uint16)[:rv.size], ro, N, K)
-        y = salr.qsalr_linear(args[0], args[1], codes, scales, args[3], rv.size, *ab)
+        ys = [salr.qsalr_linear(args[0], args[1], codes, scales, args[3], rv.size, *ab)]
     elif kind == "prepared":
-        y = salr.linear_prepared(*args, salr.build_slice_table(args[1], args[3], K), *ab)
+        ys = [salr.linear_prepared(*args, salr.build_slice_table(args[1], args[3], K), *ab)]
     else:
-        y = (salr.linear if kind == "plain" else salr.linear_2of4)(*args, *ab)
+        ys = [(salr.linear if kind == "plain" else salr.linear_2of4)(*args, *ab)]
+    if kind == "plain":
+        told = salr.salr_linear_workspace_bytes(M, K, N, R)
+        ys.append(torch.empty_like(ys[0]))
+        salr.salr_sparse_lowrank_linear(*args, *ab, ys[1], torch.empty(told, dtype=torch.uint8, device=dev()) if told else None)
     torch.cuda.synchronize()
     ref = oracle.linear(x, w, a, b)
     assert not np.isfinite(ref).all()
-    _compare(y_to_f64(y), ref, "y")
+    for y in ys:
+        _compare(y_to_f64(y), ref, "y")
 
 
 def test_quantised():

@@ -122,9 +122,12 @@ def test_row_tiled_calls_on_four_bit_values_stay_inside_their_workspace(M, K, N,
 
 
 # the small-batch kernels with T from workgroups beside their own work and from workgroups of their own, the row-tiled kernel in one launch, and
-# the gradients beside the matrix stage
-@pytest.mark.parametrize("kind,M,K,N,R", [("plain", 16, 1024, 4096, 32), ("plain", 5, 2048, 241, 8), ("prepared", 3, 2048, 1025, 64), ("codes", 16, 1024, 4096, 32),
-                                          ("2of4", 16, 1024, 4096, 32), ("plain", 24, 1120, 8384, 8), ("codes", 33, 1024, 8320, 16), ("backward", 96, 160, 192, 40)])
+# the gradients beside the matrix stage (tests/test_routes.py)
+INSIDE_A_VECTOR = [("plain", 16, 1024, 4096, 32), ("plain", 5, 2048, 241, 8), ("prepared", 3, 2048, 1025, 64), ("codes", 16, 1024, 4096, 32),
+                   ("2of4", 16, 1024, 4096, 32), ("plain", 24, 1120, 8384, 8), ("codes", 33, 1024, 8320, 16), ("backward", 96, 160, 192, 40)]
+
+
+@pytest.mark.parametrize("kind,M,K,N,R", INSIDE_A_VECTOR)
 @pytest.mark.parametrize("start", [4, 8])
 def test_workspaces_that_start_inside_a_vector(kind, M, K, N, R, start):
     """A workspace is told to be aligned to 256 bytes, and one that is not ran slowly and still does: nothing in it is exchanged 64 bits at a
