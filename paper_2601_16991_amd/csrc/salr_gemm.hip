@@ -201,8 +201,10 @@ __device__ __forceinline__ void frag_gemm_block(
     } else {
         // Sparse weight (256 x 256 and 256 x 224 tiles): one instruction per tile and step of 64 columns, half the steps' matrix time, so W is
         // requested two steps ahead and X fragments are held for two steps.  A pair of
-        // steps shares its words of positions (low and high half).  Bound by the operands' way from the L2 (64 KB a step and CU):
-        // 2048 x 4096 x 14336 153 us, 167 with W one step ahead, 203 in the kernel that reads the packed format (gemm_2of4_kernel).
+        // steps shares its words of positions (low and high half).  No unit is at its limit (counters at 2048 x 4096 x 14336): the matrix cores are
+        // busy 41 % of the cycles, the address units 61, the LDS 33, most of that conflicts of the X reads, and 23 of 64 bytes a clock come to a CU
+        // from the L2.  A SIMD has one wave, which is in s_waitcnt for 26 % of its life and waits 33 % for an instruction to be issued: the phases
+        // of a step add up.  153 us, 167 with W one step ahead, 203 in the kernel that reads the packed format (gemm_2of4_kernel).
         const int64_t pairs = (steps + 1) / 2, frag = sparse_frag_elems(K, Rpad);
         auto pair_base = [&](int64_t pr, int j) -> const char* {
             const int64_t f = f0 + j < f_last ? f0 + j : f_last;

@@ -13,7 +13,8 @@
 //            replay, starts from clear words.
 //   knockout of many: in pairs, the one that finds the tag goes on to the next round.
 // At the end of a launch sums of a split contraction handed over so were no faster than a launch that adds them up: under load a store's
-// acknowledgement, an exchange and a load are 1 us each, one after the other (16 x 4096 x 14336, two slices: 23.2 us against 23.9).
+// acknowledgement, an exchange and a load are 1 us each, one after the other (16 x 4096 x 14336 in two slices 23.2 to 24.5 us a call so, 23.9
+// with the launch; 16 x 14336 x 4096 up to 33 so, 24.4 with it).
 // Beside something longer they cost nothing (the backward pass's gradients).
 #pragma once
 

@@ -324,9 +324,10 @@ struct RowtilePlan {
 // Parts of K in a workgroup (1, 2, 4: 128, 64, 32 rows) instead of slices over workgroups, where that many row tiles and T's workgroups are one
 // round: no partial outputs and no launch that sums them, but every workgroup copies all of X to LDS, in shorter panels with as many more
 // barriers (part_step: what that adds to a chunk), and from 33 tokens on four parts' panels would hold half a unit.  Below kOneLaunchTiles row tiles
-// too few CUs take part, whatever the model says.  us a call, slices / parts: 16 x 4096 x 14336 rank 32 23.2 / 21.8 (2), 8 x 2048 x 14336 14.4 / 12.5 (2),
-// 16 x 4096 x 7168 16.0 / 13.9 (4), 64 x 4096 x 28672 51.2 / 47.2 (1), 64 x 2048 x 14336 19.9 / 17.6 (2); left with slices:
-// 64 x 8192 x 14336 51.0 / 54.0 (2), 16 x 3072 x 8192 14.4 / 15.3 (2), 24 x 8192 x 7168 26.3 / 29.2 (4).  Of 220 random calls of 1 to 128 tokens on
+// too few CUs take part, whatever the model says.  us a call, slices / parts (how many; layers of 256 MB together, one after the other, rank 32):
+// 16 x 4096 x 14336 20.8 / 19.9 (2), 32 tokens 23.8 / 22.6 (2), 8 x 2048 x 14336 14.4 / 12.3 (2), 16 x 4096 x 7168 15.6 / 13.9 (4), 64 x 4096 x 28672
+// 47.6 / 43.2 (1), 64 x 2048 x 14336 20.3 / 17.6 (2), 16 x 8192 x 28672 rank 64 60.7 / 58.1 (1); left with slices, before their starts were made
+// cheaper: 64 x 8192 x 14336 51.0 / 54.0 (2), 16 x 3072 x 8192 14.4 / 15.3 (2), 24 x 8192 x 7168 26.3 / 29.2 (4).  Of 220 random calls of 1 to 128 tokens on
 // layers 512 to 16384 columns by 3000 to 28672 rows the rule makes 4 slower by more than 2 %, at most by 6, the geometric mean 1.035.
 constexpr int64_t kOneLaunchTiles = 130;
 inline double part_step(int64_t M, int q) {
@@ -439,7 +440,8 @@ inline size_t shared_t_bytes(int64_t M, int64_t N, int64_t R) {
 // many workgroups as T has slices (SharedT::extra: of their own, where they all are one round).  us a call, T from a launch in front / so:
 // 4096 x 4096 rank 32 one token 13.2 / 11.1 (4-bit values 13.8 / 11.6), 16 tokens 15.0 / 12.8 (4-bit 15.7 / 13.8; rank 64 15.8 / 13.9);
 // 16 x 2048 x 4096 10.5 / 8.8; own workgroups: 8 x 4096 x 1024 11.4 / 8.6, 16 x 4096 x 2048 rank 128 15.0 / 12.5 (14.9 where half of the
-// workgroups form T beside their own work).  2:4 masks: 16 x 4096 x 4096 14.6 / 13.4, 16 x 4096 x 1024 rank 16 12.7 / 10.2.
+// workgroups form T beside their own work).  2:4 masks, layers of 96 MB together, rank 32: 4096 x 4096 16 tokens 13.3 / 11.1, one 11.0 / 9.0,
+// 4096 x 1024 13.1 / 9.4 and 10.3 / 6.6, 3072 x 5000 19.3 / 16.9 and 13.8 / 11.4.
 inline bool shares_t(int64_t M, int64_t K, int64_t N, int64_t R) {
     return R > 0 && R % 8 == 0 && R <= kSharedMaxRank && M <= 16 && K % 128 == 0 && K <= kSharedMaxColumns && (N + 15) / 16 < 2 * 256 &&
            ((N + 15) / 16 >= shared_t_blocks(R) || (N + 15) / 16 + shared_t_blocks(R) <= 256);
@@ -565,7 +567,9 @@ inline double small_batch_price(const SmallBatchPrices& c, bool codes, int64_t M
     const double later = M > 16 ? c.later_round * (rounds - 1.0) : 0.0;
     return c.call + (long_rows ? c.long_call : 0.0) + t + later + rounds * (c.round + (pairs ? c.pair_round : 0.0) + chunk * (double)chunks);
 }
-// p: a plan of slices over workgroups, which the prices were fitted on.  (Where parts in one launch are faster still, so is the call.)
+// p: a plan of slices over workgroups, which the prices were fitted on.  (Where parts in one launch are faster still, so is the call.  Likewise
+// small_batch_price has T's launch in front in it, which calls of shares_t are without: of those only 4-bit values of up to 16 tokens on rows of up
+// to 4096 columns ask for prices.)
 inline double rowtile_price(const SmallBatchPrices& c, const RowtilePlan& p, int64_t M, int64_t R, double nonzeros = 0.5) {
     const double full = nonzeros <= 0.7 ? 0.0 : nonzeros >= 0.8 ? 1.0 : (nonzeros - 0.7) * 10.0;   // share of the chunks that pay tiled_full
     return p.cost + c.tiled + c.tiled_rank * (double)((R + 31) / 32) +
@@ -584,8 +588,12 @@ inline bool rowtile_wide(int64_t M, int64_t K, int64_t N, int64_t R) {
     if (!rowtile_can(M, K, N)) return false;
     if (M > kStreamMaxM) return true;
     if (M <= 16 && !(N * K >= (18 << 20) || N >= 16384 || K >= 5376)) return false;
-    // T's launch in front costs the small-batch kernel as much as the sum this one: it was ahead by more than 3 % in 211 of 9119 calls without a
-    // table.  The prices would find half of them, but a caller's table gains this kernel more (1 x 14336 x 4096 27.1 us without, 22.5 with).
+    // Up to 16 tokens with adapters no prices are asked.  While the small-batch kernel had a launch for T in front everywhere it was ahead by more
+    // than 3 % in 211 of 9119 calls without a table, and a caller's table gains this kernel more (1 x 14336 x 4096 27.1 us without, 22.5 with).  Where
+    // it forms T in its own launch (shares_t) either is ahead by up to a tenth (us a call, it / this one: 8 x 5120 x 4096 12.3 / 13.2, 8 x 6144 x 4096
+    // 13.3 / 14.8, 8 x 8064 x 3000 14.3 / 15.5, 16 x 5376 x 2048 rank 128 14.2 / 15.8; 16 x 5120 x 4096 13.5 / 14.0; 16 x 8192 x 1024 15.9 / 13.8,
+    // 16 x 8192 x 2048 16.1 / 14.7, 16 x 8064 x 3000 rank 128 19.9 / 18.6), and with more row groups than CUs this one is: 8 x 4608 x 5120 20.0 / 13.0,
+    // 16 x 7168 x 7168 33.8 / 21.8.
     if (M <= 16 && R > 0) return true;
     if (M > 16 && M <= 32 && !(K >= 1024 || N >= 8192)) return false;
     return rowtile_price(kPrices, rowtile_plan(M, K, N, R, SIZE_MAX, true), M, R) < small_batch_price(kPrices, false, M, K, N, R);

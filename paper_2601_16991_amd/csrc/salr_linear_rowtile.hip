@@ -15,20 +15,19 @@
 //                34.9 us of a 16 x 4096 x 14336 call.)
 // Where the row tiles alone fill a round of the CUs (rowtile_plan), K is not split over workgroups: 128, 64 or 32 rows a workgroup, the
 // waves on one, two or four parts of K beside each other (Q), added up in LDS.  T, formed 3 to 7 us into the launch, is then handed over
-// inside it (salr_handover.hpp) and there is no second launch, which costs 4.6 us: 16 x 4096 x 14336 23.9 -> 22.0 us a layer,
-// 16 x 4096 x 7168 16.0 -> 13.9, 8 x 2048 x 14336 14.4 -> 12.5, 64 x 4096 x 28672 51.2 -> 47.2.  A part's panels of X are that much shorter,
-// and every barrier costs the waves their lead: 16 x 4096 x 14336 would take 21.2 without any.
+// inside it (salr_handover.hpp) and there is no second launch, which takes 4 to 5 us (figures at rowtile_plan).  A part's panels of X are that
+// much shorter, and every barrier costs the waves their lead: 0.8 us of a 16 x 4096 x 14336 call.
 // The work is cut so that there is one workgroup per CU and one round of them where that can be (rowtile_plan): a slice starts
 // with two dependent round trips to memory and the popcounts of the bitmap left of it, 4 us, and the longer a slice the less often
 // that is paid.  Two workgroups per CU (half the slice, 128 registers a wave) hide each other's start, but spill: 30.5 us a call.
 //
-// Measured with slices over workgroups, whole calls at p = .5, rank 32, before (two workgroups per CU, a barrier per chunk or per four, T in a
-// launch of its own) and so: 16 x 4096 x 14336 34.2 -> 24.4 us, 32 tokens 37.5 -> 26.1, 64 tokens 46.4 -> 30.3, 128 tokens 53.8 -> 40.6; 64 x 14336 x 4096
-// 56.3 -> 33.9; 16 x 8192 x 28672 101 -> 70.  The bytes of the first take 13 us at what a large copy reaches; its loop runs at 4.1 TB/s.
+// us a call at p = .5, rank 32, of the kernel before this one (two workgroups per CU, a barrier per chunk or per four, T in a launch of its own) and
+// now: 16 x 4096 x 14336 34.2 / 19.9, 32 tokens 37.5 / 22.6, 64 tokens 46.4 / 29.0, 128 tokens 53.8 / 38.5; 64 x 14336 x 4096 56.3 / 30.4;
+// 16 x 8192 x 28672 rank 64 101 / 58.1.  The bytes of the first take 13 us at what a large copy reaches; its loop runs at 4.1 TB/s.
 // Tried and left out: packed values two units ahead instead of one (+6 %); 32 weight rows per wave, which halves the operand
 // reads of X (+18 % at 16 tokens: half as many slices' starts overlap); seven waves, so that 256 instead of 224
-// workgroups share the rows of that layer (level); twelve waves on three parts (25.9 us); the partial outputs of slices added up inside the
-// launch by whoever comes last (23.2 to 24.5 us, 14336 x 4096 24.4 to 33: see salr_handover.hpp); values fetched as whole 256-byte runs of a row, half as many cycles of the
+// workgroups share the rows of that layer (level); twelve waves on three parts (25.9 us where two took 22.0); the partial outputs of slices
+// added up inside the launch by whoever comes last (see salr_handover.hpp); values fetched as whole 256-byte runs of a row, half as many cycles of the
 // address unit (the transposition into conflict-free LDS columns then meets conflicts of its own).
 #include <hip/hip_ext.h>
 
@@ -630,7 +629,7 @@ __global__ __launch_bounds__(kRtThreads, 2) void linear_rowtile_kernel(
 
 // y = sum of the slices' partial outputs + T B_cat.  A few KB a workgroup, so it is as long as its round trips to memory: the requests
 // for T, for the first kBatch slices and for B_cat all go out before any of them is used (one after the other, each waited for:
-// 4.8 us after 16 x 4096 x 14336, now 4.2; 5.3 -> 4.1 after 8 x 14336 x 4096).  kBatch: four slices or eight at a time, the fewer
+// 4.8 us behind two slices of 16 x 4096 x 14336, so 4.2; 5.3 and 4.1 behind those of 8 x 14336 x 4096).  kBatch: four slices or eight at a time, the fewer
 // registers where they are enough, for the workgroups of many rows of X.
 template <int kBatch>
 __global__ __launch_bounds__(256, kBatch == 4 ? 8 : 4) void rowtile_finish_kernel(const float* __restrict__ partial, int ksplit, int M, int64_t N,
