@@ -194,7 +194,7 @@ void launch_adapter_transpose(const uint16_t* a_cat, int64_t K, int R, int Rpad,
 template <int kRT>
 __global__ __launch_bounds__(256, kRT <= 2 ? 4 : 2) void tall_tn_kernel(RowProducts p) {
     __shared__ __attribute__((aligned(16))) uint16_t lds[kTnLdsBytes / 2];
-    tall_tn_block<kRT>(p, (int)blockIdx.x, (int)blockIdx.y, lds);
+    tall_tn_block<kRT, false>(p, (int)blockIdx.x, (int)blockIdx.y, lds);
 }
 
 __global__ __launch_bounds__(256) void row_products_reduce_kernel(RowProducts p) {

@@ -379,8 +379,10 @@ __global__ __launch_bounds__(64 * kWM * kWN, 1) void frag_gemm_kernel(
 // The same with the adapter gradients of a backward pass beside it (salr_row_products.hpp), on tiles of which two workgroups fit a CU: workgroups
 // behind the stage's `gemm_blocks`, so that they take what room the CUs have left.  The stage keeps the matrix cores busy and those stream X and dY.
 // 2048 x 4096 x 4096 rank 32: 99.4 us a step with two launches behind the stage (12.5 and 4.9 us), 89.4 so.
+// (Three workgroups a CU on the smaller tiles: four rank tiles take 172 registers of a wave if left alone, and two workgroups cost
+// 512 x 2048 x 1024 rank 64 29.7 us for 27.3, 1024 x 2048 x 2048 44.3 for 36.5.)
 template <int kMI, int kNI, bool kPartial, int kRT>
-__global__ __launch_bounds__(256, 2) void frag_gemm_gradients_kernel(
+__global__ __launch_bounds__(256, kMI == 2 && kNI <= 4 && kRT == 4 ? 3 : 2) void frag_gemm_gradients_kernel(
     const uint16_t* __restrict__ x, int64_t M, int64_t K, int64_t N, const uint16_t* wf,
     const uint16_t* __restrict__ t, int Rpad, uint16_t* __restrict__ y, int m_tiles, int n_tiles, int ksplit,
     float* __restrict__ partial, int gemm_blocks, RowProducts products) {
@@ -391,7 +393,7 @@ __global__ __launch_bounds__(256, 2) void frag_gemm_gradients_kernel(
         return;
     }
     const int id = (int)blockIdx.x - gemm_blocks, blocks = row_product_blocks(products.C[0]) + row_product_blocks(products.C[1]);
-    tall_tn_block<kRT>(products, id % blocks, id / blocks, lds);
+    tall_tn_block<kRT, true>(products, id % blocks, id / blocks, lds);
 }
 
 static unsigned gemm_grid(int workgroups) { return (unsigned)((workgroups + kGemmXcds - 1) / kGemmXcds * kGemmXcds); }

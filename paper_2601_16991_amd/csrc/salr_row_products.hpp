@@ -20,8 +20,11 @@ namespace salr {
 //   in[8 g .. 8 g + 7][16 w + i] as the A operand of 16x16x32 bf16 MFMAs, the B operand s_t[16 rt + i][8 g ..] is a plain
 //   16-byte load; kRT rank tiles per pass over the slice.  Padding columns of Rpad come out as zeros (s_t is zero there).
 // M % 32 == 0, C % 8 == 0.
-// p.words: the slices of a block meet there (salr_handover.hpp), the last sums them, in order, in a launch that has something else
+// kSameLaunch: the slices of a block meet at p.words (salr_handover.hpp) and the last sums them, in order, in a launch that has something else
 // to do meanwhile; else a launch behind this one does.
+// A product's pointers are picked from arguments that are all there, not by index, which is a second trip to memory for them.  With that trip and
+// with a branch on p.words at every store, a step whose gradients are launches of their own took 0.8 to 1.0 us more: 160 x 1024 x 2048, rank 128:
+// 33.3 us, 32.3 so.
 constexpr int kTnPitch = 64 + 8;   // bf16 elements per tile row
 constexpr int kTnBatch = 4;
 constexpr int kTnLdsBytes = 2 * kTnBatch * 32 * kTnPitch * 2;
@@ -36,7 +39,7 @@ static_assert(kRpCols * kRpPitch * 4 <= kTnLdsBytes);
 
 template <bool kSameLaunch>
 __device__ __forceinline__ void row_products_sum(const RowProducts& p, int job, int64_t c0, float* sums) {
-    const int64_t C = p.C[job];
+    const int64_t C = job == 0 ? p.C[0] : p.C[1];
     const float* partial = p.partial + (job == 0 ? 0 : (int64_t)p.ksplit * p.C[0] * p.Rpad);
     const int cols = C - c0 < kRpCols ? (int)(C - c0) : kRpCols;
     const int Rpad = p.Rpad, ksplit = p.ksplit, R = p.R, quads = Rpad >> 2;
@@ -71,16 +74,16 @@ __device__ __forceinline__ void row_products_sum(const RowProducts& p, int job, 
 }
 
 // lds: kTnLdsBytes
-template <int kRT>
+template <int kRT, bool kSameLaunch>
 __device__ __forceinline__ void tall_tn_block(const RowProducts& p, int block, int z, uint16_t* lds) {
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int i16 = lane & 15, g = lane >> 4;
     const int blocks0 = row_product_blocks(p.C[0]), job = block < blocks0 ? 0 : 1;   // the same for the whole workgroup
-    const uint16_t* in = p.in[job];
-    const uint16_t* s_t = p.s_t[job];
-    const int64_t M = p.M, C = p.C[job];
+    const uint16_t* in = job == 0 ? p.in[0] : p.in[1];
+    const uint16_t* s_t = job == 0 ? p.s_t[0] : p.s_t[1];
+    const int64_t M = p.M, C = job == 0 ? p.C[0] : p.C[1];
     const int Rpad = p.Rpad, ksplit = p.ksplit;
     float* partial = p.partial + (job == 0 ? 0 : (int64_t)ksplit * p.C[0] * Rpad);
     const int64_t c0 = (int64_t)(block - (job == 0 ? 0 : blocks0)) * 64;
@@ -144,24 +147,25 @@ __device__ __forceinline__ void tall_tn_block(const RowProducts& p, int block, i
                 const int64_t c = c0 + 16 * wave + 4 * g + e;
                 if (c < C && r < Rpad) {
                     float* to = partial + ((int64_t)z * C + c) * Rpad + r;
-                    if (p.words != nullptr) __hip_atomic_store(to, acc[rt][e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    if constexpr (kSameLaunch) __hip_atomic_store(to, acc[rt][e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     else *to = acc[rt][e];
                 }
             }
         }
     }
-    if (p.words == nullptr) return;
-    stores_done();
-    __syncthreads();   // (every wave's; the tiles have been read, too)
-    int* last = reinterpret_cast<int*>(lds);
-    if (tid == 0) *last = knockout(p.words + (int64_t)block * ksplit, z, ksplit, p.tag);
-    __syncthreads();
-    const bool mine = *last != 0;   // the same for the whole workgroup
-    __syncthreads();
-    if (!mine) return;
-    for (int64_t c = c0; c < c0 + 64 && c < C; c += kRpCols) {
-        row_products_sum<true>(p, job, c, reinterpret_cast<float*>(lds));
+    if constexpr (kSameLaunch) {
+        stores_done();
+        __syncthreads();   // (every wave's; the tiles have been read, too)
+        int* last = reinterpret_cast<int*>(lds);
+        if (tid == 0) *last = knockout(p.words + (int64_t)block * ksplit, z, ksplit, p.tag);
         __syncthreads();
+        const bool mine = *last != 0;   // the same for the whole workgroup
+        __syncthreads();
+        if (!mine) return;
+        for (int64_t c = c0; c < c0 + 64 && c < C; c += kRpCols) {
+            row_products_sum<true>(p, job, c, reinterpret_cast<float*>(lds));
+            __syncthreads();
+        }
     }
 }
 
