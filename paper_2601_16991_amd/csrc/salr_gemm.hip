@@ -643,7 +643,7 @@ bool launch_frag_gemm(const uint16_t* x, int64_t M, int64_t K, int64_t N, const 
     const dim3 grid(gemm_grid(m_tiles * n_tiles * p.ksplit));
     // (mt, nt: two of the stage's workgroups fit a CU up to 128 x 256; four rank tiles a pass have the registers up to 128 x 128)
     const bool four = Rpad % 64 == 0 && p.mt * p.nt <= 128 * 128;
-    if (beside != nullptr && gradients_beside(M, K, N, p.mt, *beside)) {
+    if (beside != nullptr && gradients_beside(M, K, N, p, *beside)) {
         RowProducts products = *beside;
         if (products.ksplit > kBesideSlices) products.ksplit = kBesideSlices;
         const int blocks = (row_product_blocks(products.C[0]) + row_product_blocks(products.C[1])) * products.ksplit;

@@ -754,15 +754,24 @@ struct RowProducts {
     uint64_t* words;
     uint64_t tag;
 };
+constexpr int row_product_blocks(int64_t C) { return (int)((C + 63) / 64); }   // of columns
 // Slices of the rows at most where the gradients are beside the stage: whoever sums them reads them all.  (With the 32 of a launch of their
 // own 2272 x 1216 x 640 at rank 32 went 33 -> 41 us; with eight 29.)
 constexpr int kBesideSlices = 8;
-// Whether they are: on tiles of the stage (of stage_rows rows) of which two fit a CU, where the stage is long enough to hide them, by what
-// they read at 3 TB/s and what the stage multiplies at 1100 TFLOP/s, and up to 96 ranks, from where on their workgroups' passes are several.  Of 200 drawn steps (128 to 4096 tokens, ranks 8 to 96) one is 1 %
-// slower so, the geometric mean 1.13 faster; at rank 128 0.86 (448 x 5248 x 640) to 1.10 (608 x 2688 x 13440).
-inline bool gradients_beside(int64_t M, int64_t K, int64_t N, int stage_rows, const RowProducts& p) {
+// Whether they are: on tiles of the stage g of which two fit a CU, where the stage is long enough to hide them, by what they read at 3 TB/s and what
+// the stage multiplies at 1100 TFLOP/s, and up to 96 ranks.  Above 64 their workgroups go through their rows three times; where they then take
+// longer than the stage and it fills half of the chip's places or more, but not all at once, those that find no place with it start behind it, and two
+// launches are as fast or faster: 768 x 3072 x 768 at rank 96 45.4 us beside, 40.8 so, 768 x 2048 x 2048 54.0 and 48.9 (against 1024 x 2048 x 2048,
+// where all find a place at once, 43.5 and 58.9).  Of 230 steps (128 to 3000 tokens, ranks 24 to 96) ten are 1 to 2 % slower beside the stage than
+// in two launches, the geometric mean 1.12 faster; at rank 128 0.86 (448 x 5248 x 640) to 1.10 (608 x 2688 x 13440).
+inline bool gradients_beside(int64_t M, int64_t K, int64_t N, const GemmPlan& g, const RowProducts& p) {
     const double gradients = (double)M * (double)(p.C[0] + p.C[1]) * 2.0 * (p.Rpad / 32) / 3e6, stage = 2.0 * (double)M * (double)N * (double)K / 1.1e9;
-    return stage_rows <= 128 && p.Rpad <= 96 && (gradients < 20.0 || gradients < 0.85 * stage);
+    if (g.mt > 128 || p.Rpad > 96 || (gradients >= 20.0 && gradients >= 0.85 * stage)) return false;
+    if (p.Rpad <= 64 || gradients < stage) return true;
+    const int64_t places = 256 * (g.mt * g.nt <= 64 * 64 ? 4 : g.mt * g.nt <= 128 * 128 ? 3 : 2);
+    const int64_t of_stage = (M + g.mt - 1) / g.mt * ((N + g.nt - 1) / g.nt) * g.ksplit;
+    const int64_t theirs = (row_product_blocks(p.C[0]) + row_product_blocks(p.C[1])) * (int64_t)(p.ksplit < kBesideSlices ? p.ksplit : kBesideSlices);
+    return 2 * of_stage < places || of_stage > places || of_stage + theirs <= places;
 }
 inline int tn_ksplit(int64_t C0, int64_t M, int64_t C1 = 0) {
     const int64_t blocks = (C0 + 63) / 64 + (C1 + 63) / 64, steps = M / 32;

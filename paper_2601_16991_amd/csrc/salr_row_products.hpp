@@ -29,8 +29,6 @@ constexpr int kTnPitch = 64 + 8;   // bf16 elements per tile row
 constexpr int kTnBatch = 4;
 constexpr int kTnLdsBytes = 2 * kTnBatch * 32 * kTnPitch * 2;
 
-__host__ __device__ inline int row_product_blocks(int64_t C) { return (int)((C + 63) / 64); }
-
 // The sums over the slices of 32 matrix columns: read along the ranks, as they lie, and through LDS into out[0] [C0, R] and out[1]
 // [R, C1] (read in the order of the outputs, dB's sums came one 128-byte line per value: 7.4 us a gradient on 4096 columns of
 // rank 32, 16 slices).  sums: kRpCols * kRpPitch floats.

@@ -43,7 +43,7 @@ int main() {
             const GemmPlan g = gemm_plan(M, N + b.Rpad, K, b.y_room);
             RowProducts p{};
             p.C[0] = K; p.C[1] = N; p.M = M; p.R = (int)R; p.Rpad = b.Rpad; p.ksplit = b.ks_tn;
-            std::printf("mt=%d nt=%d split=%d beside=%d slices=%d\n", g.mt, g.nt, g.ksplit, (int)(b.words && gradients_beside(M, N, K, g.mt, p)),
+            std::printf("mt=%d nt=%d split=%d beside=%d slices=%d\n", g.mt, g.nt, g.ksplit, (int)(b.words && gradients_beside(M, N, K, g, p)),
                         b.ks_tn < kBesideSlices ? b.ks_tn : kBesideSlices);
         }
     }

@@ -71,6 +71,13 @@ def test_gradients_are_beside_every_tile_of_the_stage(route):
     assert seen == {(m, n, s, f) for m, n in tiles for s in (False, True) for f in (False, True)} | {(128, 256, s, False) for s in (False, True)}
 
 
+# Three passes over the rows, longer than the stage: beside it only where all workgroups find a place with it, or it leaves half of them
+@pytest.mark.parametrize("M,K,N,R,beside", [(768, 2048, 2048, 64, 1), (768, 2048, 2048, 65, 0), (1024, 2048, 2048, 96, 1), (1024, 3072, 768, 96, 0),
+                                            (512, 4096, 1024, 96, 1), (800, 2080, 6720, 96, 1), (160, 2048, 2048, 97, 0)])
+def test_gradients_that_would_start_behind_the_stage_are_launches_of_their_own(route, M, K, N, R, beside):
+    assert route("backward", M, K, N, R)["beside"] == str(beside)
+
+
 def test_calls_on_workspaces_that_start_inside_a_vector_would_hand_over(route):
     import test_gpu_workspace as t
     for kind, M, K, N, R in t.INSIDE_A_VECTOR:
