@@ -152,17 +152,21 @@ struct RowtileAdapters {
     }
     // B_cat and T of the first rank step have been asked for
     __device__ __forceinline__ void add(f32x4 (&acc)[MT]) {
-        for (int rs = 0; rs < (Rpad >> 5); ++rs) {
-            if (rs > 0) {
-                load_b(rs);
-                load_t(rs);
-            }
-            __builtin_amdgcn_sched_barrier(0);
-            const uint4 bq = ranks_below(make_uint4(e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16), e[6] | (e[7] << 16)), rs * 32 + 8 * g, R);
+        auto packed = [&]() { return make_uint4(e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16), e[6] | (e[7] << 16)); };
+        auto multiply = [&](const uint4& bq) {
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt)
                 acc[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(bq), __builtin_bit_cast(bf16x8, tq[mt]), acc[mt], 0, 0, 0);
+        };
+        const int last = (Rpad >> 5) - 1;
+        for (int rs = 0; rs < last; ++rs) {
+            __builtin_amdgcn_sched_barrier(0);
+            multiply(packed());
+            load_b(rs + 1);
+            load_t(rs + 1);
         }
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(ranks_below(packed(), last * 32 + 8 * g, R));
     }
 };
 
