@@ -214,15 +214,21 @@ __global__ __launch_bounds__(kS4Threads, MT <= 4 ? 4 : 2) void linear_2of4_kerne
             *reinterpret_cast<uint2*>(&t_lds[4 * i]) = o;
         }
         __syncthreads();
-        for (int rs = 0; rs < (Rpad >> 5); ++rs) {
-            const uint4 bq = ranks_below(rs == 0 ? bq0 : load_b_cat(rs), rs * 32 + 8 * g, R);
+        auto multiply = [&](int rs, const uint4& bq) {
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt) {
                 const int m = 16 * mt + n;
                 const uint4 tq = *reinterpret_cast<const uint4*>(&t_lds[(m < M ? m : M - 1) * Rpad + rs * 32 + 8 * g]);
                 acc[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(bq), as_bf16x8(tq), acc[mt], 0, 0, 0);
             }
+        };
+        const int last = (Rpad >> 5) - 1;   // (the step that ranks past R are in)
+        uint4 bq = bq0;
+        for (int rs = 0; rs < last; ++rs) {
+            multiply(rs, bq);
+            bq = load_b_cat(rs + 1);
         }
+        multiply(last, ranks_below(bq, last * 32 + 8 * g, R));
     }
 
     // ---- store: lane holds token 16 mt + lane % 16, outputs n0 + 4 (lane / 16) + e
