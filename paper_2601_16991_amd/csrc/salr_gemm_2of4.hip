@@ -195,14 +195,18 @@ __global__ __launch_bounds__(64 * kWN * kWM, kWN * kWM <= 4 ? 2 : 1) void gemm_2
                     const int r = rs * 32 + 8 * kb + j;
                     e[j] = (uint32_t)b_cat[(int64_t)(r < R ? r : R - 1) * N + nc];
                 }
-                bq[i] = __builtin_bit_cast(g4_u32x4, ranks_below(make_uint4(e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16), e[6] | (e[7] << 16)),
-                                                                 rs * 32 + 8 * kb, R));
+                bq[i] = g4_u32x4{e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16), e[6] | (e[7] << 16)};
             }
 #pragma unroll
             for (int j = 0; j < kMJ; ++j) {
                 const int64_t m = m0 + 16 * kMJ * wm + 16 * j + li;
                 tq[j] = *reinterpret_cast<const g4_u32x4*>(t + (m < M ? m : M - 1) * Rpad + rs * 32 + 8 * kb);
             }
+            // Uniform, and when all of the step's requests are out: with a test behind each of the bq[i] the next one's requests waited for it.  1024 x 1024 x
+            // 14336, R 90: 52.7 us, 50.2 so, 200 x 1024 x 14336, R 50 26.0 / 25.4, 1024 x 4096 x 14336, R 128 126.4 / 123.3.
+            if (rs * 32 + 32 > R)
+#pragma unroll
+                for (int i = 0; i < kNI; ++i) bq[i] = __builtin_bit_cast(g4_u32x4, ranks_below(__builtin_bit_cast(uint4, bq[i]), rs * 32 + 8 * kb, R));
 #pragma unroll
             for (int i = 0; i < kNI; ++i)
 #pragma unroll
