@@ -540,7 +540,11 @@ __global__ __launch_bounds__(NW * 64, (S == 2 && MT == 1) ? 4 : 1) void linear_s
 
     // ---- adapter k-step of this wave (Sec. 3.2): A operand = T rows from LDS, B operand = bq
     if (has_rank_step) {
-        if constexpr (!kOwnT) bq = ranks_below(bq, wave * 32 + 8 * g, R);
+        if constexpr (!kOwnT) {
+            int late_tid = tid;   // (rank wave * 32 + 8 g from a register that is there anyway: kept through the stream it spilled six others)
+            asm volatile("" : "+v"(late_tid));
+            bq = ranks_below(bq, 8 * (late_tid >> 4), R);
+        }
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
             const int m = 16 * mt + n;
