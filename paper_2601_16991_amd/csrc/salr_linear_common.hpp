@@ -20,6 +20,8 @@ __device__ __forceinline__ bf16x8 as_bf16x8(const uint4& q) { return __builtin_b
 // Eight ranks of B_cat from rank r0 on, as an MFMA operand, without those that fill the padded ones: they are read from the last rank and meet
 // zeros of T, but an infinite entry would make NaN of that.  At the operand's use and only where R is no multiple of 32, which is the same for
 // the whole launch: where the loads are packed it made the small-batch kernels wait for them (4096 x 4096, 16 tokens, 4 to 13 % of a call).
+// Behind a loop over rank steps, not in it: the next step's requests would wait for the test.  So it costs ranks such as 16 or 61 up to 0.1 us a call
+// (16 x 4096 x 4096, R 16: 12.75 / 12.83; 12 x 8448 x 2048, R 61: 17.3 / 17.4) and multiples of 32 nothing.
 __device__ __forceinline__ uint4 ranks_below(uint4 b, int r0, int R) {
     if (R % 32 != 0) {
         asm volatile("" : "+v"(r0));   // (here: what follows is not worked out ahead and kept through a stream)
