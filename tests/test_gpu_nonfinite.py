@@ -73,10 +73,10 @@ def test_linear(M, K, N, R, least):
 
 # T formed by every workgroup, by the first of them beside their own work, by workgroups of their own, in a launch in front (rank 12);
 # row tiles with a split, in one launch of one, two and four parts, without adapters in parts; large batches and, under 2:4, both of their
-# kernels.  On the told workspace long rows and 17 to 64 tokens have kernels of their own.  Ranks that do not fill the padded ones.
+# kernels (row tiles of two rank steps last).  On the told workspace long rows and 17 to 64 tokens have kernels of their own.  Ranks that do not fill the padded ones.
 CALLS = [(5, 512, 300, 5), (16, 1152, 4096, 24), (3, 2048, 500, 40), (16, 2048, 500, 12), (4, 12416, 160, 5), (20, 2048, 600, 7), (40, 1120, 2100, 33),
          (100, 1120, 300, 5), (16, 4096, 6000, 24), (24, 1120, 8384, 8), (128, 576, 16640, 40), (16, 1024, 8320, 0), (200, 128, 300, 20),
-         (1024, 128, 3072, 40), (1536, 128, 2048, 40)]
+         (1024, 128, 3072, 40), (1536, 128, 2048, 40), (72, 1152, 300, 40)]
 
 
 def _places(kind, K, R):
